@@ -364,7 +364,14 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int h, const 
         } else if (t < T && d0 < dh) {
             if (a.splits == 1) {
                 const float inv = 1.f / Lsum;
-                if (DT && a.ob_hi) {
+                if (DT && a.ob_t) {
+                    uint32_t h01, l01, h23, l23;
+                    split_bf16x2(acc[0] * inv, acc[1] * inv, h01, l01);
+                    split_bf16x2(acc[2] * inv, acc[3] * inv, h23, l23);
+                    char* p = a.ob_t + plane_offset(I >> 5, a.ob_row0 + t, h * dh + d0);
+                    st_u64(p, h01, h23);
+                    st_u64(p + kTileBytes, l01, l23);
+                } else if (DT && a.ob_hi) {
                     uint32_t h01, l01, h23, l23;
                     split_bf16x2(acc[0] * inv, acc[1] * inv, h01, l01);
                     split_bf16x2(acc[2] * inv, acc[3] * inv, h23, l23);
@@ -402,6 +409,7 @@ __global__ __launch_bounds__(512) void attn_rows_kernel(BILD_ATTN_HOT_PARAMS, co
     b.T = min(kMaxRows, a.T - r0);
     b.q = a.q + (size_t)r0 * a.i_dim;
     b.out = a.out + (size_t)r0 * a.i_dim;
+    b.ob_row0 = r0;
     b.base_add = a.base_add + r0;
     attn_body<DT, DH32, REL>(b, (int)blockIdx.x, 0, smem, [] {});
 }

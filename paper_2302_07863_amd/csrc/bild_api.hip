@@ -57,12 +57,15 @@ int upload_vec(bild_model* m, const float* src, int n, const float** out) {
     return BILD_OK;
 }
 
-int upload_tiled(bild_model* m, std::vector<char>& staging, int n, int k, TMat* out) {
+// `at`: device memory for the matrix (null: allocated here)
+int upload_tiled(bild_model* m, std::vector<char>& staging, int n, int k, TMat* out, void* at = nullptr) {
     const int kt = m->cfg.dtype == BILD_DT_BF16 ? 32 : 16;
     const size_t bytes = tiled_bytes(n, k, m->cfg.dtype);
-    void* d;
-    int rc = dev_alloc(m->allocs, &d, bytes);
-    if (rc) return rc;
+    void* d = at;
+    if (!d) {
+        int rc = dev_alloc(m->allocs, &d, bytes);
+        if (rc) return rc;
+    }
     if (hipMemcpy(d, staging.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) return BILD_EHIP;
     m->device_bytes += bytes;
     out->w = d;
@@ -79,13 +82,13 @@ int upload_matrix(bild_model* m, const float* src, bool k_by_n, int n, int k, TM
     return upload_tiled(m, st, n, k, out);
 }
 
-int upload_concat(bild_model* m, std::initializer_list<const float*> srcs, int n_each, int k, TMat* out) {
+int upload_concat(bild_model* m, std::initializer_list<const float*> srcs, int n_each, int k, TMat* out, void* at = nullptr) {
     std::vector<const float*> ps(srcs);
     std::vector<int> ns(ps.size(), n_each);
     const int n = n_each * (int)ps.size();
     std::vector<char> st(tiled_bytes(n, k, m->cfg.dtype));
     tile_concat(ps.data(), ns.data(), (int)ps.size(), k, m->cfg.dtype, st.data());
-    return upload_tiled(m, st, n, k, out);
+    return upload_tiled(m, st, n, k, out, at);
 }
 
 int upload_ffn_in(bild_model* m, const float* w_in, const float* w_up, TMat* out) {
@@ -162,6 +165,16 @@ extern "C" int bild_model_create(const bild_model_config* cfg, const float* cons
         UP(upload_matrix(m, t[i++], true, d, F, &L.wout));
     }
     m->dec.resize(cfg->n_dec_layers);
+    // the cross K/V projections of all layers in one block: they read the same input, so one launch can run all of them
+    char* cwkv_at = nullptr;
+    if (cfg->cross_attn) {
+        UP(dev_alloc(m->allocs, (void**)&cwkv_at, tiled_bytes(2 * I, d, cfg->dtype) * cfg->n_dec_layers));
+        m->cwkv_all.w = cwkv_at;
+        m->cwkv_all.n = 2 * I * cfg->n_dec_layers;
+        m->cwkv_all.k = d;
+        m->cwkv_all.tn = m->cwkv_all.n / 16;
+        m->cwkv_all.tk = d / (cfg->dtype == BILD_DT_BF16 ? 32 : 16);
+    }
     for (auto& L : m->dec) {
         UP(upload_vec(m, t[i], d, &L.ln1));
         UP(upload_concat(m, {t[i + 1], t[i + 2], t[i + 3]}, I, d, &L.wqkv));
@@ -170,7 +183,8 @@ extern "C" int bild_model_create(const bild_model_config* cfg, const float* cons
         if (cfg->cross_attn) {
             UP(upload_vec(m, t[i], d, &L.lnc));
             UP(upload_matrix(m, t[i + 1], true, I, d, &L.cwq));
-            UP(upload_concat(m, {t[i + 2], t[i + 3]}, I, d, &L.cwkv));
+            UP(upload_concat(m, {t[i + 2], t[i + 3]}, I, d, &L.cwkv, cwkv_at));
+            cwkv_at += tiled_bytes(2 * I, d, cfg->dtype);
             UP(upload_matrix(m, t[i + 4], true, d, I, &L.cwo));
             i += 5;
         }
@@ -228,6 +242,7 @@ extern "C" int bild_pair_create_early_exit(bild_model* l, int k, float small_log
     v->dec_final = l->dec_final;
     v->dec_rel = l->dec_rel;
     v->dec.assign(l->dec.begin(), l->dec.begin() + k);
+    v->cwkv_all = l->cwkv_all;  // (a view's cross K/V are the large model's: never projected for the view)
     p->m[0] = v;
     p->m[1] = l;
     p->decoder_only = !l->cfg.cross_attn;
@@ -275,15 +290,6 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         delete s;
         return BILD_EHIP;
     }
-    int rc = BILD_OK;
-#define AL(ptr, bytes)                                            \
-    do {                                                          \
-        rc = dev_alloc(s->allocs, (void**)&(ptr), (bytes));       \
-        if (rc) {                                                 \
-            bild_state_destroy(s);                                \
-            return rc;                                            \
-        }                                                         \
-    } while (0)
     if (hip_stream) {
         s->stream = (hipStream_t)hip_stream;
     } else {
@@ -293,9 +299,14 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         }
         s->own_stream = true;
     }
-    AL(s->ctl, sizeof(Ctl));
-    AL(s->y, sizeof(int) * (size_t)(max_len + 1));
-    AL(s->src, sizeof(int) * (size_t)max_src);
+    // All device memory of the state is one allocation (dozens of separate ones cost a request about a millisecond); what has
+    // to start zeroed lies together at its front.
+    struct Want { void** p; size_t bytes; bool zero; };
+    std::vector<Want> wants;
+    auto want = [&](auto& ptr, size_t bytes, bool zero = false) { wants.push_back({(void**)&ptr, (bytes + 255) / 256 * 256, zero}); };
+    want(s->ctl, sizeof(Ctl), true);
+    want(s->y, sizeof(int) * (size_t)(max_len + 1));
+    want(s->src, sizeof(int) * (size_t)max_src);
     void* h = nullptr;
     if (hipHostMalloc(&h, sizeof(Ctl) + 64, hipHostMallocMapped) != hipSuccess) {
         bild_state_destroy(s);
@@ -321,82 +332,94 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* kd = std::getenv("BILD_KSPLIT_MAX_D")) s->ksplit_max_d = std::atoi(kd);
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
+    const int positions = std::max(s->cap_len, s->cap_src);
     for (int w = 0; w < 2; ++w) {
         ModelState& M = s->ms[w];
         const bild_model* m = p->m[w];
         M.m = m;
         const size_t I = m->inner(), d = m->cfg.d_model, F = m->cfg.d_ff, L = m->cfg.n_dec_layers;
         const size_t esz = m->esz();
+        const bool bf16 = m->cfg.dtype == BILD_DT_BF16, has_enc = m->cfg.n_enc_layers > 0;
         // every K/V buffer starts zeroed: rows past the valid length must hold finite values
-#define ALZ(ptr, bytes)                                                              \
-    do {                                                                             \
-        AL(ptr, bytes);                                                              \
-        if (hipMemsetAsync((ptr), 0, (bytes), s->stream) != hipSuccess) {            \
-            bild_state_destroy(s);                                                   \
-            return BILD_EHIP;                                                        \
-        }                                                                            \
-    } while (0)
-        if (w == 0 && p->trunk_layers > 0) {
-            // early-exit pair: the trunk's layers are the large model's first layers, one cache serves both
-            // (filled in below, once the large model's buffers exist)
-        } else {
-            ALZ(M.kcache, L * (size_t)s->cap_len * I * esz);
-            ALZ(M.vcache, L * (size_t)s->cap_len * I * esz);
+        if (!(w == 0 && p->trunk_layers > 0)) {  // (an early-exit pair's trunk is the large model's first layers: one cache serves both)
+            want(M.kcache, L * (size_t)s->cap_len * I * esz, true);
+            want(M.vcache, L * (size_t)s->cap_len * I * esz, true);
             if (m->cfg.cross_attn) {
-                ALZ(M.ck, L * (size_t)s->cap_src * I * esz);
-                ALZ(M.cv, L * (size_t)s->cap_src * I * esz);
+                want(M.ck, L * (size_t)s->cap_src * I * esz, true);
+                want(M.cv, L * (size_t)s->cap_src * I * esz, true);
             }
         }
         // a decoder-only model prefills its whole prompt in one pass of many row blocks
         M.rows_cap = p->decoder_only ? std::max(kMaxRows, max_src) : kMaxRows;
+        const size_t rows16 = (size_t)(M.rows_cap + 15) / 16 * 16, src16 = (size_t)(max_src + 15) / 16 * 16;  // (tile planes hold whole row tiles)
         // the two residual-stream buffers in one block: a reader of partial results gets the other buffer as a 32-bit
         // offset from the one it reads (GemmArgs::x_out)
-        AL(M.x, sizeof(float) * ((size_t)M.rows_cap + kMaxRows) * d);
-        M.x2 = M.x + (size_t)M.rows_cap * d;
-        AL(M.q, sizeof(float) * M.rows_cap * I);
-        AL(M.a, sizeof(float) * M.rows_cap * I);
-        AL(M.h, sizeof(float) * M.rows_cap * F);
-        AL(M.px, sizeof(float) * kPartSlices * kMaxRows * d);
-        if (d <= 1024) ALZ(M.pxh, sizeof(float) * kMaxHeadParts * kMaxRows * d);  // slots of heads a model does not have stay zero
-        if (m->cfg.pos == BILD_POS_SINUSOIDAL) {
-            AL(M.pe, sizeof(float) * (size_t)s->cap_len * d);
-            if (launch_pe_table(M.pe, s->cap_len, (int)d, s->stream) != hipSuccess) {
-                bild_state_destroy(s);
-                return BILD_EHIP;
-            }
+        want(M.x, sizeof(float) * ((size_t)M.rows_cap + kMaxRows) * d);
+        want(M.q, sizeof(float) * M.rows_cap * I);
+        want(M.a, sizeof(float) * rows16 * I);
+        want(M.h, sizeof(float) * rows16 * F);
+        want(M.px, sizeof(float) * kPartSlices * kMaxRows * d);
+        if (d <= 1024) want(M.pxh, sizeof(float) * kMaxHeadParts * kMaxRows * d, true);  // slots of heads a model does not have stay zero
+        if (m->cfg.pos == BILD_POS_SINUSOIDAL) want(M.pe, sizeof(float) * (size_t)positions * d);
+        if (m->cfg.pos == BILD_POS_ROPE) want(M.rope, sizeof(double2) * (size_t)positions * (m->cfg.d_head / 2));
+        if (bf16 && (has_enc || M.rows_cap > kMaxRows || (w == 0 && p->small_borrows_encoder))) {
+            M.rows_t = p->decoder_only ? M.rows_cap : max_src;
+            want(M.xt, plane_bytes(M.rows_t, d));
+            want(M.ssq_t, sizeof(float) * (size_t)M.rows_t * (d / 16));  // at most one part per feature tile
         }
-        if (m->cfg.dtype == BILD_DT_BF16) {
-            AL(M.xb, sizeof(uint16_t) * 2 * kMaxRows * d);
-            AL(M.ab, sizeof(uint16_t) * 2 * kMaxRows * I);
-            AL(M.hb, sizeof(uint16_t) * 2 * kMaxRows * F);
-            AL(M.ssq, sizeof(float) * (kMaxSsqParts + 8) * kMaxRows);
+        if (bf16) {
+            want(M.xb, sizeof(uint16_t) * 2 * kMaxRows * d);
+            want(M.ab, sizeof(uint16_t) * 2 * kMaxRows * I);
+            want(M.hb, sizeof(uint16_t) * 2 * kMaxRows * F);
+            want(M.ssq, sizeof(float) * (kMaxSsqParts + 8) * kMaxRows);
         }
-        M.nparts_cap = (m->head.tn + 0) / 1 + 1;  // at most one partial per feature tile
-        AL(M.part, sizeof(StatPart) * (size_t)M.nparts_cap * kMaxRows);
-        AL(M.zt, sizeof(float) * kMaxRows);
+        M.nparts_cap = m->head.tn + 1;  // at most one partial per feature tile
+        want(M.part, sizeof(StatPart) * (size_t)M.nparts_cap * kMaxRows);
+        want(M.zt, sizeof(float) * kMaxRows);
         M.max_splits = std::max(8, std::min(64, (std::max(max_len, max_src) + 511) / 512));
-        AL(M.att_o, sizeof(float) * (size_t)M.max_splits * kMaxRows * I);
-        AL(M.att_ml, sizeof(float) * (size_t)M.max_splits * kMaxRows * m->cfg.n_heads * 2);
-        if (m->cfg.n_enc_layers > 0) {
-            AL(M.enc_x, sizeof(float) * (size_t)max_src * d);
-            AL(M.enc_q, sizeof(float) * (size_t)max_src * I);
-            AL(M.enc_a, sizeof(float) * (size_t)max_src * I);
-            AL(M.enc_h, sizeof(float) * (size_t)max_src * F);
-            ALZ(M.enc_k, (size_t)s->cap_src * I * esz);
-            ALZ(M.enc_v, (size_t)s->cap_src * I * esz);
+        want(M.att_o, sizeof(float) * (size_t)M.max_splits * kMaxRows * I);
+        want(M.att_ml, sizeof(float) * (size_t)M.max_splits * kMaxRows * m->cfg.n_heads * 2);
+        if (has_enc) {
+            want(M.enc_x, sizeof(float) * (size_t)max_src * d);
+            want(M.enc_q, sizeof(float) * (size_t)max_src * I);
+            want(M.enc_a, sizeof(float) * src16 * I);
+            want(M.enc_h, sizeof(float) * src16 * F);
+            want(M.enc_k, (size_t)s->cap_src * I * esz, true);
+            want(M.enc_v, (size_t)s->cap_src * I * esz, true);
         }
+    }
+    if (p->trunk_layers > 0) want(s->trunk_x, sizeof(float) * (size_t)s->cap_len * p->m[1]->cfg.d_model);
+    size_t zeroed = 0, total = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        for (Want& q : wants)
+            if (q.zero == (pass == 0)) total += q.bytes;
+        if (pass == 0) zeroed = total;
+    }
+    char* block = nullptr;
+    if (int rc = dev_alloc(s->allocs, (void**)&block, total)) {
+        bild_state_destroy(s);
+        return rc;
+    }
+    char* at[2] = {block + zeroed, block};  // by zero
+    for (Want& q : wants) {
+        *q.p = at[q.zero];
+        at[q.zero] += q.bytes;
+    }
+    hipError_t e = hipMemsetAsync(block, 0, zeroed, s->stream);
+    for (int w = 0; w < 2 && e == hipSuccess; ++w) {
+        ModelState& M = s->ms[w];
+        const bild_model_config& c = p->m[w]->cfg;
+        M.x2 = M.x + (size_t)M.rows_cap * c.d_model;
+        if (M.pe) e = launch_pe_table(M.pe, positions, c.d_model, s->stream);
+        if (M.rope && e == hipSuccess) e = launch_rope_table(M.rope, positions, c.d_head, c.rope_base, s->stream);
     }
     if (p->trunk_layers > 0) {
         s->ms[0].kcache = s->ms[1].kcache;
         s->ms[0].vcache = s->ms[1].vcache;
         s->ms[0].ck = s->ms[1].ck;
         s->ms[0].cv = s->ms[1].cv;
-        AL(s->trunk_x, sizeof(float) * (size_t)s->cap_len * p->m[1]->cfg.d_model);
     }
-#undef ALZ
-#undef AL
-    if (hipMemsetAsync(s->ctl, 0, sizeof(Ctl), s->stream) != hipSuccess ||
-        hipStreamSynchronize(s->stream) != hipSuccess) {
+    if (e != hipSuccess || hipStreamSynchronize(s->stream) != hipSuccess) {
         bild_state_destroy(s);
         return BILD_EHIP;
     }
@@ -589,8 +612,175 @@ int emit_attention(bild_state* s, const ModelState& M, AttnArgs& a, int nkeys, i
     return BILD_OK;
 }
 
+// ---- bf16 passes over many rows (gemm_tile.hip): encoder, cross K/V, prompt prefill ----
+struct TilePass {  // where one such pass works
+    bild_state* s;
+    const bild_model* m;
+    int T;
+    float *x, *q;
+    char *xt, *at, *ht;
+    float* ssq;
+    int parts;  // partial sums of squares beside xt
+    const double2* rope;
+};
+
+TileGemmArgs tile_base(const TilePass& p, const TMat& W, const char* in) {
+    TileGemmArgs g;
+    std::memset((void*)&g, 0, sizeof(g));
+    g.W = W;
+    g.xp = in;
+    g.M = p.T;
+    g.ssq = p.ssq;
+    g.ssq_parts = p.parts;
+    g.ssq_ld = p.T;
+    g.eps = p.m->cfg.norm_eps;
+    g.act = p.m->cfg.act;
+    g.d_head = p.m->cfg.d_head;
+    g.i_dim = p.m->inner();
+    return g;
+}
+
+int run_tile(const TilePass& p, const TileGemmArgs& g) {
+    p.s->gemm_count += 1;
+    p.s->stage_count += 1;
+    p.s->gemm_bytes += (int64_t)g.W.n * g.W.k * p.m->esz();
+    HIPC(launch_gemm_tile(g, p.s->stream));
+    return BILD_OK;
+}
+
+// Embedding: fp32 rows, their planes times `gain`, sums of squares.
+int tile_embed(TilePass& p, const int* tokens, const int* base_ptr, const float* pe, const float* gain) {
+    const bild_model_config& c = p.m->cfg;
+    EmbedArgs e;
+    std::memset((void*)&e, 0, sizeof(e));
+    e.E = p.m->emb;
+    e.tokens = tokens;
+    e.base_ptr = base_ptr;
+    e.T = p.T;
+    e.d = c.d_model;
+    e.vocab = c.vocab;
+    e.tie_shift = c.tie_shift;
+    e.sinusoidal = c.pos == BILD_POS_SINUSOIDAL;
+    e.embed_scale = c.embed_scale;
+    e.x = p.x;
+    e.pe = pe;
+    e.nx_gain = gain;
+    e.nx_ssq = p.ssq;
+    p.parts = 1;
+    p.s->stage_count += 1;
+    HIPC(launch_embed_tiles(e, p.xt, p.s->stream));
+    return BILD_OK;
+}
+
+int tile_qkv(const TilePass& p, const TMat& W, void* k, void* v, int vcap, const int* pos_ptr) {
+    TileGemmArgs g = tile_base(p, W, p.xt);
+    g.epi = EPI_QKV;
+    g.layer_n = W.n;
+    g.q_dim = g.i_dim;
+    g.q_out = p.q;
+    g.k_cache = k;
+    g.v_cache = v;
+    g.vcap = vcap;
+    g.pos_ptr = pos_ptr;
+    g.rope = p.rope;
+    return run_tile(p, g);
+}
+
+// x += in W^T, and the planes of the new x times the gain of the norm that reads it next
+int tile_resid(TilePass& p, const TMat& W, const char* in, const float* next_gain) {
+    TileGemmArgs g = tile_base(p, W, in);
+    g.epi = EPI_RESID;
+    g.x = p.x;
+    g.ldx = p.m->cfg.d_model;
+    g.np = p.xt;
+    g.np_tk = p.m->cfg.d_model / 32;
+    g.np_gain = next_gain;
+    g.np_ssq = p.ssq;
+    p.parts = tile_gemm_parts(g);
+    return run_tile(p, g);
+}
+
+int tile_ffn(TilePass& p, const LayerW& L, const float* next_gain) {
+    TileGemmArgs g = tile_base(p, L.win, p.xt);
+    g.epi = EPI_ACT;
+    g.np = p.ht;
+    g.np_tk = p.m->cfg.d_ff / 32;
+    int rc = run_tile(p, g);
+    if (rc) return rc;
+    return tile_resid(p, L.wout, p.ht, next_gain);
+}
+
+// Prompt rows y[len .. len+T) of a bf16 decoder-only model: fills the caches of all layers.  What lies behind the last
+// layer's K/V projection has no reader (the next token comes from a later pass) unless the rows are an early-exit trunk's.
+int emit_prefill(bild_state* s, int w, int T) {
+    ModelState& M = s->ms[w];
+    const bild_model* m = M.m;
+    const bild_model_config& c = m->cfg;
+    const int* len_ptr = &s->ctl->len[w];
+    const int trunk = s->pair->trunk_layers, layer0 = (trunk > 0 && w == 1) ? trunk : 0;
+    const bool keeps_hidden = trunk > 0 && w == 0;
+    TilePass p = {s, m, T, M.x, M.q, M.xt, (char*)M.a, (char*)M.h, M.ssq_t, 0, M.rope};
+    if (T > M.rows_t) return BILD_ECAP;
+    int rc;
+    if (layer0 > 0) {  // the hidden state the trunk left for these rows
+        RowCopyArgs r;
+        std::memset((void*)&r, 0, sizeof(r));
+        r.src = s->trunk_x;
+        r.src_row_ptr = len_ptr;
+        r.dst = M.x;
+        r.d = c.d_model;
+        r.T = T;
+        s->stage_count += 1;
+        HIPC(launch_row_tiles(r, m->dec[layer0].ln1, M.xt, M.ssq_t, s->stream));
+        p.parts = 1;
+    } else {
+        rc = tile_embed(p, s->y, len_ptr, M.pe, m->dec[0].ln1);
+        if (rc) return rc;
+    }
+    for (int l = layer0; l < c.n_dec_layers; ++l) {
+        const LayerW& L = m->dec[l];
+        const bool last = l + 1 == c.n_dec_layers;
+        const size_t off = (size_t)l * s->cap_len * m->inner() * m->esz();
+        rc = tile_qkv(p, L.wqkv, M.kcache + off, M.vcache + off, s->cap_len, len_ptr);
+        if (rc) return rc;
+        if (last && !keeps_hidden) break;
+        AttnArgs a;
+        std::memset((void*)&a, 0, sizeof(a));
+        a.q = M.q; a.k = M.kcache + off; a.v = M.vcache + off; a.out = M.a; a.ob_t = p.at;
+        a.T = T; a.heads = c.n_heads; a.d_head = c.d_head; a.i_dim = m->inner();
+        a.causal = 1;
+        a.len_ptr = len_ptr;
+        a.rel_bias = m->dec_rel;
+        a.rel_d = c.rel_max_dist;
+        a.vcap = s->cap_len;
+        a.scale = 1.f / std::sqrt((float)c.d_head);
+        a.splits = 1;
+        a.nw = pick_attn_waves(c.dtype, c.d_head, std::min(T, kMaxRows), s->len[w] + T, 1);
+        s->stage_count += 1;
+        HIPC(launch_attention(a, c.dtype, s->stream));
+        rc = tile_resid(p, L.wo, p.at, L.ln2);
+        if (rc) return rc;
+        rc = tile_ffn(p, L, last ? m->dec_final : m->dec[l + 1].ln1);
+        if (rc) return rc;
+    }
+    if (keeps_hidden) {  // (as in emit_layers)
+        RowCopyArgs r;
+        std::memset((void*)&r, 0, sizeof(r));
+        r.src = M.x;
+        r.dst = s->trunk_x;
+        r.dst_row_ptr = len_ptr;
+        r.d = c.d_model;
+        r.T = T;
+        s->stage_count += 1;
+        HIPC(launch_row_copy(r, s->stream));
+    }
+    return BILD_OK;
+}
+
 // Embedding and all decoder layers of model w over rows y[len .. len+T).
-int emit_layers(bild_state* s, int w, int T, int key_hint, bool head_reads_parts, int* xb_parts_out, float** x_out, bool* parts_pending) {
+// `reads_hidden`: an LM head follows (without one, nothing reads what lies behind the last layer's K/V projection, unless
+// the rows are an early-exit trunk's).
+int emit_layers(bild_state* s, int w, int T, int key_hint, bool reads_hidden, bool head_reads_parts, int* xb_parts_out, float** x_out, bool* parts_pending) {
     ModelState& M = s->ms[w];
     const bild_model* m = M.m;
     const bild_model_config& c = m->cfg;
@@ -744,6 +934,7 @@ int emit_layers(bild_state* s, int w, int T, int key_hint, bool head_reads_parts
             int rc = emit_gemm(s, m, g);
             if (rc) return rc;
             after_parts_in();
+            if (!reads_hidden && l + 1 == c.n_dec_layers && !(trunk > 0 && w == 0)) break;
         }
         {
             AttnArgs a;
@@ -890,10 +1081,14 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     int xb_parts = 0;  // > 0: the final hidden state also sits in M.xb as bf16 planes (times the final norm's gain)
     float* xfin = M.x;  // the residual stream after the last layer ...
     bool parts = false; // ... to which the partial results in M.px are still to be added (split FFN output projection)
-    {
+    if (dt == BILD_DT_BF16 && T > kMaxRows) {
+        if (lm_rows > 0) return BILD_EINVAL;
+        const int rc = emit_prefill(s, w, T);
+        if (rc) return rc;
+    } else {
         // a single-row pass whose LM head is the one-row kernel with one feature tile per wave can add them itself
         const bool head_reads_parts = T == 1 && lm_rows == 1 && s->pair->trunk_layers == 0 && m->head.tn < 8192;
-        int rc = emit_layers(s, w, T, key_hint, head_reads_parts, &xb_parts, &xfin, &parts);
+        int rc = emit_layers(s, w, T, key_hint, lm_rows > 0, head_reads_parts, &xb_parts, &xfin, &parts);
         if (rc) return rc;
     }
     FinishArgs f;
@@ -1017,9 +1212,99 @@ int catch_up(bild_state* s, int w, int target) {
 
 namespace {
 
+// Cross K/V of every decoder layer of each model that uses the output of model w's encoder: K = norm_final(enc_x) Wk,
+// V = norm_final(enc_x) Wv.  bf16 models: one launch for all layers, from the planes of `p` (of a bf16 encoder) or from planes
+// made here (a bf16 model that borrows an fp32 encoder).
+int cross_kv(bild_state* s, int w, const TilePass& p) {
+    ModelState& M = s->ms[w];
+    const bild_model* m = M.m;
+    const int S = s->n_src;
+    for (int u = 0; u < 2; ++u) {
+        const bool uses = (u == w) || (u == 0 && w == 1 && s->pair->small_borrows_encoder);
+        if (!uses || (u == 0 && s->pair->trunk_layers > 0)) continue;  // (a view shares the large model's cross K/V)
+        ModelState& U = s->ms[u];
+        const bild_model* mu = U.m;
+        const int Iu = mu->inner();
+        const size_t layer = (size_t)s->cap_src * Iu;
+        if (mu->cfg.dtype == BILD_DT_BF16) {
+            TilePass q = p;
+            if (!q.xt) {
+                q.xt = U.xt;
+                q.ssq = U.ssq_t;
+                q.parts = 1;
+                RowCopyArgs r;
+                std::memset((void*)&r, 0, sizeof(r));
+                r.src = r.dst = M.enc_x;
+                r.d = m->cfg.d_model;
+                r.T = S;
+                HIPC(launch_row_tiles(r, m->enc_final, q.xt, q.ssq, s->stream));
+            }
+            TileGemmArgs g = tile_base(q, mu->cwkv_all, q.xt);
+            g.epi = EPI_QKV;
+            g.i_dim = Iu;
+            g.layer_n = 2 * Iu;
+            g.kv_layer = layer;
+            g.k_cache = U.ck;
+            g.v_cache = U.cv;
+            g.vcap = s->cap_src;
+            int rc = run_tile(q, g);
+            if (rc) return rc;
+            continue;
+        }
+        for (int l = 0; l < mu->cfg.n_dec_layers; ++l) {
+            GemmArgs g = gemm_base(mu, mu->dec[l].cwkv, M.enc_x, m->cfg.d_model, S, m->enc_final);
+            g.eps = m->cfg.norm_eps;
+            g.epi = EPI_QKV;
+            g.q_dim = 0;
+            g.i_dim = Iu;
+            g.k_cache = U.ck + l * layer * mu->esz();
+            g.v_cache = U.cv + l * layer * mu->esz();
+            g.vcap = s->cap_src;
+            int rc = run_gemm(s, mu, g);
+            if (rc) return rc;
+        }
+    }
+    return BILD_OK;
+}
+
+// bf16: the same on the tile kernels.
+int run_encoder_tiles(bild_state* s, int w) {
+    ModelState& M = s->ms[w];
+    const bild_model* m = M.m;
+    const bild_model_config& c = m->cfg;
+    const int S = s->n_src;
+    TilePass p = {s, m, S, M.enc_x, M.enc_q, M.xt, (char*)M.enc_a, (char*)M.enc_h, M.ssq_t, 0, M.rope};
+    int rc = tile_embed(p, s->src, nullptr, M.pe, m->enc[0].ln1);
+    if (rc) return rc;
+    for (int l = 0; l < c.n_enc_layers; ++l) {
+        const LayerW& L = m->enc[l];
+        rc = tile_qkv(p, L.wqkv, M.enc_k, M.enc_v, s->cap_src, nullptr);
+        if (rc) return rc;
+        AttnArgs a;
+        std::memset((void*)&a, 0, sizeof(a));
+        a.q = M.enc_q; a.k = M.enc_k; a.v = M.enc_v; a.out = M.enc_a; a.ob_t = p.at;
+        a.T = S; a.heads = c.n_heads; a.d_head = c.d_head; a.i_dim = m->inner();
+        a.nkeys_fixed = S;
+        a.rel_bias = m->enc_rel;
+        a.rel_d = c.rel_max_dist;
+        a.len_ptr = &s->ctl->n_src;  // not used with a fixed count, but the kernel reads it
+        a.vcap = s->cap_src;
+        a.splits = 1;
+        a.nw = pick_attn_waves(c.dtype, c.d_head, std::min(S, kMaxRows), S, 1);
+        a.scale = 1.f / std::sqrt((float)c.d_head);
+        HIPC(launch_attention(a, c.dtype, s->stream));
+        rc = tile_resid(p, L.wo, p.at, L.ln2);
+        if (rc) return rc;
+        rc = tile_ffn(p, L, l + 1 < c.n_enc_layers ? m->enc[l + 1].ln1 : m->enc_final);
+        if (rc) return rc;
+    }
+    return cross_kv(s, w, p);
+}
+
 // Encoder of model w over the source in s->src, then the cross K/V of every decoder
 // layer of each model that uses this encoder's output.
 int run_encoder(bild_state* s, int w) {
+    if (s->ms[w].m->cfg.dtype == BILD_DT_BF16) return run_encoder_tiles(s, w);
     ModelState& M = s->ms[w];
     const bild_model* m = M.m;
     const bild_model_config& c = m->cfg;
@@ -1089,30 +1374,8 @@ int run_encoder(bild_state* s, int w) {
             if (rc) return rc;
         }
     }
-    // cross K/V: K = norm_final(enc_x) Wk, V = ... for this model and, if it borrows, the small one
-    for (int u = 0; u < 2; ++u) {
-        const bool uses = (u == w) || (u == 0 && w == 1 && s->pair->small_borrows_encoder);
-        if (!uses) continue;
-        if (u == 0 && s->pair->trunk_layers > 0) continue;  // a view of the large model: the same cross K/V memory
-        ModelState& U = s->ms[u];
-        const bild_model* mu = U.m;
-        const int Iu = mu->inner();
-        const size_t esz = mu->esz();
-        for (int l = 0; l < mu->cfg.n_dec_layers; ++l) {
-            GemmArgs g = gemm_base(mu, mu->dec[l].cwkv, M.enc_x, d, S, m->enc_final);
-            g.eps = m->cfg.norm_eps;
-            g.epi = EPI_QKV;
-            g.q_dim = 0;
-            g.i_dim = Iu;
-            g.k_cache = U.ck + (size_t)l * s->cap_src * Iu * esz;
-            g.v_cache = U.cv + (size_t)l * s->cap_src * Iu * esz;
-            g.vcap = s->cap_src;
-            g.rope = 0;
-            int rc = run_gemm(s, mu, g);
-            if (rc) return rc;
-        }
-    }
-    return BILD_OK;
+    const TilePass none = {s, m, S, M.enc_x, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr};
+    return cross_kv(s, w, none);
 }
 
 }  // namespace

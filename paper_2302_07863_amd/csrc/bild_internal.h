@@ -183,6 +183,8 @@ struct AttnArgs {
     // what the output projection stages) instead of `out`; not used while the partials are left to the consumer
     uint16_t* ob_hi;
     uint16_t* ob_lo;
+    char* ob_t;                 // non-null (bf16 models, more than kMaxRows rows): the finished output as tile planes [T][I]
+    int ob_row0;                // (set by the kernel) first row of this row block
     // attention fused with the output projection (launch_attention_proj): W_o, the partial results of the residual
     // update, one per head ([heads][proj_stride], laid out [T][d_model]), and the number of column groups
     TMat wo;
@@ -281,6 +283,47 @@ hipError_t launch_gemm_dense(const GemmArgs& a, int dtype, hipStream_t st);
 // bf16 passes whose activations travel as planes (gemm_pre.hip); launch_gemm forwards to it
 hipError_t launch_gemm_pre(const GemmArgs& a, hipStream_t st);
 hipError_t gemm_pre_init();
+// GEMM of bf16 models over more than kMaxRows rows (gemm_tile.hip).  Activations travel between these kernels as tile
+// planes: [row / 16][input / 32][high part, low part][1 KiB in matrix-core B-operand order].
+__host__ __device__ inline size_t plane_offset(int tk, int row, int k) {  // of the high part; the low part is kTileBytes behind
+    return ((size_t)(row >> 4) * tk + (k >> 5)) * (2 * kTileBytes) + ((row & 15) + 16 * ((k & 31) >> 3)) * 16 + (k & 7) * 2;
+}
+inline size_t plane_bytes(size_t rows, size_t k) { return (rows + 15) / 16 * (k / 32) * (2 * kTileBytes); }
+struct TileGemmArgs {
+    TMat W;
+    const char* xp;         // input planes (times the norm's gain where there is one), W.tk input tiles wide
+    int M;                  // rows
+    const float* ssq;       // normed input: [ssq_parts][ssq_ld] partial sums of squares per row
+    int ssq_parts, ssq_ld;
+    float eps;
+    int epi;                // EPI_RESID, EPI_ACT or EPI_QKV
+    int act;
+    float* x;               // EPI_RESID: x[t][n] += v
+    int ldx;
+    char* np;               // output planes, np_tk tiles wide (EPI_RESID: of x * np_gain; EPI_ACT: of the hidden state)
+    int np_tk;
+    const float* np_gain;
+    float* np_ssq;          // EPI_RESID: [tile_gemm_parts()][ssq_ld] partial sums of x^2
+    // EPI_QKV: the features are one or more layers of [q_dim queries | i_dim keys | i_dim values]
+    int layer_n;            // features per layer
+    size_t kv_layer;        // elements between the caches of consecutive layers
+    int q_dim, i_dim;
+    float* q_out;
+    void *k_cache, *v_cache;
+    int vcap;
+    const int* pos_ptr;
+    int pos_add;
+    const double2* rope;    // null: no rotation; [position][d_head / 2] (cos, sin)
+    int d_head;
+    int wk, lwk;            // (set by the launcher) input slices per workgroup and their logarithm
+    int fgs, rbs, gr;       // (set by the launcher) feature groups, row blocks, row shares of the dies
+};
+int tile_gemm_parts(const TileGemmArgs& a);
+hipError_t launch_gemm_tile(const TileGemmArgs& a, hipStream_t st);
+hipError_t launch_embed_tiles(const EmbedArgs& a, char* np, hipStream_t st);
+// row copy (see RowCopyArgs) that also leaves the rows' planes times `gain` and their sums of squares
+hipError_t launch_row_tiles(const RowCopyArgs& a, const float* gain, char* np, float* ssq, hipStream_t st);
+hipError_t launch_rope_table(double2* table, int positions, int d_head, float base, hipStream_t st);
 hipError_t launch_attention(const AttnArgs& a, int dtype, hipStream_t st);
 hipError_t launch_attention_proj(const AttnArgs& a, int dtype, hipStream_t st);
 constexpr int kMaxHeadParts = 16;   // heads whose partial results one reader adds (attention fused with its output projection)

@@ -35,6 +35,7 @@ struct bild_model {
     const float* enc_rel = nullptr;  // relative-position models: [heads][2*rel_max_dist + 1] score biases of the
     const float* dec_rel = nullptr;  // encoder's / decoder's self-attention, shared by all layers of the stack
     std::vector<LayerW> enc, dec;
+    TMat cwkv_all;                   // the cross K/V projections of all decoder layers side by side (dec[l].cwkv points into it)
     std::vector<void*> allocs;
     size_t device_bytes = 0;
     int inner() const { return cfg.n_heads * cfg.d_head; }
@@ -85,7 +86,13 @@ struct ModelState {
     float* x2 = nullptr;      // [32][d] second residual-stream buffer (see GemmArgs::x_out)
     float* px = nullptr;      // [kPartSlices][32][d] partial results of a split FFN output projection
     float* pxh = nullptr;     // [kMaxHeadParts][32][d] one partial result per head of attention fused with its output projection
-    float* pe = nullptr;      // sinusoidal models: position table [cap_len][d] for the decoder's embedding
+    float* pe = nullptr;      // sinusoidal models: position table [max(cap_len, cap_src)][d] for the embedding
+    double2* rope = nullptr;  // rotary models: cos and sin, [max(cap_len, cap_src)][d_head / 2]
+    // bf16 models, passes over many rows: the residual stream as tile planes (see TileGemmArgs) and the partial sums of squares
+    // beside it; the attention output and the FFN hidden state use the memory of enc_a, enc_h (a, h without an encoder)
+    char* xt = nullptr;
+    float* ssq_t = nullptr;
+    int rows_t = 0;           // rows these hold
 };
 
 struct bild_state {

@@ -1,22 +1,13 @@
-// Dense-tile GEMM for passes over MANY rows (more than 512): long sources and the prompt prefill of a
-// decoder-only model (the step right in front of the decoding loop: Section 3.2 conditions both models on the
-// input x; Section 4.1 measures latency end to end per example, so this step is inside the measured quantity).
+// Dense-tile GEMM of fp32 models for passes over MANY rows (more than 512): long sources and the prompt prefill of a
+// decoder-only model (bf16 models: gemm_tile.hip).
 //
 //   y[M][N] = f(x[M][K]) W^T  with the same fused prologue (RMSNorm) and epilogues (store, residual add, activation /
 //   gating, Q/K/V split with RoPE and cache append) as the skinny decode GEMM.
 //
-// Unlike the decode GEMM, this one is a real dense contraction: with hundreds of rows per weight tile the matrix
-// cores, not the weight stream, are the resource to keep busy.  A workgroup of 4 waves owns a tile of 64 rows x
-// (4 waves x RW feature tiles x 16) features and walks K in chunks of 128 inputs:
-//   - the chunk of activations is normalised, scaled by the gain, split into high and low bf16 parts (two MFMAs per
-//     weight tile keep fp32-grade accuracy, as in the decode GEMM) and written ONCE to LDS as the MFMA B operand,
-//     64 rows deep, so every weight tile a wave loads feeds 4 row tiles x 2 MFMAs;
-//   - weights arrive in HBM already in A-operand register order (bild::TMat), so a wave loads its 1 KiB tiles
-//     straight into operand registers - no LDS round trip for A.  The tiles of the next chunk are requested while
-//     the current one is multiplied;
-//   - the LDS footprint (34 KiB) and register count let two workgroups share a compute unit: one converts while
-//     the other multiplies, and the loads of both are in flight together (a compute unit's load rate is set
-//     by the bytes it has in flight).
+// A workgroup of 4 waves owns a tile of 64 rows x (4 waves x RW feature tiles x 16) features and walks K in chunks of 128
+// inputs: the chunk of activations is scaled by the gain and written once to LDS as the MFMA B operand, 64 rows deep, so
+// every weight tile a wave loads feeds 4 row tiles; weights arrive in A-operand register order (bild::TMat), so a wave
+// loads its 1 KiB tiles straight into operand registers, those of the next chunk while the current one is multiplied.
 // Row blocks of one feature group re-read its weight tiles from L2 / the memory-side cache; blockIdx.x walks the
 // feature groups fastest, so the row blocks that are resident together share them.
 #include "kernel_common.h"
@@ -39,11 +30,11 @@ __device__ __forceinline__ void half_wave_sums(float v, float& lo, float& hi) {
 }
 
 // GATED: feature tiles 2j / 2j+1 hold the gate and the linear branch of output feature block j (RW is even).
-template <int DT, int RW, int EPI, int ROPE, bool GATED>
+template <int RW, int EPI, int ROPE, bool GATED>
 __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int KT = DT ? 32 : 16, KC = dense_kc(DT), NKT = KC / KT, NTR = kDenseRows / 16;
-    constexpr int RS = dense_row_stride(DT);
+    constexpr int KT = 16, KC = dense_kc(0), NKT = KC / KT, NTR = kDenseRows / 16;
+    constexpr int RS = dense_row_stride(0);
     constexpr bool norm = EPI != EPI_RESID;  // residual-adding projections read un-normalised input (as in the decode GEMM)
     constexpr int PPR = KC / 4;              // float4 pieces per row and chunk (32)
     constexpr int RPI = 64 / PPR;            // rows a wave stages per round (2: one per half wave)
@@ -54,9 +45,8 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
     const float* x = a.x + (size_t)r0 * a.ldx;
     const int K = a.W.k;
     const int tile0 = ((int)blockIdx.x * kDenseWaves + wave) * RW;
-    char* xs_hi = smem;
-    char* xs_lo = smem + kDenseRows * RS;  // bf16 only
-    float* ssq = (float*)(smem + kDenseRows * RS * (DT ? 2 : 1));
+    char* xs = smem;
+    float* ssq = (float*)(smem + kDenseRows * RS);
     const int tok_l = lane & 15, kq = lane >> 4;
     bool valid[RW];
     const char* wbase[RW];
@@ -119,15 +109,7 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
                         ssr[u] += w.x * w.x + w.y * w.y + w.z * w.z + w.w * w.w;
                         w.x *= g.x; w.y *= g.y; w.z *= g.z; w.w *= g.w;
                     }
-                    if (DT) {
-                        uint32_t h01, l01, h23, l23;
-                        split_bf16x2(w.x, w.y, h01, l01);
-                        split_bf16x2(w.z, w.w, h23, l23);
-                        *(uint2*)(xs_hi + row * RS + k4 * 8) = make_uint2(h01, h23);
-                        *(uint2*)(xs_lo + row * RS + k4 * 8) = make_uint2(l01, l23);
-                    } else {
-                        *(float4*)(xs_hi + row * RS + k4 * 16) = w;
-                    }
+                    *(float4*)(xs + row * RS + k4 * 16) = w;
                 }
             }
         }
@@ -141,26 +123,15 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
 #pragma unroll
                 for (int j = 0; j < NTR; ++j) {
                     const int t = j * 16 + tok_l;
-                    if (DT) {
-                        const bf16x8 Bh = __builtin_bit_cast(bf16x8, *(const uint4*)(xs_hi + t * RS + (u * 32 + kq * 8) * 2));
-                        const bf16x8 Bl = __builtin_bit_cast(bf16x8, *(const uint4*)(xs_lo + t * RS + (u * 32 + kq * 8) * 2));
+                    const float4 b = *(const float4*)(xs + t * RS + (u * 16 + kq * 4) * 4);
+                    const float bb[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-                        for (int r = 0; r < RW; ++r)
-                            acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, W[r][u]), Bh, acc[r][j], 0, 0, 0);
+                    for (int r = 0; r < RW; ++r) {
+                        const float aa[4] = {__uint_as_float(W[r][u].x), __uint_as_float(W[r][u].y),
+                                             __uint_as_float(W[r][u].z), __uint_as_float(W[r][u].w)};
 #pragma unroll
-                        for (int r = 0; r < RW; ++r)
-                            acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, W[r][u]), Bl, acc[r][j], 0, 0, 0);
-                    } else {
-                        const float4 b = *(const float4*)(xs_hi + t * RS + (u * 16 + kq * 4) * 4);
-                        const float bb[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-                        for (int r = 0; r < RW; ++r) {
-                            const float aa[4] = {__uint_as_float(W[r][u].x), __uint_as_float(W[r][u].y),
-                                                 __uint_as_float(W[r][u].z), __uint_as_float(W[r][u].w)};
-#pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(aa[q], bb[q], acc[r][j], 0, 0, 0);
-                        }
+                        for (int q = 0; q < 4; ++q)
+                            acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(aa[q], bb[q], acc[r][j], 0, 0, 0);
                     }
                 }
             }
@@ -242,18 +213,12 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
                     *(float4*)(q_out + (size_t)t * a.i_dim + nn) = make_float4(v4[0], v4[1], v4[2], v4[3]);
                 } else if (seg == 1) {  // K: [position][I]
                     const size_t e = (size_t)pos * a.i_dim + nn;
-                    if (DT)
-                        *(uint2*)((uint16_t*)a.k_cache + e) = make_uint2(pack_bf16x2(v4[0], v4[1]), pack_bf16x2(v4[2], v4[3]));
-                    else
-                        *(float4*)((float*)a.k_cache + e) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+                    *(float4*)((float*)a.k_cache + e) = make_float4(v4[0], v4[1], v4[2], v4[3]);
                 } else {  // V: transposed, [I][vcap] with the position contiguous
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const size_t e = (size_t)(nn + v) * a.vcap + pos;
-                        if (DT)
-                            ((uint16_t*)a.v_cache)[e] = (uint16_t)f2bf(v4[v]);
-                        else
-                            ((float*)a.v_cache)[e] = v4[v];
+                        ((float*)a.v_cache)[e] = v4[v];
                     }
                 }
             }
@@ -269,11 +234,11 @@ size_t dense_num_feature_groups(const GemmArgs& a) {
 hipError_t launch_gemm_dense(const GemmArgs& a, int dtype, hipStream_t st) {
     static hipError_t attr = [] {
         const void* fns[] = {
-#define BILD_DENSE(DTV)                                                                                             \
-    (const void*)gemm_dense_kernel<DTV, kDenseRW, EPI_STORE, 0, false>, (const void*)gemm_dense_kernel<DTV, kDenseRW, EPI_RESID, 0, false>, \
-    (const void*)gemm_dense_kernel<DTV, kDenseRW, EPI_QKV, 0, false>, (const void*)gemm_dense_kernel<DTV, kDenseRW, EPI_QKV, 1, false>,     \
-    (const void*)gemm_dense_kernel<DTV, kDenseRW, EPI_ACT, 0, false>, (const void*)gemm_dense_kernel<DTV, kDenseRW, EPI_ACT, 0, true>
-            BILD_DENSE(0), BILD_DENSE(1)};
+#define BILD_DENSE                                                                                             \
+    (const void*)gemm_dense_kernel<kDenseRW, EPI_STORE, 0, false>, (const void*)gemm_dense_kernel<kDenseRW, EPI_RESID, 0, false>, \
+    (const void*)gemm_dense_kernel<kDenseRW, EPI_QKV, 0, false>, (const void*)gemm_dense_kernel<kDenseRW, EPI_QKV, 1, false>,     \
+    (const void*)gemm_dense_kernel<kDenseRW, EPI_ACT, 0, false>, (const void*)gemm_dense_kernel<kDenseRW, EPI_ACT, 0, true>
+            BILD_DENSE};
 #undef BILD_DENSE
         for (const void* f : fns) {
             hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
@@ -282,26 +247,26 @@ hipError_t launch_gemm_dense(const GemmArgs& a, int dtype, hipStream_t st) {
         return hipSuccess;
     }();
     if (attr != hipSuccess) return attr;
-    if (a.T < 1 || a.W.k < 1 || a.epi == EPI_LMHEAD || a.mg_splits > 1) return hipErrorInvalidValue;
+    if (dtype || a.T < 1 || a.W.k < 1 || a.epi == EPI_LMHEAD || a.mg_splits > 1) return hipErrorInvalidValue;
     if ((a.gain != nullptr) != (a.epi != EPI_RESID)) return hipErrorInvalidValue;  // the norm is fixed by the epilogue
     const bool gated = a.epi == EPI_ACT && a.act != BILD_ACT_RELU;
     const dim3 grid((unsigned)dense_num_feature_groups(a), (unsigned)((a.T + kDenseRows - 1) / kDenseRows)), block(64 * kDenseWaves);
     const size_t smem = dense_lds_bytes(dtype);
-#define BILD_DL(DTV)                                                                                                        \
+#define BILD_DL                                                                                                        \
     switch (a.epi) {                                                                                                        \
-        case EPI_STORE: hipLaunchKernelGGL((gemm_dense_kernel<DTV, kDenseRW, EPI_STORE, 0, false>), grid, block, smem, st, a); break; \
-        case EPI_RESID: hipLaunchKernelGGL((gemm_dense_kernel<DTV, kDenseRW, EPI_RESID, 0, false>), grid, block, smem, st, a); break; \
+        case EPI_STORE: hipLaunchKernelGGL((gemm_dense_kernel<kDenseRW, EPI_STORE, 0, false>), grid, block, smem, st, a); break; \
+        case EPI_RESID: hipLaunchKernelGGL((gemm_dense_kernel<kDenseRW, EPI_RESID, 0, false>), grid, block, smem, st, a); break; \
         case EPI_QKV:                                                                                                       \
-            if (a.rope) hipLaunchKernelGGL((gemm_dense_kernel<DTV, kDenseRW, EPI_QKV, 1, false>), grid, block, smem, st, a);  \
-            else hipLaunchKernelGGL((gemm_dense_kernel<DTV, kDenseRW, EPI_QKV, 0, false>), grid, block, smem, st, a);         \
+            if (a.rope) hipLaunchKernelGGL((gemm_dense_kernel<kDenseRW, EPI_QKV, 1, false>), grid, block, smem, st, a);  \
+            else hipLaunchKernelGGL((gemm_dense_kernel<kDenseRW, EPI_QKV, 0, false>), grid, block, smem, st, a);         \
             break;                                                                                                          \
         case EPI_ACT:                                                                                                       \
-            if (gated) hipLaunchKernelGGL((gemm_dense_kernel<DTV, kDenseRW, EPI_ACT, 0, true>), grid, block, smem, st, a);    \
-            else hipLaunchKernelGGL((gemm_dense_kernel<DTV, kDenseRW, EPI_ACT, 0, false>), grid, block, smem, st, a);         \
+            if (gated) hipLaunchKernelGGL((gemm_dense_kernel<kDenseRW, EPI_ACT, 0, true>), grid, block, smem, st, a);    \
+            else hipLaunchKernelGGL((gemm_dense_kernel<kDenseRW, EPI_ACT, 0, false>), grid, block, smem, st, a);         \
             break;                                                                                                          \
         default: return hipErrorInvalidValue;                                                                               \
     }
-    if (dtype) { BILD_DL(1) } else { BILD_DL(0) }
+    BILD_DL
 #undef BILD_DL
     return hipGetLastError();
 }

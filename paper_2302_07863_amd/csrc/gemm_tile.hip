@@ -1,0 +1,543 @@
+// GEMM of bf16 models for passes over MANY rows (more than 32): the encoder, the cross K/V of a source and the prompt
+// prefill of a decoder-only model - everything a request has to wait for before its first token (Section 3.2 conditions
+// both models on the input x; Section 4.1 measures latency end to end per example).
+//
+//   y[M][N] = f(x[M][K]) W^T   with the RMSNorm scale, the residual add, the activation / gating, the Q/K/V split with RoPE
+//   and the cache append fused behind the products.
+//
+// Activations arrive as "tile planes": the kernel that produced them has split every value once into a high and a low bf16
+// part (times the gain of this projection's norm) and stored both in the order of the matrix-core B operand,
+//   [row / 16][input / 32][high, low][1 KiB: lane l holds row l % 16, inputs 8 (l / 16) .. + 7],
+// so that a wavefront fetches an operand of 16 rows x 32 inputs with one contiguous 1 KiB load, exactly as it fetches
+// a weight tile, and nothing is converted, transposed or staged here.  (Converting fp32 activations in every workgroup was
+// most of what these passes cost: a 512-row pass over a 1024-wide projection repeats the conversion 16 to 64 times.)
+//
+// Bound: matrix cores for large products (two MFMAs per tile, high and low part), otherwise the 64 bytes a clock a compute
+// unit takes from L2.  A wave owns 64 rows x 16 FT features; the operands of its next step are requested while the current
+// one is multiplied.  Waves of a workgroup share nothing in the loop (no barrier, no LDS): either they own different
+// features of the same rows (the rows' operands then come from the vector cache), or, where a product has too few tiles
+// to occupy the chip, they take slices of the inputs and add their sums in LDS at the end, in a fixed order.
+#include "kernel_common.h"
+
+namespace bild {
+
+constexpr int kTileWaves = 4;
+__host__ __device__ constexpr int tile_sums(int rt) { return rt * 16 * kTileWaves > 256 ? rt * 16 * kTileWaves : 256; }
+
+__device__ __forceinline__ void put_tile_planes(char* base, int tk, int row, int n0, const float (&w)[4]) {
+    uint32_t h01, l01, h23, l23;
+    split_bf16x2(w[0], w[1], h01, l01);
+    split_bf16x2(w[2], w[3], h23, l23);
+    char* p = base + plane_offset(tk, row, n0);
+    st_u64(p, h01, h23);
+    st_u64(p + kTileBytes, l01, l23);
+}
+
+// Buffer loads: the compiler neither folds them into their use (a plain load that feeds the next turn of a loop is moved
+// there, which undoes the requests ahead) nor needs a 64-bit address per lane.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(uint32_t)min(bytes, (size_t)0xFFFFFFFFu), 0x00027000);
+}
+__device__ __forceinline__ uint4 buf_load(__amdgpu_buffer_rsrc_t r, unsigned lane_off, int off) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, off, 0));
+}
+
+// Row block and feature group of a workgroup.  Workgroups go to the eight dies in turn; the dies form a grid of a.gr row
+// shares x 8 / a.gr feature shares (launch_gemm_tile), and a die walks the row blocks of its share before the next feature
+// group, so that the weights of a group come from memory once and are then in that die's L2 while the rows pass.
+// (Row blocks outermost, a 22016 x 4096 projection over 1023 rows streamed its 180 MB once per row block: 424 us against
+// 323 with the same tiles.)
+__device__ __forceinline__ bool tile_block(const TileGemmArgs& a, int& rb, int& fg) {
+    const int die = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
+    const int gf = 8 / a.gr, rper = (a.rbs + a.gr - 1) / a.gr;
+    const int q = j / rper;
+    rb = (j - q * rper) * a.gr + die / gf;
+    fg = q * gf + die % gf;
+    return rb < a.rbs && fg < a.fgs;
+}
+
+// FT: feature tiles per wave.  GATED: feature tiles 2j / 2j+1 hold gate and linear branch of output block j.
+// SPLIT: the waves of a workgroup (also) slice the inputs, a.wk of them per feature group.
+template <int RT, int FT, int EPI, int ROPE, bool GATED, bool SPLIT, bool SHARE>
+__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const TileGemmArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    constexpr bool norm = EPI != EPI_RESID;  // residual-adding projections read un-normalised input
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int WK = SPLIT ? a.wk : 1, wkid = SPLIT ? wave & (WK - 1) : 0, wn = SPLIT ? wave >> a.lwk : wave;
+    const int WN = SPLIT ? kTileWaves >> a.lwk : kTileWaves;
+    const int tok_l = lane & 15, kq = lane >> 4;
+    int rb, fg;
+    if (!tile_block(a, rb, fg)) return;
+    const int r0 = rb * (RT * 16), tile0 = (fg * WN + wn) * FT;
+    const int tk = a.W.tk;
+    const int rt_last = (a.M - 1) >> 4;
+    const unsigned lane16 = (unsigned)lane * 16u;
+    // operands by buffer loads: base and size in scalar registers, one lane offset, a scalar offset per tile (from the
+    // first tile of this wave, so that offsets stay small however long the pass)
+    const int wt0 = min(tile0, a.W.tn - 1), xt0 = r0 >> 4;
+    const __amdgpu_buffer_rsrc_t wr = make_rsrc((const char*)a.W.w + (size_t)wt0 * tk * kTileBytes, (size_t)(a.W.tn - wt0) * tk * kTileBytes);
+    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.xp + (size_t)xt0 * tk * (2 * kTileBytes), (size_t)(rt_last + 1 - xt0) * tk * (2 * kTileBytes));
+    int woff[FT], xoff[RT];
+#pragma unroll
+    for (int f = 0; f < FT; ++f) woff[f] = (min(tile0 + f, a.W.tn - 1) - wt0) * tk * kTileBytes;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) xoff[r] = min(r, rt_last - xt0) * tk * (2 * kTileBytes);
+
+    const int per = SPLIT ? (tk + WK - 1) >> a.lwk : tk;
+    const int kb = wkid * per, ke = min(tk, kb + per);
+    f32x4 acc[FT][RT];
+#pragma unroll
+    for (int f = 0; f < FT; ++f)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) acc[f][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](const uint4 (&W)[FT], const uint4 (&X)[RT][2]) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int f = 0; f < FT; ++f)
+                    acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, W[f]), __builtin_bit_cast(bf16x8, X[r][p]),
+                                                                        acc[f][r], 0, 0, 0);
+    };
+    float* nss = (float*)smem;              // [at least 256] sums of squares: of the input rows, or (EPI_RESID) of the output rows
+    f32x4* red = (f32x4*)(nss + tile_sums(RT));
+    // Sums of squares of the rows from the producer's partial sums: 256 / rows threads share a row's parts, eight requests at
+    // a time (one after the other they were up to 64 dependent trips to memory); added up behind the products.
+    constexpr int ROWS = RT * 16, SHARES = 256 / ROWS;
+    float ssum = 0.f;
+    auto row_sums = [&]() {
+        if (!norm) return;
+        const float* sp = a.ssq + min(r0 + (tid & (ROWS - 1)), a.M - 1);
+        for (int p0 = tid / ROWS; p0 < a.ssq_parts; p0 += 8 * SHARES) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = sp[(size_t)min(p0 + u * SHARES, a.ssq_parts - 1) * a.ssq_ld];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) ssum += p0 + u * SHARES < a.ssq_parts ? v[u] : 0.f;
+        }
+        nss[tid] = ssum;  // [share][row]
+    };
+    auto row_scale = [&](int tl) {  // 1/rms of row tl of the block
+        float sum = 0.f;
+#pragma unroll
+        for (int h = 0; h < SHARES; ++h) sum += nss[h * ROWS + tl];
+        return rsqrtf(sum / (float)a.W.k + a.eps);
+    };
+    // With sliced inputs a wave finishes 1 / WK of the row tiles: what it adds to is requested ahead of the products.
+    float4 old[FT], gain[FT];
+    if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+        for (int f = 0; f < FT; ++f) {
+            const int n0 = min(tile0 + f, a.W.tn - 1) * 16 + kq * 4;
+            gain[f] = *(const float4*)(a.np_gain + n0);
+            if (SPLIT) old[f] = *(const float4*)(a.x + (size_t)min(r0 + wkid * 16 + tok_l, a.M - 1) * a.ldx + n0);
+        }
+    }
+    if constexpr (SHARE) {
+        // The rows' operands go through LDS, two steps deep: each wave fetches a quarter of the next step's.
+        constexpr int UPW = 2 * RT / kTileWaves;  // 1 KiB units a wave fetches per step
+        char* xs = (char*)red;                    // [2][RT][2][1 KiB]
+        constexpr int D = RT == 4 ? 4 : 2;        // steps requested ahead (2000 cycles of products)
+        uint4 W[D][FT], XR[D][UPW];
+        int xu[UPW];
+#pragma unroll
+        for (int u = 0; u < UPW; ++u) {
+            const int unit = wave * UPW + u;
+            xu[u] = min(unit >> 1, rt_last - xt0) * tk * (2 * kTileBytes) + (unit & 1) * kTileBytes;
+        }
+        auto request_w = [&](uint4 (&Wd)[FT], int k) {
+            const int kc = min(k, tk - 1);
+#pragma unroll
+            for (int f = 0; f < FT; ++f) Wd[f] = buf_load(wr, lane16, woff[f] + kc * kTileBytes);
+        };
+        auto request_x = [&](uint4 (&Xd)[UPW], int k) {
+            const int kc = min(k, tk - 1);
+#pragma unroll
+            for (int u = 0; u < UPW; ++u) Xd[u] = buf_load(xr, lane16, xu[u] + kc * (2 * kTileBytes));
+        };
+        auto store_x = [&](const uint4 (&Xd)[UPW], int slot) {
+#pragma unroll
+            for (int u = 0; u < UPW; ++u) *(uint4*)(xs + slot * (2 * RT * kTileBytes) + (wave * UPW + u) * kTileBytes + lane16) = Xd[u];
+        };
+        auto compute = [&](const uint4 (&Wc)[FT], int slot) {
+            const char* xb = xs + slot * (2 * RT * kTileBytes) + lane16;
+            uint4 B[2][2];
+            auto frag = [&](int r) {
+                B[r & 1][0] = *(const uint4*)(xb + r * 2 * kTileBytes);
+                B[r & 1][1] = *(const uint4*)(xb + (r * 2 + 1) * kTileBytes);
+            };
+            frag(0);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                if (r + 1 < RT) frag(r + 1);  // read ahead of the products of this row tile
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int f = 0; f < FT; ++f)
+                        acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Wc[f]), __builtin_bit_cast(bf16x8, B[r & 1][p]), acc[f][r], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // all waves past this point have written (and read) what they were to in LDS; requests to memory stay in flight
+        auto lds_barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+        // (in the order of the loop: the memory counter retires requests in order, and the waits of the loop hold for both ways into it)
+        uint4 X0[UPW];
+        request_x(X0, 0);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            __builtin_amdgcn_sched_barrier(0);
+            request_x(XR[(d + 1) % D], d + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            request_w(W[d], d);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        row_sums();
+        store_x(X0, 0);
+        lds_barrier();
+        int k = 0;
+        for (; k + D <= tk; k += D) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                store_x(XR[(j + 1) % D], (j + 1) & 1);  // x of the next step
+                request_x(XR[(j + 1) % D], k + j + 1 + D);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(W[j], j & 1);
+                __builtin_amdgcn_sched_barrier(0);
+                request_w(W[j], k + j + D);
+                lds_barrier();
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < D - 1; ++j) {  // the steps left over; their operands are on the way
+            if (k + j < tk) {
+                store_x(XR[(j + 1) % D], (j + 1) & 1);
+                compute(W[j], j & 1);
+                lds_barrier();
+            }
+        }
+    } else {
+        constexpr int D = RT * 2 + FT == 12 ? 3 : 4;  // steps requested ahead
+        uint4 W[D][FT], X[D][RT][2];
+        auto request = [&](int d, int k) {  // a step past the end reads zeros or another feature's tile, never multiplied
+            const int kc = min(k, ke - 1);
+#pragma unroll
+            for (int f = 0; f < FT; ++f) W[d][f] = buf_load(wr, lane16, woff[f] + kc * kTileBytes);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                X[d][r][0] = buf_load(xr, lane16, xoff[r] + kc * (2 * kTileBytes));
+                X[d][r][1] = buf_load(xr, lane16 + kTileBytes, xoff[r] + kc * (2 * kTileBytes));
+            }
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) request(d, kb + d);
+        row_sums();
+        int k = kb;
+        for (; k + D <= ke; k += D) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                multiply(W[j], X[j]);
+                __builtin_amdgcn_sched_barrier(0);
+                request(j, k + j + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < D - 1; ++j)
+            if (k + j < ke) multiply(W[j], X[j]);
+    }
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int f = 0; f < FT; ++f)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) red[((wave * RT + r) * FT + f) * 64 + lane] = acc[f][r];
+    }
+    if (norm || SPLIT) __syncthreads();
+
+    const int pos0 = EPI == EPI_QKV ? (a.pos_ptr ? *a.pos_ptr : 0) + a.pos_add : 0;
+    // ---- epilogue of one row tile: lane holds features tile*16 + kq*4 + v of row r*16 + tok_l ----
+    auto finish = [&](int r, f32x4 (&c)[FT]) {
+        const int tl = r * 16 + tok_l, t = r0 + tl;
+        float ss = 0.f;
+        const float sc = norm ? row_scale(tl) : 1.f;
+        const bool row_ok = t < a.M;
+        if constexpr (GATED) {
+#pragma unroll
+            for (int p = 0; p < FT / 2; ++p) {
+                if (!row_ok || tile0 + 2 * p + 1 >= a.W.tn) continue;
+                float o[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float g = c[2 * p][v] * sc, u = c[2 * p + 1][v] * sc;
+                    o[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(g) : silu_f(g)) * u;
+                }
+                put_tile_planes(a.np, a.np_tk, t, ((tile0 >> 1) + p) * 16 + kq * 4, o);
+            }
+            return;
+        }
+#pragma unroll
+        for (int f = 0; f < FT; ++f) {
+            if (!row_ok || tile0 + f >= a.W.tn) continue;
+            const int n0 = (tile0 + f) * 16 + kq * 4;
+            float v4[4] = {c[f][0] * sc, c[f][1] * sc, c[f][2] * sc, c[f][3] * sc};
+            if constexpr (EPI == EPI_RESID) {
+                float4* px = (float4*)(a.x + (size_t)t * a.ldx + n0);
+                const float4 o = SPLIT && r == wkid ? old[f] : *px;
+                const float xn[4] = {o.x + v4[0], o.y + v4[1], o.z + v4[2], o.w + v4[3]};
+                *px = make_float4(xn[0], xn[1], xn[2], xn[3]);
+                const float4 gn = gain[f];
+                const float w[4] = {xn[0] * gn.x, xn[1] * gn.y, xn[2] * gn.z, xn[3] * gn.w};
+                put_tile_planes(a.np, a.np_tk, t, n0, w);
+                ss += xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
+            } else if constexpr (EPI == EPI_ACT) {
+                const float o[4] = {fmaxf(v4[0], 0.f), fmaxf(v4[1], 0.f), fmaxf(v4[2], 0.f), fmaxf(v4[3], 0.f)};
+                put_tile_planes(a.np, a.np_tk, t, n0, o);
+            } else {  // EPI_QKV; several layers' K/V projections side by side when a.layer_n < N
+                const int layer = n0 / a.layer_n, nl = n0 - layer * a.layer_n;
+                const int pos = pos0 + t;
+                const int seg = nl < a.q_dim ? 0 : (nl < a.q_dim + a.i_dim ? 1 : 2);
+                const int nn = nl - (seg == 0 ? 0 : (seg == 1 ? a.q_dim : a.q_dim + a.i_dim));
+                if (ROPE && seg < 2) {  // pairs (2i, 2i+1) of a head; the table holds cos and sin in double precision
+                    const double2* tb = a.rope + ((size_t)pos * a.d_head + nn % a.d_head) / 2;
+#pragma unroll
+                    for (int p2 = 0; p2 < 2; ++p2) {
+                        const double2 cs = tb[p2];
+                        const float x0 = v4[2 * p2], x1 = v4[2 * p2 + 1];
+                        v4[2 * p2] = (float)((double)x0 * cs.x - (double)x1 * cs.y);
+                        v4[2 * p2 + 1] = (float)((double)x0 * cs.y + (double)x1 * cs.x);
+                    }
+                }
+                if (seg == 0) {
+                    *(float4*)(a.q_out + (size_t)t * a.i_dim + nn) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+                } else if (seg == 1) {  // K: [position][I]
+                    uint16_t* kc = (uint16_t*)a.k_cache + (size_t)layer * a.kv_layer;
+                    st_u64(kc + (size_t)pos * a.i_dim + nn, pack_bf16x2(v4[0], v4[1]), pack_bf16x2(v4[2], v4[3]));
+                } else {  // V: transposed, [I][vcap] with the position contiguous
+                    uint16_t* vc = (uint16_t*)a.v_cache + (size_t)layer * a.kv_layer;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) vc[(size_t)(nn + v) * a.vcap + pos] = (uint16_t)f2bf(v4[v]);
+                }
+            }
+        }
+        if constexpr (EPI == EPI_RESID) {
+            ss = quad_rows_sum(ss);
+            if (kq == 0) nss[wn * (RT * 16) + tl] = ss;
+        }
+    };
+    if constexpr (SPLIT) {
+        for (int r = wkid; r < RT; r += WK) {  // the row tiles are dealt to the slices
+            f32x4 c[FT];
+#pragma unroll
+            for (int f = 0; f < FT; ++f) {
+                const f32x4* src = red + (((wn << a.lwk) * RT + r) * FT + f) * 64 + lane;
+                c[f] = src[0];
+                for (int w = 1; w < WK; ++w) c[f] += src[w * RT * FT * 64];
+            }
+            finish(r, c);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            f32x4 c[FT];
+#pragma unroll
+            for (int f = 0; f < FT; ++f) c[f] = acc[f][r];
+            finish(r, c);
+        }
+    }
+    if constexpr (EPI == EPI_RESID) {
+        __syncthreads();
+        if (tid < RT * 16 && r0 + tid < a.M) {
+            float sum = 0.f;
+            for (int w = 0; w < WN; ++w) sum += nss[w * (RT * 16) + tid];
+            a.np_ssq[(size_t)fg * a.ssq_ld + r0 + tid] = sum;
+        }
+    }
+}
+
+// Embedding of many rows: the fp32 residual stream, its tile planes (times the first norm's gain) and the rows' sums of squares.
+__global__ __launch_bounds__(256) void embed_tile_kernel(const EmbedArgs a, char* np, int np_tk) {
+    __shared__ float part[4];
+    const int t = (int)blockIdx.x, tid = threadIdx.x;
+    const int base = (a.base_ptr ? *a.base_ptr : 0) + a.base_add, pos = base + t;
+    const int row = (int)(((long long)a.tokens[pos] + a.tie_shift) % a.vocab);
+    const double lg = log2(10000.0);
+    float ss = 0.f;
+    for (int k4 = tid; k4 < a.d / 4; k4 += 256) {
+        const int k = k4 * 4;
+        const char* p = (const char*)a.E.w + ((size_t)(row >> 4) * a.E.tk + (k >> 5)) * kTileBytes + ((row & 15) + 16 * ((k & 31) >> 3)) * 16 + (k & 7) * 2;
+        const uint2 raw = *(const uint2*)p;
+        const float e[4] = {bf2f(raw.x & 0xFFFFu), bf2f(raw.x >> 16), bf2f(raw.y & 0xFFFFu), bf2f(raw.y >> 16)};
+        float v[4], w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float pterm = 0.f;
+            if (a.sinusoidal) {
+                if (a.pe) {
+                    pterm = a.pe[(size_t)pos * a.d + k + j];
+                } else {
+                    const double ang = (double)pos * exp2(-(double)(2 * ((k + j) >> 1)) / (double)a.d * lg);
+                    pterm = (float)(((k + j) & 1) ? cos(ang) : sin(ang));
+                }
+            }
+            v[j] = __builtin_fmaf(e[j], a.embed_scale, pterm);
+            ss += v[j] * v[j];
+            w[j] = v[j] * a.nx_gain[k + j];
+        }
+        *(float4*)(a.x + (size_t)t * a.d + k) = make_float4(v[0], v[1], v[2], v[3]);
+        put_tile_planes(np, np_tk, t, k, w);
+    }
+    const float tot = wave_sum(ss);
+    if ((tid & 63) == 0) part[tid >> 6] = tot;
+    __syncthreads();
+    if (tid == 0) a.nx_ssq[t] = part[0] + part[1] + part[2] + part[3];
+}
+
+hipError_t launch_embed_tiles(const EmbedArgs& a, char* np, hipStream_t st) {
+    if (!a.nx_gain || !a.nx_ssq || !np || a.d % 32 || a.T < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(embed_tile_kernel, dim3(a.T), dim3(256), 0, st, a, np, a.d / 32);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void row_tile_kernel(const RowCopyArgs a, const float* gain, char* np, int np_tk, float* ssq) {
+    __shared__ float part[4];
+    const int t = (int)blockIdx.x, tid = threadIdx.x;
+    const float4* src = (const float4*)(a.src + (size_t)((a.src_row_ptr ? *a.src_row_ptr : 0) + a.src_row_add + t) * a.d);
+    float4* dst = (float4*)(a.dst + (size_t)((a.dst_row_ptr ? *a.dst_row_ptr : 0) + a.dst_row_add + t) * a.d);
+    float ss = 0.f;
+    for (int i = tid; i < a.d / 4; i += 256) {
+        const float4 v = src[i], g = *(const float4*)(gain + i * 4);
+        dst[i] = v;
+        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        const float w[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
+        put_tile_planes(np, np_tk, t, i * 4, w);
+    }
+    const float tot = wave_sum(ss);
+    if ((tid & 63) == 0) part[tid >> 6] = tot;
+    __syncthreads();
+    if (tid == 0) ssq[t] = part[0] + part[1] + part[2] + part[3];
+}
+
+hipError_t launch_row_tiles(const RowCopyArgs& a, const float* gain, char* np, float* ssq, hipStream_t st) {
+    if (!gain || !np || !ssq || a.d % 32 || a.T < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(row_tile_kernel, dim3(a.T), dim3(256), 0, st, a, gain, np, a.d / 32, ssq);
+    return hipGetLastError();
+}
+
+// cos and sin of position * base^(-2i / d_head), in double precision
+__global__ __launch_bounds__(64) void rope_table_kernel(double2* table, int half, double base) {
+    const int pos = (int)blockIdx.x;
+    for (int i = threadIdx.x; i < half; i += 64) {
+        const double fr = exp2(-(double)(2 * i) / (double)(2 * half) * log2(base));
+        double sn, cs;
+        sincos((double)pos * fr, &sn, &cs);
+        table[(size_t)pos * half + i] = make_double2(cs, sn);
+    }
+}
+
+hipError_t launch_rope_table(double2* table, int positions, int d_head, float base, hipStream_t st) {
+    if (!table || positions < 1 || d_head < 2) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(rope_table_kernel, dim3(positions), dim3(64), 0, st, table, d_head / 2, (double)base);
+    return hipGetLastError();
+}
+
+// Launch shapes.  `us` is what one step (32 inputs; with sliced inputs 32 per slice) of a workgroup takes when it has a
+// compute unit to itself, measured over 64 .. 1531 rows x 512 .. 49152 features x 512 .. 11008 inputs: it follows the bytes
+// a step pulls (8 to 48 KiB at 45 to 60 bytes a ns).  Workgroups that share a compute unit or follow each other on it take 0.8
+// of that each.  The shape with the smallest total is taken: the wide shared tiles where there are enough of them, else
+// smaller tiles and sliced inputs.  (1023 x 22016 x 4096: 285 us, 1.3 PFLOP/s issued of the 1.75 the matrix cores keep up on
+// random operands; 512 x 1024 x 4096: 18.5 us; 64 x 1024 x 1024: 5.2 us.)
+struct TileShape {
+    int rt, ft, wk;
+    bool share;
+    float us;
+};
+static TileShape tile_shape(const TileGemmArgs& a) {
+    static const TileShape shapes[] = {{8, 4, 1, true, 0.94f}, {4, 4, 1, true, 0.57f}, {4, 4, 2, false, 0.84f},
+                                       {4, 4, 4, false, 0.80f}, {4, 2, 4, false, 0.69f}, {4, 1, 4, false, 0.60f},
+                                       {2, 4, 4, false, 0.56f}, {2, 2, 4, false, 0.42f}, {2, 1, 4, false, 0.36f}};
+    const bool gated = a.epi == EPI_ACT && a.act != BILD_ACT_RELU;
+    const TileShape* best = nullptr;
+    float least = 0.f;
+    for (const TileShape& t : shapes) {
+        if (gated && t.ft == 1) continue;
+        const int rows = t.rt * 16, feats = t.ft * (kTileWaves / t.wk);
+        const int rounds = (((a.M + rows - 1) / rows) * ((a.W.tn + feats - 1) / feats) + 255) / 256;
+        const float us = (float)((a.W.tk + t.wk - 1) / t.wk) * t.us * (rounds == 1 ? 1.f : 0.8f * (float)rounds);
+        if (!best || us < least) { best = &t; least = us; }
+    }
+    return *best;
+}
+
+int tile_gemm_parts(const TileGemmArgs& a) {
+    const TileShape t = tile_shape(a);
+    const int per = t.ft * (kTileWaves / t.wk);
+    return (a.W.tn + per - 1) / per;
+}
+
+hipError_t launch_gemm_tile(const TileGemmArgs& a0, hipStream_t st) {
+    TileGemmArgs a = a0;
+    const TileShape t = tile_shape(a);
+    a.wk = t.wk;
+    a.lwk = a.wk == 4 ? 2 : a.wk - 1;
+    const bool gated = a.epi == EPI_ACT && a.act != BILD_ACT_RELU;
+    const bool norm = a.epi != EPI_RESID;
+    if (a.M < 1 || !a.xp || a.W.tk < 1 || (norm && (!a.ssq || a.ssq_parts < 1))) return hipErrorInvalidValue;
+    if ((a.epi == EPI_RESID && (!a.x || !a.np || !a.np_gain || !a.np_ssq)) || (a.epi == EPI_ACT && !a.np)) return hipErrorInvalidValue;
+    if (a.epi == EPI_QKV && (!a.k_cache || !a.v_cache || a.layer_n < 1 || (a.q_dim > 0 && !a.q_out))) return hipErrorInvalidValue;
+    const int rows = t.rt * 16;
+    a.fgs = tile_gemm_parts(a);
+    a.rbs = (a.M + rows - 1) / rows;
+    // dies in gr row shares x 8 / gr feature shares: every feature share fetches all its rows, every row share all its weights;
+    // least bytes into the eight L2s, without leaving dies idle where there are few row blocks or feature groups
+    long least = 0;
+    for (int gr = 1; gr <= 8; gr *= 2) {
+        const int gf = 8 / gr;
+        const long slots = (long)((a.rbs + gr - 1) / gr) * ((a.fgs + gf - 1) / gf);  // workgroups of the busiest die
+        const long cost = (long)(gf * (long)a.M * 4 + gr * (long)a.W.n * 2) * (slots * 8 * 4 > 5 * (long)a.rbs * a.fgs ? 4 : 1) * 16 + slots;
+        if (gr == 1 || cost < least) { least = cost; a.gr = gr; }
+    }
+    const int gf = 8 / a.gr;
+    const dim3 grid((unsigned)(8 * ((a.rbs + a.gr - 1) / a.gr) * ((a.fgs + gf - 1) / gf))), block(64 * kTileWaves);
+    const size_t smem = (size_t)tile_sums(t.rt) * 4 + (t.share ? (size_t)4 * t.rt * 1024 : a.wk > 1 ? (size_t)kTileWaves * t.rt * t.ft * 1024 : 0);
+#define BILD_T(RTV, FTV, EPIV, ROPEV, GV, SP, SH)                                                                            \
+    do {                                                                                                                     \
+        static hipError_t e = hipFuncSetAttribute((const void*)gemm_tile_kernel<RTV, FTV, EPIV, ROPEV, GV, SP, SH>,          \
+                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);                    \
+        if (e != hipSuccess) return e;                                                                                       \
+        hipLaunchKernelGGL((gemm_tile_kernel<RTV, FTV, EPIV, ROPEV, GV, SP, SH>), grid, block, smem, st, a);                 \
+        return hipGetLastError();                                                                                            \
+    } while (0)
+#define BILD_TF(EPIV, ROPEV)                                                                                                 \
+    do {                                                                                                                     \
+        if (t.share && t.rt == 8) BILD_T(8, 4, EPIV, ROPEV, false, false, true);                                             \
+        if (t.share) BILD_T(4, 4, EPIV, ROPEV, false, false, true);                                                          \
+        if (t.rt == 2 && t.ft == 4) BILD_T(2, 4, EPIV, ROPEV, false, true, false);                                           \
+        if (t.rt == 2 && t.ft == 2) BILD_T(2, 2, EPIV, ROPEV, false, true, false);                                           \
+        if (t.rt == 2) BILD_T(2, 1, EPIV, ROPEV, false, true, false);                                                        \
+        if (t.ft == 4) BILD_T(4, 4, EPIV, ROPEV, false, true, false);                                                        \
+        if (t.ft == 2) BILD_T(4, 2, EPIV, ROPEV, false, true, false);                                                        \
+        BILD_T(4, 1, EPIV, ROPEV, false, true, false);                                                                       \
+    } while (0)
+    switch (a.epi) {
+        case EPI_RESID: BILD_TF(EPI_RESID, 0); break;
+        case EPI_ACT:
+            if (!gated) BILD_TF(EPI_ACT, 0);
+            if (t.share && t.rt == 8) BILD_T(8, 4, EPI_ACT, 0, true, false, true);
+            if (t.share) BILD_T(4, 4, EPI_ACT, 0, true, false, true);
+            if (t.rt == 2 && t.ft == 4) BILD_T(2, 4, EPI_ACT, 0, true, true, false);
+            if (t.rt == 2) BILD_T(2, 2, EPI_ACT, 0, true, true, false);
+            if (t.ft == 4) BILD_T(4, 4, EPI_ACT, 0, true, true, false);
+            BILD_T(4, 2, EPI_ACT, 0, true, true, false);
+            break;
+        case EPI_QKV:
+            if (a.rope) BILD_TF(EPI_QKV, 1); else BILD_TF(EPI_QKV, 0);
+            break;
+        default: break;
+    }
+#undef BILD_TF
+#undef BILD_T
+    return hipErrorInvalidValue;
+}
+
+}  // namespace bild

@@ -112,15 +112,15 @@ __global__ __launch_bounds__(512) void gemm_merge_kernel(BILD_GEMM_HOT_PARAMS, c
     gemm_body<DT, 1, EPI_RESID, 0, 1, gemm_batch(1, false), SPLITS, false, !SHORT>(a, (int)blockIdx.x, smem);
 }
 
-// Between kMaxRows and kDenseMinRows rows (an encoder over a source of a few hundred tokens): blockIdx.y picks a block
+// Between kMaxRows and kDenseMinRows rows of an fp32 model (bf16 models: gemm_tile.hip): blockIdx.y picks a block
 // of kMaxRows rows and the same body runs on it.  The blocks of one feature group re-read its weight tiles, which by
 // then sit in L2 or the memory-side cache, so HBM still streams every weight about once.  At these sizes a projection
 // is a GFLOP or two: too little to fill the dense-tile kernel's 64-row tiles on 256 compute units (measured on 512 rows
 // of 1024..4096-wide projections: 12..40 us per launch there, 12..25 us here); longer passes go to gemm_dense.hip.
-template <int DT, int RW, int EPI, int ROPE>
+template <int RW, int EPI, int ROPE>
 __global__ __launch_bounds__(512) void gemm_rows_kernel(BILD_GEMM_HOT_PARAMS, const GemmArgs a0) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const GemmArgs a = gemm_hot<HOT_X, DT>(a0, BILD_GEMM_HOT_NAMES);
+    const GemmArgs a = gemm_hot<HOT_X, 0>(a0, BILD_GEMM_HOT_NAMES);
     GemmArgs b = a;
     const int r0 = (int)blockIdx.y * kMaxRows;
     b.T = min(kMaxRows, a.T - r0);
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(BILD_GEMM_HOT_PARAMS, co
     if (a.out) b.out = a.out + (size_t)r0 * a.ldo;
     if (a.q_out) b.q_out = a.q_out + (size_t)r0 * a.i_dim;
     b.pos_add = a.pos_add + r0;
-    gemm_body<DT, RW, EPI, ROPE, 2>(b, (int)blockIdx.x, smem);
+    gemm_body<0, RW, EPI, ROPE, 2>(b, (int)blockIdx.x, smem);
 }
 
 // LDS a GEMM workgroup may ask for (a gfx950 compute unit has 160 KiB) and the share of it the staged chunk may take:
@@ -262,11 +262,11 @@ static hipError_t raise_lds_limits() {
     (const void*)gemm_kernel<DTV, 1, EPI_STORE, 0, 1, true>, (const void*)gemm_kernel<DTV, 1, EPI_RESID, 0, 1, true>, \
     (const void*)gemm_kernel<DTV, 1, EPI_QKV, 0, 1, true>, (const void*)gemm_kernel<DTV, 1, EPI_QKV, 1, 1, true>, \
     (const void*)gemm_kernel<DTV, 1, EPI_ACT, 0, 1, true>, \
-    (const void*)gemm_kernel<DTV, 4, EPI_LMHEAD, 0, 1>, \
-    (const void*)gemm_rows_kernel<DTV, 1, EPI_STORE, 0>, (const void*)gemm_rows_kernel<DTV, 1, EPI_RESID, 0>, \
-    (const void*)gemm_rows_kernel<DTV, 1, EPI_QKV, 0>, (const void*)gemm_rows_kernel<DTV, 1, EPI_QKV, 1>, \
-    (const void*)gemm_rows_kernel<DTV, 1, EPI_ACT, 0>, (const void*)gemm_rows_kernel<DTV, 2, EPI_ACT, 0>
+    (const void*)gemm_kernel<DTV, 4, EPI_LMHEAD, 0, 1>
         const void* fns[] = {BILD_G(0), BILD_G(1),
+                             (const void*)gemm_rows_kernel<1, EPI_RESID, 0>, (const void*)gemm_rows_kernel<1, EPI_QKV, 0>,
+                             (const void*)gemm_rows_kernel<1, EPI_QKV, 1>, (const void*)gemm_rows_kernel<1, EPI_ACT, 0>,
+                             (const void*)gemm_rows_kernel<2, EPI_ACT, 0>,
                              (const void*)gemm_merge_kernel<0, 2>, (const void*)gemm_merge_kernel<0, 4>,
                              (const void*)gemm_merge_kernel<0, 8>, (const void*)gemm_merge_kernel<1, 2>,
                              (const void*)gemm_merge_kernel<1, 4>, (const void*)gemm_merge_kernel<1, 8>,
@@ -438,6 +438,16 @@ hipError_t launch_gemm(const GemmArgs& a, int dtype, hipStream_t st) {
         return hipGetLastError();
     }
     const dim3 grid((unsigned)gemm_num_blocks(a), row_blocks), block(64 * a.nwv);
+    if (row_blocks > 1) {
+        if (dtype) return hipErrorInvalidValue;
+        if (a.epi == EPI_RESID) hipLaunchKernelGGL((gemm_rows_kernel<1, EPI_RESID, 0>), grid, block, smem, st, BILD_GEMM_HOT(a), a);
+        else if (a.epi == EPI_QKV && a.rope) hipLaunchKernelGGL((gemm_rows_kernel<1, EPI_QKV, 1>), grid, block, smem, st, BILD_GEMM_HOT(a), a);
+        else if (a.epi == EPI_QKV) hipLaunchKernelGGL((gemm_rows_kernel<1, EPI_QKV, 0>), grid, block, smem, st, BILD_GEMM_HOT(a), a);
+        else if (a.epi == EPI_ACT && a.rw == 2) hipLaunchKernelGGL((gemm_rows_kernel<2, EPI_ACT, 0>), grid, block, smem, st, BILD_GEMM_HOT(a), a);
+        else if (a.epi == EPI_ACT) hipLaunchKernelGGL((gemm_rows_kernel<1, EPI_ACT, 0>), grid, block, smem, st, BILD_GEMM_HOT(a), a);
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
     // tiles the busiest wave has: picks the batch geometry (see gemm_row_kernel)
     const bool one_chunk = a.W.k <= a.kc;
     const int per_wave = (a.W.tk + a.wk - 1) / a.wk;
@@ -446,9 +456,7 @@ hipError_t launch_gemm(const GemmArgs& a, int dtype, hipStream_t st) {
     const bool few_ok = a.T >= 2 && a.T <= 4 && one_chunk && ((n4 & 63) != 0 || a.T * n4 <= 4 * 64 * a.nwv);
 #define BILD_L(DTV, RWV, EPIV, ROPEV)                                                              \
     do {                                                                                            \
-        if (row_blocks > 1)                                                                         \
-            hipLaunchKernelGGL((gemm_rows_kernel<DTV, RWV, EPIV, ROPEV>), grid, block, smem, st, BILD_GEMM_HOT(a), a); \
-        else if (a.T == 1 && RWV == 2 && one_chunk && per_wave <= kShortBatch / 2)                  \
+        if (a.T == 1 && RWV == 2 && one_chunk && per_wave <= kShortBatch / 2)                  \
             hipLaunchKernelGGL((gemm_row_kernel<DTV, 2, EPI_ACT, 0, 1>), grid, block, smem, st, BILD_GEMM_HOT(a), a); \
         else if (a.T == 1 && RWV == 2 && one_chunk && (per_wave <= kShortBatch || (per_wave % 4 == 0 && per_wave % 6 != 0))) \
             hipLaunchKernelGGL((gemm_row_kernel<DTV, 2, EPI_ACT, 0, 2>), grid, block, smem, st, BILD_GEMM_HOT(a), a); \

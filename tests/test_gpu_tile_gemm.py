@@ -1,0 +1,47 @@
+"""The GEMM of bf16 models over many rows (encoder, cross K/V, prompt prefill) at the edges of its row and feature tiles,
+through the C ABI against the CPU oracle: every logit depends on what these passes left in the caches."""
+from dataclasses import replace
+
+import pytest
+
+import bild_inputs as bi
+import oracle
+from tests import parity
+from tests.test_gpu_parity import Rig
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(cfg, bar=None):
+    """`bar`: the configuration whose storage type sets the tolerance."""
+    R = Rig(cfg)
+    ref = oracle.bild_generate(R.req, 0.4, 1.0, 4, cfg.max_new, keep_logits=True)
+    st = R.state(cfg.max_new, 4)
+    st.encode(R.src)
+    parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, bar or cfg)
+
+
+@pytest.mark.parametrize("n_src", [1, 2, 15, 16, 17, 32, 33, 63, 64, 65, 129])
+@pytest.mark.parametrize("act", [bi.ACT_RELU, bi.ACT_GATED_GELU])
+def test_source_lengths_around_the_row_tiles(n_src, act):
+    _check(bi.toy_pair(dtype=bi.DT_BF16, act=act, truncate=True, n_src=n_src, max_new=6))
+
+
+@pytest.mark.parametrize("n_src", [34, 49, 65, 131])
+def test_prompt_lengths_around_the_row_tiles(n_src):
+    """33 rows and more of a prompt in one pass, with rotary positions; the rows behind the last whole row tile included."""
+    _check(bi.toy_pair(dtype=bi.DT_BF16, act=bi.ACT_SWIGLU, pos=bi.POS_ROPE, cross=False, tied=False, truncate=True,
+                       n_src=n_src, max_new=6))
+
+
+def test_wide_layers_take_the_shared_row_tiles():
+    """1100 rows of a 1024-wide model with 4096 hidden units: the launch shapes whose rows go through LDS."""
+    _check(bi.toy_pair(dtype=bi.DT_BF16, d=1024, heads=16, d_head=64, d_ff=4096, vocab=300, n_large=2, n_src=1100, max_new=4,
+                       logit_scale=4.0))
+
+
+@pytest.mark.parametrize("small,large", [(bi.DT_BF16, bi.DT_F32), (bi.DT_F32, bi.DT_BF16)])
+def test_pair_of_two_storage_types_with_a_borrowed_encoder(small, large):
+    """The small model attends to the encoder output of a large model that stores another type."""
+    cfg = bi.toy_pair(dtype=bi.DT_BF16, n_src=40, max_new=6)   # weights that both types hold exactly
+    _check(replace(cfg, small=replace(cfg.small, dtype=small), large=replace(cfg.large, dtype=large)), bar=cfg)
