@@ -364,14 +364,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int h, const 
         } else if (t < T && d0 < dh) {
             if (a.splits == 1) {
                 const float inv = 1.f / Lsum;
-                if (DT && a.ob_t) {
-                    uint32_t h01, l01, h23, l23;
-                    split_bf16x2(acc[0] * inv, acc[1] * inv, h01, l01);
-                    split_bf16x2(acc[2] * inv, acc[3] * inv, h23, l23);
-                    char* p = a.ob_t + plane_offset(I >> 5, a.ob_row0 + t, h * dh + d0);
-                    st_u64(p, h01, h23);
-                    st_u64(p + kTileBytes, l01, l23);
-                } else if (DT && a.ob_hi) {
+                if (DT && a.ob_hi) {
                     uint32_t h01, l01, h23, l23;
                     split_bf16x2(acc[0] * inv, acc[1] * inv, h01, l01);
                     split_bf16x2(acc[2] * inv, acc[3] * inv, h23, l23);
@@ -399,8 +392,9 @@ __global__ __launch_bounds__(512) void attn_kernel(BILD_ATTN_HOT_PARAMS, const A
     attn_body<DT, DH32, REL>(a, (int)blockIdx.x, (int)blockIdx.y, smem, [] {});  // grid: heads x key splits
 }
 
-// More than kMaxRows query rows: blockIdx.z picks the block of rows (key splits are not combined with it).
-template <int DT, int DH32, bool REL = false>
+// More than kMaxRows query rows of an fp32 model (bf16 models: attn_tile.hip): blockIdx.z picks the block of rows (key
+// splits are not combined with it).
+template <int DH32, bool REL = false>
 __global__ __launch_bounds__(512) void attn_rows_kernel(BILD_ATTN_HOT_PARAMS, const AttnArgs a0) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const AttnArgs a = attn_hot(a0, BILD_ATTN_HOT_NAMES);
@@ -409,9 +403,8 @@ __global__ __launch_bounds__(512) void attn_rows_kernel(BILD_ATTN_HOT_PARAMS, co
     b.T = min(kMaxRows, a.T - r0);
     b.q = a.q + (size_t)r0 * a.i_dim;
     b.out = a.out + (size_t)r0 * a.i_dim;
-    b.ob_row0 = r0;
     b.base_add = a.base_add + r0;
-    attn_body<DT, DH32, REL>(b, (int)blockIdx.x, 0, smem, [] {});
+    attn_body<0, DH32, REL>(b, (int)blockIdx.x, 0, smem, [] {});
 }
 
 // Attention of one head followed by that head's share of the output projection, for single-row passes of the narrow
@@ -548,15 +541,13 @@ size_t attn_lds_bytes(int dtype, int d_head, int T, int nw) {
 static hipError_t attn_raise_lds_limits() {
     static hipError_t done = [] {
         const void* fns[] = {
-                             (const void*)attn_rows_kernel<0, 1>, (const void*)attn_rows_kernel<0, 2>,
-                             (const void*)attn_rows_kernel<0, 4>, (const void*)attn_rows_kernel<1, 1>,
-                             (const void*)attn_rows_kernel<1, 2>, (const void*)attn_rows_kernel<1, 4>,
+                             (const void*)attn_rows_kernel<1>, (const void*)attn_rows_kernel<2>,
+                             (const void*)attn_rows_kernel<4>,
                              (const void*)attn_kernel<0, 1>, (const void*)attn_kernel<0, 2>,
                              (const void*)attn_kernel<0, 4>, (const void*)attn_kernel<1, 1>,
                              (const void*)attn_kernel<1, 2>, (const void*)attn_kernel<1, 4>,
-                             (const void*)attn_rows_kernel<0, 1, true>, (const void*)attn_rows_kernel<0, 2, true>,
-                             (const void*)attn_rows_kernel<0, 4, true>, (const void*)attn_rows_kernel<1, 1, true>,
-                             (const void*)attn_rows_kernel<1, 2, true>, (const void*)attn_rows_kernel<1, 4, true>,
+                             (const void*)attn_rows_kernel<1, true>, (const void*)attn_rows_kernel<2, true>,
+                             (const void*)attn_rows_kernel<4, true>,
                              (const void*)attn_kernel<0, 1, true>, (const void*)attn_kernel<0, 2, true>,
                              (const void*)attn_kernel<0, 4, true>, (const void*)attn_kernel<1, 1, true>,
                              (const void*)attn_kernel<1, 2, true>, (const void*)attn_kernel<1, 4, true>,
@@ -613,13 +604,20 @@ hipError_t launch_attention(const AttnArgs& a, int dtype, hipStream_t st) {
                         (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);  // + one head's row of the bias table
     if (smem > (size_t)kAttnLdsLimit) return hipErrorInvalidValue;
     const dim3 grid(a.heads, a.splits, row_blocks), block(64 * a.nw);
+    if (row_blocks > 1) {
+        if (dtype) return hipErrorInvalidValue;
+#define BILD_AR(DHV)                                                                                                          \
+    do {                                                                                                                      \
+        if (a.rel_bias) hipLaunchKernelGGL((attn_rows_kernel<DHV, true>), grid, block, smem, st, BILD_ATTN_HOT(a), a);        \
+        else hipLaunchKernelGGL((attn_rows_kernel<DHV>), grid, block, smem, st, BILD_ATTN_HOT(a), a);                         \
+    } while (0)
+        if (dh32 == 1) BILD_AR(1); else if (dh32 == 2) BILD_AR(2); else BILD_AR(4);
+#undef BILD_AR
+        return hipGetLastError();
+    }
 #define BILD_ATTN(DTV, DHV)                                                                     \
     do {                                                                                        \
-        if (row_blocks > 1 && a.rel_bias)                                                       \
-            hipLaunchKernelGGL((attn_rows_kernel<DTV, DHV, true>), grid, block, smem, st, BILD_ATTN_HOT(a), a);   \
-        else if (row_blocks > 1)                                                                \
-            hipLaunchKernelGGL((attn_rows_kernel<DTV, DHV>), grid, block, smem, st, BILD_ATTN_HOT(a), a);         \
-        else if (a.rel_bias)                                                                    \
+        if (a.rel_bias)                                                                         \
             hipLaunchKernelGGL((attn_kernel<DTV, DHV, true>), grid, block, smem, st, BILD_ATTN_HOT(a), a);        \
         else                                                                                    \
             hipLaunchKernelGGL((attn_kernel<DTV, DHV>), grid, block, smem, st, BILD_ATTN_HOT(a), a);              \

@@ -746,7 +746,7 @@ int emit_prefill(bild_state* s, int w, int T) {
         if (last && !keeps_hidden) break;
         AttnArgs a;
         std::memset((void*)&a, 0, sizeof(a));
-        a.q = M.q; a.k = M.kcache + off; a.v = M.vcache + off; a.out = M.a; a.ob_t = p.at;
+        a.q = M.q; a.k = M.kcache + off; a.v = M.vcache + off; a.ob_t = p.at;
         a.T = T; a.heads = c.n_heads; a.d_head = c.d_head; a.i_dim = m->inner();
         a.causal = 1;
         a.len_ptr = len_ptr;
@@ -754,10 +754,8 @@ int emit_prefill(bild_state* s, int w, int T) {
         a.rel_d = c.rel_max_dist;
         a.vcap = s->cap_len;
         a.scale = 1.f / std::sqrt((float)c.d_head);
-        a.splits = 1;
-        a.nw = pick_attn_waves(c.dtype, c.d_head, std::min(T, kMaxRows), s->len[w] + T, 1);
         s->stage_count += 1;
-        HIPC(launch_attention(a, c.dtype, s->stream));
+        HIPC(launch_attention_tile(a, s->stream));
         rc = tile_resid(p, L.wo, p.at, L.ln2);
         if (rc) return rc;
         rc = tile_ffn(p, L, last ? m->dec_final : m->dec[l + 1].ln1);
@@ -1282,17 +1280,15 @@ int run_encoder_tiles(bild_state* s, int w) {
         if (rc) return rc;
         AttnArgs a;
         std::memset((void*)&a, 0, sizeof(a));
-        a.q = M.enc_q; a.k = M.enc_k; a.v = M.enc_v; a.out = M.enc_a; a.ob_t = p.at;
+        a.q = M.enc_q; a.k = M.enc_k; a.v = M.enc_v; a.ob_t = p.at;
         a.T = S; a.heads = c.n_heads; a.d_head = c.d_head; a.i_dim = m->inner();
         a.nkeys_fixed = S;
         a.rel_bias = m->enc_rel;
         a.rel_d = c.rel_max_dist;
         a.len_ptr = &s->ctl->n_src;  // not used with a fixed count, but the kernel reads it
         a.vcap = s->cap_src;
-        a.splits = 1;
-        a.nw = pick_attn_waves(c.dtype, c.d_head, std::min(S, kMaxRows), S, 1);
         a.scale = 1.f / std::sqrt((float)c.d_head);
-        HIPC(launch_attention(a, c.dtype, s->stream));
+        HIPC(launch_attention_tile(a, s->stream));
         rc = tile_resid(p, L.wo, p.at, L.ln2);
         if (rc) return rc;
         rc = tile_ffn(p, L, l + 1 < c.n_enc_layers ? m->enc[l + 1].ln1 : m->enc_final);

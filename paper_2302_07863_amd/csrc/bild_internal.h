@@ -183,8 +183,7 @@ struct AttnArgs {
     // what the output projection stages) instead of `out`; not used while the partials are left to the consumer
     uint16_t* ob_hi;
     uint16_t* ob_lo;
-    char* ob_t;                 // non-null (bf16 models, more than kMaxRows rows): the finished output as tile planes [T][I]
-    int ob_row0;                // (set by the kernel) first row of this row block
+    char* ob_t;                 // launch_attention_tile: the finished output as tile planes [T][I]
     // attention fused with the output projection (launch_attention_proj): W_o, the partial results of the residual
     // update, one per head ([heads][proj_stride], laid out [T][d_model]), and the number of column groups
     TMat wo;
@@ -324,6 +323,7 @@ hipError_t launch_embed_tiles(const EmbedArgs& a, char* np, hipStream_t st);
 // row copy (see RowCopyArgs) that also leaves the rows' planes times `gain` and their sums of squares
 hipError_t launch_row_tiles(const RowCopyArgs& a, const float* gain, char* np, float* ssq, hipStream_t st);
 hipError_t launch_rope_table(double2* table, int positions, int d_head, float base, hipStream_t st);
+hipError_t launch_attention_tile(const AttnArgs& a, hipStream_t st);  // bf16 models, output as tile planes (attn_tile.hip)
 hipError_t launch_attention(const AttnArgs& a, int dtype, hipStream_t st);
 hipError_t launch_attention_proj(const AttnArgs& a, int dtype, hipStream_t st);
 constexpr int kMaxHeadParts = 16;   // heads whose partial results one reader adds (attention fused with its output projection)

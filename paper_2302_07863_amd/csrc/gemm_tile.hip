@@ -24,24 +24,6 @@ namespace bild {
 constexpr int kTileWaves = 4;
 __host__ __device__ constexpr int tile_sums(int rt) { return rt * 16 * kTileWaves > 256 ? rt * 16 * kTileWaves : 256; }
 
-__device__ __forceinline__ void put_tile_planes(char* base, int tk, int row, int n0, const float (&w)[4]) {
-    uint32_t h01, l01, h23, l23;
-    split_bf16x2(w[0], w[1], h01, l01);
-    split_bf16x2(w[2], w[3], h23, l23);
-    char* p = base + plane_offset(tk, row, n0);
-    st_u64(p, h01, h23);
-    st_u64(p + kTileBytes, l01, l23);
-}
-
-// Buffer loads: the compiler neither folds them into their use (a plain load that feeds the next turn of a loop is moved
-// there, which undoes the requests ahead) nor needs a 64-bit address per lane.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, size_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(uint32_t)min(bytes, (size_t)0xFFFFFFFFu), 0x00027000);
-}
-__device__ __forceinline__ uint4 buf_load(__amdgpu_buffer_rsrc_t r, unsigned lane_off, int off) {
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, off, 0));
-}
-
 // Row block and feature group of a workgroup.  Workgroups go to the eight dies in turn; the dies form a grid of a.gr row
 // shares x 8 / a.gr feature shares (launch_gemm_tile), and a die walks the row blocks of its share before the next feature
 // group, so that the weights of a group come from memory once and are then in that die's L2 while the rows pass.
@@ -180,8 +162,6 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const TileGemmArgs a)
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        // all waves past this point have written (and read) what they were to in LDS; requests to memory stay in flight
-        auto lds_barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
         // (in the order of the loop: the memory counter retires requests in order, and the waits of the loop hold for both ways into it)
         uint4 X0[UPW];
         request_x(X0, 0);

@@ -159,5 +159,27 @@ __device__ __forceinline__ void st_act4(float* p, const float4 v) { *(float4*)p 
 __device__ __forceinline__ void st_act(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st_u16(uint16_t* p, uint16_t v) { *p = v; }
 
+// Four consecutive values of a row as tile planes (see TileGemmArgs).
+__device__ __forceinline__ void put_tile_planes(char* base, int tk, int row, int n0, const float (&w)[4]) {
+    uint32_t h01, l01, h23, l23;
+    split_bf16x2(w[0], w[1], h01, l01);
+    split_bf16x2(w[2], w[3], h23, l23);
+    char* p = base + plane_offset(tk, row, n0);
+    st_u64(p, h01, h23);
+    st_u64(p + kTileBytes, l01, l23);
+}
+
+// Buffer loads: the compiler neither folds them into their use (a plain load that feeds the next turn of a loop is moved
+// there, which undoes the requests ahead) nor needs a 64-bit address per lane.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(uint32_t)min(bytes, (size_t)0xFFFFFFFFu), 0x00027000);
+}
+__device__ __forceinline__ uint4 buf_load(__amdgpu_buffer_rsrc_t r, unsigned lane_off, int off) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, off, 0));
+}
+
+// Barrier over LDS only: what the waves were to write (and read) there is done; requests to memory stay in flight, which a
+// __syncthreads would wait for.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 }  // namespace bild
