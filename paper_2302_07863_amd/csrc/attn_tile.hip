@@ -7,7 +7,7 @@
 // per lane.  q stays in registers as the B operand, high and low bf16 part, times 1/sqrt(d_head) and log2(e), so that
 // probabilities are bare base-2 exponentials.  The score tile leaves the matrix core in the B-operand order of the second
 // product (contraction index 8g + j is key 4g + j of the first 16 keys for j < 4, of the second 16 for j >= 4), so
-// probabilities never cross lanes; maximum and rescaling are per 64 keys, the row sums stay per lane until the end.
+// probabilities never cross lanes.
 //
 // Bound: vector ALU (the exponentials and the split of P, about 130 instructions per 64 keys and 16 rows against 32
 // matrix instructions).  The kernel before it gave 32 rows to eight waves that split the keys and merged: each such
@@ -38,9 +38,9 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(const AttnArgs a) {
     const __amdgpu_buffer_rsrc_t kr = make_rsrc((const uint16_t*)a.k + (size_t)h * dh, 0xFFFFFFFFu);
     const __amdgpu_buffer_rsrc_t vr = make_rsrc((const uint16_t*)a.v + (size_t)h * dh * a.vcap, 0xFFFFFFFFu);
     // this wave fetches the K of keys 16 wave .. + 15 of a block and a quarter of its V^T
-    uint4 Kn[DH32];
-    uint2 Vn[DH32][2];
-    auto request = [&](int blk) {
+    uint4 K0[DH32], K1[DH32];
+    uint2 V0[DH32][2], V1[DH32][2];
+    auto request = [&](uint4 (&Kn)[DH32], uint2 (&Vn)[DH32][2], int blk) {
         const int key = min(blk * 64 + wave * 16 + tok_l, a.vcap - 1);  // (the caches hold whole blocks of 32 positions)
 #pragma unroll
         for (int ks = 0; ks < DH32; ++ks)
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(const AttnArgs a) {
             Vn[i][1] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, (d * a.vcap + k0 + 16) * 2, 0, 0));
         }
     };
-    auto store = [&](int buf) {
+    auto store = [&](const uint4 (&Kn)[DH32], const uint2 (&Vn)[DH32][2], int buf) {
         char* kb = smem + buf * BUF + lane * 16;
 #pragma unroll
         for (int ks = 0; ks < DH32; ++ks) *(uint4*)(kb + (wave * DH32 + ks) * 1024) = Kn[ks];
@@ -62,7 +62,9 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(const AttnArgs a) {
         for (int i = 0; i < DH32; ++i)
             *(uint4*)(kb + KB + (wave * DH32 + i) * 1024) = make_uint4(Vn[i][0].x, Vn[i][0].y, Vn[i][1].x, Vn[i][1].y);
     };
-    request(0);
+    request(K0, V0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    request(K1, V1, min(1, nblk - 1));
     bf16x8 Qh[DH32], Ql[DH32];
     {
         const float sc = a.scale * kLog2e;
@@ -85,82 +87,116 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(const AttnArgs a) {
         for (int i = tid; i < nrel; i += 256) relb[i] = a.rel_bias[(size_t)h * nrel + i] * kLog2e;
     const int qpos = (a.causal ? base : a.base_add) + t;
 
-    float m_run = -INFINITY, l_run = 0.f;
-    f32x4 O[DT16];
+    // m_run is subtracted in the accumulators the products start from; it follows the row's maximum only when that has
+    // grown by more than 2^6 (or for the first block), so most blocks neither rescale O nor subtract: probabilities stay below
+    // 64, the quotient is the same.  The row sums are one more product, with a tile of ones.
+    float m_run = 0.f;
+    f32x4 O[DT16], L = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int dt = 0; dt < DT16; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    store(0);
-    lds_barrier();
-    for (int blk = 0; blk < nblk; ++blk) {
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+    auto block = [&](int blk) {
         const char* kb = smem + (blk & 1) * BUF + lane * 16;
-        request(min(blk + 1, nblk - 1));
         const int key0 = blk * 64;
-        if (!a.causal || key0 <= base + min(rw + 15, T - 1)) {  // (wave-uniform) some row of this wave sees the block
-            f32x4 s[4];
+        if (a.causal && key0 > base + min(rw + 15, T - 1)) return;  // (wave-uniform) no row of this wave sees the block
+        // All operands of the block are read ahead and the products dealt round the accumulators: left to itself the compiler
+        // reads each operand in front of its use and chains the four products of a tile, so that one wave waits for LDS and
+        // for the matrix core most of the time (39 us at 1531 rows, whatever else was taken out of the loop).
+        bf16x8 Ak[4][DH32];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                s[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ks = 0; ks < DH32; ++ks)
 #pragma unroll
-                for (int ks = 0; ks < DH32; ++ks) {
-                    const bf16x8 A = __builtin_bit_cast(bf16x8, *(const uint4*)(kb + (c * DH32 + ks) * 1024));
-                    s[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Qh[ks], s[c], 0, 0, 0);
-                    s[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Ql[ks], s[c], 0, 0, 0);
-                }
-            }
-            if constexpr (REL) {
+            for (int c = 0; c < 4; ++c) Ak[c][ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(kb + (c * DH32 + ks) * 1024));
+        f32x4 s[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < 4; ++c) s[c] = f32x4{-m_run, -m_run, -m_run, -m_run};
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int dist = max(-a.rel_d, min(a.rel_d, key0 + c * 16 + g * 4 + v - qpos));
-                        s[c][v] += relb[a.rel_d + dist];
-                    }
-            }
-            if (key0 + 63 > lim_min) {
+        for (int ks = 0; ks < DH32; ++ks) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
+            for (int c = 0; c < 4; ++c) s[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ak[c][ks], Ql[ks], s[c], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (key0 + c * 16 + g * 4 + v > lim) s[c][v] = -INFINITY;
-            }
-            float tmax = s[0][0];
+            for (int c = 0; c < 4; ++c) s[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ak[c][ks], Qh[ks], s[c], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        bf16x8 Av[2][DT16];
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
+        for (int b2 = 0; b2 < 2; ++b2)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) tmax = fmaxf(tmax, s[c][v]);
-            const float m_new = fmaxf(m_run, quad_rows_max(tmax));  // (finite: every row sees key 0)
-            const float f = __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
-            float psum = 0.f;
+            for (int dt = 0; dt < DT16; ++dt) Av[b2][dt] = __builtin_bit_cast(bf16x8, *(const uint4*)(kb + KB + (b2 * DT16 + dt) * 1024));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (REL) {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    s[c][v] = __builtin_amdgcn_exp2f(s[c][v] - m_new);
-                    psum += s[c][v];
+                    const int dist = max(-a.rel_d, min(a.rel_d, key0 + c * 16 + g * 4 + v - qpos));
+                    s[c][v] += relb[a.rel_d + dist];
                 }
-            l_run = l_run * f + psum;
+        }
+        if (key0 + 63 > lim_min) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (key0 + c * 16 + g * 4 + v > lim) s[c][v] = -INFINITY;
+        }
+        float tmax = s[0][0];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) tmax = fmaxf(tmax, s[c][v]);
+        if (blk == 0 || __builtin_amdgcn_ballot_w64(tmax > 6.f)) {
+            tmax = quad_rows_max(tmax);
+            const float up = blk == 0 ? tmax : fmaxf(tmax, 0.f);  // (block 0: every row sees key 0)
+            const float f = __builtin_amdgcn_exp2f(-up);
+            m_run += up;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s[c][v] -= up;
 #pragma unroll
             for (int dt = 0; dt < DT16; ++dt) O[dt] *= f;
-#pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) {
-                uint32_t ph[4], pl[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) split_bf16x2(s[b2 * 2 + (j >> 1)][(j & 1) * 2], s[b2 * 2 + (j >> 1)][(j & 1) * 2 + 1], ph[j], pl[j]);
-                const bf16x8 Ph = __builtin_bit_cast(bf16x8, make_uint4(ph[0], ph[1], ph[2], ph[3]));
-                const bf16x8 Pl = __builtin_bit_cast(bf16x8, make_uint4(pl[0], pl[1], pl[2], pl[3]));
-#pragma unroll
-                for (int dt = 0; dt < DT16; ++dt) {
-                    const bf16x8 A = __builtin_bit_cast(bf16x8, *(const uint4*)(kb + KB + (b2 * DT16 + dt) * 1024));
-                    O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Ph, O[dt], 0, 0, 0);
-                    O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Pl, O[dt], 0, 0, 0);
-                }
-            }
+            L *= f;
         }
-        store((blk + 1) & 1);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s[c][v] = __builtin_amdgcn_exp2f(s[c][v]);
+#pragma unroll
+        for (int b2 = 0; b2 < 2; ++b2) {
+            uint32_t ph[4], pl[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) split_bf16x2(s[b2 * 2 + (j >> 1)][(j & 1) * 2], s[b2 * 2 + (j >> 1)][(j & 1) * 2 + 1], ph[j], pl[j]);
+            const bf16x8 Ph = __builtin_bit_cast(bf16x8, make_uint4(ph[0], ph[1], ph[2], ph[3]));
+            const bf16x8 Pl = __builtin_bit_cast(bf16x8, make_uint4(pl[0], pl[1], pl[2], pl[3]));
+            __builtin_amdgcn_sched_barrier(0);
+            L = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, Ph, L, 0, 0, 0);
+#pragma unroll
+            for (int dt = 0; dt < DT16; ++dt) O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Av[b2][dt], Ph, O[dt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            L = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, Pl, L, 0, 0, 0);
+#pragma unroll
+            for (int dt = 0; dt < DT16; ++dt) O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Av[b2][dt], Pl, O[dt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    store(K0, V0, 0);
+    lds_barrier();
+    for (int blk = 0; blk < nblk; blk += 2) {  // (blocks past the end are requested again, never multiplied)
+        request(K0, V0, min(blk + 2, nblk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        block(blk);
+        store(K1, V1, 1);
+        lds_barrier();
+        request(K1, V1, min(blk + 3, nblk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        if (blk + 1 < nblk) block(blk + 1);
+        store(K0, V0, 0);
         lds_barrier();
     }
-    const float inv = 1.f / quad_rows_sum(l_run);
+    const float inv = 1.f / L[0];
     if (rw + tok_l < T) {
 #pragma unroll
         for (int dt = 0; dt < DT16; ++dt) {
