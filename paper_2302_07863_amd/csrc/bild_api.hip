@@ -308,13 +308,15 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     want(s->y, sizeof(int) * (size_t)(max_len + 1));
     want(s->src, sizeof(int) * (size_t)max_src);
     void* h = nullptr;
-    if (hipHostMalloc(&h, sizeof(Ctl) + 64, hipHostMallocMapped) != hipSuccess) {
+    if (hipHostMalloc(&h, 1024 + sizeof(int) * ((size_t)max_len + 1 + max_src), hipHostMallocMapped) != hipSuccess) {
         bild_state_destroy(s);
         return BILD_ENOMEM;
     }
     s->host_allocs.push_back(h);
     s->hctl = (Ctl*)h;
-    s->halpha = (float*)((char*)h + sizeof(Ctl));
+    static_assert(sizeof(Ctl) <= 1024, "the tokens follow behind the control block");
+    s->hy = (int*)((char*)h + 1024);
+    s->hsrc = s->hy + max_len + 1;
     void* hd = nullptr;
     if (hipHostGetDevicePointer(&hd, h, 0) != hipSuccess) {
         bild_state_destroy(s);
@@ -429,8 +431,26 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
 
 namespace {
 
-int push_ctl(bild_state* s) {
+CtlArgs ctl_args(const bild_state* s) {
+    CtlArgs a;
+    std::memset((void*)&a, 0, sizeof(a));
+    a.ctl = s->ctl;
+    const int head[6] = {s->y_len, s->draft_start, s->len[0], s->len[1], s->n_src, s->n_max};
+    std::memcpy(a.head, head, sizeof(head));
+    std::memcpy(a.head + 6, &s->alpha_fb, 4);
+    std::memcpy(a.head + 7, &s->alpha_rb, 4);
+    a.seq = s->seq_issued;
+    return a;
+}
+
+// address as the device sees it of something in the pinned block
+const int* on_device(const bild_state* s, const int* p) { return (const int*)((const char*)s->hctl_dev + ((const char*)p - (const char*)s->hctl)); }
+
+// The host's view of the request becomes the device's, with `n` tokens of hy from position `first` on and all of hsrc if
+// `sources`.  A token of hy or hsrc that the host changes again before the kernel has read it is copied by the next call.
+int push_ctl(bild_state* s, int first = 0, int n = 0, bool sources = false) {
     Ctl* h = s->hctl;
+    if (__atomic_load_n(&h->seq, __ATOMIC_ACQUIRE) != s->seq_issued) HIPC(hipStreamSynchronize(s->stream));  // (an earlier call failed half way)
     std::memset(h, 0, sizeof(Ctl));
     h->y_len = s->y_len;
     h->draft_start = s->draft_start;
@@ -441,8 +461,14 @@ int push_ctl(bild_state* s) {
     h->alpha_fb = s->alpha_fb;
     h->alpha_rb = s->alpha_rb;
     h->seq = s->seq_issued;
-    HIPC(hipMemcpyAsync(s->ctl, h, sizeof(Ctl), hipMemcpyHostToDevice, s->stream));
-    HIPC(hipStreamSynchronize(s->stream));
+    CtlArgs a = ctl_args(s);
+    a.src = on_device(s, s->hy + first);
+    a.dst = s->y + first;
+    a.n = n;
+    a.src2 = on_device(s, s->hsrc);
+    a.dst2 = s->src;
+    a.n2 = sources ? s->n_src : 0;
+    HIPC(launch_ctl(a, s->stream));
     return BILD_OK;
 }
 
@@ -450,12 +476,11 @@ int push_ctl(bild_state* s) {
 int set_alpha(bild_state* s, float fb, float rb) {
     // compare bit patterns so that +-inf and every other value round-trip exactly
     if (std::memcmp(&fb, &s->alpha_fb, 4) == 0 && std::memcmp(&rb, &s->alpha_rb, 4) == 0) return BILD_OK;
-    HIPC(hipStreamSynchronize(s->stream));  // the staging buffer may still be in use by an earlier copy
-    s->halpha[0] = fb;
-    s->halpha[1] = rb;
-    HIPC(hipMemcpyAsync(&s->ctl->alpha_fb, s->halpha, 8, hipMemcpyHostToDevice, s->stream));
     s->alpha_fb = fb;
     s->alpha_rb = rb;
+    CtlArgs a = ctl_args(s);
+    a.thresholds_only = 1;
+    HIPC(launch_ctl(a, s->stream));
     return BILD_OK;
 }
 
@@ -1107,6 +1132,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         g.y = s->y;
         g.ylen_ptr = &s->ctl->y_len;
         g.part = M.part;
+        g.part_ld = M.nparts_cap;
         g.zt = M.zt;
         g.dbg = (s->debug_logits || s->top_p > 0.f) ? M.dbg : nullptr;  // the draw of the sampling variant reads the logits
         g.row_off = 0;
@@ -1123,6 +1149,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
             if (rc) return rc;
         }
         f.part = M.part;
+        f.part_ld = g.part_ld;
         f.nparts = (int)gemm_num_blocks(g);
         f.zt = M.zt;
         f.T = lm_rows;
@@ -1390,17 +1417,16 @@ extern "C" int bild_encode(bild_state* s, const int32_t* src, int n_src) {
     s->n_src = n_src;
     s->len[0] = s->len[1] = 0;
     if (dec_only) {
-        HIPC(hipMemcpyAsync(s->y, src, sizeof(int) * (size_t)n_src, hipMemcpyHostToDevice, s->stream));
+        std::memcpy(s->hy, src, sizeof(int) * (size_t)n_src);
         s->y_len = n_src;
     } else {
-        const int32_t bos = s->pair->m[1]->cfg.bos;
-        HIPC(hipMemcpyAsync(s->src, src, sizeof(int) * (size_t)n_src, hipMemcpyHostToDevice, s->stream));
-        HIPC(hipMemcpyAsync(s->y, &bos, sizeof(int), hipMemcpyHostToDevice, s->stream));
+        std::memcpy(s->hsrc, src, sizeof(int) * (size_t)n_src);
+        s->hy[0] = s->pair->m[1]->cfg.bos;
         s->y_len = 1;
     }
     s->n0 = s->y_len;
     s->draft_start = s->y_len;
-    int rc = push_ctl(s);
+    int rc = push_ctl(s, 0, s->y_len, !dec_only);
     if (rc) return rc;
     if (dec_only) {
         for (int w = 0; w < 2; ++w) {
@@ -1414,8 +1440,14 @@ extern "C" int bild_encode(bild_state* s, const int32_t* src, int n_src) {
             rc = run_encoder(s, 0);
             if (rc) return rc;
         }
+        FinishArgs f;  // the encoder's end is counted like a pass (of no rows), so that it is waited for like one
+        std::memset((void*)&f, 0, sizeof(f));
+        f.ctl = s->ctl;
+        f.mode = 3;
+        f.host_mirror = s->hctl_dev;
+        HIPC(launch_finish(f, s->stream));
+        s->seq_issued += 1;
     }
-    HIPC(hipStreamSynchronize(s->stream));  // the encoder's kernels end with no policy kernel: wait for the stream itself
     rc = pull_ctl(s);
     if (rc) return rc;
     s->encoded = true;
@@ -1438,6 +1470,7 @@ extern "C" int bild_small_step(bild_state* s, float alpha_fb, int32_t* token, in
     if (rc) return rc;
     *token = s->hctl->res_tok;
     *fallback_flag = s->hctl->res_flag & 1;
+    if (!*fallback_flag) s->hy[s->y_len - 1] = *token;
     if (max_prob) *max_prob = s->hctl->res_pmax;
     return BILD_OK;
 }
@@ -1453,13 +1486,11 @@ extern "C" int bild_large_verify(bild_state* s, const int32_t* draft, int n, flo
         const int V = s->pair->m[1]->cfg.vocab;
         for (int i = 0; i < n; ++i)
             if (draft[i] < 0 || draft[i] >= V) return BILD_EINVAL;
-        if (n > 0)
-            HIPC(hipMemcpyAsync(s->y + s->draft_start, draft, sizeof(int) * (size_t)n, hipMemcpyHostToDevice,
-                                s->stream));
+        if (n > 0) std::memcpy(s->hy + s->draft_start, draft, sizeof(int) * (size_t)n);
         s->y_len = s->draft_start + n;
         s->len[0] = std::min(s->len[0], s->draft_start);
         s->len[1] = std::min(s->len[1], s->draft_start - 1);
-        int rc = push_ctl(s);
+        int rc = push_ctl(s, s->draft_start, n);
         if (rc) return rc;
     } else {
         n = s->y_len - s->draft_start;
@@ -1479,8 +1510,8 @@ extern "C" int bild_large_verify(bild_state* s, const int32_t* draft, int n, flo
     const int r = s->hctl->res_r;
     *rollback_pos = r;
     *n_out = r + 1;
-    HIPC(hipMemcpyAsync(out_tokens, s->y + ds, sizeof(int) * (size_t)(r + 1), hipMemcpyDeviceToHost, s->stream));
-    HIPC(hipStreamSynchronize(s->stream));
+    s->hy[ds + r] = s->hctl->res_tok;  // behind the drafts that stand
+    std::memcpy(out_tokens, s->hy + ds, sizeof(int) * (size_t)(r + 1));
     if (nll)
         for (int i = 0; i < n; ++i) nll[i] = (i <= r) ? s->hctl->res_nll[i] : NAN;
     return BILD_OK;
@@ -1517,13 +1548,12 @@ extern "C" int bild_force_tokens(bild_state* s, int first, const int32_t* tokens
     const int V = s->pair->m[1]->cfg.vocab;
     for (int i = 0; i < n; ++i)
         if (tokens[i] < 0 || tokens[i] >= V) return BILD_EINVAL;
-    if (n > 0)
-        HIPC(hipMemcpyAsync(s->y + first, tokens, sizeof(int) * (size_t)n, hipMemcpyHostToDevice, s->stream));
+    if (n > 0) std::memcpy(s->hy + first, tokens, sizeof(int) * (size_t)n);
     s->y_len = first + n;
     s->draft_start = draft_start;
     s->len[0] = std::min(s->len[0], first);
     s->len[1] = std::min(s->len[1], std::min(first, draft_start - 1));
-    return push_ctl(s);
+    return push_ctl(s, first, n);
 }
 
 extern "C" int bild_get_lengths(bild_state* s, int32_t* y_len, int32_t* draft_start, int32_t* len_small,
@@ -1539,10 +1569,7 @@ extern "C" int bild_get_lengths(bild_state* s, int32_t* y_len, int32_t* draft_st
 extern "C" int bild_get_sequence(bild_state* s, int32_t* out, int cap, int32_t* n) {
     if (!s || !out || !n) return BILD_EINVAL;
     if (cap < s->y_len) return BILD_ECAP;
-    if (s->y_len > 0) {
-        HIPC(hipMemcpyAsync(out, s->y, sizeof(int) * (size_t)s->y_len, hipMemcpyDeviceToHost, s->stream));
-        HIPC(hipStreamSynchronize(s->stream));
-    }
+    if (s->y_len > 0) std::memcpy(out, s->hy, sizeof(int) * (size_t)s->y_len);
     *n = s->y_len;
     return BILD_OK;
 }
@@ -1588,11 +1615,7 @@ extern "C" int bild_generate(bild_state* s, const int32_t* src, int n_src, float
     }
     st.n_generated = s->y_len - s->n0;
     *n_out = st.n_generated;
-    if (st.n_generated > 0) {
-        HIPC(hipMemcpyAsync(out, s->y + s->n0, sizeof(int) * (size_t)st.n_generated, hipMemcpyDeviceToHost,
-                            s->stream));
-        HIPC(hipStreamSynchronize(s->stream));
-    }
+    if (st.n_generated > 0) std::memcpy(out, s->hy + s->n0, sizeof(int) * (size_t)st.n_generated);
     if (stats) *stats = st;
     return BILD_OK;
 }
@@ -1618,13 +1641,11 @@ extern "C" int bild_greedy(bild_state* s, int which, const int32_t* src, int n_s
         rc = pull_ctl(s);
         if (rc) return rc;
         last = s->hctl->res_tok;
+        s->hy[s->y_len - 1] = last;
     }
     // leave the state consistent for a following BiLD call: the other model lags, which is allowed
     *n_out = s->y_len - s->n0;
-    if (*n_out > 0) {
-        HIPC(hipMemcpyAsync(out, s->y + s->n0, sizeof(int) * (size_t)*n_out, hipMemcpyDeviceToHost, s->stream));
-        HIPC(hipStreamSynchronize(s->stream));
-    }
+    if (*n_out > 0) std::memcpy(out, s->hy + s->n0, sizeof(int) * (size_t)*n_out);
     return BILD_OK;
 }
 

@@ -94,7 +94,8 @@ struct GemmArgs {
     int vocab;
     const int* y;        // sequence; target of row t is y[*pos_ptr + pos_add + t + 1] if below *ylen_ptr
     const int* ylen_ptr;
-    StatPart* part;      // [gridDim.x][kMaxRows]
+    StatPart* part;      // [rows][part_ld]: the partials of a row side by side, one per workgroup
+    int part_ld;
     float* zt;           // [kMaxRows] logit of each row's target
     float* dbg;          // nullable [T][vocab] full logits (tests only)
     int row_off;         // row index of x row 0 within the pass (for part / zt / dbg / targets)
@@ -227,8 +228,8 @@ struct RowCopyArgs {
 struct FinishArgs {
     Ctl* ctl;
     int* y;
-    const StatPart* part;
-    int nparts;
+    const StatPart* part;  // [rows][part_ld]
+    int nparts, part_ld;
     const float* zt;
     int T;       // rows that went through the LM head
     int row_off; // first such row within the pass
@@ -331,6 +332,17 @@ hipError_t launch_embed(const EmbedArgs& a, int dtype, hipStream_t st);
 // table[pos][k] = sin / cos of pos * 10000^(-2 floor(k/2) / d) (k even / odd), evaluated in double precision as embed_kernel does
 hipError_t launch_pe_table(float* table, int positions, int d, hipStream_t st);
 hipError_t launch_finish(const FinishArgs& a, hipStream_t st);
+// Control words and tokens from the host, as the arguments of one small kernel (the tokens from mapped pinned memory).
+struct CtlArgs {
+    Ctl* ctl;
+    int head[8];              // y_len .. alpha_rb
+    int seq;
+    int thresholds_only;      // 1: only head[6], head[7]
+    const int *src, *src2;    // tokens: n from src to dst, n2 from src2 to dst2
+    int *dst, *dst2;
+    int n, n2;
+};
+hipError_t launch_ctl(const CtlArgs& a, hipStream_t st);
 // sampling variant with the threshold rule: the same result as launch_finish, the draw spread over the chip (seven launches)
 hipError_t launch_finish_draw(const FinishArgs& a, hipStream_t st);
 constexpr int kFinishDrawStages = 7;

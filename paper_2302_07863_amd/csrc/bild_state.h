@@ -102,7 +102,8 @@ struct bild_state {
     Ctl* hctl = nullptr;  // pinned host mirror of the control block, written by the policy kernel
     int seq_issued = 0;   // passes with a policy kernel enqueued so far (the device counts them in Ctl::seq)
     Ctl* hctl_dev = nullptr;  // the same buffer as the device sees it
-    float* halpha = nullptr;  // pinned staging for threshold updates
+    int* hy = nullptr;        // pinned copy of y on the host: every token the host sets or a pass reports goes into it
+    int* hsrc = nullptr;      // pinned copy of src
     float alpha_fb = -1.f, alpha_rb = -1.f;  // thresholds currently in the device control block
     bool use_graphs = true;
     int ksplit_max_d = 2048;      // ... of models up to this wide (7B-shaped small model, 2048 wide: 0.729 -> 0.717 ms per step)

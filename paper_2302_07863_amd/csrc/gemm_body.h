@@ -852,7 +852,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const int vblock, c
             }
             StatPart o;
             o.m = r.m; o.s = r.s; o.idx = r.idx; o.pad = 0;
-            a.part[(size_t)vblock * kMaxRows + a.row_off + tid] = o;
+            a.part[(size_t)(a.row_off + tid) * a.part_ld + vblock] = o;
         }
     }
 }

@@ -16,7 +16,7 @@ using namespace bild;
 namespace {
 
 // Scratch layout (bytes): [0, 256) one int (number of target slots); [256, 512) logits of the targets, one float per
-// row; [512, ...) partial statistics, StatPart[workgroups][kMaxRows].
+// row; [512, ...) partial statistics, StatPart[rows][workgroups].
 constexpr size_t kHdrBytes = 512;
 constexpr size_t kStaticScratchBytes = (size_t)4 << 20;  // 4 MiB
 constexpr int kStaticMaxParts = (int)((kStaticScratchBytes - kHdrBytes) / (sizeof(StatPart) * kMaxRows));
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void head_stats_merge_kernel(const MergeArgs a
         float m = -INFINITY, s = 0.f;
         int idx = 0x7FFFFFFF;
         for (int p = lane; p < a.nparts; p += 64) {
-            const StatPart sp = a.part[(size_t)p * kMaxRows + t];
+            const StatPart sp = a.part[(size_t)t * a.nparts + p];
             const float mn = fmaxf(m, sp.m);
             const float sa = (m == -INFINITY) ? 0.f : s * expf(m - mn);
             const float sb = (sp.m == -INFINITY) ? 0.f : sp.s * expf(sp.m - mn);
@@ -117,6 +117,7 @@ GemmArgs head_gemm(const bild_model* m, const float* x, int rows, const int32_t*
     g.zt = (float*)((char*)scr + 256);
     g.part = (StatPart*)((char*)scr + kHdrBytes);
     gemm_pick_shape(g, c.dtype);
+    g.part_ld = (int)gemm_num_blocks(g);
     return g;
 }
 

@@ -142,6 +142,12 @@ __device__ __forceinline__ Stat stat_shfl_xor(const Stat& a, int o) {
     return b;
 }
 
+// Eight partials of a row per lane, requested at once.
+__device__ __forceinline__ void load_parts(StatPart (&sp)[8], const StatPart* row, int p0, int end) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) sp[k] = row[max(min(p0 + k * 64, end - 1), 0)];
+}
+
 __device__ __forceinline__ float gelu_tanh_f(float u) {
     // tanh(y) = 1 - 2 / (1 + e^(2y)) (saturates correctly at both ends; near zero the result is added to 1)
     const float y = 0.7978845608028654f * (u + 0.044715f * u * u * u);

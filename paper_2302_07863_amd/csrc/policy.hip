@@ -16,7 +16,7 @@ namespace bild {
 //   mode 4  measurement: merge the statistics, commit nothing
 // =====================================================================================
 // LDS use of finish_body (from the start of the workgroup's LDS)
-constexpr int kFinishLds = 4 * kMaxRows * 4;
+constexpr int kFinishLds = 3 * kMaxRows * 4;
 // LDS of the sampling variant behind that: 16 waves x 16 bins, 1024 per-thread masses, a few scalars
 constexpr int kDrawLds = 16 * 16 * 4 + 1024 * 4 + 128;
 
@@ -219,58 +219,54 @@ __device__ __forceinline__ int nucleus_draw(const float* __restrict__ z, int V, 
 // least as many waves as rows, every row gets nwv / T waves, each merging a contiguous share of the row's partials
 // (lanes stride through it, eight loads in flight per lane), so that a single row with two thousand partials (250 112
 // ids) costs one trip to memory instead of four; the shares are then joined in a fixed order.  More rows than waves: the
-// rows are dealt to the waves.  Ends with a barrier.
-__device__ __forceinline__ void merge_partials(const FinishArgs& a, float* rm, float* rsum, int* ridx) {
+// rows are dealt to the waves.  A row's partials lie side by side: 16 bytes each, where one slot per row of every workgroup
+// had a workgroup fetch a line of 128 bytes for each (1004 partials of one row: 2.6 us of the compute unit's bandwidth).
+// `first` runs between the first requests and their use.  Ends with a barrier.
+template <class First>
+__device__ __forceinline__ void merge_partials(const FinishArgs& a, float* rm, float* rsum, int* ridx, First&& first) {
     __shared__ StatPart share[16];  // [row * wpr + share] (at most 16 waves)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwv = blockDim.x >> 6;
-    auto merge_range = [&](int t, int p_begin, int p_end) {
+    const int wpr = max(nwv / a.T, 1);              // waves per row
+    const int per = (a.nparts + wpr - 1) / wpr;     // partials per share
+    const int t0 = wave / wpr, c = wave - t0 * wpr;
+    const int begin = min(c * per, a.nparts), end = min(begin + per, a.nparts);
+    StatPart sp[8];
+    load_parts(sp, a.part + (size_t)(a.row_off + min(t0, a.T - 1)) * a.part_ld, begin + lane, end);
+    first();
+    for (int t = t0; t < a.T; t += nwv) {           // (more than one turn only with one wave per row)
+        const StatPart* row = a.part + (size_t)(a.row_off + t) * a.part_ld;
         Stat r = stat_neutral();
-        for (int p0 = p_begin + lane; p0 < p_end; p0 += 64 * 8) {
-            StatPart sp[8];
+        for (int p0 = begin + lane;; p0 += 64 * 8) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                sp[k] = a.part[(size_t)min(p0 + k * 64, p_end - 1) * kMaxRows + a.row_off + t];
+            for (int k = 0; k < 8; ++k)  // (pairwise, in the order of the partials)
+                if (p0 + k * 64 < end) r = stat_merge(r, Stat{sp[k].m, sp[k].s, sp[k].idx});
+            if (__builtin_amdgcn_readfirstlane(p0) + 64 * 8 >= end) break;
+            load_parts(sp, row, p0 + 64 * 8, end);
+        }
+        if (t + nwv < a.T) load_parts(sp, row + (size_t)nwv * a.part_ld, begin + lane, end);
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (p0 + k * 64 < p_end) r = stat_merge(r, Stat{sp[k].m, sp[k].s, sp[k].idx});
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) r = stat_merge(r, stat_shfl_xor(r, o));
-        return r;
-    };
-    if (a.T <= nwv) {
-        const int wpr = nwv / a.T;                      // waves per row
-        const int per = (a.nparts + wpr - 1) / wpr;     // partials per share
-        const int t = wave / wpr, c = wave - t * wpr;
-        if (t < a.T) {
-            const int p_begin = min(c * per, a.nparts), p_end = min(p_begin + per, a.nparts);
-            const Stat r = merge_range(t, p_begin, p_end);  // (an empty share stays neutral)
-            if (lane == 0) {
-                StatPart sp;
-                sp.m = r.m; sp.s = r.s; sp.idx = r.idx; sp.pad = 0;
-                share[wave] = sp;
-            }
-        }
-        __syncthreads();
-        if (tid < a.T) {
-            Stat r = stat_neutral();
-            for (int c2 = 0; c2 < wpr; ++c2) {
-                const StatPart sp = share[tid * wpr + c2];
-                r = stat_merge(r, Stat{sp.m, sp.s, sp.idx});
-            }
-            rm[tid] = r.m;
-            rsum[tid] = r.s;
-            ridx[tid] = r.idx;
-        }
-    } else {
-        for (int t = wave; t < a.T; t += nwv) {
-            const Stat r = merge_range(t, 0, a.nparts);
-            if (lane == 0) {
+        for (int o = 32; o > 0; o >>= 1) r = stat_merge(r, stat_shfl_xor(r, o));  // (an empty share stays neutral)
+        if (lane == 0) {
+            if (wpr == 1) {
                 rm[t] = r.m;
                 rsum[t] = r.s;
                 ridx[t] = r.idx;
+            } else {
+                share[wave] = StatPart{r.m, r.s, r.idx, 0};
             }
         }
+    }
+    __syncthreads();
+    if (wpr == 1) return;
+    if (tid < a.T) {
+        Stat r = stat_neutral();
+        for (int c2 = 0; c2 < wpr; ++c2) {
+            const StatPart q = share[tid * wpr + c2];
+            r = stat_merge(r, Stat{q.m, q.s, q.idx});
+        }
+        rm[tid] = r.m;
+        rsum[tid] = r.s;
+        ridx[tid] = r.idx;
     }
     __syncthreads();
 }
@@ -286,10 +282,12 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int 
     Ctl* c = a.ctl;
     // the control words the policy needs, requested now (nothing in this kernel writes them before they are used): their
     // trip from memory overlaps with the partials' instead of following it
-    const int c_ylen = c->y_len, c_ds = c->draft_start, c_nmax = c->n_max, c_len0 = c->len[0], c_lenw = c->len[a.which];
+    const int c_ylen = c->y_len, c_ds = c->draft_start, c_nmax = c->n_max, c_len0 = c->len[0], c_len1 = c->len[1], c_lenw = c->len[a.which];
     const float c_afb = c->alpha_fb, c_arb = c->alpha_rb;
     const int c_seq = c->seq;
-    if (a.mode != 3) merge_partials(a, rm, rsum, ridx);
+    float z_draft = 0.f;
+    if (a.mode != 3)
+        merge_partials(a, rm, rsum, ridx, [&] { if (a.mode == 1) z_draft = a.zt[a.row_off + min(lane, max(a.T - 2, 0))]; });
     // Sampling variant: the token that will be committed is drawn by the whole workgroup from the row the
     // policy selects (the last row of a step; row r of a review), at the position it will occupy.
     int drawn = drawn_in;
@@ -376,88 +374,80 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int 
             }
         }
     }
-    // The results go to the control block and, for the caller, to its mirror in pinned host memory: every changed word
-    // is written to both from here (the unchanged words of the mirror are the host's own); the pass counter goes last,
-    // behind a system-wide fence, so that a host that sees the new count also sees every other word.
-    Ctl* hm = a.host_mirror;
-    float* nlls = (float*)(ridx + kMaxRows);  // [kMaxRows] (mode 1)
-    if (a.mode == 1 && tid < a.T - 1) nlls[tid] = (rm[tid] + logf(rsum[tid])) - a.zt[a.row_off + tid];  // -ln p_L(draft)
-    if (a.mode != 3 && tid < a.T) {
-        c->res_rowtok[tid] = ridx[tid];
-        if (hm) ((volatile int*)hm->res_rowtok)[tid] = ridx[tid];
-    }
-    __syncthreads();
-    if (a.mode == 1 && tid < a.T - 1 && (r_given < 0 || tid <= r_given)) {
-        c->res_nll[tid] = nlls[tid];
-        if (hm) ((volatile float*)hm->res_nll)[tid] = nlls[tid];
-    }
-    if (tid == 0) {
-        const int w = a.which;
-        const int y_len = c_ylen, ds = c_ds, n_max = c_nmax;
-        int n_ylen = y_len, n_ds = ds, n_len0 = c_len0, n_lenw = c_lenw;
-        int res_tok = 0, res_flag = 0, res_r = 0, res_n = 0;
-        float res_pmax = 0.f;
-        if (a.mode == 3) {
-            n_lenw = c_lenw + a.rows_consumed;
-        } else if (a.mode == 0 || a.mode == 2) {
-            const int tok = drawn >= 0 ? drawn : ridx[a.T - 1];
-            const float pmax = 1.f / rsum[a.T - 1];
-            const bool low = (a.mode == 0) && (pmax < c_afb);
-            const bool forced = (a.mode == 0) && n_max > 0 && (y_len - ds) >= n_max;
-            const bool fb = low || forced;
-            n_lenw = c_lenw + a.rows_consumed;
-            if (!fb && y_len < a.y_cap) {
-                a.y[y_len] = tok;
-                n_ylen = y_len + 1;
-                if (a.mode == 2) n_ds = y_len + 1;
-            }
-            res_tok = tok;
-            res_flag = (fb ? 1 : 0) | ((forced && !low) ? 2 : 0);
-            res_pmax = pmax;
-        } else if (a.mode == 1) {  // review of n = T - 1 drafts
-            const int n = a.T - 1;
-            const float alpha = c_arb;
-            int r = n;
-            if (r_given >= 0) {
-                r = r_given;  // (the rejection rule decided above)
-            } else {
-                for (int i = 0; i < n; ++i)
-                    if (nlls[i] > alpha) {
-                        r = i;
-                        break;
-                    }
-            }
-            const int tok = drawn >= 0 ? drawn : ridx[r];
-            a.y[ds + r] = tok;
-            n_ylen = ds + r + 1;
-            n_lenw = ds + r;            // (w == 1)
-            n_len0 = min(c_len0, ds + r);
-            n_ds = ds + r + 1;
-            res_r = r;
-            res_n = n;
-            res_tok = tok;
-            res_pmax = 1.f / rsum[r];
-        }
-        if (a.mode != 4) {
-            const int l0 = w == 0 ? n_lenw : n_len0, l1 = w == 1 ? n_lenw : c->len[1];
-            c->y_len = n_ylen; c->draft_start = n_ds; c->len[0] = l0; c->len[1] = l1;
-            c->res_tok = res_tok; c->res_flag = res_flag; c->res_r = res_r; c->res_n = res_n; c->res_pmax = res_pmax;
-            if (hm) {
-                volatile Ctl* v = hm;
-                v->y_len = n_ylen; v->draft_start = n_ds; v->len[0] = l0; v->len[1] = l1;
-                v->res_tok = res_tok; v->res_flag = res_flag; v->res_r = res_r; v->res_n = res_n; v->res_pmax = res_pmax;
-            }
+    // From here on wave 0 alone, lane t with row t: no barrier, no trip through LDS.  The results go to the control block and,
+    // for the caller, to its mirror in pinned host memory (the words not written are the host's own).  The mirror is written
+    // past the caches and the pass counter once those stores have been acknowledged, so that a host that sees the new count also
+    // sees every other word.  (Volatile stores, one word after the other, each waited for its acknowledgement over the host
+    // link, and a system-wide fence writes the L2 back besides: 5 us for this kernel and 10 us for a wide one.)
+    if (tid >= 64) return;
+    const int w = a.which, n = a.T - 1;
+    Ctl* v = a.host_mirror;
+    const __amdgpu_buffer_rsrc_t mirror = make_rsrc(v, v ? sizeof(Ctl) : 0);  // (none: the stores are out of bounds and dropped)
+    auto tell = [&](int word, int off) { __builtin_amdgcn_raw_buffer_store_b32((unsigned)word, mirror, off, 0, 17); };  // sc0 sc1
+    const int t = min(lane, max(n, 0));
+    int row_tok = 0;
+    float nll = 0.f, pmax = 0.f;
+    if (a.mode != 3) {
+        row_tok = ridx[t];
+        pmax = 1.f / rsum[t];
+        if (lane <= n) {
+            c->res_rowtok[lane] = row_tok;
+            tell(row_tok, (int)offsetof(Ctl, res_rowtok) + lane * 4);
         }
     }
-    if (hm) {
+    int n_ylen = c_ylen, n_ds = c_ds, n_len0 = c_len0, n_lenw = c_lenw + a.rows_consumed;
+    int res_tok = 0, res_flag = 0, res_r = 0, res_n = 0, y_at = -1;
+    float res_pmax = 0.f;
+    if (a.mode == 0 || a.mode == 2) {
+        res_tok = drawn >= 0 ? drawn : __builtin_amdgcn_readlane(row_tok, n);
+        res_pmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pmax), n));
+        const bool low = a.mode == 0 && res_pmax < c_afb;
+        const bool forced = a.mode == 0 && c_nmax > 0 && (c_ylen - c_ds) >= c_nmax;
+        if (!low && !forced && c_ylen < a.y_cap) {
+            y_at = c_ylen;
+            n_ylen = c_ylen + 1;
+            if (a.mode == 2) n_ds = c_ylen + 1;
+        }
+        res_flag = (low || forced ? 1 : 0) | ((forced && !low) ? 2 : 0);
+    } else if (a.mode == 1) {  // review of n drafts: -ln p_L(draft) of each against the threshold
+        nll = (rm[t] + logf(rsum[t])) - z_draft;
+        int r = r_given;       // (the rejection rule decided above)
+        if (r < 0) {
+            const unsigned long long over = __builtin_amdgcn_ballot_w64(lane < n && nll > c_arb);
+            r = over ? (int)__builtin_ctzll(over) : n;
+        }
+        if (lane < n && (r_given < 0 || lane <= r)) {
+            c->res_nll[lane] = nll;
+            tell(__float_as_int(nll), (int)offsetof(Ctl, res_nll) + lane * 4);
+        }
+        res_tok = drawn >= 0 ? drawn : __builtin_amdgcn_readlane(row_tok, r);
+        res_pmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pmax), r));
+        y_at = c_ds + r;
+        n_ylen = n_ds = c_ds + r + 1;
+        n_lenw = c_ds + r;     // (w == 1)
+        n_len0 = min(c_len0, c_ds + r);
+        res_r = r;
+        res_n = n;
+    }
+    const int l0 = w == 0 ? n_lenw : n_len0, l1 = w == 1 ? n_lenw : c_len1;
+    const int sq = c_seq + 1;
+    if (a.mode != 4) {
+        if (lane == 0 && y_at >= 0) a.y[y_at] = res_tok;
+        static_assert(offsetof(Ctl, res_tok) == 32 && offsetof(Ctl, res_pmax) == 48, "words 0 .. 3 and 8 .. 12");
+        const int words[13] = {n_ylen, n_ds, l0, l1, 0, 0, 0, 0, res_tok, res_flag, res_r, res_n, __float_as_int(res_pmax)};
+        int mine = 0;  // lane i has word i: one store
+#pragma unroll
+        for (int i = 0; i < 13; ++i) mine = lane == i ? words[i] : mine;
+        if (lane < 13 && (lane < 4 || lane >= 8)) {
+            tell(mine, lane * 4);
+            ((int*)c)[lane] = mine;
+        }
+    }
+    if (v) {
         static_assert(offsetof(Ctl, seq) == sizeof(Ctl) - 4, "seq must be the last word of the control block");
-        __threadfence_system();
-        __syncthreads();
-        if (tid == 0) {
-            const int sq = c_seq + 1;
-            c->seq = sq;
-            ((volatile Ctl*)hm)->seq = sq;
-        }
+        if (lane == 0) c->seq = sq;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) tell(sq, (int)offsetof(Ctl, seq));
     }
 }
 
@@ -588,7 +578,7 @@ __global__ __launch_bounds__(1024) void draw_select_kernel(const FinishArgs a) {
     DrawWs* ws = a.dws;
     u64* hist = &ws->hist[0][0];
     for (int i = tid; i < 4 * 256; i += blockDim.x) hist[i] = 0ull;
-    merge_partials(a, rm, rsum, ridx);
+    merge_partials(a, rm, rsum, ridx, [] {});
     if (tid < a.T) {
         StatPart sp;
         sp.m = rm[tid]; sp.s = rsum[tid]; sp.idx = ridx[tid]; sp.pad = 0;
@@ -745,6 +735,28 @@ __global__ __launch_bounds__(256) void finish_draw_kernel(const FinishArgs a, co
     finish_body<false>(a, lds, (int)sc[2]);
 }
 
+// What the host changes between passes.  As a kernel's arguments it costs its enqueueing, about 3 us and no wait; as a copy
+// (pageable or pinned) with the synchronization that keeps its source valid it cost 15 us, and 22 us more per piece of tokens.
+// The tokens come over the host link: one per thread, so that all of them cost one trip.
+__global__ __launch_bounds__(256) void ctl_kernel(const CtlArgs a) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < a.n) a.dst[i] = a.src[i];
+    else if (i < a.n + a.n2) a.dst2[i - a.n] = a.src2[i - a.n];
+    if (blockIdx.x == 0) {
+        int* c = (int*)a.ctl;
+        constexpr int words = sizeof(Ctl) / 4;
+        static_assert(offsetof(Ctl, alpha_rb) == 28 && words <= 256, "one word per thread");
+        if (threadIdx.x < words && (!a.thresholds_only || threadIdx.x == 6 || threadIdx.x == 7))
+            c[threadIdx.x] = threadIdx.x < 8 ? a.head[threadIdx.x & 7] : threadIdx.x == words - 1 ? a.seq : 0;
+    }
+}
+
+hipError_t launch_ctl(const CtlArgs& a, hipStream_t st) {
+    if (!a.ctl || a.n < 0 || a.n2 < 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(ctl_kernel, dim3((a.n + a.n2 + 255) / 256 + (a.n + a.n2 == 0)), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_finish_draw(const FinishArgs& a, hipStream_t st) {
     if (!(a.top_p > 0.f) || a.mode > 2 || a.accept_mode != 0 || !a.logits || !a.u || !a.dws || a.vocab < 1 || a.T < 1 || a.T > kMaxRows)
         return hipErrorInvalidValue;
@@ -758,7 +770,7 @@ hipError_t launch_finish_draw(const FinishArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(draw_mass_kernel, dim3(ns), dim3(256), 0, st, a);
     FinishArgs f = a;  // the commit merges one "partial" per row: the statistics draw_select_kernel left
     f.part = a.dws->merged;  // (address arithmetic only: dws is a device pointer)
-    f.nparts = 1;
+    f.nparts = f.part_ld = 1;
     hipLaunchKernelGGL(finish_draw_kernel, dim3(1), dim3(256), 0, st, f, ns);
     return hipGetLastError();
 }
