@@ -3,6 +3,7 @@
 #pragma once
 #include <array>
 #include <map>
+#include <mutex>
 #include <vector>
 
 #include "bild_internal.h"
@@ -27,6 +28,54 @@ struct LayerW {
     TMat win, wout;
 };
 
+// Scratch buffers of bild_head_stats between its calls: whoever needs one takes it (calls of several threads take several),
+// at most kKept wait here, and they are freed with the model.
+struct HeadScratch {
+    void* p = nullptr;
+    size_t bytes = 0;
+    int dev = -1;
+};
+class HeadPool {
+    static constexpr int kKept = 4;
+    std::mutex mu;
+    std::vector<HeadScratch> kept;
+
+public:
+    HeadScratch take(size_t bytes) {
+        HeadScratch b;
+        if (hipGetDevice(&b.dev) != hipSuccess) return b;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            for (size_t i = 0; i < kept.size(); ++i)
+                if (kept[i].dev == b.dev && kept[i].bytes >= bytes) {
+                    b = kept[i];
+                    kept.erase(kept.begin() + i);
+                    return b;
+                }
+        }
+        b.bytes = bytes;
+        if (hipMalloc(&b.p, bytes) != hipSuccess) b.p = nullptr;
+        return b;
+    }
+    void give(const HeadScratch& b) {  // (no kernel uses it any more); the smallest of too many goes
+        HeadScratch out = b;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            kept.push_back(b);
+            if (kept.size() <= (size_t)kKept) return;
+            size_t least = 0;
+            for (size_t i = 1; i < kept.size(); ++i)
+                if (kept[i].bytes < kept[least].bytes) least = i;
+            out = kept[least];
+            kept.erase(kept.begin() + least);
+        }
+        (void)hipFree(out.p);
+    }
+    ~HeadPool() {
+        for (HeadScratch& b : kept) (void)hipFree(b.p);
+    }
+};
+
 struct bild_model {
     bild_model_config cfg;
     TMat emb, head;
@@ -37,6 +86,7 @@ struct bild_model {
     std::vector<LayerW> enc, dec;
     TMat cwkv_all;                   // the cross K/V projections of all decoder layers side by side (dec[l].cwkv points into it)
     std::vector<void*> allocs;
+    mutable HeadPool head_pool;
     size_t device_bytes = 0;
     int inner() const { return cfg.n_heads * cfg.d_head; }
     int esz() const { return cfg.dtype == BILD_DT_BF16 ? 2 : 4; }

@@ -142,10 +142,35 @@ __device__ __forceinline__ Stat stat_shfl_xor(const Stat& a, int o) {
     return b;
 }
 
-// Eight partials of a row per lane, requested at once.
+// One wave's merge of the partials [begin, end) of a row: eight requests per lane in flight, the maximum first and then all
+// exponentials side by side (a chain of pairwise merges is as long as its number of exponentials).
+__device__ __forceinline__ void take_parts(Stat& r, const StatPart (&sp)[8], int p0, int end) {
+    float m[8], bm = r.m;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        m[k] = p0 + k * 64 < end ? sp[k].m : -INFINITY;
+        if (m[k] > bm || (m[k] == bm && sp[k].idx < r.idx)) r.idx = sp[k].idx;  // (equal maxima: the lower id)
+        bm = fmaxf(bm, m[k]);
+    }
+    const float base = bm == -INFINITY ? 0.f : bm;
+    float s = r.s * fexp(r.m - base);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += sp[k].s * fexp(m[k] - base);
+    r.m = bm;
+    r.s = s;
+}
 __device__ __forceinline__ void load_parts(StatPart (&sp)[8], const StatPart* row, int p0, int end) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) sp[k] = row[max(min(p0 + k * 64, end - 1), 0)];
+}
+__device__ __forceinline__ Stat join_parts(const Stat& r) {
+    Stat o;
+    o.m = wave_max(r.m);
+    o.s = wave_sum(r.s * fexp(r.m - (o.m == -INFINITY ? 0.f : o.m)));
+    o.idx = 0x7FFFFFFF;
+    for (unsigned long long at = __builtin_amdgcn_ballot_w64(r.m == o.m); at; at &= at - 1)  // (one lane, but for ties)
+        o.idx = min(o.idx, __builtin_amdgcn_readlane(r.idx, (int)__builtin_ctzll(at)));
+    return o;
 }
 
 __device__ __forceinline__ float gelu_tanh_f(float u) {
