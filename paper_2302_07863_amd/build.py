@@ -20,6 +20,7 @@ UNITS = [
     ("gemm_pre.hip", "gemm_pre.o", []),
     ("gemm_dense.hip", "gemm_dense.o", []),
     ("gemm_tile.hip", "gemm_tile.o", []),
+    ("pass_kernel.hip", "pass_kernel.o", []),
     ("attn_tile.hip", "attn_tile.o", []),
     ("attention.hip", "attention.o", []),
     ("policy.hip", "policy.o", []),

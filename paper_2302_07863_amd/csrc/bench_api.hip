@@ -71,6 +71,7 @@ extern "C" int bild_bench_pass(bild_state* s, int which, int rows, int reps, flo
     for (int i = 0; i < reps && rc == BILD_OK; ++i) rc = run_pass(s, w, rows, rows, 4);
     if (rc == BILD_OK && hipEventRecord(e1, s->stream) != hipSuccess) rc = BILD_EHIP;
     if (rc == BILD_OK && hipEventSynchronize(e1) != hipSuccess) rc = BILD_EHIP;
+    end_turn(s);
     float ms = 0.f;
     if (rc == BILD_OK && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = BILD_EHIP;
     (void)hipEventDestroy(e0);
@@ -96,7 +97,7 @@ extern "C" int bild_bench_gemm(bild_state* s, int which, int rows, int reps, flo
     s->gemm_count = s->gemm_bytes = 0;
     const bool graphs = s->use_graphs;
     s->use_graphs = false;
-    rc = decoder_pass(s, w, rows, rows, 4, key_bucket(s->len[w] + rows));  // count the launches of one pass
+    rc = decoder_pass(s, w, rows, rows, 4, key_bucket(s->len[w] + rows), false);  // count the launches of one pass
     s->use_graphs = graphs;
     *launches = s->gemm_count;
     *bytes = s->gemm_bytes;

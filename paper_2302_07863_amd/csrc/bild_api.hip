@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <map>
@@ -261,9 +262,33 @@ extern "C" int bild_pair_destroy(bild_pair* p) {
 }
 
 // ======================================================================= state
+namespace {
+
+// A pass kernel's workgroups wait for each other, so all of them have to be on the chip: two such passes at a time could keep
+// half of each other's out.  One state per device has the turn, from the launch of its pass until it has seen the result;
+// who does not get it runs the pass as separate kernels.
+constexpr int kMaxDevices = 64;
+std::atomic<bool> g_turn[kMaxDevices];
+
+bool take_turn(bild_state* s) {
+    if (s->has_turn) return true;
+    bool free = false;
+    s->has_turn = s->device < kMaxDevices && g_turn[s->device].compare_exchange_strong(free, true, std::memory_order_acquire);
+    return s->has_turn;
+}
+
+}  // namespace
+
+void bild::end_turn(bild_state* s) {
+    if (!s->has_turn) return;
+    s->has_turn = false;
+    g_turn[s->device].store(false, std::memory_order_release);
+}
+
 extern "C" int bild_state_destroy(bild_state* s) {
     if (!s) return BILD_EINVAL;
     if (s->stream) (void)hipStreamSynchronize(s->stream);
+    end_turn(s);
     for (void* p : s->allocs) (void)hipFree(p);
     for (void* p : s->host_allocs) (void)hipHostFree(p);
     for (hipEvent_t e : s->prof_ev) (void)hipEventDestroy(e);
@@ -326,6 +351,8 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     {
         const char* ng = std::getenv("BILD_NO_GRAPH");
         s->use_graphs = !(ng && ng[0] == '1');
+        if (const char* ok = std::getenv("BILD_ONE_KERNEL")) s->one_kernel = ok[0] != '0';  // tests and measurements
+        if (const char* sp = std::getenv("BILD_PASS_SPINS")) s->pass_spins = std::atoi(sp);  // tests
         if (const char* pm = std::getenv("BILD_PRE_MIN_ROWS")) s->pre_min_rows = std::atoi(pm);  // experiments; > 32 turns the planes off
         if (const char* fa = std::getenv("BILD_FUSE_ATTN")) s->fuse_attn = fa[0] != '0';      // experiments / tests
         if (const char* fk = std::getenv("BILD_FUSE_MAX_KV")) s->fuse_max_kv = std::atoi(fk);
@@ -335,6 +362,12 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
     const int positions = std::max(s->cap_len, s->cap_src);
+    int cus = 0;
+    if (hipGetDevice(&s->device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess) {
+        bild_state_destroy(s);
+        return BILD_EHIP;
+    }
+    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * kPassSyncWords, true);
     for (int w = 0; w < 2; ++w) {
         ModelState& M = s->ms[w];
         const bild_model* m = p->m[w];
@@ -374,6 +407,11 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             want(M.ab, sizeof(uint16_t) * 2 * kMaxRows * I);
             want(M.hb, sizeof(uint16_t) * 2 * kMaxRows * F);
             want(M.ssq, sizeof(float) * (kMaxSsqParts + 8) * kMaxRows);
+            M.pass_groups = s->one_kernel && m->cfg.pos != BILD_POS_ROPE ? pass_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), cus) : 0;
+            if (M.pass_groups) {
+                want(M.pass_layers, sizeof(PassLayer) * L);
+                want(M.pass_scratch, L * (size_t)pass_plan(kPassRows, (int)d, (int)I, (int)F).layer);
+            }
         }
         M.nparts_cap = m->head.tn + 1;  // at most one partial per feature tile
         want(M.part, sizeof(StatPart) * (size_t)M.nparts_cap * kMaxRows);
@@ -420,6 +458,22 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         s->ms[0].vcache = s->ms[1].vcache;
         s->ms[0].ck = s->ms[1].ck;
         s->ms[0].cv = s->ms[1].cv;
+    }
+    std::vector<PassLayer> layers[2];
+    for (int w = 0; w < 2 && e == hipSuccess; ++w) {
+        ModelState& M = s->ms[w];
+        if (!M.pass_groups) continue;
+        const size_t kv = (size_t)s->cap_len * M.m->inner() * M.m->esz(), ckv = (size_t)s->cap_src * M.m->inner() * M.m->esz();
+        for (size_t l = 0; l < M.m->dec.size(); ++l) {
+            const LayerW& W = M.m->dec[l];
+            PassLayer q = {W.wqkv.w, W.wo.w, W.cwq.w, W.cwo.w, W.win.w, W.wout.w, W.ln1, W.lnc, W.ln2, M.kcache + l * kv, M.vcache + l * kv, nullptr, nullptr};
+            if (M.m->cfg.cross_attn) {
+                q.ck = M.ck + l * ckv;
+                q.cv = M.cv + l * ckv;
+            }
+            layers[w].push_back(q);
+        }
+        e = hipMemcpyAsync(M.pass_layers, layers[w].data(), sizeof(PassLayer) * layers[w].size(), hipMemcpyHostToDevice, s->stream);
     }
     if (e != hipSuccess || hipStreamSynchronize(s->stream) != hipSuccess) {
         bild_state_destroy(s);
@@ -488,6 +542,7 @@ int set_alpha(bild_state* s, float fb, float rb) {
 // counter is polled first (the kernel writes it last, behind a system-wide fence): that sees the result a few
 // microseconds before the stream's completion reaches the host.  If the count does not arrive in time (a failed
 // launch) the stream is waited for as usual and the two counts are brought together again.
+constexpr int kPassFailed = 1;  // (never leaves this file)
 int pull_ctl(bild_state* s) {
     bool seen = false;
     {
@@ -506,6 +561,8 @@ int pull_ctl(bild_state* s) {
         HIPC(hipStreamSynchronize(s->stream));
         s->seq_issued = __atomic_load_n(&s->hctl->seq, __ATOMIC_ACQUIRE);
     }
+    end_turn(s);
+    if (s->hctl->res_flag & kFlagFailed) return kPassFailed;
     s->y_len = s->hctl->y_len;
     s->draft_start = s->hctl->draft_start;
     s->len[0] = s->hctl->len[0];
@@ -1094,7 +1151,8 @@ namespace bild {
 // One decoder pass of model w over rows y[len .. len+T): embed, layers, and (lm_rows > 0)
 // the LM head over the last lm_rows rows followed by the policy `mode`; lm_rows == 0
 // only advances the cache (catch-up / prefill).
-int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hint) {
+// `one`: as the pass kernel (takes_one_kernel).
+int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hint, bool one) {
     ModelState& M = s->ms[w];
     const bild_model* m = M.m;
     const bild_model_config& c = m->cfg;
@@ -1104,7 +1162,31 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     int xb_parts = 0;  // > 0: the final hidden state also sits in M.xb as bf16 planes (times the final norm's gain)
     float* xfin = M.x;  // the residual stream after the last layer ...
     bool parts = false; // ... to which the partial results in M.px are still to be added (split FFN output projection)
-    if (dt == BILD_DT_BF16 && T > kMaxRows) {
+    if (one) {
+        const int trunk = s->pair->trunk_layers, layer0 = w == 1 ? trunk : 0;
+        PassArgs p;
+        std::memset((void*)&p, 0, sizeof(p));
+        p.layers = M.pass_layers + layer0;
+        p.n_layers = c.n_dec_layers - layer0;
+        p.T = T; p.d = d; p.heads = c.n_heads; p.I = m->inner(); p.F = c.d_ff; p.act = c.act; p.cross = c.cross_attn;
+        p.emb = layer0 ? nullptr : m->emb.w;
+        p.tokens = s->y;
+        p.pe = M.pe;
+        p.x_in = s->trunk_x;
+        p.vocab = c.vocab; p.tie_shift = c.tie_shift; p.embed_scale = c.embed_scale;
+        p.len_ptr = len_ptr; p.nsrc_ptr = &s->ctl->n_src;
+        p.vcap = s->cap_len; p.scap = s->cap_src;
+        p.rel_bias = m->dec_rel; p.rel_d = c.rel_max_dist;
+        p.att_scale = 1.f / std::sqrt((float)c.d_head); p.eps = c.norm_eps;
+        p.x_out = M.x;
+        p.x_keep = trunk > 0 && w == 0 ? s->trunk_x : nullptr;
+        p.scratch = M.pass_scratch;
+        p.at = pass_plan(T, d, p.I, p.F);
+        p.sync = s->pass_sync;
+        p.spins = s->pass_spins;
+        s->stage_count += 1;
+        HIPC(launch_pass(p, M.pass_groups, s->stream));
+    } else if (dt == BILD_DT_BF16 && T > kMaxRows) {
         if (lm_rows > 0) return BILD_EINVAL;
         const int rc = emit_prefill(s, w, T);
         if (rc) return rc;
@@ -1122,6 +1204,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     f.rows_consumed = T;
     f.y_cap = s->max_len;
     f.host_mirror = s->hctl_dev;
+    if (one) f.sync = s->pass_sync;
     if (lm_rows > 0) {
         GemmArgs g = gemm_base(m, m->head, xfin + (size_t)(T - lm_rows) * d, d, lm_rows, m->dec_final);
         if (parts) { g.px = M.px; g.px_stride = (int64_t)kMaxRows * d; g.pn = kPartSlices; g.x_out = xfin == M.x ? M.x2 : M.x; }
@@ -1178,6 +1261,16 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     return BILD_OK;
 }
 
+// Passes that produce a token, of shapes and row counts the pass kernel is made for (pass_groups); a caught-up row is rare and
+// its passes follow each other without the host's look at their outcome.  One workgroup per head has all its keys to itself:
+// up to 512 of the source arrive ahead of their use, each further one costs a layer 9 ns more than as kernels that split them,
+// against a gain per layer of 2 us for one row, 7 for two, 9 for four, 14 for eight (T5-large shape; T5-small, one row: 0.9).
+// Keys of the sequence itself are not asked for ahead; past 256 of them the waves have more than a block each.
+static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
+    return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
+           s->n_src <= (T == 1 ? 640 : 896 + 128 * T) && s->len[w] + T <= 256;
+}
+
 int key_bucket(int nkeys) {
     int b = 64;
     while (b < nkeys) b *= 2;
@@ -1195,17 +1288,18 @@ int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
     }
     const int bucket = key_bucket(s->len[w] + T);
     if (lm_rows > 0) s->ms[w].last_rows = lm_rows;
+    const bool one = takes_one_kernel(s, w, T, lm_rows) && take_turn(s);
     if (!s->use_graphs || s->prof_on || mode == 3) {
-        const int rc = decoder_pass(s, w, T, lm_rows, mode, bucket);
+        const int rc = decoder_pass(s, w, T, lm_rows, mode, bucket, one);
         if (rc == BILD_OK && !s->gemm_only) s->seq_issued += 1;  // its policy kernel will count this pass
         return rc;
     }
-    const std::array<int, 6> key = {w, T, lm_rows, mode, bucket, (s->debug_logits ? 1 : 0) | (s->gemm_only ? 2 : 0) | (s->top_p > 0.f ? 4 : 0) | (s->accept_mode ? 8 : 0)};
+    const std::array<int, 6> key = {w, T, lm_rows, mode, bucket, (s->debug_logits ? 1 : 0) | (s->gemm_only ? 2 : 0) | (s->top_p > 0.f ? 4 : 0) | (s->accept_mode ? 8 : 0) | (one ? 16 : 0)};
     auto it = s->graphs.find(key);
     if (it == s->graphs.end()) {
         hipGraph_t g = nullptr;
         HIPC(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-        const int rc = decoder_pass(s, w, T, lm_rows, mode, bucket);
+        const int rc = decoder_pass(s, w, T, lm_rows, mode, bucket, one);
         const hipError_t e = hipStreamEndCapture(s->stream, &g);
         if (rc != BILD_OK || e != hipSuccess) {
             if (g) (void)hipGraphDestroy(g);
@@ -1236,6 +1330,20 @@ int catch_up(bild_state* s, int w, int target) {
 }  // namespace bild
 
 namespace {
+
+// One pass and its result.  A pass kernel whose workgroups did not all get to run has changed nothing that counts: the pass runs
+// again as separate kernels, and so do this state's passes from then on.
+int finish_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
+    int rc = run_pass(s, w, T, lm_rows, mode);
+    if (rc == BILD_OK) rc = pull_ctl(s);
+    if (rc == kPassFailed) {
+        s->one_kernel = false;
+        rc = run_pass(s, w, T, lm_rows, mode);
+        if (rc == BILD_OK) rc = pull_ctl(s);
+    }
+    end_turn(s);
+    return rc;
+}
 
 // Cross K/V of every decoder layer of each model that uses the output of model w's encoder: K = norm_final(enc_x) Wk,
 // V = norm_final(enc_x) Wv.  bf16 models: one launch for all layers, from the planes of `p` (of a bf16 encoder) or from planes
@@ -1464,9 +1572,7 @@ extern "C" int bild_small_step(bild_state* s, float alpha_fb, int32_t* token, in
     if (rc) return rc;
     rc = catch_up(s, 0, s->y_len - 1);
     if (rc) return rc;
-    rc = run_pass(s, 0, 1, 1, 0);
-    if (rc) return rc;
-    rc = pull_ctl(s);
+    rc = finish_pass(s, 0, 1, 1, 0);
     if (rc) return rc;
     *token = s->hctl->res_tok;
     *fallback_flag = s->hctl->res_flag & 1;
@@ -1503,9 +1609,7 @@ extern "C" int bild_large_verify(bild_state* s, const int32_t* draft, int n, flo
     rc = catch_up(s, 1, s->draft_start - 1);
     if (rc) return rc;
     const int ds = s->draft_start;
-    rc = run_pass(s, 1, n + 1, n + 1, 1);
-    if (rc) return rc;
-    rc = pull_ctl(s);
+    rc = finish_pass(s, 1, n + 1, n + 1, 1);
     if (rc) return rc;
     const int r = s->hctl->res_r;
     *rollback_pos = r;
@@ -1636,9 +1740,7 @@ extern "C" int bild_greedy(bild_state* s, int which, const int32_t* src, int n_s
     while (s->y_len - s->n0 < max_new && !(s->y_len > s->n0 && last == eos && eos >= 0)) {
         rc = catch_up(s, w, s->y_len - 1);
         if (rc) return rc;
-        rc = run_pass(s, w, 1, 1, 2);
-        if (rc) return rc;
-        rc = pull_ctl(s);
+        rc = finish_pass(s, w, 1, 1, 2);
         if (rc) return rc;
         last = s->hctl->res_tok;
         s->hy[s->y_len - 1] = last;

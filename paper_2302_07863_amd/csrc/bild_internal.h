@@ -48,6 +48,8 @@ struct Ctl {
     int seq;          // passes finished so far; the LAST word, and the last one the policy kernel mirrors to the host
 };
 
+constexpr int kFlagFailed = 4;  // res_flag: the pass did not take place (see pass_kernel.hip)
+
 // Partial softmax statistics of one row over a slice of the vocabulary.
 struct StatPart {
     float m;    // max logit
@@ -194,6 +196,44 @@ struct AttnArgs {
     int d_model;
 };
 
+// A whole decoder pass in one kernel (pass_kernel.hip).
+constexpr int kPassRows = 16;
+constexpr int kPassCounters = 64;  // one per lane of the polling wave
+constexpr int kPassStride = 64;  // words
+constexpr int kPassSyncWords = (kPassCounters + 1) * kPassStride;  // counters on lines of their own; the last word: a workgroup gave up
+struct PassLayer {
+    const void *wqkv, *wo, *cwq, *cwo, *win, *wout;
+    const float *ln1, *lnc, *ln2;
+    char *kc, *vc, *ck, *cv;
+};
+struct PassPlan {  // where a layer's hand-over buffers lie in its piece of the scratch memory
+    int x1, s1, q, a1, x2, s2, a2, x3, s3, h, layer;
+};
+struct PassArgs {
+    const PassLayer* layers;  // device array, from the pass' first layer on
+    int n_layers;
+    int T, d, heads, I, F, act, cross;
+    // embedding of y[len ..]; emb null: the rows are x_in[len ..]
+    const void* emb;
+    const int* tokens;
+    const float *pe, *x_in;
+    int vocab, tie_shift;
+    float embed_scale;
+    const int *len_ptr, *nsrc_ptr;
+    int vcap, scap;
+    const float* rel_bias;
+    int rel_d;
+    float att_scale, eps;
+    float *x_out, *x_keep;    // the residual stream after the last layer: [T][d]; at [len ..] too (null: not kept)
+    char* scratch;            // [n_layers][at.layer]
+    PassPlan at;
+    int spins;                // polls (of about 0.7 us) after which a workgroup gives up
+    unsigned* sync;           // [kPassSyncWords], zero before the pass; the policy kernel clears it
+};
+int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // workgroups, 0: not a shape it is made for
+PassPlan pass_plan(int T, int d, int I, int F);
+hipError_t launch_pass(const PassArgs& a, int groups, hipStream_t st);
+
 struct EmbedArgs {
     TMat E;
     const int* tokens;      // token of row t is tokens[base + t]
@@ -249,6 +289,7 @@ struct FinishArgs {
     const float* u_acc;   // uniform number per sequence position for the acceptance test
     float* s_ring;        // [kMaxRows][vocab] the small model's logits of each pending draft, by draft index
     float4* s_draw;       // [sequence capacity] (max logit, nucleus threshold key, nucleus mass, -) of the small model's row
+    unsigned* sync;       // counters of the pass kernel, cleared here for its next pass; a flagged pass is not committed
     // nucleus draw spread over the chip (launch_finish_draw): its workspace
     struct DrawWs* dws;
 };

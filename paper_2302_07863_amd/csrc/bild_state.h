@@ -143,6 +143,10 @@ struct ModelState {
     char* xt = nullptr;
     float* ssq_t = nullptr;
     int rows_t = 0;           // rows these hold
+    // whole passes in one kernel (pass_kernel.hip)
+    int pass_groups = 0;      // workgroups; 0: the shape is not made for it
+    bild::PassLayer* pass_layers = nullptr;  // device
+    char* pass_scratch = nullptr;
 };
 
 struct bild_state {
@@ -156,6 +160,11 @@ struct bild_state {
     int* hsrc = nullptr;      // pinned copy of src
     float alpha_fb = -1.f, alpha_rb = -1.f;  // thresholds currently in the device control block
     bool use_graphs = true;
+    bool one_kernel = true;   // passes of up to kPassRows rows of a narrow bf16 model run as one kernel
+    unsigned* pass_sync = nullptr;
+    int pass_spins = 6000;    // 4 ms: kernels of other streams come to an end in that time, the same kernel of another process does not
+    int device = 0;
+    bool has_turn = false;    // (see take_turn)
     int ksplit_max_d = 2048;      // ... of models up to this wide (7B-shaped small model, 2048 wide: 0.729 -> 0.717 ms per step)
     int ksplit_min_f = 2048;      // FFN widths from which the output projection of a narrow model (d <= 1024) is cut into input slices
     int fuse_max_kv = 32 << 10;   // ... while one head's cached K/V are at most this many bytes
@@ -201,8 +210,9 @@ namespace bild {
 int dev_alloc(std::vector<void*>& keep, void** p, size_t bytes);
 int key_bucket(int nkeys);
 int catch_up(bild_state* s, int w, int target);
+void end_turn(bild_state* s);
 int run_pass(bild_state* s, int w, int T, int lm_rows, int mode);
-int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hint);
+int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hint, bool one);
 int pick_splits_raw(int d_head, int esz, int max_splits, int nkeys, int heads, int T, bool* defer);
 int pick_attn_waves(int dtype, int d_head, int T, int nkeys, int splits);
 }  // namespace bild

@@ -1,0 +1,698 @@
+// One decoder pass of a narrow bf16 model in ONE kernel: embedding and all layers for up to 16 rows.
+//
+// Such a pass is a chain of some 50 (T5-small shape) to 190 (T5-large shape) dependent stages, each far too small to use the
+// chip for long.  As kernels of their own they cost 3.5 - 8 us each: 1.5 us of launch, a trip to memory for the activations and
+// a longer one for the weights, which can only be asked for once the kernel runs.  Here workgroups stay for the whole pass (one
+// per compute unit at most) and walk the stages:
+//
+//   - hand-over.  A stage's results are written through the caches; the wave that wrote them waits until they are in memory and
+//     counts its workgroup in on one of 64 counters, each on lines of its own; a workgroup that needs them polls all of them
+//     with one load.  Publish, count, poll and read back take about 2 us over 200 workgroups, most of it trips to memory (one
+//     row of the T5-large shape: 739 us with 8 counters, 645 with 32, 635 with 64, 890 with a flag word per workgroup on shared
+//     lines; the fences of a barrier at agent scope, which write back and drop whole L2s, cost above 10 us each).  What is
+//     handed over lies at an address of its own for every layer and stage, which no die has read before in this kernel: plain
+//     loads cannot find an older copy of it in a cache, and a die's workgroups share one fetch through their L2;
+//   - weights depend on nothing: they are requested while a workgroup has nothing else to do, those of the FFN and of the next
+//     layer during the cross-attention (a wave's loads come back in order, so a request just before a wait delays what follows);
+//   - eight waves share a feature tile's inputs; activations arrive as high and low bf16 parts in the order of the matrix core's
+//     operand, so that no stage has anything to convert or to share: load, multiply, add up over the waves in LDS in wave order;
+//   - a workgroup that owns sixteen features of the residual stream owns them in all layers: they stay in its registers (fp32);
+//   - the cross query is worked out by the workgroup of the head that uses it, which saves a hand-over.
+//
+// Per pass, us, before (a kernel per stage) and now, 512 source tokens: T5-small shape one row 149 -> 142; T5-large shape 1, 2, 5,
+// 8, 16 rows 683, 799, 977, 998, 1223 -> 634, 642, 653, 651, 730; mT5-large shape, 64 tokens, 1 and 8 rows 809, 1063 -> 709, 725.
+//
+// A workgroup that has polled `spins` times in vain flags the pass as failed and walks on without waiting again (nothing
+// handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
+// the pass again as separate kernels.  That happens only if the workgroups cannot all be resident, because of another process'
+// kernel of the same kind, for instance.
+#include "kernel_common.h"
+
+namespace bild {
+
+constexpr int kPassWaves = 8, kPassThreads = 64 * kPassWaves;
+constexpr int kThrough = 17;       // buffer access flags sc0 sc1: through the caches
+
+typedef __attribute__((address_space(4))) const PassLayer CLayer;  // (read through the scalar cache)
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+// (an address worked out here, not behind the wait that follows)
+template <class P>
+__device__ __forceinline__ P* pinned(P* p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ Rsrc whole(const void* p) { return make_rsrc(p, 0xFFFFFFFFu); }
+__device__ __forceinline__ float4 ldf4(Rsrc r, int off) { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0)); }
+__device__ __forceinline__ bf16x8 as_bf(const uint4& v) { return __builtin_bit_cast(bf16x8, v); }
+__device__ __forceinline__ void st8(Rsrc r, int off, unsigned a, unsigned b) {
+    const v2u v = {a, b};
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kThrough);
+}
+
+// LDS: sums of the waves (up to four tiles each; attention joins its waves there too), their (max, sum), the head's query, the
+// head's relative-position biases
+constexpr int kRed = 0, kMl = kPassWaves * 4 * 1024, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kRel = kQ + 16 * kQLd * 4;
+
+struct Walk {
+    char* lds;
+    unsigned* counters;
+    unsigned* failed;
+    int spins;
+    int wg, wave, lane, tok, g, t, t8;  // t: this lane's row, clamped to the last one; t8: of the packed order
+    unsigned target;                // wave 0: arrivals this lane's counter has to show
+    bool dead;
+
+    int T;
+    __device__ __forceinline__ void place(int rows) {
+        T = rows;
+        tok = lane & 15;
+        g = lane >> 4;
+        t = min(tok, T - 1);
+        t8 = min(tok & 7, T - 1);
+    }
+    // the stage just described has `n` active workgroups from `base` on
+    __device__ __forceinline__ void expect(int base, int n) { target += (unsigned)(n + kPassCounters - 1 - ((lane - base) & (kPassCounters - 1))) / kPassCounters; }
+    __device__ __forceinline__ void arrive() const {  // one wave, after its stores
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) asm volatile("global_atomic_add %0, %1, off sc1" ::"v"(counters + (wg & (kPassCounters - 1)) * kPassStride), "v"(1u) : "memory");
+    }
+    __device__ __forceinline__ void wait() {
+        if (wave == 0 && !dead) {
+            const unsigned* p = counters + lane * kPassStride;
+            int n = 0;
+            unsigned v;
+            unsigned long long missing;
+#pragma unroll 1
+            do {
+                asm volatile("global_load_dword %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
+                missing = __builtin_amdgcn_ballot_w64((int)(v - target) < 0);
+            } while (missing && ++n < spins);
+            if (n >= spins) {
+                dead = true;
+                if (lane == 0) asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(failed), "v"(1u) : "memory");
+            }
+        }
+        lds_barrier();
+    }
+};
+
+// This wave's run of input tiles of a projection over tk tiles.
+struct Run {
+    int k0, n;
+};
+__device__ __forceinline__ Run run_of(int wave, int tk) {
+    const int per = (tk + kPassWaves - 1) / kPassWaves;
+    return {wave * per, max(0, min(per, tk - wave * per))};
+}
+
+template <int N, int RW>
+__device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const void* w, int unit, int tk) {
+    const Run r = run_of(c.wave, tk);
+    const Rsrc rs = whole((const char*)w + (size_t)unit * RW * tk * kTileBytes);
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        if (j < r.n) {
+#pragma unroll
+            for (int q = 0; q < RW; ++q) W[j * RW + q] = buf_load(rs, (unsigned)c.lane * 16u, (q * tk + r.k0 + j) * kTileBytes);
+        }
+}
+
+// acc = W x over this wave's inputs.  x lies in tiles of 32 inputs in the order in which the operand's lanes want it: quarters of
+// eight inputs, in each the rows one after the other, 16 bytes per row; the high parts of a tile and then its low parts.  (A load
+// is then one dense piece: with the rows' 64 bytes 128 apart a pass of eight rows took 854 us instead of 737.)
+// Up to eight rows (PACK) one operand holds the high parts of the rows in its columns 0 .. 7 and the low parts in 8 .. 15: half
+// the loads and products (a compute unit's 64 bytes a cycle are what the FFN output's 256 loads of 1 KiB wait for); the halves
+// are added in total().  A quarter then has the rows' high parts and their low parts.
+template <int N, int RW, bool PACK>
+__device__ __forceinline__ void multiply(const Walk& c, f32x4 (&acc)[RW], const uint4 (&W)[N * RW], const void* planes, int tk) {
+    const Run r = run_of(c.wave, tk);
+    const Rsrc xs = whole(planes);
+    const int S = c.T * 128;
+    const int at = (PACK ? (c.g * 2 + (c.tok >> 3)) * c.T + c.t8 : c.g * c.T + c.t) * 16, k0 = r.k0 * S;
+    constexpr int P = PACK ? 1 : 2, B = N < 8 / P ? N : 8 / P;  // tiles requested at once
+    uint4 X[2][P * B];
+    f32x4 low[RW];
+#pragma unroll
+    for (int q = 0; q < RW; ++q) acc[q] = low[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto get = [&](uint4 (&x)[P * B], int j0) {
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+            if (j0 + j < r.n) {
+                x[P * j] = buf_load(xs, (unsigned)at, k0 + (j0 + j) * S);
+                if (!PACK) x[P * j + 1] = buf_load(xs, (unsigned)at, k0 + (j0 + j) * S + S / 2);
+            }
+    };
+    auto mul = [&](const uint4 (&x)[P * B], int j0) {
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+            if (j0 + j < r.n) {
+#pragma unroll
+                for (int q = 0; q < RW; ++q) {
+                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j]), acc[q], 0, 0, 0);
+                    f32x4& lo_acc = RW == 1 ? low[q] : acc[q];
+                    if (!PACK) lo_acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j + 1]), lo_acc, 0, 0, 0);
+                }
+            }
+    };
+    get(X[0], 0);
+#pragma unroll
+    for (int j0 = 0; j0 < N; j0 += B) {
+        if (j0 + B < N && j0 + B < r.n) get(X[(j0 / B + 1) & 1], j0 + B);
+        mul(X[(j0 / B) & 1], j0);
+    }
+    if constexpr (RW == 1 && !PACK) acc[0] += low[0];
+}
+
+// The waves' results side by side in LDS; `tile`'s total over the waves, in wave order.
+template <int RW>
+__device__ __forceinline__ void leave(const Walk& c, const f32x4 (&acc)[RW]) {
+#pragma unroll
+    for (int q = 0; q < RW; ++q) *(f32x4*)(c.lds + kRed + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
+    lds_barrier();
+}
+template <int RW, bool PACK>
+__device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
+    f32x4 p[kPassWaves];
+#pragma unroll
+    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const f32x4*)(c.lds + kRed + ((v * RW + tile) * 64 + c.lane) * 16);
+    f32x4 s = p[0];
+#pragma unroll
+    for (int v = 1; v < kPassWaves; ++v) s += p[v];
+    if constexpr (PACK) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s[v] += dpp_f<0x128, 0xF>(0.f, s[v]);  // row_ror:8: columns 8 .. 15 to 0 .. 7
+    }
+    return s;
+}
+
+// RMSNorm's factor of this lane's row from the owners' partial sums of squares, [t][d / 16]: requested and, later, added up.
+struct Norm {
+    float4 v[4] = {};
+    __device__ __forceinline__ void get(const Walk& c, const float* ssq, int nd) {
+        const Rsrc r = whole(ssq);
+        const int per = nd >> 2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = i * 4 < per ? ldf4(r, (c.t * nd + c.g * per + i * 4) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __device__ __forceinline__ float factor(int d, float eps) const {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+        return __builtin_amdgcn_rsqf(quad_rows_sum(s) * __builtin_amdgcn_rcpf((float)d) + eps);
+    }
+};
+
+// Sixteen features of a row's activations in that order: this lane's four.
+template <bool PACK>
+__device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, const float (&w)[4]) {
+    uint32_t h01, l01, h23, l23;
+    split_bf16x2(w[0], w[1], h01, l01);
+    split_bf16x2(w[2], w[3], h23, l23);
+    const Rsrc r = whole(planes);
+    const int off = (n0 >> 5) * c.T * 128 + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.T + c.tok) * 16 + (n0 & 7) * 2;
+    st8(r, off, h01, h23);
+    st8(r, off + (PACK ? 16 : 64) * c.T, l01, l23);
+}
+
+// Attention of one head over its keys for all rows: the waves take blocks of 32 keys in turn; (max, sum, O) joined through LDS.
+template <bool CAUSAL, bool PACK>
+struct Attend {
+    const Rsrc kr, vr;
+    const int I, cap, nkeys, nblk;
+    uint4 K0[2][2], K1[2][2], V0[4], V1[4];
+
+    __device__ __forceinline__ void load(const Walk& c, uint4 (&Kr)[2][2], uint4 (&Vr)[4], int blk) const {
+        const int key0 = min(blk, nblk - 1) * 32;
+#pragma unroll
+        for (int ab = 0; ab < 2; ++ab)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) Kr[ab][ks] = buf_load(kr, (unsigned)(((ab * 16 + c.tok) * I + c.g * 8) * 2), key0 * I * 2 + ks * 64);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) {
+            const int off = ((dt * 16 + c.tok) * cap + c.g * 4) * 2;
+            const uint2 va = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, off, key0 * 2, 0));
+            const uint2 vb = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, off + 32, key0 * 2, 0));
+            Vr[dt] = make_uint4(va.x, va.y, vb.x, vb.y);
+        }
+    }
+    // q: this lane's row and inputs g * 8 .. of both halves of the head (scaled)
+    template <class Query>
+    __device__ __forceinline__ void run(const Walk& c, Query&& query, float scale, int len, const float* relb, int rel_d, void* out, int T, int h) {
+        bf16x8 Qh[2], Ql[2];
+        auto split_query = [&](const float4 (&qv)[2][2]) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                uint32_t hi[4], lo[4];
+                split_bf16x2(qv[ks][0].x * scale, qv[ks][0].y * scale, hi[0], lo[0]);
+                split_bf16x2(qv[ks][0].z * scale, qv[ks][0].w * scale, hi[1], lo[1]);
+                split_bf16x2(qv[ks][1].x * scale, qv[ks][1].y * scale, hi[2], lo[2]);
+                split_bf16x2(qv[ks][1].z * scale, qv[ks][1].w * scale, hi[3], lo[3]);
+                Qh[ks] = as_bf(make_uint4(hi[0], hi[1], hi[2], hi[3]));
+                Ql[ks] = as_bf(make_uint4(lo[0], lo[1], lo[2], lo[3]));
+            }
+        };
+        float m_run = -INFINITY, l_run = 0.f;
+        f32x4 O[4];
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int lim = CAUSAL ? len + c.t : nkeys - 1;
+        auto process = [&](const uint4 (&Kr)[2][2], const uint4 (&Vr)[4], int blk) {
+            const int key0 = blk * 32;
+            f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int ab = 0; ab < 2; ++ab) {
+                    s[ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Kr[ab][ks]), Qh[ks], s[ab], 0, 0, 0);
+                    s[ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Kr[ab][ks]), Ql[ks], s[ab], 0, 0, 0);
+                }
+            if (CAUSAL && relb) {
+#pragma unroll
+                for (int ab = 0; ab < 2; ++ab)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) s[ab][v] += relb[rel_d + max(-rel_d, min(rel_d, key0 + ab * 16 + c.g * 4 + v - (len + c.t)))];
+            }
+            float tmax = -INFINITY;
+#pragma unroll
+            for (int ab = 0; ab < 2; ++ab)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int key = key0 + ab * 16 + c.g * 4 + v;
+                    if (key > lim) s[ab][v] = -INFINITY;
+                    tmax = fmaxf(tmax, s[ab][v]);
+                }
+            tmax = quad_rows_max(tmax);
+            const float m_new = fmaxf(m_run, tmax);
+            const float f = m_run == -INFINITY ? 0.f : fexp(m_run - m_new);
+            float p[2][4], psum = 0.f;
+#pragma unroll
+            for (int ab = 0; ab < 2; ++ab)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    p[ab][v] = m_new == -INFINITY ? 0.f : fexp(s[ab][v] - m_new);
+                    psum += p[ab][v];
+                }
+            l_run = l_run * f + quad_rows_sum(psum);
+            m_run = m_new;
+            uint32_t ph[4], pl[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) split_bf16x2(p[j >> 1][(j & 1) * 2], p[j >> 1][(j & 1) * 2 + 1], ph[j], pl[j]);
+            const bf16x8 Ph = as_bf(make_uint4(ph[0], ph[1], ph[2], ph[3])), Pl = as_bf(make_uint4(pl[0], pl[1], pl[2], pl[3]));
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) {
+                O[dt] *= f;
+                O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Vr[dt]), Ph, O[dt], 0, 0, 0);
+                O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Vr[dt]), Pl, O[dt], 0, 0, 0);
+            }
+        };
+        if constexpr (CAUSAL) {  // (few blocks: a wave without one requests nothing)
+            if (c.wave < nblk) {
+                float4 qv[2][2];
+                query(qv);
+                load(c, K0, V0, c.wave);
+                __builtin_amdgcn_sched_barrier(0);
+                // (all of it is here: the compiler would move requests to their uses, one trip to memory after the other)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    asm volatile("" : "+v"(qv[i >> 1][i & 1].x), "+v"(qv[i >> 1][i & 1].y), "+v"(qv[i >> 1][i & 1].z), "+v"(qv[i >> 1][i & 1].w));
+                    asm volatile("" : "+v"(K0[i >> 1][i & 1].x), "+v"(K0[i >> 1][i & 1].y), "+v"(K0[i >> 1][i & 1].z), "+v"(K0[i >> 1][i & 1].w));
+                    asm volatile("" : "+v"(V0[i].x), "+v"(V0[i].y), "+v"(V0[i].z), "+v"(V0[i].w));
+                }
+                split_query(qv);
+                process(K0, V0, c.wave);
+            }
+            for (int blk = c.wave + kPassWaves; blk < nblk; blk += kPassWaves) {
+                load(c, K0, V0, blk);
+                process(K0, V0, blk);
+            }
+        } else {
+            float4 qv[2][2];
+            query(qv);
+            split_query(qv);
+            for (int blk = c.wave; blk < nblk; blk += 2 * kPassWaves) {
+                process(K0, V0, blk);
+                if (blk + 2 * kPassWaves < nblk) load(c, K0, V0, blk + 2 * kPassWaves);
+                if (blk + kPassWaves < nblk) {
+                    process(K1, V1, blk + kPassWaves);
+                    if (blk + 3 * kPassWaves < nblk) load(c, K1, V1, blk + 3 * kPassWaves);
+                }
+            }
+        }
+        float* cm = (float*)(c.lds + kMl);
+        float* cl = cm + kPassWaves * 16;
+        if (c.g == 0) {
+            cm[c.wave * 16 + c.tok] = m_run;
+            cl[c.wave * 16 + c.tok] = l_run;
+        }
+        leave<4>(c, O);
+        if (c.wave < 4) {
+            float w[kPassWaves], M = -INFINITY, L = 0.f;
+            f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int v = 0; v < kPassWaves; ++v) {
+                w[v] = cm[v * 16 + c.tok];
+                M = fmaxf(M, w[v]);
+            }
+#pragma unroll
+            for (int v = 0; v < kPassWaves; ++v) {
+                w[v] = w[v] == -INFINITY ? 0.f : fexp(w[v] - M);
+                L += cl[v * 16 + c.tok] * w[v];
+                o += *(const f32x4*)(c.lds + kRed + ((v * 4 + c.wave) * 64 + c.lane) * 16) * w[v];
+            }
+            const float inv = 1.f / L;
+            const float r[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
+            if (c.tok < T) put_planes<PACK>(c, out, h * 64 + c.wave * 16 + c.g * 4, r);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        lds_barrier();  // all four waves' stores are in memory
+        if (c.wave == 0) c.arrive();
+    }
+};
+
+// Workgroups [0, workers) do the projections; the first d / 16 of them own sixteen features of the residual stream each.
+template <bool GATED, bool PACK>
+__device__ __forceinline__ void worker(Walk& c, const PassArgs& a) {
+    int T = a.T, d = a.d, I = a.I, F = a.F;
+    const int base = (int)gridDim.x - a.heads;  // the workgroups with a head each follow
+    const int len = *a.len_ptr;
+    auto nd = [&] { return d >> 4; };
+    auto nq = [&] { return 3 * (I >> 4); };
+    auto nf = [&] { return GATED ? F >> 4 : F >> 5; };  // two tiles each
+    const bool owner = c.wg < nd(), qkv = c.wg < nq(), ffn = c.wg < nf();
+    uint4 Wq[4], Wo[4], Wi[8], Wf[16];
+    float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);  // (owners, wave 0) the residual stream of this lane's row, features n0 .. n0 + 3
+    auto n0 = [&] { return c.wg * 16 + c.g * 4; };
+    // the gain of the norm that reads x next, requested before the wait for what is added to it
+    auto gain = [&](const float* g) { return ldf4(whole(g), n0() * 4); };
+    auto publish = [&](const float4& gn, char* planes, char* ssq) {
+        const float w[4] = {x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w};
+        const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
+        if (c.tok < T) {
+            put_planes<PACK>(c, planes, n0(), w);
+            if (c.g == 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(ssq), (c.tok * nd() + c.wg) * 4, 0, kThrough);
+        }
+        c.arrive();
+    };
+    auto add = [&](const f32x4& s) { x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]); };
+    const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
+    char* z = a.scratch;  // this layer's hand-over buffers
+    if (owner && c.wave == 0) {
+        const int pos = len + c.t;
+        const float4 gn = gain(L->ln1);
+        if (a.emb) {
+            int er = a.tokens[pos] + a.tie_shift;
+            er = er >= a.vocab ? er - a.vocab : er;
+            const char* p = (const char*)a.emb + ((size_t)(er >> 4) * (d >> 5) + (n0() >> 5)) * kTileBytes + ((er & 15) + 16 * ((n0() & 31) >> 3)) * 16 + (n0() & 7) * 2;
+            const uint2 raw = *(const uint2*)p;
+            float4 pe = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (a.pe) pe = *(const float4*)(a.pe + (size_t)pos * d + n0());
+            const float sc = a.embed_scale;
+            x = make_float4(__builtin_fmaf(bf2f(raw.x & 0xFFFFu), sc, pe.x), __builtin_fmaf(bf2f(raw.x >> 16), sc, pe.y),
+                            __builtin_fmaf(bf2f(raw.y & 0xFFFFu), sc, pe.z), __builtin_fmaf(bf2f(raw.y >> 16), sc, pe.w));
+        } else {
+            x = *(const float4*)(a.x_in + (size_t)pos * d + n0());
+        }
+        publish(gn, z + a.at.x1, z + a.at.s1);
+    }
+    if (qkv) request<4, 1>(c, Wq, L->wqkv, c.wg, d >> 5);
+    c.expect(0, nd());
+    for (int l = 0; l < a.n_layers; ++l, z += a.at.layer) {
+        L = (const CLayer*)(uintptr_t)a.layers + l;
+        const bool last = l + 1 == a.n_layers;
+        // (addresses are worked out where they are needed: kept across the loop they would not fit the registers)
+        asm volatile("" : "+v"(c.lane));
+        asm volatile("" : "+s"(T), "+s"(d), "+s"(I), "+s"(F));
+        c.place(T);
+        // ---- q, k, v ----
+        if (qkv) {
+            const char *xs = pinned(z + a.at.x1), *ss = pinned(z + a.at.s1);
+            const int ni = I >> 4;
+            char* out = pinned(c.wg < ni ? z + a.at.q : c.wg < 2 * ni ? L->kc : L->vc);
+            c.wait();
+            Norm nm;
+            if (c.wave == 0) nm.get(c, (const float*)ss, nd());
+            f32x4 acc[1];
+            multiply<4, 1, PACK>(c, acc, Wq, xs, d >> 5);
+            const float f = nm.factor(d, a.eps);
+            leave<1>(c, acc);
+            if (c.wave == 0) {
+                const f32x4 s = total<1, PACK>(c, 0) * f;
+                const int seg = c.wg < ni ? 0 : c.wg < 2 * ni ? 1 : 2, nn = n0() - seg * I, pos = len + c.tok;
+                if (c.tok < T) {
+                    if (seg == 0) {
+                        const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
+                        __builtin_amdgcn_raw_buffer_store_b128(v, whole(out), (c.tok * I + nn) * 4, 0, kThrough);
+                    } else if (seg == 1) {
+                        st8(whole(out), (pos * I + nn) * 2, pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
+                    } else {
+                        const Rsrc vr = whole(out);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)f2bf(s[v]), vr, ((nn + v) * a.vcap + pos) * 2, 0, kThrough);
+                    }
+                }
+                c.arrive();
+            }
+        }
+        c.expect(0, nq());
+        c.expect(base, a.heads);  // (self-attention)
+        // ---- output projection ----
+        // Requests go out where the workgroup has several microseconds before it is needed again (a wave's loads come back in
+        // order: what is asked for late delays the next stage's activations): here, while the heads work, and below.
+        if (owner) {
+            request<4, 1>(c, Wo, L->wo, c.wg, I >> 5);
+            const float4 gn = gain(a.cross ? L->lnc : L->ln2);
+            if (!a.cross) {
+                next_gain = gain(last ? L->ln2 : L[1].ln1);
+                request<16, 1>(c, Wf, L->wout, c.wg, F >> 5);
+            }
+            const char* xs = pinned(z + a.at.a1);
+            char *ox = pinned(z + a.at.x2), *os = pinned(z + a.at.s2);
+            c.wait();
+            f32x4 acc[1];
+            multiply<4, 1, PACK>(c, acc, Wo, xs, I >> 5);
+            leave<1>(c, acc);
+            if (c.wave == 0) {
+                add(total<1, PACK>(c, 0));
+                publish(gn, ox, os);
+            }
+        }
+        c.expect(0, nd());
+        const char *xf = z + a.at.x2, *sf = z + a.at.s2;  // what the FFN reads
+        if (a.cross) {
+            c.expect(base, a.heads);
+            // ---- output projection of the cross-attention ----
+            if (owner) {
+                request<4, 1>(c, Wo, L->cwo, c.wg, I >> 5);
+                const float4 gn = gain(L->ln2);
+                next_gain = gain(last ? L->ln2 : L[1].ln1);
+                if (ffn) request<4, 2>(c, Wi, L->win, c.wg, d >> 5);
+                request<16, 1>(c, Wf, L->wout, c.wg, F >> 5);
+                if (qkv && !last) request<4, 1>(c, Wq, L[1].wqkv, c.wg, d >> 5);
+                const char* xs = pinned(z + a.at.a2);
+                char *ox = pinned(z + a.at.x3), *os = pinned(z + a.at.s3);
+                c.wait();
+                f32x4 acc[1];
+                multiply<4, 1, PACK>(c, acc, Wo, xs, I >> 5);
+                leave<1>(c, acc);
+                if (c.wave == 0) {
+                    add(total<1, PACK>(c, 0));
+                    publish(gn, ox, os);
+                }
+            }
+            c.expect(0, nd());
+            xf = z + a.at.x3;
+            sf = z + a.at.s3;
+        }
+        // ---- FFN ----
+        if (ffn) {
+            if (!owner || !a.cross) request<4, 2>(c, Wi, L->win, c.wg, d >> 5);
+            const char *xs = pinned(xf), *ss = pinned(sf);
+            char* out = pinned(z + a.at.h);
+            c.wait();
+            Norm nm;
+            if (c.wave == 0) nm.get(c, (const float*)ss, nd());
+            f32x4 acc[2];
+            multiply<4, 2, PACK>(c, acc, Wi, xs, d >> 5);
+            const float r = nm.factor(d, a.eps);
+            leave<2>(c, acc);
+            if (c.wave == 0) {
+                const f32x4 s = total<2, PACK>(c, 0) * r, u = total<2, PACK>(c, 1) * r;
+                float w[4];
+                if constexpr (GATED) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) w[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(s[v]) : silu_f(s[v])) * u[v];
+                    if (c.tok < T) put_planes<PACK>(c, out, n0(), w);
+                } else {
+                    float y[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        w[v] = fmaxf(s[v], 0.f);
+                        y[v] = fmaxf(u[v], 0.f);
+                    }
+                    if (c.tok < T) {
+                        put_planes<PACK>(c, out, c.wg * 32 + c.g * 4, w);
+                        put_planes<PACK>(c, out, c.wg * 32 + 16 + c.g * 4, y);
+                    }
+                }
+                c.arrive();
+            }
+        }
+        c.expect(0, nf());
+        if (qkv && !last && (!owner || !a.cross)) request<4, 1>(c, Wq, L[1].wqkv, c.wg, d >> 5);
+        if (owner) {
+            const char* xs = pinned(z + a.at.h);
+            char *ox = pinned(z + a.at.layer + a.at.x1), *os = pinned(z + a.at.layer + a.at.s1);
+            c.wait();
+            f32x4 acc[1];
+            multiply<16, 1, PACK>(c, acc, Wf, xs, F >> 5);
+            leave<1>(c, acc);
+            if (c.wave == 0) {
+                add(total<1, PACK>(c, 0));
+                if (!last) publish(next_gain, ox, os);
+            }
+        }
+        c.expect(0, nd());
+    }
+    if (owner && c.wave == 0 && c.tok < T) {
+        *(float4*)(a.x_out + (size_t)c.tok * d + n0()) = x;
+        if (a.x_keep) *(float4*)(a.x_keep + (size_t)(len + c.tok) * d + n0()) = x;
+    }
+}
+
+// The last `heads` workgroups: a head each, of the self-attention and of the cross-attention (query included).
+template <bool GATED, bool PACK>
+__device__ __forceinline__ void header(Walk& c, const PassArgs& a) {
+    const int base = (int)gridDim.x - a.heads, h = c.wg - base;
+    int T = a.T, d = a.d, I = a.I;
+    const int len = *a.len_ptr, nsrc = a.cross ? *a.nsrc_ptr : 0;
+    const float* relb = nullptr;
+    if (a.rel_bias) {
+        float* r = (float*)(c.lds + kRel);
+        const int n = 2 * a.rel_d + 1;
+        for (int i = threadIdx.x; i < n; i += kPassThreads) r[i] = a.rel_bias[(size_t)h * n + i];
+        relb = r;
+    }
+    uint4 Wc[16];  // of the cross query
+    const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
+    char* z = a.scratch;
+    if (a.cross) request<4, 4>(c, Wc, L->cwq, h, d >> 5);
+    c.expect(0, d >> 4);
+    for (int l = 0; l < a.n_layers; ++l, z += a.at.layer) {
+        L = (const CLayer*)(uintptr_t)a.layers + l;
+        asm volatile("" : "+v"(c.lane));
+        asm volatile("" : "+s"(T), "+s"(d), "+s"(I));
+        c.place(T);
+        c.expect(0, 3 * (I >> 4));
+        // the cross-attention's keys and values while the heads have nothing else to do
+        Attend<false, PACK> cross = {whole(L->ck + (size_t)h * 128), whole(L->cv + (size_t)h * 64 * a.scap * 2), I, a.scap, nsrc, (nsrc + 31) >> 5, {}, {}, {}, {}};
+        if (a.cross) {
+            cross.load(c, cross.K0, cross.V0, c.wave);
+            if (cross.nblk > kPassWaves) cross.load(c, cross.K1, cross.V1, c.wave + kPassWaves);
+        }
+        {
+            Attend<true, PACK> at = {whole(pinned(L->kc + (size_t)h * 128)), whole(pinned(L->vc + (size_t)h * 64 * a.vcap * 2)), I, a.vcap, len + T, (len + T + 31) >> 5, {}, {}, {}, {}};
+            const Rsrc qr = whole(pinned(z + a.at.q));
+            char* out = pinned(z + a.at.a1);
+            const float sc = a.att_scale;
+            c.wait();
+            auto query = [&](float4 (&qv)[2][2]) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) qv[ks][p] = ldf4(qr, (c.t * I + h * 64 + ks * 32 + c.g * 8 + p * 4) * 4);
+            };
+            at.run(c, query, sc, len, relb, a.rel_d, out, T, h);
+        }
+        c.expect(base, a.heads);
+        c.expect(0, d >> 4);
+        if (a.cross) {
+            const char *xs = pinned(z + a.at.x2), *ss = pinned(z + a.at.s2);
+            char* out = pinned(z + a.at.a2);
+            const float sc = a.att_scale;
+            c.wait();
+            Norm nm;
+            if (c.wave < 4) nm.get(c, (const float*)ss, d >> 4);
+            f32x4 acc[4];
+            multiply<4, 4, PACK>(c, acc, Wc, xs, d >> 5);
+            const float f = nm.factor(d, a.eps);
+            leave<4>(c, acc);
+            float* q = (float*)(c.lds + kQ);
+            if (c.wave < 4) {
+                const f32x4 s = total<4, PACK>(c, c.wave) * f;
+                *(f32x4*)(q + c.tok * kQLd + c.wave * 16 + c.g * 4) = s;
+            }
+            lds_barrier();
+            auto query = [&](float4 (&qv)[2][2]) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) qv[ks][p] = *(const float4*)(q + c.t * kQLd + ks * 32 + c.g * 8 + p * 4);
+            };
+            cross.run(c, query, sc, len, nullptr, 0, out, T, h);
+            if (l + 1 < a.n_layers) request<4, 4>(c, Wc, L[1].cwq, h, d >> 5);
+            c.expect(base, a.heads);
+            c.expect(0, d >> 4);
+        }
+        c.expect(0, GATED ? a.F >> 4 : a.F >> 5);
+        c.expect(0, d >> 4);
+    }
+}
+
+template <bool GATED, bool PACK>
+__global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    Walk c;
+    c.lds = smem;
+    c.counters = a.sync;
+    c.failed = a.sync + kPassSyncWords - 1;
+    c.spins = a.spins;
+    c.wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    c.lane = (int)threadIdx.x & 63;
+    c.wg = (int)blockIdx.x;
+    c.place(a.T);
+    c.target = 0;
+    c.dead = false;
+    if (c.wg < (int)gridDim.x - a.heads) worker<GATED, PACK>(c, a);
+    else header<GATED, PACK>(c, a);
+}
+
+// Sizes the kernel is made for: one unit of every stage per workgroup, runs of inputs that fit the registers (four tiles a
+// wave, sixteen of the FFN's hidden state).  Wider models are bound by the weights' bandwidth, not by the hand-overs.
+int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
+    const int I = heads * d_head;
+    if (d_head != 64 || d % 256 != 0 || d > 1024 || I > 1024 || F % 32 != 0 || F > 4096) return 0;
+    const int g = std::max(std::max(3 * I / 16, gated ? F / 16 : F / 32), d / 16) + heads;
+    return g <= cus ? g : 0;
+}
+
+PassPlan pass_plan(int T, int d, int I, int F) {
+    PassPlan p;
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+        const size_t r = at;
+        at += (bytes + 255) / 256 * 256;
+        return (int)r;
+    };
+    const size_t per = 4 * T, x = per * d, i = per * I, s = (size_t)T * (d / 16) * 4;  //
+    p.x1 = take(x); p.s1 = take(s); p.q = take((size_t)T * I * 4); p.a1 = take(i);
+    p.x2 = take(x); p.s2 = take(s); p.a2 = take(i); p.x3 = take(x); p.s3 = take(s);
+    p.h = take(per * F);
+    p.layer = (int)at;
+    return p;
+}
+
+hipError_t launch_pass(const PassArgs& a, int groups, hipStream_t st) {
+    if (groups < 1 || a.T < 1 || a.T > kPassRows || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr || (a.cross && !a.nsrc_ptr)) return hipErrorInvalidValue;
+    const size_t smem = kRel + (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);
+    if (smem > 64 * 1024) return hipErrorInvalidValue;
+    const bool gated = a.act != BILD_ACT_RELU;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(groups), dim3(kPassThreads), smem, st, a); };
+    if (a.T <= 8) gated ? go(pass_kernel<true, true>) : go(pass_kernel<false, true>);
+    else gated ? go(pass_kernel<true, false>) : go(pass_kernel<false, false>);
+    return hipGetLastError();
+}
+
+}  // namespace bild

@@ -285,6 +285,7 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int 
     const int c_ylen = c->y_len, c_ds = c->draft_start, c_nmax = c->n_max, c_len0 = c->len[0], c_len1 = c->len[1], c_lenw = c->len[a.which];
     const float c_afb = c->alpha_fb, c_arb = c->alpha_rb;
     const int c_seq = c->seq;
+    const bool failed = a.sync && a.sync[kPassSyncWords - 1] != 0u;
     float z_draft = 0.f;
     if (a.mode != 3)
         merge_partials(a, rm, rsum, ridx, [&] { if (a.mode == 1) z_draft = a.zt[a.row_off + min(lane, max(a.T - 2, 0))]; });
@@ -393,6 +394,19 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int 
         if (lane <= n) {
             c->res_rowtok[lane] = row_tok;
             tell(row_tok, (int)offsetof(Ctl, res_rowtok) + lane * 4);
+        }
+    }
+    if (a.sync) {
+        a.sync[lane * kPassStride] = 0u;
+        if (lane == 0) a.sync[kPassSyncWords - 1] = 0u;
+        if (failed) {  // the pass kernel's workgroups did not all run: nothing happened but the count of passes
+            if (lane == 0) {
+                c->seq = c_seq + 1;
+                tell(kFlagFailed, (int)offsetof(Ctl, res_flag));
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0) tell(c_seq + 1, (int)offsetof(Ctl, seq));
+            return;
         }
     }
     int n_ylen = c_ylen, n_ds = c_ds, n_len0 = c_len0, n_lenw = c_lenw + a.rows_consumed;

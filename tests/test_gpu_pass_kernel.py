@@ -1,0 +1,47 @@
+"""Decoder passes of narrow bf16 models as one kernel, at the edges of its shapes, rows and key blocks, through the C ABI against
+the CPU oracle."""
+import pytest
+
+import bild_inputs as bi
+import oracle
+from tests import parity
+from tests.test_gpu_parity import Rig
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(n_max=4, alpha_fb=0.4, max_new=8, **shape):
+    cfg = bi.toy_pair(**{**dict(dtype=bi.DT_BF16, d=256, heads=4, d_head=64, d_ff=512, truncate=True, n_src=20, max_new=max_new), **shape})
+    R = Rig(cfg)
+    ref = oracle.bild_generate(R.req, alpha_fb, 1.0, n_max, cfg.max_new, keep_logits=True)
+    st = R.state(cfg.max_new, n_max)
+    st.encode(R.src)
+    parity.teacher_forced(st, ref, R.n0, alpha_fb, 1.0, cfg)
+
+
+@pytest.mark.parametrize("shape", [
+    dict(d=256, heads=1, d_ff=32),                                           # fewer inputs and units than waves
+    dict(d=512, heads=6, d_ff=1024, act=bi.ACT_GATED_GELU),                  # attention narrower than the model
+    dict(d=768, heads=12, d_ff=2112),                                        # a wave's last inputs missing
+    dict(d=1024, heads=16, d_ff=4096, vocab=300, n_large=2, logit_scale=4.0),  # the largest of each
+    dict(d=512, heads=8, d_ff=1024, cross=False),
+])
+def test_shapes(shape):
+    _check(**shape)
+
+
+@pytest.mark.parametrize("n_max", [7, 8, 15])
+def test_rows_of_a_review(n_max):
+    """8, 9 and 16 rows: the packed operand, the plain one, and the most the kernel takes."""
+    _check(n_max=n_max, alpha_fb=0.0, max_new=2 * n_max)
+
+
+@pytest.mark.parametrize("n_src", [1, 32, 33, 257, 530])
+def test_source_lengths_around_the_key_blocks(n_src):
+    _check(n_src=n_src)
+
+
+def test_a_pass_that_gives_up_runs_again_as_kernels(monkeypatch):
+    """No poll is waited for: the first pass is flagged, commits nothing, and the request goes on without the kernel."""
+    monkeypatch.setenv("BILD_PASS_SPINS", "1")
+    _check()
