@@ -352,6 +352,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         const char* ng = std::getenv("BILD_NO_GRAPH");
         s->use_graphs = !(ng && ng[0] == '1');
         if (const char* ok = std::getenv("BILD_ONE_KERNEL")) s->one_kernel = ok[0] != '0';  // tests and measurements
+        if (const char* od = std::getenv("BILD_ONE_DIE")) s->one_die = od[0] != '0';  // tests and measurements
         if (const char* sp = std::getenv("BILD_PASS_SPINS")) s->pass_spins = std::atoi(sp);  // tests
         if (const char* pm = std::getenv("BILD_PRE_MIN_ROWS")) s->pre_min_rows = std::atoi(pm);  // experiments; > 32 turns the planes off
         if (const char* fa = std::getenv("BILD_FUSE_ATTN")) s->fuse_attn = fa[0] != '0';      // experiments / tests
@@ -362,8 +363,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
     const int positions = std::max(s->cap_len, s->cap_src);
-    int cus = 0;
-    if (hipGetDevice(&s->device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess) {
+    if (hipGetDevice(&s->device) != hipSuccess || hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess) {
         bild_state_destroy(s);
         return BILD_EHIP;
     }
@@ -407,7 +407,8 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             want(M.ab, sizeof(uint16_t) * 2 * kMaxRows * I);
             want(M.hb, sizeof(uint16_t) * 2 * kMaxRows * F);
             want(M.ssq, sizeof(float) * (kMaxSsqParts + 8) * kMaxRows);
-            M.pass_groups = s->one_kernel && m->cfg.pos != BILD_POS_ROPE ? pass_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), cus) : 0;
+            M.pass_groups = s->one_kernel && m->cfg.pos != BILD_POS_ROPE ? pass_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus) : 0;
+            if (M.pass_groups && s->one_die && s->cus == 256) M.pass_die_groups = pass_die_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated());
             if (M.pass_groups) {
                 want(M.pass_layers, sizeof(PassLayer) * L);
                 want(M.pass_scratch, L * (size_t)pass_plan(kPassRows, (int)d, (int)I, (int)F).layer);
@@ -1185,7 +1186,9 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         p.sync = s->pass_sync;
         p.spins = s->pass_spins;
         s->stage_count += 1;
-        HIPC(launch_pass(p, M.pass_groups, s->stream));
+        p.die = M.pass_die_groups > 0 && T <= kPassDieRows;
+        p.groups = p.die ? M.pass_die_groups : M.pass_groups;
+        HIPC(launch_pass(p, p.die ? s->cus : p.groups, s->stream));
     } else if (dt == BILD_DT_BF16 && T > kMaxRows) {
         if (lm_rows > 0) return BILD_EINVAL;
         const int rc = emit_prefill(s, w, T);
@@ -1266,9 +1269,10 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // up to 512 of the source arrive ahead of their use, each further one costs a layer 9 ns more than as kernels that split them,
 // against a gain per layer of 2 us for one row, 7 for two, 9 for four, 14 for eight (T5-large shape; T5-small, one row: 0.9).
 // Keys of the sequence itself are not asked for ahead; past 256 of them the waves have more than a block each.
+// (On one die the gain is 6 us per layer at 512 keys and gone at 1000, T5-small shape.)
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
-           s->n_src <= (T == 1 ? 640 : 896 + 128 * T) && s->len[w] + T <= 256;
+           s->n_src <= (s->ms[w].pass_die_groups > 0 && T <= kPassDieRows ? 1000 : T == 1 ? 640 : 896 + 128 * T) && s->len[w] + T <= 256;
 }
 
 int key_bucket(int nkeys) {

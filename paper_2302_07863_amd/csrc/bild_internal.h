@@ -197,10 +197,10 @@ struct AttnArgs {
 };
 
 // A whole decoder pass in one kernel (pass_kernel.hip).
-constexpr int kPassRows = 16;
+constexpr int kPassRows = 16, kPassDieRows = 8;
 constexpr int kPassCounters = 64;  // one per lane of the polling wave
 constexpr int kPassStride = 64;  // words
-constexpr int kPassSyncWords = (kPassCounters + 1) * kPassStride;  // counters on lines of their own; the last word: a workgroup gave up
+constexpr int kPassSyncWords = (kPassCounters + 1) * kPassStride;  // counters on lines of their own, then the ranks given out on a die; the last word: a workgroup gave up
 struct PassLayer {
     const void *wqkv, *wo, *cwq, *cwo, *win, *wout;
     const float *ln1, *lnc, *ln2;
@@ -227,12 +227,14 @@ struct PassArgs {
     float *x_out, *x_keep;    // the residual stream after the last layer: [T][d]; at [len ..] too (null: not kept)
     char* scratch;            // [n_layers][at.layer]
     PassPlan at;
+    int groups, die;          // workgroups that take part; 1: all on die 0
     int spins;                // polls (of about 0.7 us) after which a workgroup gives up
     unsigned* sync;           // [kPassSyncWords], zero before the pass; the policy kernel clears it
 };
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // workgroups, 0: not a shape it is made for
+int pass_die_groups(int d, int heads, int d_head, int F, bool gated);
 PassPlan pass_plan(int T, int d, int I, int F);
-hipError_t launch_pass(const PassArgs& a, int groups, hipStream_t st);
+hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st);
 
 struct EmbedArgs {
     TMat E;

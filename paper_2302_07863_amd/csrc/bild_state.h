@@ -145,6 +145,7 @@ struct ModelState {
     int rows_t = 0;           // rows these hold
     // whole passes in one kernel (pass_kernel.hip)
     int pass_groups = 0;      // workgroups; 0: the shape is not made for it
+    int pass_die_groups = 0;  // the same of the form on one die
     bild::PassLayer* pass_layers = nullptr;  // device
     char* pass_scratch = nullptr;
 };
@@ -161,9 +162,10 @@ struct bild_state {
     float alpha_fb = -1.f, alpha_rb = -1.f;  // thresholds currently in the device control block
     bool use_graphs = true;
     bool one_kernel = true;   // passes of up to kPassRows rows of a narrow bf16 model run as one kernel
+    bool one_die = true;      // ... on one die, if it fits
     unsigned* pass_sync = nullptr;
     int pass_spins = 6000;    // 4 ms: kernels of other streams come to an end in that time, the same kernel of another process does not
-    int device = 0;
+    int device = 0, cus = 0;
     bool has_turn = false;    // (see take_turn)
     int ksplit_max_d = 2048;      // ... of models up to this wide (7B-shaped small model, 2048 wide: 0.729 -> 0.717 ms per step)
     int ksplit_min_f = 2048;      // FFN widths from which the output projection of a narrow model (d <= 1024) is cut into input slices

@@ -19,8 +19,14 @@
 //   - a workgroup that owns sixteen features of the residual stream owns them in all layers: they stay in its registers (fp32);
 //   - the cross query is worked out by the workgroup of the head that uses it, which saves a hand-over.
 //
-// Per pass, us, before (a kernel per stage) and now, 512 source tokens: T5-small shape one row 149 -> 142; T5-large shape 1, 2, 5,
-// 8, 16 rows 683, 799, 977, 998, 1223 -> 634, 642, 653, 651, 730; mT5-large shape, 64 tokens, 1 and 8 rows 809, 1063 -> 709, 725.
+// A model small enough for the 32 compute units of one die (pass_die_groups: T5-small, mT5-small) walks there: what is handed over
+// then only goes to that die's L2 and back (1.2 us instead of 1.9), at 1.25 TB/s for the weights instead of the chip's 4.8, which
+// a layer of 7 MB in 17 us does not notice.  Workgroups of the other dies end at once.
+//
+// Per pass, us, before (a kernel per stage) and now, 512 source tokens: T5-small shape one row 149 -> 114 (on the
+// whole chip 139), mT5-small shape 257 -> 196 (224); T5-large shape 1, 2, 5,
+// 8, 16 rows 683, 799, 977, 998, 1223 -> 634, 642, 653, 651, 730; mT5-large shape, 64 tokens, 1 and 8 rows 809, 1063 ->
+// 709, 725.
 //
 // A workgroup that has polled `spins` times in vain flags the pass as failed and walks on without waiting again (nothing
 // handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
@@ -31,7 +37,6 @@
 namespace bild {
 
 constexpr int kPassWaves = 8, kPassThreads = 64 * kPassWaves;
-constexpr int kThrough = 17;       // buffer access flags sc0 sc1: through the caches
 
 typedef __attribute__((address_space(4))) const PassLayer CLayer;  // (read through the scalar cache)
 typedef __amdgpu_buffer_rsrc_t Rsrc;
@@ -46,16 +51,20 @@ __device__ __forceinline__ P* pinned(P* p) {
 __device__ __forceinline__ Rsrc whole(const void* p) { return make_rsrc(p, 0xFFFFFFFFu); }
 __device__ __forceinline__ float4 ldf4(Rsrc r, int off) { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0)); }
 __device__ __forceinline__ bf16x8 as_bf(const uint4& v) { return __builtin_bit_cast(bf16x8, v); }
+template <int AUX>
 __device__ __forceinline__ void st8(Rsrc r, int off, unsigned a, unsigned b) {
     const v2u v = {a, b};
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kThrough);
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, AUX);
 }
 
-// LDS: sums of the waves (up to four tiles each; attention joins its waves there too), their (max, sum), the head's query, the
+// LDS: sums of the waves (up to six tiles each; attention joins its waves there too), their (max, sum), the head's query, the
 // head's relative-position biases
-constexpr int kRed = 0, kMl = kPassWaves * 4 * 1024, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kRel = kQ + 16 * kQLd * 4;
+constexpr int kRed = 0, kMl = kPassWaves * 6 * 1024, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kRel = kQ + 16 * kQLd * 4;
 
+template <bool DIE>
 struct Walk {
+    // what is handed over goes as far as all readers see it: to the die's L2 (the L1s write through), or past the L2s (sc0 sc1)
+    static constexpr int kOut = DIE ? 0 : 17;
     char* lds;
     unsigned* counters;
     unsigned* failed;
@@ -76,7 +85,11 @@ struct Walk {
     __device__ __forceinline__ void expect(int base, int n) { target += (unsigned)(n + kPassCounters - 1 - ((lane - base) & (kPassCounters - 1))) / kPassCounters; }
     __device__ __forceinline__ void arrive() const {  // one wave, after its stores
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == 0) asm volatile("global_atomic_add %0, %1, off sc1" ::"v"(counters + (wg & (kPassCounters - 1)) * kPassStride), "v"(1u) : "memory");
+        if (lane == 0) {
+            unsigned* p = counters + (wg & (kPassCounters - 1)) * kPassStride;
+            if constexpr (DIE) asm volatile("global_atomic_add %0, %1, off" ::"v"(p), "v"(1u) : "memory");
+            else asm volatile("global_atomic_add %0, %1, off sc1" ::"v"(p), "v"(1u) : "memory");
+        }
     }
     __device__ __forceinline__ void wait() {
         if (wave == 0 && !dead) {
@@ -86,7 +99,8 @@ struct Walk {
             unsigned long long missing;
 #pragma unroll 1
             do {
-                asm volatile("global_load_dword %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
+                if constexpr (DIE) asm volatile("global_load_dword %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
+                else asm volatile("global_load_dword %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
                 missing = __builtin_amdgcn_ballot_w64((int)(v - target) < 0);
             } while (missing && ++n < spins);
             if (n >= spins) {
@@ -107,15 +121,17 @@ __device__ __forceinline__ Run run_of(int wave, int tk) {
     return {wave * per, max(0, min(per, tk - wave * per))};
 }
 
-template <int N, int RW>
-__device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const void* w, int unit, int tk) {
+// (tiles past the last of the `tiles` there are: the last one again)
+template <int N, int RW, class Walk>
+__device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const void* w, int unit, int tk, int tiles) {
     const Run r = run_of(c.wave, tk);
     const Rsrc rs = whole((const char*)w + (size_t)unit * RW * tk * kTileBytes);
+    const int most = tiles - 1 - unit * RW;
 #pragma unroll
     for (int j = 0; j < N; ++j)
         if (j < r.n) {
 #pragma unroll
-            for (int q = 0; q < RW; ++q) W[j * RW + q] = buf_load(rs, (unsigned)c.lane * 16u, (q * tk + r.k0 + j) * kTileBytes);
+            for (int q = 0; q < RW; ++q) W[j * RW + q] = buf_load(rs, (unsigned)c.lane * 16u, ((RW == 1 ? 0 : min(q, most)) * tk + r.k0 + j) * kTileBytes);
         }
 }
 
@@ -125,7 +141,7 @@ __device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const
 // Up to eight rows (PACK) one operand holds the high parts of the rows in its columns 0 .. 7 and the low parts in 8 .. 15: half
 // the loads and products (a compute unit's 64 bytes a cycle are what the FFN output's 256 loads of 1 KiB wait for); the halves
 // are added in total().  A quarter then has the rows' high parts and their low parts.
-template <int N, int RW, bool PACK>
+template <int N, int RW, bool PACK, class Walk>
 __device__ __forceinline__ void multiply(const Walk& c, f32x4 (&acc)[RW], const uint4 (&W)[N * RW], const void* planes, int tk) {
     const Run r = run_of(c.wave, tk);
     const Rsrc xs = whole(planes);
@@ -166,13 +182,13 @@ __device__ __forceinline__ void multiply(const Walk& c, f32x4 (&acc)[RW], const 
 }
 
 // The waves' results side by side in LDS; `tile`'s total over the waves, in wave order.
-template <int RW>
+template <int RW, class Walk>
 __device__ __forceinline__ void leave(const Walk& c, const f32x4 (&acc)[RW]) {
 #pragma unroll
     for (int q = 0; q < RW; ++q) *(f32x4*)(c.lds + kRed + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
     lds_barrier();
 }
-template <int RW, bool PACK>
+template <int RW, bool PACK, class Walk>
 __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
     f32x4 p[kPassWaves];
 #pragma unroll
@@ -190,6 +206,7 @@ __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
 // RMSNorm's factor of this lane's row from the owners' partial sums of squares, [t][d / 16]: requested and, later, added up.
 struct Norm {
     float4 v[4] = {};
+    template <class Walk>
     __device__ __forceinline__ void get(const Walk& c, const float* ssq, int nd) {
         const Rsrc r = whole(ssq);
         const int per = nd >> 2;
@@ -205,19 +222,19 @@ struct Norm {
 };
 
 // Sixteen features of a row's activations in that order: this lane's four.
-template <bool PACK>
+template <bool PACK, class Walk>
 __device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, const float (&w)[4]) {
     uint32_t h01, l01, h23, l23;
     split_bf16x2(w[0], w[1], h01, l01);
     split_bf16x2(w[2], w[3], h23, l23);
     const Rsrc r = whole(planes);
     const int off = (n0 >> 5) * c.T * 128 + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.T + c.tok) * 16 + (n0 & 7) * 2;
-    st8(r, off, h01, h23);
-    st8(r, off + (PACK ? 16 : 64) * c.T, l01, l23);
+    st8<Walk::kOut>(r, off, h01, h23);
+    st8<Walk::kOut>(r, off + (PACK ? 16 : 64) * c.T, l01, l23);
 }
 
 // Attention of one head over its keys for all rows: the waves take blocks of 32 keys in turn; (max, sum, O) joined through LDS.
-template <bool CAUSAL, bool PACK>
+template <bool CAUSAL, bool PACK, class Walk>
 struct Attend {
     const Rsrc kr, vr;
     const int I, cap, nkeys, nblk;
@@ -237,76 +254,112 @@ struct Attend {
             Vr[dt] = make_uint4(va.x, va.y, vb.x, vb.y);
         }
     }
-    // q: this lane's row and inputs g * 8 .. of both halves of the head (scaled)
+    // `query`: this lane's row and inputs g * 8 .. of both halves of the head.  Up to eight rows are packed as in multiply().
     template <class Query>
     __device__ __forceinline__ void run(const Walk& c, Query&& query, float scale, int len, const float* relb, int rel_d, void* out, int T, int h) {
-        bf16x8 Qh[2], Ql[2];
+        constexpr int P = PACK ? 1 : 2;
+        bf16x8 Q[2][P];  // scaled, high parts (columns 0 .. 7 if packed) and low parts
+        const bool low = c.tok >= 8;
+        const int row = PACK ? c.t8 : c.t;
+        // high and low parts of eight values in operand order
+        auto parts = [&](const float (&v)[8], bf16x8 (&o)[P]) {
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) split_bf16x2(v[2 * j], v[2 * j + 1], hi[j], lo[j]);
+            if constexpr (PACK) {
+                o[0] = as_bf(make_uint4(low ? lo[0] : hi[0], low ? lo[1] : hi[1], low ? lo[2] : hi[2], low ? lo[3] : hi[3]));
+            } else {
+                o[0] = as_bf(make_uint4(hi[0], hi[1], hi[2], hi[3]));
+                o[1] = as_bf(make_uint4(lo[0], lo[1], lo[2], lo[3]));
+            }
+        };
         auto split_query = [&](const float4 (&qv)[2][2]) {
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                uint32_t hi[4], lo[4];
-                split_bf16x2(qv[ks][0].x * scale, qv[ks][0].y * scale, hi[0], lo[0]);
-                split_bf16x2(qv[ks][0].z * scale, qv[ks][0].w * scale, hi[1], lo[1]);
-                split_bf16x2(qv[ks][1].x * scale, qv[ks][1].y * scale, hi[2], lo[2]);
-                split_bf16x2(qv[ks][1].z * scale, qv[ks][1].w * scale, hi[3], lo[3]);
-                Qh[ks] = as_bf(make_uint4(hi[0], hi[1], hi[2], hi[3]));
-                Ql[ks] = as_bf(make_uint4(lo[0], lo[1], lo[2], lo[3]));
+                const float v[8] = {qv[ks][0].x * scale, qv[ks][0].y * scale, qv[ks][0].z * scale, qv[ks][0].w * scale,
+                                    qv[ks][1].x * scale, qv[ks][1].y * scale, qv[ks][1].z * scale, qv[ks][1].w * scale};
+                parts(v, Q[ks]);
             }
         };
         float m_run = -INFINITY, l_run = 0.f;
         f32x4 O[4];
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const int lim = CAUSAL ? len + c.t : nkeys - 1;
-        auto process = [&](const uint4 (&Kr)[2][2], const uint4 (&Vr)[4], int blk) {
-            const int key0 = blk * 32;
-            f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        const int lim = CAUSAL ? len + row : nkeys - 1;  // the last key this row sees
+        const int safe = CAUSAL ? len : nkeys - 1;       // ... and every row
+        // NB blocks at once: one maximum, one rescaling
+        auto process = [&](auto nb, const uint4 (*const (&Kr)[decltype(nb)::value])[2], const uint4* const (&Vr)[decltype(nb)::value], const int (&blk)[decltype(nb)::value], bool first) {
+            constexpr int NB = decltype(nb)::value;
+            f32x4 s[NB][2];
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int ab = 0; ab < 2; ++ab) s[b][ab] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                for (int ab = 0; ab < 2; ++ab) {
-                    s[ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Kr[ab][ks]), Qh[ks], s[ab], 0, 0, 0);
-                    s[ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Kr[ab][ks]), Ql[ks], s[ab], 0, 0, 0);
-                }
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+#pragma unroll
+                        for (int ab = 0; ab < 2; ++ab) s[b][ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Kr[b][ab][ks]), Q[ks][p], s[b][ab], 0, 0, 0);
+            if constexpr (PACK) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) s[b][v >> 2][v & 3] += dpp_f<0x128, 0xF>(0.f, s[b][v >> 2][v & 3]);
+            }
             if (CAUSAL && relb) {
 #pragma unroll
-                for (int ab = 0; ab < 2; ++ab)
+                for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) s[ab][v] += relb[rel_d + max(-rel_d, min(rel_d, key0 + ab * 16 + c.g * 4 + v - (len + c.t)))];
+                    for (int v = 0; v < 8; ++v)
+                        s[b][v >> 2][v & 3] += relb[rel_d + max(-rel_d, min(rel_d, blk[b] * 32 + (v >> 2) * 16 + c.g * 4 + (v & 3) - (len + row)))];
             }
-            float tmax = -INFINITY;
+            if (blk[NB - 1] * 32 + 31 > safe) {
 #pragma unroll
-            for (int ab = 0; ab < 2; ++ab)
+                for (int b = 0; b < NB; ++b)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int key = key0 + ab * 16 + c.g * 4 + v;
-                    if (key > lim) s[ab][v] = -INFINITY;
-                    tmax = fmaxf(tmax, s[ab][v]);
+                    for (int v = 0; v < 8; ++v)
+                        if (blk[b] * 32 + (v >> 2) * 16 + c.g * 4 + (v & 3) > lim) s[b][v >> 2][v & 3] = -INFINITY;
+            }
+            float tmax = m_run;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int v = 0; v < 8; ++v) tmax = fmaxf(tmax, s[b][v >> 2][v & 3]);
+            const float m_new = quad_rows_max(tmax), base = m_new == -INFINITY ? 0.f : m_new;
+            bf16x8 W[NB][P];
+            float psum = 0.f;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                float p[8];
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    p[v] = fexp(s[b][v >> 2][v & 3] - base);
+                    psum += p[v];
                 }
-            tmax = quad_rows_max(tmax);
-            const float m_new = fmaxf(m_run, tmax);
-            const float f = m_run == -INFINITY ? 0.f : fexp(m_run - m_new);
-            float p[2][4], psum = 0.f;
+                parts(p, W[b]);
+            }
+            psum = quad_rows_sum(psum);
+            if (first) {
+                l_run = psum;
+            } else {
+                const float f = fexp(m_run - base);
+                l_run = l_run * f + psum;
 #pragma unroll
-            for (int ab = 0; ab < 2; ++ab)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    p[ab][v] = m_new == -INFINITY ? 0.f : fexp(s[ab][v] - m_new);
-                    psum += p[ab][v];
-                }
-            l_run = l_run * f + quad_rows_sum(psum);
+                for (int dt = 0; dt < 4; ++dt) O[dt] *= f;
+            }
             m_run = m_new;
-            uint32_t ph[4], pl[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) split_bf16x2(p[j >> 1][(j & 1) * 2], p[j >> 1][(j & 1) * 2 + 1], ph[j], pl[j]);
-            const bf16x8 Ph = as_bf(make_uint4(ph[0], ph[1], ph[2], ph[3])), Pl = as_bf(make_uint4(pl[0], pl[1], pl[2], pl[3]));
+            for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt) {
-                O[dt] *= f;
-                O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Vr[dt]), Ph, O[dt], 0, 0, 0);
-                O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Vr[dt]), Pl, O[dt], 0, 0, 0);
-            }
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt) O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Vr[b][dt]), W[b][p], O[dt], 0, 0, 0);
         };
+        using One = std::integral_constant<int, 1>;
+        using Two = std::integral_constant<int, 2>;
         if constexpr (CAUSAL) {  // (few blocks: a wave without one requests nothing)
             if (c.wave < nblk) {
                 float4 qv[2][2];
@@ -321,23 +374,21 @@ struct Attend {
                     asm volatile("" : "+v"(V0[i].x), "+v"(V0[i].y), "+v"(V0[i].z), "+v"(V0[i].w));
                 }
                 split_query(qv);
-                process(K0, V0, c.wave);
+                process(One{}, {K0}, {V0}, {c.wave}, true);
             }
             for (int blk = c.wave + kPassWaves; blk < nblk; blk += kPassWaves) {
                 load(c, K0, V0, blk);
-                process(K0, V0, blk);
+                process(One{}, {K0}, {V0}, {blk}, false);
             }
         } else {
             float4 qv[2][2];
             query(qv);
             split_query(qv);
             for (int blk = c.wave; blk < nblk; blk += 2 * kPassWaves) {
-                process(K0, V0, blk);
+                if (blk + kPassWaves < nblk) process(Two{}, {K0, K1}, {V0, V1}, {blk, blk + kPassWaves}, blk == c.wave);
+                else process(One{}, {K0}, {V0}, {blk}, blk == c.wave);
                 if (blk + 2 * kPassWaves < nblk) load(c, K0, V0, blk + 2 * kPassWaves);
-                if (blk + kPassWaves < nblk) {
-                    process(K1, V1, blk + kPassWaves);
-                    if (blk + 3 * kPassWaves < nblk) load(c, K1, V1, blk + 3 * kPassWaves);
-                }
+                if (blk + 3 * kPassWaves < nblk) load(c, K1, V1, blk + 3 * kPassWaves);
             }
         }
         float* cm = (float*)(c.lds + kMl);
@@ -352,14 +403,19 @@ struct Attend {
             f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int v = 0; v < kPassWaves; ++v) {
-                w[v] = cm[v * 16 + c.tok];
+                w[v] = v < nblk ? cm[v * 16 + c.tok] : -INFINITY;
                 M = fmaxf(M, w[v]);
             }
 #pragma unroll
-            for (int v = 0; v < kPassWaves; ++v) {
-                w[v] = w[v] == -INFINITY ? 0.f : fexp(w[v] - M);
-                L += cl[v * 16 + c.tok] * w[v];
-                o += *(const f32x4*)(c.lds + kRed + ((v * 4 + c.wave) * 64 + c.lane) * 16) * w[v];
+            for (int v = 0; v < kPassWaves; ++v)
+                if (v < nblk) {  // (waves with keys)
+                    w[v] = fexp(w[v] - M);
+                    L += cl[v * 16 + c.tok] * w[v];
+                    o += *(const f32x4*)(c.lds + kRed + ((v * 4 + c.wave) * 64 + c.lane) * 16) * w[v];
+                }
+            if constexpr (PACK) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[v] += dpp_f<0x128, 0xF>(0.f, o[v]);
             }
             const float inv = 1.f / L;
             const float r[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
@@ -371,54 +427,86 @@ struct Attend {
     }
 };
 
-// Workgroups [0, workers) do the projections; the first d / 16 of them own sixteen features of the residual stream each.
-template <bool GATED, bool PACK>
-__device__ __forceinline__ void worker(Walk& c, const PassArgs& a) {
+// How the projections are cut: feature tiles per workgroup of q, k, v (QT), of the residual stream (OT), of the FFN (FT, pairs of
+// tiles where it is gated), input tiles per wave of the model's width (KD) and of the FFN's hidden state (KF).
+struct ChipCut {
+    static constexpr int QT = 1, OT = 1, FT = 2, KD = 4, KF = 16;
+};
+struct DieCut {
+    static constexpr int QT = 4, OT = 2, FT = 6, KD = 2, KF = 8;
+};
+__host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Workgroups [0, workers) do the projections; the first of them own sixteen features (OT times) of the residual stream each: wave
+// q holds those of tile q.
+template <bool GATED, bool PACK, class Cut, class Walk>
+__device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
+    constexpr int QT = Cut::QT, OT = Cut::OT, FT = Cut::FT, KD = Cut::KD, KF = Cut::KF;
     int T = a.T, d = a.d, I = a.I, F = a.F;
-    const int base = (int)gridDim.x - a.heads;  // the workgroups with a head each follow
+    const int base = groups - a.heads;  // the workgroups with a head each follow
     const int len = *a.len_ptr;
     auto nd = [&] { return d >> 4; };
-    auto nq = [&] { return 3 * (I >> 4); };
-    auto nf = [&] { return GATED ? F >> 4 : F >> 5; };  // two tiles each
-    const bool owner = c.wg < nd(), qkv = c.wg < nq(), ffn = c.wg < nf();
-    uint4 Wq[4], Wo[4], Wi[8], Wf[16];
+    auto tq = [&] { return 3 * (I >> 4); };
+    auto tf = [&] { return GATED ? F >> 3 : F >> 4; };  // tiles
+    auto no = [&] { return ceil_div(nd(), OT); };
+    auto nq = [&] { return ceil_div(tq(), QT); };
+    auto nf = [&] { return ceil_div(tf(), FT); };       // workgroups
+    const bool owner = c.wg < no(), qkv = c.wg < nq(), ffn = c.wg < nf();
+    uint4 Wq[KD * QT], Wo[KD * OT], Wi[KD * FT], Wf[KF * OT];
     float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f);
-    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);  // (owners, wave 0) the residual stream of this lane's row, features n0 .. n0 + 3
-    auto n0 = [&] { return c.wg * 16 + c.g * 4; };
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);  // (owners, waves below OT) the residual stream of this lane's row, features n0 .. n0 + 3
+    const bool mine = c.wave < OT && c.wg * OT + c.wave < nd();
+    auto n0 = [&] { return (c.wg * OT + c.wave) * 16 + c.g * 4; };
     // the gain of the norm that reads x next, requested before the wait for what is added to it
-    auto gain = [&](const float* g) { return ldf4(whole(g), n0() * 4); };
-    auto publish = [&](const float4& gn, char* planes, char* ssq) {
-        const float w[4] = {x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w};
-        const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
-        if (c.tok < T) {
-            put_planes<PACK>(c, planes, n0(), w);
-            if (c.g == 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(ssq), (c.tok * nd() + c.wg) * 4, 0, kThrough);
+    auto gain = [&](const float* g) { return ldf4(whole(g), mine ? n0() * 4 : 0); };
+    // the waves that had something to write have written it
+    auto done = [&](auto waves) {
+        if constexpr (decltype(waves)::value > 1) {
+            if (c.wave < decltype(waves)::value) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lds_barrier();
         }
-        c.arrive();
+        if (c.wave == 0) c.arrive();
     };
-    auto add = [&](const f32x4& s) { x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]); };
+    using OWaves = std::integral_constant<int, OT>;
+    auto publish = [&](const float4& gn, char* planes, char* ssq) {
+        if (mine) {
+            const float w[4] = {x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w};
+            const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
+            if (c.tok < T) {
+                put_planes<PACK>(c, planes, n0(), w);
+                if (c.g == 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(ssq), (c.tok * nd() + c.wg * OT + c.wave) * 4, 0, Walk::kOut);
+            }
+        }
+        done(OWaves{});
+    };
+    auto add = [&] {
+        const f32x4 s = total<OT, PACK>(c, c.wave);
+        x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]);
+    };
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
     char* z = a.scratch;  // this layer's hand-over buffers
-    if (owner && c.wave == 0) {
+    if (owner) {
         const int pos = len + c.t;
         const float4 gn = gain(L->ln1);
-        if (a.emb) {
-            int er = a.tokens[pos] + a.tie_shift;
-            er = er >= a.vocab ? er - a.vocab : er;
-            const char* p = (const char*)a.emb + ((size_t)(er >> 4) * (d >> 5) + (n0() >> 5)) * kTileBytes + ((er & 15) + 16 * ((n0() & 31) >> 3)) * 16 + (n0() & 7) * 2;
-            const uint2 raw = *(const uint2*)p;
-            float4 pe = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (a.pe) pe = *(const float4*)(a.pe + (size_t)pos * d + n0());
-            const float sc = a.embed_scale;
-            x = make_float4(__builtin_fmaf(bf2f(raw.x & 0xFFFFu), sc, pe.x), __builtin_fmaf(bf2f(raw.x >> 16), sc, pe.y),
-                            __builtin_fmaf(bf2f(raw.y & 0xFFFFu), sc, pe.z), __builtin_fmaf(bf2f(raw.y >> 16), sc, pe.w));
-        } else {
-            x = *(const float4*)(a.x_in + (size_t)pos * d + n0());
+        if (mine) {
+            if (a.emb) {
+                int er = a.tokens[pos] + a.tie_shift;
+                er = er >= a.vocab ? er - a.vocab : er;
+                const char* p = (const char*)a.emb + ((size_t)(er >> 4) * (d >> 5) + (n0() >> 5)) * kTileBytes + ((er & 15) + 16 * ((n0() & 31) >> 3)) * 16 + (n0() & 7) * 2;
+                const uint2 raw = *(const uint2*)p;
+                float4 pe = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (a.pe) pe = *(const float4*)(a.pe + (size_t)pos * d + n0());
+                const float sc = a.embed_scale;
+                x = make_float4(__builtin_fmaf(bf2f(raw.x & 0xFFFFu), sc, pe.x), __builtin_fmaf(bf2f(raw.x >> 16), sc, pe.y),
+                                __builtin_fmaf(bf2f(raw.y & 0xFFFFu), sc, pe.z), __builtin_fmaf(bf2f(raw.y >> 16), sc, pe.w));
+            } else {
+                x = *(const float4*)(a.x_in + (size_t)pos * d + n0());
+            }
         }
         publish(gn, z + a.at.x1, z + a.at.s1);
     }
-    if (qkv) request<4, 1>(c, Wq, L->wqkv, c.wg, d >> 5);
-    c.expect(0, nd());
+    if (qkv) request<KD, QT>(c, Wq, L->wqkv, c.wg, d >> 5, tq());
+    c.expect(0, no());
     for (int l = 0; l < a.n_layers; ++l, z += a.at.layer) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         const bool last = l + 1 == a.n_layers;
@@ -426,35 +514,35 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a) {
         asm volatile("" : "+v"(c.lane));
         asm volatile("" : "+s"(T), "+s"(d), "+s"(I), "+s"(F));
         c.place(T);
-        // ---- q, k, v ----
+        // ---- q, k, v (a workgroup's tiles are of one of the three) ----
         if (qkv) {
             const char *xs = pinned(z + a.at.x1), *ss = pinned(z + a.at.s1);
-            const int ni = I >> 4;
-            char* out = pinned(c.wg < ni ? z + a.at.q : c.wg < 2 * ni ? L->kc : L->vc);
+            const int seg = c.wg * QT * 16 / I;
+            char* out = pinned(seg == 0 ? z + a.at.q : seg == 1 ? L->kc : L->vc);
             c.wait();
             Norm nm;
-            if (c.wave == 0) nm.get(c, (const float*)ss, nd());
-            f32x4 acc[1];
-            multiply<4, 1, PACK>(c, acc, Wq, xs, d >> 5);
+            if (c.wave < QT) nm.get(c, (const float*)ss, nd());
+            f32x4 acc[QT];
+            multiply<KD, QT, PACK>(c, acc, Wq, xs, d >> 5);
             const float f = nm.factor(d, a.eps);
-            leave<1>(c, acc);
-            if (c.wave == 0) {
-                const f32x4 s = total<1, PACK>(c, 0) * f;
-                const int seg = c.wg < ni ? 0 : c.wg < 2 * ni ? 1 : 2, nn = n0() - seg * I, pos = len + c.tok;
+            leave<QT>(c, acc);
+            if (c.wave < QT) {
+                const f32x4 s = total<QT, PACK>(c, c.wave) * f;
+                const int nn = (c.wg * QT + c.wave) * 16 + c.g * 4 - seg * I, pos = len + c.tok;
+                const Rsrc o = whole(out);
                 if (c.tok < T) {
                     if (seg == 0) {
                         const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
-                        __builtin_amdgcn_raw_buffer_store_b128(v, whole(out), (c.tok * I + nn) * 4, 0, kThrough);
+                        __builtin_amdgcn_raw_buffer_store_b128(v, o, (c.tok * I + nn) * 4, 0, Walk::kOut);
                     } else if (seg == 1) {
-                        st8(whole(out), (pos * I + nn) * 2, pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
+                        st8<Walk::kOut>(o, (pos * I + nn) * 2, pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
                     } else {
-                        const Rsrc vr = whole(out);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)f2bf(s[v]), vr, ((nn + v) * a.vcap + pos) * 2, 0, kThrough);
+                        for (int v = 0; v < 4; ++v) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)f2bf(s[v]), o, ((nn + v) * a.vcap + pos) * 2, 0, Walk::kOut);
                     }
                 }
-                c.arrive();
             }
+            done(std::integral_constant<int, QT>{});
         }
         c.expect(0, nq());
         c.expect(base, a.heads);  // (self-attention)
@@ -462,110 +550,100 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a) {
         // Requests go out where the workgroup has several microseconds before it is needed again (a wave's loads come back in
         // order: what is asked for late delays the next stage's activations): here, while the heads work, and below.
         if (owner) {
-            request<4, 1>(c, Wo, L->wo, c.wg, I >> 5);
+            request<KD, OT>(c, Wo, L->wo, c.wg, I >> 5, nd());
             const float4 gn = gain(a.cross ? L->lnc : L->ln2);
             if (!a.cross) {
                 next_gain = gain(last ? L->ln2 : L[1].ln1);
-                request<16, 1>(c, Wf, L->wout, c.wg, F >> 5);
+                request<KF, OT>(c, Wf, L->wout, c.wg, F >> 5, nd());
             }
             const char* xs = pinned(z + a.at.a1);
             char *ox = pinned(z + a.at.x2), *os = pinned(z + a.at.s2);
             c.wait();
-            f32x4 acc[1];
-            multiply<4, 1, PACK>(c, acc, Wo, xs, I >> 5);
-            leave<1>(c, acc);
-            if (c.wave == 0) {
-                add(total<1, PACK>(c, 0));
-                publish(gn, ox, os);
-            }
+            f32x4 acc[OT];
+            multiply<KD, OT, PACK>(c, acc, Wo, xs, I >> 5);
+            leave<OT>(c, acc);
+            if (mine) add();
+            publish(gn, ox, os);
         }
-        c.expect(0, nd());
+        c.expect(0, no());
         const char *xf = z + a.at.x2, *sf = z + a.at.s2;  // what the FFN reads
         if (a.cross) {
             c.expect(base, a.heads);
             // ---- output projection of the cross-attention ----
             if (owner) {
-                request<4, 1>(c, Wo, L->cwo, c.wg, I >> 5);
+                request<KD, OT>(c, Wo, L->cwo, c.wg, I >> 5, nd());
                 const float4 gn = gain(L->ln2);
                 next_gain = gain(last ? L->ln2 : L[1].ln1);
-                if (ffn) request<4, 2>(c, Wi, L->win, c.wg, d >> 5);
-                request<16, 1>(c, Wf, L->wout, c.wg, F >> 5);
-                if (qkv && !last) request<4, 1>(c, Wq, L[1].wqkv, c.wg, d >> 5);
+                if (ffn) request<KD, FT>(c, Wi, L->win, c.wg, d >> 5, tf());
+                request<KF, OT>(c, Wf, L->wout, c.wg, F >> 5, nd());
+                if (qkv && !last) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> 5, tq());
                 const char* xs = pinned(z + a.at.a2);
                 char *ox = pinned(z + a.at.x3), *os = pinned(z + a.at.s3);
                 c.wait();
-                f32x4 acc[1];
-                multiply<4, 1, PACK>(c, acc, Wo, xs, I >> 5);
-                leave<1>(c, acc);
-                if (c.wave == 0) {
-                    add(total<1, PACK>(c, 0));
-                    publish(gn, ox, os);
-                }
+                f32x4 acc[OT];
+                multiply<KD, OT, PACK>(c, acc, Wo, xs, I >> 5);
+                leave<OT>(c, acc);
+                if (mine) add();
+                publish(gn, ox, os);
             }
-            c.expect(0, nd());
+            c.expect(0, no());
             xf = z + a.at.x3;
             sf = z + a.at.s3;
         }
         // ---- FFN ----
         if (ffn) {
-            if (!owner || !a.cross) request<4, 2>(c, Wi, L->win, c.wg, d >> 5);
+            if (!owner || !a.cross) request<KD, FT>(c, Wi, L->win, c.wg, d >> 5, tf());
             const char *xs = pinned(xf), *ss = pinned(sf);
             char* out = pinned(z + a.at.h);
             c.wait();
+            constexpr int FW = GATED ? FT / 2 : FT;  // waves with results
             Norm nm;
-            if (c.wave == 0) nm.get(c, (const float*)ss, nd());
-            f32x4 acc[2];
-            multiply<4, 2, PACK>(c, acc, Wi, xs, d >> 5);
+            if (c.wave < FW) nm.get(c, (const float*)ss, nd());
+            f32x4 acc[FT];
+            multiply<KD, FT, PACK>(c, acc, Wi, xs, d >> 5);
             const float r = nm.factor(d, a.eps);
-            leave<2>(c, acc);
-            if (c.wave == 0) {
-                const f32x4 s = total<2, PACK>(c, 0) * r, u = total<2, PACK>(c, 1) * r;
+            leave<FT>(c, acc);
+            const int tile = c.wg * FW + c.wave;  // of the hidden state
+            if (c.wave < FW && tile < F >> 4) {
                 float w[4];
                 if constexpr (GATED) {
+                    const f32x4 s = total<FT, PACK>(c, 2 * c.wave) * r, u = total<FT, PACK>(c, 2 * c.wave + 1) * r;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(s[v]) : silu_f(s[v])) * u[v];
-                    if (c.tok < T) put_planes<PACK>(c, out, n0(), w);
                 } else {
-                    float y[4];
+                    const f32x4 s = total<FT, PACK>(c, c.wave) * r;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        w[v] = fmaxf(s[v], 0.f);
-                        y[v] = fmaxf(u[v], 0.f);
-                    }
-                    if (c.tok < T) {
-                        put_planes<PACK>(c, out, c.wg * 32 + c.g * 4, w);
-                        put_planes<PACK>(c, out, c.wg * 32 + 16 + c.g * 4, y);
-                    }
+                    for (int v = 0; v < 4; ++v) w[v] = fmaxf(s[v], 0.f);
                 }
-                c.arrive();
+                if (c.tok < T) put_planes<PACK>(c, out, tile * 16 + c.g * 4, w);
             }
+            done(std::integral_constant<int, FW>{});
         }
         c.expect(0, nf());
-        if (qkv && !last && (!owner || !a.cross)) request<4, 1>(c, Wq, L[1].wqkv, c.wg, d >> 5);
+        if (qkv && !last && (!owner || !a.cross)) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> 5, tq());
         if (owner) {
             const char* xs = pinned(z + a.at.h);
             char *ox = pinned(z + a.at.layer + a.at.x1), *os = pinned(z + a.at.layer + a.at.s1);
             c.wait();
-            f32x4 acc[1];
-            multiply<16, 1, PACK>(c, acc, Wf, xs, F >> 5);
-            leave<1>(c, acc);
-            if (c.wave == 0) {
-                add(total<1, PACK>(c, 0));
-                if (!last) publish(next_gain, ox, os);
-            }
+            f32x4 acc[OT];
+            multiply<KF, OT, PACK>(c, acc, Wf, xs, F >> 5);
+            leave<OT>(c, acc);
+            if (mine) add();
+            if (!last) publish(next_gain, ox, os);
         }
-        c.expect(0, nd());
+        c.expect(0, no());
     }
-    if (owner && c.wave == 0 && c.tok < T) {
+    if (owner && mine && c.tok < T) {
         *(float4*)(a.x_out + (size_t)c.tok * d + n0()) = x;
         if (a.x_keep) *(float4*)(a.x_keep + (size_t)(len + c.tok) * d + n0()) = x;
     }
 }
 
 // The last `heads` workgroups: a head each, of the self-attention and of the cross-attention (query included).
-template <bool GATED, bool PACK>
-__device__ __forceinline__ void header(Walk& c, const PassArgs& a) {
-    const int base = (int)gridDim.x - a.heads, h = c.wg - base;
+template <bool GATED, bool PACK, class Cut, class Walk>
+__device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
+    constexpr int KD = Cut::KD;
+    const int base = groups - a.heads, h = c.wg - base;
     int T = a.T, d = a.d, I = a.I;
     const int len = *a.len_ptr, nsrc = a.cross ? *a.nsrc_ptr : 0;
     const float* relb = nullptr;
@@ -575,25 +653,25 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a) {
         for (int i = threadIdx.x; i < n; i += kPassThreads) r[i] = a.rel_bias[(size_t)h * n + i];
         relb = r;
     }
-    uint4 Wc[16];  // of the cross query
+    uint4 Wc[KD * 4];  // of the cross query
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
     char* z = a.scratch;
-    if (a.cross) request<4, 4>(c, Wc, L->cwq, h, d >> 5);
-    c.expect(0, d >> 4);
+    if (a.cross) request<KD, 4>(c, Wc, L->cwq, h, d >> 5, I >> 4);
+    c.expect(0, ceil_div(d >> 4, Cut::OT));
     for (int l = 0; l < a.n_layers; ++l, z += a.at.layer) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         asm volatile("" : "+v"(c.lane));
         asm volatile("" : "+s"(T), "+s"(d), "+s"(I));
         c.place(T);
-        c.expect(0, 3 * (I >> 4));
+        c.expect(0, ceil_div(3 * (I >> 4), Cut::QT));
         // the cross-attention's keys and values while the heads have nothing else to do
-        Attend<false, PACK> cross = {whole(L->ck + (size_t)h * 128), whole(L->cv + (size_t)h * 64 * a.scap * 2), I, a.scap, nsrc, (nsrc + 31) >> 5, {}, {}, {}, {}};
+        Attend<false, PACK, Walk> cross = {whole(L->ck + (size_t)h * 128), whole(L->cv + (size_t)h * 64 * a.scap * 2), I, a.scap, nsrc, (nsrc + 31) >> 5, {}, {}, {}, {}};
         if (a.cross) {
             cross.load(c, cross.K0, cross.V0, c.wave);
             if (cross.nblk > kPassWaves) cross.load(c, cross.K1, cross.V1, c.wave + kPassWaves);
         }
         {
-            Attend<true, PACK> at = {whole(pinned(L->kc + (size_t)h * 128)), whole(pinned(L->vc + (size_t)h * 64 * a.vcap * 2)), I, a.vcap, len + T, (len + T + 31) >> 5, {}, {}, {}, {}};
+            Attend<true, PACK, Walk> at = {whole(pinned(L->kc + (size_t)h * 128)), whole(pinned(L->vc + (size_t)h * 64 * a.vcap * 2)), I, a.vcap, len + T, (len + T + 31) >> 5, {}, {}, {}, {}};
             const Rsrc qr = whole(pinned(z + a.at.q));
             char* out = pinned(z + a.at.a1);
             const float sc = a.att_scale;
@@ -602,12 +680,12 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a) {
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) qv[ks][p] = ldf4(qr, (c.t * I + h * 64 + ks * 32 + c.g * 8 + p * 4) * 4);
+                    for (int p = 0; p < 2; ++p) qv[ks][p] = ldf4(qr, ((PACK ? c.t8 : c.t) * I + h * 64 + ks * 32 + c.g * 8 + p * 4) * 4);
             };
             at.run(c, query, sc, len, relb, a.rel_d, out, T, h);
         }
         c.expect(base, a.heads);
-        c.expect(0, d >> 4);
+        c.expect(0, ceil_div(d >> 4, Cut::OT));
         if (a.cross) {
             const char *xs = pinned(z + a.at.x2), *ss = pinned(z + a.at.s2);
             char* out = pinned(z + a.at.a2);
@@ -616,7 +694,7 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a) {
             Norm nm;
             if (c.wave < 4) nm.get(c, (const float*)ss, d >> 4);
             f32x4 acc[4];
-            multiply<4, 4, PACK>(c, acc, Wc, xs, d >> 5);
+            multiply<KD, 4, PACK>(c, acc, Wc, xs, d >> 5);
             const float f = nm.factor(d, a.eps);
             leave<4>(c, acc);
             float* q = (float*)(c.lds + kQ);
@@ -629,22 +707,23 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a) {
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) qv[ks][p] = *(const float4*)(q + c.t * kQLd + ks * 32 + c.g * 8 + p * 4);
+                    for (int p = 0; p < 2; ++p) qv[ks][p] = *(const float4*)(q + (PACK ? c.t8 : c.t) * kQLd + ks * 32 + c.g * 8 + p * 4);
             };
             cross.run(c, query, sc, len, nullptr, 0, out, T, h);
-            if (l + 1 < a.n_layers) request<4, 4>(c, Wc, L[1].cwq, h, d >> 5);
+            if (l + 1 < a.n_layers) request<KD, 4>(c, Wc, L[1].cwq, h, d >> 5, I >> 4);
             c.expect(base, a.heads);
-            c.expect(0, d >> 4);
+            c.expect(0, ceil_div(d >> 4, Cut::OT));
         }
-        c.expect(0, GATED ? a.F >> 4 : a.F >> 5);
-        c.expect(0, d >> 4);
+        c.expect(0, ceil_div(GATED ? a.F >> 3 : a.F >> 4, Cut::FT));
+        c.expect(0, ceil_div(d >> 4, Cut::OT));
     }
 }
 
-template <bool GATED, bool PACK>
+template <bool GATED, bool PACK, bool DIE>
 __global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    Walk c;
+    using Cut = std::conditional_t<DIE, DieCut, ChipCut>;
+    Walk<DIE> c;
     c.lds = smem;
     c.counters = a.sync;
     c.failed = a.sync + kPassSyncWords - 1;
@@ -652,20 +731,46 @@ __global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a)
     c.wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     c.lane = (int)threadIdx.x & 63;
     c.wg = (int)blockIdx.x;
+    if constexpr (DIE) {  // the workgroups of die 0 in the order in which they get here
+        if (__builtin_amdgcn_s_getreg((3 << 11) | 20) != 0) return;
+        if (threadIdx.x == 0) {
+            unsigned rank;
+            asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)" : "=v"(rank) : "v"(a.sync + kPassCounters * kPassStride), "v"(1u) : "memory");
+            *(unsigned*)smem = rank;
+        }
+        lds_barrier();
+        c.wg = __builtin_amdgcn_readfirstlane(*(volatile int*)smem);
+        if (c.wg >= a.groups) return;
+        lds_barrier();
+    }
     c.place(a.T);
     c.target = 0;
     c.dead = false;
-    if (c.wg < (int)gridDim.x - a.heads) worker<GATED, PACK>(c, a);
-    else header<GATED, PACK>(c, a);
+    if (c.wg < a.groups - a.heads) worker<GATED, PACK, Cut>(c, a, a.groups);
+    else header<GATED, PACK, Cut>(c, a, a.groups);
 }
 
-// Sizes the kernel is made for: one unit of every stage per workgroup, runs of inputs that fit the registers (four tiles a
-// wave, sixteen of the FFN's hidden state).  Wider models are bound by the weights' bandwidth, not by the hand-overs.
+template <class Cut>
+static int cut_groups(int d, int heads, int F, bool gated) {
+    return std::max(std::max(ceil_div(3 * heads * 4, Cut::QT), ceil_div(gated ? F / 8 : F / 16, Cut::FT)), ceil_div(d / 16, Cut::OT)) + heads;
+}
+template <class Cut>
+static bool cut_fits(int d, int I, int F) {
+    return ceil_div(std::max(d, I) / 32, kPassWaves) <= Cut::KD && ceil_div(F / 32, kPassWaves) <= Cut::KF;
+}
+
+// Sizes the kernel is made for: runs of inputs that fit the registers, the workgroups on the chip at once.  Wider models are bound
+// by the weights' bandwidth, not by the hand-overs.
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
-    const int I = heads * d_head;
-    if (d_head != 64 || d % 256 != 0 || d > 1024 || I > 1024 || F % 32 != 0 || F > 4096) return 0;
-    const int g = std::max(std::max(3 * I / 16, gated ? F / 16 : F / 32), d / 16) + heads;
+    if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<ChipCut>(d, heads * 64, F)) return 0;
+    const int g = cut_groups<ChipCut>(d, heads, F, gated);
     return g <= cus ? g : 0;
+}
+// ... and of the form on one die: all of it on the 32 compute units of one.
+int pass_die_groups(int d, int heads, int d_head, int F, bool gated) {
+    if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<DieCut>(d, heads * 64, F)) return 0;
+    const int g = cut_groups<DieCut>(d, heads, F, gated);
+    return g <= 32 ? g : 0;
 }
 
 PassPlan pass_plan(int T, int d, int I, int F) {
@@ -684,14 +789,17 @@ PassPlan pass_plan(int T, int d, int I, int F) {
     return p;
 }
 
-hipError_t launch_pass(const PassArgs& a, int groups, hipStream_t st) {
-    if (groups < 1 || a.T < 1 || a.T > kPassRows || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr || (a.cross && !a.nsrc_ptr)) return hipErrorInvalidValue;
+hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
+    if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > (a.die ? kPassDieRows : kPassRows) || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
+        (a.cross && !a.nsrc_ptr))
+        return hipErrorInvalidValue;
     const size_t smem = kRel + (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);
     if (smem > 64 * 1024) return hipErrorInvalidValue;
     const bool gated = a.act != BILD_ACT_RELU;
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(groups), dim3(kPassThreads), smem, st, a); };
-    if (a.T <= 8) gated ? go(pass_kernel<true, true>) : go(pass_kernel<false, true>);
-    else gated ? go(pass_kernel<true, false>) : go(pass_kernel<false, false>);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kPassThreads), smem, st, a); };
+    if (a.die) gated ? go(pass_kernel<true, true, true>) : go(pass_kernel<false, true, true>);
+    else if (a.T <= 8) gated ? go(pass_kernel<true, true, false>) : go(pass_kernel<false, true, false>);
+    else gated ? go(pass_kernel<true, false, false>) : go(pass_kernel<false, false, false>);
     return hipGetLastError();
 }
 
