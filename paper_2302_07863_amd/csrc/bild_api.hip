@@ -639,7 +639,6 @@ GemmArgs gemm_base(const bild_model* m, const TMat& W, const float* x, int ldx, 
     g.eps = m->cfg.norm_eps;
     g.d_head = m->cfg.d_head;
     g.i_dim = m->inner();
-    g.rope_base = m->cfg.rope_base;
     g.act = m->cfg.act;
     g.vocab = m->cfg.vocab;
     return g;
@@ -1005,7 +1004,7 @@ int emit_layers(bild_state* s, int w, int T, int key_hint, bool reads_hidden, bo
             g.v_cache = vc;
             g.vcap = s->cap_len;
             g.pos_ptr = len_ptr;
-            g.rope = c.pos == BILD_POS_ROPE;
+            g.rope = M.rope;
             set_in(g);
             if (embed_in_proj && l == layer0) {
                 g.e_w = e.E.w; g.e_tk = e.E.tk; g.e_tokens = e.tokens; g.e_base_ptr = e.base_ptr; g.e_base_add = e.base_add;
@@ -1464,7 +1463,7 @@ int run_encoder(bild_state* s, int w) {
             g.k_cache = M.enc_k;
             g.v_cache = M.enc_v;
             g.vcap = s->cap_src;
-            g.rope = c.pos == BILD_POS_ROPE;
+            g.rope = M.rope;
             int rc = run_gemm(s, m, g);
             if (rc) return rc;
         }

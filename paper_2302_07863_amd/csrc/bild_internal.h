@@ -86,8 +86,7 @@ struct GemmArgs {
     int vcap;
     const int* pos_ptr;  // position of row 0 = (pos_ptr ? *pos_ptr : 0) + pos_add
     int pos_add;
-    int rope;
-    float rope_base;
+    const double2* rope;  // rotary positions: cos and sin per position and pair (null: none)
     int d_head;
     // EPI_ACT
     int act;

@@ -667,6 +667,20 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const int vblock, c
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[r][j] += acc2[r][j];
     if constexpr (PRE && norm) ssq_reduce();
+    // Rotary positions: cos and sin (double precision) of this lane's pairs, requested here, to arrive during the reduction.
+    // (Worked out here they were a power, a sine and a cosine in double precision per pair at the end of every workgroup.)
+    double2 turn[rope ? RW : 1][2][2];
+    if constexpr (rope) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int n0 = min(tile0 + r, a.W.tn - 1) * 16 + kq * 4;
+                const double2* tb = a.rope + ((size_t)(pos0 + min(nt * 16 + tok_l, T - 1)) * a.d_head + (n0 < a.q_dim ? n0 : n0 - a.q_dim) % a.d_head) / 2;
+                turn[r][nt][0] = tb[0];
+                turn[r][nt][1] = tb[1];
+            }
+    }
     // ---- RMSNorm row scales and cross-wave k reduction ----
     if (WK > 1 && !owner) {
 #pragma unroll
@@ -773,12 +787,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const int vblock, c
                     const int seg = n0 < a.q_dim ? 0 : (n0 < a.q_dim + a.i_dim ? 1 : 2);
                     const int nn = n0 - (seg == 0 ? 0 : (seg == 1 ? a.q_dim : a.q_dim + a.i_dim));
                     if (rope && seg < 2) {
-                        const int hd = nn % a.d_head;
 #pragma unroll
                         for (int p2 = 0; p2 < 2; ++p2) {
-                            const double fr = exp2(-(double)(hd + 2 * p2) / (double)a.d_head * log2((double)a.rope_base));
-                            double sn, cs;
-                            sincos((double)pos * fr, &sn, &cs);
+                            const double cs = turn[rope ? rwi : 0][nt][p2].x, sn = turn[rope ? rwi : 0][nt][p2].y;
                             const float x0 = v4[2 * p2], x1 = v4[2 * p2 + 1];
                             v4[2 * p2] = (float)((double)x0 * cs - (double)x1 * sn);
                             v4[2 * p2 + 1] = (float)((double)x0 * sn + (double)x1 * cs);

@@ -198,12 +198,10 @@ __global__ __launch_bounds__(256, 2) void gemm_dense_kernel(const GemmArgs a) {
                 const int seg = n0 < a.q_dim ? 0 : (n0 < a.q_dim + a.i_dim ? 1 : 2);
                 const int nn = n0 - (seg == 0 ? 0 : (seg == 1 ? a.q_dim : a.q_dim + a.i_dim));
                 if (ROPE && seg < 2) {  // pairs (2i, 2i+1) of a head rotate by position * base^(-2i/d_head)
-                    const int hd = nn % a.d_head;
+                    const double2* tb = a.rope + ((size_t)pos * a.d_head + nn % a.d_head) / 2;
 #pragma unroll
                     for (int p2 = 0; p2 < 2; ++p2) {
-                        const double fr = exp2(-(double)(hd + 2 * p2) / (double)a.d_head * log2((double)a.rope_base));
-                        double sn, cs;
-                        sincos((double)pos * fr, &sn, &cs);
+                        const double cs = tb[p2].x, sn = tb[p2].y;
                         const float x0 = v4[2 * p2], x1 = v4[2 * p2 + 1];
                         v4[2 * p2] = (float)((double)x0 * cs - (double)x1 * sn);
                         v4[2 * p2 + 1] = (float)((double)x0 * sn + (double)x1 * cs);

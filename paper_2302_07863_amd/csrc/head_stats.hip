@@ -102,7 +102,6 @@ GemmArgs head_gemm(const bild_model* m, const float* x, int rows, const int32_t*
     g.eps = c.norm_eps;
     g.d_head = c.d_head;
     g.i_dim = m->inner();
-    g.rope_base = c.rope_base;
     g.act = c.act;
     g.vocab = c.vocab;
     g.epi = EPI_LMHEAD;
