@@ -190,6 +190,8 @@ struct bild_state {
     int* src = nullptr;   // device [max_src]
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    hipStream_t aside = nullptr;  // the small model's encoder runs here, beside the large one's
+    hipEvent_t fork = nullptr, join = nullptr;
     int max_src = 0, max_len = 0, n_max = 0;
     int cap_len = 0, cap_src = 0;  // cache capacities: max_len / max_src rounded up to 32 rows
     // host mirror of the control block (kept exact by reading back after every pass)
