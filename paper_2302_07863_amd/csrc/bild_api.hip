@@ -370,7 +370,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         bild_state_destroy(s);
         return BILD_EHIP;
     }
-    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * kPassSyncWords, true);
+    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + 2 * (kPassDieRows + 1)), true);
     for (int w = 0; w < 2; ++w) {
         ModelState& M = s->ms[w];
         const bild_model* m = p->m[w];
@@ -414,6 +414,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             if (M.pass_groups && s->one_die && s->cus == 256) M.pass_die_groups = pass_die_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated());
             if (M.pass_groups) {
                 want(M.pass_layers, sizeof(PassLayer) * L);
+                for (int T = 1; T <= kPassDieRows && M.pass_die_groups; ++T) want(M.pass_die_scratch[T], 2 * L * (size_t)pass_plan(T, (int)d, (int)I, (int)F).layer);
                 want(M.pass_scratch, L * (size_t)pass_plan(kPassRows, (int)d, (int)I, (int)F).layer);
             }
         }
@@ -467,6 +468,9 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     for (int w = 0; w < 2 && e == hipSuccess; ++w) {
         ModelState& M = s->ms[w];
         if (!M.pass_groups) continue;
+        for (int T = 1; T <= kPassDieRows && M.pass_die_groups && e == hipSuccess; ++T)
+            e = hipMemsetAsync(M.pass_die_scratch[T], 0xFF, 2 * M.m->dec.size() * (size_t)pass_plan(T, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff).layer, s->stream);
+        if (e != hipSuccess) break;
         const size_t kv = (size_t)s->cap_len * M.m->inner() * M.m->esz(), ckv = (size_t)s->cap_src * M.m->inner() * M.m->esz();
         for (size_t l = 0; l < M.m->dec.size(); ++l) {
             const LayerW& W = M.m->dec[l];
@@ -1183,14 +1187,20 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         p.att_scale = 1.f / std::sqrt((float)c.d_head); p.eps = c.norm_eps;
         p.x_out = M.x;
         p.x_keep = trunk > 0 && w == 0 ? s->trunk_x : nullptr;
-        p.scratch = M.pass_scratch;
         p.at = pass_plan(T, d, p.I, p.F);
+        const bool die = M.pass_die_groups > 0 && T <= kPassDieRows;
+        if (die) {
+            p.scratch = M.pass_die_scratch[T];
+            p.set_bytes = (size_t)p.n_layers * p.at.layer;
+            p.turn = s->pass_sync + kPassSyncWords + w * (kPassDieRows + 1) + T;
+        } else {
+            p.scratch = M.pass_scratch;
+        }
         p.sync = s->pass_sync;
         p.spins = s->pass_spins;
         s->stage_count += 1;
-        p.die = M.pass_die_groups > 0 && T <= kPassDieRows;
-        p.groups = p.die ? M.pass_die_groups : M.pass_groups;
-        HIPC(launch_pass(p, p.die ? s->cus : p.groups, s->stream));
+        p.groups = die ? M.pass_die_groups : M.pass_groups;
+        HIPC(launch_pass(p, die ? s->cus : p.groups, s->stream));
     } else if (dt == BILD_DT_BF16 && T > kMaxRows) {
         if (lm_rows > 0) return BILD_EINVAL;
         const int rc = emit_prefill(s, w, T);
@@ -1209,7 +1219,10 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     f.rows_consumed = T;
     f.y_cap = s->max_len;
     f.host_mirror = s->hctl_dev;
-    if (one) f.sync = s->pass_sync;
+    if (one) {
+        f.sync = s->pass_sync;
+        if (M.pass_die_groups > 0 && T <= kPassDieRows) f.turn = s->pass_sync + kPassSyncWords + w * (kPassDieRows + 1) + T;
+    }
     if (lm_rows > 0) {
         GemmArgs g = gemm_base(m, m->head, xfin + (size_t)(T - lm_rows) * d, d, lm_rows, m->dec_final);
         if (parts) { g.px = M.px; g.px_stride = (int64_t)kMaxRows * d; g.pn = kPartSlices; g.x_out = xfin == M.x ? M.x2 : M.x; }

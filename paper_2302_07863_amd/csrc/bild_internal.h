@@ -196,7 +196,7 @@ struct AttnArgs {
 };
 
 // A whole decoder pass in one kernel (pass_kernel.hip).
-constexpr int kPassRows = 16, kPassDieRows = 8;
+constexpr int kPassRows = 16, kPassDieRows = 4;  // most rows; on one die
 constexpr int kPassCounters = 64;  // one per lane of the polling wave
 constexpr int kPassStride = 64;  // words
 constexpr int kPassSyncWords = (kPassCounters + 1) * kPassStride;  // counters on lines of their own, then the ranks given out on a die; the last word: a workgroup gave up
@@ -224,9 +224,11 @@ struct PassArgs {
     int rel_d;
     float att_scale, eps;
     float *x_out, *x_keep;    // the residual stream after the last layer: [T][d]; at [len ..] too (null: not kept)
-    char* scratch;            // [n_layers][at.layer]
+    char* scratch;            // [n_layers][at.layer]; on one die: two sets of that, everything "not there" in the one this pass uses
+    size_t set_bytes;
+    const unsigned* turn;     // on one die: which set (passes so far); null: on the whole chip
     PassPlan at;
-    int groups, die;          // workgroups that take part; 1: all on die 0
+    int groups;               // workgroups that take part
     int spins;                // polls (of about 0.7 us) after which a workgroup gives up
     unsigned* sync;           // [kPassSyncWords], zero before the pass; the policy kernel clears it
 };
@@ -290,6 +292,7 @@ struct FinishArgs {
     const float* u_acc;   // uniform number per sequence position for the acceptance test
     float* s_ring;        // [kMaxRows][vocab] the small model's logits of each pending draft, by draft index
     float4* s_draw;       // [sequence capacity] (max logit, nucleus threshold key, nucleus mass, -) of the small model's row
+    unsigned* turn;       // counts the passes of a number of rows on one die
     unsigned* sync;       // counters of the pass kernel, cleared here for its next pass; a flagged pass is not committed
     // nucleus draw spread over the chip (launch_finish_draw): its workspace
     struct DrawWs* dws;

@@ -148,6 +148,7 @@ struct ModelState {
     int pass_die_groups = 0;  // the same of the form on one die
     bild::PassLayer* pass_layers = nullptr;  // device
     char* pass_scratch = nullptr;
+    char* pass_die_scratch[bild::kPassDieRows + 1] = {};  // by rows: two sets each
 };
 
 struct bild_state {

@@ -20,13 +20,16 @@
 //   - the cross query is worked out by the workgroup of the head that uses it, which saves a hand-over.
 //
 // A model small enough for the 32 compute units of one die (pass_die_groups: T5-small, mT5-small) walks there: what is handed over
-// then only goes to that die's L2 and back (1.2 us instead of 1.9), at 1.25 TB/s for the weights instead of the chip's 4.8, which
-// a layer of 7 MB in 17 us does not notice.  Workgroups of the other dies end at once.
+// then only goes to that die's L2 and back, at 1.25 TB/s for the weights instead of the chip's 4.8, which a layer of 7 MB in 13 us
+// does not notice.  Workgroups of the other dies end at once.  There everything but q, k and v is also its own flag: the memory
+// is filled with words that no result has, and who needs a piece reads it until none of them is left (two sets take turns: a
+// producer writes its part of one and fills its part of the other), which saves the counting and the wait before it (T5-small
+// shape, one row: 112 -> 98 us).  Over the whole chip this loses (623 -> 714 us, T5-large shape): reads past the L2s are not
+// shared by a die's workgroups.
 //
-// Per pass, us, before (a kernel per stage) and now, 512 source tokens: T5-small shape one row 149 -> 114 (on the
-// whole chip 139), mT5-small shape 257 -> 196 (224); T5-large shape 1, 2, 5,
-// 8, 16 rows 683, 799, 977, 998, 1223 -> 634, 642, 653, 651, 730; mT5-large shape, 64 tokens, 1 and 8 rows 809, 1063 ->
-// 709, 725.
+// Per pass, us, before (a kernel per stage) and now, 512 source tokens: T5-small shape one row 149 -> 99 (on the whole chip 139),
+// mT5-small shape, 64 tokens, 239 -> 169 (217); T5-large shape 1, 2, 5, 8, 16 rows 683, 799, 977, 998, 1223 -> 623, 630, 643,
+// 636, 715; mT5-large shape, 64 tokens, 1 and 8 rows 809, 1063 -> 703, 720.
 //
 // A workgroup that has polled `spins` times in vain flags the pass as failed and walks on without waiting again (nothing
 // handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
@@ -49,7 +52,8 @@ __device__ __forceinline__ P* pinned(P* p) {
     return p;
 }
 __device__ __forceinline__ Rsrc whole(const void* p) { return make_rsrc(p, 0xFFFFFFFFu); }
-__device__ __forceinline__ float4 ldf4(Rsrc r, int off) { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0)); }
+template <int AUX = 0>
+__device__ __forceinline__ float4 ldf4(Rsrc r, int off) { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX)); }
 __device__ __forceinline__ bf16x8 as_bf(const uint4& v) { return __builtin_bit_cast(bf16x8, v); }
 template <int AUX>
 __device__ __forceinline__ void st8(Rsrc r, int off, unsigned a, unsigned b) {
@@ -57,12 +61,18 @@ __device__ __forceinline__ void st8(Rsrc r, int off, unsigned a, unsigned b) {
     __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, AUX);
 }
 
+constexpr unsigned kNotThere = 0xFFFFFFFFu;  // (two NaNs of a kind no conversion gives, as bf16 parts; one as a sum)
+
 // LDS: sums of the waves (up to six tiles each; attention joins its waves there too), their (max, sum), the head's query, the
 // head's relative-position biases
-constexpr int kRed = 0, kMl = kPassWaves * 6 * 1024, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kRel = kQ + 16 * kQLd * 4;
+constexpr int kRedBytes = kPassWaves * 6 * 1024;  // twice: a stage's sums are read while the next one's are written
+constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kRel = kQ + 16 * kQLd * 4;
 
 template <bool DIE>
 struct Walk {
+    // on one die all but q, k and v are handed over without counters (see the head of this file)
+    static constexpr bool TAG = DIE;
+    static constexpr int kIn = 16;  // reads of what may not be there yet: past the L1 (sc1)
     // what is handed over goes as far as all readers see it: to the die's L2 (the L1s write through), or past the L2s (sc0 sc1)
     static constexpr int kOut = DIE ? 0 : 17;
     char* lds;
@@ -72,6 +82,8 @@ struct Walk {
     int wg, wave, lane, tok, g, t, t8;  // t: this lane's row, clamped to the last one; t8: of the packed order
     unsigned target;                // wave 0: arrivals this lane's counter has to show
     bool dead;
+    int red = 0;                    // half of the sums' memory in use
+    long clear = 0;                 // from what this pass hands over to where the next one will: filled with "not there yet"
 
     int T;
     __device__ __forceinline__ void place(int rows) {
@@ -82,6 +94,16 @@ struct Walk {
         t8 = min(tok & 7, T - 1);
     }
     // the stage just described has `n` active workgroups from `base` on
+    __device__ __forceinline__ char* scratch(const PassArgs& a) {
+        if constexpr (!TAG) return a.scratch;
+        const bool second = (*a.turn & 1u) != 0u;
+        clear = second ? -(long)a.set_bytes : (long)a.set_bytes;
+        return a.scratch + (second ? a.set_bytes : 0);
+    }
+    __device__ __forceinline__ void give_up() {
+        dead = true;
+        if (lane == 0) asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(failed), "v"(1u) : "memory");
+    }
     __device__ __forceinline__ void expect(int base, int n) { target += (unsigned)(n + kPassCounters - 1 - ((lane - base) & (kPassCounters - 1))) / kPassCounters; }
     __device__ __forceinline__ void arrive() const {  // one wave, after its stores
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -103,10 +125,7 @@ struct Walk {
                 else asm volatile("global_load_dword %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
                 missing = __builtin_amdgcn_ballot_w64((int)(v - target) < 0);
             } while (missing && ++n < spins);
-            if (n >= spins) {
-                dead = true;
-                if (lane == 0) asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(failed), "v"(1u) : "memory");
-            }
+            if (n >= spins) give_up();
         }
         lds_barrier();
     }
@@ -135,6 +154,30 @@ __device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const
         }
 }
 
+// RMSNorm's factor of this lane's row from the owners' partial sums of squares, [t][d / 16]: requested and, later, added up.
+struct Norm {
+    float4 v[4] = {};
+    template <class Walk>
+    __device__ __forceinline__ void get(const Walk& c, const float* ssq, int nd) {
+        const Rsrc r = whole(ssq);
+        const int per = nd >> 2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = i * 4 < per ? ldf4<Walk::TAG ? Walk::kIn : 0>(r, (c.t * nd + c.g * per + i * 4) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __device__ __forceinline__ unsigned largest() const {
+        unsigned m = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m = max(max(m, max(__float_as_uint(v[i].x), __float_as_uint(v[i].y))), max(__float_as_uint(v[i].z), __float_as_uint(v[i].w)));
+        return m;
+    }
+    __device__ __forceinline__ float factor(int d, float eps) const {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+        return __builtin_amdgcn_rsqf(quad_rows_sum(s) * __builtin_amdgcn_rcpf((float)d) + eps);
+    }
+};
+
 // acc = W x over this wave's inputs.  x lies in tiles of 32 inputs in the order in which the operand's lanes want it: quarters of
 // eight inputs, in each the rows one after the other, 16 bytes per row; the high parts of a tile and then its low parts.  (A load
 // is then one dense piece: with the rows' 64 bytes 128 apart a pass of eight rows took 854 us instead of 737.)
@@ -142,7 +185,8 @@ __device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const
 // the loads and products (a compute unit's 64 bytes a cycle are what the FFN output's 256 loads of 1 KiB wait for); the halves
 // are added in total().  A quarter then has the rows' high parts and their low parts.
 template <int N, int RW, bool PACK, class Walk>
-__device__ __forceinline__ void multiply(const Walk& c, f32x4 (&acc)[RW], const uint4 (&W)[N * RW], const void* planes, int tk) {
+__device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 (&W)[N * RW], const void* planes, int tk, Norm& nm, bool normed = false,
+                                         const void* ssq = nullptr, int nd = 0) {
     const Run r = run_of(c.wave, tk);
     const Rsrc xs = whole(planes);
     const int S = c.T * 128;
@@ -156,7 +200,7 @@ __device__ __forceinline__ void multiply(const Walk& c, f32x4 (&acc)[RW], const 
 #pragma unroll
         for (int j = 0; j < B; ++j)
             if (j0 + j < r.n) {
-                x[P * j] = buf_load(xs, (unsigned)at, k0 + (j0 + j) * S);
+                x[P * j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at, k0 + (j0 + j) * S, Walk::TAG ? Walk::kIn : 0));
                 if (!PACK) x[P * j + 1] = buf_load(xs, (unsigned)at, k0 + (j0 + j) * S + S / 2);
             }
     };
@@ -172,27 +216,56 @@ __device__ __forceinline__ void multiply(const Walk& c, f32x4 (&acc)[RW], const 
                 }
             }
     };
-    get(X[0], 0);
+    if constexpr (Walk::TAG) {  // all of it at once, again and again until every word is there
+        static_assert(P == 1 && N <= 2 * B, "two pieces at most");
+        int n = 0;
+        bool missing;
+#pragma unroll 1
+        do {
+            asm volatile("" ::: "memory");
+            get(X[0], 0);
+            if constexpr (N > B) get(X[1], B);
+            unsigned m = 0u;
+            if (normed) {
+                nm.get(c, (const float*)ssq, nd);
+                m = nm.largest();
+            }
 #pragma unroll
-    for (int j0 = 0; j0 < N; j0 += B) {
-        if (j0 + B < N && j0 + B < r.n) get(X[(j0 / B + 1) & 1], j0 + B);
-        mul(X[(j0 / B) & 1], j0);
+            for (int j = 0; j < N; ++j)
+                if (j < r.n) {
+                    const uint4 v = X[j / B][j % B];
+                    m = max(max(m, max(v.x, v.y)), max(v.z, v.w));
+                }
+            missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+        } while (missing && ++n < c.spins);
+        if (missing) c.give_up();
+#pragma unroll
+        for (int j0 = 0; j0 < N; j0 += B) mul(X[j0 / B], j0);
+    } else {
+        if (normed) nm.get(c, (const float*)ssq, nd);
+        get(X[0], 0);
+#pragma unroll
+        for (int j0 = 0; j0 < N; j0 += B) {
+            if (j0 + B < N && j0 + B < r.n) get(X[(j0 / B + 1) & 1], j0 + B);
+            mul(X[(j0 / B) & 1], j0);
+        }
     }
     if constexpr (RW == 1 && !PACK) acc[0] += low[0];
 }
 
 // The waves' results side by side in LDS; `tile`'s total over the waves, in wave order.
 template <int RW, class Walk>
-__device__ __forceinline__ void leave(const Walk& c, const f32x4 (&acc)[RW]) {
+__device__ __forceinline__ void leave(Walk& c, const f32x4 (&acc)[RW]) {
+    c.red = kRedBytes - c.red;
 #pragma unroll
-    for (int q = 0; q < RW; ++q) *(f32x4*)(c.lds + kRed + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
+    for (int q = 0; q < RW; ++q) *(f32x4*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
     lds_barrier();
 }
 template <int RW, bool PACK, class Walk>
 __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
     f32x4 p[kPassWaves];
 #pragma unroll
-    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const f32x4*)(c.lds + kRed + ((v * RW + tile) * 64 + c.lane) * 16);
+    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const f32x4*)(c.lds + kRed + c.red + ((v * RW + tile) * 64 + c.lane) * 16);
     f32x4 s = p[0];
 #pragma unroll
     for (int v = 1; v < kPassWaves; ++v) s += p[v];
@@ -202,24 +275,6 @@ __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
     }
     return s;
 }
-
-// RMSNorm's factor of this lane's row from the owners' partial sums of squares, [t][d / 16]: requested and, later, added up.
-struct Norm {
-    float4 v[4] = {};
-    template <class Walk>
-    __device__ __forceinline__ void get(const Walk& c, const float* ssq, int nd) {
-        const Rsrc r = whole(ssq);
-        const int per = nd >> 2;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = i * 4 < per ? ldf4(r, (c.t * nd + c.g * per + i * 4) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    __device__ __forceinline__ float factor(int d, float eps) const {
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-        return __builtin_amdgcn_rsqf(quad_rows_sum(s) * __builtin_amdgcn_rcpf((float)d) + eps);
-    }
-};
 
 // Sixteen features of a row's activations in that order: this lane's four.
 template <bool PACK, class Walk>
@@ -231,6 +286,11 @@ __device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, 
     const int off = (n0 >> 5) * c.T * 128 + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.T + c.tok) * 16 + (n0 & 7) * 2;
     st8<Walk::kOut>(r, off, h01, h23);
     st8<Walk::kOut>(r, off + (PACK ? 16 : 64) * c.T, l01, l23);
+    if constexpr (Walk::TAG) {
+        const Rsrc n = whole((const char*)planes + c.clear);
+        st8<Walk::kOut>(n, off, kNotThere, kNotThere);
+        st8<Walk::kOut>(n, off + 16 * c.T, kNotThere, kNotThere);
+    }
 }
 
 // Attention of one head over its keys for all rows: the waves take blocks of 32 keys in turn; (max, sum, O) joined through LDS.
@@ -256,7 +316,7 @@ struct Attend {
     }
     // `query`: this lane's row and inputs g * 8 .. of both halves of the head.  Up to eight rows are packed as in multiply().
     template <class Query>
-    __device__ __forceinline__ void run(const Walk& c, Query&& query, float scale, int len, const float* relb, int rel_d, void* out, int T, int h) {
+    __device__ __forceinline__ void run(Walk& c, Query&& query, float scale, int len, const float* relb, int rel_d, void* out, int T, int h) {
         constexpr int P = PACK ? 1 : 2;
         bf16x8 Q[2][P];  // scaled, high parts (columns 0 .. 7 if packed) and low parts
         const bool low = c.tok >= 8;
@@ -411,7 +471,7 @@ struct Attend {
                 if (v < nblk) {  // (waves with keys)
                     w[v] = fexp(w[v] - M);
                     L += cl[v * 16 + c.tok] * w[v];
-                    o += *(const f32x4*)(c.lds + kRed + ((v * 4 + c.wave) * 64 + c.lane) * 16) * w[v];
+                    o += *(const f32x4*)(c.lds + kRed + c.red + ((v * 4 + c.wave) * 64 + c.lane) * 16) * w[v];
                 }
             if constexpr (PACK) {
 #pragma unroll
@@ -420,10 +480,12 @@ struct Attend {
             const float inv = 1.f / L;
             const float r[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
             if (c.tok < T) put_planes<PACK>(c, out, h * 64 + c.wave * 16 + c.g * 4, r);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (!Walk::TAG) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
-        lds_barrier();  // all four waves' stores are in memory
-        if (c.wave == 0) c.arrive();
+        if constexpr (!Walk::TAG) {
+            lds_barrier();  // all four waves' stores are in memory
+            if (c.wave == 0) c.arrive();
+        }
     }
 };
 
@@ -454,6 +516,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     const bool owner = c.wg < no(), qkv = c.wg < nq(), ffn = c.wg < nf();
     uint4 Wq[KD * QT], Wo[KD * OT], Wi[KD * FT], Wf[KF * OT];
     float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f);
+    Norm none;
     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);  // (owners, waves below OT) the residual stream of this lane's row, features n0 .. n0 + 3
     const bool mine = c.wave < OT && c.wg * OT + c.wave < nd();
     auto n0 = [&] { return (c.wg * OT + c.wave) * 16 + c.g * 4; };
@@ -474,17 +537,21 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
             if (c.tok < T) {
                 put_planes<PACK>(c, planes, n0(), w);
-                if (c.g == 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(ssq), (c.tok * nd() + c.wg * OT + c.wave) * 4, 0, Walk::kOut);
+                if (c.g == 0) {
+                    const int off = (c.tok * nd() + c.wg * OT + c.wave) * 4;
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(ssq), off, 0, Walk::kOut);
+                    if (Walk::TAG) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, whole(ssq + c.clear), off, 0, Walk::kOut);
+                }
             }
         }
-        done(OWaves{});
+        if (!Walk::TAG) done(OWaves{});
     };
     auto add = [&] {
         const f32x4 s = total<OT, PACK>(c, c.wave);
         x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]);
     };
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
-    char* z = a.scratch;  // this layer's hand-over buffers
+    char* z = c.scratch(a);  // this layer's hand-over buffers
     if (owner) {
         const int pos = len + c.t;
         const float4 gn = gain(L->ln1);
@@ -506,7 +573,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         publish(gn, z + a.at.x1, z + a.at.s1);
     }
     if (qkv) request<KD, QT>(c, Wq, L->wqkv, c.wg, d >> 5, tq());
-    c.expect(0, no());
+    if (!Walk::TAG) c.expect(0, no());
     for (int l = 0; l < a.n_layers; ++l, z += a.at.layer) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         const bool last = l + 1 == a.n_layers;
@@ -519,11 +586,10 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             const char *xs = pinned(z + a.at.x1), *ss = pinned(z + a.at.s1);
             const int seg = c.wg * QT * 16 / I;
             char* out = pinned(seg == 0 ? z + a.at.q : seg == 1 ? L->kc : L->vc);
-            c.wait();
+            if (!Walk::TAG) c.wait();
             Norm nm;
-            if (c.wave < QT) nm.get(c, (const float*)ss, nd());
             f32x4 acc[QT];
-            multiply<KD, QT, PACK>(c, acc, Wq, xs, d >> 5);
+            multiply<KD, QT, PACK>(c, acc, Wq, xs, d >> 5, nm, c.wave < QT, ss, nd());
             const float f = nm.factor(d, a.eps);
             leave<QT>(c, acc);
             if (c.wave < QT) {
@@ -545,7 +611,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             done(std::integral_constant<int, QT>{});
         }
         c.expect(0, nq());
-        c.expect(base, a.heads);  // (self-attention)
+        if (!Walk::TAG) c.expect(base, a.heads);  // (self-attention)
         // ---- output projection ----
         // Requests go out where the workgroup has several microseconds before it is needed again (a wave's loads come back in
         // order: what is asked for late delays the next stage's activations): here, while the heads work, and below.
@@ -558,17 +624,17 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             }
             const char* xs = pinned(z + a.at.a1);
             char *ox = pinned(z + a.at.x2), *os = pinned(z + a.at.s2);
-            c.wait();
+            if (!Walk::TAG) c.wait();
             f32x4 acc[OT];
-            multiply<KD, OT, PACK>(c, acc, Wo, xs, I >> 5);
+            multiply<KD, OT, PACK>(c, acc, Wo, xs, I >> 5, none);
             leave<OT>(c, acc);
             if (mine) add();
             publish(gn, ox, os);
         }
-        c.expect(0, no());
+        if (!Walk::TAG) c.expect(0, no());
         const char *xf = z + a.at.x2, *sf = z + a.at.s2;  // what the FFN reads
         if (a.cross) {
-            c.expect(base, a.heads);
+            if (!Walk::TAG) c.expect(base, a.heads);
             // ---- output projection of the cross-attention ----
             if (owner) {
                 request<KD, OT>(c, Wo, L->cwo, c.wg, I >> 5, nd());
@@ -579,14 +645,14 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 if (qkv && !last) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> 5, tq());
                 const char* xs = pinned(z + a.at.a2);
                 char *ox = pinned(z + a.at.x3), *os = pinned(z + a.at.s3);
-                c.wait();
+                if (!Walk::TAG) c.wait();
                 f32x4 acc[OT];
-                multiply<KD, OT, PACK>(c, acc, Wo, xs, I >> 5);
+                multiply<KD, OT, PACK>(c, acc, Wo, xs, I >> 5, none);
                 leave<OT>(c, acc);
                 if (mine) add();
                 publish(gn, ox, os);
             }
-            c.expect(0, no());
+            if (!Walk::TAG) c.expect(0, no());
             xf = z + a.at.x3;
             sf = z + a.at.s3;
         }
@@ -595,12 +661,11 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             if (!owner || !a.cross) request<KD, FT>(c, Wi, L->win, c.wg, d >> 5, tf());
             const char *xs = pinned(xf), *ss = pinned(sf);
             char* out = pinned(z + a.at.h);
-            c.wait();
+            if (!Walk::TAG) c.wait();
             constexpr int FW = GATED ? FT / 2 : FT;  // waves with results
             Norm nm;
-            if (c.wave < FW) nm.get(c, (const float*)ss, nd());
             f32x4 acc[FT];
-            multiply<KD, FT, PACK>(c, acc, Wi, xs, d >> 5);
+            multiply<KD, FT, PACK>(c, acc, Wi, xs, d >> 5, nm, c.wave < FW, ss, nd());
             const float r = nm.factor(d, a.eps);
             leave<FT>(c, acc);
             const int tile = c.wg * FW + c.wave;  // of the hidden state
@@ -617,21 +682,21 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 }
                 if (c.tok < T) put_planes<PACK>(c, out, tile * 16 + c.g * 4, w);
             }
-            done(std::integral_constant<int, FW>{});
+            if (!Walk::TAG) done(std::integral_constant<int, FW>{});
         }
-        c.expect(0, nf());
+        if (!Walk::TAG) c.expect(0, nf());
         if (qkv && !last && (!owner || !a.cross)) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> 5, tq());
         if (owner) {
             const char* xs = pinned(z + a.at.h);
             char *ox = pinned(z + a.at.layer + a.at.x1), *os = pinned(z + a.at.layer + a.at.s1);
-            c.wait();
+            if (!Walk::TAG) c.wait();
             f32x4 acc[OT];
-            multiply<KF, OT, PACK>(c, acc, Wf, xs, F >> 5);
+            multiply<KF, OT, PACK>(c, acc, Wf, xs, F >> 5, none);
             leave<OT>(c, acc);
             if (mine) add();
             if (!last) publish(next_gain, ox, os);
         }
-        c.expect(0, no());
+        if (!Walk::TAG) c.expect(0, no());
     }
     if (owner && mine && c.tok < T) {
         *(float4*)(a.x_out + (size_t)c.tok * d + n0()) = x;
@@ -655,9 +720,9 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
     }
     uint4 Wc[KD * 4];  // of the cross query
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
-    char* z = a.scratch;
+    char* z = c.scratch(a);
     if (a.cross) request<KD, 4>(c, Wc, L->cwq, h, d >> 5, I >> 4);
-    c.expect(0, ceil_div(d >> 4, Cut::OT));
+    if (!Walk::TAG) c.expect(0, ceil_div(d >> 4, Cut::OT));
     for (int l = 0; l < a.n_layers; ++l, z += a.at.layer) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         asm volatile("" : "+v"(c.lane));
@@ -684,17 +749,16 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
             };
             at.run(c, query, sc, len, relb, a.rel_d, out, T, h);
         }
-        c.expect(base, a.heads);
-        c.expect(0, ceil_div(d >> 4, Cut::OT));
+        if (!Walk::TAG) c.expect(base, a.heads);
+        if (!Walk::TAG) c.expect(0, ceil_div(d >> 4, Cut::OT));
         if (a.cross) {
             const char *xs = pinned(z + a.at.x2), *ss = pinned(z + a.at.s2);
             char* out = pinned(z + a.at.a2);
             const float sc = a.att_scale;
-            c.wait();
+            if (!Walk::TAG) c.wait();
             Norm nm;
-            if (c.wave < 4) nm.get(c, (const float*)ss, d >> 4);
             f32x4 acc[4];
-            multiply<KD, 4, PACK>(c, acc, Wc, xs, d >> 5);
+            multiply<KD, 4, PACK>(c, acc, Wc, xs, d >> 5, nm, c.wave < 4, ss, d >> 4);
             const float f = nm.factor(d, a.eps);
             leave<4>(c, acc);
             float* q = (float*)(c.lds + kQ);
@@ -711,11 +775,11 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
             };
             cross.run(c, query, sc, len, nullptr, 0, out, T, h);
             if (l + 1 < a.n_layers) request<KD, 4>(c, Wc, L[1].cwq, h, d >> 5, I >> 4);
-            c.expect(base, a.heads);
-            c.expect(0, ceil_div(d >> 4, Cut::OT));
+            if (!Walk::TAG) c.expect(base, a.heads);
+            if (!Walk::TAG) c.expect(0, ceil_div(d >> 4, Cut::OT));
         }
-        c.expect(0, ceil_div(GATED ? a.F >> 3 : a.F >> 4, Cut::FT));
-        c.expect(0, ceil_div(d >> 4, Cut::OT));
+        if (!Walk::TAG) c.expect(0, ceil_div(GATED ? a.F >> 3 : a.F >> 4, Cut::FT));
+        if (!Walk::TAG) c.expect(0, ceil_div(d >> 4, Cut::OT));
     }
 }
 
@@ -790,17 +854,29 @@ PassPlan pass_plan(int T, int d, int I, int F) {
 }
 
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
-    if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > (a.die ? kPassDieRows : kPassRows) || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
+    if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > (a.turn ? kPassDieRows : kPassRows) || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
         (a.cross && !a.nsrc_ptr))
         return hipErrorInvalidValue;
     const size_t smem = kRel + (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);
-    if (smem > 64 * 1024) return hipErrorInvalidValue;
+    if (smem > 160 * 1024) return hipErrorInvalidValue;
     const bool gated = a.act != BILD_ACT_RELU;
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kPassThreads), smem, st, a); };
-    if (a.die) gated ? go(pass_kernel<true, true, true>) : go(pass_kernel<false, true, true>);
-    else if (a.T <= 8) gated ? go(pass_kernel<true, true, false>) : go(pass_kernel<false, true, false>);
-    else gated ? go(pass_kernel<true, false, false>) : go(pass_kernel<false, false, false>);
-    return hipGetLastError();
+#define BILD_P(GV, PV, DV)                                                                                                   \
+    do {                                                                                                                     \
+        static hipError_t e = hipFuncSetAttribute((const void*)pass_kernel<GV, PV, DV>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
+        if (e != hipSuccess) return e;                                                                                       \
+        hipLaunchKernelGGL((pass_kernel<GV, PV, DV>), dim3(grid), dim3(kPassThreads), smem, st, a);                          \
+        return hipGetLastError();                                                                                            \
+    } while (0)
+#define BILD_PG(PV, DV)                                                                                                      \
+    do {                                                                                                                     \
+        if (gated) BILD_P(true, PV, DV);                                                                                     \
+        BILD_P(false, PV, DV);                                                                                               \
+    } while (0)
+    if (a.turn) BILD_PG(true, true);
+    if (a.T <= 8) BILD_PG(true, false);
+    BILD_PG(false, false);
+#undef BILD_PG
+#undef BILD_P
 }
 
 }  // namespace bild

@@ -285,6 +285,7 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int 
     const int c_ylen = c->y_len, c_ds = c->draft_start, c_nmax = c->n_max, c_len0 = c->len[0], c_len1 = c->len[1], c_lenw = c->len[a.which];
     const float c_afb = c->alpha_fb, c_arb = c->alpha_rb;
     const int c_seq = c->seq;
+    const unsigned c_turn = a.turn ? *a.turn : 0u;
     const bool failed = a.sync && a.sync[kPassSyncWords - 1] != 0u;
     float z_draft = 0.f;
     if (a.mode != 3)
@@ -398,6 +399,7 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int 
     }
     if (a.sync) {
         a.sync[lane * kPassStride] = 0u;
+        if (lane == 0 && a.turn) *a.turn = c_turn + 1u;
         if (lane == 0) a.sync[kPassCounters * kPassStride] = a.sync[kPassSyncWords - 1] = 0u;
         if (failed) {  // the pass kernel's workgroups did not all run: nothing happened but the count of passes
             if (lane == 0) {
