@@ -1,7 +1,7 @@
 // bild_head_stats / bild_head_stats_static: the final norm + LM head + softmax statistics of the decoding path
 // (the fused vocabulary sweep of a decoder pass) as a call of its own on hidden rows the caller already holds
 // on the device.  Both entry points run the same kernels; they differ only in where the scratch buffer lives
-// (per-workgroup partial statistics, the logits of the targets, one length word):
+// (per-workgroup partial statistics, the logits of the targets):
 //   bild_head_stats         takes it from the model's pool (a few buffers at most, freed with the model) and gives it back
 //                           before returning: an allocation and its release cost more than a row of a small vocabulary;
 //   bild_head_stats_static  uses a file-scope device array, so the call allocates nothing at all.
