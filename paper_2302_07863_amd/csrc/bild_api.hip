@@ -293,9 +293,6 @@ extern "C" int bild_state_destroy(bild_state* s) {
     for (void* p : s->host_allocs) (void)hipHostFree(p);
     for (hipEvent_t e : s->prof_ev) (void)hipEventDestroy(e);
     for (auto& kv : s->graphs) (void)hipGraphExecDestroy(kv.second);
-    if (s->fork) (void)hipEventDestroy(s->fork);
-    if (s->join) (void)hipEventDestroy(s->join);
-    if (s->aside) (void)hipStreamDestroy(s->aside);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
     return BILD_OK;
@@ -318,15 +315,21 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         delete s;
         return BILD_EHIP;
     }
+    if (hipGetDevice(&s->device) != hipSuccess || hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess) {
+        delete s;
+        return BILD_EHIP;
+    }
     if (hip_stream) {
         s->stream = (hipStream_t)hip_stream;
     } else {
-        if (hipStreamCreate(&s->stream) != hipSuccess) {
+        s->stream = p->spare.take(s->device);
+        if (!s->stream) {
             delete s;
             return BILD_EHIP;
         }
         s->own_stream = true;
     }
+    if (!p->decoder_only && !p->small_borrows_encoder) p->spare.renew(s->device);
     // All device memory of the state is one allocation (dozens of separate ones cost a request about a millisecond); what has
     // to start zeroed lies together at its front.
     struct Want { void** p; size_t bytes; bool zero; };
@@ -366,10 +369,6 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
     const int positions = std::max(s->cap_len, s->cap_src);
-    if (hipGetDevice(&s->device) != hipSuccess || hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess) {
-        bild_state_destroy(s);
-        return BILD_EHIP;
-    }
     if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + 2 * (kPassDieRows + 1)), true);
     for (int w = 0; w < 2; ++w) {
         ModelState& M = s->ms[w];
@@ -1528,25 +1527,16 @@ int run_encoder(bild_state* s, int w) {
     return cross_kv(s, w, none);
 }
 
-// Both encoders; the small model's beside the large one's on a stream of its own: neither fills the chip over a few hundred rows
-// (T5 shapes, 77, 512, 1531 tokens: 1.22, 2.16, 4.82 -> 1.07, 1.98, 4.54 ms; mT5 shapes, 64 tokens: 1.24 -> 1.04 ms).
+// Both encoders; the small model's beside the large one's on the pair's spare stream: neither fills the chip over a few hundred
+// rows (T5 shapes, 77, 512, 1531 tokens: 1.22, 2.16, 4.82 -> 1.07, 1.98, 4.54 ms; mT5 shapes, 64 tokens: 1.24 -> 1.04 ms).
 int run_encoders(bild_state* s) {
-    const bool two = !s->pair->small_borrows_encoder;
-    if (two && !s->aside) {
-        HIPC(hipStreamCreateWithFlags(&s->aside, hipStreamNonBlocking));
-        HIPC(hipEventCreateWithFlags(&s->fork, hipEventDisableTiming));
-        HIPC(hipEventCreateWithFlags(&s->join, hipEventDisableTiming));
-    }
-    if (two) HIPC(hipEventRecord(s->fork, s->stream));
-    int rc = run_encoder(s, 1);
-    if (rc || !two) return rc;
-    HIPC(hipStreamWaitEvent(s->aside, s->fork, 0));
-    std::swap(s->stream, s->aside);
-    rc = run_encoder(s, 0);
-    std::swap(s->stream, s->aside);
-    HIPC(hipEventRecord(s->join, s->aside));
-    HIPC(hipStreamWaitEvent(s->stream, s->join, 0));  // (also behind an error: what follows on the stream waits for both)
-    return rc;
+    auto large = [&] { return run_encoder(s, 1); };
+    if (s->pair->small_borrows_encoder) return large();
+    auto small = [&] { return run_encoder(s, 0); };
+    int rc = BILD_OK;
+    if (s->pair->spare.beside(s->device, s->stream, large, small, &rc)) return rc;
+    rc = large();
+    return rc ? rc : small();
 }
 
 }  // namespace

@@ -1,0 +1,59 @@
+"""Independent requests at once, each a state and a host thread of its own: what they produce and that one does not hold up the
+others."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# Best of five generations of one request alone and of two at once, beside an idle third state; in a process of its own, because
+# the streams a process has made decide which hardware queue the next one gets.
+OVERLAP = """
+import threading, time
+import bild_inputs as bi
+import paper_2302_07863_amd as pkg
+from tests import parity
+cfg = bi.toy_pair(dtype=bi.DT_BF16, d=256, heads=4, d_head=64, d_ff=512, vocab=2000, truncate=True, n_small=4, n_large=12,
+                  n_src=20, max_new=64)
+pair = parity.make_gpu_pair(cfg, *bi.make_pair_weights(cfg))
+src = bi.make_source(cfg)
+state = lambda: pkg.State(pair, len(src), cfg.max_new + 2, cfg.n_max)
+whole = lambda s: s.generate(src, cfg.alpha_fb, cfg.alpha_rb, cfg.max_new)[0]
+idle = state()
+want = whole(idle)
+states = [state(), state()]
+assert all(whole(s) == want for s in states)
+
+def both(n):
+    got, start = [None] * n, threading.Barrier(n + 1)
+    def work(i):
+        start.wait()
+        states[i].seq_truncate(1)
+        got[i] = states[i].generate(None, cfg.alpha_fb, cfg.alpha_rb, cfg.max_new)[0]
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(n)]
+    for t in threads: t.start()
+    start.wait()
+    t0 = time.perf_counter()
+    for t in threads: t.join()
+    dt = time.perf_counter() - t0
+    assert all(g == want for g in got)
+    return dt
+
+one, two = (min(both(n) for _ in range(5)) for n in (1, 2))
+print("ratio", two / one, "one", one)
+"""
+
+
+def test_streams_of_requests_at_once_do_not_share_a_queue():
+    """Passes as kernels of their own: two requests at once take little longer than one (1.1 times; twice as long where their
+    streams are on one hardware queue)."""
+    r = subprocess.run([sys.executable, "-c", OVERLAP], cwd=ROOT, env={**os.environ, "BILD_ONE_KERNEL": "0"}, capture_output=True,
+                       text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    ratio = float(r.stdout.split("ratio")[1].split()[0])
+    print(r.stdout.strip())
+    assert ratio < 1.6
