@@ -58,6 +58,9 @@ int bild_gemm_tally(bild_state* s, int64_t* launches, int64_t* bytes, int reset)
 /* Kernel launches (dependent stages) of the pass the host issued last - the one bild_bench_gemm issues to count its
  * GEMM launches counts here too; replays of captured graphs do not change it. */
 int bild_pass_stages(bild_state* s, int32_t* stages);
+/* Passes with an LM head the state has run so far: out = {as one kernel over the whole chip, as one kernel on one die,
+ * as a chain of kernels, those of the first two whose workgroups did not all get to run and that were run again}. */
+int bild_pass_routes(bild_state* s, int64_t out[4]);
 int bild_profile_begin(bild_state* s, int max_records);
 int bild_profile_end(bild_state* s, bild_profile* out);
 

@@ -59,6 +59,7 @@ static hipError_t launch_probe_copy(const void* src, void* dst, size_t bytes, hi
 extern "C" int bild_bench_pass(bild_state* s, int which, int rows, int reps, float* ms_per_pass) {
     if (!s || !ms_per_pass || which < 1 || which > 2 || rows < 1 || rows > kMaxRows || reps < 1) return BILD_EINVAL;
     if (!s->encoded) return BILD_ESTATE;
+    const Call call(s);
     const int w = which - 1;
     if (s->y_len - s->len[w] < rows) return BILD_ESTATE;
     int rc = catch_up(s, w, s->y_len - rows);  // the timed passes cover exactly the last `rows` tokens
@@ -71,7 +72,7 @@ extern "C" int bild_bench_pass(bild_state* s, int which, int rows, int reps, flo
     for (int i = 0; i < reps && rc == BILD_OK; ++i) rc = run_pass(s, w, rows, rows, 4);
     if (rc == BILD_OK && hipEventRecord(e1, s->stream) != hipSuccess) rc = BILD_EHIP;
     if (rc == BILD_OK && hipEventSynchronize(e1) != hipSuccess) rc = BILD_EHIP;
-    end_turn(s);
+    if (rc) (void)hipStreamSynchronize(s->stream);  // (no pass outlives the call)
     float ms = 0.f;
     if (rc == BILD_OK && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = BILD_EHIP;
     (void)hipEventDestroy(e0);
@@ -86,6 +87,7 @@ extern "C" int bild_bench_gemm(bild_state* s, int which, int rows, int reps, flo
     if (!s || !ms_per_pass || !launches || !bytes || which < 1 || which > 2 || rows < 1 || rows > kMaxRows || reps < 1)
         return BILD_EINVAL;
     if (!s->encoded) return BILD_ESTATE;
+    const Call call(s);
     const int w = which - 1;
     if (s->y_len - s->len[w] < rows) return BILD_ESTATE;
     int rc = catch_up(s, w, s->y_len - rows);
@@ -119,6 +121,12 @@ extern "C" int bild_bench_gemm(bild_state* s, int which, int rows, int reps, flo
 extern "C" int bild_pass_stages(bild_state* s, int32_t* stages) {
     if (!s || !stages) return BILD_EINVAL;
     *stages = s->stage_count;
+    return BILD_OK;
+}
+
+extern "C" int bild_pass_routes(bild_state* s, int64_t out[4]) {
+    if (!s || !out) return BILD_EINVAL;
+    std::copy(s->routes, s->routes + 4, out);
     return BILD_OK;
 }
 

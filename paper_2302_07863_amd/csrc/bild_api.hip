@@ -264,31 +264,32 @@ extern "C" int bild_pair_destroy(bild_pair* p) {
 // ======================================================================= state
 namespace {
 
-// A pass kernel's workgroups wait for each other, so all of them have to be on the chip: two such passes at a time could keep
-// half of each other's out.  One state per device has the turn, from the launch of its pass until it has seen the result;
-// who does not get it runs the pass as separate kernels.
+// States that are inside a call, by device.  The workgroups of a pass kernel wait for each other, so all of them have to be on the
+// chip: two such passes at a time could keep half of each other's out, and a pass of separate kernels crawls where it finds them.
+// So only a state that is inside a call alone takes the pass kernel.  Calls return when their passes have ended: no other pass
+// kernel is in flight then.
+// Two, three, four requests together, six generations each, T5-large / T5-small shapes, tokens/s, each on a hardware queue of its
+// own: a pass kernel for whoever finds none in flight 3870, 4066, 4320, this rule 3930, 5050, 5980, and 4100, 5560, 6800 once the
+// graphs of the separate kernels are captured (one alone: 3040 with the pass kernel, 2265 without).
+// (Three whose streams share a queue: 3600 and 3090.  Staying with separate kernels for 5 ms after two calls have met, for
+// requests driven call by call: no gain.)
 constexpr int kMaxDevices = 64;
-std::atomic<bool> g_turn[kMaxDevices];
-
-bool take_turn(bild_state* s) {
-    if (s->has_turn) return true;
-    bool free = false;
-    s->has_turn = s->device < kMaxDevices && g_turn[s->device].compare_exchange_strong(free, true, std::memory_order_acquire);
-    return s->has_turn;
-}
+std::atomic<int> g_inside[kMaxDevices];
+std::atomic<int>& inside(const bild_state* s) { return g_inside[s->device % kMaxDevices]; }
+bool alone(const bild_state* s) { return inside(s).load(std::memory_order_acquire) <= 1; }
 
 }  // namespace
 
-void bild::end_turn(bild_state* s) {
-    if (!s->has_turn) return;
-    s->has_turn = false;
-    g_turn[s->device].store(false, std::memory_order_release);
+bild::Call::Call(bild_state* state) : s(state) {
+    if (s->depth++ == 0) inside(s).fetch_add(1, std::memory_order_acq_rel);
+}
+bild::Call::~Call() {
+    if (--s->depth == 0) inside(s).fetch_sub(1, std::memory_order_acq_rel);
 }
 
 extern "C" int bild_state_destroy(bild_state* s) {
     if (!s) return BILD_EINVAL;
     if (s->stream) (void)hipStreamSynchronize(s->stream);
-    end_turn(s);
     for (void* p : s->allocs) (void)hipFree(p);
     for (void* p : s->host_allocs) (void)hipHostFree(p);
     for (hipEvent_t e : s->prof_ev) (void)hipEventDestroy(e);
@@ -568,7 +569,6 @@ int pull_ctl(bild_state* s) {
         HIPC(hipStreamSynchronize(s->stream));
         s->seq_issued = __atomic_load_n(&s->hctl->seq, __ATOMIC_ACQUIRE);
     }
-    end_turn(s);
     if (s->hctl->res_flag & kFlagFailed) return kPassFailed;
     s->y_len = s->hctl->y_len;
     s->draft_start = s->hctl->draft_start;
@@ -1284,9 +1284,10 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // against a gain per layer of 2 us for one row, 7 for two, 9 for four, 14 for eight (T5-large shape; T5-small, one row: 0.9).
 // Keys of the sequence itself are not asked for ahead; past 256 of them the waves have more than a block each.
 // (On one die the gain is 6 us per layer at 512 keys and gone at 1000, T5-small shape.)
+static bool on_one_die(const bild_state* s, int w, int T) { return s->ms[w].pass_die_groups > 0 && T <= kPassDieRows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
-           s->n_src <= (s->ms[w].pass_die_groups > 0 && T <= kPassDieRows ? 1000 : T == 1 ? 640 : 896 + 128 * T) && s->len[w] + T <= 256;
+           s->n_src <= (on_one_die(s, w, T) ? 1000 : T == 1 ? 640 : 896 + 128 * T) && s->len[w] + T <= 256;
 }
 
 int key_bucket(int nkeys) {
@@ -1306,7 +1307,8 @@ int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
     }
     const int bucket = key_bucket(s->len[w] + T);
     if (lm_rows > 0) s->ms[w].last_rows = lm_rows;
-    const bool one = takes_one_kernel(s, w, T, lm_rows) && take_turn(s);
+    const bool one = takes_one_kernel(s, w, T, lm_rows) && alone(s);
+    if (lm_rows > 0 && !s->gemm_only) s->routes[!one ? ROUTE_KERNELS : on_one_die(s, w, T) ? ROUTE_DIE : ROUTE_CHIP] += 1;
     if (!s->use_graphs || s->prof_on || mode == 3) {
         const int rc = decoder_pass(s, w, T, lm_rows, mode, bucket, one);
         if (rc == BILD_OK && !s->gemm_only) s->seq_issued += 1;  // its policy kernel will count this pass
@@ -1355,11 +1357,11 @@ int finish_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
     int rc = run_pass(s, w, T, lm_rows, mode);
     if (rc == BILD_OK) rc = pull_ctl(s);
     if (rc == kPassFailed) {
+        s->routes[ROUTE_GAVE_UP] += 1;
         s->one_kernel = false;
         rc = run_pass(s, w, T, lm_rows, mode);
         if (rc == BILD_OK) rc = pull_ctl(s);
     }
-    end_turn(s);
     return rc;
 }
 
@@ -1544,6 +1546,7 @@ int run_encoders(bild_state* s) {
 // ======================================================================= request API
 extern "C" int bild_encode(bild_state* s, const int32_t* src, int n_src) {
     if (!s || !src) return BILD_EINVAL;
+    const Call call(s);
     if (n_src < 1) return BILD_EINVAL;
     if (n_src > s->max_src) return BILD_ECAP;
     const int V = s->pair->m[1]->cfg.vocab;
@@ -1591,6 +1594,7 @@ extern "C" int bild_encode(bild_state* s, const int32_t* src, int n_src) {
 extern "C" int bild_small_step(bild_state* s, float alpha_fb, int32_t* token, int32_t* fallback_flag,
                                float* max_prob) {
     if (!s || !token || !fallback_flag) return BILD_EINVAL;
+    const Call call(s);
     if (!s->encoded) return BILD_ESTATE;
     if (s->len[0] >= s->y_len) return BILD_ESTATE;  // nothing unconsumed
     if (s->y_len >= s->max_len) return BILD_ECAP;
@@ -1610,6 +1614,7 @@ extern "C" int bild_small_step(bild_state* s, float alpha_fb, int32_t* token, in
 extern "C" int bild_large_verify(bild_state* s, const int32_t* draft, int n, float alpha_rb, int32_t* out_tokens,
                                  int32_t* n_out, int32_t* rollback_pos, float* nll) {
     if (!s || !out_tokens || !n_out || !rollback_pos) return BILD_EINVAL;
+    const Call call(s);
     if (!s->encoded) return BILD_ESTATE;
     if (draft) {
         if (n < 0) return BILD_EINVAL;
@@ -1707,6 +1712,7 @@ extern "C" int bild_get_sequence(bild_state* s, int32_t* out, int cap, int32_t* 
 extern "C" int bild_generate(bild_state* s, const int32_t* src, int n_src, float alpha_fb, float alpha_rb,
                              int max_new, int32_t eos, int32_t* out, int32_t* n_out, bild_stats* stats) {
     if (!s || !out || !n_out || max_new < 0) return BILD_EINVAL;
+    const Call call(s);
     int rc = BILD_OK;
     if (src) {
         rc = bild_encode(s, src, n_src);
@@ -1753,6 +1759,7 @@ extern "C" int bild_generate(bild_state* s, const int32_t* src, int n_src, float
 extern "C" int bild_greedy(bild_state* s, int which, const int32_t* src, int n_src, int max_new, int32_t eos,
                            int32_t* out, int32_t* n_out) {
     if (!s || !out || !n_out || max_new < 0 || which < 1 || which > 2) return BILD_EINVAL;
+    const Call call(s);
     int rc = BILD_OK;
     if (src) {
         rc = bild_encode(s, src, n_src);

@@ -208,6 +208,9 @@ struct ModelState {
     char* pass_die_scratch[bild::kPassDieRows + 1] = {};  // by rows: two sets each
 };
 
+// How a pass ran (ROUTE_GAVE_UP: those of the first two that were run again as kernels).
+enum Route : int { ROUTE_CHIP = 0, ROUTE_DIE = 1, ROUTE_KERNELS = 2, ROUTE_GAVE_UP = 3 };
+
 struct bild_state {
     const bild_pair* pair = nullptr;
     ModelState ms[2];
@@ -224,7 +227,8 @@ struct bild_state {
     unsigned* pass_sync = nullptr;
     int pass_spins = 6000;    // 4 ms: kernels of other streams come to an end in that time, the same kernel of another process does not
     int device = 0, cus = 0;
-    bool has_turn = false;    // (see take_turn)
+    int depth = 0;            // calls of this state that are on the stack (see Call)
+    int64_t routes[4] = {};   // passes with an LM head so far, by Route
     int ksplit_max_d = 2048;      // ... of models up to this wide (7B-shaped small model, 2048 wide: 0.729 -> 0.717 ms per step)
     int ksplit_min_f = 2048;      // FFN widths from which the output projection of a narrow model (d <= 1024) is cut into input slices
     int fuse_max_kv = 32 << 10;   // ... while one head's cached K/V are at most this many bytes
@@ -270,7 +274,13 @@ namespace bild {
 int dev_alloc(std::vector<void*>& keep, void** p, size_t bytes);
 int key_bucket(int nkeys);
 int catch_up(bild_state* s, int w, int target);
-void end_turn(bild_state* s);
+// A call of the library that runs passes, from its entry to its end (see g_inside, bild_api.hip).
+struct Call {
+    bild_state* s;
+    explicit Call(bild_state* state);
+    ~Call();
+    Call(const Call&) = delete;
+};
 int run_pass(bild_state* s, int w, int T, int lm_rows, int mode);
 int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hint, bool one);
 int pick_splits_raw(int d_head, int esz, int max_splits, int nkeys, int heads, int T, bool* defer);

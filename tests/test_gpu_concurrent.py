@@ -3,8 +3,13 @@ others."""
 import os
 import subprocess
 import sys
+import threading
 
 import pytest
+
+import bild_inputs as bi
+import paper_2302_07863_amd as pkg
+from tests import parity
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +62,56 @@ def test_streams_of_requests_at_once_do_not_share_a_queue():
     ratio = float(r.stdout.split("ratio")[1].split()[0])
     print(r.stdout.strip())
     assert ratio < 1.6
+
+
+def test_pass_kernel_only_for_a_request_that_is_alone():
+    """Two requests at once run their passes as separate kernels, from the first moment both are at work, and produce what they
+    produce alone; a request that is alone again takes the pass kernel again.  (Both models of this pair are shapes it is made for.)"""
+    cfg = bi.toy_pair(dtype=bi.DT_BF16, d=256, heads=4, d_head=64, d_ff=512, vocab=2000, truncate=True, n_small=4, n_large=12,
+                      n_src=20, max_new=64)
+    pair = parity.make_gpu_pair(cfg, *bi.make_pair_weights(cfg))
+    src = bi.make_source(cfg)
+    states = [pkg.State(pair, len(src), cfg.max_new + 2, cfg.n_max) for _ in range(2)]
+
+    def one(st):
+        st.seq_truncate(1)
+        return st.generate(None, cfg.alpha_fb, cfg.alpha_rb, cfg.max_new)
+
+    def routes(st):
+        r = st.pass_routes()
+        return r["chip"] + r["die"], r["kernels"]
+
+    want = None
+    for st in states:
+        st.encode(src)
+        got = one(st)
+        assert want is None or got == want
+        want = got
+        passes, kernels = routes(st)
+        assert passes == got[1]["small_steps"] + got[1]["large_calls"] and kernels == 0
+    reps, met, at_work, wrong = 12, [], threading.Barrier(2), []
+
+    def work(i):
+        at_work.wait()
+        before = routes(states[i])
+        for _ in range(reps):
+            if one(states[i]) != want:
+                wrong.append(i)
+        met.append(tuple(b - a for a, b in zip(before, routes(states[i]))))
+        while len(met) < 2:      # keep the other one company to its end
+            one(states[i])
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=60)
+    assert len(met) == 2 and not wrong
+    print(met, want[1])
+    for as_one, kernels in met:  # (a request that waits for the interpreter between two generations leaves the other alone for a while)
+        assert kernels > 0.7 * (as_one + kernels), met
+    a = routes(states[0])
+    assert one(states[0]) == want
+    b = routes(states[0])
+    assert b[1] == a[1] and b[0] - a[0] == passes
+    assert states[0].pass_routes()["gave_up"] == 0
