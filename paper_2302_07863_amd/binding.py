@@ -84,6 +84,7 @@ _SIGS = {
     "bild_gemm_tally": (C.c_int, [C.c_void_p, C.POINTER(C.c_int64), C.POINTER(C.c_int64), C.c_int]),
     "bild_pass_stages": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32)]),
     "bild_pass_routes": (C.c_int, [C.c_void_p, C.POINTER(C.c_int64)]),
+    "bild_debug_pass_spins": (C.c_int, [C.c_void_p, C.c_int]),
     "bild_probe_stream": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_float)]),
     "bild_probe_launch": (C.c_int, [C.c_void_p, C.c_int, C.POINTER(C.c_float)]),
     "bild_debug_tiled_bytes": (C.c_int64, [C.c_int, C.c_int, C.c_int]),
@@ -322,6 +323,9 @@ class State:
         out = (C.c_int64 * 4)()
         _check(lib().bild_pass_routes(self.h, out), "bild_pass_routes")
         return dict(zip(("chip", "die", "kernels", "gave_up"), out))
+
+    def debug_pass_spins(self, spins: int):
+        _check(lib().bild_debug_pass_spins(self.h, spins), "bild_debug_pass_spins")
 
     def gemm_tally(self, reset: bool = False) -> dict:
         n, b = C.c_int64(), C.c_int64()

@@ -64,6 +64,8 @@ extern "C" int bild_bench_pass(bild_state* s, int which, int rows, int reps, flo
     if (s->y_len - s->len[w] < rows) return BILD_ESTATE;
     int rc = catch_up(s, w, s->y_len - rows);  // the timed passes cover exactly the last `rows` tokens
     if (rc) return rc;
+    HIPC(hipStreamSynchronize(s->stream));
+    s->hctl->res_flag = 0;  // (no pass in flight; a pass that commits nothing only leaves here that it gave up)
     hipEvent_t e0, e1;
     HIPC(hipEventCreate(&e0));
     HIPC(hipEventCreate(&e1));
@@ -73,6 +75,10 @@ extern "C" int bild_bench_pass(bild_state* s, int which, int rows, int reps, flo
     if (rc == BILD_OK && hipEventRecord(e1, s->stream) != hipSuccess) rc = BILD_EHIP;
     if (rc == BILD_OK && hipEventSynchronize(e1) != hipSuccess) rc = BILD_EHIP;
     if (rc) (void)hipStreamSynchronize(s->stream);  // (no pass outlives the call)
+    if (s->hctl->res_flag & kFlagFailed) {
+        const int rc2 = pass_gave_up(s, w, rows);
+        if (rc == BILD_OK) rc = rc2;
+    }
     float ms = 0.f;
     if (rc == BILD_OK && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = BILD_EHIP;
     (void)hipEventDestroy(e0);

@@ -48,6 +48,18 @@ bool config_ok(const bild_model_config& c) {
     return true;
 }
 
+// the two sets of what the workgroups of a pass on one die hand over
+size_t pass_die_bytes(const ModelState& M, int T) {
+    return 2 * M.m->dec.size() * (size_t)pass_plan(T, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff).layer;
+}
+
+// captured passes carry some of the state's settings by value: where one changes they are captured anew
+void drop_graphs(bild_state* s) {
+    (void)hipStreamSynchronize(s->stream);
+    for (auto& kv : s->graphs) (void)hipGraphExecDestroy(kv.second);
+    s->graphs.clear();
+}
+
 int upload_vec(bild_model* m, const float* src, int n, const float** out) {
     void* d;
     int rc = dev_alloc(m->allocs, &d, (size_t)n * 4);
@@ -414,7 +426,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             if (M.pass_groups && s->one_die && s->cus == 256) M.pass_die_groups = pass_die_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated());
             if (M.pass_groups) {
                 want(M.pass_layers, sizeof(PassLayer) * L);
-                for (int T = 1; T <= kPassDieRows && M.pass_die_groups; ++T) want(M.pass_die_scratch[T], 2 * L * (size_t)pass_plan(T, (int)d, (int)I, (int)F).layer);
+                for (int T = 1; T <= kPassDieRows && M.pass_die_groups; ++T) want(M.pass_die_scratch[T], pass_die_bytes(M, T));
                 want(M.pass_scratch, L * (size_t)pass_plan(kPassRows, (int)d, (int)I, (int)F).layer);
             }
         }
@@ -469,7 +481,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         ModelState& M = s->ms[w];
         if (!M.pass_groups) continue;
         for (int T = 1; T <= kPassDieRows && M.pass_die_groups && e == hipSuccess; ++T)
-            e = hipMemsetAsync(M.pass_die_scratch[T], 0xFF, 2 * M.m->dec.size() * (size_t)pass_plan(T, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff).layer, s->stream);
+            e = hipMemsetAsync(M.pass_die_scratch[T], 0xFF, pass_die_bytes(M, T), s->stream);
         if (e != hipSuccess) break;
         const size_t kv = (size_t)s->cap_len * M.m->inner() * M.m->esz(), ckv = (size_t)s->cap_src * M.m->inner() * M.m->esz();
         for (size_t l = 0; l < M.m->dec.size(); ++l) {
@@ -1307,7 +1319,12 @@ int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
     }
     const int bucket = key_bucket(s->len[w] + T);
     if (lm_rows > 0) s->ms[w].last_rows = lm_rows;
-    const bool one = takes_one_kernel(s, w, T, lm_rows) && alone(s);
+    bool one = takes_one_kernel(s, w, T, lm_rows) && alone(s);
+    if (one && s->pass_pause > 0) {  // (see pass_gave_up)
+        s->pass_pause -= 1;
+        one = false;
+    }
+    s->last_one = one;
     if (lm_rows > 0 && !s->gemm_only) s->routes[!one ? ROUTE_KERNELS : on_one_die(s, w, T) ? ROUTE_DIE : ROUTE_CHIP] += 1;
     if (!s->use_graphs || s->prof_on || mode == 3) {
         const int rc = decoder_pass(s, w, T, lm_rows, mode, bucket, one);
@@ -1336,6 +1353,20 @@ int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
     return BILD_OK;
 }
 
+// After a pass of T rows that gave up.  What kept workgroups out may be gone by the next pass (work of another stream) or stay
+// (another process' pass kernel), and each attempt takes 4 ms: the state's next 16 passes run as separate kernels, twice as many
+// after each further attempt in vain, 65 536 at most (which is 40 s of passes for 4 ms).
+int pass_gave_up(bild_state* s, int w, int T) {
+    s->routes[ROUTE_GAVE_UP] += 1;
+    s->pass_pause = 16 << s->pass_fails;
+    s->pass_fails = std::min(s->pass_fails + 1, 12);
+    // the form on one die leaves its two sets in no known state: nothing is there yet in either
+    const ModelState& M = s->ms[w];
+    if (on_one_die(s, w, T))
+        HIPC(hipMemsetAsync(M.pass_die_scratch[T], 0xFF, pass_die_bytes(M, T), s->stream));
+    return BILD_OK;
+}
+
 // Brings model w's cache up to `target` consumed rows with LM-head-less passes.
 int catch_up(bild_state* s, int w, int target) {
     while (s->len[w] < target) {
@@ -1352,14 +1383,14 @@ int catch_up(bild_state* s, int w, int target) {
 namespace {
 
 // One pass and its result.  A pass kernel whose workgroups did not all get to run has changed nothing that counts: the pass runs
-// again as separate kernels, and so do this state's passes from then on.
+// again as separate kernels.
 int finish_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
     int rc = run_pass(s, w, T, lm_rows, mode);
     if (rc == BILD_OK) rc = pull_ctl(s);
+    if (rc == BILD_OK && s->last_one) s->pass_fails = 0;
     if (rc == kPassFailed) {
-        s->routes[ROUTE_GAVE_UP] += 1;
-        s->one_kernel = false;
-        rc = run_pass(s, w, T, lm_rows, mode);
+        rc = pass_gave_up(s, w, T);
+        if (rc == BILD_OK) rc = run_pass(s, w, T, lm_rows, mode);
         if (rc == BILD_OK) rc = pull_ctl(s);
     }
     return rc;
@@ -1807,14 +1838,8 @@ extern "C" int bild_debug_enable_logits(bild_state* s, int enable) {
 
 extern "C" int bild_set_sampling(bild_state* s, float top_p, const float* u_small, const float* u_large, int n) {
     if (!s) return BILD_EINVAL;
-    // captured passes carry top_p by value: a new value starts from fresh captures
-    auto drop_graphs = [&]() {
-        (void)hipStreamSynchronize(s->stream);
-        for (auto& kv : s->graphs) (void)hipGraphExecDestroy(kv.second);
-        s->graphs.clear();
-    };
     if (!(top_p > 0.f)) {  // back to argmax (and to the threshold rule of the review, which is all argmax decoding has)
-        if (s->top_p > 0.f) drop_graphs();
+        if (s->top_p > 0.f) drop_graphs(s);
         s->top_p = 0.f;
         s->accept_mode = 0;
         return BILD_OK;
@@ -1838,22 +1863,17 @@ extern "C" int bild_set_sampling(bild_state* s, float top_p, const float* u_smal
         rc = dev_alloc(s->allocs, (void**)&s->draw_ws, sizeof(DrawWs));
         if (rc) return rc;
         HIPC(hipMemset(s->draw_ws, 0, sizeof(DrawWs)));
-        drop_graphs();  // (none can have been captured with a draw yet; kept for safety)
+        drop_graphs(s);  // (none can have been captured with a draw yet; kept for safety)
     }
-    if (s->top_p != top_p) drop_graphs();
+    if (s->top_p != top_p) drop_graphs(s);
     s->top_p = top_p;
     return BILD_OK;
 }
 
 extern "C" int bild_set_acceptance(bild_state* s, int rule, const float* u_accept, int n) {
     if (!s || (rule != BILD_ACCEPT_THRESHOLD && rule != BILD_ACCEPT_REJECTION)) return BILD_EINVAL;
-    auto drop_graphs = [&]() {  // captured passes carry the rule by value
-        (void)hipStreamSynchronize(s->stream);
-        for (auto& kv : s->graphs) (void)hipGraphExecDestroy(kv.second);
-        s->graphs.clear();
-    };
     if (rule == BILD_ACCEPT_THRESHOLD) {
-        if (s->accept_mode != 0) drop_graphs();
+        if (s->accept_mode != 0) drop_graphs(s);
         s->accept_mode = 0;
         return BILD_OK;
     }
@@ -1874,8 +1894,15 @@ extern "C" int bild_set_acceptance(bild_state* s, int rule, const float* u_accep
         HIPC(hipMemset(s->s_draw, 0, sizeof(float4) * (size_t)(s->max_len + 1)));
     }
     HIPC(hipMemcpy(s->u_acc, u_accept, sizeof(float) * (size_t)s->max_len, hipMemcpyHostToDevice));
-    if (s->accept_mode != 1) drop_graphs();
+    if (s->accept_mode != 1) drop_graphs(s);
     s->accept_mode = 1;
+    return BILD_OK;
+}
+
+extern "C" int bild_debug_pass_spins(bild_state* s, int spins) {
+    if (!s || spins < 1) return BILD_EINVAL;
+    drop_graphs(s);
+    s->pass_spins = spins;
     return BILD_OK;
 }
 

@@ -225,6 +225,8 @@ struct bild_state {
     bool one_kernel = true;   // passes of up to kPassRows rows of a narrow bf16 model run as one kernel
     bool one_die = true;      // ... on one die, if it fits
     unsigned* pass_sync = nullptr;
+    bool last_one = false;    // the pass issued last is one kernel
+    int pass_pause = 0, pass_fails = 0;  // passes to run as separate kernels before the next attempt; attempts in vain in a row
     int pass_spins = 6000;    // 4 ms: kernels of other streams come to an end in that time, the same kernel of another process does not
     int device = 0, cus = 0;
     int depth = 0;            // calls of this state that are on the stack (see Call)
@@ -282,6 +284,7 @@ struct Call {
     Call(const Call&) = delete;
 };
 int run_pass(bild_state* s, int w, int T, int lm_rows, int mode);
+int pass_gave_up(bild_state* s, int w, int T);
 int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hint, bool one);
 int pick_splits_raw(int d_head, int esz, int max_splits, int nkeys, int heads, int T, bool* defer);
 int pick_attn_waves(int dtype, int d_head, int T, int nkeys, int splits);

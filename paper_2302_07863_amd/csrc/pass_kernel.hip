@@ -33,8 +33,8 @@
 //
 // A workgroup that has polled `spins` times in vain flags the pass as failed and walks on without waiting again (nothing
 // handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
-// the pass again as separate kernels.  That happens only if the workgroups cannot all be resident, because of another process'
-// kernel of the same kind, for instance.
+// the pass again as separate kernels; after some passes it tries this kernel again.  That happens only if the workgroups cannot
+// all be resident, because of another process' kernel of the same kind, for instance.
 #include "kernel_common.h"
 
 namespace bild {

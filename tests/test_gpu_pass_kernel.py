@@ -4,6 +4,7 @@ import pytest
 
 import bild_inputs as bi
 import oracle
+import paper_2302_07863_amd as pkg
 from tests import parity
 from tests.test_gpu_parity import Rig
 
@@ -45,3 +46,32 @@ def test_a_pass_that_gives_up_runs_again_as_kernels(monkeypatch):
     """No poll is waited for: the first pass is flagged, commits nothing, and the request goes on without the kernel."""
     monkeypatch.setenv("BILD_PASS_SPINS", "1")
     _check()
+
+
+@pytest.mark.parametrize("how", ["passes", "measurement"])
+def test_the_kernel_is_tried_again_after_a_pass_gave_up(how):
+    """Both forms (one die up to four rows, the whole chip above): what made a pass give up may be gone, so the state comes back to
+    the kernel, with the tokens it would have produced anyway."""
+    cfg = bi.toy_pair(dtype=bi.DT_BF16, d=256, heads=4, d_head=64, d_ff=512, truncate=True, n_src=20, max_new=40)
+    R = Rig(cfg)
+    generate = lambda st: st.generate(R.src, cfg.alpha_fb, cfg.alpha_rb, cfg.max_new)
+    sound = R.state(cfg.max_new, cfg.n_max)
+    want = generate(sound)
+    r = sound.pass_routes()
+    assert r["chip"] > 0 and r["die"] > 0 and r["kernels"] == r["gave_up"] == 0
+    st = R.state(cfg.max_new, cfg.n_max)
+    st.debug_pass_spins(1)
+    if how == "passes":
+        assert generate(st) == want
+    else:
+        st.encode(R.src)
+        st.bench_pass(pkg.SMALL, 1, 3)
+    failed = st.pass_routes()["gave_up"]
+    assert failed > 0
+    st.debug_pass_spins(6000)
+    for _ in range(8):                 # (a few attempts in vain: at most some hundred passes as kernels follow)
+        before = st.pass_routes()
+        assert generate(st) == want
+        now = {k: v - before[k] for k, v in st.pass_routes().items()}
+    assert now == r
+    assert st.pass_routes()["gave_up"] == failed
