@@ -208,7 +208,17 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(const AttnArgs a) {
     }
 }
 
+hipError_t attn_tile_init() {
+    static hipError_t done = [] {
+        const void* fns[] = {(const void*)attn_tile_kernel<1, false>, (const void*)attn_tile_kernel<2, false>, (const void*)attn_tile_kernel<4, false>,
+                             (const void*)attn_tile_kernel<1, true>, (const void*)attn_tile_kernel<2, true>, (const void*)attn_tile_kernel<4, true>};
+        return raise_lds_limit(fns, 160 * 1024);
+    }();
+    return done;
+}
+
 hipError_t launch_attention_tile(const AttnArgs& a, hipStream_t st) {
+    if (hipError_t e = attn_tile_init(); e != hipSuccess) return e;
     if (a.T < 1 || !a.ob_t || !a.len_ptr || a.heads < 1 || a.d_head < 8 || a.d_head > 128 || a.d_head % 8 || a.vcap < 32 || a.vcap % 32 ||
         (!a.causal && (a.nkeys_fixed < 1 || a.nkeys_fixed > a.vcap)) || (a.rel_bias && a.rel_d < 1))
         return hipErrorInvalidValue;
@@ -218,8 +228,6 @@ hipError_t launch_attention_tile(const AttnArgs& a, hipStream_t st) {
     const dim3 grid((unsigned)a.heads, (unsigned)((a.T + 63) / 64)), block(256);
 #define BILD_AT(DHV, RV)                                                                                                     \
     do {                                                                                                                     \
-        static hipError_t e = hipFuncSetAttribute((const void*)attn_tile_kernel<DHV, RV>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
-        if (e != hipSuccess) return e;                                                                                       \
         hipLaunchKernelGGL((attn_tile_kernel<DHV, RV>), grid, block, smem, st, a);                                           \
         return hipGetLastError();                                                                                            \
     } while (0)

@@ -392,8 +392,19 @@ hipError_t launch_ctl(const CtlArgs& a, hipStream_t st);
 hipError_t launch_finish_draw(const FinishArgs& a, hipStream_t st);
 constexpr int kFinishDrawStages = 7;
 hipError_t launch_row_copy(const RowCopyArgs& a, hipStream_t st);
-hipError_t kernels_init();  // one-time function attributes; call before any stream capture
-hipError_t attention_init();  // (attention.hip; called by kernels_init)
+hipError_t kernels_init();  // one-time function attributes, which also load the kernels; call before any stream capture
+// (called by kernels_init)
+hipError_t gemm_init();  // what an LM head alone needs
+hipError_t attention_init();
+hipError_t gemm_tile_init();
+hipError_t attn_tile_init();
+hipError_t pass_init();
+template <size_t N>
+inline hipError_t raise_lds_limit(const void* const (&fns)[N], int bytes) {
+    for (const void* f : fns)
+        if (hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); e != hipSuccess) return e;
+    return hipSuccess;
+}
 size_t gemm_num_blocks(const GemmArgs& a);
 size_t attn_lds_bytes(int dtype, int d_head, int T, int nw);
 void gemm_pick_shape(GemmArgs& a, int dtype);

@@ -455,7 +455,27 @@ int tile_gemm_parts(const TileGemmArgs& a) {
     return (a.W.tn + per - 1) / per;
 }
 
+hipError_t gemm_tile_init() {
+    static hipError_t done = [] {
+#define BILD_T(RTV, FTV, EPIV, ROPEV, GV, SP, SH) (const void*)gemm_tile_kernel<RTV, FTV, EPIV, ROPEV, GV, SP, SH>
+#define BILD_TF(EPIV, ROPEV)                                                                                                 \
+    BILD_T(8, 4, EPIV, ROPEV, false, false, true), BILD_T(4, 4, EPIV, ROPEV, false, false, true),                            \
+    BILD_T(2, 4, EPIV, ROPEV, false, true, false), BILD_T(2, 2, EPIV, ROPEV, false, true, false),                            \
+    BILD_T(2, 1, EPIV, ROPEV, false, true, false), BILD_T(4, 4, EPIV, ROPEV, false, true, false),                            \
+    BILD_T(4, 2, EPIV, ROPEV, false, true, false), BILD_T(4, 1, EPIV, ROPEV, false, true, false)
+        const void* fns[] = {BILD_TF(EPI_RESID, 0), BILD_TF(EPI_ACT, 0), BILD_TF(EPI_QKV, 0), BILD_TF(EPI_QKV, 1),
+                             BILD_T(8, 4, EPI_ACT, 0, true, false, true), BILD_T(4, 4, EPI_ACT, 0, true, false, true),
+                             BILD_T(2, 4, EPI_ACT, 0, true, true, false), BILD_T(2, 2, EPI_ACT, 0, true, true, false),
+                             BILD_T(4, 4, EPI_ACT, 0, true, true, false), BILD_T(4, 2, EPI_ACT, 0, true, true, false)};
+#undef BILD_TF
+#undef BILD_T
+        return raise_lds_limit(fns, 80 * 1024);
+    }();
+    return done;
+}
+
 hipError_t launch_gemm_tile(const TileGemmArgs& a0, hipStream_t st) {
+    if (hipError_t e = gemm_tile_init(); e != hipSuccess) return e;
     TileGemmArgs a = a0;
     const TileShape t = tile_shape(a);
     a.wk = t.wk;
@@ -482,9 +502,6 @@ hipError_t launch_gemm_tile(const TileGemmArgs& a0, hipStream_t st) {
     const size_t smem = (size_t)tile_sums(t.rt) * 4 + (t.share ? (size_t)4 * t.rt * 1024 : a.wk > 1 ? (size_t)kTileWaves * t.rt * t.ft * 1024 : 0);
 #define BILD_T(RTV, FTV, EPIV, ROPEV, GV, SP, SH)                                                                            \
     do {                                                                                                                     \
-        static hipError_t e = hipFuncSetAttribute((const void*)gemm_tile_kernel<RTV, FTV, EPIV, ROPEV, GV, SP, SH>,          \
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);                    \
-        if (e != hipSuccess) return e;                                                                                       \
         hipLaunchKernelGGL((gemm_tile_kernel<RTV, FTV, EPIV, ROPEV, GV, SP, SH>), grid, block, smem, st, a);                 \
         return hipGetLastError();                                                                                            \
     } while (0)

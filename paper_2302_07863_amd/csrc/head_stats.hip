@@ -142,7 +142,7 @@ int check_args(const bild_model* m, const float* x, int rows, bild_row_stats* ou
 extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows, const int32_t* targets_dev,
                                bild_row_stats* out_dev, void* hip_stream) {
     if (int rc = check_args(m, x_dev, rows, out_dev)) return rc;
-    if (kernels_init() != hipSuccess) return BILD_EHIP;
+    if (gemm_init() != hipSuccess) return BILD_EHIP;
     hipStream_t st = (hipStream_t)hip_stream;
     void* slots = nullptr;
     if (int rc = of_device(g_counts_ptr, HIP_SYMBOL(counts), &slots)) return rc;
@@ -161,7 +161,7 @@ extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows
 extern "C" int bild_head_stats_static(const bild_model* m, const float* x_dev, int rows, const int32_t* targets_dev,
                                       bild_row_stats* out_dev, void* hip_stream) {
     if (int rc = check_args(m, x_dev, rows, out_dev)) return rc;
-    if (kernels_init() != hipSuccess) return BILD_EHIP;
+    if (gemm_init() != hipSuccess) return BILD_EHIP;
     void *scr = nullptr, *slots = nullptr;
     if (int rc = of_device(g_scratch_ptr, HIP_SYMBOL(scratch), &scr)) return rc;
     if (int rc = of_device(g_counts_ptr, HIP_SYMBOL(counts), &slots)) return rc;

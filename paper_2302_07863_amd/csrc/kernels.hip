@@ -286,9 +286,16 @@ static hipError_t raise_lds_limits() {
     return done;
 }
 
-hipError_t kernels_init() {
+hipError_t gemm_init() {
     if (hipError_t e = raise_lds_limits(); e != hipSuccess) return e;
-    if (hipError_t e = gemm_pre_init(); e != hipSuccess) return e;
+    return gemm_pre_init();
+}
+
+hipError_t kernels_init() {
+    if (hipError_t e = gemm_init(); e != hipSuccess) return e;
+    if (hipError_t e = gemm_tile_init(); e != hipSuccess) return e;
+    if (hipError_t e = attn_tile_init(); e != hipSuccess) return e;
+    if (hipError_t e = pass_init(); e != hipSuccess) return e;
     return attention_init();
 }
 

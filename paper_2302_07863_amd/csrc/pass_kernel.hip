@@ -853,7 +853,18 @@ PassPlan pass_plan(int T, int d, int I, int F) {
     return p;
 }
 
+hipError_t pass_init() {
+    static hipError_t done = [] {
+        const void* fns[] = {(const void*)pass_kernel<false, true, true>, (const void*)pass_kernel<true, true, true>,
+                             (const void*)pass_kernel<false, true, false>, (const void*)pass_kernel<true, true, false>,
+                             (const void*)pass_kernel<false, false, false>, (const void*)pass_kernel<true, false, false>};
+        return raise_lds_limit(fns, 160 * 1024);
+    }();
+    return done;
+}
+
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
+    if (hipError_t e = pass_init(); e != hipSuccess) return e;
     if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > (a.turn ? kPassDieRows : kPassRows) || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
         (a.cross && !a.nsrc_ptr))
         return hipErrorInvalidValue;
@@ -862,8 +873,6 @@ hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
     const bool gated = a.act != BILD_ACT_RELU;
 #define BILD_P(GV, PV, DV)                                                                                                   \
     do {                                                                                                                     \
-        static hipError_t e = hipFuncSetAttribute((const void*)pass_kernel<GV, PV, DV>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
-        if (e != hipSuccess) return e;                                                                                       \
         hipLaunchKernelGGL((pass_kernel<GV, PV, DV>), dim3(grid), dim3(kPassThreads), smem, st, a);                          \
         return hipGetLastError();                                                                                            \
     } while (0)
