@@ -1,5 +1,6 @@
 """Decoder passes of narrow bf16 models as one kernel, at the edges of its shapes, rows and key blocks, through the C ABI against
 the CPU oracle."""
+import numpy as np
 import pytest
 
 import bild_inputs as bi
@@ -75,3 +76,42 @@ def test_the_kernel_is_tried_again_after_a_pass_gave_up(how):
         now = {k: v - before[k] for k, v in st.pass_routes().items()}
     assert now == r
     assert st.pass_routes()["gave_up"] == failed
+
+
+FORMS = {"die": {}, "chip": {"BILD_ONE_DIE": "0"}, "kernels": {"BILD_ONE_KERNEL": "0"}}
+
+
+@pytest.mark.parametrize("shape", [dict(), dict(act=bi.ACT_GATED_GELU, pos=bi.POS_RELATIVE, d_ff=256), dict(cross=False), dict(act=bi.ACT_SWIGLU, n_src=300)])
+def test_the_forms_of_a_pass_agree(shape, monkeypatch):
+    """Reviews of 1 .. 16 rows and a small step on one die (up to four rows), on the whole chip and as separate kernels.  Each form is
+    within logit_tol of the oracle (teacher-forced), so two of them are within twice that of each other."""
+    cfg = bi.toy_pair(**{**dict(dtype=bi.DT_BF16, d=256, heads=4, d_head=64, d_ff=512, truncate=True, n_src=20, max_new=24), **shape})
+    R = Rig(cfg)
+    ref = oracle.bild_generate(R.req, 0.4, 1.0, 15, 6, keep_logits=True)
+    got = {}
+    for form, env in FORMS.items():
+        with monkeypatch.context() as m:
+            for k, v in env.items():
+                m.setenv(k, v)
+            st = R.state(cfg.max_new, 15)
+        st.encode(R.src)
+        parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, cfg)
+        st.debug_enable_logits(True)
+        logits = []
+        for rows in (1, 2, 3, 4, 5, 8, 9, 16):
+            st.seq_truncate(R.n0)
+            before = st.pass_routes()
+            st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+            now = {k for k, v in st.pass_routes().items() if v > before[k]}
+            assert now == {"chip" if form == "die" and rows > 4 else form}, (form, rows)
+            logits += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+        before = st.pass_routes()[form]
+        st.small_step(0.0)
+        assert st.pass_routes()[form] == before + 1
+        logits.append(st.debug_logits(pkg.SMALL, 0))
+        got[form] = np.stack(logits)
+    tol = 2 * parity.logit_tol(cfg)
+    for a, b in (("die", "chip"), ("die", "kernels"), ("chip", "kernels")):
+        worst = float(np.abs(got[a] - got[b]).max())
+        print(a, b, worst)
+        assert worst <= tol
