@@ -1291,11 +1291,21 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 }
 
 // Passes that produce a token, of shapes and row counts the pass kernel is made for (pass_groups); a caught-up row is rare and
-// its passes follow each other without the host's look at their outcome.  One workgroup per head has all its keys to itself:
-// up to 512 of the source arrive ahead of their use, each further one costs a layer 9 ns more than as kernels that split them,
-// against a gain per layer of 2 us for one row, 7 for two, 9 for four, 14 for eight (T5-large shape; T5-small, one row: 0.9).
-// Keys of the sequence itself are not asked for ahead; past 256 of them the waves have more than a block each.
-// (On one die the gain is 6 us per layer at 512 keys and gone at 1000, T5-small shape.)
+// its passes follow each other without the host's look at their outcome.
+//
+// Source.  One workgroup per head has all its keys to itself: up to 512 arrive ahead of their use, each further one costs a layer
+// 11 ns, where the separate kernels split them over more workgroups and stay as they are.  us per pass, separate kernels / one
+// kernel over the chip, at 512, 640, 1024, 1536 tokens: T5-large shape one row 675 / 617, 672 / 649, 675 / 749, 714 / 882; two rows
+// 784 / 625, 791 / 657, 795 / 756, 833 / 890; four 852 / 619, 854 / 651, 861 / 752, 900 / 886; eight 988 / 634, 1017 / 665, 1025 / 766,
+// 1066 / 899; mT5-large shape one row 722 / 641, 724 / 671, 726 / 772, 768 / 907; 768-wide, one row 348 / 280, 348 / 294, 350 / 341,
+// 373 / 408.  Break-even lies at 735 (T5-large, one row) to 1080 tokens (768-wide), and at 1150, 1580, above 2048 for two, four,
+// eight rows: the lines below are inside of it for every width, activation and row count measured (256 to 1024 wide).
+// On one die one row costs 146 / 97, 147 / 104, 147 / 126, 157 / 158 (T5-small shape; four rows 185 / 100, 189 / 105, 189 / 126,
+// 199 / 159; mT5-small one row 203 / 120, 204 / 129, 205 / 159, 217 / 202; 256-wide 95 / 68, 96 / 72, 96 / 87, 102 / 109).
+//
+// Sequence.  Its keys are not asked for ahead; past 256 of them the waves have more than a block each, and no pass has been
+// tested there.  At 256, 512, 1024 positions: T5-large shape one row 672 / 652, 672 / 708, 705 / 823; two rows 789 / 664, 795 / 720,
+// 830 / 834; eight 988 / 682, 1018 / 739, 1054 / 850; T5-small shape on one die 144 / 104, 145 / 115, 153 / 134.
 static bool on_one_die(const bild_state* s, int w, int T) { return s->ms[w].pass_die_groups > 0 && T <= kPassDieRows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&

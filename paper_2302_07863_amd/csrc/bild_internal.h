@@ -196,7 +196,9 @@ struct AttnArgs {
 };
 
 // A whole decoder pass in one kernel (pass_kernel.hip).
-constexpr int kPassRows = 16, kPassDieRows = 4;  // most rows; on one die
+// Most rows; on one die.  (One die, the whole chip, us, T5-small shape, 512 tokens: one row 97, 137, two 99, 138, four 100, 140;
+// mT5-small shape 120, 178; 121, 180; 122, 181.  The small model of a pair has one row; a narrow large one reviews.)
+constexpr int kPassRows = 16, kPassDieRows = 4;
 constexpr int kPassCounters = 64;  // one per lane of the polling wave
 constexpr int kPassStride = 64;  // words
 constexpr int kPassSyncWords = (kPassCounters + 1) * kPassStride;  // counters on lines of their own, then the ranks given out on a die; the last word: a workgroup gave up
