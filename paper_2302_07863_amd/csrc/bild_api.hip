@@ -1318,9 +1318,10 @@ int key_bucket(int nkeys) {
     return b;
 }
 
-// One pass, replayed from a captured graph when possible.  Launch parameters that depend on the cache
-// length are chosen per power-of-two bucket of the key count, so a graph stays valid while the
-// sequence grows inside its bucket; everything else the kernels need they read from the control block.
+// One pass, replayed from a captured graph when possible.  Launch parameters that depend on the
+// lengths are chosen per power-of-two buckets of the key counts (the sequence's; the source's, which the separate kernels of
+// the cross-attention split), so a graph stays valid while the sequence grows inside its bucket; everything else the kernels
+// need they read from the control block.
 int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
     if (s->pair->trunk_layers > 0 && w == 1 && s->len[0] < s->len[1] + T) {
         // early-exit pair: the upper layers continue from what the trunk left for these rows
@@ -1341,7 +1342,8 @@ int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
         if (rc == BILD_OK && !s->gemm_only) s->seq_issued += 1;  // its policy kernel will count this pass
         return rc;
     }
-    const std::array<int, 6> key = {w, T, lm_rows, mode, bucket, (s->debug_logits ? 1 : 0) | (s->gemm_only ? 2 : 0) | (s->top_p > 0.f ? 4 : 0) | (s->accept_mode ? 8 : 0) | (one ? 16 : 0)};
+    const int source = one || s->pair->decoder_only ? 0 : key_bucket(s->n_src);
+    const std::array<int, 7> key = {w, T, lm_rows, mode, bucket, source, (s->debug_logits ? 1 : 0) | (s->gemm_only ? 2 : 0) | (s->top_p > 0.f ? 4 : 0) | (s->accept_mode ? 8 : 0) | (one ? 16 : 0)};
     auto it = s->graphs.find(key);
     if (it == s->graphs.end()) {
         hipGraph_t g = nullptr;
