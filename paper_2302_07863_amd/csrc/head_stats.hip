@@ -75,7 +75,7 @@ __global__ __launch_bounds__(1024) void head_stats_merge_kernel(const MergeArgs 
     if (lane == 0) share[wave] = StatPart{r.m, r.s, r.idx, 0};
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < nwv; ++w) r = stat_merge(r, Stat{share[w].m, share[w].s, share[w].idx});
+        for (int w = 1; w < nwv; ++w) r = stat_merge<true>(r, Stat{share[w].m, share[w].s, share[w].idx});
         bild_row_stats o;
         o.zmax = r.m;
         o.lse = r.m + logf(r.s);
