@@ -89,7 +89,12 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(const AttnArgs a) {
 
     // m_run is subtracted in the accumulators the products start from; it follows the row's maximum only when that has
     // grown by more than 2^6 (or for the first block), so most blocks neither rescale O nor subtract: probabilities stay below
-    // 64, the quotient is the same.  The row sums are one more product, with a tile of ones.
+    // 64, the quotient is the same.  The row sums are one more product, with a tile of ones: of the weights' high and low bf16
+    // parts (17 bits or more), not of the weights themselves, accumulated in fp32.  O is made of the same parts, so that what a
+    // weight loses cancels in the quotient: error of an output row against 64 bits, sums of the weights / of their parts, scores of
+    // standard deviation 0.5, 2, 5 (simulated, 60 rows each, 2-norms): 8 keys 1.68e-6 / 1.58e-6, 9.7e-7 / 9.1e-7, 4.7e-7 / 4.5e-7;
+    // 512 keys 2.43e-6 / 2.42e-6, 1.65e-6 / 1.61e-6, 9.6e-7 / 9.2e-7; 1531 keys 2.39e-6 / 2.39e-6, 1.73e-6 / 1.71e-6, 9.5e-7 / 9.1e-7;
+    // 4097 keys 2.54e-6 / 2.54e-6, 1.92e-6 / 1.91e-6, 1.09e-6 / 1.08e-6; the worst row never larger.
     float m_run = 0.f;
     f32x4 O[DT16], L = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
