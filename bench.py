@@ -5,9 +5,11 @@ A "step" is one whole BiLD generation (Algorithm 1) of `max_new` tokens for one
 request of the chosen synthetic pair, with the source already encoded and all
 weights resident in HBM.  Prints one JSON line:
   value        generated tokens / second of the BiLD loop (batch 1), passes replayed from captured graphs
-  roofline     the weight-streaming GEMM kernel (the dominant kernel): algorithmic weight bytes per launch /
-               mean duration of a launch (its launches of one BiLD generation replayed alone between two HIP
-               events on the library's stream), vs 8 TB/s; rocprofv3's mean for the same launches beside it
+  roofline     the dominant kernel vs 8 TB/s.  Pairs whose passes run as one kernel (bf16, up to 1024 wide): the whole pass
+               (that kernel, LM head, policy), its algorithmic bytes / its time over the pass mix of one BiLD generation.
+               Others: the weight-streaming GEMM kernel, algorithmic weight bytes per launch / mean duration of a launch (its
+               launches of one generation replayed alone between two HIP events on the library's stream).  rocprofv3's mean
+               for the same kernel beside it
   cpu_baseline the CPU oracle timed on this host on the same workload
 plus per-pass achieved GB/s (algorithmic bytes of one decoder pass / its time) for this pair and, in the default
 run, for the mT5-shaped pair as well, large-model-only greedy tokens/s and the BiLD-vs-large-only speedup.
@@ -49,15 +51,15 @@ def profile_value(name: str, key: str):
     return None
 
 
-def setup(workload: str, shared_trunk: bool = False, top_p: float = 0.0):
-    """Seeded weights and source of one pair, uploaded, with the request encoded."""
+def setup(workload: str, shared_trunk: bool = False, top_p: float = 0.0, n_src: int = 0):
+    """Seeded weights and source (of n_src tokens; 0: the workload's) of one pair, uploaded, with the request encoded."""
     import bild_inputs as bi
     import paper_2302_07863_amd as pkg
 
     cfg = bi.PAIRS[workload]()
     t0 = time.time()
     ws, wl = bi.make_pair_weights(cfg)
-    src = bi.make_source(cfg)
+    src = bi.make_source(cfg, n_src or None)
     log(f"[bench] {workload}: weights generated in {time.time() - t0:.1f}s")
     t0 = time.time()
     large = pkg.Model(pkg.config_from_shape(cfg.large), [wl[n] for n in bi.tensor_names(cfg.large)])
@@ -80,6 +82,7 @@ def setup(workload: str, shared_trunk: bool = False, top_p: float = 0.0):
     st.encode(src)
     encode_ms = (time.perf_counter() - t0) * 1e3
     return SimpleNamespace(cfg=cfg, ws=ws, wl=wl, src=src, pair=pair, st=st, n0=n0, sampler_u=sampler_u,
+                           trunk=cfg.small.n_dec if shared_trunk else 0,
                            encode_ms=encode_ms, pkg=pkg, bi=bi, top_p=top_p)
 
 
@@ -132,16 +135,16 @@ def concurrent_leg(c, fb, rb, streams: int, reps: int, want_tokens):
         if c.sampler_u:
             st.set_sampling(c.top_p, *c.sampler_u)
         st.encode(c.src)
-        st.generate(None, fb, rb, cfg.max_new)  # captures the graphs of this state
     results = [None] * streams
     barrier = threading.Barrier(streams + 1)
 
     def worker(i):
         st = states[i]
-        barrier.wait()
-        for _ in range(reps):
+        for rep in range(reps + 1):
             st.seq_truncate(c.n0)
             results[i] = st.generate(None, fb, rb, cfg.max_new)[0]
+            if rep == 0:       # captures the graphs of this state, those of passes among others' too
+                barrier.wait()
         barrier.wait()
 
     threads = [threading.Thread(target=worker, args=(i,)) for i in range(streams)]
@@ -154,11 +157,13 @@ def concurrent_leg(c, fb, rb, streams: int, reps: int, want_tokens):
     for t in threads:
         t.join()
     same = all(r == want_tokens for r in results)
+    routes = [st.pass_routes() for st in states]
     for st in states:
         st.close()
     n_tok = len(want_tokens)
     return dict(streams=streams, tokens_per_s=round(streams * reps * n_tok / dt, 1),
-                ms_per_generation=round(dt / reps * 1e3, 3), same_tokens_as_single_stream=same)
+                ms_per_generation=round(dt / reps * 1e3, 3), same_tokens_as_single_stream=same,
+                passes={k: sum(r[k] for r in routes) for k in routes[0]})
 
 
 def review_histogram(c, fb, rb):
@@ -177,17 +182,65 @@ def review_histogram(c, fb, rb):
     return small_steps, hist
 
 
+def pass_shape(c, which):
+    """(layers one pass runs, dependent stages of a pass as one kernel with its LM head and policy kernel)"""
+    shape = c.cfg.small if which == c.pkg.SMALL else c.cfg.large
+    layers = shape.n_dec - (c.trunk if which == c.pkg.LARGE else 0)
+    return layers, layers * (7 if shape.cross else 5) + 3  # + embedding, head, policy
+
+
+def route_of(c, which, rows, reps):
+    """Time of a pass over the last `rows` tokens, how it ran and its kernel launches."""
+    st, have = c.st, c.st.lengths()
+    st.kv_truncate(which, min(have["len_small" if which == c.pkg.SMALL else "len_large"], have["y_len"] - rows))
+    before = st.pass_routes()
+    ms = st.bench_pass(which, rows, reps)
+    after = st.pass_routes()
+    return ms, max(("chip", "die", "kernels"), key=lambda k: after[k] - before[k]), st.pass_stages()
+
+
 def roofline_leg(c, fb, rb, stats):
-    """The dominant kernel, the weight-streaming GEMM (layer projections and LM head of both models: one device
-    function).  Its launches are replayed ALONE, in pass order and from the same captured graphs, between two HIP events
-    on the library's stream: the small model's pass and the large model's pass at every row count the BiLD generation
+    pkg = c.pkg
+    small_steps, hist = review_histogram(c, fb, rb)
+    assert small_steps == stats["small_steps"] and sum(hist.values()) == stats["large_calls"], (small_steps, hist, stats)
+    mix = [(pkg.SMALL, 1, small_steps)] + [(pkg.LARGE, rows, count) for rows, count in sorted(hist.items())]
+    timed = [(which, rows, count) + route_of(c, which, rows, 50 if which == pkg.SMALL else 20) for which, rows, count in mix]
+    if any(route == "kernels" for *_, route, _ in timed):
+        return gemm_roofline(c, small_steps, hist)
+    y_len = c.st.lengths()["y_len"]
+    nbytes = ms = launches = 0
+    by_rows, stages = {}, {}
+    for which, rows, count, t, route, n in timed:
+        one = c.st.pass_bytes(which, y_len - rows, rows)
+        nbytes, ms, launches = nbytes + count * one, ms + count * t, launches + count * n
+        rec = dict(passes=count, launches=n, form=route, ms=round(t, 4), us_per_stage=round(t * 1e3 / pass_shape(c, which)[1], 3),
+                   gbs=round(one / t / 1e6, 1))
+        if which == pkg.SMALL:
+            small, stages["small"] = rec, n
+        else:
+            by_rows[rows], stages[f"large_{rows}"] = rec, n
+    achieved, passes = nbytes / ms / 1e6, sum(count for _, _, count in mix)
+    traffic = profile_value(f"gemm_{c.cfg.name}_pmc.txt", "pass_traffic_bytes_per_launch")
+    rocprof_us = profile_value(f"bild_{c.cfg.name}_kernel_stats.txt", "pass_mean_us")
+    return dict(bound="hbm", bound_by="hand-over latency between the dependent stages inside the kernel",
+                kernel="bild::pass_kernel with the LM head (bild::gemm_kernel) and the policy kernel: whole passes",
+                achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s", frac=round(achieved / HBM_PEAK_GBS, 4),
+                traffic=None if traffic is None else int(traffic),  # counted bytes of a launch of pass_kernel alone
+                launches_per_step=launches, passes_per_step=passes, mean_pass_us=round(ms / passes * 1e3, 3),
+                mean_bytes_per_pass=int(nbytes / passes), stages_per_pass=stages,
+                rocprofv3_mean_us=rocprof_us,  # of pass_kernel alone
+                small_pass=small, large_pass_by_rows=by_rows)
+
+
+def gemm_roofline(c, small_steps, hist):
+    """The dominant kernel where passes are chains of kernels, the weight-streaming GEMM (layer projections and LM head of both
+    models: one device function).  Its launches are replayed ALONE, in pass order and from the same captured graphs, between two
+    HIP events on the library's stream: the small model's pass and the large model's pass at every row count the BiLD generation
     uses, weighted by how often each occurs.  Elapsed time / launches is the mean duration of a launch including the
     gap to the next one (an empty kernel measured the same way costs 1.5 us, of which rocprofv3 reports 1.4 us as the
     kernel's own duration).  An event pair around every single launch is not used: around a kernel that does nothing
     such a pair already reads about 6 us."""
     pkg, st, cfg = c.pkg, c.st, c.cfg
-    small_steps, hist = review_histogram(c, fb, rb)
-    assert small_steps == stats["small_steps"] and sum(hist.values()) == stats["large_calls"], (small_steps, hist, stats)
 
     def uncovered(which, rows):  # leave exactly `rows` tokens unconsumed by model `which`
         have = st.lengths()
@@ -334,6 +387,8 @@ def main() -> int:
                          "profiles/ are taken from (with BILD_NO_GRAPH=1)")
     ap.add_argument("--profile-rows", type=int, default=0,
                     help="with --profile-run: instead of generations, --steps large-model passes of this many rows")
+    ap.add_argument("--profile-encode", type=int, default=0,
+                    help="with --profile-run: instead of generations, --steps encodes (prompt prefills) of this many tokens")
     ap.add_argument("--profile-model", choices=("small", "large"), default="large",
                     help="with --profile-rows: the model whose passes are run")
     ap.add_argument("--pmc-probe", action="store_true",
@@ -361,7 +416,7 @@ def main() -> int:
     import paper_2302_07863_amd as pkg
 
     pkg.lib()  # fails loudly if the HIP library has not been built
-    c = setup(args.workload, args.shared_trunk, args.top_p)
+    c = setup(args.workload, args.shared_trunk, args.top_p, args.profile_encode)
     cfg, st, n0, bi = c.cfg, c.st, c.n0, c.bi
     fb = cfg.alpha_fb if args.alpha_fb is None else args.alpha_fb
     rb = cfg.alpha_rb if args.alpha_rb is None else args.alpha_rb
@@ -380,7 +435,10 @@ def main() -> int:
         if args.pmc_probe:
             st.probe_copy(1 << 30, 3)      # bild::probe_copy_kernel: reads 1 GiB and writes 1 GiB per launch
         st.probe_launch(200)               # bild::probe_empty_kernel: what a launch that does nothing costs
-        if args.profile_rows > 0:
+        if args.profile_encode > 0:
+            for _ in range(args.steps):
+                st.encode(c.src)
+        elif args.profile_rows > 0:
             toks, _ = st.generate(None, fb, rb, cfg.max_new)
             ln = st.lengths()
             which = pkg.SMALL if args.profile_model == "small" else pkg.LARGE
@@ -392,7 +450,7 @@ def main() -> int:
                 st.seq_truncate(n0)
                 st.generate(None, fb, rb, cfg.max_new)
         tally = st.gemm_tally()
-        log(f"[bench] profile run done: gemm launches issued {tally['launches']}, algorithmic weight bytes "
+        log(f"[bench] profile run done: passes {st.pass_routes()}; gemm launches issued {tally['launches']}, algorithmic weight bytes "
             f"{tally['bytes']}, mean {tally['bytes'] / max(tally['launches'], 1):.0f} B/launch")
         return 0
 
@@ -424,23 +482,18 @@ def main() -> int:
     toks, stats = st.generate(None, fb, rb, cfg.max_new)
     log(f"[bench] roofline {roofline}")
 
-    # The third line of the report: these passes are chains of dependent stages, so beside the bandwidth roofline stands
-    # stage count x the cost of a launch that does nothing.
+    # The third line of the report: a pass is a chain of dependent stages, so beside the bandwidth roofline stand its launches x
+    # the cost of a launch that does nothing and, where it runs as one kernel, its time per stage inside.
     launch_us = st.probe_launch(2000)
-
-    # kernel launches of a single-row pass as the library issues them (embedding, layer pieces, LM head, policy)
-    n_small = roofline["stages_per_pass"]["small"]
-    n_large = roofline["stages_per_pass"].get("large_1")
-    if n_large is None:
-        uncov = st.lengths()
-        st.kv_truncate(pkg.LARGE, min(uncov["len_large"], uncov["y_len"] - 1))
-        st.bench_gemm(pkg.LARGE, 1, 1)
-        n_large = st.pass_stages()
-    stage_latency = dict(empty_launch_us=round(launch_us, 3),
-                         small_pass=dict(stages=n_small, launch_floor_ms=round(n_small * launch_us * 1e-3, 4),
-                                         measured_ms=passes["small_step"]["ms"]),
-                         large_pass=dict(stages=n_large, launch_floor_ms=round(n_large * launch_us * 1e-3, 4),
-                                         measured_ms=passes["large_step"]["ms"]))
+    stage_latency = dict(empty_launch_us=round(launch_us, 3))
+    for name, which in (("small_pass", pkg.SMALL), ("large_pass", pkg.LARGE)):
+        ms, route, n = route_of(c, which, 1, 50)
+        layers, stages = pass_shape(c, which)
+        stages = n if route == "kernels" else stages
+        stage_latency[name] = dict(form=route, launches=n, stages=stages, launch_floor_ms=round(n * launch_us * 1e-3, 4),
+                                   measured_ms=round(ms, 4), us_per_stage=round(ms * 1e3 / stages, 3))
+    st.seq_truncate(n0)
+    toks, stats = st.generate(None, fb, rb, cfg.max_new)
     log(f"[bench] stage latency {stage_latency}")
 
     # several independent requests at once (one state and one stream each): what the chip delivers when it is not left

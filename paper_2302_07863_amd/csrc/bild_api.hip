@@ -56,7 +56,7 @@ size_t pass_die_bytes(const ModelState& M, int T) {
 // captured passes carry some of the state's settings by value: where one changes they are captured anew
 void drop_graphs(bild_state* s) {
     (void)hipStreamSynchronize(s->stream);
-    for (auto& kv : s->graphs) (void)hipGraphExecDestroy(kv.second);
+    for (auto& kv : s->graphs) (void)hipGraphExecDestroy(kv.second.exec);
     s->graphs.clear();
 }
 
@@ -305,7 +305,7 @@ extern "C" int bild_state_destroy(bild_state* s) {
     for (void* p : s->allocs) (void)hipFree(p);
     for (void* p : s->host_allocs) (void)hipHostFree(p);
     for (hipEvent_t e : s->prof_ev) (void)hipEventDestroy(e);
-    for (auto& kv : s->graphs) (void)hipGraphExecDestroy(kv.second);
+    for (auto& kv : s->graphs) (void)hipGraphExecDestroy(kv.second.exec);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
     return BILD_OK;
@@ -1358,9 +1358,10 @@ int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
         const hipError_t e2 = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
         (void)hipGraphDestroy(g);
         if (e2 != hipSuccess) return BILD_EHIP;
-        it = s->graphs.emplace(key, ge).first;
+        it = s->graphs.emplace(key, bild_state::Captured{ge, s->stage_count}).first;
     }
-    HIPC(hipGraphLaunch(it->second, s->stream));
+    s->stage_count = it->second.stages;
+    HIPC(hipGraphLaunch(it->second.exec, s->stream));
     if (!s->gemm_only) s->seq_issued += 1;
     return BILD_OK;
 }

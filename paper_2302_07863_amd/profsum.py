@@ -2,7 +2,7 @@
 
   python -m paper_2302_07863_amd.profsum stats  <kernel_stats.csv>
   python -m paper_2302_07863_amd.profsum pmc    <fetch counter_collection.csv> <write counter_collection.csv>
-  python -m paper_2302_07863_amd.profsum counters <counter_collection.csv>
+  python -m paper_2302_07863_amd.profsum counters <counter_collection.csv> [full]
   python -m paper_2302_07863_amd.profsum passes <kernel_trace.csv> [passes]
 
 `passes` lists, per kernel instantiation and launch size, the launches of the last `passes` (default 10) decoder passes
@@ -49,6 +49,9 @@ def stats(path: str) -> str:
     g = agg.get("bild::gemm_kernel<*>")
     if g:
         lines.append(f"gemm_mean_us={g[1] / g[0] / 1e3:.3f}")
+    g = agg.get("bild::pass_kernel<*>")
+    if g:
+        lines.append(f"pass_mean_us={g[1] / g[0] / 1e3:.3f}")
     return "\n".join(lines)
 
 
@@ -76,23 +79,29 @@ def pmc(fetch_path: str, write_path: str) -> str:
         lines.append(f"{k:34s} {n:10d} {fb:15.0f} {wb:15.0f}")
         if k.startswith("bild::gemm_kernel"):
             lines.append(f"traffic_bytes_per_launch={fb + wb:.0f}")
+        if k.startswith("bild::pass_kernel"):
+            lines.append(f"pass_traffic_bytes_per_launch={fb + wb:.0f}")
     return "\n".join(lines)
 
 
-def counters(path: str) -> str:
-    """Sums every counter of a --pmc run per kernel group: one line per group with dispatches and, per counter, the
-    mean value per dispatch."""
+def counters(path: str, full: bool = False) -> str:
+    """Sums every counter of a --pmc run per kernel group (`full`: per instantiation and launch size): one line per group with
+    dispatches and, per counter, the mean value per dispatch."""
     agg = collections.defaultdict(lambda: collections.defaultdict(float))
     disp = collections.defaultdict(set)
     for r in csv.DictReader(open(path)):
         g = _group(r["Kernel_Name"])
+        if full:
+            g = re.sub(r"\(.*$", "", r["Kernel_Name"].replace("void ", "")) + f" {int(r['Grid_Size']) // int(r['Workgroup_Size'])}"
         agg[g][r["Counter_Name"]] += float(r["Counter_Value"])
         disp[g].add(r["Dispatch_Id"])
     names = sorted({c for v in agg.values() for c in v})
-    lines = [f"{'kernel':34s} {'dispatches':>10s} " + " ".join(f"{c:>24s}" for c in names)]
+    width = max([34] + [len(g) for g in agg])
+    lines = [f"{'kernel' + (' (template arguments as compiled), workgroups' if full else ''):{width}s} {'dispatches':>10s} " +
+             " ".join(f"{c:>24s}" for c in names)]
     for g in sorted(agg, key=lambda k: -len(disp[k])):
         n = len(disp[g])
-        lines.append(f"{g:34s} {n:10d} " + " ".join(f"{agg[g].get(c, 0.0) / n:24.1f}" for c in names))
+        lines.append(f"{g:{width}s} {n:10d} " + " ".join(f"{agg[g].get(c, 0.0) / n:24.1f}" for c in names))
     return "\n".join(lines)
 
 
@@ -160,7 +169,7 @@ if __name__ == "__main__":
     elif len(sys.argv) >= 3 and sys.argv[1] == "stats":
         print(stats(sys.argv[2]))
     elif len(sys.argv) >= 3 and sys.argv[1] == "counters":
-        print(counters(sys.argv[2]))
+        print(counters(sys.argv[2], sys.argv[3:] == ["full"]))
     elif len(sys.argv) >= 4 and sys.argv[1] == "pmc":
         print(pmc(sys.argv[2], sys.argv[3]))
     else:

@@ -30,6 +30,4 @@ def test_passes_over_another_source_take_its_launch_shapes(dtype, monkeypatch):
     one = pkg.State(pair, len(src), 16, 4)
     for n in (20, 600, 20, 130):
         for (got_stages, got), (stages, want) in zip(passes(one, n), passes(pkg.State(pair, len(src), 16, 4), n)):
-            assert np.array_equal(got, want), n
-            if n != 20 or one.pass_routes()["kernels"] == 2:  # (replays leave the count of the pass captured last)
-                assert got_stages == stages, n
+            assert np.array_equal(got, want) and got_stages == stages, n
