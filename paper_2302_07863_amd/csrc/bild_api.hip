@@ -559,8 +559,8 @@ int set_alpha(bild_state* s, float fb, float rb) {
 }
 
 // Waits for the last pass; its policy kernel has mirrored the control block into pinned host memory.  The mirror's pass
-// counter is polled first (the kernel writes it last, behind a system-wide fence): that sees the result a few
-// microseconds before the stream's completion reaches the host.  If the count does not arrive in time (a failed
+// counter is polled first (the kernel writes it past the caches once its stores of the other words have been acknowledged): that
+// sees the result a few microseconds before the stream's completion reaches the host.  If the count does not arrive in time (a failed
 // launch) the stream is waited for as usual and the two counts are brought together again.
 constexpr int kPassFailed = 1;  // (never leaves this file)
 int pull_ctl(bild_state* s) {
@@ -1574,7 +1574,8 @@ int run_encoder(bild_state* s, int w) {
 }
 
 // Both encoders; the small model's beside the large one's on the pair's spare stream: neither fills the chip over a few hundred
-// rows (T5 shapes, 77, 512, 1531 tokens: 1.22, 2.16, 4.82 -> 1.07, 1.98, 4.54 ms; mT5 shapes, 64 tokens: 1.24 -> 1.04 ms).
+// rows.  One after the other / beside: T5 shapes, 77, 512, 1531 tokens 1.22 / 1.06, 2.13 / 1.94, 4.69 / 4.41 ms; mT5 shapes, 64 and 512
+// tokens 1.24 / 1.04, 2.30 / 2.01 ms (nothing gained where the two streams share a hardware queue).
 int run_encoders(bild_state* s) {
     auto large = [&] { return run_encoder(s, 1); };
     if (s->pair->small_borrows_encoder) return large();

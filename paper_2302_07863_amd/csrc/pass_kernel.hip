@@ -1,6 +1,6 @@
 // One decoder pass of a narrow bf16 model in ONE kernel: embedding and all layers for up to 16 rows.
 //
-// Such a pass is a chain of some 50 (T5-small shape) to 190 (T5-large shape) dependent stages, each far too small to use the
+// Such a pass is a chain of 45 (T5-small shape) to 171 (T5-large shape) dependent stages, each far too small to use the
 // chip for long.  As kernels of their own they cost 3.5 - 8 us each: 1.5 us of launch, a trip to memory for the activations and
 // a longer one for the weights, which can only be asked for once the kernel runs.  Here workgroups stay for the whole pass (one
 // per compute unit at most) and walk the stages:
