@@ -77,3 +77,26 @@ def replace_large_with_small(cfg):
     """A pair whose `large` is the small model's shape: weights of the small model alone, without drawing the large one."""
     from dataclasses import replace
     return replace(cfg, large=cfg.small)
+
+
+def test_merge_of_many_partials_is_exact_to_the_sums_rounding():
+    """One id at 0 and 250 111 ids at -x, x = 11.1 .. 12.2, where x log2(e) rounds by up to 9.5e-7: were the weight exp(-x) of each
+    partial taken from the rounded product, all would be off the same way, by up to 6.6e-7 of the sum's larger part (5e-7 in the
+    result, and the rest on top: 5.8e-7).  What 32 bits leave: about 20 additions on the way of a term, 3.4e-8 rms each, three
+    times their root sum times the larger part's 0.7, and the last addition: 3 sqrt(20) 3.4e-8 0.7 + 1.2e-7 = 4.4e-7 (3.3e-7 seen)."""
+    cfg = bi.toy_pair(vocab=250112, d=64)
+    _, wl = bi.make_pair_weights(cfg)
+    shape = cfg.large
+    emb, norm = bi.tensor_names(shape)[0], next(n for n in bi.tensor_names(shape) if wl[n].shape == (64,) and "dec" in n and "norm" in n)
+    wl = dict(wl)
+    wl[emb] = np.full((shape.vocab, 64), -12.2 / 64 / shape.logit_scale, dtype=np.float32)
+    wl[emb][0] = 0.0
+    wl[norm] = np.ones(64, dtype=np.float32)
+    model = parity.make_gpu_model(shape, wl)
+    bend = np.linspace(0.0, 0.45, 32)[:, None] * np.where(np.arange(64) % 2, 1.0, -1.0)
+    got = run_head_stats(model, 1.0 + bend, np.ones(32, dtype=np.int64))
+    z = got["z_target"].astype(np.float64)
+    assert np.all(got["zmax"] == 0) and np.all(got["argmax"] == 0) and z.max() < -11.0 and z.min() > -12.3
+    err = got["lse"] - np.log1p((shape.vocab - 1) * np.exp(z))
+    print("error of lse", np.abs(err).max(), np.sqrt(np.mean(err ** 2)))
+    assert np.abs(err).max() < 4.4e-7
