@@ -426,7 +426,8 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             if (M.pass_groups && s->one_die && s->cus == 256) M.pass_die_groups = pass_die_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated());
             if (M.pass_groups) {
                 want(M.pass_layers, sizeof(PassLayer) * L);
-                for (int T = 1; T <= kPassDieRows && M.pass_die_groups; ++T) want(M.pass_die_scratch[T], pass_die_bytes(M, T));
+                M.pass_die_rows = M.pass_die_groups == 0 ? 0 : w == 0 ? 1 : kPassDieRows;
+                for (int T = 1; T <= M.pass_die_rows; ++T) want(M.pass_die_scratch[T], pass_die_bytes(M, T));
                 want(M.pass_scratch, L * (size_t)pass_plan(kPassRows, (int)d, (int)I, (int)F).layer);
             }
         }
@@ -480,7 +481,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     for (int w = 0; w < 2 && e == hipSuccess; ++w) {
         ModelState& M = s->ms[w];
         if (!M.pass_groups) continue;
-        for (int T = 1; T <= kPassDieRows && M.pass_die_groups && e == hipSuccess; ++T)
+        for (int T = 1; T <= M.pass_die_rows && e == hipSuccess; ++T)
             e = hipMemsetAsync(M.pass_die_scratch[T], 0xFF, pass_die_bytes(M, T), s->stream);
         if (e != hipSuccess) break;
         const size_t kv = (size_t)s->cap_len * M.m->inner() * M.m->esz(), ckv = (size_t)s->cap_src * M.m->inner() * M.m->esz();
@@ -1199,7 +1200,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         p.x_out = M.x;
         p.x_keep = trunk > 0 && w == 0 ? s->trunk_x : nullptr;
         p.at = pass_plan(T, d, p.I, p.F);
-        const bool die = M.pass_die_groups > 0 && T <= kPassDieRows;
+        const bool die = T <= M.pass_die_rows;
         if (die) {
             p.scratch = M.pass_die_scratch[T];
             p.set_bytes = (size_t)p.n_layers * p.at.layer;
@@ -1232,7 +1233,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     f.host_mirror = s->hctl_dev;
     if (one) {
         f.sync = s->pass_sync;
-        if (M.pass_die_groups > 0 && T <= kPassDieRows) f.turn = s->pass_sync + kPassSyncWords + w * (kPassDieRows + 1) + T;
+        if (T <= M.pass_die_rows) f.turn = s->pass_sync + kPassSyncWords + w * (kPassDieRows + 1) + T;
     }
     if (lm_rows > 0) {
         GemmArgs g = gemm_base(m, m->head, xfin + (size_t)(T - lm_rows) * d, d, lm_rows, m->dec_final);
@@ -1306,7 +1307,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // Sequence.  Its keys are not asked for ahead; past 256 of them the waves have more than a block each, and no pass has been
 // tested there.  At 256, 512, 1024 positions: T5-large shape one row 672 / 652, 672 / 708, 705 / 823; two rows 789 / 664, 795 / 720,
 // 830 / 834; eight 988 / 682, 1018 / 739, 1054 / 850; T5-small shape on one die 144 / 104, 145 / 115, 153 / 134.
-static bool on_one_die(const bild_state* s, int w, int T) { return s->ms[w].pass_die_groups > 0 && T <= kPassDieRows; }
+static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
            s->n_src <= (on_one_die(s, w, T) ? 1000 : T == 1 ? 640 : 896 + 128 * T) && s->len[w] + T <= 256;

@@ -205,6 +205,7 @@ struct ModelState {
     int pass_die_groups = 0;  // the same of the form on one die
     bild::PassLayer* pass_layers = nullptr;  // device
     char* pass_scratch = nullptr;
+    int pass_die_rows = 0;    // most rows there (the small model's passes with an LM head have one)
     char* pass_die_scratch[bild::kPassDieRows + 1] = {};  // by rows: two sets each
 };
 
