@@ -48,9 +48,9 @@ bool config_ok(const bild_model_config& c) {
     return true;
 }
 
-// the two sets of what the workgroups of a pass on one die hand over
-size_t pass_die_bytes(const ModelState& M, int T) {
-    return 2 * M.m->dec.size() * (size_t)pass_plan(T, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff).layer;
+// what the workgroups of a pass in one kernel hand over: three layers' memory
+size_t pass_turns_bytes(const ModelState& M, int room) {
+    return 3 * (size_t)pass_plan(1 << room, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff).layer;
 }
 
 // captured passes carry some of the state's settings by value: where one changes they are captured anew
@@ -382,7 +382,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
     const int positions = std::max(s->cap_len, s->cap_src);
-    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + 2 * (kPassDieRows + 1)), true);
+    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + 2 * kPassRooms), true);
     for (int w = 0; w < 2; ++w) {
         ModelState& M = s->ms[w];
         const bild_model* m = p->m[w];
@@ -427,8 +427,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             if (M.pass_groups) {
                 want(M.pass_layers, sizeof(PassLayer) * L);
                 M.pass_die_rows = M.pass_die_groups == 0 ? 0 : w == 0 ? 1 : kPassDieRows;
-                for (int T = 1; T <= M.pass_die_rows; ++T) want(M.pass_die_scratch[T], pass_die_bytes(M, T));
-                want(M.pass_scratch, L * (size_t)pass_plan(kPassRows, (int)d, (int)I, (int)F).layer);
+                for (int r = 0; r < kPassRooms; ++r) want(M.pass_turns[r], pass_turns_bytes(M, r));
             }
         }
         M.nparts_cap = m->head.tn + 1;  // at most one partial per feature tile
@@ -481,8 +480,8 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     for (int w = 0; w < 2 && e == hipSuccess; ++w) {
         ModelState& M = s->ms[w];
         if (!M.pass_groups) continue;
-        for (int T = 1; T <= M.pass_die_rows && e == hipSuccess; ++T)
-            e = hipMemsetAsync(M.pass_die_scratch[T], 0xFF, pass_die_bytes(M, T), s->stream);
+        for (int r = 0; r < kPassRooms && e == hipSuccess; ++r)
+            e = hipMemsetAsync(M.pass_turns[r], 0xFF, pass_turns_bytes(M, r), s->stream);
         if (e != hipSuccess) break;
         const size_t kv = (size_t)s->cap_len * M.m->inner() * M.m->esz(), ckv = (size_t)s->cap_src * M.m->inner() * M.m->esz();
         for (size_t l = 0; l < M.m->dec.size(); ++l) {
@@ -1167,6 +1166,9 @@ int emit_layers(bild_state* s, int w, int T, int key_hint, bool reads_hidden, bo
 
 namespace bild {
 
+// Counts the passes of model w with room for T rows.
+static unsigned* pass_turn(const bild_state* s, int w, int T) { return s->pass_sync + kPassSyncWords + w * kPassRooms + pass_room_index(T); }
+
 // One decoder pass of model w over rows y[len .. len+T): embed, layers, and (lm_rows > 0)
 // the LM head over the last lm_rows rows followed by the policy `mode`; lm_rows == 0
 // only advances the cache (catch-up / prefill).
@@ -1199,15 +1201,12 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         p.att_scale = 1.f / std::sqrt((float)c.d_head); p.eps = c.norm_eps;
         p.x_out = M.x;
         p.x_keep = trunk > 0 && w == 0 ? s->trunk_x : nullptr;
-        p.at = pass_plan(T, d, p.I, p.F);
         const bool die = T <= M.pass_die_rows;
-        if (die) {
-            p.scratch = M.pass_die_scratch[T];
-            p.set_bytes = (size_t)p.n_layers * p.at.layer;
-            p.turn = s->pass_sync + kPassSyncWords + w * (kPassDieRows + 1) + T;
-        } else {
-            p.scratch = M.pass_scratch;
-        }
+        p.die = die;
+        p.room = 1 << pass_room_index(T);
+        p.at = pass_plan(p.room, d, p.I, p.F);
+        p.turn = pass_turn(s, w, T);
+        p.scratch = M.pass_turns[pass_room_index(T)];
         p.sync = s->pass_sync;
         p.spins = s->pass_spins;
         s->stage_count += 1;
@@ -1233,7 +1232,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     f.host_mirror = s->hctl_dev;
     if (one) {
         f.sync = s->pass_sync;
-        if (T <= M.pass_die_rows) f.turn = s->pass_sync + kPassSyncWords + w * (kPassDieRows + 1) + T;
+        f.turn = pass_turn(s, w, T);
     }
     if (lm_rows > 0) {
         GemmArgs g = gemm_base(m, m->head, xfin + (size_t)(T - lm_rows) * d, d, lm_rows, m->dec_final);
@@ -1296,21 +1295,21 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 //
 // Source.  One workgroup per head has all its keys to itself: up to 512 arrive ahead of their use, each further one costs a layer
 // 11 ns, where the separate kernels split them over more workgroups and stay as they are.  us per pass, separate kernels / one
-// kernel over the chip, at 512, 640, 1024, 1536 tokens: T5-large shape one row 675 / 617, 672 / 649, 675 / 749, 714 / 882; two rows
-// 784 / 625, 791 / 657, 795 / 756, 833 / 890; four 852 / 619, 854 / 651, 861 / 752, 900 / 886; eight 988 / 634, 1017 / 665, 1025 / 766,
-// 1066 / 899; mT5-large shape one row 722 / 641, 724 / 671, 726 / 772, 768 / 907; 768-wide, one row 348 / 280, 348 / 294, 350 / 341,
-// 373 / 408.  Break-even lies at 735 (T5-large, one row) to 1080 tokens (768-wide), and at 1150, 1580, above 2048 for two, four,
-// eight rows: the lines below are inside of it for every width, activation and row count measured (256 to 1024 wide).
-// On one die one row costs 146 / 97, 147 / 104, 147 / 126, 157 / 158 (T5-small shape; four rows 185 / 100, 189 / 105, 189 / 126,
-// 199 / 159; mT5-small one row 203 / 120, 204 / 129, 205 / 159, 217 / 202; 256-wide 95 / 68, 96 / 72, 96 / 87, 102 / 109).
+// kernel over the chip, at 512, 1024, 1536, 2048 tokens: T5-large shape one row 676 / 447, 675 / 575, 714 / 704, 713 / 834; two rows
+// 785 / 448, 796 / 578, 836 / 705, 836 / 835; eight 986 / 475, 1020 / 597, 1062 / 729, 1066 / 859; mT5-large shape one row 726 / 456,
+// 731 / 586, 772 / 715, 773 / 846; 768-wide, one row 348 / 212, 349 / 275, 369 / 339, 373 / 401; 256-wide, two rows 112 / 73, 114 / 93,
+// 121 / 114, 124 / 135.  Break-even lies at 1580 (T5-large, one row) to 1720 tokens (768-wide) and above 1700 for more rows: the lines
+// below are inside of it for every width, activation and row count measured (256 to 1024 wide).
+// On one die one row costs 148 / 96, 149 / 125, 159 / 156, 159 / 187 (T5-small shape; mT5-small 206 / 117, 206 / 159, 220 / 199,
+// 219 / 241; 256-wide 95 / 67, 96 / 87, 102 / 108, 104 / 128).
 //
-// Sequence.  Its keys are not asked for ahead; past 256 of them the waves have more than a block each, and no pass has been
-// tested there.  At 256, 512, 1024 positions: T5-large shape one row 672 / 652, 672 / 708, 705 / 823; two rows 789 / 664, 795 / 720,
-// 830 / 834; eight 988 / 682, 1018 / 739, 1054 / 850; T5-small shape on one die 144 / 104, 145 / 115, 153 / 134.
+// Sequence.  Its keys past the first 256 are not asked for ahead.  At 256, 512, 1024 positions: T5-large shape one row 708 / 478,
+// 713 / 522, 746 / 639; eight 1053 / 526, 1091 / 575, 1125 / 688; T5-small shape on one die 158 / 105, 160 / 113, 167 / 134; no shape and
+// row count loses before the 1024 that were measured.
 static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
-           s->n_src <= (on_one_die(s, w, T) ? 1000 : T == 1 ? 640 : 896 + 128 * T) && s->len[w] + T <= 256;
+           s->n_src <= (on_one_die(s, w, T) ? 1280 : T == 1 ? 1408 : 1536) && s->len[w] + T <= 1024;
 }
 
 int key_bucket(int nkeys) {
@@ -1374,10 +1373,9 @@ int pass_gave_up(bild_state* s, int w, int T) {
     s->routes[ROUTE_GAVE_UP] += 1;
     s->pass_pause = 16 << s->pass_fails;
     s->pass_fails = std::min(s->pass_fails + 1, 12);
-    // the form on one die leaves its two sets in no known state: nothing is there yet in either
+    // what it handed over is in no known state: nothing is there yet
     const ModelState& M = s->ms[w];
-    if (on_one_die(s, w, T))
-        HIPC(hipMemsetAsync(M.pass_die_scratch[T], 0xFF, pass_die_bytes(M, T), s->stream));
+    HIPC(hipMemsetAsync(M.pass_turns[pass_room_index(T)], 0xFF, pass_turns_bytes(M, pass_room_index(T)), s->stream));
     return BILD_OK;
 }
 

@@ -199,21 +199,24 @@ struct AttnArgs {
 // Most rows; on one die.  (One die, the whole chip, us, T5-small shape, 512 tokens: one row 97, 137, two 99, 138, four 100, 140;
 // mT5-small shape 120, 178; 121, 180; 122, 181.  The small model of a pair has one row; a narrow large one reviews.)
 constexpr int kPassRows = 16, kPassDieRows = 4;
-constexpr int kPassCounters = 64;  // one per lane of the polling wave
-constexpr int kPassStride = 64;  // words
-constexpr int kPassSyncWords = (kPassCounters + 1) * kPassStride;  // counters on lines of their own, then the ranks given out on a die; the last word: a workgroup gave up
+// The hand-over memory is laid out for 1, 2, 4, 8 or 16 rows.
+constexpr int kPassRooms = 5;
+constexpr int pass_room_index(int rows) { return rows <= 1 ? 0 : rows <= 2 ? 1 : rows <= 4 ? 2 : rows <= 8 ? 3 : 4; }
+constexpr int kPassSyncWords = 128;  // the ranks given out on a die; on another line, the last word: a workgroup gave up
 struct PassLayer {
     const void *wqkv, *wo, *cwq, *cwo, *win, *wout;
     const float *ln1, *lnc, *ln2;
     char *kc, *vc, *ck, *cv;
 };
 struct PassPlan {  // where a layer's hand-over buffers lie in its piece of the scratch memory
-    int x1, s1, q, a1, x2, s2, a2, x3, s3, h, layer;
+    int x1, q, k, v, a1, x2, a2, x3, h, layer;
 };
 struct PassArgs {
     const PassLayer* layers;  // device array, from the pass' first layer on
     int n_layers;
-    int T, d, heads, I, F, act, cross;
+    int T, room;              // rows; rows there is room for in the hand-over memory
+    int die;                  // 1: on one die
+    int d, heads, I, F, act, cross;
     // embedding of y[len ..]; emb null: the rows are x_in[len ..]
     const void* emb;
     const int* tokens;
@@ -226,9 +229,8 @@ struct PassArgs {
     int rel_d;
     float att_scale, eps;
     float *x_out, *x_keep;    // the residual stream after the last layer: [T][d]; at [len ..] too (null: not kept)
-    char* scratch;            // [n_layers][at.layer]; on one die: two sets of that, everything "not there" in the one this pass uses
-    size_t set_bytes;
-    const unsigned* turn;     // on one die: which set (passes so far); null: on the whole chip
+    char* scratch;            // [3][at.layer]: layer l of the pass uses the place (turn * n_layers + l) mod 3
+    const unsigned* turn;     // passes so far, mod 3
     PassPlan at;
     int groups;               // workgroups that take part
     int spins;                // polls (of about 0.7 us) after which a workgroup gives up
@@ -236,7 +238,7 @@ struct PassArgs {
 };
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // workgroups, 0: not a shape it is made for
 int pass_die_groups(int d, int heads, int d_head, int F, bool gated);
-PassPlan pass_plan(int T, int d, int I, int F);
+PassPlan pass_plan(int room, int d, int I, int F);
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st);
 
 struct EmbedArgs {
@@ -294,8 +296,8 @@ struct FinishArgs {
     const float* u_acc;   // uniform number per sequence position for the acceptance test
     float* s_ring;        // [kMaxRows][vocab] the small model's logits of each pending draft, by draft index
     float4* s_draw;       // [sequence capacity] (max logit, nucleus threshold key, nucleus mass, -) of the small model's row
-    unsigned* turn;       // counts the passes of a number of rows on one die
-    unsigned* sync;       // counters of the pass kernel, cleared here for its next pass; a flagged pass is not committed
+    unsigned* turn;       // counts the passes with room for a number of rows, mod 3
+    unsigned* sync;       // of the pass kernel, cleared here for its next pass; a flagged pass is not committed
     // nucleus draw spread over the chip (launch_finish_draw): its workspace
     struct DrawWs* dws;
 };

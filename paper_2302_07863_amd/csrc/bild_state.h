@@ -204,9 +204,8 @@ struct ModelState {
     int pass_groups = 0;      // workgroups; 0: the shape is not made for it
     int pass_die_groups = 0;  // the same of the form on one die
     bild::PassLayer* pass_layers = nullptr;  // device
-    char* pass_scratch = nullptr;
     int pass_die_rows = 0;    // most rows there (the small model's passes with an LM head have one)
-    char* pass_die_scratch[bild::kPassDieRows + 1] = {};  // by rows: two sets each
+    char* pass_turns[bild::kPassRooms] = {};  // what its workgroups hand over, by the rows there is room for
 };
 
 // How a pass ran (ROUTE_GAVE_UP: those of the first two that were run again as kernels).

@@ -5,13 +5,20 @@
 // a longer one for the weights, which can only be asked for once the kernel runs.  Here workgroups stay for the whole pass (one
 // per compute unit at most) and walk the stages:
 //
-//   - hand-over.  A stage's results are written through the caches; the wave that wrote them waits until they are in memory and
-//     counts its workgroup in on one of 64 counters, each on lines of its own; a workgroup that needs them polls all of them
-//     with one load.  Publish, count, poll and read back take about 2 us over 200 workgroups, most of it trips to memory (one
-//     row of the T5-large shape: 739 us with 8 counters, 645 with 32, 635 with 64, 890 with a flag word per workgroup on shared
-//     lines; the fences of a barrier at agent scope, which write back and drop whole L2s, cost above 10 us each).  What is
-//     handed over lies at an address of its own for every layer and stage, which no die has read before in this kernel: plain
-//     loads cannot find an older copy of it in a cache, and a die's workgroups share one fetch through their L2;
+//   - hand-over.  Results are their own flags: the memory they are handed over in is filled with words that no result has, and who
+//     needs a piece reads it until none of them is left.  Three layers' memory takes turns: who produces a piece for layer l fills its
+//     place for layer l + 2.  What was there, of layer l - 1, has been read by then, because layer l's results come from it; and the
+//     filling has been seen before somebody looks there, because its producer has waited for a later read since and what it
+//     produced then for layer l + 1 is what the reader has seen before.  Nothing is counted, nothing waits for a store to be acknowledged, and the read that finds the flag
+//     has brought the data: between two dies 0.65 - 0.8 us from a store to its reader, 0.3 us on one die, where publish, count, poll
+//     and read back took 1.8 us over the chip.  A read misses its die's L2 only after somebody has written the line, so waiting
+//     workgroups stay off the fabric.  A line that is polled before it is written has to be taken away from eight L2s and
+//     fetched again, 0.3 us: where a stage's results cannot be there yet its readers sleep first (nap: q, k, v and the FFN's
+//     input projection 0.35 us, its output projection 0.65; together 474 -> 447 us a pass of the T5-large shape; half as much
+//     again, or naps in front of the other stages, gain nothing);
+//   - what belongs together lies together: a row's sums of squares beside its planes (a line that all producers write is taken
+//     away from its readers by each of them: 623 -> 714 us when the sums had two lines of their own), a head's query, keys
+//     and values of the new rows, which it needs before they can be read from the caches;
 //   - weights depend on nothing: they are requested while a workgroup has nothing else to do, those of the FFN and of the next
 //     layer during the cross-attention (a wave's loads come back in order, so a request just before a wait delays what follows);
 //   - eight waves share a feature tile's inputs; activations arrive as high and low bf16 parts in the order of the matrix core's
@@ -21,15 +28,11 @@
 //
 // A model small enough for the 32 compute units of one die (pass_die_groups: T5-small, mT5-small) walks there: what is handed over
 // then only goes to that die's L2 and back, at 1.25 TB/s for the weights instead of the chip's 4.8, which a layer of 7 MB in 13 us
-// does not notice.  Workgroups of the other dies end at once.  There everything but q, k and v is also its own flag: the memory
-// is filled with words that no result has, and who needs a piece reads it until none of them is left (two sets take turns: a
-// producer writes its part of one and fills its part of the other), which saves the counting and the wait before it (T5-small
-// shape, one row: 112 -> 98 us).  Over the whole chip this loses (623 -> 714 us, T5-large shape): reads past the L2s are not
-// shared by a die's workgroups.
+// does not notice.  Workgroups of the other dies end at once.
 //
-// Per pass, us, before (a kernel per stage) and now, 512 source tokens: T5-small shape one row 149 -> 99 (on the whole chip 139),
-// mT5-small shape, 64 tokens, 239 -> 169 (217); T5-large shape 1, 2, 5, 8, 16 rows 683, 799, 977, 998, 1223 -> 623, 630, 643,
-// 636, 715; mT5-large shape, 64 tokens, 1 and 8 rows 809, 1063 -> 703, 720.
+// Per pass, us, as separate kernels, with counters (and flags on one die) and now, 512 source tokens: T5-small shape one row 147, 97, 96;
+// mT5-small shape 206, 121, 117; T5-large shape 1, 2, 4, 8, 11, 16 rows 676, 785, 853, 986, -, 1211 / 623, 631, 624, 638, 702, 713 / 447,
+// 448, 456, 475, 570, 552; mT5-large shape 1 and 8 rows 726, 1045 / 644, 666 / 456, 477.
 //
 // A workgroup that has polled `spins` times in vain flags the pass as failed and walks on without waiting again (nothing
 // handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
@@ -64,70 +67,52 @@ __device__ __forceinline__ void st8(Rsrc r, int off, unsigned a, unsigned b) {
 constexpr unsigned kNotThere = 0xFFFFFFFFu;  // (two NaNs of a kind no conversion gives, as bf16 parts; one as a sum)
 
 // LDS: sums of the waves (up to six tiles each; attention joins its waves there too), their (max, sum), the head's query, the
-// head's relative-position biases
+// waves' sums of squares (twice, like the sums), the head's relative-position biases
 constexpr int kRedBytes = kPassWaves * 6 * 1024;  // twice: a stage's sums are read while the next one's are written
-constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kRel = kQ + 16 * kQLd * 4;
+constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kSq = kQ + 16 * kQLd * 4, kSqBytes = kPassWaves * 16 * 4, kRel = kSq + 2 * kSqBytes;
 
 template <bool DIE>
 struct Walk {
-    // on one die all but q, k and v are handed over without counters (see the head of this file)
-    static constexpr bool TAG = DIE;
     static constexpr int kIn = 16;  // reads of what may not be there yet: past the L1 (sc1)
     // what is handed over goes as far as all readers see it: to the die's L2 (the L1s write through), or past the L2s (sc0 sc1)
     static constexpr int kOut = DIE ? 0 : 17;
     char* lds;
-    unsigned* counters;
     unsigned* failed;
     int spins;
     int wg, wave, lane, tok, g, t, t8;  // t: this lane's row, clamped to the last one; t8: of the packed order
-    unsigned target;                // wave 0: arrivals this lane's counter has to show
     bool dead;
-    int red = 0;                    // half of the sums' memory in use
-    long clear = 0;                 // from what this pass hands over to where the next one will: filled with "not there yet"
+    int red = 0, sq = 0;            // halves of the sums' memory in use
+    float ss;                       // this wave's part of its lane's row's sum of squares
+    int slot, clear;                // clear: from what this layer hands over to where the layer after the next will: filled with "not there yet"
 
-    int T;
-    __device__ __forceinline__ void place(int rows) {
+    int T, R;                       // rows; rows there is room for (the layout's)
+    __device__ __forceinline__ void place(int rows, int room) {
         T = rows;
+        R = room;
         tok = lane & 15;
         g = lane >> 4;
         t = min(tok, T - 1);
         t8 = min(tok & 7, T - 1);
     }
-    // the stage just described has `n` active workgroups from `base` on
+    // This layer's hand-over memory, of three that take turns (see the head of this file); next(): of the layer after it.
     __device__ __forceinline__ char* scratch(const PassArgs& a) {
-        if constexpr (!TAG) return a.scratch;
-        const bool second = (*a.turn & 1u) != 0u;
-        clear = second ? -(long)a.set_bytes : (long)a.set_bytes;
-        return a.scratch + (second ? a.set_bytes : 0);
+        slot = (int)(*a.turn * (unsigned)a.n_layers % 3u);
+        clear = slot == 0 ? 2 * a.at.layer : -a.at.layer;
+        return a.scratch + slot * a.at.layer;
+    }
+    __device__ __forceinline__ char* next(char* z, int layer) const { return z + (slot == 2 ? -2 * layer : layer); }
+    __device__ __forceinline__ void walk_on(int layer) {
+        slot = slot == 2 ? 0 : slot + 1;
+        clear = slot == 0 ? 2 * layer : -layer;
     }
     __device__ __forceinline__ void give_up() {
         dead = true;
         if (lane == 0) asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(failed), "v"(1u) : "memory");
     }
-    __device__ __forceinline__ void expect(int base, int n) { target += (unsigned)(n + kPassCounters - 1 - ((lane - base) & (kPassCounters - 1))) / kPassCounters; }
-    __device__ __forceinline__ void arrive() const {  // one wave, after its stores
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == 0) {
-            unsigned* p = counters + (wg & (kPassCounters - 1)) * kPassStride;
-            if constexpr (DIE) asm volatile("global_atomic_add %0, %1, off" ::"v"(p), "v"(1u) : "memory");
-            else asm volatile("global_atomic_add %0, %1, off sc1" ::"v"(p), "v"(1u) : "memory");
-        }
-    }
-    __device__ __forceinline__ void wait() {
-        if (wave == 0 && !dead) {
-            const unsigned* p = counters + lane * kPassStride;
-            int n = 0;
-            unsigned v;
-            unsigned long long missing;
-#pragma unroll 1
-            do {
-                if constexpr (DIE) asm volatile("global_load_dword %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
-                else asm volatile("global_load_dword %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
-                missing = __builtin_amdgcn_ballot_w64((int)(v - target) < 0);
-            } while (missing && ++n < spins);
-            if (n >= spins) give_up();
-        }
-        lds_barrier();
+    // (about NS nanoseconds; see the head of this file)
+    template <int NS>
+    __device__ __forceinline__ void nap() const {
+        if constexpr (!DIE) __builtin_amdgcn_s_sleep(NS / 27);
     }
 };
 
@@ -154,29 +139,19 @@ __device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const
         }
 }
 
-// RMSNorm's factor of this lane's row from the owners' partial sums of squares, [t][d / 16]: requested and, later, added up.
-struct Norm {
-    float4 v[4] = {};
-    template <class Walk>
-    __device__ __forceinline__ void get(const Walk& c, const float* ssq, int nd) {
-        const Rsrc r = whole(ssq);
-        const int per = nd >> 2;
+// A tile of planes that a norm's projection reads has its producers' sums of squares behind it, [row][first, second sixteen
+// inputs] (an own line: a producer's part of a row lies where its planes' readers look anyway).
+__host__ __device__ __forceinline__ int tile_bytes(bool normed, int room) { return room * 128 + (normed ? 128 : 0); }
+// 1/rms of this lane's row, behind leave()
+template <class Walk>
+__device__ __forceinline__ float norm_factor(const Walk& c, int d, float eps) {
+    float p[kPassWaves], s = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = i * 4 < per ? ldf4<Walk::TAG ? Walk::kIn : 0>(r, (c.t * nd + c.g * per + i * 4) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    __device__ __forceinline__ unsigned largest() const {
-        unsigned m = 0u;
+    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const float*)(c.lds + kSq + c.sq + (v * 16 + c.tok) * 4);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) m = max(max(m, max(__float_as_uint(v[i].x), __float_as_uint(v[i].y))), max(__float_as_uint(v[i].z), __float_as_uint(v[i].w)));
-        return m;
-    }
-    __device__ __forceinline__ float factor(int d, float eps) const {
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-        return __builtin_amdgcn_rsqf(quad_rows_sum(s) * __builtin_amdgcn_rcpf((float)d) + eps);
-    }
-};
+    for (int v = 0; v < kPassWaves; ++v) s += p[v];
+    return __builtin_amdgcn_rsqf(s * __builtin_amdgcn_rcpf((float)d) + eps);
+}
 
 // acc = W x over this wave's inputs.  x lies in tiles of 32 inputs in the order in which the operand's lanes want it: quarters of
 // eight inputs, in each the rows one after the other, 16 bytes per row; the high parts of a tile and then its low parts.  (A load
@@ -184,15 +159,18 @@ struct Norm {
 // Up to eight rows (PACK) one operand holds the high parts of the rows in its columns 0 .. 7 and the low parts in 8 .. 15: half
 // the loads and products (a compute unit's 64 bytes a cycle are what the FFN output's 256 loads of 1 KiB wait for); the halves
 // are added in total().  A quarter then has the rows' high parts and their low parts.
-template <int N, int RW, bool PACK, class Walk>
-__device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 (&W)[N * RW], const void* planes, int tk, Norm& nm, bool normed = false,
-                                         const void* ssq = nullptr, int nd = 0) {
+// NORM: the rows' sums of squares as well, to c.ss.
+template <int N, int RW, bool PACK, bool NORM, class Walk>
+__device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 (&W)[N * RW], const void* planes, int tk) {
     const Run r = run_of(c.wave, tk);
     const Rsrc xs = whole(planes);
-    const int S = c.T * 128;
-    const int at = (PACK ? (c.g * 2 + (c.tok >> 3)) * c.T + c.t8 : c.g * c.T + c.t) * 16, k0 = r.k0 * S;
-    constexpr int P = PACK ? 1 : 2, B = N < 8 / P ? N : 8 / P;  // tiles requested at once
-    uint4 X[2][P * B];
+    const int S = tile_bytes(NORM, c.R);
+    const int at = (PACK ? (c.g * 2 + (c.tok >> 3)) * c.R + c.t8 : c.g * c.R + c.t) * 16, k0 = r.k0 * S;
+    constexpr int P = PACK ? 1 : 2, B = N * P <= 16 ? N : 4;  // tiles requested at once
+    constexpr int IN = Walk::kIn;
+    static_assert(N % B == 0 && (!NORM || N <= 4), "whole pieces; a lane group per tile");
+    uint4 X[N > B ? 2 : 1][P * B];
+    v2u sq = {0u, 0u};
     f32x4 low[RW];
 #pragma unroll
     for (int q = 0; q < RW; ++q) acc[q] = low[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -200,9 +178,32 @@ __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 
 #pragma unroll
         for (int j = 0; j < B; ++j)
             if (j0 + j < r.n) {
-                x[P * j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at, k0 + (j0 + j) * S, Walk::TAG ? Walk::kIn : 0));
-                if (!PACK) x[P * j + 1] = buf_load(xs, (unsigned)at, k0 + (j0 + j) * S + S / 2);
+#pragma unroll
+                for (int p = 0; p < P; ++p) x[P * j + p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at + p * c.R * 64, k0 + (j0 + j) * S, IN));
             }
+        if constexpr (NORM) {  // (lane group g: tile g)
+            const v2u v = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, min(c.g, max(r.n - 1, 0)) * S + c.R * 128 + c.t * 8, r.n > 0 ? k0 : 0, IN));
+            sq = c.g < r.n ? v : v2u{0u, 0u};
+        }
+    };
+    // all of it again and again until every word is there
+    auto wait = [&](uint4 (&x)[P * B], int j0) {
+        int n = 0;
+        bool missing;
+#pragma unroll 1
+        do {
+            asm volatile("" ::: "memory");
+            if (N == B || n > 0) get(x, j0);
+            unsigned m = max(sq.x, sq.y);
+#pragma unroll
+            for (int j = 0; j < B; ++j)
+                if (j0 + j < r.n) {
+#pragma unroll
+                    for (int p = 0; p < P; ++p) m = max(max(m, max(x[P * j + p].x, x[P * j + p].y)), max(x[P * j + p].z, x[P * j + p].w));
+                }
+            missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+        } while (missing && ++n < c.spins);
+        if (missing) c.give_up();
     };
     auto mul = [&](const uint4 (&x)[P * B], int j0) {
 #pragma unroll
@@ -216,47 +217,32 @@ __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 
                 }
             }
     };
-    if constexpr (Walk::TAG) {  // all of it at once, again and again until every word is there
-        static_assert(P == 1 && N <= 2 * B, "two pieces at most");
-        int n = 0;
-        bool missing;
-#pragma unroll 1
-        do {
-            asm volatile("" ::: "memory");
-            get(X[0], 0);
-            if constexpr (N > B) get(X[1], B);
-            unsigned m = 0u;
-            if (normed) {
-                nm.get(c, (const float*)ssq, nd);
-                m = nm.largest();
-            }
-#pragma unroll
-            for (int j = 0; j < N; ++j)
-                if (j < r.n) {
-                    const uint4 v = X[j / B][j % B];
-                    m = max(max(m, max(v.x, v.y)), max(v.z, v.w));
-                }
-            missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
-        } while (missing && ++n < c.spins);
-        if (missing) c.give_up();
-#pragma unroll
-        for (int j0 = 0; j0 < N; j0 += B) mul(X[j0 / B], j0);
-    } else {
-        if (normed) nm.get(c, (const float*)ssq, nd);
+    if constexpr (N == B) {
+        wait(X[0], 0);
+        mul(X[0], 0);
+    } else {  // two pieces on their way
         get(X[0], 0);
+        get(X[1], B);
 #pragma unroll
         for (int j0 = 0; j0 < N; j0 += B) {
-            if (j0 + B < N && j0 + B < r.n) get(X[(j0 / B + 1) & 1], j0 + B);
+            if (j0 >= r.n) break;
+            wait(X[(j0 / B) & 1], j0);
             mul(X[(j0 / B) & 1], j0);
+            if (j0 + 2 * B < N) get(X[(j0 / B) & 1], j0 + 2 * B);
         }
     }
     if constexpr (RW == 1 && !PACK) acc[0] += low[0];
+    if constexpr (NORM) c.ss = quad_rows_sum(__uint_as_float(sq.x) + __uint_as_float(sq.y));
 }
 
 // The waves' results side by side in LDS; `tile`'s total over the waves, in wave order.
-template <int RW, class Walk>
+template <int RW, bool NORM, class Walk>
 __device__ __forceinline__ void leave(Walk& c, const f32x4 (&acc)[RW]) {
     c.red = kRedBytes - c.red;
+    if constexpr (NORM) {
+        c.sq = kSqBytes - c.sq;
+        if (c.g == 0) *(float*)(c.lds + kSq + c.sq + (c.wave * 16 + c.tok) * 4) = c.ss;
+    }
 #pragma unroll
     for (int q = 0; q < RW; ++q) *(f32x4*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
     lds_barrier();
@@ -277,27 +263,38 @@ __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
 }
 
 // Sixteen features of a row's activations in that order: this lane's four.
-template <bool PACK, class Walk>
+template <bool PACK, bool NORM, class Walk>
 __device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, const float (&w)[4]) {
     uint32_t h01, l01, h23, l23;
     split_bf16x2(w[0], w[1], h01, l01);
     split_bf16x2(w[2], w[3], h23, l23);
     const Rsrc r = whole(planes);
-    const int off = (n0 >> 5) * c.T * 128 + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.T + c.tok) * 16 + (n0 & 7) * 2;
-    st8<Walk::kOut>(r, off, h01, h23);
-    st8<Walk::kOut>(r, off + (PACK ? 16 : 64) * c.T, l01, l23);
-    if constexpr (Walk::TAG) {
+    const int off = (n0 >> 5) * tile_bytes(NORM, c.R) + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.R + c.tok) * 16 + (n0 & 7) * 2;
+    const int lo = (PACK ? 16 : 64) * c.R;
+    if (c.tok < c.T) {
+        st8<Walk::kOut>(r, off, h01, h23);
+        st8<Walk::kOut>(r, off + lo, l01, l23);
+    }
+    if (c.tok < c.R) {
         const Rsrc n = whole((const char*)planes + c.clear);
         st8<Walk::kOut>(n, off, kNotThere, kNotThere);
-        st8<Walk::kOut>(n, off + 16 * c.T, kNotThere, kNotThere);
+        st8<Walk::kOut>(n, off + lo, kNotThere, kNotThere);
     }
 }
+
+// What the projections hand over to a head: [row][64] queries (fp32) and keys (bf16), [64][row] values (bf16 in the upper half of a
+// word, so that four rows' values are one load; `room` rows, a multiple of four).
+struct Fresh {
+    Rsrc q, k, v;
+    int room;
+};
+__host__ __device__ inline int fresh_room(int rows) { return (rows + 3) & ~3; }
 
 // Attention of one head over its keys for all rows: the waves take blocks of 32 keys in turn; (max, sum, O) joined through LDS.
 template <bool CAUSAL, bool PACK, class Walk>
 struct Attend {
     const Rsrc kr, vr;
-    const int I, cap, nkeys, nblk;
+    const int I, cap, nkeys, nblk;  // (causal: the keys of earlier passes)
     uint4 K0[2][2], K1[2][2], V0[4], V1[4];
 
     __device__ __forceinline__ void load(const Walk& c, uint4 (&Kr)[2][2], uint4 (&Vr)[4], int blk) const {
@@ -314,10 +311,10 @@ struct Attend {
             Vr[dt] = make_uint4(va.x, va.y, vb.x, vb.y);
         }
     }
-    // `query`: this lane's row and inputs g * 8 .. of both halves of the head.  Up to eight rows are packed as in multiply().
-    template <class Query>
-    __device__ __forceinline__ void run(Walk& c, Query&& query, float scale, int len, const float* relb, int rel_d, void* out, int T, int h) {
-        constexpr int P = PACK ? 1 : 2;
+    // Up to eight rows are packed as in multiply().  Causal: query, keys and values of this pass' rows are handed over in `fresh`,
+    // a block of keys of its own that one wave takes; else the query lies in LDS.
+    __device__ __forceinline__ void run(Walk& c, const Fresh& fresh, float scale, int len, const float* relb, int rel_d, void* out, int h) {
+        constexpr int P = PACK ? 1 : 2, IN = Walk::kIn;
         bf16x8 Q[2][P];  // scaled, high parts (columns 0 .. 7 if packed) and low parts
         const bool low = c.tok >= 8;
         const int row = PACK ? c.t8 : c.t;
@@ -345,10 +342,8 @@ struct Attend {
         f32x4 O[4];
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const int lim = CAUSAL ? len + row : nkeys - 1;  // the last key this row sees
-        const int safe = CAUSAL ? len : nkeys - 1;       // ... and every row
-        // NB blocks at once: one maximum, one rescaling
-        auto process = [&](auto nb, const uint4 (*const (&Kr)[decltype(nb)::value])[2], const uint4* const (&Vr)[decltype(nb)::value], const int (&blk)[decltype(nb)::value], bool first) {
+        // NB blocks at once, whose keys begin at `key`: one maximum, one rescaling; keys behind `lim` (of this lane's row) are not seen
+        auto process = [&](auto nb, const uint4 (*const (&Kr)[decltype(nb)::value])[2], const uint4* const (&Vr)[decltype(nb)::value], const int (&key)[decltype(nb)::value], bool edge, int lim, bool first) {
             constexpr int NB = decltype(nb)::value;
             f32x4 s[NB][2];
 #pragma unroll
@@ -374,14 +369,14 @@ struct Attend {
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
                     for (int v = 0; v < 8; ++v)
-                        s[b][v >> 2][v & 3] += relb[rel_d + max(-rel_d, min(rel_d, blk[b] * 32 + (v >> 2) * 16 + c.g * 4 + (v & 3) - (len + row)))];
+                        s[b][v >> 2][v & 3] += relb[rel_d + max(-rel_d, min(rel_d, key[b] + (v >> 2) * 16 + c.g * 4 + (v & 3) - (len + row)))];
             }
-            if (blk[NB - 1] * 32 + 31 > safe) {
+            if (edge) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
                     for (int v = 0; v < 8; ++v)
-                        if (blk[b] * 32 + (v >> 2) * 16 + c.g * 4 + (v & 3) > lim) s[b][v >> 2][v & 3] = -INFINITY;
+                        if (key[b] + (v >> 2) * 16 + c.g * 4 + (v & 3) > lim) s[b][v >> 2][v & 3] = -INFINITY;
             }
             float tmax = m_run;
 #pragma unroll
@@ -420,33 +415,67 @@ struct Attend {
         };
         using One = std::integral_constant<int, 1>;
         using Two = std::integral_constant<int, 2>;
-        if constexpr (CAUSAL) {  // (few blocks: a wave without one requests nothing)
-            if (c.wave < nblk) {
-                float4 qv[2][2];
-                query(qv);
-                load(c, K0, V0, c.wave);
-                __builtin_amdgcn_sched_barrier(0);
-                // (all of it is here: the compiler would move requests to their uses, one trip to memory after the other)
+        if constexpr (CAUSAL) {
+            const bool newest = c.wave == (nblk & (kPassWaves - 1));
+            if (c.wave < nblk || newest) {
+                float4 qv[2][2], vn[4];
+                uint4 kn[2];
+                int n = 0;
+                bool missing;
+#pragma unroll 1
+                do {
+                    asm volatile("" ::: "memory");
+                    unsigned m = 0u;
+                    auto see = [&](unsigned a, unsigned b, unsigned d, unsigned e) { m = max(max(m, max(a, b)), max(d, e)); };
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    asm volatile("" : "+v"(qv[i >> 1][i & 1].x), "+v"(qv[i >> 1][i & 1].y), "+v"(qv[i >> 1][i & 1].z), "+v"(qv[i >> 1][i & 1].w));
-                    asm volatile("" : "+v"(K0[i >> 1][i & 1].x), "+v"(K0[i >> 1][i & 1].y), "+v"(K0[i >> 1][i & 1].z), "+v"(K0[i >> 1][i & 1].w));
-                    asm volatile("" : "+v"(V0[i].x), "+v"(V0[i].y), "+v"(V0[i].z), "+v"(V0[i].w));
-                }
+                    for (int i = 0; i < 4; ++i) qv[i >> 1][i & 1] = ldf4<IN>(fresh.q, row * 256 + (i >> 1) * 128 + c.g * 32 + (i & 1) * 16);
+                    if (newest) {
+#pragma unroll
+                        for (int ks = 0; ks < 2; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fresh.k, c.t * 128 + ks * 64 + c.g * 16, 0, IN));
+#pragma unroll
+                        for (int dt = 0; dt < 4; ++dt) vn[dt] = ldf4<IN>(fresh.v, ((dt * 16 + c.tok) * fresh.room + min(c.g * 4, fresh.room - 4)) * 4);
+#pragma unroll
+                        for (int ks = 0; ks < 2; ++ks) see(kn[ks].x, kn[ks].y, kn[ks].z, kn[ks].w);
+#pragma unroll
+                        for (int dt = 0; dt < 4; ++dt) see(__float_as_uint(vn[dt].x), __float_as_uint(vn[dt].y), __float_as_uint(vn[dt].z), __float_as_uint(vn[dt].w));
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float4 v = qv[i >> 1][i & 1];
+                        see(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w));
+                    }
+                    missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+                } while (missing && ++n < c.spins);
+                if (missing) c.give_up();
                 split_query(qv);
-                process(One{}, {K0}, {V0}, {c.wave}, true);
-            }
-            for (int blk = c.wave + kPassWaves; blk < nblk; blk += kPassWaves) {
-                load(c, K0, V0, blk);
-                process(One{}, {K0}, {V0}, {blk}, false);
+                if (c.wave < nblk) process(One{}, {K0}, {V0}, {c.wave * 32}, c.wave * 32 + 31 >= nkeys, nkeys - 1, true);
+                for (int blk = c.wave + kPassWaves; blk < nblk; blk += kPassWaves) {
+                    load(c, K0, V0, blk);
+                    process(One{}, {K0}, {V0}, {blk * 32}, blk * 32 + 31 >= nkeys, nkeys - 1, false);
+                }
+                if (newest) {
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) {
+                        K0[0][ks] = kn[ks];
+                        K0[1][ks] = make_uint4(0u, 0u, 0u, 0u);
+                    }
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt)  // (bf16 values in the upper halves)
+                        V0[dt] = make_uint4(__builtin_amdgcn_perm(__float_as_uint(vn[dt].y), __float_as_uint(vn[dt].x), 0x07060302u),
+                                            __builtin_amdgcn_perm(__float_as_uint(vn[dt].w), __float_as_uint(vn[dt].z), 0x07060302u), 0u, 0u);
+                    process(One{}, {K0}, {V0}, {len}, true, len + row, c.wave >= nblk);
+                }
             }
         } else {
+            const float* q = (const float*)(c.lds + kQ);
             float4 qv[2][2];
-            query(qv);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) qv[i >> 1][i & 1] = *(const float4*)(q + row * kQLd + (i >> 1) * 32 + c.g * 8 + (i & 1) * 4);
             split_query(qv);
             for (int blk = c.wave; blk < nblk; blk += 2 * kPassWaves) {
-                if (blk + kPassWaves < nblk) process(Two{}, {K0, K1}, {V0, V1}, {blk, blk + kPassWaves}, blk == c.wave);
-                else process(One{}, {K0}, {V0}, {blk}, blk == c.wave);
+                const bool first = blk == c.wave;
+                if (blk + kPassWaves < nblk) process(Two{}, {K0, K1}, {V0, V1}, {blk * 32, (blk + kPassWaves) * 32}, (blk + kPassWaves) * 32 + 31 >= nkeys, nkeys - 1, first);
+                else process(One{}, {K0}, {V0}, {blk * 32}, blk * 32 + 31 >= nkeys, nkeys - 1, first);
                 if (blk + 2 * kPassWaves < nblk) load(c, K0, V0, blk + 2 * kPassWaves);
                 if (blk + 3 * kPassWaves < nblk) load(c, K1, V1, blk + 3 * kPassWaves);
             }
@@ -457,34 +486,32 @@ struct Attend {
             cm[c.wave * 16 + c.tok] = m_run;
             cl[c.wave * 16 + c.tok] = l_run;
         }
-        leave<4>(c, O);
+        leave<4, false>(c, O);
         if (c.wave < 4) {
-            float w[kPassWaves], M = -INFINITY, L = 0.f;
-            f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+            // (all of it read at once and without a test: a wave without keys has left a maximum of minus infinity and zeros)
+            float w[kPassWaves], l[kPassWaves], M = -INFINITY, L = 0.f;
+            f32x4 p[kPassWaves], o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int v = 0; v < kPassWaves; ++v) {
-                w[v] = v < nblk ? cm[v * 16 + c.tok] : -INFINITY;
-                M = fmaxf(M, w[v]);
+                w[v] = cm[v * 16 + c.tok];
+                l[v] = cl[v * 16 + c.tok];
+                p[v] = *(const f32x4*)(c.lds + kRed + c.red + ((v * 4 + c.wave) * 64 + c.lane) * 16);
             }
 #pragma unroll
-            for (int v = 0; v < kPassWaves; ++v)
-                if (v < nblk) {  // (waves with keys)
-                    w[v] = fexp(w[v] - M);
-                    L += cl[v * 16 + c.tok] * w[v];
-                    o += *(const f32x4*)(c.lds + kRed + c.red + ((v * 4 + c.wave) * 64 + c.lane) * 16) * w[v];
-                }
+            for (int v = 0; v < kPassWaves; ++v) M = fmaxf(M, w[v]);
+#pragma unroll
+            for (int v = 0; v < kPassWaves; ++v) {
+                w[v] = fexp(w[v] - M);
+                L += l[v] * w[v];
+                o += p[v] * w[v];
+            }
             if constexpr (PACK) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) o[v] += dpp_f<0x128, 0xF>(0.f, o[v]);
             }
             const float inv = 1.f / L;
             const float r[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
-            if (c.tok < T) put_planes<PACK>(c, out, h * 64 + c.wave * 16 + c.g * 4, r);
-            if (!Walk::TAG) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
-        if constexpr (!Walk::TAG) {
-            lds_barrier();  // all four waves' stores are in memory
-            if (c.wave == 0) c.arrive();
+            put_planes<PACK, false>(c, out, h * 64 + c.wave * 16 + c.g * 4, r);
         }
     }
 };
@@ -516,35 +543,22 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     const bool owner = c.wg < no(), qkv = c.wg < nq(), ffn = c.wg < nf();
     uint4 Wq[KD * QT], Wo[KD * OT], Wi[KD * FT], Wf[KF * OT];
     float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f);
-    Norm none;
     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);  // (owners, waves below OT) the residual stream of this lane's row, features n0 .. n0 + 3
     const bool mine = c.wave < OT && c.wg * OT + c.wave < nd();
     auto n0 = [&] { return (c.wg * OT + c.wave) * 16 + c.g * 4; };
     // the gain of the norm that reads x next, requested before the wait for what is added to it
     auto gain = [&](const float* g) { return ldf4(whole(g), mine ? n0() * 4 : 0); };
-    // the waves that had something to write have written it
-    auto done = [&](auto waves) {
-        if constexpr (decltype(waves)::value > 1) {
-            if (c.wave < decltype(waves)::value) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            lds_barrier();
-        }
-        if (c.wave == 0) c.arrive();
-    };
-    using OWaves = std::integral_constant<int, OT>;
-    auto publish = [&](const float4& gn, char* planes, char* ssq) {
+    auto publish = [&](const float4& gn, char* planes) {
         if (mine) {
             const float w[4] = {x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w};
             const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
-            if (c.tok < T) {
-                put_planes<PACK>(c, planes, n0(), w);
-                if (c.g == 0) {
-                    const int off = (c.tok * nd() + c.wg * OT + c.wave) * 4;
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(ssq), off, 0, Walk::kOut);
-                    if (Walk::TAG) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, whole(ssq + c.clear), off, 0, Walk::kOut);
-                }
+            put_planes<PACK, true>(c, planes, n0(), w);
+            if (c.g == 0) {
+                const int off = (n0() >> 5) * tile_bytes(true, c.R) + c.R * 128 + (c.tok * 2 + ((n0() >> 4) & 1)) * 4;
+                if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(planes), off, 0, Walk::kOut);
+                if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, whole(planes + c.clear), off, 0, Walk::kOut);
             }
         }
-        if (!Walk::TAG) done(OWaves{});
     };
     auto add = [&] {
         const f32x4 s = total<OT, PACK>(c, c.wave);
@@ -570,48 +584,57 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 x = *(const float4*)(a.x_in + (size_t)pos * d + n0());
             }
         }
-        publish(gn, z + a.at.x1, z + a.at.s1);
+        publish(gn, z + a.at.x1);
     }
     if (qkv) request<KD, QT>(c, Wq, L->wqkv, c.wg, d >> 5, tq());
-    if (!Walk::TAG) c.expect(0, no());
-    for (int l = 0; l < a.n_layers; ++l, z += a.at.layer) {
+    for (int l = 0; l < a.n_layers; ++l) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         const bool last = l + 1 == a.n_layers;
         // (addresses are worked out where they are needed: kept across the loop they would not fit the registers)
         asm volatile("" : "+v"(c.lane));
         asm volatile("" : "+s"(T), "+s"(d), "+s"(I), "+s"(F));
-        c.place(T);
+        c.place(T, a.room);
         // ---- q, k, v (a workgroup's tiles are of one of the three) ----
         if (qkv) {
-            const char *xs = pinned(z + a.at.x1), *ss = pinned(z + a.at.s1);
+            const char* xs = pinned(z + a.at.x1);
             const int seg = c.wg * QT * 16 / I;
-            char* out = pinned(seg == 0 ? z + a.at.q : seg == 1 ? L->kc : L->vc);
-            if (!Walk::TAG) c.wait();
-            Norm nm;
+            char* kept = pinned(seg == 1 ? L->kc : L->vc);
+            char* out = pinned(z + (seg == 0 ? a.at.q : seg == 1 ? a.at.k : a.at.v));
             f32x4 acc[QT];
-            multiply<KD, QT, PACK>(c, acc, Wq, xs, d >> 5, nm, c.wave < QT, ss, nd());
-            const float f = nm.factor(d, a.eps);
-            leave<QT>(c, acc);
+            c.template nap<350>();
+            multiply<KD, QT, PACK, true>(c, acc, Wq, xs, d >> 5);
+            leave<QT, true>(c, acc);
             if (c.wave < QT) {
+                const float f = norm_factor(c, d, a.eps);
                 const f32x4 s = total<QT, PACK>(c, c.wave) * f;
                 const int nn = (c.wg * QT + c.wave) * 16 + c.g * 4 - seg * I, pos = len + c.tok;
-                const Rsrc o = whole(out);
-                if (c.tok < T) {
-                    if (seg == 0) {
-                        const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
-                        __builtin_amdgcn_raw_buffer_store_b128(v, o, (c.tok * I + nn) * 4, 0, Walk::kOut);
-                    } else if (seg == 1) {
-                        st8<Walk::kOut>(o, (pos * I + nn) * 2, pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
-                    } else {
+                const Rsrc o = whole(out), n = whole(out + c.clear), kv = whole(kept);
+                const int hd = nn >> 6, f0 = nn & 63;
+                if (seg == 0) {
+                    const int off = ((hd * c.R + c.tok) * 64 + f0) * 4;
+                    const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
+                    if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b128(v, o, off, 0, Walk::kOut);
+                    if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, n, off, 0, Walk::kOut);
+                } else if (seg == 1) {
+                    const int off = ((hd * c.R + c.tok) * 64 + f0) * 2;
+                    const unsigned k01 = pack_bf16x2(s[0], s[1]), k23 = pack_bf16x2(s[2], s[3]);
+                    if (c.tok < T) {
+                        st8<Walk::kOut>(o, off, k01, k23);
+                        st8<Walk::kOut>(kv, (pos * I + nn) * 2, k01, k23);
+                    }
+                    if (c.tok < c.R) st8<Walk::kOut>(n, off, kNotThere, kNotThere);
+                } else {
+                    const int room = fresh_room(c.R), off = ((hd * 64 + f0) * room + c.tok) * 4;
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)f2bf(s[v]), o, ((nn + v) * a.vcap + pos) * 2, 0, Walk::kOut);
+                    for (int v = 0; v < 4; ++v) {
+                        const unsigned b = f2bf(s[v]);
+                        if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(c.tok < T ? b << 16 : 0u, o, off + v * room * 4, 0, Walk::kOut);
+                        if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, kv, ((nn + v) * a.vcap + pos) * 2, 0, Walk::kOut);
+                        if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, n, off + v * room * 4, 0, Walk::kOut);
                     }
                 }
             }
-            done(std::integral_constant<int, QT>{});
         }
-        c.expect(0, nq());
-        if (!Walk::TAG) c.expect(base, a.heads);  // (self-attention)
         // ---- output projection ----
         // Requests go out where the workgroup has several microseconds before it is needed again (a wave's loads come back in
         // order: what is asked for late delays the next stage's activations): here, while the heads work, and below.
@@ -623,18 +646,15 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 request<KF, OT>(c, Wf, L->wout, c.wg, F >> 5, nd());
             }
             const char* xs = pinned(z + a.at.a1);
-            char *ox = pinned(z + a.at.x2), *os = pinned(z + a.at.s2);
-            if (!Walk::TAG) c.wait();
+            char* ox = pinned(z + a.at.x2);
             f32x4 acc[OT];
-            multiply<KD, OT, PACK>(c, acc, Wo, xs, I >> 5, none);
-            leave<OT>(c, acc);
+            multiply<KD, OT, PACK, false>(c, acc, Wo, xs, I >> 5);
+            leave<OT, false>(c, acc);
             if (mine) add();
-            publish(gn, ox, os);
+            publish(gn, ox);
         }
-        if (!Walk::TAG) c.expect(0, no());
-        const char *xf = z + a.at.x2, *sf = z + a.at.s2;  // what the FFN reads
+        const char* xf = z + a.at.x2;  // what the FFN reads
         if (a.cross) {
-            if (!Walk::TAG) c.expect(base, a.heads);
             // ---- output projection of the cross-attention ----
             if (owner) {
                 request<KD, OT>(c, Wo, L->cwo, c.wg, I >> 5, nd());
@@ -644,32 +664,28 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 request<KF, OT>(c, Wf, L->wout, c.wg, F >> 5, nd());
                 if (qkv && !last) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> 5, tq());
                 const char* xs = pinned(z + a.at.a2);
-                char *ox = pinned(z + a.at.x3), *os = pinned(z + a.at.s3);
-                if (!Walk::TAG) c.wait();
+                char* ox = pinned(z + a.at.x3);
                 f32x4 acc[OT];
-                multiply<KD, OT, PACK>(c, acc, Wo, xs, I >> 5, none);
-                leave<OT>(c, acc);
+                multiply<KD, OT, PACK, false>(c, acc, Wo, xs, I >> 5);
+                leave<OT, false>(c, acc);
                 if (mine) add();
-                publish(gn, ox, os);
+                publish(gn, ox);
             }
-            if (!Walk::TAG) c.expect(0, no());
             xf = z + a.at.x3;
-            sf = z + a.at.s3;
         }
         // ---- FFN ----
         if (ffn) {
             if (!owner || !a.cross) request<KD, FT>(c, Wi, L->win, c.wg, d >> 5, tf());
-            const char *xs = pinned(xf), *ss = pinned(sf);
+            const char* xs = pinned(xf);
             char* out = pinned(z + a.at.h);
-            if (!Walk::TAG) c.wait();
             constexpr int FW = GATED ? FT / 2 : FT;  // waves with results
-            Norm nm;
             f32x4 acc[FT];
-            multiply<KD, FT, PACK>(c, acc, Wi, xs, d >> 5, nm, c.wave < FW, ss, nd());
-            const float r = nm.factor(d, a.eps);
-            leave<FT>(c, acc);
+            c.template nap<350>();
+            multiply<KD, FT, PACK, true>(c, acc, Wi, xs, d >> 5);
+            leave<FT, true>(c, acc);
             const int tile = c.wg * FW + c.wave;  // of the hidden state
             if (c.wave < FW && tile < F >> 4) {
+                const float r = norm_factor(c, d, a.eps);
                 float w[4];
                 if constexpr (GATED) {
                     const f32x4 s = total<FT, PACK>(c, 2 * c.wave) * r, u = total<FT, PACK>(c, 2 * c.wave + 1) * r;
@@ -680,23 +696,23 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = fmaxf(s[v], 0.f);
                 }
-                if (c.tok < T) put_planes<PACK>(c, out, tile * 16 + c.g * 4, w);
+                put_planes<PACK, false>(c, out, tile * 16 + c.g * 4, w);
             }
-            if (!Walk::TAG) done(std::integral_constant<int, FW>{});
         }
-        if (!Walk::TAG) c.expect(0, nf());
         if (qkv && !last && (!owner || !a.cross)) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> 5, tq());
+        const char* hidden = z + a.at.h;
+        z = c.next(z, a.at.layer);
+        c.walk_on(a.at.layer);
         if (owner) {
-            const char* xs = pinned(z + a.at.h);
-            char *ox = pinned(z + a.at.layer + a.at.x1), *os = pinned(z + a.at.layer + a.at.s1);
-            if (!Walk::TAG) c.wait();
+            const char* xs = pinned(hidden);
+            char* ox = pinned(z + a.at.x1);
             f32x4 acc[OT];
-            multiply<KF, OT, PACK>(c, acc, Wf, xs, F >> 5, none);
-            leave<OT>(c, acc);
+            c.template nap<650>();
+            multiply<KF, OT, PACK, false>(c, acc, Wf, xs, F >> 5);
+            leave<OT, false>(c, acc);
             if (mine) add();
-            if (!last) publish(next_gain, ox, os);
+            if (!last) publish(next_gain, ox);
         }
-        if (!Walk::TAG) c.expect(0, no());
     }
     if (owner && mine && c.tok < T) {
         *(float4*)(a.x_out + (size_t)c.tok * d + n0()) = x;
@@ -722,13 +738,13 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
     char* z = c.scratch(a);
     if (a.cross) request<KD, 4>(c, Wc, L->cwq, h, d >> 5, I >> 4);
-    if (!Walk::TAG) c.expect(0, ceil_div(d >> 4, Cut::OT));
-    for (int l = 0; l < a.n_layers; ++l, z += a.at.layer) {
+    for (int l = 0; l < a.n_layers; ++l, z = c.next(z, a.at.layer), c.walk_on(a.at.layer)) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         asm volatile("" : "+v"(c.lane));
         asm volatile("" : "+s"(T), "+s"(d), "+s"(I));
-        c.place(T);
-        c.expect(0, ceil_div(3 * (I >> 4), Cut::QT));
+        c.place(T, a.room);
+        Attend<true, PACK, Walk> self = {whole(L->kc + (size_t)h * 128), whole(L->vc + (size_t)h * 64 * a.vcap * 2), I, a.vcap, len, (len + 31) >> 5, {}, {}, {}, {}};
+        if (c.wave < self.nblk) self.load(c, self.K0, self.V0, c.wave);
         // the cross-attention's keys and values while the heads have nothing else to do
         Attend<false, PACK, Walk> cross = {whole(L->ck + (size_t)h * 128), whole(L->cv + (size_t)h * 64 * a.scap * 2), I, a.scap, nsrc, (nsrc + 31) >> 5, {}, {}, {}, {}};
         if (a.cross) {
@@ -736,50 +752,28 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
             if (cross.nblk > kPassWaves) cross.load(c, cross.K1, cross.V1, c.wave + kPassWaves);
         }
         {
-            Attend<true, PACK, Walk> at = {whole(pinned(L->kc + (size_t)h * 128)), whole(pinned(L->vc + (size_t)h * 64 * a.vcap * 2)), I, a.vcap, len + T, (len + T + 31) >> 5, {}, {}, {}, {}};
-            const Rsrc qr = whole(pinned(z + a.at.q));
+            const int room = fresh_room(c.R);
+            const Fresh fresh = {whole(pinned(z + a.at.q + h * c.R * 256)), whole(pinned(z + a.at.k + h * c.R * 128)), whole(pinned(z + a.at.v + h * room * 256)), room};
             char* out = pinned(z + a.at.a1);
             const float sc = a.att_scale;
-            c.wait();
-            auto query = [&](float4 (&qv)[2][2]) {
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) qv[ks][p] = ldf4(qr, ((PACK ? c.t8 : c.t) * I + h * 64 + ks * 32 + c.g * 8 + p * 4) * 4);
-            };
-            at.run(c, query, sc, len, relb, a.rel_d, out, T, h);
+            self.run(c, fresh, sc, len, relb, a.rel_d, out, h);
+            if (!a.cross) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (waves without keys wait for nothing else)
         }
-        if (!Walk::TAG) c.expect(base, a.heads);
-        if (!Walk::TAG) c.expect(0, ceil_div(d >> 4, Cut::OT));
         if (a.cross) {
-            const char *xs = pinned(z + a.at.x2), *ss = pinned(z + a.at.s2);
+            const char* xs = pinned(z + a.at.x2);
             char* out = pinned(z + a.at.a2);
             const float sc = a.att_scale;
-            if (!Walk::TAG) c.wait();
-            Norm nm;
             f32x4 acc[4];
-            multiply<KD, 4, PACK>(c, acc, Wc, xs, d >> 5, nm, c.wave < 4, ss, d >> 4);
-            const float f = nm.factor(d, a.eps);
-            leave<4>(c, acc);
-            float* q = (float*)(c.lds + kQ);
+            multiply<KD, 4, PACK, true>(c, acc, Wc, xs, d >> 5);
+            leave<4, true>(c, acc);
             if (c.wave < 4) {
-                const f32x4 s = total<4, PACK>(c, c.wave) * f;
-                *(f32x4*)(q + c.tok * kQLd + c.wave * 16 + c.g * 4) = s;
+                const f32x4 s = total<4, PACK>(c, c.wave) * norm_factor(c, d, a.eps);
+                *(f32x4*)((float*)(c.lds + kQ) + c.tok * kQLd + c.wave * 16 + c.g * 4) = s;
             }
             lds_barrier();
-            auto query = [&](float4 (&qv)[2][2]) {
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) qv[ks][p] = *(const float4*)(q + (PACK ? c.t8 : c.t) * kQLd + ks * 32 + c.g * 8 + p * 4);
-            };
-            cross.run(c, query, sc, len, nullptr, 0, out, T, h);
+            cross.run(c, Fresh{}, sc, len, nullptr, 0, out, h);
             if (l + 1 < a.n_layers) request<KD, 4>(c, Wc, L[1].cwq, h, d >> 5, I >> 4);
-            if (!Walk::TAG) c.expect(base, a.heads);
-            if (!Walk::TAG) c.expect(0, ceil_div(d >> 4, Cut::OT));
         }
-        if (!Walk::TAG) c.expect(0, ceil_div(GATED ? a.F >> 3 : a.F >> 4, Cut::FT));
-        if (!Walk::TAG) c.expect(0, ceil_div(d >> 4, Cut::OT));
     }
 }
 
@@ -789,7 +783,6 @@ __global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a)
     using Cut = std::conditional_t<DIE, DieCut, ChipCut>;
     Walk<DIE> c;
     c.lds = smem;
-    c.counters = a.sync;
     c.failed = a.sync + kPassSyncWords - 1;
     c.spins = a.spins;
     c.wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -799,7 +792,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a)
         if (__builtin_amdgcn_s_getreg((3 << 11) | 20) != 0) return;
         if (threadIdx.x == 0) {
             unsigned rank;
-            asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)" : "=v"(rank) : "v"(a.sync + kPassCounters * kPassStride), "v"(1u) : "memory");
+            asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)" : "=v"(rank) : "v"(a.sync), "v"(1u) : "memory");
             *(unsigned*)smem = rank;
         }
         lds_barrier();
@@ -807,8 +800,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a)
         if (c.wg >= a.groups) return;
         lds_barrier();
     }
-    c.place(a.T);
-    c.target = 0;
+    c.place(a.T, a.room);
     c.dead = false;
     if (c.wg < a.groups - a.heads) worker<GATED, PACK, Cut>(c, a, a.groups);
     else header<GATED, PACK, Cut>(c, a, a.groups);
@@ -837,7 +829,7 @@ int pass_die_groups(int d, int heads, int d_head, int F, bool gated) {
     return g <= 32 ? g : 0;
 }
 
-PassPlan pass_plan(int T, int d, int I, int F) {
+PassPlan pass_plan(int room, int d, int I, int F) {
     PassPlan p;
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -845,10 +837,10 @@ PassPlan pass_plan(int T, int d, int I, int F) {
         at += (bytes + 255) / 256 * 256;
         return (int)r;
     };
-    const size_t per = 4 * T, x = per * d, i = per * I, s = (size_t)T * (d / 16) * 4;  //
-    p.x1 = take(x); p.s1 = take(s); p.q = take((size_t)T * I * 4); p.a1 = take(i);
-    p.x2 = take(x); p.s2 = take(s); p.a2 = take(i); p.x3 = take(x); p.s3 = take(s);
-    p.h = take(per * F);
+    const size_t x = (size_t)(d / 32) * tile_bytes(true, room), i = (size_t)(I / 32) * tile_bytes(false, room);
+    p.x1 = take(x); p.q = take((size_t)room * I * 4); p.k = take((size_t)room * I * 2); p.v = take((size_t)fresh_room(room) * I * 4);
+    p.a1 = take(i); p.x2 = take(x); p.a2 = take(i); p.x3 = take(x);
+    p.h = take((size_t)(F / 32) * tile_bytes(false, room));
     p.layer = (int)at;
     return p;
 }
@@ -865,7 +857,7 @@ hipError_t pass_init() {
 
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
     if (hipError_t e = pass_init(); e != hipSuccess) return e;
-    if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > (a.turn ? kPassDieRows : kPassRows) || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
+    if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > kPassRows || a.room < a.T || (a.die && a.T > kPassDieRows) || !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
         (a.cross && !a.nsrc_ptr))
         return hipErrorInvalidValue;
     const size_t smem = kRel + (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);
@@ -881,7 +873,7 @@ hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
         if (gated) BILD_P(true, PV, DV);                                                                                     \
         BILD_P(false, PV, DV);                                                                                               \
     } while (0)
-    if (a.turn) BILD_PG(true, true);
+    if (a.die) BILD_PG(true, true);
     if (a.T <= 8) BILD_PG(true, false);
     BILD_PG(false, false);
 #undef BILD_PG

@@ -398,9 +398,8 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int 
         }
     }
     if (a.sync) {
-        a.sync[lane * kPassStride] = 0u;
-        if (lane == 0 && a.turn) *a.turn = c_turn + 1u;
-        if (lane == 0) a.sync[kPassCounters * kPassStride] = a.sync[kPassSyncWords - 1] = 0u;
+        if (lane == 0 && a.turn) *a.turn = c_turn == 2u ? 0u : c_turn + 1u;
+        if (lane == 0) a.sync[0] = a.sync[kPassSyncWords - 1] = 0u;
         if (failed) {  // the pass kernel's workgroups did not all run: nothing happened but the count of passes
             if (lane == 0) {
                 c->seq = c_seq + 1;

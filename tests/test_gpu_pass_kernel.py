@@ -38,6 +38,43 @@ def test_rows_of_a_review(n_max):
     _check(n_max=n_max, alpha_fb=0.0, max_new=2 * n_max)
 
 
+@pytest.mark.parametrize("d_ff", [2112, 4096])
+def test_rows_of_a_review_of_a_wide_ffn(d_ff):
+    """Sixteen rows: the hidden state's tiles in pieces, the last one short."""
+    _check(n_max=15, alpha_fb=0.0, max_new=32, d=1024, heads=16, d_ff=d_ff, vocab=300, n_large=2, logit_scale=4.0)
+
+
+@pytest.mark.parametrize("shape", [dict(), dict(pos=bi.POS_RELATIVE)])
+def test_blocks_of_earlier_keys(shape, monkeypatch):
+    """The new rows' keys are a block of their own, which the wave behind the last block of earlier keys takes; more than eight
+    blocks of those.  Against the separate kernels: each is within logit_tol of the exact value."""
+    cfg = bi.toy_pair(**{**dict(dtype=bi.DT_BF16, d=256, heads=4, d_head=64, d_ff=512, truncate=True, n_src=20, max_new=700), **shape})
+    R = Rig(cfg)
+    got = {}
+    for form, env in FORMS.items():
+        with monkeypatch.context() as m:
+            for k, v in env.items():
+                m.setenv(k, v)
+            st = R.state(cfg.max_new, 15)
+        st.encode(R.src)
+        st.debug_enable_logits(True)
+        logits = []
+        for have in (1, 32, 33, 64, 225, 256, 257, 600):  # tokens before the review, the last of them not yet consumed
+            st.seq_truncate(R.n0)
+            st.force_tokens(R.n0, bi.make_tokens(cfg.large.vocab, have - R.n0, seed=have), have)
+            st.large_verify(float("inf"), draft=[])  # (brings the cache up)
+            for rows in (1, 4, 8, 13):
+                st.seq_truncate(have)
+                before = st.pass_routes()
+                st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+                assert {k for k, v in st.pass_routes().items() if v > before[k]} == {"chip" if form == "die" and rows > 4 else form}, (form, have, rows)
+                logits += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+        got[form] = np.stack(logits)
+    tol = 2 * parity.logit_tol(cfg)
+    for form in ("die", "chip"):
+        assert float(np.abs(got[form] - got["kernels"]).max()) <= tol, form
+
+
 @pytest.mark.parametrize("n_src", [1, 32, 33, 257, 530])
 def test_source_lengths_around_the_key_blocks(n_src):
     _check(n_src=n_src)
