@@ -20,8 +20,10 @@ UNITS = [
     ("gemm_pre.hip", "gemm_pre.o", []),
     ("gemm_dense.hip", "gemm_dense.o", []),
     ("gemm_tile.hip", "gemm_tile.o", []),
+    ("gemm_thin.hip", "gemm_thin.o", []),
     ("pass_kernel.hip", "pass_kernel.o", []),
     ("attn_tile.hip", "attn_tile.o", []),
+    ("attn_split.hip", "attn_split.o", []),
     ("attention.hip", "attention.o", []),
     ("policy.hip", "policy.o", []),
     ("bild_api.hip", "bild_api.o", []),

@@ -370,6 +370,9 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const int h, const 
                     split_bf16x2(acc[2] * inv, acc[3] * inv, h23, l23);
                     st_u64(a.ob_hi + (size_t)t * I + h * dh + d0, h01, h23);
                     st_u64(a.ob_lo + (size_t)t * I + h * dh + d0, l01, l23);
+                } else if (DT && a.ob_t) {
+                    const float w[4] = {acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+                    put_tile_planes(a.ob_t, I >> 5, t, h * dh + d0, w);
                 } else {
                     st_act4(a.out + (size_t)t * I + h * dh + d0, make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv));
                 }
@@ -524,6 +527,9 @@ __device__ __forceinline__ void attn_merge_body(const AttnArgs& a, const int u) 
         split_bf16x2(r.z * inv, r.w * inv, h23, l23);
         st_u64(a.ob_hi + (size_t)t * I + n, h01, h23);
         st_u64(a.ob_lo + (size_t)t * I + n, l01, l23);
+    } else if (a.ob_t) {
+        const float w[4] = {r.x * inv, r.y * inv, r.z * inv, r.w * inv};
+        put_tile_planes(a.ob_t, I >> 5, t, n, w);
     } else {
         st_act4(a.out + (size_t)t * I + n, make_float4(r.x * inv, r.y * inv, r.z * inv, r.w * inv));
     }

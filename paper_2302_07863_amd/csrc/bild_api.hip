@@ -16,6 +16,8 @@
 #include <vector>
 
 #include "bild_state.h"
+#include "attn_split.h"
+#include "gemm_thin.h"
 
 using namespace bild;
 
@@ -379,10 +381,17 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* dw = std::getenv("BILD_DRAW_ONE_WG")) s->draw_spread = dw[0] == '0';
         if (const char* fe = std::getenv("BILD_FUSE_EMBED")) s->fuse_embed = std::atoi(fe) != 0;  // tests and measurements
         if (const char* kd = std::getenv("BILD_KSPLIT_MAX_D")) s->ksplit_max_d = std::atoi(kd);
+        if (const char* tr = std::getenv("BILD_THIN_MIN_ROWS")) s->thin_min_rows = std::atoi(tr);  // tests and measurements
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
     const int positions = std::max(s->cap_len, s->cap_src);
     if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + 2 * kPassRooms), true);
+    if (p->m[0]->cfg.dtype == BILD_DT_BF16 || p->m[1]->cfg.dtype == BILD_DT_BF16) {
+        want(s->thin_sums, sizeof(float) * kThinSums);
+        want(s->thin_arrived, sizeof(unsigned) * kThinArrivals, true);
+        want(s->split_part, sizeof(float) * kAttnSplitFloats);
+        want(s->split_arrived, sizeof(unsigned) * kAttnSplitHeads, true);
+    }
     for (int w = 0; w < 2; ++w) {
         ModelState& M = s->ms[w];
         const bild_model* m = p->m[w];
@@ -662,29 +671,31 @@ GemmArgs gemm_base(const bild_model* m, const TMat& W, const float* x, int ldx, 
     return g;
 }
 
-int launch_gemm_profiled(bild_state* s, const bild_model* m, const GemmArgs& g) {
+template <class Launch>
+int launch_profiled(bild_state* s, const bild_model* m, const TMat& W, int epi, Launch&& launch) {
+    const int64_t bytes = (int64_t)W.n * W.k * m->esz();
     s->gemm_count += 1;
     s->stage_count += 1;
-    s->gemm_bytes += (int64_t)g.W.n * g.W.k * m->esz();
-    if (!s->prof_on) {
-        HIPC(launch_gemm(g, m->cfg.dtype, s->stream));
-        return BILD_OK;
-    }
-    if (s->prof_used >= s->prof_cap) {
-        s->prof_dropped++;
-        HIPC(launch_gemm(g, m->cfg.dtype, s->stream));
+    s->gemm_bytes += bytes;
+    if (s->prof_on && s->prof_used >= s->prof_cap) s->prof_dropped++;
+    if (!s->prof_on || s->prof_used >= s->prof_cap) {
+        HIPC(launch());
         return BILD_OK;
     }
     const int i = s->prof_used++;
     HIPC(hipEventRecord(s->prof_ev[2 * i], s->stream));
-    HIPC(launch_gemm(g, m->cfg.dtype, s->stream));
+    HIPC(launch());
     HIPC(hipEventRecord(s->prof_ev[2 * i + 1], s->stream));
     bild_state::ProfRec r;
     r.model = (m == s->pair->m[1]) ? 1 : 0;
-    r.cls = g.epi == EPI_LMHEAD ? 1 : 0;
-    r.bytes = (int64_t)g.W.n * g.W.k * m->esz();
+    r.cls = epi == EPI_LMHEAD ? 1 : 0;
+    r.bytes = bytes;
     s->prof_rec.push_back(r);
     return BILD_OK;
+}
+
+int launch_gemm_profiled(bild_state* s, const bild_model* m, const GemmArgs& g) {
+    return launch_profiled(s, m, g.W, g.epi, [&] { return launch_gemm(g, m->cfg.dtype, s->stream); });
 }
 
 int run_gemm(bild_state* s, const bild_model* m, GemmArgs& g) {
@@ -698,17 +709,35 @@ int emit_gemm(bild_state* s, const bild_model* m, GemmArgs& g) {
 }
 
 // `deferred` receives the number of key splits whose partials the following output projection must merge
-// (1: the attention output is complete).
+// (1: the attention output is complete; null: it is to be).
 int emit_attention(bild_state* s, const ModelState& M, AttnArgs& a, int nkeys, int* deferred) {
     const int dt = M.m->cfg.dtype;
-    *deferred = 1;
+    if (deferred) *deferred = 1;
     bool defer = false;
     a.splits = a.T > kMaxRows ? 1 : pick_splits(M, nkeys, a.heads, a.T, &defer);  // row blocks and key splits do not combine
     a.nw = pick_attn_waves(dt, a.d_head, std::min(a.T, kMaxRows), nkeys, a.splits);
-    a.defer_merge = a.splits > 1 && defer;
+    a.defer_merge = a.splits > 1 && defer && deferred;  // (null: the attention output is to be complete)
     if (a.defer_merge) *deferred = a.splits;
     s->stage_count += (a.splits > 1 && !a.defer_merge) ? 2 : 1;  // (the merge kernel is a stage of its own)
     if (!s->gemm_only) HIPC(launch_attention(a, dt, s->stream));
+    return BILD_OK;
+}
+
+// Attention over a long cache whose workgroups join their keys themselves (attn_split.hip); 0: not made for it.
+int emit_attention_split(bild_state* s, const ModelState& M, const AttnArgs& a, int nkeys, bool* done) {
+    AttnSplitArgs b;
+    std::memset((void*)&b, 0, sizeof(b));
+    *done = false;
+    if (M.m->cfg.dtype != BILD_DT_BF16 || a.rel_bias || a.T > kMaxRows || !s->split_part) return BILD_OK;
+    attn_split_shape(a.heads, a.d_head, nkeys, &b.splits, &b.waves);
+    if (!b.splits) return BILD_OK;
+    b.q = a.q; b.k = a.k; b.v = a.v; b.vcap = a.vcap; b.i_dim = a.i_dim; b.heads = a.heads; b.d_head = a.d_head; b.T = a.T;
+    b.causal = a.causal; b.len_ptr = a.len_ptr; b.scale = a.scale;
+    b.part = s->split_part; b.arrived = s->split_arrived;
+    b.out = a.out; b.ob_t = a.ob_t;
+    s->stage_count += 1;
+    if (!s->gemm_only) HIPC(launch_attn_split(b, s->stream));
+    *done = true;
     return BILD_OK;
 }
 
@@ -872,6 +901,148 @@ int emit_prefill(bild_state* s, int w, int T) {
         s->stage_count += 1;
         HIPC(launch_row_copy(r, s->stream));
     }
+    return BILD_OK;
+}
+
+// ---- bf16 passes of a few rows on gemm_thin.hip: the planes lie where the row-major ones do (M.xb, M.ab, M.hb) ----
+int run_thin(bild_state* s, const bild_model* m, const ThinArgs& g) {
+    return launch_profiled(s, m, g.W, g.epi, [&] { return launch_gemm_thin(g, s->stream); });
+}
+
+ThinArgs thin_base(const bild_state* s, int w, int T, const TMat& W, const void* in, int parts) {
+    const ModelState& M = s->ms[w];
+    const bild_model_config& c = M.m->cfg;
+    ThinArgs g;
+    std::memset((void*)&g, 0, sizeof(g));
+    g.W = W;
+    g.xp = (const char*)in;
+    g.T = T;
+    g.ssq = M.ssq;
+    g.ssq_parts = parts;
+    g.eps = c.norm_eps;
+    g.act = c.act;
+    g.d_head = c.d_head;
+    g.i_dim = M.m->inner();
+    g.pos_ptr = &s->ctl->len[w];
+    g.sums = s->thin_sums;
+    g.arrived = s->thin_arrived;
+    return g;
+}
+
+// Passes of 2 .. kMaxRows rows of models whose planes the thin GEMM reads; `parts` receives the number of partial sums of squares
+// beside the final hidden state's planes (M.xb, times the final norm's gain).
+int emit_thin(bild_state* s, int w, int T, int key_hint, bool reads_hidden, int* parts_out) {
+    ModelState& M = s->ms[w];
+    const bild_model* m = M.m;
+    const bild_model_config& c = m->cfg;
+    const int d = c.d_model, I = m->inner();
+    const size_t esz = m->esz();
+    const int* len_ptr = &s->ctl->len[w];
+    const int trunk = s->pair->trunk_layers, layer0 = (trunk > 0 && w == 1) ? trunk : 0;
+    const bool keeps_hidden = trunk > 0 && w == 0;
+    int parts = 1;
+    s->stage_count += 1;
+    if (!s->gemm_only) {
+        if (layer0 > 0) {  // the hidden state the trunk left for these rows
+            RowCopyArgs r;
+            std::memset((void*)&r, 0, sizeof(r));
+            r.src = s->trunk_x;
+            r.src_row_ptr = len_ptr;
+            r.dst = M.x;
+            r.d = d;
+            r.T = T;
+            HIPC(launch_row_tiles(r, m->dec[layer0].ln1, (char*)M.xb, M.ssq, s->stream));
+        } else {
+            EmbedArgs e;
+            std::memset((void*)&e, 0, sizeof(e));
+            e.E = m->emb;
+            e.tokens = s->y;
+            e.base_ptr = len_ptr;
+            e.T = T;
+            e.d = d;
+            e.vocab = c.vocab;
+            e.tie_shift = c.tie_shift;
+            e.sinusoidal = c.pos == BILD_POS_SINUSOIDAL;
+            e.embed_scale = c.embed_scale;
+            e.x = M.x;
+            e.pe = M.pe;
+            e.nx_gain = m->dec[0].ln1;
+            e.nx_ssq = M.ssq;
+            HIPC(launch_embed_tiles(e, (char*)M.xb, s->stream));
+        }
+    }
+    auto resid = [&](const TMat& W, const void* in, const float* next_gain) {
+        ThinArgs g = thin_base(s, w, T, W, in, 0);
+        g.epi = EPI_RESID;
+        g.out = M.x;
+        g.ldo = d;
+        g.np = (char*)M.xb;
+        g.np_tk = d / 32;
+        g.np_gain = next_gain;
+        g.np_ssq = M.ssq;
+        parts = W.tn;
+        return run_thin(s, m, g);
+    };
+    auto attend = [&](void* k, void* v, int vcap, bool causal, int nkeys) {
+        AttnArgs a;
+        std::memset((void*)&a, 0, sizeof(a));
+        a.q = M.q; a.k = k; a.v = v; a.vcap = vcap;
+        a.T = T; a.heads = c.n_heads; a.d_head = c.d_head; a.i_dim = I;
+        a.causal = causal;
+        a.len_ptr = causal ? len_ptr : &s->ctl->n_src;
+        if (causal) { a.rel_bias = m->dec_rel; a.rel_d = c.rel_max_dist; }
+        a.part_o = M.att_o; a.part_ml = M.att_ml;
+        a.scale = 1.f / std::sqrt((float)c.d_head);
+        a.ob_t = (char*)M.ab;
+        bool done = false;
+        const int rc = emit_attention_split(s, M, a, nkeys, &done);
+        return rc || done ? rc : emit_attention(s, M, a, nkeys, nullptr);
+    };
+    int rc;
+    for (int l = layer0; l < c.n_dec_layers; ++l) {
+        const LayerW& L = m->dec[l];
+        const bool last = l + 1 == c.n_dec_layers;
+        const size_t off = (size_t)l * s->cap_len * I * esz, coff = (size_t)l * s->cap_src * I * esz;
+        ThinArgs g = thin_base(s, w, T, L.wqkv, M.xb, parts);
+        g.epi = EPI_QKV;
+        g.q_dim = I;
+        g.q_out = M.q;
+        g.k_cache = M.kcache + off;
+        g.v_cache = M.vcache + off;
+        g.vcap = s->cap_len;
+        g.rope = M.rope;
+        if ((rc = run_thin(s, m, g))) return rc;
+        if (last && !reads_hidden && !keeps_hidden) break;
+        if ((rc = attend(M.kcache + off, M.vcache + off, s->cap_len, true, key_hint))) return rc;
+        if ((rc = resid(L.wo, M.ab, c.cross_attn ? L.lnc : L.ln2))) return rc;
+        if (c.cross_attn) {
+            ThinArgs q = thin_base(s, w, T, L.cwq, M.xb, parts);
+            q.epi = EPI_STORE;
+            q.out = M.q;
+            q.ldo = I;
+            if ((rc = run_thin(s, m, q))) return rc;
+            if ((rc = attend(M.ck + coff, M.cv + coff, s->cap_src, false, s->n_src))) return rc;
+            if ((rc = resid(L.cwo, M.ab, L.ln2))) return rc;
+        }
+        ThinArgs f = thin_base(s, w, T, L.win, M.xb, parts);
+        f.epi = EPI_ACT;
+        f.np = (char*)M.hb;
+        f.np_tk = c.d_ff / 32;
+        if ((rc = run_thin(s, m, f))) return rc;
+        if ((rc = resid(L.wout, M.hb, last ? m->dec_final : m->dec[l + 1].ln1))) return rc;
+    }
+    if (keeps_hidden) s->stage_count += 1;
+    if (keeps_hidden && !s->gemm_only) {  // remember what the trunk produced for these positions
+        RowCopyArgs r;
+        std::memset((void*)&r, 0, sizeof(r));
+        r.src = M.x;
+        r.dst = s->trunk_x;
+        r.dst_row_ptr = len_ptr;
+        r.d = d;
+        r.T = T;
+        HIPC(launch_row_copy(r, s->stream));
+    }
+    *parts_out = parts;
     return BILD_OK;
 }
 
@@ -1050,7 +1221,12 @@ int emit_layers(bild_state* s, int w, int T, int key_hint, bool reads_hidden, bo
             fused = fuse_attention(a, L.wo, key_hint);
             if (fused < 0) return fused;
             if (!fused) {
-                int rc = emit_attention(s, M, a, key_hint, &merge_splits);
+                bool done = false;
+                // (16 layers 2048 wide with the projection that joins the keys / with this kernel, 104, 340, 1064, 4137 keys: 632 / 607,
+                // 642 / 642, 670 / 659, 777 / 756 us a pass; 8 layers 4096 wide 759 / 743, 767 / 760, 785 / 771, 845 / 843)
+                int rc = T == 1 && d > 1024 ? emit_attention_split(s, M, a, key_hint, &done) : BILD_OK;
+                if (done) merge_splits = 1;
+                if (rc == BILD_OK && !done) rc = emit_attention(s, M, a, key_hint, &merge_splits);
                 if (rc) return rc;
             }
         }
@@ -1166,6 +1342,17 @@ int emit_layers(bild_state* s, int w, int T, int key_hint, bool reads_hidden, bo
 
 namespace bild {
 
+// Passes on the thin GEMM (gemm_thin.hip): where a projection has about a feature tile per compute unit (4096 wide) always, in
+// narrower models where the rows outweigh that.  us per pass, row-major planes / thin, over 1024 keys, 8 layers of the 7B shape, 2, 4, 8,
+// 12, 16, 17, 32 rows: 869 / 838, 884 / 841, 931 / 844, 1006 / 890, 1053 / 893, 1128 / 971, 1341 / 982; 16 layers 2048 wide, 2, 4, 8, 16, 32 rows:
+// 736 / 797, 790 / 800, 859 / 808, 957 / 881, 1328 / 1105; T5-large shape 16, 17, 24, 32 rows: 1242 / 1258, 1474 / 1563, 1645 / 1564, 1690 / 1571.
+static bool takes_thin(const bild_state* s, int w, int T) {
+    const bild_model_config& c = s->ms[w].m->cfg;
+    const int from = s->thin_min_rows > 0 ? s->thin_min_rows : c.d_model >= 4096 ? 2 : c.d_model >= 2048 ? 5 : 24;
+    // (a reader adds kMaxSsqParts sums of squares of sixteen features at most)
+    return c.dtype == BILD_DT_BF16 && T >= std::max(2, from) && T <= kMaxRows && c.d_model <= 16 * kMaxSsqParts;
+}
+
 // Counts the passes of model w with room for T rows.
 static unsigned* pass_turn(const bild_state* s, int w, int T) { return s->pass_sync + kPassSyncWords + w * kPassRooms + pass_room_index(T); }
 
@@ -1182,6 +1369,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     s->stage_count = 0;
     int xb_parts = 0;  // > 0: the final hidden state also sits in M.xb as bf16 planes (times the final norm's gain)
     float* xfin = M.x;  // the residual stream after the last layer ...
+    int thin_parts = 0;  // > 0: the final hidden state lies in M.xb as tile planes (times the final norm's gain)
     bool parts = false; // ... to which the partial results in M.px are still to be added (split FFN output projection)
     if (one) {
         const int trunk = s->pair->trunk_layers, layer0 = w == 1 ? trunk : 0;
@@ -1212,6 +1400,9 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         s->stage_count += 1;
         p.groups = die ? M.pass_die_groups : M.pass_groups;
         HIPC(launch_pass(p, die ? s->cus : p.groups, s->stream));
+    } else if (takes_thin(s, w, T)) {
+        const int rc = emit_thin(s, w, T, key_hint, lm_rows > 0, &thin_parts);
+        if (rc) return rc;
     } else if (dt == BILD_DT_BF16 && T > kMaxRows) {
         if (lm_rows > 0) return BILD_EINVAL;
         const int rc = emit_prefill(s, w, T);
@@ -1234,7 +1425,23 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         f.sync = s->pass_sync;
         f.turn = pass_turn(s, w, T);
     }
-    if (lm_rows > 0) {
+    if (lm_rows > 0 && thin_parts > 0) {
+        ThinArgs g = thin_base(s, w, T, m->head, M.xb, thin_parts);
+        g.epi = EPI_LMHEAD;
+        g.first = T - lm_rows;
+        g.scale = c.logit_scale;
+        g.vocab = c.vocab;
+        g.y = s->y;
+        g.ylen_ptr = &s->ctl->y_len;
+        g.part = M.part;
+        g.part_ld = M.nparts_cap;
+        g.zt = M.zt;
+        g.dbg = (s->debug_logits || s->top_p > 0.f) ? M.dbg : nullptr;
+        f.nparts = thin_shape(g.W, g.epi, g.act, T).groups;
+        if (f.nparts > M.nparts_cap) return BILD_ECAP;
+        const int rc = run_thin(s, m, g);
+        if (rc) return rc;
+    } else if (lm_rows > 0) {
         GemmArgs g = gemm_base(m, m->head, xfin + (size_t)(T - lm_rows) * d, d, lm_rows, m->dec_final);
         if (parts) { g.px = M.px; g.px_stride = (int64_t)kMaxRows * d; g.pn = kPartSlices; g.x_out = xfin == M.x ? M.x2 : M.x; }
         g.epi = EPI_LMHEAD;
@@ -1260,9 +1467,11 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
             int rc = launch_gemm_profiled(s, m, g);
             if (rc) return rc;
         }
-        f.part = M.part;
-        f.part_ld = g.part_ld;
         f.nparts = (int)gemm_num_blocks(g);
+    }
+    if (lm_rows > 0) {
+        f.part = M.part;
+        f.part_ld = M.nparts_cap;
         f.zt = M.zt;
         f.T = lm_rows;
         f.mode = mode;

@@ -401,6 +401,8 @@ hipError_t kernels_init();  // one-time function attributes, which also load the
 hipError_t gemm_init();  // what an LM head alone needs
 hipError_t attention_init();
 hipError_t gemm_tile_init();
+hipError_t gemm_thin_init();
+hipError_t attn_split_init();
 hipError_t attn_tile_init();
 hipError_t pass_init();
 template <size_t N>

@@ -224,6 +224,11 @@ struct bild_state {
     bool use_graphs = true;
     bool one_kernel = true;   // passes of up to kPassRows rows of a narrow bf16 model run as one kernel
     bool one_die = true;      // ... on one die, if it fits
+    float* thin_sums = nullptr;  // of the slices of the thin GEMM's projections
+    unsigned* thin_arrived = nullptr;
+    float* split_part = nullptr;  // of the workgroups that share a head's keys
+    unsigned* split_arrived = nullptr;
+    int thin_min_rows = 0;    // > 0: passes of a bf16 model from so many rows on take the thin GEMM (else see takes_thin)
     unsigned* pass_sync = nullptr;
     bool last_one = false;    // the pass issued last is one kernel
     int pass_pause = 0, pass_fails = 0;  // passes to run as separate kernels before the next attempt; attempts in vain in a row

@@ -294,6 +294,8 @@ hipError_t gemm_init() {
 hipError_t kernels_init() {
     if (hipError_t e = gemm_init(); e != hipSuccess) return e;
     if (hipError_t e = gemm_tile_init(); e != hipSuccess) return e;
+    if (hipError_t e = gemm_thin_init(); e != hipSuccess) return e;
+    if (hipError_t e = attn_split_init(); e != hipSuccess) return e;
     if (hipError_t e = attn_tile_init(); e != hipSuccess) return e;
     if (hipError_t e = pass_init(); e != hipSuccess) return e;
     return attention_init();
