@@ -27,6 +27,7 @@ UNITS = [
     ("attention.hip", "attention.o", []),
     ("policy.hip", "policy.o", []),
     ("bild_api.hip", "bild_api.o", []),
+    ("head.hip", "head.o", []),
     ("head_stats.hip", "head_stats.o", []),
     ("bench_api.hip", "bench_api.o", []),
     ("layout.cpp", "layout.o", []),

@@ -18,6 +18,7 @@
 #include "bild_state.h"
 #include "attn_split.h"
 #include "gemm_thin.h"
+#include "head.h"
 
 using namespace bild;
 
@@ -1342,6 +1343,15 @@ int emit_layers(bild_state* s, int w, int T, int key_hint, bool reads_hidden, bo
 
 namespace bild {
 
+// LM heads whose workgroups stay for the whole sweep (head.hip).  One row of a matrix that a chip full of short workgroups reads in
+// 15 us loses 1 us there.  us per pass before / with it: 32 128 ids, T5-small shape one row 97.9 / 99.1, T5-large shape 1, 3, 8, 11 rows
+// 454 / 455, 463 / 464, 480 / 480, 552 / 551; 250 112 ids 153 / 144, 543 / 527, 555 / 535, 570 / 549, 647 / 626.  (A head alone, 32 000 x 2048,
+// 1, 8, 21, 32 rows: 28.4, 31.7, 52.4, 60.8 / 27.7, 30.1, 33.9, 36.1.)
+static bool takes_sweep(const bild_model* m, int rows) {
+    const size_t bytes = (size_t)m->head.tn * m->head.tk * kTileBytes;
+    return m->cfg.dtype == BILD_DT_BF16 && rows > 0 && (rows > 1 || bytes >= (size_t)96 << 20);
+}
+
 // Passes on the thin GEMM (gemm_thin.hip): where a projection has about a feature tile per compute unit (4096 wide) always, in
 // narrower models where the rows outweigh that.  us per pass, row-major planes / thin, over 1024 keys, 8 layers of the 7B shape, 2, 4, 8,
 // 12, 16, 17, 32 rows: 869 / 838, 884 / 841, 931 / 844, 1006 / 890, 1053 / 893, 1128 / 971, 1341 / 982; 16 layers 2048 wide, 2, 4, 8, 16, 32 rows:
@@ -1441,6 +1451,29 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         if (f.nparts > M.nparts_cap) return BILD_ECAP;
         const int rc = run_thin(s, m, g);
         if (rc) return rc;
+    } else if (const int groups = takes_sweep(m, lm_rows) && !parts ? head_groups(m->head, lm_rows) : 0; groups > 0) {
+        HeadArgs h;
+        std::memset((void*)&h, 0, sizeof(h));
+        h.W = m->head;
+        h.x = xfin + (size_t)(T - lm_rows) * d;
+        h.ldx = d;
+        h.T = lm_rows;
+        h.gain = m->dec_final;
+        h.eps = c.norm_eps;
+        h.scale = c.logit_scale;
+        h.vocab = c.vocab;
+        h.y = s->y;
+        h.ylen_ptr = &s->ctl->y_len;
+        h.pos_ptr = len_ptr;
+        h.pos_add = T - lm_rows;
+        h.part = M.part;
+        h.part_ld = M.nparts_cap;
+        h.zt = M.zt;
+        h.dbg = (s->debug_logits || s->top_p > 0.f) ? M.dbg : nullptr;  // the draw of the sampling variant reads the logits
+        if (groups > M.nparts_cap) return BILD_ECAP;
+        const int rc = launch_profiled(s, m, h.W, EPI_LMHEAD, [&] { return launch_head(h, s->stream); });
+        if (rc) return rc;
+        f.nparts = groups;
     } else if (lm_rows > 0) {
         GemmArgs g = gemm_base(m, m->head, xfin + (size_t)(T - lm_rows) * d, d, lm_rows, m->dec_final);
         if (parts) { g.px = M.px; g.px_stride = (int64_t)kMaxRows * d; g.pn = kPartSlices; g.x_out = xfin == M.x ? M.x2 : M.x; }

@@ -1,6 +1,8 @@
 // Host-side objects behind the opaque handles of bild.h, shared by the product entry points (bild_api.hip)
 // and the measurement entry points (bench_api.hip).  Not part of the public ABI.
 #pragma once
+#include <algorithm>
+#include <cstring>
 #include <array>
 #include <map>
 #include <mutex>
@@ -35,6 +37,12 @@ struct HeadScratch {
     void* p = nullptr;
     size_t bytes = 0;
     int dev = -1;
+    unsigned *done = nullptr, *done_dev = nullptr;  // pinned, a word per row: the number of the last call whose result is there
+    unsigned calls = 0;
+    void release() {  // (the first waits for whatever is still running)
+        (void)hipFree(p);
+        if (done) (void)hipHostFree(done);
+    }
 };
 class HeadPool {
     static constexpr int kKept = 4;
@@ -56,6 +64,21 @@ public:
         }
         b.bytes = bytes;
         if (hipMalloc(&b.p, bytes) != hipSuccess) b.p = nullptr;
+        if (b.p && hipMemset(b.p, 0, std::min(bytes, (size_t)256)) != hipSuccess) {  // (the count of workgroups that arrive)
+            (void)hipFree(b.p);
+            b.p = nullptr;
+        }
+        void* h = nullptr;
+        if (b.p && hipHostMalloc(&h, sizeof(unsigned) * kMaxRows, hipHostMallocMapped) == hipSuccess) {
+            void* dp = nullptr;
+            if (hipHostGetDevicePointer(&dp, h, 0) == hipSuccess) {
+                std::memset(h, 0, sizeof(unsigned) * kMaxRows);
+                b.done = (unsigned*)h;
+                b.done_dev = (unsigned*)dp;
+            } else {
+                (void)hipHostFree(h);
+            }
+        }
         return b;
     }
     void give(const HeadScratch& b) {  // (no kernel uses it any more); the smallest of too many goes
@@ -70,10 +93,10 @@ public:
             out = kept[least];
             kept.erase(kept.begin() + least);
         }
-        (void)hipFree(out.p);
+        out.release();
     }
     ~HeadPool() {
-        for (HeadScratch& b : kept) (void)hipFree(b.p);
+        for (HeadScratch& b : kept) b.release();
     }
 };
 

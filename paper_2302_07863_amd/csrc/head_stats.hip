@@ -7,17 +7,20 @@
 //   bild_head_stats_static  uses a file-scope device array, so the call allocates nothing at all.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 
 #include "bild_state.h"
+#include "head.h"
 #include "kernel_common.h"
 
 using namespace bild;
 
 namespace {
 
-// Scratch layout (bytes): [256, 512) logits of the targets, one float per row; [512, ...) partial statistics,
+// Scratch layout (bytes): [0, 256) workgroups that have arrived (pool buffers: zero between calls); [256, 512) logits of the targets, one float per row; [512, ...) partial statistics,
 // StatPart[rows][workgroups].
 constexpr size_t kHdrBytes = 512;
 constexpr size_t kStaticScratchBytes = (size_t)4 << 20;  // 4 MiB
@@ -56,6 +59,8 @@ struct MergeArgs {
     const int* targets;
     int vocab;
     bild_row_stats* out;
+    unsigned* done;  // (see HeadArgs)
+    unsigned call;
 };
 
 // Merges the per-workgroup partial statistics of one row per workgroup, in a fixed order, and writes the row's result.  One
@@ -76,16 +81,9 @@ __global__ __launch_bounds__(1024) void head_stats_merge_kernel(const MergeArgs 
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < nwv; ++w) r = stat_merge<true>(r, Stat{share[w].m, share[w].s, share[w].idx});
-        bild_row_stats o;
-        o.zmax = r.m;
-        o.lse = r.m + logf(r.s);
-        o.argmax = r.idx;
-        o.z_target = __builtin_nanf("");
-        if (a.targets) {
-            const int tgt = a.targets[t];
-            if (tgt >= 0 && tgt < a.vocab) o.z_target = a.zt[t];  // (the head kernel has left it)
-        }
-        a.out[t] = o;
+        const int tgt = a.targets ? a.targets[t] : -1;
+        const bool has = tgt >= 0 && tgt < a.vocab;
+        put_row_stats(a.out, t, r.m, r.s, r.idx, has, has ? a.zt[t] : 0.f, a.done, a.call);  // (the head kernel has left it)
     }
 }
 
@@ -117,7 +115,7 @@ GemmArgs head_gemm(const bild_model* m, const float* x, int rows, const int32_t*
     return g;
 }
 
-int head_stats_run(const bild_model* m, int rows, const int32_t* targets, bild_row_stats* out, hipStream_t st, const GemmArgs& g) {
+int head_stats_run(const bild_model* m, int rows, const int32_t* targets, bild_row_stats* out, hipStream_t st, const GemmArgs& g, unsigned* done, unsigned call) {
     HIPC(launch_gemm(g, m->cfg.dtype, st));
     MergeArgs ma;
     ma.part = g.part;
@@ -126,9 +124,58 @@ int head_stats_run(const bild_model* m, int rows, const int32_t* targets, bild_r
     ma.targets = targets;
     ma.vocab = m->cfg.vocab;
     ma.out = out;
+    ma.done = done;
+    ma.call = call;
     hipLaunchKernelGGL(head_stats_merge_kernel, dim3(rows), dim3(ma.nparts > 2048 ? 1024 : 256), 0, st, ma);
     HIPC(hipGetLastError());
     return BILD_OK;
+}
+
+// The same by the kernel whose workgroups stay for the whole sweep, where it is made for the shape (workgroups > 0).  `joins`: its
+// last workgroup writes the results itself, which takes a count that no other call touches; else a launch of its own does.
+int head_sweep_run(const bild_model* m, const float* x, int rows, const int32_t* targets, bild_row_stats* out, hipStream_t st, const GemmArgs& g, int groups, bool joins, unsigned* done,
+                   unsigned call) {
+    HeadArgs h;
+    std::memset((void*)&h, 0, sizeof(h));
+    h.W = m->head;
+    h.x = x;
+    h.ldx = m->cfg.d_model;
+    h.T = rows;
+    h.gain = g.gain;
+    h.eps = g.eps;
+    h.scale = g.scale;
+    h.vocab = g.vocab;
+    h.y = g.y;
+    h.ylen_ptr = g.ylen_ptr;
+    h.part = g.part;
+    h.part_ld = groups;
+    h.zt = g.zt;
+    if (joins) {
+        h.out = out;
+        h.arrived = (unsigned*)((char*)g.zt - 256);
+        h.done = done;
+        h.call = call;
+    }
+    HIPC(launch_head(h, st));
+    if (!joins) {
+        const MergeArgs ma = {g.part, groups, g.zt, targets, m->cfg.vocab, out, done, call};
+        hipLaunchKernelGGL(head_stats_merge_kernel, dim3(rows), dim3(256), 0, st, ma);
+        HIPC(hipGetLastError());
+    }
+    return BILD_OK;
+}
+int sweep_groups(const bild_model* m, int rows) { return m->cfg.dtype == BILD_DT_BF16 ? head_groups(m->head, rows) : 0; }
+
+// Whether all rows' results are in memory, seen in the words the kernel leaves in pinned memory: some microseconds before the stream's
+// completion reaches the host.  Not for long: what else is on the stream is waited for without spinning.
+bool rows_done(const unsigned* done, unsigned call, int rows) {
+    const auto t0 = std::chrono::steady_clock::now();
+    int r = 0;
+    for (unsigned spins = 1;; ++spins) {
+        while (r < rows && __atomic_load_n(done + r, __ATOMIC_ACQUIRE) == call) ++r;
+        if (r == rows) return true;
+        if ((spins & 255) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) return false;
+    }
 }
 
 int check_args(const bild_model* m, const float* x, int rows, bild_row_stats* out) {
@@ -142,18 +189,23 @@ int check_args(const bild_model* m, const float* x, int rows, bild_row_stats* ou
 extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows, const int32_t* targets_dev,
                                bild_row_stats* out_dev, void* hip_stream) {
     if (int rc = check_args(m, x_dev, rows, out_dev)) return rc;
-    if (gemm_init() != hipSuccess) return BILD_EHIP;
+    if (gemm_init() != hipSuccess || head_init() != hipSuccess) return BILD_EHIP;
     hipStream_t st = (hipStream_t)hip_stream;
     void* slots = nullptr;
     if (int rc = of_device(g_counts_ptr, HIP_SYMBOL(counts), &slots)) return rc;
     GemmArgs g = head_gemm(m, x_dev, rows, targets_dev, nullptr, (const int*)slots);
-    const size_t bytes = kHdrBytes + (size_t)g.part_ld * sizeof(StatPart) * rows;
+    const int groups = sweep_groups(m, rows);
+    const size_t bytes = kHdrBytes + (size_t)std::max(g.part_ld, groups) * sizeof(StatPart) * rows;
     HeadScratch b = m->head_pool.take(bytes);
     if (!b.p) return BILD_ENOMEM;
     g.zt = (float*)((char*)b.p + 256);
     g.part = (StatPart*)((char*)b.p + kHdrBytes);
-    int rc = head_stats_run(m, rows, targets_dev, out_dev, st, g);
-    if (hipStreamSynchronize(st) != hipSuccess && rc == BILD_OK) rc = BILD_EHIP;  // the scratch is in use until here
+    // (one row per wave of the last workgroup: more are joined sooner by a launch of a workgroup each; 512 x 32 128 ids, 1, 8, 16, 32
+    // rows: 22.2, 23.0, 25.0, 29.9 us joined in the sweep, 22.9, 23.3, 23.6, 25.4 by a launch)
+    b.calls += 1;
+    int rc = groups ? head_sweep_run(m, x_dev, rows, targets_dev, out_dev, st, g, groups, rows <= 8, b.done_dev, b.calls)
+                    : head_stats_run(m, rows, targets_dev, out_dev, st, g, b.done_dev, b.calls);
+    if (!(rc == BILD_OK && b.done && rows_done(b.done, b.calls, rows)) && hipStreamSynchronize(st) != hipSuccess && rc == BILD_OK) rc = BILD_EHIP;  // the scratch is in use until here
     m->head_pool.give(b);
     return rc;
 }
@@ -161,11 +213,13 @@ extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows
 extern "C" int bild_head_stats_static(const bild_model* m, const float* x_dev, int rows, const int32_t* targets_dev,
                                       bild_row_stats* out_dev, void* hip_stream) {
     if (int rc = check_args(m, x_dev, rows, out_dev)) return rc;
-    if (gemm_init() != hipSuccess) return BILD_EHIP;
+    if (gemm_init() != hipSuccess || head_init() != hipSuccess) return BILD_EHIP;
     void *scr = nullptr, *slots = nullptr;
     if (int rc = of_device(g_scratch_ptr, HIP_SYMBOL(scratch), &scr)) return rc;
     if (int rc = of_device(g_counts_ptr, HIP_SYMBOL(counts), &slots)) return rc;
     const GemmArgs g = head_gemm(m, x_dev, rows, targets_dev, scr, (const int*)slots);
     if (g.part_ld > kStaticMaxParts) return BILD_ECAP;  // more partial statistics than the array holds
-    return head_stats_run(m, rows, targets_dev, out_dev, (hipStream_t)hip_stream, g);
+    // (calls that overlap on a GPU share the scratch: a count left wrong by them would outlast them)
+    if (const int groups = sweep_groups(m, rows)) return head_sweep_run(m, x_dev, rows, targets_dev, out_dev, (hipStream_t)hip_stream, g, groups, false, nullptr, 0);
+    return head_stats_run(m, rows, targets_dev, out_dev, (hipStream_t)hip_stream, g, nullptr, 0);
 }

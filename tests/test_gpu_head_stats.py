@@ -100,3 +100,25 @@ def test_merge_of_many_partials_is_exact_to_the_sums_rounding():
     err = got["lse"] - np.log1p((shape.vocab - 1) * np.exp(z))
     print("error of lse", np.abs(err).max(), np.sqrt(np.mean(err ** 2)))
     assert np.abs(err).max() < 4.4e-7
+
+
+@pytest.mark.parametrize("d,vocab", [(64, 17), (512, 4100), (1056, 1030), (2048, 9000), (512, 66000), (4096, 600)])
+def test_sweep_shapes(d, vocab):
+    """Input tiles per wave (none for some waves, a short last one), feature tiles per group, several groups per workgroup, both
+    entry points: the same results from a launch that joins and from one that does not."""
+    cfg = bi.toy_pair(dtype=bi.DT_BF16, d=d, vocab=vocab, n_large=1)
+    _, wl = bi.make_pair_weights(cfg)
+    shape = cfg.large
+    model = parity.make_gpu_model(shape, wl)
+    rng = np.random.default_rng(13)
+    x = rng.standard_normal((32, shape.d)).astype(np.float32)
+    targets = rng.integers(0, shape.vocab, size=32)
+    targets[:3] = (0, shape.vocab - 1, 16)
+    for rows in (1, 2, 8, 9, 16, 17, 32):
+        for _ in range(2):  # (the second call finds the scratch of the first)
+            got = run_head_stats(model, x[:rows], targets[:rows])
+            check_against_oracle(shape, wl, x[:rows], targets[:rows], got, parity.logit_tol(cfg))
+        other = run_head_stats(model, x[:rows], targets[:rows], "bild_head_stats_static")
+        for k in ("zmax", "argmax", "z_target"):
+            assert (got[k] == other[k]).all(), (rows, k)
+        assert np.abs(got["lse"] - other["lse"]).max() <= 2e-6 * max(1.0, float(np.abs(got["lse"]).max()))
