@@ -53,7 +53,7 @@ bool config_ok(const bild_model_config& c) {
 
 // what the workgroups of a pass in one kernel hand over: three layers' memory
 size_t pass_turns_bytes(const ModelState& M, int room) {
-    return 3 * (size_t)pass_plan(1 << room, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff).layer;
+    return 3 * (size_t)pass_plan(1 << room, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff, M.m->cfg.dtype == BILD_DT_F32).layer;
 }
 
 // captured passes carry some of the state's settings by value: where one changes they are captured anew
@@ -432,11 +432,14 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             want(M.ab, sizeof(uint16_t) * 2 * kMaxRows * I);
             want(M.hb, sizeof(uint16_t) * 2 * kMaxRows * F);
             want(M.ssq, sizeof(float) * (kMaxSsqParts + 8) * kMaxRows);
-            M.pass_groups = s->one_kernel && m->cfg.pos != BILD_POS_ROPE ? pass_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus) : 0;
-            if (M.pass_groups && s->one_die && s->cus == 256) M.pass_die_groups = pass_die_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated());
+        }
+        if (s->one_kernel && m->cfg.pos != BILD_POS_ROPE) {
+            const int die = s->one_die && s->cus == 256 ? pass_die_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), !bf16) : 0;
+            M.pass_groups = bf16 ? pass_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus) : die;
             if (M.pass_groups) {
+                M.pass_die_groups = die;
+                M.pass_die_rows = die == 0 ? 0 : !bf16 ? kPassRows : w == 0 ? 1 : kPassDieRows;
                 want(M.pass_layers, sizeof(PassLayer) * L);
-                M.pass_die_rows = M.pass_die_groups == 0 ? 0 : w == 0 ? 1 : kPassDieRows;
                 for (int r = 0; r < kPassRooms; ++r) want(M.pass_turns[r], pass_turns_bytes(M, r));
             }
         }
@@ -1402,7 +1405,8 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         const bool die = T <= M.pass_die_rows;
         p.die = die;
         p.room = 1 << pass_room_index(T);
-        p.at = pass_plan(p.room, d, p.I, p.F);
+        p.f32 = dt == BILD_DT_F32;
+        p.at = pass_plan(p.room, d, p.I, p.F, p.f32);
         p.turn = pass_turn(s, w, T);
         p.scratch = M.pass_turns[pass_room_index(T)];
         p.sync = s->pass_sync;
@@ -1545,13 +1549,15 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // On one die one row costs 148 / 96, 149 / 125, 159 / 156, 159 / 187 (T5-small shape; mT5-small 206 / 117, 206 / 159, 220 / 199,
 // 219 / 241; 256-wide 95 / 67, 96 / 87, 102 / 108, 104 / 128).
 //
+// fp32, 256 wide, 4 layers, one row at 32, 256, 512, 1024 tokens 120 / 63, 126 / 73, 130 / 86, 130 / 115; 2 layers 68 / 41, 72 / 45, 72 / 53, 72 / 67.
+//
 // Sequence.  Its keys past the first 256 are not asked for ahead.  At 256, 512, 1024 positions: T5-large shape one row 708 / 478,
 // 713 / 522, 746 / 639; eight 1053 / 526, 1091 / 575, 1125 / 688; T5-small shape on one die 158 / 105, 160 / 113, 167 / 134; no shape and
 // row count loses before the 1024 that were measured.
 static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
-           s->n_src <= (on_one_die(s, w, T) ? 1280 : T == 1 ? 1408 : 1536) && s->len[w] + T <= 1024;
+           s->n_src <= (s->ms[w].m->cfg.dtype == BILD_DT_F32 ? 1024 : on_one_die(s, w, T) ? 1280 : T == 1 ? 1408 : 1536) && s->len[w] + T <= 1024;
 }
 
 int key_bucket(int nkeys) {

@@ -216,6 +216,7 @@ struct PassArgs {
     int n_layers;
     int T, room;              // rows; rows there is room for in the hand-over memory
     int die;                  // 1: on one die
+    int f32;                  // 1: of an fp32 model (on one die)
     int d, heads, I, F, act, cross;
     // embedding of y[len ..]; emb null: the rows are x_in[len ..]
     const void* emb;
@@ -237,8 +238,8 @@ struct PassArgs {
     unsigned* sync;           // [kPassSyncWords], zero before the pass; the policy kernel clears it
 };
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // workgroups, 0: not a shape it is made for
-int pass_die_groups(int d, int heads, int d_head, int F, bool gated);
-PassPlan pass_plan(int room, int d, int I, int F);
+int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32);
+PassPlan pass_plan(int room, int d, int I, int F, bool f32);
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st);
 
 struct EmbedArgs {

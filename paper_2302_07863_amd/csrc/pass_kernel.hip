@@ -1,4 +1,4 @@
-// One decoder pass of a narrow bf16 model in ONE kernel: embedding and all layers for up to 16 rows.
+// One decoder pass of a narrow model in ONE kernel: embedding and all layers for up to 16 rows (bf16; fp32 up to 256 wide, on one die).
 //
 // Such a pass is a chain of 45 (T5-small shape) to 171 (T5-large shape) dependent stages, each far too small to use the
 // chip for long.  As kernels of their own they cost 3.5 - 8 us each: 1.5 us of launch, a trip to memory for the activations and
@@ -30,9 +30,14 @@
 // then only goes to that die's L2 and back, at 1.25 TB/s for the weights instead of the chip's 4.8, which a layer of 7 MB in 13 us
 // does not notice.  Workgroups of the other dies end at once.
 //
+// fp32 models keep fp32 everywhere: activations travel as they are, sixteen rows in a matrix-core operand, attention in blocks of sixteen
+// keys (a block's 64 fp32 products take 0.85 us of a wave's SIMD for 32 keys); one row's projections run on the vector ALU (multiply).
+//
 // Per pass, us, as separate kernels, with counters (and flags on one die) and now, 512 source tokens: T5-small shape one row 147, 97, 96;
 // mT5-small shape 206, 121, 117; T5-large shape 1, 2, 4, 8, 11, 16 rows 676, 785, 853, 986, -, 1211 / 623, 631, 624, 638, 702, 713 / 447,
-// 448, 456, 475, 570, 552; mT5-large shape 1 and 8 rows 726, 1045 / 644, 666 / 456, 477.
+// 448, 456, 475, 544, 552; mT5-large shape 1 and 8 rows 726, 1045 / 644, 666 / 443, 462.  fp32, 256 wide, 32 source tokens, as separate kernels
+// and now: 2 layers, one row 68, 40.5 (49.7 with the matrix cores for it, 43.5 with blocks of 32 keys); 4 layers, 1, 4, 11 rows 120, 145,
+// 154, 63, 74, 78.
 //
 // A workgroup that has polled `spins` times in vain flags the pass as failed and walks on without waiting again (nothing
 // handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
@@ -71,8 +76,13 @@ constexpr unsigned kNotThere = 0xFFFFFFFFu;  // (two NaNs of a kind no conversio
 constexpr int kRedBytes = kPassWaves * 6 * 1024;  // twice: a stage's sums are read while the next one's are written
 constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kSq = kQ + 16 * kQLd * 4, kSqBytes = kPassWaves * 16 * 4, kRel = kSq + 2 * kSqBytes;
 
-template <bool DIE>
+template <bool DIE, bool FP32, bool ONE_ROW>
 struct Walk {
+    static constexpr bool F32 = FP32;      // of an fp32 model
+    static constexpr bool ONE = ONE_ROW;   // ... and one row (see multiply)
+    static constexpr int KS = F32 ? 4 : 5;  // inputs of a weight tile, logarithm
+    static constexpr int ESZ = F32 ? 4 : 2;
+    static constexpr int BK = F32 ? 16 : 32;  // keys a wave takes at a time
     static constexpr int kIn = 16;  // reads of what may not be there yet: past the L1 (sc1)
     // what is handed over goes as far as all readers see it: to the die's L2 (the L1s write through), or past the L2s (sc0 sc1)
     static constexpr int kOut = DIE ? 0 : 17;
@@ -116,6 +126,14 @@ struct Walk {
     }
 };
 
+// fp32: sixteen inputs, component v of a lane group g is input 4 g + v (two sums, so that products do not wait for each other)
+__device__ __forceinline__ void products(f32x4& a, f32x4& b, const uint4& w, const uint4& x) {
+    a = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w.x), __uint_as_float(x.x), a, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w.y), __uint_as_float(x.y), b, 0, 0, 0);
+    a = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w.z), __uint_as_float(x.z), a, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w.w), __uint_as_float(x.w), b, 0, 0, 0);
+}
+
 // This wave's run of input tiles of a projection over tk tiles.
 struct Run {
     int k0, n;
@@ -141,7 +159,8 @@ __device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const
 
 // A tile of planes that a norm's projection reads has its producers' sums of squares behind it, [row][first, second sixteen
 // inputs] (an own line: a producer's part of a row lies where its planes' readers look anyway).
-__host__ __device__ __forceinline__ int tile_bytes(bool normed, int room) { return room * 128 + (normed ? 128 : 0); }
+// (fp32 models: tiles of sixteen inputs, a producer each, [four inputs][row] and one sum per row)
+__host__ __device__ __forceinline__ int tile_bytes(bool normed, int room, bool f32) { return f32 ? room * 64 + (normed ? 64 : 0) : room * 128 + (normed ? 128 : 0); }
 // 1/rms of this lane's row, behind leave()
 template <class Walk>
 __device__ __forceinline__ float norm_factor(const Walk& c, int d, float eps) {
@@ -160,13 +179,15 @@ __device__ __forceinline__ float norm_factor(const Walk& c, int d, float eps) {
 // the loads and products (a compute unit's 64 bytes a cycle are what the FFN output's 256 loads of 1 KiB wait for); the halves
 // are added in total().  A quarter then has the rows' high parts and their low parts.
 // NORM: the rows' sums of squares as well, to c.ss.
+// One row of an fp32 model (Walk::ONE) has no use for the matrix cores, whose fp32 products of sixteen rows take eight times as long
+// as a lane's own four inputs: lane (feature, four inputs) sums those, leave() adds the four lanes of a feature.
 template <int N, int RW, bool PACK, bool NORM, class Walk>
 __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 (&W)[N * RW], const void* planes, int tk) {
     const Run r = run_of(c.wave, tk);
     const Rsrc xs = whole(planes);
-    const int S = tile_bytes(NORM, c.R);
+    const int S = tile_bytes(NORM, c.R, Walk::F32);
     const int at = (PACK ? (c.g * 2 + (c.tok >> 3)) * c.R + c.t8 : c.g * c.R + c.t) * 16, k0 = r.k0 * S;
-    constexpr int P = PACK ? 1 : 2, B = N * P <= 16 ? N : 4;  // tiles requested at once
+    constexpr int P = PACK || Walk::F32 ? 1 : 2, B = N * P <= 16 ? N : 4;  // tiles requested at once
     constexpr int IN = Walk::kIn;
     static_assert(N % B == 0 && (!NORM || N <= 4), "whole pieces; a lane group per tile");
     uint4 X[N > B ? 2 : 1][P * B];
@@ -182,8 +203,14 @@ __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 
                 for (int p = 0; p < P; ++p) x[P * j + p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at + p * c.R * 64, k0 + (j0 + j) * S, IN));
             }
         if constexpr (NORM) {  // (lane group g: tile g)
-            const v2u v = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, min(c.g, max(r.n - 1, 0)) * S + c.R * 128 + c.t * 8, r.n > 0 ? k0 : 0, IN));
-            sq = c.g < r.n ? v : v2u{0u, 0u};
+            const int tile = min(c.g, max(r.n - 1, 0)) * S, from = r.n > 0 ? k0 : 0;
+            if constexpr (Walk::F32) {
+                const unsigned v = __builtin_amdgcn_raw_buffer_load_b32(xs, tile + c.R * 64 + c.t * 4, from, IN);
+                sq = v2u{c.g < r.n ? v : 0u, 0u};
+            } else {
+                const v2u v = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, tile + c.R * 128 + c.t * 8, from, IN));
+                sq = c.g < r.n ? v : v2u{0u, 0u};
+            }
         }
     };
     // all of it again and again until every word is there
@@ -211,9 +238,21 @@ __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 
             if (j0 + j < r.n) {
 #pragma unroll
                 for (int q = 0; q < RW; ++q) {
+                    if constexpr (Walk::ONE) {
+                        const uint4 w = W[(j0 + j) * RW + q];
+                        acc[q][0] = __builtin_fmaf(__uint_as_float(w.x), __uint_as_float(x[j].x), acc[q][0]);
+                        acc[q][1] = __builtin_fmaf(__uint_as_float(w.y), __uint_as_float(x[j].y), acc[q][1]);
+                        acc[q][2] = __builtin_fmaf(__uint_as_float(w.z), __uint_as_float(x[j].z), acc[q][2]);
+                        acc[q][3] = __builtin_fmaf(__uint_as_float(w.w), __uint_as_float(x[j].w), acc[q][3]);
+                        continue;
+                    }
+                    if constexpr (Walk::F32) {
+                        products(acc[q], RW == 1 ? low[q] : acc[q], W[(j0 + j) * RW + q], x[j]);
+                        continue;
+                    }
                     acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j]), acc[q], 0, 0, 0);
                     f32x4& lo_acc = RW == 1 ? low[q] : acc[q];
-                    if (!PACK) lo_acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j + 1]), lo_acc, 0, 0, 0);
+                    if (!PACK) lo_acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j + P - 1]), lo_acc, 0, 0, 0);
                 }
             }
     };
@@ -236,7 +275,8 @@ __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 
 }
 
 // The waves' results side by side in LDS; `tile`'s total over the waves, in wave order.
-template <int RW, bool NORM, class Walk>
+// (ROW: multiply()'s sums of one row, [wave][tile][feature])
+template <int RW, bool NORM, bool ROW, class Walk>
 __device__ __forceinline__ void leave(Walk& c, const f32x4 (&acc)[RW]) {
     c.red = kRedBytes - c.red;
     if constexpr (NORM) {
@@ -244,14 +284,21 @@ __device__ __forceinline__ void leave(Walk& c, const f32x4 (&acc)[RW]) {
         if (c.g == 0) *(float*)(c.lds + kSq + c.sq + (c.wave * 16 + c.tok) * 4) = c.ss;
     }
 #pragma unroll
-    for (int q = 0; q < RW; ++q) *(f32x4*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
+    for (int q = 0; q < RW; ++q) {
+        if constexpr (ROW) {
+            const float s = quad_rows_sum((acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3]));
+            if (c.g == 0) *(float*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 16 + c.tok) * 4) = s;
+        } else {
+            *(f32x4*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
+        }
+    }
     lds_barrier();
 }
 template <int RW, bool PACK, class Walk>
 __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
     f32x4 p[kPassWaves];
 #pragma unroll
-    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const f32x4*)(c.lds + kRed + c.red + ((v * RW + tile) * 64 + c.lane) * 16);
+    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const f32x4*)(c.lds + kRed + c.red + (Walk::ONE ? ((v * RW + tile) * 16 + c.g * 4) * 4 : ((v * RW + tile) * 64 + c.lane) * 16));
     f32x4 s = p[0];
 #pragma unroll
     for (int v = 1; v < kPassWaves; ++v) s += p[v];
@@ -265,11 +312,18 @@ __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
 // Sixteen features of a row's activations in that order: this lane's four.
 template <bool PACK, bool NORM, class Walk>
 __device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, const float (&w)[4]) {
+    if constexpr (Walk::F32) {
+        const int off = (n0 >> 4) * tile_bytes(NORM, c.R, true) + (((n0 & 15) >> 2) * c.R + c.tok) * 16;
+        const v4u v = {__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
+        if (c.tok < c.T) __builtin_amdgcn_raw_buffer_store_b128(v, whole(planes), off, 0, Walk::kOut);
+        if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, whole((const char*)planes + c.clear), off, 0, Walk::kOut);
+        return;
+    }
     uint32_t h01, l01, h23, l23;
     split_bf16x2(w[0], w[1], h01, l01);
     split_bf16x2(w[2], w[3], h23, l23);
     const Rsrc r = whole(planes);
-    const int off = (n0 >> 5) * tile_bytes(NORM, c.R) + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.R + c.tok) * 16 + (n0 & 7) * 2;
+    const int off = (n0 >> 5) * tile_bytes(NORM, c.R, false) + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.R + c.tok) * 16 + (n0 & 7) * 2;
     const int lo = (PACK ? 16 : 64) * c.R;
     if (c.tok < c.T) {
         st8<Walk::kOut>(r, off, h01, h23);
@@ -295,20 +349,28 @@ template <bool CAUSAL, bool PACK, class Walk>
 struct Attend {
     const Rsrc kr, vr;
     const int I, cap, nkeys, nblk;  // (causal: the keys of earlier passes)
-    uint4 K0[2][2], K1[2][2], V0[4], V1[4];
+    static constexpr bool F32 = Walk::F32;
+    // blocks of sixteen or (bf16) twice sixteen keys; pieces of sixteen keys' rows and of a block's values
+    static constexpr int AB = F32 ? 1 : 2, BK = 16 * AB, KC = F32 ? 4 : 2, VC = 4;
+    uint4 K0[AB][KC], K1[AB][KC], V0[VC], V1[VC];
 
-    __device__ __forceinline__ void load(const Walk& c, uint4 (&Kr)[2][2], uint4 (&Vr)[4], int blk) const {
-        const int key0 = min(blk, nblk - 1) * 32;
+    __device__ __forceinline__ void load(const Walk& c, uint4 (&Kr)[AB][KC], uint4 (&Vr)[VC], int blk) const {
+        const int key0 = min(blk, nblk - 1) * BK;
+        constexpr int E = Walk::ESZ;
 #pragma unroll
-        for (int ab = 0; ab < 2; ++ab)
+        for (int ab = 0; ab < AB; ++ab)
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) Kr[ab][ks] = buf_load(kr, (unsigned)(((ab * 16 + c.tok) * I + c.g * 8) * 2), key0 * I * 2 + ks * 64);
+            for (int ks = 0; ks < KC; ++ks) Kr[ab][ks] = buf_load(kr, (unsigned)((ab * 16 + c.tok) * I * E + c.g * 16), key0 * I * E + ks * 64);
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) {
-            const int off = ((dt * 16 + c.tok) * cap + c.g * 4) * 2;
-            const uint2 va = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, off, key0 * 2, 0));
-            const uint2 vb = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, off + 32, key0 * 2, 0));
-            Vr[dt] = make_uint4(va.x, va.y, vb.x, vb.y);
+            const int off = ((dt * 16 + c.tok) * cap + c.g * 4) * E;
+            if constexpr (F32) {
+                Vr[dt] = buf_load(vr, (unsigned)off, key0 * E);
+            } else {
+                const uint2 va = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, off, key0 * 2, 0));
+                const uint2 vb = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, off + 32, key0 * 2, 0));
+                Vr[dt] = make_uint4(va.x, va.y, vb.x, vb.y);
+            }
         }
     }
     // Up to eight rows are packed as in multiply().  Causal: query, keys and values of this pass' rows are handed over in `fresh`,
@@ -316,6 +378,7 @@ struct Attend {
     __device__ __forceinline__ void run(Walk& c, const Fresh& fresh, float scale, int len, const float* relb, int rel_d, void* out, int h) {
         constexpr int P = PACK ? 1 : 2, IN = Walk::kIn;
         bf16x8 Q[2][P];  // scaled, high parts (columns 0 .. 7 if packed) and low parts
+        uint4 Qf[4];     // fp32: scaled, inputs c * 16 + g * 4 ..
         const bool low = c.tok >= 8;
         const int row = PACK ? c.t8 : c.t;
         // high and low parts of eight values in operand order
@@ -333,6 +396,14 @@ struct Attend {
         auto split_query = [&](const float4 (&qv)[2][2]) {
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
+                if constexpr (F32) {
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        const float4 q = qv[ks][p];
+                        Qf[ks * 2 + p] = make_uint4(__float_as_uint(q.x * scale), __float_as_uint(q.y * scale), __float_as_uint(q.z * scale), __float_as_uint(q.w * scale));
+                    }
+                    continue;
+                }
                 const float v[8] = {qv[ks][0].x * scale, qv[ks][0].y * scale, qv[ks][0].z * scale, qv[ks][0].w * scale,
                                     qv[ks][1].x * scale, qv[ks][1].y * scale, qv[ks][1].z * scale, qv[ks][1].w * scale};
                 parts(v, Q[ks]);
@@ -343,13 +414,21 @@ struct Attend {
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         // NB blocks at once, whose keys begin at `key`: one maximum, one rescaling; keys behind `lim` (of this lane's row) are not seen
-        auto process = [&](auto nb, const uint4 (*const (&Kr)[decltype(nb)::value])[2], const uint4* const (&Vr)[decltype(nb)::value], const int (&key)[decltype(nb)::value], bool edge, int lim, bool first) {
+        auto process = [&](auto nb, const uint4 (*const (&Kr)[decltype(nb)::value])[KC], const uint4* const (&Vr)[decltype(nb)::value], const int (&key)[decltype(nb)::value], bool edge, int lim, bool first) {
             constexpr int NB = decltype(nb)::value;
-            f32x4 s[NB][2];
+            f32x4 s[NB][AB];
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
-                for (int ab = 0; ab < 2; ++ab) s[b][ab] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int ab = 0; ab < AB; ++ab) s[b][ab] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (F32) {
+#pragma unroll
+                for (int ks = 0; ks < KC; ++ks)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+#pragma unroll
+                        for (int ab = 0; ab < AB; ++ab) products(s[b][ab], s[b][ab], Kr[b][ab][ks], Qf[ks]);
+            } else
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -357,44 +436,49 @@ struct Attend {
 #pragma unroll
                     for (int b = 0; b < NB; ++b)
 #pragma unroll
-                        for (int ab = 0; ab < 2; ++ab) s[b][ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Kr[b][ab][ks]), Q[ks][p], s[b][ab], 0, 0, 0);
+                        for (int ab = 0; ab < AB; ++ab) s[b][ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(Kr[b][ab][ks]), Q[ks][p], s[b][ab], 0, 0, 0);
             if constexpr (PACK) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int v = 0; v < 8; ++v) s[b][v >> 2][v & 3] += dpp_f<0x128, 0xF>(0.f, s[b][v >> 2][v & 3]);
+                    for (int v = 0; v < 4 * AB; ++v) s[b][v >> 2][v & 3] += dpp_f<0x128, 0xF>(0.f, s[b][v >> 2][v & 3]);
             }
             if (CAUSAL && relb) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int v = 0; v < 8; ++v)
+                    for (int v = 0; v < 4 * AB; ++v)
                         s[b][v >> 2][v & 3] += relb[rel_d + max(-rel_d, min(rel_d, key[b] + (v >> 2) * 16 + c.g * 4 + (v & 3) - (len + row)))];
             }
             if (edge) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int v = 0; v < 8; ++v)
+                    for (int v = 0; v < 4 * AB; ++v)
                         if (key[b] + (v >> 2) * 16 + c.g * 4 + (v & 3) > lim) s[b][v >> 2][v & 3] = -INFINITY;
             }
             float tmax = m_run;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
-                for (int v = 0; v < 8; ++v) tmax = fmaxf(tmax, s[b][v >> 2][v & 3]);
+                for (int v = 0; v < 4 * AB; ++v) tmax = fmaxf(tmax, s[b][v >> 2][v & 3]);
             const float m_new = quad_rows_max(tmax), base = m_new == -INFINITY ? 0.f : m_new;
             bf16x8 W[NB][P];
+            uint4 Wf[NB];
             float psum = 0.f;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                float p[8];
+                float p[8] = {};
 #pragma unroll
-                for (int v = 0; v < 8; ++v) {
+                for (int v = 0; v < 4 * AB; ++v) {
                     p[v] = fexp(s[b][v >> 2][v & 3] - base);
                     psum += p[v];
                 }
-                parts(p, W[b]);
+                if constexpr (F32) {
+                    Wf[b] = make_uint4(__float_as_uint(p[0]), __float_as_uint(p[1]), __float_as_uint(p[2]), __float_as_uint(p[3]));
+                } else {
+                    parts(p, W[b]);
+                }
             }
             psum = quad_rows_sum(psum);
             if (first) {
@@ -408,6 +492,10 @@ struct Attend {
             m_run = m_new;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
+                if constexpr (F32) {
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt) products(O[dt], O[dt], Vr[b][dt], Wf[b]);
+                } else
 #pragma unroll
                 for (int p = 0; p < P; ++p)
 #pragma unroll
@@ -419,7 +507,7 @@ struct Attend {
             const bool newest = c.wave == (nblk & (kPassWaves - 1));
             if (c.wave < nblk || newest) {
                 float4 qv[2][2], vn[4];
-                uint4 kn[2];
+                uint4 kn[KC];
                 int n = 0;
                 bool missing;
 #pragma unroll 1
@@ -428,14 +516,14 @@ struct Attend {
                     unsigned m = 0u;
                     auto see = [&](unsigned a, unsigned b, unsigned d, unsigned e) { m = max(max(m, max(a, b)), max(d, e)); };
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) qv[i >> 1][i & 1] = ldf4<IN>(fresh.q, row * 256 + (i >> 1) * 128 + c.g * 32 + (i & 1) * 16);
+                    for (int i = 0; i < 4; ++i) qv[i >> 1][i & 1] = ldf4<IN>(fresh.q, row * 256 + (F32 ? i * 64 + c.g * 16 : (i >> 1) * 128 + c.g * 32 + (i & 1) * 16));
                     if (newest) {
 #pragma unroll
-                        for (int ks = 0; ks < 2; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fresh.k, c.t * 128 + ks * 64 + c.g * 16, 0, IN));
+                        for (int ks = 0; ks < KC; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fresh.k, c.t * (64 * Walk::ESZ) + ks * 64 + c.g * 16, 0, IN));
 #pragma unroll
                         for (int dt = 0; dt < 4; ++dt) vn[dt] = ldf4<IN>(fresh.v, ((dt * 16 + c.tok) * fresh.room + min(c.g * 4, fresh.room - 4)) * 4);
 #pragma unroll
-                        for (int ks = 0; ks < 2; ++ks) see(kn[ks].x, kn[ks].y, kn[ks].z, kn[ks].w);
+                        for (int ks = 0; ks < KC; ++ks) see(kn[ks].x, kn[ks].y, kn[ks].z, kn[ks].w);
 #pragma unroll
                         for (int dt = 0; dt < 4; ++dt) see(__float_as_uint(vn[dt].x), __float_as_uint(vn[dt].y), __float_as_uint(vn[dt].z), __float_as_uint(vn[dt].w));
                     }
@@ -448,21 +536,26 @@ struct Attend {
                 } while (missing && ++n < c.spins);
                 if (missing) c.give_up();
                 split_query(qv);
-                if (c.wave < nblk) process(One{}, {K0}, {V0}, {c.wave * 32}, c.wave * 32 + 31 >= nkeys, nkeys - 1, true);
+                if (c.wave < nblk) process(One{}, {K0}, {V0}, {c.wave * BK}, c.wave * BK + BK - 1 >= nkeys, nkeys - 1, true);
                 for (int blk = c.wave + kPassWaves; blk < nblk; blk += kPassWaves) {
                     load(c, K0, V0, blk);
-                    process(One{}, {K0}, {V0}, {blk * 32}, blk * 32 + 31 >= nkeys, nkeys - 1, false);
+                    process(One{}, {K0}, {V0}, {blk * BK}, blk * BK + BK - 1 >= nkeys, nkeys - 1, false);
                 }
                 if (newest) {
 #pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) {
+                    for (int ks = 0; ks < KC; ++ks) {
                         K0[0][ks] = kn[ks];
-                        K0[1][ks] = make_uint4(0u, 0u, 0u, 0u);
+                        if constexpr (AB == 2) K0[AB - 1][ks] = make_uint4(0u, 0u, 0u, 0u);
                     }
 #pragma unroll
-                    for (int dt = 0; dt < 4; ++dt)  // (bf16 values in the upper halves)
-                        V0[dt] = make_uint4(__builtin_amdgcn_perm(__float_as_uint(vn[dt].y), __float_as_uint(vn[dt].x), 0x07060302u),
-                                            __builtin_amdgcn_perm(__float_as_uint(vn[dt].w), __float_as_uint(vn[dt].z), 0x07060302u), 0u, 0u);
+                    for (int dt = 0; dt < 4; ++dt) {
+                        const uint4 v = __builtin_bit_cast(uint4, vn[dt]);
+                        if constexpr (F32) {
+                            V0[dt] = v;
+                        } else {  // (bf16 values in the upper halves)
+                            V0[dt] = make_uint4(__builtin_amdgcn_perm(v.y, v.x, 0x07060302u), __builtin_amdgcn_perm(v.w, v.z, 0x07060302u), 0u, 0u);
+                        }
+                    }
                     process(One{}, {K0}, {V0}, {len}, true, len + row, c.wave >= nblk);
                 }
             }
@@ -470,14 +563,21 @@ struct Attend {
             const float* q = (const float*)(c.lds + kQ);
             float4 qv[2][2];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) qv[i >> 1][i & 1] = *(const float4*)(q + row * kQLd + (i >> 1) * 32 + c.g * 8 + (i & 1) * 4);
+            for (int i = 0; i < 4; ++i) qv[i >> 1][i & 1] = *(const float4*)(q + row * kQLd + (F32 ? i * 16 + c.g * 4 : (i >> 1) * 32 + c.g * 8 + (i & 1) * 4));
             split_query(qv);
-            for (int blk = c.wave; blk < nblk; blk += 2 * kPassWaves) {
-                const bool first = blk == c.wave;
-                if (blk + kPassWaves < nblk) process(Two{}, {K0, K1}, {V0, V1}, {blk * 32, (blk + kPassWaves) * 32}, (blk + kPassWaves) * 32 + 31 >= nkeys, nkeys - 1, first);
-                else process(One{}, {K0}, {V0}, {blk * 32}, blk * 32 + 31 >= nkeys, nkeys - 1, first);
-                if (blk + 2 * kPassWaves < nblk) load(c, K0, V0, blk + 2 * kPassWaves);
-                if (blk + 3 * kPassWaves < nblk) load(c, K1, V1, blk + 3 * kPassWaves);
+            if constexpr (F32) {  // (one set of registers)
+                for (int blk = c.wave; blk < nblk; blk += kPassWaves) {
+                    process(One{}, {K0}, {V0}, {blk * BK}, blk * BK + BK - 1 >= nkeys, nkeys - 1, blk == c.wave);
+                    if (blk + kPassWaves < nblk) load(c, K0, V0, blk + kPassWaves);
+                }
+            } else {
+                for (int blk = c.wave; blk < nblk; blk += 2 * kPassWaves) {
+                    const bool first = blk == c.wave;
+                    if (blk + kPassWaves < nblk) process(Two{}, {K0, K1}, {V0, V1}, {blk * BK, (blk + kPassWaves) * BK}, (blk + kPassWaves) * BK + BK - 1 >= nkeys, nkeys - 1, first);
+                    else process(One{}, {K0}, {V0}, {blk * BK}, blk * BK + BK - 1 >= nkeys, nkeys - 1, first);
+                    if (blk + 2 * kPassWaves < nblk) load(c, K0, V0, blk + 2 * kPassWaves);
+                    if (blk + 3 * kPassWaves < nblk) load(c, K1, V1, blk + 3 * kPassWaves);
+                }
             }
         }
         float* cm = (float*)(c.lds + kMl);
@@ -486,7 +586,7 @@ struct Attend {
             cm[c.wave * 16 + c.tok] = m_run;
             cl[c.wave * 16 + c.tok] = l_run;
         }
-        leave<4, false>(c, O);
+        leave<4, false, false>(c, O);
         if (c.wave < 4) {
             // (all of it read at once and without a test: a wave without keys has left a maximum of minus infinity and zeros)
             float w[kPassWaves], l[kPassWaves], M = -INFINITY, L = 0.f;
@@ -524,6 +624,9 @@ struct ChipCut {
 struct DieCut {
     static constexpr int QT = 4, OT = 2, FT = 6, KD = 2, KF = 8;
 };
+struct DieCutF32 {
+    static constexpr int QT = 2, OT = 1, FT = 4, KD = 2, KF = 8;
+};
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Workgroups [0, workers) do the projections; the first of them own sixteen features (OT times) of the residual stream each: wave
@@ -554,7 +657,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
             put_planes<PACK, true>(c, planes, n0(), w);
             if (c.g == 0) {
-                const int off = (n0() >> 5) * tile_bytes(true, c.R) + c.R * 128 + (c.tok * 2 + ((n0() >> 4) & 1)) * 4;
+                const int off = Walk::F32 ? (n0() >> 4) * tile_bytes(true, c.R, true) + c.R * 64 + c.tok * 4
+                                          : (n0() >> 5) * tile_bytes(true, c.R, false) + c.R * 128 + (c.tok * 2 + ((n0() >> 4) & 1)) * 4;
                 if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(planes), off, 0, Walk::kOut);
                 if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, whole(planes + c.clear), off, 0, Walk::kOut);
             }
@@ -573,20 +677,25 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             if (a.emb) {
                 int er = a.tokens[pos] + a.tie_shift;
                 er = er >= a.vocab ? er - a.vocab : er;
-                const char* p = (const char*)a.emb + ((size_t)(er >> 4) * (d >> 5) + (n0() >> 5)) * kTileBytes + ((er & 15) + 16 * ((n0() & 31) >> 3)) * 16 + (n0() & 7) * 2;
-                const uint2 raw = *(const uint2*)p;
+                const char* p = (const char*)a.emb + ((size_t)(er >> 4) * (d >> c.KS) + (n0() >> c.KS)) * kTileBytes;
+                float4 e;
+                if constexpr (Walk::F32) {
+                    e = *(const float4*)(p + ((er & 15) + 16 * ((n0() & 15) >> 2)) * 16);
+                } else {
+                    const uint2 raw = *(const uint2*)(p + ((er & 15) + 16 * ((n0() & 31) >> 3)) * 16 + (n0() & 7) * 2);
+                    e = make_float4(bf2f(raw.x & 0xFFFFu), bf2f(raw.x >> 16), bf2f(raw.y & 0xFFFFu), bf2f(raw.y >> 16));
+                }
                 float4 pe = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (a.pe) pe = *(const float4*)(a.pe + (size_t)pos * d + n0());
                 const float sc = a.embed_scale;
-                x = make_float4(__builtin_fmaf(bf2f(raw.x & 0xFFFFu), sc, pe.x), __builtin_fmaf(bf2f(raw.x >> 16), sc, pe.y),
-                                __builtin_fmaf(bf2f(raw.y & 0xFFFFu), sc, pe.z), __builtin_fmaf(bf2f(raw.y >> 16), sc, pe.w));
+                x = make_float4(__builtin_fmaf(e.x, sc, pe.x), __builtin_fmaf(e.y, sc, pe.y), __builtin_fmaf(e.z, sc, pe.z), __builtin_fmaf(e.w, sc, pe.w));
             } else {
                 x = *(const float4*)(a.x_in + (size_t)pos * d + n0());
             }
         }
         publish(gn, z + a.at.x1);
     }
-    if (qkv) request<KD, QT>(c, Wq, L->wqkv, c.wg, d >> 5, tq());
+    if (qkv) request<KD, QT>(c, Wq, L->wqkv, c.wg, d >> c.KS, tq());
     for (int l = 0; l < a.n_layers; ++l) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         const bool last = l + 1 == a.n_layers;
@@ -602,8 +711,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             char* out = pinned(z + (seg == 0 ? a.at.q : seg == 1 ? a.at.k : a.at.v));
             f32x4 acc[QT];
             c.template nap<350>();
-            multiply<KD, QT, PACK, true>(c, acc, Wq, xs, d >> 5);
-            leave<QT, true>(c, acc);
+            multiply<KD, QT, PACK, true>(c, acc, Wq, xs, d >> c.KS);
+            leave<QT, true, Walk::ONE>(c, acc);
             if (c.wave < QT) {
                 const float f = norm_factor(c, d, a.eps);
                 const f32x4 s = total<QT, PACK>(c, c.wave) * f;
@@ -614,6 +723,14 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                     const int off = ((hd * c.R + c.tok) * 64 + f0) * 4;
                     const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
                     if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b128(v, o, off, 0, Walk::kOut);
+                    if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, n, off, 0, Walk::kOut);
+                } else if (Walk::F32 && seg == 1) {
+                    const int off = ((hd * c.R + c.tok) * 64 + f0) * 4;
+                    const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
+                    if (c.tok < T) {
+                        __builtin_amdgcn_raw_buffer_store_b128(v, o, off, 0, Walk::kOut);
+                        __builtin_amdgcn_raw_buffer_store_b128(v, kv, (pos * I + nn) * 4, 0, Walk::kOut);
+                    }
                     if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, n, off, 0, Walk::kOut);
                 } else if (seg == 1) {
                     const int off = ((hd * c.R + c.tok) * 64 + f0) * 2;
@@ -627,9 +744,12 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                     const int room = fresh_room(c.R), off = ((hd * 64 + f0) * room + c.tok) * 4;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const unsigned b = f2bf(s[v]);
-                        if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(c.tok < T ? b << 16 : 0u, o, off + v * room * 4, 0, Walk::kOut);
-                        if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, kv, ((nn + v) * a.vcap + pos) * 2, 0, Walk::kOut);
+                        const unsigned b = Walk::F32 ? __float_as_uint(s[v]) : f2bf(s[v]);
+                        if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(c.tok < T ? (Walk::F32 ? b : b << 16) : 0u, o, off + v * room * 4, 0, Walk::kOut);
+                        if (c.tok < T) {
+                            if constexpr (Walk::F32) __builtin_amdgcn_raw_buffer_store_b32(b, kv, ((nn + v) * a.vcap + pos) * 4, 0, Walk::kOut);
+                            else __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, kv, ((nn + v) * a.vcap + pos) * 2, 0, Walk::kOut);
+                        }
                         if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, n, off + v * room * 4, 0, Walk::kOut);
                     }
                 }
@@ -639,17 +759,17 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         // Requests go out where the workgroup has several microseconds before it is needed again (a wave's loads come back in
         // order: what is asked for late delays the next stage's activations): here, while the heads work, and below.
         if (owner) {
-            request<KD, OT>(c, Wo, L->wo, c.wg, I >> 5, nd());
+            request<KD, OT>(c, Wo, L->wo, c.wg, I >> c.KS, nd());
             const float4 gn = gain(a.cross ? L->lnc : L->ln2);
             if (!a.cross) {
                 next_gain = gain(last ? L->ln2 : L[1].ln1);
-                request<KF, OT>(c, Wf, L->wout, c.wg, F >> 5, nd());
+                request<KF, OT>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
             }
             const char* xs = pinned(z + a.at.a1);
             char* ox = pinned(z + a.at.x2);
             f32x4 acc[OT];
-            multiply<KD, OT, PACK, false>(c, acc, Wo, xs, I >> 5);
-            leave<OT, false>(c, acc);
+            multiply<KD, OT, PACK, false>(c, acc, Wo, xs, I >> c.KS);
+            leave<OT, false, Walk::ONE>(c, acc);
             if (mine) add();
             publish(gn, ox);
         }
@@ -657,17 +777,17 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         if (a.cross) {
             // ---- output projection of the cross-attention ----
             if (owner) {
-                request<KD, OT>(c, Wo, L->cwo, c.wg, I >> 5, nd());
+                request<KD, OT>(c, Wo, L->cwo, c.wg, I >> c.KS, nd());
                 const float4 gn = gain(L->ln2);
                 next_gain = gain(last ? L->ln2 : L[1].ln1);
-                if (ffn) request<KD, FT>(c, Wi, L->win, c.wg, d >> 5, tf());
-                request<KF, OT>(c, Wf, L->wout, c.wg, F >> 5, nd());
-                if (qkv && !last) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> 5, tq());
+                if (ffn) request<KD, FT>(c, Wi, L->win, c.wg, d >> c.KS, tf());
+                request<KF, OT>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
+                if (qkv && !last) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> c.KS, tq());
                 const char* xs = pinned(z + a.at.a2);
                 char* ox = pinned(z + a.at.x3);
                 f32x4 acc[OT];
-                multiply<KD, OT, PACK, false>(c, acc, Wo, xs, I >> 5);
-                leave<OT, false>(c, acc);
+                multiply<KD, OT, PACK, false>(c, acc, Wo, xs, I >> c.KS);
+                leave<OT, false, Walk::ONE>(c, acc);
                 if (mine) add();
                 publish(gn, ox);
             }
@@ -675,14 +795,14 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         }
         // ---- FFN ----
         if (ffn) {
-            if (!owner || !a.cross) request<KD, FT>(c, Wi, L->win, c.wg, d >> 5, tf());
+            if (!owner || !a.cross) request<KD, FT>(c, Wi, L->win, c.wg, d >> c.KS, tf());
             const char* xs = pinned(xf);
             char* out = pinned(z + a.at.h);
             constexpr int FW = GATED ? FT / 2 : FT;  // waves with results
             f32x4 acc[FT];
             c.template nap<350>();
-            multiply<KD, FT, PACK, true>(c, acc, Wi, xs, d >> 5);
-            leave<FT, true>(c, acc);
+            multiply<KD, FT, PACK, true>(c, acc, Wi, xs, d >> c.KS);
+            leave<FT, true, Walk::ONE>(c, acc);
             const int tile = c.wg * FW + c.wave;  // of the hidden state
             if (c.wave < FW && tile < F >> 4) {
                 const float r = norm_factor(c, d, a.eps);
@@ -699,7 +819,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 put_planes<PACK, false>(c, out, tile * 16 + c.g * 4, w);
             }
         }
-        if (qkv && !last && (!owner || !a.cross)) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> 5, tq());
+        if (qkv && !last && (!owner || !a.cross)) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> c.KS, tq());
         const char* hidden = z + a.at.h;
         z = c.next(z, a.at.layer);
         c.walk_on(a.at.layer);
@@ -708,8 +828,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             char* ox = pinned(z + a.at.x1);
             f32x4 acc[OT];
             c.template nap<650>();
-            multiply<KF, OT, PACK, false>(c, acc, Wf, xs, F >> 5);
-            leave<OT, false>(c, acc);
+            multiply<KF, OT, PACK, false>(c, acc, Wf, xs, F >> c.KS);
+            leave<OT, false, Walk::ONE>(c, acc);
             if (mine) add();
             if (!last) publish(next_gain, ox);
         }
@@ -737,23 +857,23 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
     uint4 Wc[KD * 4];  // of the cross query
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
     char* z = c.scratch(a);
-    if (a.cross) request<KD, 4>(c, Wc, L->cwq, h, d >> 5, I >> 4);
+    if (a.cross) request<KD, 4>(c, Wc, L->cwq, h, d >> c.KS, I >> 4);
     for (int l = 0; l < a.n_layers; ++l, z = c.next(z, a.at.layer), c.walk_on(a.at.layer)) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         asm volatile("" : "+v"(c.lane));
         asm volatile("" : "+s"(T), "+s"(d), "+s"(I));
         c.place(T, a.room);
-        Attend<true, PACK, Walk> self = {whole(L->kc + (size_t)h * 128), whole(L->vc + (size_t)h * 64 * a.vcap * 2), I, a.vcap, len, (len + 31) >> 5, {}, {}, {}, {}};
+        Attend<true, PACK, Walk> self = {whole(L->kc + (size_t)h * 64 * c.ESZ), whole(L->vc + (size_t)h * 64 * a.vcap * c.ESZ), I, a.vcap, len, (len + Walk::BK - 1) / Walk::BK, {}, {}, {}, {}};
         if (c.wave < self.nblk) self.load(c, self.K0, self.V0, c.wave);
         // the cross-attention's keys and values while the heads have nothing else to do
-        Attend<false, PACK, Walk> cross = {whole(L->ck + (size_t)h * 128), whole(L->cv + (size_t)h * 64 * a.scap * 2), I, a.scap, nsrc, (nsrc + 31) >> 5, {}, {}, {}, {}};
+        Attend<false, PACK, Walk> cross = {whole(L->ck + (size_t)h * 64 * c.ESZ), whole(L->cv + (size_t)h * 64 * a.scap * c.ESZ), I, a.scap, nsrc, (nsrc + Walk::BK - 1) / Walk::BK, {}, {}, {}, {}};
         if (a.cross) {
             cross.load(c, cross.K0, cross.V0, c.wave);
-            if (cross.nblk > kPassWaves) cross.load(c, cross.K1, cross.V1, c.wave + kPassWaves);
+            if (!Walk::F32 && cross.nblk > kPassWaves) cross.load(c, cross.K1, cross.V1, c.wave + kPassWaves);
         }
         {
             const int room = fresh_room(c.R);
-            const Fresh fresh = {whole(pinned(z + a.at.q + h * c.R * 256)), whole(pinned(z + a.at.k + h * c.R * 128)), whole(pinned(z + a.at.v + h * room * 256)), room};
+            const Fresh fresh = {whole(pinned(z + a.at.q + h * c.R * 256)), whole(pinned(z + a.at.k + h * c.R * 64 * c.ESZ)), whole(pinned(z + a.at.v + h * room * 256)), room};
             char* out = pinned(z + a.at.a1);
             const float sc = a.att_scale;
             self.run(c, fresh, sc, len, relb, a.rel_d, out, h);
@@ -764,24 +884,24 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
             char* out = pinned(z + a.at.a2);
             const float sc = a.att_scale;
             f32x4 acc[4];
-            multiply<KD, 4, PACK, true>(c, acc, Wc, xs, d >> 5);
-            leave<4, true>(c, acc);
+            multiply<KD, 4, PACK, true>(c, acc, Wc, xs, d >> c.KS);
+            leave<4, true, Walk::ONE>(c, acc);
             if (c.wave < 4) {
                 const f32x4 s = total<4, PACK>(c, c.wave) * norm_factor(c, d, a.eps);
                 *(f32x4*)((float*)(c.lds + kQ) + c.tok * kQLd + c.wave * 16 + c.g * 4) = s;
             }
             lds_barrier();
             cross.run(c, Fresh{}, sc, len, nullptr, 0, out, h);
-            if (l + 1 < a.n_layers) request<KD, 4>(c, Wc, L[1].cwq, h, d >> 5, I >> 4);
+            if (l + 1 < a.n_layers) request<KD, 4>(c, Wc, L[1].cwq, h, d >> c.KS, I >> 4);
         }
     }
 }
 
-template <bool GATED, bool PACK, bool DIE>
+template <bool GATED, bool PACK, bool DIE, bool F32, bool ONE>
 __global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    using Cut = std::conditional_t<DIE, DieCut, ChipCut>;
-    Walk<DIE> c;
+    using Cut = std::conditional_t<F32, DieCutF32, std::conditional_t<DIE, DieCut, ChipCut>>;
+    Walk<DIE, F32, ONE> c;
     c.lds = smem;
     c.failed = a.sync + kPassSyncWords - 1;
     c.spins = a.spins;
@@ -811,25 +931,25 @@ static int cut_groups(int d, int heads, int F, bool gated) {
     return std::max(std::max(ceil_div(3 * heads * 4, Cut::QT), ceil_div(gated ? F / 8 : F / 16, Cut::FT)), ceil_div(d / 16, Cut::OT)) + heads;
 }
 template <class Cut>
-static bool cut_fits(int d, int I, int F) {
-    return ceil_div(std::max(d, I) / 32, kPassWaves) <= Cut::KD && ceil_div(F / 32, kPassWaves) <= Cut::KF;
+static bool cut_fits(int d, int I, int F, int inputs) {
+    return ceil_div(std::max(d, I) / inputs, kPassWaves) <= Cut::KD && ceil_div(F / inputs, kPassWaves) <= Cut::KF;
 }
 
 // Sizes the kernel is made for: runs of inputs that fit the registers, the workgroups on the chip at once.  Wider models are bound
 // by the weights' bandwidth, not by the hand-overs.
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
-    if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<ChipCut>(d, heads * 64, F)) return 0;
+    if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<ChipCut>(d, heads * 64, F, 32)) return 0;
     const int g = cut_groups<ChipCut>(d, heads, F, gated);
     return g <= cus ? g : 0;
 }
 // ... and of the form on one die: all of it on the 32 compute units of one.
-int pass_die_groups(int d, int heads, int d_head, int F, bool gated) {
-    if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<DieCut>(d, heads * 64, F)) return 0;
-    const int g = cut_groups<DieCut>(d, heads, F, gated);
+int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32) {
+    if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !(f32 ? cut_fits<DieCutF32>(d, heads * 64, F, 16) : cut_fits<DieCut>(d, heads * 64, F, 32))) return 0;
+    const int g = f32 ? cut_groups<DieCutF32>(d, heads, F, gated) : cut_groups<DieCut>(d, heads, F, gated);
     return g <= 32 ? g : 0;
 }
 
-PassPlan pass_plan(int room, int d, int I, int F) {
+PassPlan pass_plan(int room, int d, int I, int F, bool f32) {
     PassPlan p;
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -837,19 +957,22 @@ PassPlan pass_plan(int room, int d, int I, int F) {
         at += (bytes + 255) / 256 * 256;
         return (int)r;
     };
-    const size_t x = (size_t)(d / 32) * tile_bytes(true, room), i = (size_t)(I / 32) * tile_bytes(false, room);
-    p.x1 = take(x); p.q = take((size_t)room * I * 4); p.k = take((size_t)room * I * 2); p.v = take((size_t)fresh_room(room) * I * 4);
+    const int inputs = f32 ? 16 : 32;
+    const size_t x = (size_t)(d / inputs) * tile_bytes(true, room, f32), i = (size_t)(I / inputs) * tile_bytes(false, room, f32);
+    p.x1 = take(x); p.q = take((size_t)room * I * 4); p.k = take((size_t)room * I * (f32 ? 4 : 2)); p.v = take((size_t)fresh_room(room) * I * 4);
     p.a1 = take(i); p.x2 = take(x); p.a2 = take(i); p.x3 = take(x);
-    p.h = take((size_t)(F / 32) * tile_bytes(false, room));
+    p.h = take((size_t)(F / inputs) * tile_bytes(false, room, f32));
     p.layer = (int)at;
     return p;
 }
 
 hipError_t pass_init() {
     static hipError_t done = [] {
-        const void* fns[] = {(const void*)pass_kernel<false, true, true>, (const void*)pass_kernel<true, true, true>,
-                             (const void*)pass_kernel<false, true, false>, (const void*)pass_kernel<true, true, false>,
-                             (const void*)pass_kernel<false, false, false>, (const void*)pass_kernel<true, false, false>};
+        const void* fns[] = {(const void*)pass_kernel<false, true, true, false, false>, (const void*)pass_kernel<true, true, true, false, false>,
+                             (const void*)pass_kernel<false, true, false, false, false>, (const void*)pass_kernel<true, true, false, false, false>,
+                             (const void*)pass_kernel<false, false, false, false, false>, (const void*)pass_kernel<true, false, false, false, false>,
+                             (const void*)pass_kernel<false, false, true, true, false>, (const void*)pass_kernel<true, false, true, true, false>,
+                             (const void*)pass_kernel<false, false, true, true, true>, (const void*)pass_kernel<true, false, true, true, true>};
         return raise_lds_limit(fns, 160 * 1024);
     }();
     return done;
@@ -857,25 +980,27 @@ hipError_t pass_init() {
 
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
     if (hipError_t e = pass_init(); e != hipSuccess) return e;
-    if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > kPassRows || a.room < a.T || (a.die && a.T > kPassDieRows) || !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
+    if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > kPassRows || a.room < a.T || (a.die && !a.f32 && a.T > kPassDieRows) || (a.f32 && !a.die) || !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
         (a.cross && !a.nsrc_ptr))
         return hipErrorInvalidValue;
     const size_t smem = kRel + (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);
     if (smem > 160 * 1024) return hipErrorInvalidValue;
     const bool gated = a.act != BILD_ACT_RELU;
-#define BILD_P(GV, PV, DV)                                                                                                   \
+#define BILD_P(GV, PV, DV, FV, OV)                                                                                                   \
     do {                                                                                                                     \
-        hipLaunchKernelGGL((pass_kernel<GV, PV, DV>), dim3(grid), dim3(kPassThreads), smem, st, a);                          \
+        hipLaunchKernelGGL((pass_kernel<GV, PV, DV, FV, OV>), dim3(grid), dim3(kPassThreads), smem, st, a);                          \
         return hipGetLastError();                                                                                            \
     } while (0)
-#define BILD_PG(PV, DV)                                                                                                      \
+#define BILD_PG(PV, DV, FV, OV)                                                                                                      \
     do {                                                                                                                     \
-        if (gated) BILD_P(true, PV, DV);                                                                                     \
-        BILD_P(false, PV, DV);                                                                                               \
+        if (gated) BILD_P(true, PV, DV, FV, OV);                                                                                     \
+        BILD_P(false, PV, DV, FV, OV);                                                                                               \
     } while (0)
-    if (a.die) BILD_PG(true, true);
-    if (a.T <= 8) BILD_PG(true, false);
-    BILD_PG(false, false);
+    if (a.f32 && a.T == 1) BILD_PG(false, true, true, true);
+    if (a.f32) BILD_PG(false, true, true, false);
+    if (a.die) BILD_PG(true, true, false, false);
+    if (a.T <= 8) BILD_PG(true, false, false, false);
+    BILD_PG(false, false, false, false);
 #undef BILD_PG
 #undef BILD_P
 }

@@ -152,3 +152,49 @@ def test_the_forms_of_a_pass_agree(shape, monkeypatch):
         worst = float(np.abs(got[a] - got[b]).max())
         print(a, b, worst)
         assert worst <= tol
+
+
+F32 = dict(dtype=bi.DT_F32, truncate=False, d=256, heads=4, d_head=64, n_src=20)
+
+
+@pytest.mark.parametrize("shape", [
+    dict(d_ff=1024), dict(d_ff=32, heads=1), dict(d_ff=480, heads=3, act=bi.ACT_GATED_GELU),
+    dict(d_ff=512, cross=False), dict(d_ff=256, act=bi.ACT_SWIGLU, pos=bi.POS_RELATIVE, n_src=300), dict(d_ff=512, n_src=33, tied=False)])
+def test_fp32_models_on_one_die(shape):
+    """Against the oracle, teacher-forced, and the route: rows of 1 .. 16 and keys past a block and past eight."""
+    cfg = bi.toy_pair(**{**F32, "max_new": 700, **shape})
+    R = Rig(cfg)
+    ref = oracle.bild_generate(R.req, 0.4, 1.0, 15, 24, keep_logits=True)
+    st = R.state(cfg.max_new, 15)
+    st.encode(R.src)
+    parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, cfg)
+    r = st.pass_routes()
+    assert r["die"] > 0 and r["chip"] == r["kernels"] == r["gave_up"] == 0
+
+
+@pytest.mark.parametrize("shape", [dict(d_ff=1024), dict(d_ff=256, act=bi.ACT_SWIGLU, pos=bi.POS_RELATIVE)])
+def test_fp32_blocks_of_earlier_keys(shape, monkeypatch):
+    """One die against the separate kernels (each is within logit_tol of the exact value)."""
+    cfg = bi.toy_pair(**{**F32, "max_new": 700, **shape})
+    R = Rig(cfg)
+    got = {}
+    for form in ("die", "kernels"):
+        with monkeypatch.context() as m:
+            for k, v in FORMS[form].items():
+                m.setenv(k, v)
+            st = R.state(cfg.max_new, 15)
+        st.encode(R.src)
+        st.debug_enable_logits(True)
+        logits = []
+        for have in (1, 32, 33, 225, 257, 600):
+            st.seq_truncate(R.n0)
+            st.force_tokens(R.n0, bi.make_tokens(cfg.large.vocab, have - R.n0, seed=have), have)
+            st.large_verify(float("inf"), draft=[])
+            for rows in (1, 3, 8, 16):
+                st.seq_truncate(have)
+                before = st.pass_routes()
+                st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+                assert {k for k, v in st.pass_routes().items() if v > before[k]} == {form}, (have, rows)
+                logits += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+        got[form] = np.stack(logits)
+    assert float(np.abs(got["die"] - got["kernels"]).max()) <= 2 * parity.logit_tol(cfg)
