@@ -22,6 +22,7 @@ UNITS = [
     ("gemm_tile.hip", "gemm_tile.o", []),
     ("gemm_thin.hip", "gemm_thin.o", []),
     ("pass_kernel.hip", "pass_kernel.o", []),
+    ("pass_wide.hip", "pass_wide.o", []),
     ("attn_tile.hip", "attn_tile.o", []),
     ("attn_split.hip", "attn_split.o", []),
     ("attention.hip", "attention.o", []),

@@ -53,7 +53,7 @@ bool config_ok(const bild_model_config& c) {
 
 // what the workgroups of a pass in one kernel hand over: three layers' memory
 size_t pass_turns_bytes(const ModelState& M, int room) {
-    return 3 * (size_t)pass_plan(1 << room, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff, M.m->cfg.dtype == BILD_DT_F32).layer;
+    return 3 * (size_t)pass_plan(1 << room, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff, M.m->cfg.dtype == BILD_DT_F32, M.pass_wide).layer;
 }
 
 // captured passes carry some of the state's settings by value: where one changes they are captured anew
@@ -443,6 +443,14 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
                 for (int r = 0; r < kPassRooms; ++r) want(M.pass_turns[r], pass_turns_bytes(M, r));
             }
         }
+        if (s->one_kernel && bf16 && !m->cfg.cross_attn && m->cfg.pos != BILD_POS_RELATIVE && !M.pass_groups) {
+            M.pass_groups = wide_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus);
+            if (M.pass_groups) {
+                M.pass_wide = true;
+                want(M.pass_layers, sizeof(PassLayer) * L);
+                for (int r = 0; r <= pass_room_index(kWideRows); ++r) want(M.pass_turns[r], pass_turns_bytes(M, r));
+            }
+        }
         M.nparts_cap = m->head.tn + 1;  // at most one partial per feature tile
         want(M.part, sizeof(StatPart) * (size_t)M.nparts_cap * kMaxRows);
         want(M.zt, sizeof(float) * kMaxRows);
@@ -494,7 +502,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         ModelState& M = s->ms[w];
         if (!M.pass_groups) continue;
         for (int r = 0; r < kPassRooms && e == hipSuccess; ++r)
-            e = hipMemsetAsync(M.pass_turns[r], 0xFF, pass_turns_bytes(M, r), s->stream);
+            if (M.pass_turns[r]) e = hipMemsetAsync(M.pass_turns[r], 0xFF, pass_turns_bytes(M, r), s->stream);
         if (e != hipSuccess) break;
         const size_t kv = (size_t)s->cap_len * M.m->inner() * M.m->esz(), ckv = (size_t)s->cap_src * M.m->inner() * M.m->esz();
         for (size_t l = 0; l < M.m->dec.size(); ++l) {
@@ -1406,14 +1414,16 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         p.die = die;
         p.room = 1 << pass_room_index(T);
         p.f32 = dt == BILD_DT_F32;
-        p.at = pass_plan(p.room, d, p.I, p.F, p.f32);
+        p.at = pass_plan(p.room, d, p.I, p.F, p.f32, M.pass_wide);
         p.turn = pass_turn(s, w, T);
         p.scratch = M.pass_turns[pass_room_index(T)];
         p.sync = s->pass_sync;
         p.spins = s->pass_spins;
         s->stage_count += 1;
         p.groups = die ? M.pass_die_groups : M.pass_groups;
-        HIPC(launch_pass(p, die ? s->cus : p.groups, s->stream));
+        p.wide = M.pass_wide;
+        p.rope = M.rope;
+        HIPC(M.pass_wide ? launch_wide(p, s->stream) : launch_pass(p, die ? s->cus : p.groups, s->stream));
     } else if (takes_thin(s, w, T)) {
         const int rc = emit_thin(s, w, T, key_hint, lm_rows > 0, &thin_parts);
         if (rc) return rc;
@@ -1554,8 +1564,14 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // Sequence.  Its keys past the first 256 are not asked for ahead.  At 256, 512, 1024 positions: T5-large shape one row 708 / 478,
 // 713 / 522, 746 / 639; eight 1053 / 526, 1091 / 575, 1125 / 688; T5-small shape on one die 158 / 105, 160 / 113, 167 / 134; no shape and
 // row count loses before the 1024 that were measured.
+//
+// Wide models (pass_wide.hip), rows 1, 2, 4, 8, separate kernels / one, 6 layers: 1280 wide at 40 positions 161, 193, 206, 230 / 123, 124,
+// 128, 137, at 8100 258, 271, 279, 298 / 227, 228, 234, 243; 2048 wide 228, 265, 285, 284 / 174, 176, 182, 196 and 338, 342, 357, 384 / 291, 295,
+// 303, 316; 3072 wide 374, 402, 445, 383 / 318, 309, 320, 341 and 546, 556, 598, 539 / 476, 479, 488, 509; 4096 wide 534, 575, 577, 580 /
+// 476, 467, 475, 495 and 743, 762, 762, 766 / 655, 660, 668, 686: never slower up to the 8192 positions that were measured.
 static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
+    if (s->ms[w].pass_wide) return s->one_kernel && T <= kWideRows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= 8192;
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
            s->n_src <= (s->ms[w].m->cfg.dtype == BILD_DT_F32 ? 1024 : on_one_die(s, w, T) ? 1280 : T == 1 ? 1408 : 1536) && s->len[w] + T <= 1024;
 }

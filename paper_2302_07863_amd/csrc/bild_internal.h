@@ -195,7 +195,7 @@ struct AttnArgs {
     int d_model;
 };
 
-// A whole decoder pass in one kernel (pass_kernel.hip).
+// A whole decoder pass in one kernel (pass_kernel.hip, pass_wide.hip).
 // Most rows; on one die.  (One die, the whole chip, us, T5-small shape, 512 tokens: one row 97, 137, two 99, 138, four 100, 140;
 // mT5-small shape 120, 178; 121, 180; 122, 181.  The small model of a pair has one row; a narrow large one reviews.)
 constexpr int kPassRows = 16, kPassDieRows = 4;
@@ -209,7 +209,9 @@ struct PassLayer {
     char *kc, *vc, *ck, *cv;
 };
 struct PassPlan {  // where a layer's hand-over buffers lie in its piece of the scratch memory
-    int x1, q, k, v, a1, x2, a2, x3, h, layer;
+    int x1, q, k, v, a1, x2, a2, x3, h;
+    int part, top;            // (pass_wide.hip) attention results of the key ranges, their (max, sum)
+    int layer;
 };
 struct PassArgs {
     const PassLayer* layers;  // device array, from the pass' first layer on
@@ -217,6 +219,7 @@ struct PassArgs {
     int T, room;              // rows; rows there is room for in the hand-over memory
     int die;                  // 1: on one die
     int f32;                  // 1: of an fp32 model (on one die)
+    int wide;                 // 1: pass_wide.hip
     int d, heads, I, F, act, cross;
     // embedding of y[len ..]; emb null: the rows are x_in[len ..]
     const void* emb;
@@ -228,6 +231,7 @@ struct PassArgs {
     int vcap, scap;
     const float* rel_bias;
     int rel_d;
+    const double2* rope;      // rotary models (wide ones only): cos and sin, [position][d_head / 2]
     float att_scale, eps;
     float *x_out, *x_keep;    // the residual stream after the last layer: [T][d]; at [len ..] too (null: not kept)
     char* scratch;            // [3][at.layer]: layer l of the pass uses the place (turn * n_layers + l) mod 3
@@ -239,8 +243,12 @@ struct PassArgs {
 };
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // workgroups, 0: not a shape it is made for
 int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32);
-PassPlan pass_plan(int room, int d, int I, int F, bool f32);
+PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide);
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st);
+constexpr int kWideRows = 8, kWideHead = 128;  // most rows; features of a head
+constexpr int kWideSplits = 8;                 // most key ranges of a head
+int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // as pass_groups, of pass_wide.hip
+hipError_t launch_wide(const PassArgs& a, hipStream_t st);
 
 struct EmbedArgs {
     TMat E;

@@ -226,6 +226,7 @@ struct ModelState {
     // whole passes in one kernel (pass_kernel.hip)
     int pass_groups = 0;      // workgroups; 0: the shape is not made for it
     int pass_die_groups = 0;  // the same of the form on one die
+    bool pass_wide = false;   // the form of pass_wide.hip
     bild::PassLayer* pass_layers = nullptr;  // device
     int pass_die_rows = 0;    // most rows there (the small model's passes with an LM head have one)
     char* pass_turns[bild::kPassRooms] = {};  // what its workgroups hand over, by the rows there is room for
@@ -245,7 +246,7 @@ struct bild_state {
     int* hsrc = nullptr;      // pinned copy of src
     float alpha_fb = -1.f, alpha_rb = -1.f;  // thresholds currently in the device control block
     bool use_graphs = true;
-    bool one_kernel = true;   // passes of up to kPassRows rows of a narrow bf16 model run as one kernel
+    bool one_kernel = true;   // passes of a few rows run as one kernel where there is one for the shape (takes_one_kernel)
     bool one_die = true;      // ... on one die, if it fits
     float* thin_sums = nullptr;  // of the slices of the thin GEMM's projections
     unsigned* thin_arrived = nullptr;

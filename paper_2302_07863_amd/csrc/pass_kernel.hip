@@ -43,306 +43,9 @@
 // handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
 // the pass again as separate kernels; after some passes it tries this kernel again.  That happens only if the workgroups cannot
 // all be resident, because of another process' kernel of the same kind, for instance.
-#include "kernel_common.h"
+#include "pass_walk.h"
 
 namespace bild {
-
-constexpr int kPassWaves = 8, kPassThreads = 64 * kPassWaves;
-
-typedef __attribute__((address_space(4))) const PassLayer CLayer;  // (read through the scalar cache)
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
-// (an address worked out here, not behind the wait that follows)
-template <class P>
-__device__ __forceinline__ P* pinned(P* p) {
-    asm volatile("" : "+s"(p));
-    return p;
-}
-__device__ __forceinline__ Rsrc whole(const void* p) { return make_rsrc(p, 0xFFFFFFFFu); }
-template <int AUX = 0>
-__device__ __forceinline__ float4 ldf4(Rsrc r, int off) { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX)); }
-__device__ __forceinline__ bf16x8 as_bf(const uint4& v) { return __builtin_bit_cast(bf16x8, v); }
-template <int AUX>
-__device__ __forceinline__ void st8(Rsrc r, int off, unsigned a, unsigned b) {
-    const v2u v = {a, b};
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, AUX);
-}
-
-constexpr unsigned kNotThere = 0xFFFFFFFFu;  // (two NaNs of a kind no conversion gives, as bf16 parts; one as a sum)
-
-// LDS: sums of the waves (up to six tiles each; attention joins its waves there too), their (max, sum), the head's query, the
-// waves' sums of squares (twice, like the sums), the head's relative-position biases
-constexpr int kRedBytes = kPassWaves * 6 * 1024;  // twice: a stage's sums are read while the next one's are written
-constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kSq = kQ + 16 * kQLd * 4, kSqBytes = kPassWaves * 16 * 4, kRel = kSq + 2 * kSqBytes;
-
-template <bool DIE, bool FP32, bool ONE_ROW>
-struct Walk {
-    static constexpr bool F32 = FP32;      // of an fp32 model
-    static constexpr bool ONE = ONE_ROW;   // ... and one row (see multiply)
-    static constexpr int KS = F32 ? 4 : 5;  // inputs of a weight tile, logarithm
-    static constexpr int ESZ = F32 ? 4 : 2;
-    static constexpr int BK = F32 ? 16 : 32;  // keys a wave takes at a time
-    static constexpr int kIn = 16;  // reads of what may not be there yet: past the L1 (sc1)
-    // what is handed over goes as far as all readers see it: to the die's L2 (the L1s write through), or past the L2s (sc0 sc1)
-    static constexpr int kOut = DIE ? 0 : 17;
-    char* lds;
-    unsigned* failed;
-    int spins;
-    int wg, wave, lane, tok, g, t, t8;  // t: this lane's row, clamped to the last one; t8: of the packed order
-    bool dead;
-    int red = 0, sq = 0;            // halves of the sums' memory in use
-    float ss;                       // this wave's part of its lane's row's sum of squares
-    int slot, clear;                // clear: from what this layer hands over to where the layer after the next will: filled with "not there yet"
-
-    int T, R;                       // rows; rows there is room for (the layout's)
-    __device__ __forceinline__ void place(int rows, int room) {
-        T = rows;
-        R = room;
-        tok = lane & 15;
-        g = lane >> 4;
-        t = min(tok, T - 1);
-        t8 = min(tok & 7, T - 1);
-    }
-    // This layer's hand-over memory, of three that take turns (see the head of this file); next(): of the layer after it.
-    __device__ __forceinline__ char* scratch(const PassArgs& a) {
-        slot = (int)(*a.turn * (unsigned)a.n_layers % 3u);
-        clear = slot == 0 ? 2 * a.at.layer : -a.at.layer;
-        return a.scratch + slot * a.at.layer;
-    }
-    __device__ __forceinline__ char* next(char* z, int layer) const { return z + (slot == 2 ? -2 * layer : layer); }
-    __device__ __forceinline__ void walk_on(int layer) {
-        slot = slot == 2 ? 0 : slot + 1;
-        clear = slot == 0 ? 2 * layer : -layer;
-    }
-    __device__ __forceinline__ void give_up() {
-        dead = true;
-        if (lane == 0) asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(failed), "v"(1u) : "memory");
-    }
-    // (about NS nanoseconds; see the head of this file)
-    template <int NS>
-    __device__ __forceinline__ void nap() const {
-        if constexpr (!DIE) __builtin_amdgcn_s_sleep(NS / 27);
-    }
-};
-
-// fp32: sixteen inputs, component v of a lane group g is input 4 g + v (two sums, so that products do not wait for each other)
-__device__ __forceinline__ void products(f32x4& a, f32x4& b, const uint4& w, const uint4& x) {
-    a = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w.x), __uint_as_float(x.x), a, 0, 0, 0);
-    b = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w.y), __uint_as_float(x.y), b, 0, 0, 0);
-    a = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w.z), __uint_as_float(x.z), a, 0, 0, 0);
-    b = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w.w), __uint_as_float(x.w), b, 0, 0, 0);
-}
-
-// This wave's run of input tiles of a projection over tk tiles.
-struct Run {
-    int k0, n;
-};
-__device__ __forceinline__ Run run_of(int wave, int tk) {
-    const int per = (tk + kPassWaves - 1) / kPassWaves;
-    return {wave * per, max(0, min(per, tk - wave * per))};
-}
-
-// (tiles past the last of the `tiles` there are: the last one again)
-template <int N, int RW, class Walk>
-__device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const void* w, int unit, int tk, int tiles) {
-    const Run r = run_of(c.wave, tk);
-    const Rsrc rs = whole((const char*)w + (size_t)unit * RW * tk * kTileBytes);
-    const int most = tiles - 1 - unit * RW;
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-        if (j < r.n) {
-#pragma unroll
-            for (int q = 0; q < RW; ++q) W[j * RW + q] = buf_load(rs, (unsigned)c.lane * 16u, ((RW == 1 ? 0 : min(q, most)) * tk + r.k0 + j) * kTileBytes);
-        }
-}
-
-// A tile of planes that a norm's projection reads has its producers' sums of squares behind it, [row][first, second sixteen
-// inputs] (an own line: a producer's part of a row lies where its planes' readers look anyway).
-// (fp32 models: tiles of sixteen inputs, a producer each, [four inputs][row] and one sum per row)
-__host__ __device__ __forceinline__ int tile_bytes(bool normed, int room, bool f32) { return f32 ? room * 64 + (normed ? 64 : 0) : room * 128 + (normed ? 128 : 0); }
-// 1/rms of this lane's row, behind leave()
-template <class Walk>
-__device__ __forceinline__ float norm_factor(const Walk& c, int d, float eps) {
-    float p[kPassWaves], s = 0.f;
-#pragma unroll
-    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const float*)(c.lds + kSq + c.sq + (v * 16 + c.tok) * 4);
-#pragma unroll
-    for (int v = 0; v < kPassWaves; ++v) s += p[v];
-    return __builtin_amdgcn_rsqf(s * __builtin_amdgcn_rcpf((float)d) + eps);
-}
-
-// acc = W x over this wave's inputs.  x lies in tiles of 32 inputs in the order in which the operand's lanes want it: quarters of
-// eight inputs, in each the rows one after the other, 16 bytes per row; the high parts of a tile and then its low parts.  (A load
-// is then one dense piece: with the rows' 64 bytes 128 apart a pass of eight rows took 854 us instead of 737.)
-// Up to eight rows (PACK) one operand holds the high parts of the rows in its columns 0 .. 7 and the low parts in 8 .. 15: half
-// the loads and products (a compute unit's 64 bytes a cycle are what the FFN output's 256 loads of 1 KiB wait for); the halves
-// are added in total().  A quarter then has the rows' high parts and their low parts.
-// NORM: the rows' sums of squares as well, to c.ss.
-// One row of an fp32 model (Walk::ONE) has no use for the matrix cores, whose fp32 products of sixteen rows take eight times as long
-// as a lane's own four inputs: lane (feature, four inputs) sums those, leave() adds the four lanes of a feature.
-template <int N, int RW, bool PACK, bool NORM, class Walk>
-__device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 (&W)[N * RW], const void* planes, int tk) {
-    const Run r = run_of(c.wave, tk);
-    const Rsrc xs = whole(planes);
-    const int S = tile_bytes(NORM, c.R, Walk::F32);
-    const int at = (PACK ? (c.g * 2 + (c.tok >> 3)) * c.R + c.t8 : c.g * c.R + c.t) * 16, k0 = r.k0 * S;
-    constexpr int P = PACK || Walk::F32 ? 1 : 2, B = N * P <= 16 ? N : 4;  // tiles requested at once
-    constexpr int IN = Walk::kIn;
-    static_assert(N % B == 0 && (!NORM || N <= 4), "whole pieces; a lane group per tile");
-    uint4 X[N > B ? 2 : 1][P * B];
-    v2u sq = {0u, 0u};
-    f32x4 low[RW];
-#pragma unroll
-    for (int q = 0; q < RW; ++q) acc[q] = low[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto get = [&](uint4 (&x)[P * B], int j0) {
-#pragma unroll
-        for (int j = 0; j < B; ++j)
-            if (j0 + j < r.n) {
-#pragma unroll
-                for (int p = 0; p < P; ++p) x[P * j + p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at + p * c.R * 64, k0 + (j0 + j) * S, IN));
-            }
-        if constexpr (NORM) {  // (lane group g: tile g)
-            const int tile = min(c.g, max(r.n - 1, 0)) * S, from = r.n > 0 ? k0 : 0;
-            if constexpr (Walk::F32) {
-                const unsigned v = __builtin_amdgcn_raw_buffer_load_b32(xs, tile + c.R * 64 + c.t * 4, from, IN);
-                sq = v2u{c.g < r.n ? v : 0u, 0u};
-            } else {
-                const v2u v = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, tile + c.R * 128 + c.t * 8, from, IN));
-                sq = c.g < r.n ? v : v2u{0u, 0u};
-            }
-        }
-    };
-    // all of it again and again until every word is there
-    auto wait = [&](uint4 (&x)[P * B], int j0) {
-        int n = 0;
-        bool missing;
-#pragma unroll 1
-        do {
-            asm volatile("" ::: "memory");
-            if (N == B || n > 0) get(x, j0);
-            unsigned m = max(sq.x, sq.y);
-#pragma unroll
-            for (int j = 0; j < B; ++j)
-                if (j0 + j < r.n) {
-#pragma unroll
-                    for (int p = 0; p < P; ++p) m = max(max(m, max(x[P * j + p].x, x[P * j + p].y)), max(x[P * j + p].z, x[P * j + p].w));
-                }
-            missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
-        } while (missing && ++n < c.spins);
-        if (missing) c.give_up();
-    };
-    auto mul = [&](const uint4 (&x)[P * B], int j0) {
-#pragma unroll
-        for (int j = 0; j < B; ++j)
-            if (j0 + j < r.n) {
-#pragma unroll
-                for (int q = 0; q < RW; ++q) {
-                    if constexpr (Walk::ONE) {
-                        const uint4 w = W[(j0 + j) * RW + q];
-                        acc[q][0] = __builtin_fmaf(__uint_as_float(w.x), __uint_as_float(x[j].x), acc[q][0]);
-                        acc[q][1] = __builtin_fmaf(__uint_as_float(w.y), __uint_as_float(x[j].y), acc[q][1]);
-                        acc[q][2] = __builtin_fmaf(__uint_as_float(w.z), __uint_as_float(x[j].z), acc[q][2]);
-                        acc[q][3] = __builtin_fmaf(__uint_as_float(w.w), __uint_as_float(x[j].w), acc[q][3]);
-                        continue;
-                    }
-                    if constexpr (Walk::F32) {
-                        products(acc[q], RW == 1 ? low[q] : acc[q], W[(j0 + j) * RW + q], x[j]);
-                        continue;
-                    }
-                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j]), acc[q], 0, 0, 0);
-                    f32x4& lo_acc = RW == 1 ? low[q] : acc[q];
-                    if (!PACK) lo_acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j + P - 1]), lo_acc, 0, 0, 0);
-                }
-            }
-    };
-    if constexpr (N == B) {
-        wait(X[0], 0);
-        mul(X[0], 0);
-    } else {  // two pieces on their way
-        get(X[0], 0);
-        get(X[1], B);
-#pragma unroll
-        for (int j0 = 0; j0 < N; j0 += B) {
-            if (j0 >= r.n) break;
-            wait(X[(j0 / B) & 1], j0);
-            mul(X[(j0 / B) & 1], j0);
-            if (j0 + 2 * B < N) get(X[(j0 / B) & 1], j0 + 2 * B);
-        }
-    }
-    if constexpr (RW == 1 && !PACK) acc[0] += low[0];
-    if constexpr (NORM) c.ss = quad_rows_sum(__uint_as_float(sq.x) + __uint_as_float(sq.y));
-}
-
-// The waves' results side by side in LDS; `tile`'s total over the waves, in wave order.
-// (ROW: multiply()'s sums of one row, [wave][tile][feature])
-template <int RW, bool NORM, bool ROW, class Walk>
-__device__ __forceinline__ void leave(Walk& c, const f32x4 (&acc)[RW]) {
-    c.red = kRedBytes - c.red;
-    if constexpr (NORM) {
-        c.sq = kSqBytes - c.sq;
-        if (c.g == 0) *(float*)(c.lds + kSq + c.sq + (c.wave * 16 + c.tok) * 4) = c.ss;
-    }
-#pragma unroll
-    for (int q = 0; q < RW; ++q) {
-        if constexpr (ROW) {
-            const float s = quad_rows_sum((acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3]));
-            if (c.g == 0) *(float*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 16 + c.tok) * 4) = s;
-        } else {
-            *(f32x4*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
-        }
-    }
-    lds_barrier();
-}
-template <int RW, bool PACK, class Walk>
-__device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
-    f32x4 p[kPassWaves];
-#pragma unroll
-    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const f32x4*)(c.lds + kRed + c.red + (Walk::ONE ? ((v * RW + tile) * 16 + c.g * 4) * 4 : ((v * RW + tile) * 64 + c.lane) * 16));
-    f32x4 s = p[0];
-#pragma unroll
-    for (int v = 1; v < kPassWaves; ++v) s += p[v];
-    if constexpr (PACK) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) s[v] += dpp_f<0x128, 0xF>(0.f, s[v]);  // row_ror:8: columns 8 .. 15 to 0 .. 7
-    }
-    return s;
-}
-
-// Sixteen features of a row's activations in that order: this lane's four.
-template <bool PACK, bool NORM, class Walk>
-__device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, const float (&w)[4]) {
-    if constexpr (Walk::F32) {
-        const int off = (n0 >> 4) * tile_bytes(NORM, c.R, true) + (((n0 & 15) >> 2) * c.R + c.tok) * 16;
-        const v4u v = {__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
-        if (c.tok < c.T) __builtin_amdgcn_raw_buffer_store_b128(v, whole(planes), off, 0, Walk::kOut);
-        if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, whole((const char*)planes + c.clear), off, 0, Walk::kOut);
-        return;
-    }
-    uint32_t h01, l01, h23, l23;
-    split_bf16x2(w[0], w[1], h01, l01);
-    split_bf16x2(w[2], w[3], h23, l23);
-    const Rsrc r = whole(planes);
-    const int off = (n0 >> 5) * tile_bytes(NORM, c.R, false) + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.R + c.tok) * 16 + (n0 & 7) * 2;
-    const int lo = (PACK ? 16 : 64) * c.R;
-    if (c.tok < c.T) {
-        st8<Walk::kOut>(r, off, h01, h23);
-        st8<Walk::kOut>(r, off + lo, l01, l23);
-    }
-    if (c.tok < c.R) {
-        const Rsrc n = whole((const char*)planes + c.clear);
-        st8<Walk::kOut>(n, off, kNotThere, kNotThere);
-        st8<Walk::kOut>(n, off + lo, kNotThere, kNotThere);
-    }
-}
-
-// What the projections hand over to a head: [row][64] queries (fp32) and keys (bf16), [64][row] values (bf16 in the upper half of a
-// word, so that four rows' values are one load; `room` rows, a multiple of four).
-struct Fresh {
-    Rsrc q, k, v;
-    int room;
-};
-__host__ __device__ inline int fresh_room(int rows) { return (rows + 3) & ~3; }
 
 // Attention of one head over its keys for all rows: the waves take blocks of 32 keys in turn; (max, sum, O) joined through LDS.
 template <bool CAUSAL, bool PACK, class Walk>
@@ -949,7 +652,7 @@ int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32) {
     return g <= 32 ? g : 0;
 }
 
-PassPlan pass_plan(int room, int d, int I, int F, bool f32) {
+PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide) {
     PassPlan p;
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -962,6 +665,10 @@ PassPlan pass_plan(int room, int d, int I, int F, bool f32) {
     p.x1 = take(x); p.q = take((size_t)room * I * 4); p.k = take((size_t)room * I * (f32 ? 4 : 2)); p.v = take((size_t)fresh_room(room) * I * 4);
     p.a1 = take(i); p.x2 = take(x); p.a2 = take(i); p.x3 = take(x);
     p.h = take((size_t)(F / inputs) * tile_bytes(false, room, f32));
+    if (wide) {
+        p.part = take((size_t)kWideSplits * room * I * 4);
+        p.top = take((size_t)kWideSplits * room * (I / kWideHead) * 8);
+    }
     p.layer = (int)at;
     return p;
 }

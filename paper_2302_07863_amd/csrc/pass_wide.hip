@@ -1,0 +1,637 @@
+// One decoder pass of a wide bf16 model without cross-attention (above 1024 and up to 4096 wide, heads of 128) in ONE kernel, up to
+// eight rows: pass_kernel.hip's way of handing results over (its head explains it; nothing is counted, results are their own flags),
+// for layers of 60 to 400 MB.
+//
+// Bound: the weights from memory.  As kernels of their own the six stages of a layer each end with a few microseconds in which the
+// memory has little to do (the last workgroups, the launch, the trip for the activations, cold instructions) and attention keeps it
+// idle for ten; here a workgroup per compute unit stays, and asks for the next stage's weights before that stage's activations exist:
+//
+//   - two pieces of a stage's weights wait in registers (8 to 16 KB a wave, up to 256 KB a compute unit), the rest follow while they
+//     are multiplied.  A compute unit takes new requests only as fast as the old ones are answered, so a request that is not the
+//     critical path's holds up what comes behind it: results are published BEFORE the next stage's weights are asked for, and the
+//     other waves wait for that too (with the requests first, publishing took 2 to 13 us of each stage: 2048-wide, 16 layers, 527 us
+//     either way because the weights then come later; 4096-wide, 8 layers, 708 -> 663);
+//   - models up to 2048 wide ask for all of the FFN's first weights already when q, k and v are handed over, which keeps the memory
+//     busy while the heads work (536 -> 455 us); so much of a 4096-wide model's would only delay the output projection's activations
+//     (663 -> 685).  Asking for the FFN's second weights or the next layer's first ones a stage earlier loses for the same reason
+//     (455 -> 466, 482);
+//   - a head's keys are cut into ranges of at least 256 keys, eight at most, a workgroup each, whose waves take blocks of 32; the
+//     ranges' results are handed over once more and each of the head's workgroups joins 128 / ranges of its features;
+//   - a workgroup has the same sixteen features of the residual stream in all layers: they stay in registers.
+//
+// us per pass with the LM head, separate kernels / this, at 1064 positions: 2048-wide, 16 layers, 1, 2, 4, 8 rows 661, 731, 784, 805 /
+// 455, 459, 480, 513; 4096-wide, 8 layers 772, 836, 838, 841 / 663, 667, 679, 714, of which the layers' weights alone take 270 and 530 at
+// the 6.1 TB/s of a large copy.
+#include "pass_walk.h"
+
+namespace bild {
+
+// A projection's weights on their way: N input tiles per wave at most, RW feature tiles, in pieces of CH input tiles of which two
+// are requested before their activations are there.  The next piece's activations are requested ahead of the weights that follow
+// (a wave's loads come back in order).
+template <int N, int RW, int CH, bool NORM>
+struct Stream {
+    static constexpr int NC = (N + CH - 1) / CH, SQ = (CH + 3) / 4;
+    uint4 W[NC > 1 ? 2 : 1][CH * RW];
+
+    struct Where {
+        Rsrc rs;
+        int k0, n, tk, most;
+    };
+    __device__ __forceinline__ static Where where(int wave, const void* w, int unit, int tk, int tiles) {
+        const Run r = run_of(wave, tk);
+        return {whole((const char*)w + (size_t)unit * RW * tk * kTileBytes), min(r.k0, tk - 1), r.n, tk, tiles - 1 - unit * RW};
+    }
+    __device__ __forceinline__ static void ask(int lane, uint4 (&w)[CH * RW], const Where& a, int i) {
+#pragma unroll
+        for (int j = 0; j < CH; ++j)
+            if (i * CH + j < N) {
+                const int k = a.k0 + min(i * CH + j, max(a.n - 1, 0));  // (past the wave's last tile: that one again, not used)
+#pragma unroll
+                for (int q = 0; q < RW; ++q) w[j * RW + q] = buf_load(a.rs, (unsigned)lane * 16u, ((RW == 1 ? 0 : min(q, a.most)) * a.tk + k) * kTileBytes);
+            }
+    }
+    // (the registers hold nothing: without this they would be kept through the paths on which they are not filled anew)
+    __device__ __forceinline__ void forget() {
+#pragma unroll
+        for (uint4 (&w)[CH * RW] : W)
+#pragma unroll
+            for (uint4& v : w) asm volatile("" : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w));
+    }
+    template <class Walk>
+    __device__ __forceinline__ void open(const Walk& c, const void* w, int unit, int tk, int tiles) {
+        const Where a = where(c.wave, w, unit, tk, tiles);
+        ask(c.lane, W[0], a, 0);
+        if constexpr (NC > 1) ask(c.lane, W[1], a, 1);
+    }
+    // acc = W x over this wave's inputs, up to eight rows packed (see multiply() in pass_walk.h)
+    template <class Walk>
+    __device__ __forceinline__ void run(Walk& c, f32x4 (&acc)[RW], const void* planes, const void* weights, int unit, int tk, int tiles) {
+        const Where a = where(c.wave, weights, unit, tk, tiles);
+        const int k0 = a.k0, n = a.n;
+        const Rsrc xs = whole(planes);
+        const int S = tile_bytes(NORM, c.R, false), at = ((c.g * 2 + (c.tok >> 3)) * c.R + c.t8) * 16;
+        uint4 X[NC > 1 ? 2 : 1][CH];
+        v2u sq[NC > 1 ? 2 : 1][SQ];
+        float ss = 0.f;
+        auto get = [&](uint4 (&x)[CH], v2u (&s)[SQ], int i) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (i * CH + j < N) x[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at, (k0 + min(i * CH + j, max(n - 1, 0))) * S, Walk::kIn));
+            if constexpr (NORM) {  // (lane group g: tiles g, g + 4 of the piece)
+#pragma unroll
+                for (int u = 0; u < SQ; ++u)
+                    s[u] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, min(i * CH + u * 4 + c.g, max(n - 1, 0)) * S + c.R * 128 + c.t8 * 8, k0 * S, Walk::kIn));
+            }
+        };
+        auto missing = [&](const uint4 (&x)[CH], const v2u (&s)[SQ], int i) {
+            unsigned m = 0u;
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (i * CH + j < N) m = max(max(m, max(x[j].x, x[j].y)), max(x[j].z, x[j].w));
+            if constexpr (NORM) {
+#pragma unroll
+                for (int u = 0; u < SQ; ++u) m = max(m, max(s[u].x, s[u].y));
+            }
+            return __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+        };
+#pragma unroll
+        for (int q = 0; q < RW; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        get(X[0], sq[0], 0);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            uint4 (&x)[CH] = X[i & 1];
+            v2u (&s)[SQ] = sq[i & 1];
+            // (the first look apart: the wait of a loop would be for everything requested since)
+            if (__builtin_expect(missing(x, s, i), 0)) {
+                int tries = 0;
+                bool more;
+#pragma unroll 1
+                do {
+                    asm volatile("" ::: "memory");
+                    get(x, s, i);
+                    more = missing(x, s, i);
+                } while (more && ++tries < c.spins);
+                if (more) c.give_up();
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 1 < NC) get(X[(i + 1) & 1], sq[(i + 1) & 1], i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (i * CH + j < N && i * CH + j < n) {
+#pragma unroll
+                    for (int q = 0; q < RW; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[i & 1][j * RW + q]), as_bf(x[j]), acc[q], 0, 0, 0);
+                }
+            if constexpr (NORM) {
+#pragma unroll
+                for (int u = 0; u < SQ; ++u)
+                    if (u * 4 + c.g < CH && i * CH + u * 4 + c.g < n) ss += __uint_as_float(s[u].x) + __uint_as_float(s[u].y);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 2 < NC) ask(c.lane, W[i & 1], a, i + 2);
+        }
+        if constexpr (NORM) c.ss = quad_rows_sum(ss);
+    }
+};
+
+// One key range of a head: the waves of the head's workgroups take blocks of 32 keys in turn.
+template <class Walk>
+struct Range {
+    const Rsrc kr, vr;
+    const int I, cap, nblk;  // (blocks of the keys of earlier passes)
+    uint4 K[2][4], V[8];
+
+    __device__ __forceinline__ void load(const Walk& c, int blk) {
+        const int key = min(blk, max(nblk - 1, 0)) * 32;
+#pragma unroll
+        for (int ab = 0; ab < 2; ++ab)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) K[ab][ks] = buf_load(kr, (unsigned)((c.tok * I + c.g * 8) * 2), ((key + ab * 16) * I + ks * 32) * 2);
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) {
+            const int off = (dt * 16 * cap + key) * 2, vo = (c.tok * cap + c.g * 4) * 2;
+            const uint2 x = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, vo, off, 0));
+            const uint2 y = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, vo + 32, off, 0));
+            V[dt] = make_uint4(x.x, x.y, y.x, y.y);
+        }
+    }
+};
+
+// (the attention's results [wave][8][64] take both halves of the sums' memory)
+static_assert(2 * kRedBytes >= kPassWaves * 8 * 1024, "room for eight waves' results");
+
+template <int QTV, int FTV, int KDV, int KFV, int QC, int FC>
+struct WideCut {
+    static constexpr int QT = QTV, FT = FTV, KD = KDV, KF = KFV;  // as in pass_kernel.hip
+    using Qkv = Stream<KD, QT, QC, true>;
+    using Out = Stream<KD, 1, 8, false>;
+    using In = Stream<KD, FT, FC, true>;
+    using Ffn = Stream<KF, 1, 8, false>;
+};
+// (pieces of the 4096-wide cut: 8 and 6 tiles a request of q, k, v and the FFN 669 and 673 us, 12 and 12 663, 15 and 18 the same)
+using Cut2048 = WideCut<2, 4, 8, 24, 4, 4>;
+using Cut4096 = WideCut<3, 6, 16, 44, 4, 2>;
+
+// Key ranges of a head: 256 keys each, a power of two, as long as there are workgroups.
+__device__ inline int wide_splits(int nkeys, int heads, int groups) {
+    int s = 1;
+    while (s < kWideSplits && s * 256 < nkeys && heads * s * 2 <= groups) s *= 2;
+    return s;
+}
+
+// Workgroups [0, d / 16) own sixteen features of the residual stream each; the last heads x ranges are the heads'.
+template <bool GATED, class Cut>
+__global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    using Way = Walk<false, false, false>;
+    constexpr int QT = Cut::QT, FT = Cut::FT, DH = kWideHead;
+    constexpr bool EARLY = Cut::In::NC <= 2;  // the FFN's first weights all fit the registers
+    Way c;
+    c.lds = smem;
+    c.failed = a.sync + kPassSyncWords - 1;
+    c.spins = a.spins;
+    c.wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    c.lane = (int)threadIdx.x & 63;
+    c.wg = (int)blockIdx.x;
+    c.dead = false;
+    c.place(a.T, a.room);
+    int T = a.T, d = a.d, I = a.I, F = a.F;
+    const int len = *a.len_ptr;
+    auto tq = [&] { return 3 * (I >> 4); };
+    auto tf = [&] { return GATED ? F >> 3 : F >> 4; };
+    const bool owner = c.wg < d >> 4, qkv = c.wg * QT < tq(), ffn = c.wg * FT < tf();
+    const bool mine = owner && c.wave == 0;
+    const int S = wide_splits(len + T, a.heads, a.groups), place = c.wg - (a.groups - a.heads * S);
+    const bool att = place >= 0;
+    const int h = att ? place / S : 0, split = att ? place % S : 0;
+
+    float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f), x = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto n0 = [&] { return c.wg * 16 + c.g * 4; };
+    auto gain = [&](const float* g) { return ldf4(whole(g), mine ? n0() * 4 : 0); };
+    auto publish = [&](const float4& gn, char* planes) {
+        if (!mine) return;
+        const float w[4] = {x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w};
+        const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
+        put_planes<true, true>(c, planes, n0(), w);
+        if (c.g == 0) {
+            const int off = (n0() >> 5) * tile_bytes(true, c.R, false) + c.R * 128 + (c.tok * 2 + ((n0() >> 4) & 1)) * 4;
+            if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(planes), off, 0, Way::kOut);
+            if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, whole(planes + c.clear), off, 0, Way::kOut);
+        }
+    };
+    auto add = [&] {
+        const f32x4 s = total<1, true>(c, 0);
+        x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]);
+    };
+    typename Cut::Qkv sq;
+    typename Cut::Out so;
+    typename Cut::In si;
+    typename Cut::Ffn sf;
+    const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
+    char* z = c.scratch(a);
+    if (owner) {
+        const int pos = len + c.t;
+        const float4 gn = gain(L->ln1);
+        if (mine) {
+            if (a.emb) {
+                int er = a.tokens[pos] + a.tie_shift;
+                er = er >= a.vocab ? er - a.vocab : er;
+                const char* p = (const char*)a.emb + ((size_t)(er >> 4) * (d >> 5) + (n0() >> 5)) * kTileBytes + ((er & 15) + 16 * ((n0() & 31) >> 3)) * 16 + (n0() & 7) * 2;
+                const uint2 raw = *(const uint2*)p;
+                float4 pe = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (a.pe) pe = *(const float4*)(a.pe + (size_t)pos * d + n0());
+                const float sc = a.embed_scale;
+                x = make_float4(__builtin_fmaf(bf2f(raw.x & 0xFFFFu), sc, pe.x), __builtin_fmaf(bf2f(raw.x >> 16), sc, pe.y),
+                                __builtin_fmaf(bf2f(raw.y & 0xFFFFu), sc, pe.z), __builtin_fmaf(bf2f(raw.y >> 16), sc, pe.w));
+            } else {
+                x = *(const float4*)(a.x_in + (size_t)pos * d + n0());
+            }
+        }
+        publish(gn, z + a.at.x1);
+    }
+    sq.forget();
+    if (qkv) sq.open(c, L->wqkv, c.wg, d >> 5, tq());
+    for (int l = 0; l < a.n_layers; ++l) {
+        L = (const CLayer*)(uintptr_t)a.layers + l;
+        const bool last = l + 1 == a.n_layers;
+        asm volatile("" : "+v"(c.lane));
+        asm volatile("" : "+s"(T), "+s"(d), "+s"(I), "+s"(F));
+        c.place(T, a.room);
+        // ---- q, k, v ----
+        if (qkv) {
+            const int nf = min(c.wg * QT + c.wave, tq() - 1) * 16 + c.g * 4;
+            double2 turn[2] = {};  // cos and sin of this lane's two pairs
+            if (a.rope && c.wave < QT) {
+                const double2* tb = a.rope + ((size_t)(len + c.t) * DH + nf % DH) / 2;
+                turn[0] = tb[0];
+                turn[1] = tb[1];
+            }
+            const char* xs = pinned(z + a.at.x1);
+            f32x4 acc[QT];
+            c.template nap<350>();
+            sq.run(c, acc, xs, L->wqkv, c.wg, d >> 5, tq());
+            leave<QT, true, false>(c, acc);
+            if (c.wave < QT && c.wg * QT + c.wave < tq()) {
+                const float f = norm_factor(c, d, a.eps);
+                f32x4 s = total<QT, true>(c, c.wave) * f;
+                const int seg = nf / I, nn = nf - seg * I, pos = len + c.tok, hd = nn / DH, f0 = nn % DH;
+                if (a.rope && seg < 2) {
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        const float x0 = s[2 * p], x1 = s[2 * p + 1];
+                        s[2 * p] = (float)((double)x0 * turn[p].x - (double)x1 * turn[p].y);
+                        s[2 * p + 1] = (float)((double)x0 * turn[p].y + (double)x1 * turn[p].x);
+                    }
+                }
+                char* out = z + (seg == 0 ? a.at.q : seg == 1 ? a.at.k : a.at.v);
+                const Rsrc o = whole(out), n = whole(out + c.clear), kv = whole(seg == 1 ? L->kc : L->vc);
+                if (seg == 0) {
+                    const int off = ((hd * c.R + c.tok) * DH + f0) * 4;
+                    const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
+                    if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b128(v, o, off, 0, Way::kOut);
+                    if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, n, off, 0, Way::kOut);
+                } else if (seg == 1) {
+                    const int off = ((hd * c.R + c.tok) * DH + f0) * 2;
+                    const unsigned k01 = pack_bf16x2(s[0], s[1]), k23 = pack_bf16x2(s[2], s[3]);
+                    if (c.tok < T) {
+                        st8<Way::kOut>(o, off, k01, k23);
+                        st8<Way::kOut>(kv, (pos * I + nn) * 2, k01, k23);
+                    }
+                    if (c.tok < c.R) st8<Way::kOut>(n, off, kNotThere, kNotThere);
+                } else {
+                    const int room = fresh_room(c.R), off = ((hd * DH + f0) * room + c.tok) * 4;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const unsigned b = f2bf(s[v]);
+                        if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(c.tok < T ? b << 16 : 0u, o, off + v * room * 4, 0, Way::kOut);
+                        if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, kv, ((nn + v) * a.vcap + pos) * 2, 0, Way::kOut);
+                        if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, n, off + v * room * 4, 0, Way::kOut);
+                    }
+                }
+            }
+            lds_barrier();  // (stored: see the head of this file)
+        }
+        // ---- attention ----
+        float4 gn = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (owner) {
+            gn = gain(L->ln2);
+            next_gain = gain(last ? L->ln2 : L[1].ln1);
+        }
+        if (!att) {
+            so.forget();
+            if (owner) so.open(c, L->wo, c.wg, I >> 5, d >> 4);
+            if constexpr (EARLY) {
+                c.template nap<1000>();  // (behind the keys and values)
+                si.forget();
+                if (ffn) si.open(c, L->win, c.wg, d >> 5, tf());
+            }
+        } else {
+            const int nblk = (len + 31) >> 5;
+            Range<Way> r = {whole(L->kc + (size_t)h * DH * 2), whole(L->vc + (size_t)h * DH * a.vcap * 2), I, a.vcap, nblk, {}, {}};
+            const int first = split + S * c.wave;
+            const bool newest = split == nblk % S && c.wave == nblk / S % kPassWaves, busy = first < nblk;
+            if (busy && !newest) r.load(c, first);
+            float m_run = -INFINITY, l_run = 0.f;
+            f32x4 O[8];
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const bool low = c.tok >= 8;
+            if (busy || newest) {
+                const int room = fresh_room(c.R);
+                const Rsrc fq = whole(z + a.at.q + h * c.R * DH * 4), fk = whole(z + a.at.k + h * c.R * DH * 2), fv = whole(z + a.at.v + h * room * DH * 4);
+                float4 qv[4][2];
+                uint4 kn[4];
+                float4 vn[8];
+                auto fetch = [&](bool fresh) {  // the queries; the new rows' keys and values too
+                    int tries = 0;
+                    bool missing;
+#pragma unroll 1
+                    do {
+                        asm volatile("" ::: "memory");
+                        unsigned m = 0u;
+                        auto see = [&](const uint4& v) { m = max(max(m, max(v.x, v.y)), max(v.z, v.w)); };
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) qv[i >> 1][i & 1] = ldf4<Way::kIn>(fq, c.t8 * DH * 4 + (i >> 1) * 128 + c.g * 32 + (i & 1) * 16);
+                        if (fresh) {
+#pragma unroll
+                            for (int ks = 0; ks < 4; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fk, c.t * DH * 2 + ks * 64 + c.g * 16, 0, Way::kIn));
+#pragma unroll
+                            for (int dt = 0; dt < 8; ++dt) vn[dt] = ldf4<Way::kIn>(fv, ((dt * 16 + c.tok) * room + min(c.g * 4, room - 4)) * 4);
+#pragma unroll
+                            for (int ks = 0; ks < 4; ++ks) see(kn[ks]);
+#pragma unroll
+                            for (int dt = 0; dt < 8; ++dt) see(__builtin_bit_cast(uint4, vn[dt]));
+                        }
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) see(__builtin_bit_cast(uint4, qv[i >> 1][i & 1]));
+                        missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+                    } while (missing && ++tries < c.spins);
+                    if (missing) c.give_up();
+                };
+                auto parts = [&](const float (&v)[8]) {  // high parts in columns 0 .. 7, low parts in 8 .. 15
+                    uint32_t hi[4], lo[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) split_bf16x2(v[2 * j], v[2 * j + 1], hi[j], lo[j]);
+                    return as_bf(make_uint4(low ? lo[0] : hi[0], low ? lo[1] : hi[1], low ? lo[2] : hi[2], low ? lo[3] : hi[3]));
+                };
+                bf16x8 Q[4];
+                auto split_query = [&] {
+                    const float sc = a.att_scale;
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) {
+                        const float v[8] = {qv[ks][0].x * sc, qv[ks][0].y * sc, qv[ks][0].z * sc, qv[ks][0].w * sc,
+                                            qv[ks][1].x * sc, qv[ks][1].y * sc, qv[ks][1].z * sc, qv[ks][1].w * sc};
+                        Q[ks] = parts(v);
+                    }
+                };
+                auto process = [&](int key, bool edge, int lim) {
+                    f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                        for (int ab = 0; ab < 2; ++ab) s[ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(r.K[ab][ks]), Q[ks], s[ab], 0, 0, 0);
+                    float p[8], top = m_run;
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) {
+                        p[v] = s[v >> 2][v & 3];
+                        p[v] += dpp_f<0x128, 0xF>(0.f, p[v]);
+                        if (edge && key + (v >> 2) * 16 + c.g * 4 + (v & 3) > lim) p[v] = -INFINITY;
+                        top = fmaxf(top, p[v]);
+                    }
+                    const float m_new = quad_rows_max(top), base = m_new == -INFINITY ? 0.f : m_new;
+                    float sum = 0.f;
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) {
+                        p[v] = fexp(p[v] - base);
+                        sum += p[v];
+                    }
+                    const float f = fexp(m_run - base);
+                    l_run = l_run * f + quad_rows_sum(sum);
+                    m_run = m_new;
+                    const bf16x8 w = parts(p);
+#pragma unroll
+                    for (int dt = 0; dt < 8; ++dt) {
+                        O[dt] *= f;
+                        O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(r.V[dt]), w, O[dt], 0, 0, 0);
+                    }
+                };
+                if (newest) {
+                    fetch(true);
+                    split_query();
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) {
+                        r.K[0][ks] = kn[ks];
+                        r.K[1][ks] = make_uint4(0u, 0u, 0u, 0u);
+                    }
+#pragma unroll
+                    for (int dt = 0; dt < 8; ++dt) {  // (bf16 values in the upper halves)
+                        const uint4 v = __builtin_bit_cast(uint4, vn[dt]);
+                        r.V[dt] = make_uint4(__builtin_amdgcn_perm(v.y, v.x, 0x07060302u), __builtin_amdgcn_perm(v.w, v.z, 0x07060302u), 0u, 0u);
+                    }
+                    process(len, true, len + c.t8);
+                    if (busy) r.load(c, first);
+                } else {
+                    fetch(false);
+                    split_query();
+                }
+#pragma unroll 1
+                for (int blk = first; blk < nblk; blk += S * kPassWaves) {
+                    process(blk * 32, blk * 32 + 31 >= len, len - 1);
+                    if (blk + S * kPassWaves < nblk) r.load(c, blk + S * kPassWaves);
+                }
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (its filling of the last layer: other waves have waited for a read since)
+            }
+            // the waves' results: joined in LDS, a wave per sixteen features
+            float* cm = (float*)(c.lds + kMl);
+            float* cl = cm + kPassWaves * 16;
+            lds_barrier();  // (both halves of the sums' memory are free)
+            if (c.g == 0) {
+                cm[c.wave * 16 + c.tok] = m_run;
+                cl[c.wave * 16 + c.tok] = l_run;
+            }
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) *(f32x4*)(c.lds + kRed + ((c.wave * 8 + dt) * 64 + c.lane) * 16) = O[dt];
+            lds_barrier();
+            float w[kPassWaves], M = -INFINITY, Lsum = 0.f;
+            f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int v = 0; v < kPassWaves; ++v) {
+                w[v] = cm[v * 16 + c.tok];
+                M = fmaxf(M, w[v]);
+            }
+            const float base = M == -INFINITY ? 0.f : M;
+#pragma unroll
+            for (int v = 0; v < kPassWaves; ++v) {
+                const float f = fexp(w[v] - base);
+                Lsum += cl[v * 16 + c.tok] * f;
+                o += *(const f32x4*)(c.lds + kRed + ((v * 8 + c.wave) * 64 + c.lane) * 16) * f;
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) o[v] += dpp_f<0x128, 0xF>(0.f, o[v]);
+            lds_barrier();  // (read: the next stage's sums may come)
+            char* out = pinned(z + a.at.a1);
+            auto give = [&](int dt, const f32x4& v, float sum) {
+                const float inv = 1.f / sum;
+                const float t4[4] = {v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv};
+                put_planes<true, false>(c, out, h * DH + dt * 16 + c.g * 4, t4);
+            };
+            {
+                // parts handed over between its workgroups, each of which joins 128 / S of the features
+                char* pp = z + a.at.part + h * kWideSplits * c.R * DH * 4;
+                char* pt = z + a.at.top + h * kWideSplits * c.R * 8;
+                const Rsrc po = whole(pp), to = whole(pt), pn = whole(pp + c.clear), tn = whole(pt + c.clear);
+                if (S > 1 && c.tok < T) {
+                    const v4u v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
+                    __builtin_amdgcn_raw_buffer_store_b128(v, po, ((split * c.R + c.tok) * DH + c.wave * 16 + c.g * 4) * 4, 0, Way::kOut);
+                    if (c.wave == 0 && c.g == 0) st8<Way::kOut>(to, (split * c.R + c.tok) * 8, __float_as_uint(M), __float_as_uint(Lsum));
+                }
+                for (int s = split; s < kWideSplits; s += S)  // (also the places of ranges that there are not in this pass)
+                    if (c.tok < c.R) {
+                        __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, pn, ((s * c.R + c.tok) * DH + c.wave * 16 + c.g * 4) * 4, 0, Way::kOut);
+                        if (c.wave == 0 && c.g == 0) st8<Way::kOut>(tn, (s * c.R + c.tok) * 8, kNotThere, kNotThere);
+                    }
+                const int per = 8 / S, dt = split * per + c.wave;
+                if (S == 1) {
+                    give(c.wave, o, Lsum);
+                } else if (c.wave < per) {
+                    float4 v[kWideSplits];
+                    v2u ml[kWideSplits];
+                    int tries = 0;
+                    bool missing;
+#pragma unroll 1
+                    do {
+                        asm volatile("" ::: "memory");
+                        unsigned m = 0u;
+#pragma unroll
+                        for (int s = 0; s < kWideSplits; ++s) {
+                            const int e = min(s, S - 1) * c.R + c.t8;
+                            v[s] = ldf4<Way::kIn>(po, (e * DH + dt * 16 + c.g * 4) * 4);
+                            ml[s] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(to, e * 8, 0, Way::kIn));
+                        }
+#pragma unroll
+                        for (int s = 0; s < kWideSplits; ++s) {
+                            const uint4 b = __builtin_bit_cast(uint4, v[s]);
+                            m = max(max(m, max(max(b.x, b.y), max(b.z, b.w))), max(ml[s].x, ml[s].y));
+                        }
+                        missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+                    } while (missing && ++tries < c.spins);
+                    if (missing) c.give_up();
+                    float all = -INFINITY, sum = 0.f;
+                    f32x4 j = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int s = 0; s < kWideSplits; ++s) all = fmaxf(all, __uint_as_float(ml[s].x));
+#pragma unroll
+                    for (int s = 0; s < kWideSplits; ++s) {
+                        const float f = s < S ? fexp(__uint_as_float(ml[s].x) - all) : 0.f;
+                        sum += __uint_as_float(ml[s].y) * f;
+                        j += f32x4{v[s].x, v[s].y, v[s].z, v[s].w} * f;
+                    }
+                    give(dt, j, sum);
+                }
+            }
+            lds_barrier();
+            so.forget();
+            if (owner) so.open(c, L->wo, c.wg, I >> 5, d >> 4);
+            if constexpr (EARLY) {
+                si.forget();
+                if (ffn) si.open(c, L->win, c.wg, d >> 5, tf());
+            }
+        }
+        // ---- output projection ----
+        if (owner) {
+            const char* xs = pinned(z + a.at.a1);
+            f32x4 acc[1];
+            so.run(c, acc, xs, L->wo, c.wg, I >> 5, d >> 4);
+            leave<1, false, false>(c, acc);
+            if (mine) add();
+            publish(gn, z + a.at.x2);
+            lds_barrier();
+        }
+        if constexpr (!EARLY) {
+            si.forget();
+            if (ffn) si.open(c, L->win, c.wg, d >> 5, tf());
+        }
+        // ---- FFN ----
+        if (ffn) {
+            constexpr int FW = GATED ? FT / 2 : FT;  // waves with results
+            const char* xs = pinned(z + a.at.x2);
+            f32x4 acc[FT];
+            c.template nap<350>();
+            si.run(c, acc, xs, L->win, c.wg, d >> 5, tf());
+            leave<FT, true, false>(c, acc);
+            const int tile = c.wg * FW + c.wave;  // of the hidden state
+            if (c.wave < FW && tile < F >> 4) {
+                const float rms = norm_factor(c, d, a.eps);
+                float w[4];
+                if constexpr (GATED) {
+                    const f32x4 s = total<FT, true>(c, 2 * c.wave) * rms, u = total<FT, true>(c, 2 * c.wave + 1) * rms;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) w[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(s[v]) : silu_f(s[v])) * u[v];
+                } else {
+                    const f32x4 s = total<FT, true>(c, c.wave) * rms;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) w[v] = fmaxf(s[v], 0.f);
+                }
+                put_planes<true, false>(c, z + a.at.h, tile * 16 + c.g * 4, w);
+            }
+            lds_barrier();
+        }
+        sf.forget();
+        if (owner) sf.open(c, L->wout, c.wg, F >> 5, d >> 4);
+        const char* hidden = z + a.at.h;
+        z = c.next(z, a.at.layer);
+        c.walk_on(a.at.layer);
+        if (owner) {
+            const char* xs = pinned(hidden);
+            f32x4 acc[1];
+            c.template nap<650>();
+            sf.run(c, acc, xs, L->wout, c.wg, F >> 5, d >> 4);
+            leave<1, false, false>(c, acc);
+            if (mine) add();
+            if (!last) publish(next_gain, z + a.at.x1);
+            lds_barrier();
+        }
+        sq.forget();
+        if (qkv && !last) sq.open(c, L[1].wqkv, c.wg, d >> 5, tq());
+    }
+    if (mine && c.tok < T) {
+        *(float4*)(a.x_out + (size_t)c.tok * d + n0()) = x;
+        if (a.x_keep) *(float4*)(a.x_keep + (size_t)(len + c.tok) * d + n0()) = x;
+    }
+}
+
+// Sizes the kernel is made for: runs of inputs that fit the registers, all of it on the chip at once.
+template <class Cut>
+static bool wide_fits(int d, int heads, int F, bool gated, int cus) {
+    const int I = heads * kWideHead, in = (std::max(d, I) / 32 + kPassWaves - 1) / kPassWaves, tf = gated ? F / 8 : F / 16;
+    return in <= Cut::KD && (F / 32 + kPassWaves - 1) / kPassWaves <= Cut::KF && (3 * I / 16 + Cut::QT - 1) / Cut::QT <= cus && (tf + Cut::FT - 1) / Cut::FT <= cus &&
+           d / 16 <= cus && heads <= cus;
+}
+
+int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
+    if (d_head != kWideHead || d <= 1024 || d % 256 != 0 || F % 32 != 0) return 0;
+    return wide_fits<Cut2048>(d, heads, F, gated, cus) || wide_fits<Cut4096>(d, heads, F, gated, cus) ? cus : 0;
+}
+
+hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
+    static hipError_t done = [] {
+        const void* fns[] = {(const void*)wide_kernel<false, Cut2048>, (const void*)wide_kernel<true, Cut2048>, (const void*)wide_kernel<false, Cut4096>, (const void*)wide_kernel<true, Cut4096>};
+        return raise_lds_limit(fns, 160 * 1024);
+    }();
+    if (done != hipSuccess) return done;
+    const bool gated = a.act != BILD_ACT_RELU;
+    if (a.groups < 1 || a.groups != wide_groups(a.d, a.heads, a.I / std::max(a.heads, 1), a.F, gated, a.groups) || a.T < 1 || a.T > kWideRows || a.room < a.T || a.cross || a.rel_bias ||
+        !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr)
+        return hipErrorInvalidValue;
+    const dim3 grid(a.groups), block(kPassThreads);
+    const bool small = wide_fits<Cut2048>(a.d, a.heads, a.F, gated, a.groups);
+    if (small && gated) hipLaunchKernelGGL((wide_kernel<true, Cut2048>), grid, block, kRel, st, a);
+    else if (small) hipLaunchKernelGGL((wide_kernel<false, Cut2048>), grid, block, kRel, st, a);
+    else if (gated) hipLaunchKernelGGL((wide_kernel<true, Cut4096>), grid, block, kRel, st, a);
+    else hipLaunchKernelGGL((wide_kernel<false, Cut4096>), grid, block, kRel, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace bild
