@@ -501,8 +501,10 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     for (int w = 0; w < 2 && e == hipSuccess; ++w) {
         ModelState& M = s->ms[w];
         if (!M.pass_groups) continue;
-        for (int r = 0; r < kPassRooms && e == hipSuccess; ++r)
-            if (M.pass_turns[r]) e = hipMemsetAsync(M.pass_turns[r], 0xFF, pass_turns_bytes(M, r), s->stream);
+        size_t bytes = 0;  // (one behind the other, as they were asked for)
+        for (int r = 0; r < kPassRooms; ++r)
+            if (M.pass_turns[r]) bytes = (size_t)(M.pass_turns[r] - M.pass_turns[0]) + pass_turns_bytes(M, r);
+        e = hipMemsetAsync(M.pass_turns[0], 0xFF, bytes, s->stream);
         if (e != hipSuccess) break;
         const size_t kv = (size_t)s->cap_len * M.m->inner() * M.m->esz(), ckv = (size_t)s->cap_src * M.m->inner() * M.m->esz();
         for (size_t l = 0; l < M.m->dec.size(); ++l) {

@@ -663,7 +663,8 @@ PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide) {
     const int inputs = f32 ? 16 : 32;
     const size_t x = (size_t)(d / inputs) * tile_bytes(true, room, f32), i = (size_t)(I / inputs) * tile_bytes(false, room, f32);
     p.x1 = take(x); p.q = take((size_t)room * I * 4); p.k = take((size_t)room * I * (f32 ? 4 : 2)); p.v = take((size_t)fresh_room(room) * I * 4);
-    p.a1 = take(i); p.x2 = take(x); p.a2 = take(i); p.x3 = take(x);
+    p.a1 = take(i); p.x2 = take(x);
+    p.a2 = wide ? 0 : take(i); p.x3 = wide ? 0 : take(x);  // (cross-attention)
     p.h = take((size_t)(F / inputs) * tile_bytes(false, room, f32));
     if (wide) {
         p.part = take((size_t)kWideSplits * room * I * 4);
