@@ -24,6 +24,9 @@ namespace bild {
 constexpr int kTileWaves = 4;
 __host__ __device__ constexpr int tile_sums(int rt) { return rt * 16 * kTileWaves > 256 ? rt * 16 * kTileWaves : 256; }
 
+// Three workgroups per compute unit (see the shared form below)
+constexpr bool tile_lean(int rt, int epi, bool gated) { return rt == 4 && (epi == EPI_QKV || gated); }
+
 // Row block and feature group of a workgroup.  Workgroups go to the eight dies in turn; the dies form a grid of a.gr row
 // shares x 8 / a.gr feature shares (launch_gemm_tile), and a die walks the row blocks of its share before the next feature
 // group, so that the weights of a group come from memory once and are then in that die's L2 while the rows pass.
@@ -41,7 +44,7 @@ __device__ __forceinline__ bool tile_block(const TileGemmArgs& a, int& rb, int& 
 // FT: feature tiles per wave.  GATED: feature tiles 2j / 2j+1 hold gate and linear branch of output block j.
 // SPLIT: the waves of a workgroup (also) slice the inputs, a.wk of them per feature group.
 template <int RT, int FT, int EPI, int ROPE, bool GATED, bool SPLIT, bool SHARE>
-__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const TileGemmArgs a) {
+__global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) void gemm_tile_kernel(const TileGemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr bool norm = EPI != EPI_RESID;  // residual-adding projections read un-normalised input
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -117,83 +120,105 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const TileGemmArgs a)
         }
     }
     if constexpr (SHARE) {
-        // The rows' operands go through LDS, two steps deep: each wave fetches a quarter of the next step's.
+        // The rows' operands go through LDS: in step k each wave stores its part of a later step's.
+        // Four row tiles, but for an FFN without gate: of step k + 2, so that the first row tile of step k + 1 is read ahead of the
+        // barrier between the two and a step begins with products; the requests are spread among the products (all at once they
+        // hold up the wave that issues them); registers for three workgroups per compute unit unless the epilogue needs them.  1023
+        // rows: 12288 features 176 -> 167 us; 4096 features, 4096 and 11008 inputs, one workgroup per compute unit, on average 157
+        // -> 149; 11264 features, gated, 86 -> 83 (1531 rows x 4096 x 1024 without gate: 31.9 -> 32.2, and 1 % off the encoder).
+        // Else of step k + 1, requests in one go.  Eight row tiles have room for two steps ahead (the other way 280 -> 285 us at 22016
+        // features, 1531 rows x 49152 x 1024 291 -> 307; spread as well 310).
         constexpr int UPW = 2 * RT / kTileWaves;  // 1 KiB units a wave fetches per step
-        char* xs = (char*)red;                    // [2][RT][2][1 KiB]
-        constexpr int D = RT == 4 ? 4 : 2;        // steps requested ahead (2000 cycles of products)
-        uint4 W[D][FT], XR[D][UPW];
+        constexpr int SLOT = 2 * RT * kTileBytes;
+        constexpr bool SPREAD = tile_lean(RT, EPI, GATED) || (RT == 4 && EPI == EPI_RESID);
+        constexpr int AH = SPREAD ? 2 : 1;        // steps from the store to the use
+        char* xs = (char*)red;                    // [2 AH][RT][2][1 KiB]
+        constexpr int D = RT == 8 ? 2 : tile_lean(RT, EPI, GATED) ? 3 : 4;  // steps requested ahead (spread: one less of the weights)
+        uint4 W[D][FT], XR[D][UPW], B[2][2];
         int xu[UPW];
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             const int unit = wave * UPW + u;
             xu[u] = min(unit >> 1, rt_last - xt0) * tk * (2 * kTileBytes) + (unit & 1) * kTileBytes;
         }
-        auto request_w = [&](uint4 (&Wd)[FT], int k) {
-            const int kc = min(k, tk - 1);
+        auto request_w = [&](uint4 (&Wd)[FT], int k, int f) { Wd[f] = buf_load(wr, lane16, woff[f] + min(k, tk - 1) * kTileBytes); };
+        auto request_x = [&](uint4 (&Xd)[UPW], int k, int u) { Xd[u] = buf_load(xr, lane16, xu[u] + min(k, tk - 1) * (2 * kTileBytes)); };
+        static_assert(UPW + FT <= 2 * RT, "a request per half row tile");
+        auto store_x = [&](const uint4 (&Xd)[UPW], int k) {
 #pragma unroll
-            for (int f = 0; f < FT; ++f) Wd[f] = buf_load(wr, lane16, woff[f] + kc * kTileBytes);
+            for (int u = 0; u < UPW; ++u) *(uint4*)(xs + (k & (2 * AH - 1)) * SLOT + (wave * UPW + u) * kTileBytes + lane16) = Xd[u];
         };
-        auto request_x = [&](uint4 (&Xd)[UPW], int k) {
-            const int kc = min(k, tk - 1);
-#pragma unroll
-            for (int u = 0; u < UPW; ++u) Xd[u] = buf_load(xr, lane16, xu[u] + kc * (2 * kTileBytes));
+        auto frag = [&](int k, int r) {
+            const char* xb = xs + (k & (2 * AH - 1)) * SLOT + r * 2 * kTileBytes + lane16;
+            B[r & 1][0] = *(const uint4*)xb;
+            B[r & 1][1] = *(const uint4*)(xb + kTileBytes);
         };
-        auto store_x = [&](const uint4 (&Xd)[UPW], int slot) {
-#pragma unroll
-            for (int u = 0; u < UPW; ++u) *(uint4*)(xs + slot * (2 * RT * kTileBytes) + (wave * UPW + u) * kTileBytes + lane16) = Xd[u];
-        };
-        auto compute = [&](const uint4 (&Wc)[FT], int slot) {
-            const char* xb = xs + slot * (2 * RT * kTileBytes) + lane16;
-            uint4 B[2][2];
-            auto frag = [&](int r) {
-                B[r & 1][0] = *(const uint4*)(xb + r * 2 * kTileBytes);
-                B[r & 1][1] = *(const uint4*)(xb + (r * 2 + 1) * kTileBytes);
-            };
-            frag(0);
+        auto compute = [&](const uint4 (&Wc)[FT], uint4 (&Xn)[UPW], uint4 (&Wn)[FT], int k, bool more) {
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
-                if (r + 1 < RT) frag(r + 1);  // read ahead of the products of this row tile
+                if (AH == 1 && r == 0) frag(k, 0);
+                if (AH == 2 || r + 1 < RT) frag(r + 1 < RT ? k : k + 1, r + 1 < RT ? r + 1 : 0);  // read ahead of the products of this row tile
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int p = 0; p < 2; ++p)
+                for (int p = 0; p < 2; ++p) {
 #pragma unroll
                     for (int f = 0; f < FT; ++f)
                         acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Wc[f]), __builtin_bit_cast(bf16x8, B[r & 1][p]), acc[f][r], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const int i = r * 2 + p;
+                    if (SPREAD && more && i < UPW + FT) {
+                        if (i < UPW) request_x(Xn, k + AH + D, i); else request_w(Wn, k + D - 1, i - UPW);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         };
         // (in the order of the loop: the memory counter retires requests in order, and the waits of the loop hold for both ways into it)
-        uint4 X0[UPW];
-        request_x(X0, 0);
+        uint4 X0[AH][UPW];
+#pragma unroll
+        for (int i = 0; i < AH; ++i)
+#pragma unroll
+            for (int u = 0; u < UPW; ++u) request_x(X0[i], i, u);
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             __builtin_amdgcn_sched_barrier(0);
-            request_x(XR[(d + 1) % D], d + 1);
+#pragma unroll
+            for (int u = 0; u < UPW; ++u) request_x(XR[d], d + AH, u);
             __builtin_amdgcn_sched_barrier(0);
-            request_w(W[d], d);
+            if (d >= SPREAD)
+#pragma unroll
+                for (int f = 0; f < FT; ++f) request_w(W[d - SPREAD], d - SPREAD, f);
         }
         __builtin_amdgcn_sched_barrier(0);
         row_sums();
-        store_x(X0, 0);
+#pragma unroll
+        for (int i = 0; i < AH; ++i) store_x(X0[i], i);
         lds_barrier();
+        if constexpr (AH == 2) frag(0, 0);
         int k = 0;
         for (; k + D <= tk; k += D) {
 #pragma unroll
             for (int j = 0; j < D; ++j) {
-                store_x(XR[(j + 1) % D], (j + 1) & 1);  // x of the next step
-                request_x(XR[(j + 1) % D], k + j + 1 + D);
+                store_x(XR[j], k + j + AH);
+                if constexpr (!SPREAD) {
+#pragma unroll
+                    for (int u = 0; u < UPW; ++u) request_x(XR[j], k + j + AH + D, u);
+                }
                 __builtin_amdgcn_sched_barrier(0);
-                compute(W[j], j & 1);
+                compute(W[j], XR[j], W[(j + D - 1) % D], k + j, true);
                 __builtin_amdgcn_sched_barrier(0);
-                request_w(W[j], k + j + D);
+                if constexpr (!SPREAD) {
+#pragma unroll
+                    for (int f = 0; f < FT; ++f) request_w(W[j], k + j + D, f);
+                }
                 lds_barrier();
             }
         }
 #pragma unroll
         for (int j = 0; j < D - 1; ++j) {  // the steps left over; their operands are on the way
             if (k + j < tk) {
-                store_x(XR[(j + 1) % D], (j + 1) & 1);
-                compute(W[j], j & 1);
+                store_x(XR[j], k + j + AH);
+                compute(W[j], XR[j], W[(j + D - 1) % D], k + j, false);
                 lds_barrier();
             }
         }
@@ -499,7 +524,7 @@ hipError_t launch_gemm_tile(const TileGemmArgs& a0, hipStream_t st) {
     }
     const int gf = 8 / a.gr;
     const dim3 grid((unsigned)(8 * ((a.rbs + a.gr - 1) / a.gr) * ((a.fgs + gf - 1) / gf))), block(64 * kTileWaves);
-    const size_t smem = (size_t)tile_sums(t.rt) * 4 + (t.share ? (size_t)4 * t.rt * 1024 : a.wk > 1 ? (size_t)kTileWaves * t.rt * t.ft * 1024 : 0);
+    const size_t smem = (size_t)tile_sums(t.rt) * 4 + (t.share ? (size_t)32 * 1024 : a.wk > 1 ? (size_t)kTileWaves * t.rt * t.ft * 1024 : 0);
 #define BILD_T(RTV, FTV, EPIV, ROPEV, GV, SP, SH)                                                                            \
     do {                                                                                                                     \
         hipLaunchKernelGGL((gemm_tile_kernel<RTV, FTV, EPIV, ROPEV, GV, SP, SH>), grid, block, smem, st, a);                 \
