@@ -186,7 +186,8 @@ def pass_shape(c, which):
     """(layers one pass runs, dependent stages of a pass as one kernel with its LM head and policy kernel)"""
     shape = c.cfg.small if which == c.pkg.SMALL else c.cfg.large
     layers = shape.n_dec - (c.trunk if which == c.pkg.LARGE else 0)
-    return layers, layers * (7 if shape.cross else 5) + 3  # + embedding, head, policy
+    stages = 7 if shape.cross else 6 if shape.d > 1024 else 5  # (wide models: the key ranges are joined)
+    return layers, layers * stages + 3  # + embedding, head, policy
 
 
 def route_of(c, which, rows, reps):
@@ -205,7 +206,7 @@ def roofline_leg(c, fb, rb, stats):
     assert small_steps == stats["small_steps"] and sum(hist.values()) == stats["large_calls"], (small_steps, hist, stats)
     mix = [(pkg.SMALL, 1, small_steps)] + [(pkg.LARGE, rows, count) for rows, count in sorted(hist.items())]
     timed = [(which, rows, count) + route_of(c, which, rows, 50 if which == pkg.SMALL else 20) for which, rows, count in mix]
-    if any(route == "kernels" for *_, route, _ in timed):
+    if all(route == "kernels" for *_, route, _ in timed):
         return gemm_roofline(c, small_steps, hist)
     y_len = c.st.lengths()["y_len"]
     nbytes = ms = launches = 0
@@ -213,7 +214,7 @@ def roofline_leg(c, fb, rb, stats):
     for which, rows, count, t, route, n in timed:
         one = c.st.pass_bytes(which, y_len - rows, rows)
         nbytes, ms, launches = nbytes + count * one, ms + count * t, launches + count * n
-        rec = dict(passes=count, launches=n, form=route, ms=round(t, 4), us_per_stage=round(t * 1e3 / pass_shape(c, which)[1], 3),
+        rec = dict(passes=count, launches=n, form=route, ms=round(t, 4), us_per_stage=round(t * 1e3 / (n if route == "kernels" else pass_shape(c, which)[1]), 3),
                    gbs=round(one / t / 1e6, 1))
         if which == pkg.SMALL:
             small, stages["small"] = rec, n
@@ -222,13 +223,14 @@ def roofline_leg(c, fb, rb, stats):
     achieved, passes = nbytes / ms / 1e6, sum(count for _, _, count in mix)
     traffic = profile_value(f"gemm_{c.cfg.name}_pmc.txt", "pass_traffic_bytes_per_launch")
     rocprof_us = profile_value(f"bild_{c.cfg.name}_kernel_stats.txt", "pass_mean_us")
-    return dict(bound="hbm", bound_by="hand-over latency between the dependent stages inside the kernel",
-                kernel="bild::pass_kernel with the LM head (bild::gemm_kernel) and the policy kernel: whole passes",
+    wide = c.cfg.large.d > 1024
+    return dict(bound="hbm", bound_by="weight stream" if wide else "hand-over latency between the dependent stages inside the kernel",
+                kernel=f"bild::{'wide' if wide else 'pass'}_kernel with the LM head and the policy kernel: whole passes",
                 achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s", frac=round(achieved / HBM_PEAK_GBS, 4),
-                traffic=None if traffic is None else int(traffic),  # counted bytes of a launch of pass_kernel alone
+                traffic=None if traffic is None else int(traffic),  # counted bytes of a launch of the pass' kernel alone
                 launches_per_step=launches, passes_per_step=passes, mean_pass_us=round(ms / passes * 1e3, 3),
                 mean_bytes_per_pass=int(nbytes / passes), stages_per_pass=stages,
-                rocprofv3_mean_us=rocprof_us,  # of pass_kernel alone
+                rocprofv3_mean_us=rocprof_us,  # of the pass' kernel alone
                 small_pass=small, large_pass_by_rows=by_rows)
 
 

@@ -638,8 +638,7 @@ static bool cut_fits(int d, int I, int F, int inputs) {
     return ceil_div(std::max(d, I) / inputs, kPassWaves) <= Cut::KD && ceil_div(F / inputs, kPassWaves) <= Cut::KF;
 }
 
-// Sizes the kernel is made for: runs of inputs that fit the registers, the workgroups on the chip at once.  Wider models are bound
-// by the weights' bandwidth, not by the hand-overs.
+// Sizes the kernel is made for: runs of inputs that fit the registers, the workgroups on the chip at once.  Wider models: pass_wide.hip.
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<ChipCut>(d, heads * 64, F, 32)) return 0;
     const int g = cut_groups<ChipCut>(d, heads, F, gated);

@@ -49,7 +49,7 @@ def stats(path: str) -> str:
     g = agg.get("bild::gemm_kernel<*>")
     if g:
         lines.append(f"gemm_mean_us={g[1] / g[0] / 1e3:.3f}")
-    g = agg.get("bild::pass_kernel<*>")
+    g = agg.get("bild::pass_kernel<*>") or agg.get("bild::wide_kernel<*>")
     if g:
         lines.append(f"pass_mean_us={g[1] / g[0] / 1e3:.3f}")
     return "\n".join(lines)
@@ -79,7 +79,7 @@ def pmc(fetch_path: str, write_path: str) -> str:
         lines.append(f"{k:34s} {n:10d} {fb:15.0f} {wb:15.0f}")
         if k.startswith("bild::gemm_kernel"):
             lines.append(f"traffic_bytes_per_launch={fb + wb:.0f}")
-        if k.startswith("bild::pass_kernel"):
+        if k.startswith(("bild::pass_kernel", "bild::wide_kernel")):
             lines.append(f"pass_traffic_bytes_per_launch={fb + wb:.0f}")
     return "\n".join(lines)
 
