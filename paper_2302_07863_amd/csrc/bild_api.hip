@@ -443,7 +443,8 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
                 for (int r = 0; r < kPassRooms; ++r) want(M.pass_turns[r], pass_turns_bytes(M, r));
             }
         }
-        if (s->one_kernel && bf16 && !m->cfg.cross_attn && m->cfg.pos != BILD_POS_RELATIVE && !M.pass_groups) {
+        // (a layer's cache is addressed by 32-bit byte offsets)
+        if (s->one_kernel && bf16 && !m->cfg.cross_attn && m->cfg.pos != BILD_POS_RELATIVE && !M.pass_groups && (size_t)s->cap_len * I * 2 < (size_t)1 << 31) {
             M.pass_groups = wide_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus);
             if (M.pass_groups) {
                 M.pass_wide = true;
