@@ -84,6 +84,9 @@ int bild_debug_gemm_shape(int n, int k, int rows, int gated, int lm_head, int dt
 /* The launch shape of attention for `rows` query rows over nkeys cached keys: out = {key splits, 1 if the consumer
  * projection merges the split partials (no merge kernel), waves per workgroup, dynamic LDS bytes}. */
 int bild_debug_attn_shape(int heads, int d_head, int rows, int nkeys, int max_splits, int dtype, int32_t out[4]);
+/* Kernels that address a bf16 layer's cache of `positions` by 32-bit offsets: out = {1 if they may take it (passes in one
+ * kernel), key splits of the attention that joins its ranges itself for up to nkeys keys (0: it is not taken), its waves}. */
+int bild_debug_cache_rule(int heads, int d_head, int positions, int nkeys, int32_t out[3]);
 
 #ifdef __cplusplus
 }

@@ -89,6 +89,7 @@ _SIGS = {
     "bild_probe_launch": (C.c_int, [C.c_void_p, C.c_int, C.POINTER(C.c_float)]),
     "bild_debug_tiled_bytes": (C.c_int64, [C.c_int, C.c_int, C.c_int]),
     "bild_debug_tile_matrix": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]),
+    "bild_debug_cache_rule": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
     "bild_debug_attn_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
     "bild_debug_gemm_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
     "bild_probe_copy": (C.c_int, [C.c_void_p, C.c_int64, C.c_int]),
@@ -385,3 +386,9 @@ def attn_shape(heads: int, d_head: int, rows: int, nkeys: int, max_splits: int =
     out = (C.c_int32 * 4)()
     _check(lib().bild_debug_attn_shape(heads, d_head, rows, nkeys, max_splits, dtype, out), "bild_debug_attn_shape")
     return dict(zip(("splits", "defer", "waves", "lds"), [int(v) for v in out]))
+
+
+def cache_rule(heads: int, d_head: int, positions: int, nkeys: int) -> dict:
+    out = (C.c_int32 * 3)()
+    _check(lib().bild_debug_cache_rule(heads, d_head, positions, nkeys, out), "bild_debug_cache_rule")
+    return dict(zip(("one_kernel", "splits", "waves"), [int(v) for v in out]))

@@ -20,8 +20,8 @@ struct AttnSplitArgs {
 };
 constexpr int kAttnSplitGroups = 512, kAttnSplitHeads = 256;
 constexpr size_t kAttnSplitFloats = (size_t)kAttnSplitGroups * (32 * 128 + 64);
-// splits and waves for up to `keys` keys; 0 splits: not a shape the kernel is made for
-void attn_split_shape(int heads, int d_head, int keys, int* splits, int* waves);
+// splits and waves for up to `keys` keys of a cache of `vcap`; 0 splits: not a shape the kernel is made for
+void attn_split_shape(int heads, int d_head, int i_dim, int vcap, int keys, int* splits, int* waves);
 hipError_t launch_attn_split(const AttnSplitArgs& a, hipStream_t st);
 hipError_t attn_split_init();
 

@@ -240,9 +240,9 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(const void* __restri
     }
 }
 
-void attn_split_shape(int heads, int d_head, int keys, int* splits, int* waves) {
+void attn_split_shape(int heads, int d_head, int i_dim, int vcap, int keys, int* splits, int* waves) {
     *splits = *waves = 0;
-    if ((d_head != 64 && d_head != 128) || heads < 1 || heads > kAttnSplitHeads) return;
+    if ((d_head != 64 && d_head != 128) || heads < 1 || heads > kAttnSplitHeads || !cache_in_int(vcap, i_dim, 2)) return;
     const int blocks = (keys + 31) / 32;
     int s = 1;
     while (heads * s * 2 <= 256 && s < 16 && blocks > s * (s < 8 ? 4 : 8)) s *= 2;
@@ -268,7 +268,7 @@ hipError_t attn_split_init() {
 hipError_t launch_attn_split(const AttnSplitArgs& a, hipStream_t st) {
     if (hipError_t e = attn_split_init(); e != hipSuccess) return e;
     if (a.T < 1 || a.T > kMaxRows || (a.d_head != 64 && a.d_head != 128) || a.splits < 1 || a.heads * a.splits > kAttnSplitGroups || a.heads > kAttnSplitHeads ||
-        (a.waves != 4 && a.waves != 8) || a.splits > 16 || a.vcap < 32 || a.vcap % 32 || !a.q || !a.k || !a.v || !a.len_ptr || (!a.out && !a.ob_t) || (a.splits > 1 && (!a.part || !a.arrived)))
+        (a.waves != 4 && a.waves != 8) || a.splits > 16 || a.vcap < 32 || a.vcap % 32 || !cache_in_int(a.vcap, a.i_dim, 2) || !a.q || !a.k || !a.v || !a.len_ptr || (!a.out && !a.ob_t) || (a.splits > 1 && (!a.part || !a.arrived)))
         return hipErrorInvalidValue;
 #define BILD_D(DHV) (a.T <= 8 ? launch_split<DHV, 1, true>(a, st) : a.T <= 16 ? launch_split<DHV, 1, false>(a, st) : launch_split<DHV, 2, false>(a, st))
     return a.d_head == 64 ? BILD_D(2) : BILD_D(4);

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "bild_bench.h"
+#include "attn_split.h"
 #include "bild_state.h"
 
 using namespace bild;
@@ -317,3 +318,12 @@ extern "C" int bild_debug_attn_shape(int heads, int d_head, int rows, int nkeys,
     return BILD_OK;
 }
 
+extern "C" int bild_debug_cache_rule(int heads, int d_head, int positions, int nkeys, int32_t out[3]) {
+    if (!out || heads < 1 || d_head < 8 || d_head > 128 || positions < 1 || nkeys < 1) return BILD_EINVAL;
+    out[0] = cache_in_int(positions, (size_t)heads * d_head, 2) ? 1 : 0;
+    int splits, waves;
+    attn_split_shape(heads, d_head, heads * d_head, positions, nkeys, &splits, &waves);
+    out[1] = splits;
+    out[2] = waves;
+    return BILD_OK;
+}

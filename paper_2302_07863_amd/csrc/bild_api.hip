@@ -433,7 +433,8 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             want(M.hb, sizeof(uint16_t) * 2 * kMaxRows * F);
             want(M.ssq, sizeof(float) * (kMaxSsqParts + 8) * kMaxRows);
         }
-        if (s->one_kernel && m->cfg.pos != BILD_POS_ROPE) {
+        const bool in_int = cache_in_int(s->cap_len, I, esz) && (!m->cfg.cross_attn || cache_in_int(s->cap_src, I, esz));
+        if (s->one_kernel && in_int && m->cfg.pos != BILD_POS_ROPE) {
             const int die = s->one_die && s->cus == 256 ? pass_die_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), !bf16) : 0;
             M.pass_groups = bf16 ? pass_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus) : die;
             if (M.pass_groups) {
@@ -443,8 +444,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
                 for (int r = 0; r < kPassRooms; ++r) want(M.pass_turns[r], pass_turns_bytes(M, r));
             }
         }
-        // (a layer's cache is addressed by 32-bit byte offsets)
-        if (s->one_kernel && bf16 && !m->cfg.cross_attn && m->cfg.pos != BILD_POS_RELATIVE && !M.pass_groups && (size_t)s->cap_len * I * 2 < (size_t)1 << 31) {
+        if (s->one_kernel && in_int && bf16 && !m->cfg.cross_attn && m->cfg.pos != BILD_POS_RELATIVE && !M.pass_groups) {
             M.pass_groups = wide_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus);
             if (M.pass_groups) {
                 M.pass_wide = true;
@@ -744,7 +744,7 @@ int emit_attention_split(bild_state* s, const ModelState& M, const AttnArgs& a, 
     std::memset((void*)&b, 0, sizeof(b));
     *done = false;
     if (M.m->cfg.dtype != BILD_DT_BF16 || a.rel_bias || a.T > kMaxRows || !s->split_part) return BILD_OK;
-    attn_split_shape(a.heads, a.d_head, nkeys, &b.splits, &b.waves);
+    attn_split_shape(a.heads, a.d_head, a.i_dim, a.vcap, nkeys, &b.splits, &b.waves);
     if (!b.splits) return BILD_OK;
     b.q = a.q; b.k = a.k; b.v = a.v; b.vcap = a.vcap; b.i_dim = a.i_dim; b.heads = a.heads; b.d_head = a.d_head; b.T = a.T;
     b.causal = a.causal; b.len_ptr = a.len_ptr; b.scale = a.scale;

@@ -140,3 +140,18 @@ def test_launch_shapes_of_ragged_widths_keep_a_power_of_two_of_input_slices():
                     s = b.gemm_shape(n, k, rows, False, False, dtype)
                     assert s["wk"] in (1, 2, 4, 8) and s["nwv"] in (1, 2, 4, 8) and s["nwv"] % s["wk"] == 0, (n, k, rows, s)
                     assert s["wk"] <= max(1, min(s["kc"], k) // kt), (n, k, rows, s)
+
+
+@pytest.mark.parametrize("heads,d_head", [(32, 128), (16, 64), (16, 128)])
+def test_caches_past_32_bit_offsets_stay_with_64_bit_addresses(heads, d_head):
+    """Keys of a layer lie [position][heads * d_head] in bf16: the kernels with 32-bit offsets take a cache below 2 GiB only."""
+    last = (1 << 31) // (heads * d_head * 2) - 1
+    if heads * d_head == 4096:
+        assert last == 262143
+    for positions in (32, 8192, last):
+        for nkeys in (64, positions):
+            s = b.cache_rule(heads, d_head, positions, nkeys)
+            assert s["one_kernel"] == 1 and 1 <= s["splits"] <= 16 and s["waves"] in (4, 8), (positions, s)
+    for positions in (last + 1, last + 33, 2 * (last + 1), 4 * (last + 1)):
+        for nkeys in (64, positions):
+            assert b.cache_rule(heads, d_head, positions, nkeys) == dict(one_kernel=0, splits=0, waves=0), positions
