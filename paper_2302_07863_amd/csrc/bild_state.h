@@ -50,7 +50,9 @@ class HeadPool {
     std::vector<HeadScratch> kept;
 
 public:
-    HeadScratch take(size_t bytes) {
+    // For a call on stream `st`: what a fresh buffer has to hold is put there on it, in front of the call's kernels.  (A fill on the null stream
+    // is not ordered with a stream that does not wait for it.)
+    HeadScratch take(size_t bytes, hipStream_t st) {
         HeadScratch b;
         if (hipGetDevice(&b.dev) != hipSuccess) return b;
         {
@@ -64,7 +66,7 @@ public:
         }
         b.bytes = bytes;
         if (hipMalloc(&b.p, bytes) != hipSuccess) b.p = nullptr;
-        if (b.p && hipMemset(b.p, 0, std::min(bytes, (size_t)256)) != hipSuccess) {  // (the count of workgroups that arrive)
+        if (b.p && hipMemsetAsync(b.p, 0, std::min(bytes, (size_t)256), st) != hipSuccess) {  // (the count of workgroups that arrive)
             (void)hipFree(b.p);
             b.p = nullptr;
         }

@@ -166,6 +166,11 @@ int head_sweep_run(const bild_model* m, const float* x, int rows, const int32_t*
 }
 int sweep_groups(const bild_model* m, int rows) { return m->cfg.dtype == BILD_DT_BF16 ? head_groups(m->head, rows) : 0; }
 
+bool all_done(const unsigned* done, unsigned call, int rows) {
+    for (int r = 0; r < rows; ++r)
+        if (__atomic_load_n(done + r, __ATOMIC_ACQUIRE) != call) return false;
+    return true;
+}
 // Whether all rows' results are in memory, seen in the words the kernel leaves in pinned memory: some microseconds before the stream's
 // completion reaches the host.  Not for long: what else is on the stream is waited for without spinning.
 bool rows_done(const unsigned* done, unsigned call, int rows) {
@@ -196,7 +201,7 @@ extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows
     GemmArgs g = head_gemm(m, x_dev, rows, targets_dev, nullptr, (const int*)slots);
     const int groups = sweep_groups(m, rows);
     const size_t bytes = kHdrBytes + (size_t)std::max(g.part_ld, groups) * sizeof(StatPart) * rows;
-    HeadScratch b = m->head_pool.take(bytes);
+    HeadScratch b = m->head_pool.take(bytes, st);
     if (!b.p) return BILD_ENOMEM;
     g.zt = (float*)((char*)b.p + 256);
     g.part = (StatPart*)((char*)b.p + kHdrBytes);
@@ -205,8 +210,12 @@ extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows
     b.calls += 1;
     int rc = groups ? head_sweep_run(m, x_dev, rows, targets_dev, out_dev, st, g, groups, rows <= 8, b.done_dev, b.calls)
                     : head_stats_run(m, rows, targets_dev, out_dev, st, g, b.done_dev, b.calls);
-    if (!(rc == BILD_OK && b.done && rows_done(b.done, b.calls, rows)) && hipStreamSynchronize(st) != hipSuccess && rc == BILD_OK) rc = BILD_EHIP;  // the scratch is in use until here
-    m->head_pool.give(b);
+    // the scratch is in use until here
+    const bool seen = rc == BILD_OK && b.done && rows_done(b.done, b.calls, rows);
+    if (!seen && hipStreamSynchronize(st) != hipSuccess && rc == BILD_OK) rc = BILD_EHIP;
+    if (!seen && rc == BILD_OK && b.done && !all_done(b.done, b.calls, rows)) rc = BILD_EHIP;  // (nobody wrote the results)
+    if (rc == BILD_OK) m->head_pool.give(b);
+    else b.release();  // what it holds is not known
     return rc;
 }
 

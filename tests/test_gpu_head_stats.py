@@ -1,5 +1,8 @@
 """bild_head_stats: the fused final norm + LM head + softmax statistics as a call of its own, on hidden rows the
 caller holds on the device, against the oracle's head and policy quantities (Sections 3.2-3.4)."""
+import ctypes as C
+import threading
+
 import numpy as np
 import pytest
 
@@ -8,7 +11,7 @@ import oracle
 import paper_2302_07863_amd as pkg
 from paper_2302_07863_amd import binding as b
 from tests import parity
-from tests.hipmem import DeviceArray
+from tests.hipmem import DeviceArray, hip
 
 pytestmark = pytest.mark.gpu
 
@@ -122,3 +125,52 @@ def test_sweep_shapes(d, vocab):
         for k in ("zmax", "argmax", "z_target"):
             assert (got[k] == other[k]).all(), (rows, k)
         assert np.abs(got["lse"] - other["lse"]).max() <= 2e-6 * max(1.0, float(np.abs(got["lse"]).max()))
+
+
+NON_BLOCKING = 1  # hipStreamNonBlocking
+
+
+def _stream():
+    s = C.c_void_p()
+    assert hip().hipStreamCreateWithFlags(C.byref(s), NON_BLOCKING) == 0
+    return s
+
+
+@pytest.mark.parametrize("rows", [1, 9])  # joined by the sweep's last workgroup, and by a launch of its own
+def test_first_calls_on_streams_that_do_not_wait_for_the_null_stream(rows):
+    """A fresh scratch is made ready on the caller's stream: the call ends while the null stream still works, with the oracle's
+    results; then two threads at once, each with a stream and a buffer of its own."""
+    cfg = bi.toy_pair(dtype=bi.DT_BF16, tied=False, vocab=40000)
+    _, wl = bi.make_pair_weights(cfg)
+    shape = cfg.large
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((rows, shape.d)).astype(np.float32)
+    targets = rng.integers(0, shape.vocab, size=rows).astype(np.int32)
+    xd, td = DeviceArray(x), DeviceArray(targets)
+    # (the kernels are loaded, and a model's first call is over, before the model that counts is made)
+    run_head_stats(parity.make_gpu_model(shape, wl), x, targets)
+    model, out, s = parity.make_gpu_model(shape, wl), DeviceArray(nbytes=rows * 16), _stream()
+    a, c = DeviceArray(nbytes=1 << 30), DeviceArray(nbytes=1 << 30)
+    for _ in range(200):  # 2 GiB of traffic each: some 80 ms on the null stream
+        assert hip().hipMemcpyAsync(a.ptr, c.ptr, 1 << 30, 3, None) == 0
+    b.head_stats(model, xd.ptr.value, rows, td.ptr.value, out.ptr.value, s.value)
+    busy = hip().hipStreamQuery(None)
+    got = out.to_host(b.ROW_STATS_DTYPE, rows)
+    assert busy == 600  # hipErrorNotReady: nothing in the call has waited for the null stream
+    check_against_oracle(shape, wl, x, targets, got, parity.logit_tol(cfg))
+    model, outs, streams, start = parity.make_gpu_model(shape, wl), [DeviceArray(nbytes=rows * 16) for _ in range(2)], [_stream(), _stream()], threading.Barrier(2)
+
+    def work(i):
+        start.wait()
+        for _ in range(20):
+            b.head_stats(model, xd.ptr.value, rows, td.ptr.value, outs[i].ptr.value, streams[i].value)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for o in outs:
+        assert (o.to_host(b.ROW_STATS_DTYPE, rows) == got).all()
+    for q in [s] + streams:
+        assert hip().hipStreamDestroy(q) == 0
