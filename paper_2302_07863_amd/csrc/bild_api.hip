@@ -1239,7 +1239,8 @@ int emit_layers(bild_state* s, int w, int T, int key_hint, bool reads_hidden, bo
                 bool done = false;
                 // (16 layers 2048 wide with the projection that joins the keys / with this kernel, 104, 340, 1064, 4137 keys: 632 / 607,
                 // 642 / 642, 670 / 659, 777 / 756 us a pass; 8 layers 4096 wide 759 / 743, 767 / 760, 785 / 771, 845 / 843)
-                int rc = T == 1 && d > 1024 ? emit_attention_split(s, M, a, key_hint, &done) : BILD_OK;
+                // (it writes fp32 rows, not the planes that the projection reads where producers hand those over)
+                int rc = T == 1 && d > 1024 && !planes ? emit_attention_split(s, M, a, key_hint, &done) : BILD_OK;
                 if (done) merge_splits = 1;
                 if (rc == BILD_OK && !done) rc = emit_attention(s, M, a, key_hint, &merge_splits);
                 if (rc) return rc;

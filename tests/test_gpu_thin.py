@@ -66,3 +66,15 @@ def test_the_same_pass_twice_gives_the_same_bits(monkeypatch):
             st.large_verify(float("inf"), draft=draft)
             seen.append(np.stack([st.debug_logits(pkg.LARGE, i) for i in range(rows)]))
         assert all((s == seen[0]).all() for s in seen[1:]), rows
+
+
+def test_single_rows_whose_producers_hand_over_planes(monkeypatch):
+    """BILD_PRE_MIN_ROWS=1: the output projection of a single row reads the attention's planes, whichever kernel leaves them."""
+    cfg = bi.toy_pair(**{**dict(dtype=bi.DT_BF16, truncate=True, n_src=40, max_new=8), **WIDE, "d": 1280, "heads": 10, "d_ff": 96})
+    R = Rig(cfg)
+    ref = oracle.bild_generate(R.req, 0.4, 1.0, 4, 8, keep_logits=True)
+    monkeypatch.setenv("BILD_ONE_KERNEL", "0")
+    monkeypatch.setenv("BILD_PRE_MIN_ROWS", "1")
+    st = R.state(cfg.max_new, 8)
+    st.encode(R.src)
+    parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, cfg)
