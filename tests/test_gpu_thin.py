@@ -75,6 +75,6 @@ def test_single_rows_whose_producers_hand_over_planes(monkeypatch):
     ref = oracle.bild_generate(R.req, 0.4, 1.0, 4, 8, keep_logits=True)
     monkeypatch.setenv("BILD_ONE_KERNEL", "0")
     monkeypatch.setenv("BILD_PRE_MIN_ROWS", "1")
-    st = R.state(cfg.max_new, 8)
+    st = R.state(cfg.max_new, 4)
     st.encode(R.src)
     parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, cfg)
