@@ -220,13 +220,13 @@ __global__ __launch_bounds__(512, 1) void attn_split_kernel(const void* __restri
             float top = M;
 #pragma unroll
             for (int s = 0; s < 8; ++s) top = fmaxf(top, __uint_as_float(ml[s].x));
-            const float base = top == -INFINITY ? 0.f : top, f = fexp(M - base);
+            const float base = top == -INFINITY ? 0.f : top, f = fexp_full(M - base);
             M = top;
             L *= f;
             o *= f;
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
-                const float w = s0 + s < a.splits ? fexp(__uint_as_float(ml[s].x) - base) : 0.f;
+                const float w = s0 + s < a.splits ? fexp_full(__uint_as_float(ml[s].x) - base) : 0.f;
                 L += __uint_as_float(ml[s].y) * w;
                 o += p[s] * w;
             }

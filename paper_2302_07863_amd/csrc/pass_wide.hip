@@ -524,7 +524,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                     for (int s = 0; s < kWideSplits; ++s) all = fmaxf(all, __uint_as_float(ml[s].x));
 #pragma unroll
                     for (int s = 0; s < kWideSplits; ++s) {
-                        const float f = s < S ? fexp(__uint_as_float(ml[s].x) - all) : 0.f;
+                        const float f = s < S ? fexp_full(__uint_as_float(ml[s].x) - all) : 0.f;
                         sum += __uint_as_float(ml[s].y) * f;
                         j += f32x4{v[s].x, v[s].y, v[s].z, v[s].w} * f;
                     }
