@@ -417,6 +417,7 @@ hipError_t gemm_thin_init();
 hipError_t attn_split_init();
 hipError_t attn_tile_init();
 hipError_t pass_init();
+hipError_t wide_init();
 template <size_t N>
 inline hipError_t raise_lds_limit(const void* const (&fns)[N], int bytes) {
     for (const void* f : fns)

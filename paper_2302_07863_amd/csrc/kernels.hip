@@ -23,6 +23,7 @@
 // activations at fp32 accuracy by splitting each value into a high and a low bf16 part
 // and issuing two MFMAs per weight tile; the matrix cores have an order of magnitude
 // more throughput than the stream needs, so this is free.
+#include "head.h"
 #include "kernel_common.h"
 #include "gemm_body.h"
 
@@ -298,6 +299,8 @@ hipError_t kernels_init() {
     if (hipError_t e = attn_split_init(); e != hipSuccess) return e;
     if (hipError_t e = attn_tile_init(); e != hipSuccess) return e;
     if (hipError_t e = pass_init(); e != hipSuccess) return e;
+    if (hipError_t e = wide_init(); e != hipSuccess) return e;
+    if (hipError_t e = head_init(); e != hipSuccess) return e;
     return attention_init();
 }
 

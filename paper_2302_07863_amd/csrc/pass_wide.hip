@@ -615,12 +615,16 @@ int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     return wide_fits<Cut2048>(d, heads, F, gated, cus) || wide_fits<Cut4096>(d, heads, F, gated, cus) ? cus : 0;
 }
 
-hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
+hipError_t wide_init() {
     static hipError_t done = [] {
         const void* fns[] = {(const void*)wide_kernel<false, Cut2048>, (const void*)wide_kernel<true, Cut2048>, (const void*)wide_kernel<false, Cut4096>, (const void*)wide_kernel<true, Cut4096>};
         return raise_lds_limit(fns, 160 * 1024);
     }();
-    if (done != hipSuccess) return done;
+    return done;
+}
+
+hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
+    if (hipError_t e = wide_init(); e != hipSuccess) return e;
     const bool gated = a.act != BILD_ACT_RELU;
     if (a.groups < 1 || a.groups != wide_groups(a.d, a.heads, a.I / std::max(a.heads, 1), a.F, gated, a.groups) || a.T < 1 || a.T > kWideRows || a.room < a.T || a.cross || a.rel_bias ||
         !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr)
