@@ -8,6 +8,7 @@ import oracle
 import paper_2302_07863_amd as pkg
 from tests import parity
 from tests.test_gpu_parity import Rig
+from tests.test_gpu_pass_wide import one_token_moves
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +79,35 @@ def test_single_rows_whose_producers_hand_over_planes(monkeypatch):
     st = R.state(cfg.max_new, 4)
     st.encode(R.src)
     parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, cfg)
+
+
+@pytest.mark.parametrize("heads", [2, 16])
+def test_long_caches(heads, monkeypatch):
+    """Attention that joins its key ranges at more than 2048 keys: sixteen ranges a head, joined in two rounds (four heads), and more
+    blocks of 32 keys than ranges x waves, so that a wave loads a second one (32 heads).  Against the kernels they stand beside, from
+    which they differ by less than a quarter of what one other token among the earlier ones does."""
+    cfg = bi.toy_pair(dtype=bi.DT_BF16, cross=False, act=bi.ACT_SWIGLU, pos=bi.POS_ROPE, d=256, heads=heads, d_head=128 if heads == 2 else 64, d_ff=256, n_small=1, n_large=2, vocab=300,
+                      logit_scale=4.0, truncate=True, n_src=40, max_new=4240)
+    R = Rig(cfg)
+    monkeypatch.setenv("BILD_ONE_KERNEL", "0")
+    got = {}
+    for route in ("2", "99"):
+        monkeypatch.setenv("BILD_THIN_MIN_ROWS", route)
+        st = R.state(cfg.max_new, 31)
+        st.encode(R.src)
+        st.debug_enable_logits(True)
+        rows_seen = []
+        for have in (2040, 2049, 2100, 4170):
+            st.seq_truncate(R.n0)
+            st.force_tokens(R.n0, bi.make_tokens(cfg.large.vocab, have - R.n0, seed=have), have)
+            st.large_verify(float("inf"), draft=[])
+            for rows in (2, 8, 9, 17, 32):
+                st.seq_truncate(have)
+                st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+                rows_seen += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+        got[route] = np.stack(rows_seen)
+        moved = one_token_moves(st, R, 4170)
+        st.close()
+    worst = float(np.abs(got["2"] - got["99"]).max())
+    print("worst", worst, "one token", moved, flush=True)
+    assert worst <= min(moved / 4, 2 * parity.logit_tol(cfg))
