@@ -147,6 +147,7 @@ extern "C" int bild_model_create(const bild_model_config* cfg, const float* cons
     bild_model* m = new (std::nothrow) bild_model();
     if (!m) return BILD_ENOMEM;
     m->cfg = *cfg;
+    m->cfg.tie_shift %= cfg->vocab;  // (kernels take the row below vocab with one subtraction)
     const int d = cfg->d_model, I = m->inner(), F = cfg->d_ff, V = cfg->vocab;
     int i = 0, rc = BILD_OK;
 #define UP(call)                         \
@@ -1173,7 +1174,7 @@ int emit_layers(bild_state* s, int w, int T, int key_hint, bool reads_hidden, bo
     // Every workgroup of that projection repeats the gather, so it is taken only where one round of two pieces per
     // thread covers the row (a 4096-wide row in workgroups of two waves would be four dependent rounds: measured slower).
     bool embed_in_proj = s->fuse_embed && T == 1 && !planes && !above_trunk && (!e.sinusoidal || e.pe != nullptr) &&
-                         c.tie_shift >= 0 && c.tie_shift < c.vocab && layer0 < c.n_dec_layers;
+                         layer0 < c.n_dec_layers;
     if (embed_in_proj) {
         GemmArgs probe = gemm_base(m, m->dec[layer0].wqkv, M.x, d, T, m->dec[layer0].ln1);
         probe.epi = EPI_QKV;

@@ -198,3 +198,20 @@ def test_fp32_blocks_of_earlier_keys(shape, monkeypatch):
                 logits += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
         got[form] = np.stack(logits)
     assert float(np.abs(got["die"] - got["kernels"]).max()) <= 2 * parity.logit_tol(cfg)
+
+
+@pytest.mark.parametrize("one", ["1", "0"])
+@pytest.mark.parametrize("shape", [dict(d=256, heads=4, d_head=64, d_ff=512, dtype=bi.DT_BF16, truncate=True), dict(d=256, heads=4, d_head=64, d_ff=512, n_small=2),
+                                   dict(d=1280, heads=10, d_head=128, d_ff=96, dtype=bi.DT_BF16, truncate=True, cross=False, act=bi.ACT_SWIGLU, pos=bi.POS_ROPE, logit_scale=4.0)])
+def test_embedding_rows_past_twice_the_vocabulary(shape, one, monkeypatch):
+    """The row of token t is (t + tie_shift) mod vocab for every tie_shift: here five vocabularies and some more, bf16, fp32 and wide models,
+    passes in one kernel and as kernels of their own."""
+    monkeypatch.setenv("BILD_ONE_KERNEL", one)
+    cfg = bi.toy_pair(**{**dict(n_large=2, vocab=200, tie_shift=5 * 200 + 137, max_new=8), **shape})
+    R = Rig(cfg)
+    ref = oracle.bild_generate(R.req, 0.4, 1.0, 4, cfg.max_new, keep_logits=True)
+    st = R.state(cfg.max_new, 4)
+    st.encode(R.src)
+    parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, cfg)
+    routes = st.pass_routes()
+    assert (routes["chip"] + routes["die"] > 0) == (one == "1"), routes
