@@ -131,12 +131,16 @@ def verify(path: str) -> str:
     for i, seg in enumerate(segs[:len(t_values)]):
         T = t_values[i]
         lines.append(f"rows T={T}")
+        util = {}
         for k, ds in sorted(seg.items(), key=lambda kv: -len(kv[1])):
             names = sorted({c for d in ds for c in d})
             means = {c: sum(d.get(c, 0.0) for d in ds) / len(ds) for c in names}
             lines.append(f"  {k:34s} dispatches {len(ds):6d}  " + "  ".join(f"{c}={means[c]:.4g}" for c in names))
-            if k == "bild::gemm_kernel<*>" and "MfmaUtil" in means:
-                lines.append(f"mfma_util_T{T}={means['MfmaUtil'] / 100.0:.5f}")
+            util[k] = means.get("MfmaUtil")
+        # of the kernel that streams the layers' weights
+        main = next((k for k in ("bild::wide_kernel<*>", "bild::thin_kernel<*>", "bild::gemm_kernel<*>") if util.get(k) is not None), None)
+        if main:
+            lines.append(f"mfma_util_T{T}={util[main] / 100.0:.5f}")
     return "\n".join(lines)
 
 
