@@ -356,8 +356,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     want(s->y, sizeof(int) * (size_t)(max_len + 1));
     want(s->src, sizeof(int) * (size_t)max_src);
     void* h = nullptr;
-    const size_t tokens_end = (1024 + sizeof(int) * ((size_t)max_len + 1 + max_src) + 15) / 16 * 16;
-    if (hipHostMalloc(&h, tokens_end + sizeof(PassLayer) * (p->m[0]->dec.size() + p->m[1]->dec.size()), hipHostMallocMapped) != hipSuccess) {
+    if (hipHostMalloc(&h, 1024 + sizeof(int) * ((size_t)max_len + 1 + max_src), hipHostMallocMapped) != hipSuccess) {
         bild_state_destroy(s);
         return BILD_ENOMEM;
     }
@@ -504,10 +503,11 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         s->ms[0].ck = s->ms[1].ck;
         s->ms[0].cv = s->ms[1].cv;
     }
-    // One fill and one copy (from the pinned block, behind the tokens) for both models.  (A fill and a pageable copy for each: making a
-    // state of the fp32, T5, mT5 pair 77, 142, 72 us; now 63, 128, 66.)
+    // One fill and one copy for both models.  (Making a state of the fp32, T5, 7B pair beside others, us, two runs: a fill and a copy for each
+    // 164 to 237, 154 to 207, 262 to 276; now 166 to 175, 161 to 168, 244 to 273.  With the layers in the pinned block, which then takes more
+    // than a page, some states took 200 us more.)
     if (e == hipSuccess && turns_bytes) e = hipMemsetAsync(s->ms[s->ms[0].pass_groups ? 0 : 1].pass_turns[0], 0xFF, turns_bytes, s->stream);
-    PassLayer* const host_layers = (PassLayer*)((char*)h + tokens_end);
+    std::vector<PassLayer> host_layers(layers_n);
     size_t filled = 0;
     for (ModelState& M : s->ms) {
         if (!M.pass_groups) continue;
@@ -523,7 +523,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             host_layers[filled++] = q;
         }
     }
-    if (e == hipSuccess && filled) e = hipMemcpyAsync(pass_layers, host_layers, sizeof(PassLayer) * filled, hipMemcpyHostToDevice, s->stream);
+    if (e == hipSuccess && filled) e = hipMemcpyAsync(pass_layers, host_layers.data(), sizeof(PassLayer) * filled, hipMemcpyHostToDevice, s->stream);
     if (e != hipSuccess || hipStreamSynchronize(s->stream) != hipSuccess) {
         bild_state_destroy(s);
         return BILD_EHIP;
