@@ -164,7 +164,21 @@ int head_sweep_run(const bild_model* m, const float* x, int rows, const int32_t*
     }
     return BILD_OK;
 }
-int sweep_groups(const bild_model* m, int rows) { return m->cfg.dtype == BILD_DT_BF16 ? head_groups(m->head, rows) : 0; }
+// Its workgroups; 0: the GEMM's short workgroups and the merge.  One rule for both entry points, whose results are the same bits.  Up to eight
+// rows of matrices of 50 MB or so are the short workgroups', of which more are on a compute unit when weights begin to arrive.  us, short
+// workgroups / sweep, a call that does not wait and one that does (there the sweep joins its results itself), one row: 512 x 16 000 ids
+// 9.4 / 9.1, 17.1 / 16.8; x 32 128 9.9 / 10.4, 17.8 / 18.0; x 64 000 17.2 / 18.6, 25.0 / 24.0; 1024 x 4000 8.8 / 8.8, 16.8 / 16.6; x 16 000 9.9 / 10.4, 17.9 / 17.9;
+// x 32 128 16.7 / 18.4, 24.6 / 24.1; 2048 x 1000 9.7 / 10.4, 17.3 / 16.2; x 7809 10.3 / 11.4, 18.6 / 19.3; x 16 000 17.0 / 17.9, 24.7 / 24.2; 125 MB 512, 1024,
+// 2048 wide 32.7 / 27.7, 25.6 / 26.8, 28.2 / 26.8 and 41.2 / 33.0, 33.6 / 32.7, 35.7 / 32.3.  Two, four, eight rows: 512 x 64 000 20.7, 20.7, 21.2 / 18.3, 18.6,
+// 18.7; 1024 x 16 000 10.7, 11.4, 13.0 / 10.3, 10.8, 11.8; x 32 128 16.8, 17.1, 17.8 / 18.0, 18.2, 19.1; 2048 x 7809 11.4, 12.5, 14.7 / 11.5, 12.4, 13.8; x 16 000 17.4,
+// 17.4, 20.9 / 18.3, 19.2, 20.6.  From nine rows on the sweep is never slower.
+int sweep_groups(const bild_model* m, int rows) {
+    if (m->cfg.dtype != BILD_DT_BF16) return 0;
+    const int tk = m->head.tk;
+    const size_t mb = ((size_t)m->head.tn * tk * kTileBytes) >> 20;
+    const bool taken = rows > 8 || mb >= 96 || (rows > 1 ? mb < 48 || tk <= 16 : mb < (tk > 32 ? 8u : 24u));
+    return taken ? head_groups(m->head, rows) : 0;
+}
 
 bool all_done(const unsigned* done, unsigned call, int rows) {
     for (int r = 0; r < rows; ++r)
