@@ -253,8 +253,12 @@ int bild_greedy(bild_state* s, int which, const int32_t* src, int n_src, int max
  * maxima) and z_target = logit of targets_dev[row] (NaN without targets or for an id outside the vocabulary), so
  * that max p = exp(zmax - lse) and -ln p(target) = lse - z_target.  Logits are never written to memory.
  * x_dev [rows][d_model] fp32 (16-byte aligned), targets_dev [rows] int32 (nullable) and out_dev [rows] are DEVICE
- * memory of the caller, read and written by kernels on hip_stream (NULL: the default stream).  The call allocates
- * a scratch buffer for its kernels' partial results and returns after the stream has finished with it. */
+ * memory of the caller, read and written by kernels on hip_stream (NULL: the default stream), behind what is on that
+ * stream already.  The call takes a scratch buffer for its kernels' partial results from a pool of the model's, or
+ * allocates one, and returns when the results are in memory: the kernels then read and write nothing of the caller's
+ * or of the scratch any more.  The stream itself may still be retiring the launches (hipStreamQuery: not ready), and an
+ * error that the runtime finds afterwards is reported by the next call that waits for the stream.  The host polls for
+ * the results for up to 2 ms and then waits for the stream. */
 typedef struct bild_row_stats {
     float zmax;
     float lse;
@@ -264,12 +268,13 @@ typedef struct bild_row_stats {
 int bild_head_stats(const bild_model* m, const float* x_dev, int rows, const int32_t* targets_dev,
                     bild_row_stats* out_dev, void* hip_stream);
 /* bild_head_stats for callers that cannot allocate device memory (code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc): same arguments, same kernels, same results, but the scratch buffer is a
+ * loops, harnesses that forbid hipMalloc): same arguments, same results, but the scratch buffer is a
  * 4 MiB device array inside the library (one per GPU, held until the process ends), and the call neither allocates
- * nor frees anything and does not wait for the stream: it returns once its three kernels are enqueued on hip_stream.
+ * nor frees anything and does not wait for the stream: it returns once its two kernels (the head, the merge of its
+ * workgroups' statistics) are enqueued on hip_stream.
  * Limit: the head's launch must not have more than 8191 workgroups (one 512-byte block of partial statistics each),
  * else BILD_ECAP; vocabularies up to 250112 at widths of 512 and 1024 are well inside it.  Every call on a GPU uses
- * that GPU's one array, which keeps the previous call's contents (the call clears what it reads before writing): calls
+ * that GPU's one array, which keeps the previous call's contents (the head writes all that the merge reads): calls
  * that overlap on one GPU - two streams, two threads - race; calls on one stream are ordered and safe. */
 int bild_head_stats_static(const bild_model* m, const float* x_dev, int rows, const int32_t* targets_dev,
                            bild_row_stats* out_dev, void* hip_stream);

@@ -13,8 +13,8 @@
 // Up to eight rows one operand holds the high parts of the rows in its columns 0 .. 7 and the low parts in 8 .. 15 (PACK): half the
 // loads of x and half the products.
 //
-// 7B shape, us per launch with rows staged in every workgroup and now (floor at 5.5 TB/s): 32 rows q, k, v 33.4, 24.9 (18.3); gated FFN
-// input 46.5, 40.9 (32.8); residual projections, mean of two, 28.6, 18.9 (11.2); 8 rows 20.1, 39.0, 14.8.  The whole pass over 1024
+// 7B shape, us per launch with rows staged in every workgroup and now (floor at 5.5 TB/s): 32 rows q, k, v 33.4, 23.1 (18.3); gated FFN
+// input 46.5, 39.7 (32.8); residual projections, mean of two, 28.6, 18.1 (11.2); 11 rows 20.4, 38.3, 16.2.  The whole pass over 1024
 // keys, 2, 4, 8, 12, 16, 32 rows: 3406, 3443, 3592, 3869, 4045, 5053 -> 3156, 3160, 3177, 3367, 3379, 3742 us (attn_split.hip included).
 // Without slices the 32-row residual projections take 25.3; sliced q, k, v 34.6 instead of 30.6; workgroups that begin at the same
 // inputs 2 % more in all; the sums of squares fetched one load after the other in front of the weights 2.5 us a launch.

@@ -9,8 +9,8 @@
 //
 // us per launch, floor at 6.1 TB/s / workgroups of eight feature tiles that each stage all rows / now: 32 128 x 512, 1 and 32 rows 5.4 /
 // 10.3, 16.6 / 11.3, 13.9; 250 112 x 512 42 / 52.8, 80.3 / 43.9, 45.3; 250 112 x 1024, 1, 21, 32 rows 84 / 109, 133, 141 / 91, 93, 95;
-// 131 072 x 2048, 1, 21 rows 88 / 103, 136 / 94, 103.  bild_head_stats of one row, 32 128 x 512: 22.4 -> 19.9 (22.2 when the host waits for the
-// stream and not for the word the kernel leaves it).  Sums against 64 bits as before: rms of lse 4.1e-7, 6.3e-7, 6.4e-7 at 1000,
+// 131 072 x 2048, 1, 21 rows 88 / 103, 136 / 94, 103.  bild_head_stats where this kernel joins and the host polls, one row: 512 x 16 000 ids 21.7 -> 16.6,
+// 2048 x 32 000 40.3 -> 32.0 (the short workgroups and the merge with the host polling 17.1, 35.7: where they are taken, see head_stats.hip).  Sums against 64 bits as before: rms of lse 4.1e-7, 6.3e-7, 6.4e-7 at 1000,
 // 32 128 and 250 112 ids (4.0e-7, 6.4e-7, 6.3e-7).
 #include "head.h"
 

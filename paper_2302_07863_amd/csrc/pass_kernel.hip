@@ -15,7 +15,9 @@
 //     workgroups stay off the fabric.  A line that is polled before it is written has to be taken away from eight L2s and
 //     fetched again, 0.3 us: where a stage's results cannot be there yet its readers sleep first (nap: q, k, v and the FFN's
 //     input projection 0.35 us, its output projection 0.65; together 474 -> 447 us a pass of the T5-large shape; half as much
-//     again, or naps in front of the other stages, gain nothing);
+//     again, or naps in front of the other stages, gain nothing.  12 layers over the chip, 64 source tokens, without / with half / with
+//     all of it, one row: 256 wide 186, 178, 181, 512 199, 191, 193, 768 213, 206, 207, 1024 244, 237, 237; 16 rows 206, 196, 198; 233, 225, 223; 262,
+//     253, 249; 303, 291, 288);
 //   - what belongs together lies together: a row's sums of squares beside its planes (a line that all producers write is taken
 //     away from its readers by each of them: 623 -> 714 us when the sums had two lines of their own), a head's query, keys
 //     and values of the new rows, which it needs before they can be read from the caches;
