@@ -14,13 +14,15 @@
 //     and read back took 1.8 us over the chip.  A read misses its die's L2 only after somebody has written the line, so waiting
 //     workgroups stay off the fabric.  A line that is polled before it is written has to be taken away from eight L2s and
 //     fetched again, 0.3 us: where a stage's results cannot be there yet its readers sleep first (nap: q, k, v and the FFN's
-//     input projection 0.35 us, its output projection 0.65; together 474 -> 447 us a pass of the T5-large shape; half as much
-//     again, or naps in front of the other stages, gain nothing.  12 layers over the chip, 64 source tokens, without / with half / with
-//     all of it, one row: 256 wide 186, 178, 181, 512 199, 191, 193, 768 213, 206, 207, 1024 244, 237, 237; 16 rows 206, 196, 198; 233, 225, 223; 262,
-//     253, 249; 303, 291, 288);
+//     input projection 0.25 us, its output projection 0.4, behind a gated input projection 0.65.  T5-large shape, one row, without / with:
+//     q, k, v 413 / 413, input 413 / 412, output 418 / 406; two to eight rows gain 2, 5 to 10 and 10 us by the three.  mT5-large shape,
+//     eight rows, output 550 / 538; one row 480 / 479.  Twice as long loses 5 to 20 us everywhere, naps in front of the other stages
+//     gain nothing or 2 us.  As much was measured from 256 to 1024 wide with somewhat longer ones, 2 to 20 us of 180 to 290);
 //   - what belongs together lies together: a row's sums of squares beside its planes (a line that all producers write is taken
 //     away from its readers by each of them: 623 -> 714 us when the sums had two lines of their own), a head's query, keys
-//     and values of the new rows, which it needs before they can be read from the caches;
+//     and values of the new rows, which it needs before they can be read from the caches.  Sixteen features' high and low parts
+//     are one store, and with one row their sum of squares lies in the same line and comes by the same load: a line that is written
+//     twice is fetched twice (one row, T5-large shape, 441 -> 411 us; in a kernel of hand-overs alone 2.0 -> 1.3 us a stage);
 //   - weights depend on nothing: they are requested while a workgroup has nothing else to do, those of the FFN and of the next
 //     layer during the cross-attention (a wave's loads come back in order, so a request just before a wait delays what follows);
 //   - eight waves share a feature tile's inputs; activations arrive as high and low bf16 parts in the order of the matrix core's
@@ -40,6 +42,9 @@
 // 448, 456, 475, 544, 552; mT5-large shape 1 and 8 rows 726, 1045 / 644, 666 / 443, 462.  fp32, 256 wide, 32 source tokens, as separate kernels
 // and now: 2 layers, one row 68, 40.5 (49.7 with the matrix cores for it, 43.5 with blocks of 32 keys); 4 layers, 1, 4, 11 rows 120, 145,
 // 154, 63, 74, 78.
+// Loads of several tiles, one store and one line a producer (multiply, put_planes), with head and policy, before / with: T5-large shape,
+// 1, 2, 4, 8 rows 455, 455, 465, 479 / 412, 429, 455, 474; mT5-large shape 514, 511, 523, 537 / 477, 497, 515, 532; T5-small 97 / 96; fp32, 4
+// layers, one row 60.4 / 57.5.
 //
 // A workgroup that has polled `spins` times in vain flags the pass as failed and walks on without waiting again (nothing
 // handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
@@ -339,6 +344,7 @@ __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; 
 template <bool GATED, bool PACK, class Cut, class Walk>
 __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     constexpr int QT = Cut::QT, OT = Cut::OT, FT = Cut::FT, KD = Cut::KD, KF = Cut::KF;
+    constexpr bool RD = Walk::template side<KD>() > 1, RF = Walk::template side<KF>() > 1;  // (tiles beside each other: sums by row)
     int T = a.T, d = a.d, I = a.I, F = a.F;
     const int base = groups - a.heads;  // the workgroups with a head each follow
     const int len = *a.len_ptr;
@@ -360,8 +366,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         if (mine) {
             const float w[4] = {x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w};
             const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
-            put_planes<PACK, true>(c, planes, n0(), w);
-            if (c.g == 0) {
+            put_planes<PACK, true>(c, planes, n0(), w, ss);
+            if (!Walk::ROOM1 && c.g == 0) {
                 const int off = Walk::F32 ? (n0() >> 4) * tile_bytes(true, c.R, true) + c.R * 64 + c.tok * 4
                                           : (n0() >> 5) * tile_bytes(true, c.R, false) + c.R * 128 + (c.tok * 2 + ((n0() >> 4) & 1)) * 4;
                 if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(planes), off, 0, Walk::kOut);
@@ -369,8 +375,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             }
         }
     };
-    auto add = [&] {
-        const f32x4 s = total<OT, PACK>(c, c.wave);
+    auto add = [&](auto row) {
+        const f32x4 s = total<OT, PACK, decltype(row)::value>(c, c.wave);
         x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]);
     };
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
@@ -415,12 +421,12 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             char* kept = pinned(seg == 1 ? L->kc : L->vc);
             char* out = pinned(z + (seg == 0 ? a.at.q : seg == 1 ? a.at.k : a.at.v));
             f32x4 acc[QT];
-            c.template nap<350>();
+            c.template nap<250>();
             multiply<KD, QT, PACK, true>(c, acc, Wq, xs, d >> c.KS);
-            leave<QT, true, Walk::ONE>(c, acc);
+            leave<QT, true, RD>(c, acc);
             if (c.wave < QT) {
                 const float f = norm_factor(c, d, a.eps);
-                const f32x4 s = total<QT, PACK>(c, c.wave) * f;
+                const f32x4 s = total<QT, PACK, RD>(c, c.wave) * f;
                 const int nn = (c.wg * QT + c.wave) * 16 + c.g * 4 - seg * I, pos = len + c.tok;
                 const Rsrc o = whole(out), n = whole(out + c.clear), kv = whole(kept);
                 const int hd = nn >> 6, f0 = nn & 63;
@@ -474,8 +480,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             char* ox = pinned(z + a.at.x2);
             f32x4 acc[OT];
             multiply<KD, OT, PACK, false>(c, acc, Wo, xs, I >> c.KS);
-            leave<OT, false, Walk::ONE>(c, acc);
-            if (mine) add();
+            leave<OT, false, RD>(c, acc);
+            if (mine) add(std::bool_constant<RD>{});
             publish(gn, ox);
         }
         const char* xf = z + a.at.x2;  // what the FFN reads
@@ -492,8 +498,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 char* ox = pinned(z + a.at.x3);
                 f32x4 acc[OT];
                 multiply<KD, OT, PACK, false>(c, acc, Wo, xs, I >> c.KS);
-                leave<OT, false, Walk::ONE>(c, acc);
-                if (mine) add();
+                leave<OT, false, RD>(c, acc);
+                if (mine) add(std::bool_constant<RD>{});
                 publish(gn, ox);
             }
             xf = z + a.at.x3;
@@ -505,19 +511,19 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             char* out = pinned(z + a.at.h);
             constexpr int FW = GATED ? FT / 2 : FT;  // waves with results
             f32x4 acc[FT];
-            c.template nap<350>();
+            c.template nap<250>();
             multiply<KD, FT, PACK, true>(c, acc, Wi, xs, d >> c.KS);
-            leave<FT, true, Walk::ONE>(c, acc);
+            leave<FT, true, RD>(c, acc);
             const int tile = c.wg * FW + c.wave;  // of the hidden state
             if (c.wave < FW && tile < F >> 4) {
                 const float r = norm_factor(c, d, a.eps);
                 float w[4];
                 if constexpr (GATED) {
-                    const f32x4 s = total<FT, PACK>(c, 2 * c.wave) * r, u = total<FT, PACK>(c, 2 * c.wave + 1) * r;
+                    const f32x4 s = total<FT, PACK, RD>(c, 2 * c.wave) * r, u = total<FT, PACK, RD>(c, 2 * c.wave + 1) * r;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(s[v]) : silu_f(s[v])) * u[v];
                 } else {
-                    const f32x4 s = total<FT, PACK>(c, c.wave) * r;
+                    const f32x4 s = total<FT, PACK, RD>(c, c.wave) * r;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = fmaxf(s[v], 0.f);
                 }
@@ -532,10 +538,10 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             const char* xs = pinned(hidden);
             char* ox = pinned(z + a.at.x1);
             f32x4 acc[OT];
-            c.template nap<650>();
+            c.template nap<GATED ? 650 : 400>();
             multiply<KF, OT, PACK, false>(c, acc, Wf, xs, F >> c.KS);
-            leave<OT, false, Walk::ONE>(c, acc);
-            if (mine) add();
+            leave<OT, false, RF>(c, acc);
+            if (mine) add(std::bool_constant<RF>{});
             if (!last) publish(next_gain, ox);
         }
     }
@@ -549,6 +555,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
 template <bool GATED, bool PACK, class Cut, class Walk>
 __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
     constexpr int KD = Cut::KD;
+    constexpr bool RD = Walk::template side<KD>() > 1;
     const int base = groups - a.heads, h = c.wg - base;
     int T = a.T, d = a.d, I = a.I;
     const int len = *a.len_ptr, nsrc = a.cross ? *a.nsrc_ptr : 0;
@@ -590,9 +597,9 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
             const float sc = a.att_scale;
             f32x4 acc[4];
             multiply<KD, 4, PACK, true>(c, acc, Wc, xs, d >> c.KS);
-            leave<4, true, Walk::ONE>(c, acc);
+            leave<4, true, RD>(c, acc);
             if (c.wave < 4) {
-                const f32x4 s = total<4, PACK>(c, c.wave) * norm_factor(c, d, a.eps);
+                const f32x4 s = total<4, PACK, RD>(c, c.wave) * norm_factor(c, d, a.eps);
                 *(f32x4*)((float*)(c.lds + kQ) + c.tok * kQLd + c.wave * 16 + c.g * 4) = s;
             }
             lds_barrier();
@@ -602,11 +609,12 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
     }
 }
 
-template <bool GATED, bool PACK, bool DIE, bool F32, bool ONE>
+template <bool GATED, bool DIE, bool F32, int ROOM>
 __global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     using Cut = std::conditional_t<F32, DieCutF32, std::conditional_t<DIE, DieCut, ChipCut>>;
-    Walk<DIE, F32, ONE> c;
+    constexpr bool PACK = !F32 && ROOM <= 8;
+    Walk<DIE, F32, ROOM> c;
     c.lds = smem;
     c.failed = a.sync + kPassSyncWords - 1;
     c.spins = a.spins;
@@ -677,11 +685,10 @@ PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide) {
 
 hipError_t pass_init() {
     static hipError_t done = [] {
-        const void* fns[] = {(const void*)pass_kernel<false, true, true, false, false>, (const void*)pass_kernel<true, true, true, false, false>,
-                             (const void*)pass_kernel<false, true, false, false, false>, (const void*)pass_kernel<true, true, false, false, false>,
-                             (const void*)pass_kernel<false, false, false, false, false>, (const void*)pass_kernel<true, false, false, false, false>,
-                             (const void*)pass_kernel<false, false, true, true, false>, (const void*)pass_kernel<true, false, true, true, false>,
-                             (const void*)pass_kernel<false, false, true, true, true>, (const void*)pass_kernel<true, false, true, true, true>};
+#define BILD_P(DV, FV, RV) (const void*)pass_kernel<false, DV, FV, RV>, (const void*)pass_kernel<true, DV, FV, RV>
+        const void* fns[] = {BILD_P(true, false, 1), BILD_P(true, false, 2), BILD_P(true, false, 4), BILD_P(false, false, 1), BILD_P(false, false, 2), BILD_P(false, false, 4),
+                             BILD_P(false, false, 8), BILD_P(false, false, 16), BILD_P(true, true, 1), BILD_P(true, true, 0)};
+#undef BILD_P
         return raise_lds_limit(fns, 160 * 1024);
     }();
     return done;
@@ -695,23 +702,24 @@ hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
     const size_t smem = kRel + (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);
     if (smem > 160 * 1024) return hipErrorInvalidValue;
     const bool gated = a.act != BILD_ACT_RELU;
-#define BILD_P(GV, PV, DV, FV, OV)                                                                                                   \
+#define BILD_P(DV, FV, RV)                                                                                                   \
     do {                                                                                                                     \
-        hipLaunchKernelGGL((pass_kernel<GV, PV, DV, FV, OV>), dim3(grid), dim3(kPassThreads), smem, st, a);                          \
+        if (gated) hipLaunchKernelGGL((pass_kernel<true, DV, FV, RV>), dim3(grid), dim3(kPassThreads), smem, st, a);         \
+        else hipLaunchKernelGGL((pass_kernel<false, DV, FV, RV>), dim3(grid), dim3(kPassThreads), smem, st, a);              \
         return hipGetLastError();                                                                                            \
     } while (0)
-#define BILD_PG(PV, DV, FV, OV)                                                                                                      \
-    do {                                                                                                                     \
-        if (gated) BILD_P(true, PV, DV, FV, OV);                                                                                     \
-        BILD_P(false, PV, DV, FV, OV);                                                                                               \
-    } while (0)
-    if (a.f32 && a.T == 1) BILD_PG(false, true, true, true);
-    if (a.f32) BILD_PG(false, true, true, false);
-    if (a.die) BILD_PG(true, true, false, false);
-    if (a.T <= 8) BILD_PG(true, false, false, false);
-    BILD_PG(false, false, false, false);
-#undef BILD_PG
+    if (a.f32 && a.room == 1) BILD_P(true, true, 1);
+    if (a.f32) BILD_P(true, true, 0);
+    if (a.die && a.room == 1) BILD_P(true, false, 1);
+    if (a.die && a.room == 2) BILD_P(true, false, 2);
+    if (a.die && a.room == 4) BILD_P(true, false, 4);
+    if (!a.die && a.room == 1) BILD_P(false, false, 1);
+    if (!a.die && a.room == 2) BILD_P(false, false, 2);
+    if (!a.die && a.room == 4) BILD_P(false, false, 4);
+    if (!a.die && a.room == 8) BILD_P(false, false, 8);
+    if (!a.die && a.room == 16) BILD_P(false, false, 16);
 #undef BILD_P
+    return hipErrorInvalidValue;
 }
 
 }  // namespace bild

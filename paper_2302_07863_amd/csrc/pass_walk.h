@@ -34,10 +34,28 @@ constexpr unsigned kNotThere = 0xFFFFFFFFu;  // (two NaNs of a kind no conversio
 constexpr int kRedBytes = kPassWaves * 6 * 1024;  // twice: a stage's sums are read while the next one's are written
 constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kSq = kQ + 16 * kQLd * 4, kSqBytes = kPassWaves * 16 * 4, kRel = kSq + 2 * kSqBytes;
 
-template <bool DIE, bool FP32, bool ONE_ROW>
-struct Walk {
+// Rows there is room for in the hand-over memory (the layout's): known to the kernel, or (0) not.
+template <int ROOM>
+struct Room {
+    static constexpr int R = ROOM;
+    __device__ __forceinline__ void room(int) {}
+};
+template <>
+struct Room<0> {
+    int R;
+    __device__ __forceinline__ void room(int r) { R = r; }
+};
+template <bool DIE, bool FP32, int ROOM>
+struct Walk : Room<ROOM> {
+    using Room<ROOM>::R;
     static constexpr bool F32 = FP32;      // of an fp32 model
-    static constexpr bool ONE = ONE_ROW;   // ... and one row (see multiply)
+    static constexpr bool ONE = FP32 && ROOM == 1;  // ... and one row (see multiply)
+    static constexpr bool ROOM1 = !FP32 && ROOM == 1;  // a producer's sum of squares behind its sixteen features, in one line
+    // Input tiles beside each other in a load of a projection with N of them per wave (see multiply).  One row fills an eighth of
+    // a load, so always.  Two rows where there are more than four tiles: for fewer the sums by row cost more than the loads (T5-large
+    // shape 434 us with and 428 without).  Four rows nowhere: the FFN's output alone 455 -> 452 there, but 514 -> 523 at the mT5-large shape.
+    template <int N>
+    static constexpr int side() { return FP32 ? (ROOM == 1 ? 16 : 1) : ROOM == 1 ? 8 : ROOM == 2 && N > 4 ? 4 : 1; }
     static constexpr int KS = F32 ? 4 : 5;  // inputs of a weight tile, logarithm
     static constexpr int ESZ = F32 ? 4 : 2;
     static constexpr int BK = F32 ? 16 : 32;  // keys a wave takes at a time
@@ -53,10 +71,10 @@ struct Walk {
     float ss;                       // this wave's part of its lane's row's sum of squares
     int slot, clear;                // clear: from what this layer hands over to where the layer after the next will: filled with "not there yet"
 
-    int T, R;                       // rows; rows there is room for (the layout's)
+    int T;                          // rows
     __device__ __forceinline__ void place(int rows, int room) {
         T = rows;
-        R = room;
+        this->room(room);
         tok = lane & 15;
         g = lane >> 4;
         t = min(tok, T - 1);
@@ -119,10 +137,29 @@ __device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const
 // inputs] (an own line: a producer's part of a row lies where its planes' readers look anyway).
 // (fp32 models: tiles of sixteen inputs, a producer each, [four inputs][row] and one sum per row)
 __host__ __device__ __forceinline__ int tile_bytes(bool normed, int room, bool f32) { return f32 ? room * 64 + (normed ? 64 : 0) : room * 128 + (normed ? 128 : 0); }
+// What lane j of this lane's sixteen has; j is a constant once unrolled.
+template <int J>
+__device__ __forceinline__ uint4 from_lane(const uint4& v, int j) {
+    if constexpr (J < 16) {
+        if (j != J) return from_lane<J + 1>(v, j);
+        return make_uint4(__builtin_amdgcn_update_dpp(0, v.x, 0x150 + J, 0xF, 0xF, true), __builtin_amdgcn_update_dpp(0, v.y, 0x150 + J, 0xF, 0xF, true),
+                          __builtin_amdgcn_update_dpp(0, v.z, 0x150 + J, 0xF, 0xF, true), __builtin_amdgcn_update_dpp(0, v.w, 0x150 + J, 0xF, 0xF, true));
+    }
+    return v;
+}
 // 1/rms of this lane's row, behind leave()
 template <class Walk>
 __device__ __forceinline__ float norm_factor(const Walk& c, int d, float eps) {
     float p[kPassWaves], s = 0.f;
+    if constexpr (Walk::ROOM1) {
+        const float4 v = *(const float4*)(c.lds + kSq + c.sq + c.tok * 16);
+        s = (v.x + v.y) + (v.z + v.w);
+        s += dpp_f<0x128, 0xF>(0.f, s);
+        s += dpp_f<0x124, 0xF>(0.f, s);
+        s += dpp_f<0x122, 0xF>(0.f, s);
+        s += dpp_f<0x121, 0xF>(0.f, s);
+        return __builtin_amdgcn_rsqf(s * __builtin_amdgcn_rcpf((float)d) + eps);
+    }
 #pragma unroll
     for (int v = 0; v < kPassWaves; ++v) p[v] = *(const float*)(c.lds + kSq + c.sq + (v * 16 + c.tok) * 4);
 #pragma unroll
@@ -137,6 +174,15 @@ __device__ __forceinline__ float norm_factor(const Walk& c, int d, float eps) {
 // the loads and products (a compute unit's 64 bytes a cycle are what the FFN output's 256 loads of 1 KiB wait for); the halves
 // are added in total().  A quarter then has the rows' high parts and their low parts.
 // NORM: the rows' sums of squares as well, to c.ss.
+//
+// A load takes the compute unit's first cache sixteen cycles however few of its bytes differ, so with one or two rows it brings
+// 8 / rows tiles: lane (tile, row; quarter) a piece of its own.  The operands change places (activations first), so that a product's
+// rows are the tiles' in their places, of which one is of use: it lies in one register of one pair of lane groups, and what the
+// tiles contribute is picked by a register's number and one select instead of masks on the operands (four instructions a tile).
+// The sums are then by row: acc[.][t], feature = lane & 15, a part in each lane group (leave() adds those).  One row with the sums
+// of squares behind its producers' features gets them by the same load, in columns 4 .. 7.  All-to-all hand-overs of 64 lines in a
+// kernel of their own: 1.51 us a stage with eight loads a wave, 0.89 with one; 128 lines 2.24 and 0.93.
+//
 // One row of an fp32 model (Walk::ONE) has no use for the matrix cores, whose fp32 products of sixteen rows take eight times as long
 // as a lane's own four inputs: lane (feature, four inputs) sums those, leave() adds the four lanes of a feature.
 template <int N, int RW, bool PACK, bool NORM, class Walk>
@@ -144,23 +190,34 @@ __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 
     const Run r = run_of(c.wave, tk);
     const Rsrc xs = whole(planes);
     const int S = tile_bytes(NORM, c.R, Walk::F32);
-    const int at = (PACK ? (c.g * 2 + (c.tok >> 3)) * c.R + c.t8 : c.g * c.R + c.t) * 16, k0 = r.k0 * S;
-    constexpr int P = PACK || Walk::F32 ? 1 : 2, B = N * P <= 16 ? N : 4;  // tiles requested at once
+    constexpr int SIDE = Walk::template side<N>();
+    constexpr int P = PACK || Walk::F32 ? 1 : 2, NL = (N + SIDE - 1) / SIDE, B = NL * P <= 16 ? NL : 4;  // loads of a piece
     constexpr int IN = Walk::kIn;
-    static_assert(N % B == 0 && (!NORM || N <= 4), "whole pieces; a lane group per tile");
-    uint4 X[N > B ? 2 : 1][P * B];
+    static_assert(NL % B == 0 && (!NORM || N <= 4) && (SIDE == 1 || B == NL), "whole pieces; a lane group per tile");
+    const int beside = SIDE == 1 ? 0 : Walk::F32 ? c.tok : (c.tok & (NORM && Walk::ROOM1 ? 3 : 7)) / c.R;  // this lane's tile of a load
+    const int row = SIDE == 1 ? (PACK ? c.t8 : c.t) : Walk::F32 ? 0 : min((c.tok & 7) & (c.R - 1), c.T - 1);
+    constexpr bool SUMS = NORM && Walk::ROOM1;  // lanes of columns 4 .. 7 get the sums of squares: four tiles' two each
+    static_assert(!SUMS || N <= 4, "room for the sums beside the tiles");
+    const int at = !SUMS ? (PACK ? (c.g * 2 + (c.tok >> 3)) * c.R + row : c.g * c.R + row) * 16
+                         : (c.tok & 4) ? (c.g & 1) * 128 + 64 : (c.g >> 1) * 128 + (c.g & 1) * 32 + (c.tok >> 3) * 16;
+    const int k0 = r.k0 * S;
+    uint4 X[NL > B ? 2 : 1][P * B];
     v2u sq = {0u, 0u};
     f32x4 low[RW];
 #pragma unroll
     for (int q = 0; q < RW; ++q) acc[q] = low[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto get = [&](uint4 (&x)[P * B], int j0) {
+    auto get = [&](uint4 (&x)[P * B], v2u& sq, int j0) {
 #pragma unroll
         for (int j = 0; j < B; ++j)
-            if (j0 + j < r.n) {
+            if ((j0 + j) * SIDE < r.n) {
 #pragma unroll
-                for (int p = 0; p < P; ++p) x[P * j + p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at + p * c.R * 64, k0 + (j0 + j) * S, IN));
+                for (int p = 0; p < P; ++p) {
+                    // (tiles past the wave's last one: that one again)
+                    const int off = SIDE == 1 ? at + p * c.R * 64 : at + min((j0 + j) * SIDE + beside, r.n - 1) * S, from = SIDE == 1 ? k0 + (j0 + j) * S : k0;
+                    x[P * j + p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, off, from, IN));
+                }
             }
-        if constexpr (NORM) {  // (lane group g: tile g)
+        if constexpr (NORM && !SUMS) {  // (lane group g: tile g)
             const int tile = min(c.g, max(r.n - 1, 0)) * S, from = r.n > 0 ? k0 : 0;
             if constexpr (Walk::F32) {
                 const unsigned v = __builtin_amdgcn_raw_buffer_load_b32(xs, tile + c.R * 64 + c.t * 4, from, IN);
@@ -171,6 +228,16 @@ __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 
             }
         }
     };
+    auto lacks = [&](const uint4 (&x)[P * B], const v2u& sums, int j0) {
+        unsigned m = max(sums.x, sums.y);
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+            if ((j0 + j) * SIDE < r.n) {
+#pragma unroll
+                for (int p = 0; p < P; ++p) m = max(max(m, max(x[P * j + p].x, x[P * j + p].y)), max(x[P * j + p].z, x[P * j + p].w));
+            }
+        return __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+    };
     // all of it again and again until every word is there
     auto wait = [&](uint4 (&x)[P * B], int j0) {
         int n = 0;
@@ -178,58 +245,80 @@ __device__ __forceinline__ void multiply(Walk& c, f32x4 (&acc)[RW], const uint4 
 #pragma unroll 1
         do {
             asm volatile("" ::: "memory");
-            if (N == B || n > 0) get(x, j0);
-            unsigned m = max(sq.x, sq.y);
-#pragma unroll
-            for (int j = 0; j < B; ++j)
-                if (j0 + j < r.n) {
-#pragma unroll
-                    for (int p = 0; p < P; ++p) m = max(max(m, max(x[P * j + p].x, x[P * j + p].y)), max(x[P * j + p].z, x[P * j + p].w));
-                }
-            missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+            if (NL == B || n > 0) get(x, sq, j0);
+            missing = lacks(x, sq, j0);
         } while (missing && ++n < c.spins);
         if (missing) c.give_up();
     };
     auto mul = [&](const uint4 (&x)[P * B], int j0) {
+        if constexpr (SIDE > 1 && !Walk::F32) {
+            constexpr int ND = N < SIDE ? N : SIDE;
+            f32x4 D[RW][ND];  // of the tiles in one place: rows of the others' places are of no use
 #pragma unroll
-        for (int j = 0; j < B; ++j)
+            for (int q = 0; q < RW; ++q)
+#pragma unroll
+                for (int j = 0; j < ND; ++j) D[q][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                if (j < r.n) {
+#pragma unroll
+                    for (int q = 0; q < RW; ++q) D[q][j % SIDE] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(x[j / SIDE]), as_bf(W[j * RW + q]), D[q][j % SIDE], 0, 0, 0);
+                }
+#pragma unroll
+            for (int q = 0; q < RW; ++q)
+#pragma unroll
+                for (int t = 0; t < Walk::R; ++t) {
+                    float even = 0.f, odd = 0.f;
+#pragma unroll
+                    for (int j = 0; j < ND; ++j) {
+                        const int m = j * Walk::R + t;
+                        (m < 4 ? even : odd) += D[q][j][m & 3];
+                    }
+                    acc[q][t] = c.g & 1 ? odd : even;
+                }
+            return;
+        }
+#pragma unroll
+        for (int j = 0; j < (SIDE == 1 ? B : N); ++j)
             if (j0 + j < r.n) {
+                uint4 v = x[SIDE == 1 ? P * j : j / SIDE];
+                if constexpr (Walk::ONE) v = from_lane<0>(v, j % SIDE);
 #pragma unroll
                 for (int q = 0; q < RW; ++q) {
+                    const uint4 w = W[(j0 + j) * RW + q];
                     if constexpr (Walk::ONE) {
-                        const uint4 w = W[(j0 + j) * RW + q];
-                        acc[q][0] = __builtin_fmaf(__uint_as_float(w.x), __uint_as_float(x[j].x), acc[q][0]);
-                        acc[q][1] = __builtin_fmaf(__uint_as_float(w.y), __uint_as_float(x[j].y), acc[q][1]);
-                        acc[q][2] = __builtin_fmaf(__uint_as_float(w.z), __uint_as_float(x[j].z), acc[q][2]);
-                        acc[q][3] = __builtin_fmaf(__uint_as_float(w.w), __uint_as_float(x[j].w), acc[q][3]);
-                        continue;
+                        acc[q][0] = __builtin_fmaf(__uint_as_float(w.x), __uint_as_float(v.x), acc[q][0]);
+                        acc[q][1] = __builtin_fmaf(__uint_as_float(w.y), __uint_as_float(v.y), acc[q][1]);
+                        acc[q][2] = __builtin_fmaf(__uint_as_float(w.z), __uint_as_float(v.z), acc[q][2]);
+                        acc[q][3] = __builtin_fmaf(__uint_as_float(w.w), __uint_as_float(v.w), acc[q][3]);
+                    } else if constexpr (Walk::F32) {
+                        products(acc[q], RW == 1 ? low[q] : acc[q], w, v);
+                    } else {
+                        f32x4& even = RW == 1 && PACK && (j & 1) ? low[q] : acc[q];
+                        even = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(w), as_bf(v), even, 0, 0, 0);
+                        f32x4& lo_acc = RW == 1 ? low[q] : acc[q];
+                        if (!PACK) lo_acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(w), as_bf(x[P * j + P - 1]), lo_acc, 0, 0, 0);
                     }
-                    if constexpr (Walk::F32) {
-                        products(acc[q], RW == 1 ? low[q] : acc[q], W[(j0 + j) * RW + q], x[j]);
-                        continue;
-                    }
-                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j]), acc[q], 0, 0, 0);
-                    f32x4& lo_acc = RW == 1 ? low[q] : acc[q];
-                    if (!PACK) lo_acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[(j0 + j) * RW + q]), as_bf(x[P * j + P - 1]), lo_acc, 0, 0, 0);
                 }
             }
     };
-    if constexpr (N == B) {
+    if constexpr (NL == B) {
         wait(X[0], 0);
         mul(X[0], 0);
     } else {  // two pieces on their way
-        get(X[0], 0);
-        get(X[1], B);
+        get(X[0], sq, 0);
+        get(X[1], sq, B);
 #pragma unroll
         for (int j0 = 0; j0 < N; j0 += B) {
             if (j0 >= r.n) break;
             wait(X[(j0 / B) & 1], j0);
             mul(X[(j0 / B) & 1], j0);
-            if (j0 + 2 * B < N) get(X[(j0 / B) & 1], j0 + 2 * B);
+            if (j0 + 2 * B < N) get(X[(j0 / B) & 1], sq, j0 + 2 * B);
         }
     }
-    if constexpr (RW == 1 && !PACK) acc[0] += low[0];
-    if constexpr (NORM) c.ss = quad_rows_sum(__uint_as_float(sq.x) + __uint_as_float(sq.y));
+    if constexpr (RW == 1 && SIDE == 1) acc[0] += low[0];
+    if constexpr (SUMS) c.ss = (c.tok & 3) < r.n ? __uint_as_float(X[0][0].x) : 0.f;
+    else if constexpr (NORM) c.ss = quad_rows_sum(__uint_as_float(sq.x) + __uint_as_float(sq.y));
 }
 
 // The waves' results side by side in LDS; `tile`'s total over the waves, in wave order.
@@ -239,28 +328,38 @@ __device__ __forceinline__ void leave(Walk& c, const f32x4 (&acc)[RW]) {
     c.red = kRedBytes - c.red;
     if constexpr (NORM) {
         c.sq = kSqBytes - c.sq;
-        if (c.g == 0) *(float*)(c.lds + kSq + c.sq + (c.wave * 16 + c.tok) * 4) = c.ss;
+        if constexpr (Walk::ROOM1) {
+            if (c.g < 2 && (c.tok & 12) == 4) *(float*)(c.lds + kSq + c.sq + (c.wave * 8 + c.g * 4 + (c.tok & 3)) * 4) = c.ss;
+        } else {
+            if (c.g == 0) *(float*)(c.lds + kSq + c.sq + (c.wave * 16 + c.tok) * 4) = c.ss;
+        }
     }
 #pragma unroll
     for (int q = 0; q < RW; ++q) {
         if constexpr (ROW) {
-            const float s = quad_rows_sum((acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3]));
-            if (c.g == 0) *(float*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 16 + c.tok) * 4) = s;
+            float s[Walk::R];
+#pragma unroll
+            for (int t = 0; t < Walk::R; ++t) s[t] = quad_rows_sum(Walk::ONE ? (acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3]) : acc[q][t]);
+            float v = s[0];  // of row g
+#pragma unroll
+            for (int t = 1; t < Walk::R; ++t) v = c.g == t ? s[t] : v;
+            if (c.g < Walk::R) *(float*)(c.lds + kRed + c.red + (((c.wave * RW + q) * Walk::R + c.g) * 16 + c.tok) * 4) = v;
         } else {
             *(f32x4*)(c.lds + kRed + c.red + ((c.wave * RW + q) * 64 + c.lane) * 16) = acc[q];
         }
     }
     lds_barrier();
 }
-template <int RW, bool PACK, class Walk>
+template <int RW, bool PACK, bool ROW, class Walk>
 __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
     f32x4 p[kPassWaves];
 #pragma unroll
-    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const f32x4*)(c.lds + kRed + c.red + (Walk::ONE ? ((v * RW + tile) * 16 + c.g * 4) * 4 : ((v * RW + tile) * 64 + c.lane) * 16));
+    for (int v = 0; v < kPassWaves; ++v)
+        p[v] = *(const f32x4*)(c.lds + kRed + c.red + (ROW ? (((v * RW + tile) * c.R + min(c.tok, c.R - 1)) * 16 + c.g * 4) * 4 : ((v * RW + tile) * 64 + c.lane) * 16));
     f32x4 s = p[0];
 #pragma unroll
     for (int v = 1; v < kPassWaves; ++v) s += p[v];
-    if constexpr (PACK) {
+    if constexpr (PACK && !ROW) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) s[v] += dpp_f<0x128, 0xF>(0.f, s[v]);  // row_ror:8: columns 8 .. 15 to 0 .. 7
     }
@@ -269,7 +368,7 @@ __device__ __forceinline__ f32x4 total(const Walk& c, int tile) {
 
 // Sixteen features of a row's activations in that order: this lane's four.
 template <bool PACK, bool NORM, class Walk>
-__device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, const float (&w)[4]) {
+__device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, const float (&w)[4], float ss = 0.f) {
     if constexpr (Walk::F32) {
         const int off = (n0 >> 4) * tile_bytes(NORM, c.R, true) + (((n0 & 15) >> 2) * c.R + c.tok) * 16;
         const v4u v = {__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
@@ -280,18 +379,22 @@ __device__ __forceinline__ void put_planes(const Walk& c, void* planes, int n0, 
     uint32_t h01, l01, h23, l23;
     split_bf16x2(w[0], w[1], h01, l01);
     split_bf16x2(w[2], w[3], h23, l23);
-    const Rsrc r = whole(planes);
-    const int off = (n0 >> 5) * tile_bytes(NORM, c.R, false) + (((n0 & 31) >> 3) * (PACK ? 2 : 1) * c.R + c.tok) * 16 + (n0 & 7) * 2;
-    const int lo = (PACK ? 16 : 64) * c.R;
-    if (c.tok < c.T) {
-        st8<Walk::kOut>(r, off, h01, h23);
-        st8<Walk::kOut>(r, off + lo, l01, l23);
+    // (eight features' high parts to the even lane groups, their low parts to the odd ones: one store, one write of a line)
+    const auto p01 = __builtin_amdgcn_permlane16_swap(h01, l01, false, false), p23 = __builtin_amdgcn_permlane16_swap(h23, l23, false, false);
+    v4u v = {p01[0], p23[0], p01[1], p23[1]};
+    const int tile = (n0 >> 5) * tile_bytes(NORM, c.R, false), half = (n0 >> 4) & 1;
+    int off = tile + (half * 2 + (c.g >> 1)) * (PACK ? 32 : 16) * c.R + (c.g & 1) * (PACK ? 16 : 64) * c.R + c.tok * 16;
+    bool put = c.tok < c.T, fill = c.tok < c.R;
+    if constexpr (NORM && Walk::ROOM1) {
+        off = tile + half * 128 + c.g * 16;
+        if (c.tok == 1) {
+            off = tile + half * 128 + 64;
+            v = v4u{__float_as_uint(ss), __float_as_uint(ss), __float_as_uint(ss), __float_as_uint(ss)};
+        }
+        put = fill = c.tok == 0 || (c.tok == 1 && c.g == 0);
     }
-    if (c.tok < c.R) {
-        const Rsrc n = whole((const char*)planes + c.clear);
-        st8<Walk::kOut>(n, off, kNotThere, kNotThere);
-        st8<Walk::kOut>(n, off + lo, kNotThere, kNotThere);
-    }
+    if (put) __builtin_amdgcn_raw_buffer_store_b128(v, whole(planes), off, 0, Walk::kOut);
+    if (fill) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, whole((const char*)planes + c.clear), off, 0, Walk::kOut);
 }
 
 // What the projections hand over to a head: [row][64] queries (fp32) and keys (bf16), [64][row] values (bf16 in the upper half of a

@@ -184,7 +184,7 @@ __device__ inline int wide_splits(int nkeys, int heads, int groups) {
 template <bool GATED, class Cut>
 __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    using Way = Walk<false, false, false>;
+    using Way = Walk<false, false, 0>;
     constexpr int QT = Cut::QT, FT = Cut::FT, DH = kWideHead;
     constexpr bool EARLY = Cut::In::NC <= 2;  // the FFN's first weights all fit the registers
     Way c;
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         }
     };
     auto add = [&] {
-        const f32x4 s = total<1, true>(c, 0);
+        const f32x4 s = total<1, true, false>(c, 0);
         x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]);
     };
     typename Cut::Qkv sq;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
             leave<QT, true, false>(c, acc);
             if (c.wave < QT && c.wg * QT + c.wave < tq()) {
                 const float f = norm_factor(c, d, a.eps);
-                f32x4 s = total<QT, true>(c, c.wave) * f;
+                f32x4 s = total<QT, true, false>(c, c.wave) * f;
                 const int seg = nf / I, nn = nf - seg * I, pos = len + c.tok, hd = nn / DH, f0 = nn % DH;
                 if (a.rope && seg < 2) {
 #pragma unroll
@@ -566,11 +566,11 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                 const float rms = norm_factor(c, d, a.eps);
                 float w[4];
                 if constexpr (GATED) {
-                    const f32x4 s = total<FT, true>(c, 2 * c.wave) * rms, u = total<FT, true>(c, 2 * c.wave + 1) * rms;
+                    const f32x4 s = total<FT, true, false>(c, 2 * c.wave) * rms, u = total<FT, true, false>(c, 2 * c.wave + 1) * rms;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(s[v]) : silu_f(s[v])) * u[v];
                 } else {
-                    const f32x4 s = total<FT, true>(c, c.wave) * rms;
+                    const f32x4 s = total<FT, true, false>(c, c.wave) * rms;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = fmaxf(s[v], 0.f);
                 }
