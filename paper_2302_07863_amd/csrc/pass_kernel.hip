@@ -59,7 +59,7 @@ template <bool CAUSAL, bool PACK, class Walk>
 struct Attend {
     const Rsrc kr, vr;
     const int I, cap, nkeys, nblk;  // (causal: the keys of earlier passes)
-    static constexpr bool F32 = Walk::F32;
+    static constexpr bool F32 = Walk::F32, ONE = Walk::ROOM1;
     // blocks of sixteen or (bf16) twice sixteen keys; pieces of sixteen keys' rows and of a block's values
     static constexpr int AB = F32 ? 1 : 2, BK = 16 * AB, KC = F32 ? 4 : 2, VC = 4;
     uint4 K0[AB][KC], K1[AB][KC], V0[VC], V1[VC];
@@ -73,8 +73,8 @@ struct Attend {
             for (int ks = 0; ks < KC; ++ks) Kr[ab][ks] = buf_load(kr, (unsigned)((ab * 16 + c.tok) * I * E + c.g * 16), key0 * I * E + ks * 64);
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) {
-            const int off = ((dt * 16 + c.tok) * cap + c.g * 4) * E;
-            if constexpr (F32) {
+            const int off = ((dt * 16 + c.tok) * cap + c.g * (ONE ? 8 : 4)) * E;
+            if constexpr (F32 || ONE) {
                 Vr[dt] = buf_load(vr, (unsigned)off, key0 * E);
             } else {
                 const uint2 va = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, off, key0 * 2, 0));
@@ -83,11 +83,183 @@ struct Attend {
             }
         }
     }
+    // One row: the query is the first operand, so that a product's columns are keys and its rows all the query (high parts in the lane
+    // groups 0 and 1, low parts in 2 and 3): after one exchange of the halves each lane has ONE of the wave's 64 keys (two blocks),
+    // where the other order leaves sixteen scores to each of the four lanes of the row's column and the same work to all columns.
+    // The weights reach the second product's order through LDS, its result is a feature per lane.  With head and policy, us: T5-large
+    // shape 412 -> 381, mT5-large 477 -> 441, T5-small on one die 96 -> 87.5; for two rows the two chains of maxima and sums take more
+    // than the columns save (420 -> 438), for four 443 -> 498.
+    __device__ __forceinline__ void run_one(Walk& c, const Fresh& fresh, int len, const float* relb, int rel_d, void* out, int h) {
+        constexpr int IN = Walk::kIn;
+        const bool odd = c.g & 1, upper = c.g >= 2;
+        char* const w = c.lds + kP + c.wave * 256;  // the weights' high parts and their low parts
+        bf16x8 Q[2];
+        float m_run = -INFINITY, l_run = 0.f;  // (the sum: this lane's)
+        f32x4 O[4];
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // of four tiles' values this lane's: tile g's, high and low parts added
+        auto mine = [&](const f32x4 (&v)[4]) {
+            const float a = odd ? v[1][0] : v[0][0], b = odd ? v[3][0] : v[2][0];
+            const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+            return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+        };
+        // a block of keys to the lower lanes and one to the upper ones, either may be missing; keys behind `lim` are not seen
+        auto step = [&](bool lower_has, int lower_key, int lower_lim, bool upper_has, int upper_key, int upper_lim, bool first) {
+            f32x4 s[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (lower_has) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int ab = 0; ab < 2; ++ab) s[ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Q[ks], as_bf(K0[ab][ks]), s[ab], 0, 0, 0);
+            }
+            if (upper_has) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int ab = 0; ab < 2; ++ab) s[2 + ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Q[ks], as_bf(K1[ab][ks]), s[2 + ab], 0, 0, 0);
+            }
+            const int key = (upper ? upper_key : lower_key) + (odd ? 16 : 0) + c.tok, lim = upper ? (upper_has ? upper_lim : -1) : (lower_has ? lower_lim : -1);
+            float z = mine(s);
+            if (CAUSAL && relb) z += relb[rel_d + max(-rel_d, min(rel_d, key - len))];
+            if (key > lim) z = -INFINITY;
+            const float m_new = fmaxf(m_run, wave_max(z)), base = m_new == -INFINITY ? 0.f : m_new;
+            const float p = fexp(z - base);
+            if (first) {
+                l_run = p;
+            } else {
+                const float f = fexp(m_run - base);
+                l_run = l_run * f + p;
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt) O[dt] *= f;
+            }
+            m_run = m_new;
+            uint32_t hi, lo;
+            split_bf16x2(p, 0.f, hi, lo);
+            *(uint16_t*)(w + c.lane * 2) = (uint16_t)hi;
+            *(uint16_t*)(w + 128 + c.lane * 2) = (uint16_t)lo;
+            asm volatile("" ::: "memory");
+            const char* const wr = w + (c.tok >> 3) * 128 + c.g * 16;
+            const bf16x8 wl = as_bf(*(const uint4*)wr), wu = as_bf(*(const uint4*)(wr + 64));
+            asm volatile("" ::: "memory");
+            if (lower_has) {
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt) O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wl, as_bf(V0[dt]), O[dt], 0, 0, 0);
+            }
+            if (upper_has) {
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt) O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wu, as_bf(V1[dt]), O[dt], 0, 0, 0);
+            }
+        };
+        if constexpr (CAUSAL) {
+            const bool newest = c.wave == (nblk & (kPassWaves - 1)), old = c.wave < nblk;
+            if (old || newest) {
+                uint4 qv[2], kn[2];
+                unsigned vn[4];
+                int n = 0;
+                bool missing;
+#pragma unroll 1
+                do {
+                    asm volatile("" ::: "memory");
+                    unsigned m = 0u;
+                    auto see = [&](const uint4& v) { m = max(max(m, max(v.x, v.y)), max(v.z, v.w)); };
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) qv[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fresh.q, query_piece<true>(c, ks, 0), 0, IN));
+                    if (newest) {
+#pragma unroll
+                        for (int ks = 0; ks < 2; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fresh.k, ks * 64 + c.g * 16, 0, IN));
+#pragma unroll
+                        for (int dt = 0; dt < 4; ++dt) {
+                            vn[dt] = __builtin_amdgcn_raw_buffer_load_b32(fresh.v, (dt * 16 + c.tok) * 4, 0, IN);
+                            m = max(m, vn[dt]);
+                        }
+                        see(kn[0]);
+                        see(kn[1]);
+                    }
+                    see(qv[0]);
+                    see(qv[1]);
+                    missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+                } while (missing && ++n < c.spins);
+                if (missing) c.give_up();
+                Q[0] = as_bf(qv[0]);
+                Q[1] = as_bf(qv[1]);
+                if (newest) {
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) {
+                        K1[0][ks] = kn[ks];
+                        K1[1][ks] = make_uint4(0u, 0u, 0u, 0u);
+                    }
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt) V1[dt] = make_uint4(c.g == 0 ? vn[dt] >> 16 : 0u, 0u, 0u, 0u);  // (one key: lane group 0's first)
+                }
+                step(old, c.wave * BK, nkeys - 1, newest, len, len, true);
+                for (int blk = c.wave + kPassWaves; blk < nblk; blk += kPassWaves) {
+                    load(c, K0, V0, blk);
+                    step(true, blk * BK, nkeys - 1, false, 0, 0, false);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) Q[ks] = as_bf(*(const uint4*)(c.lds + kQ + query_piece<true>(c, ks, 0)));
+            for (int blk = c.wave; blk < nblk; blk += 2 * kPassWaves) {
+                step(true, blk * BK, nkeys - 1, blk + kPassWaves < nblk, (blk + kPassWaves) * BK, nkeys - 1, blk == c.wave);
+                if (blk + 2 * kPassWaves < nblk) load(c, K0, V0, blk + 2 * kPassWaves);
+                if (blk + 3 * kPassWaves < nblk) load(c, K1, V1, blk + 3 * kPassWaves);
+            }
+        }
+        float* const cm = (float*)(c.lds + kMl);  // the waves' maxima and sums
+        c.red = kRedBytes - c.red;
+        float* const co = (float*)(c.lds + kRed + c.red) + c.lane;
+        const float sum = wave_sum(l_run);
+        co[c.wave * 64] = mine(O);
+        if (c.lane == 0) {
+            cm[c.wave] = m_run;
+            cm[kPassWaves + c.wave] = sum;
+        }
+        lds_barrier();
+        if (c.wave == 0) {
+            // (a wave without keys has left a maximum of minus infinity and zeros)
+            float m[kPassWaves], l[kPassWaves], p[kPassWaves], M = -INFINITY, L = 0.f, o = 0.f;
+#pragma unroll
+            for (int v = 0; v < kPassWaves; ++v) {
+                m[v] = cm[v];
+                l[v] = cm[kPassWaves + v];
+                p[v] = co[v * 64];
+            }
+#pragma unroll
+            for (int v = 0; v < kPassWaves; ++v) M = fmaxf(M, m[v]);
+#pragma unroll
+            for (int v = 0; v < kPassWaves; ++v) {
+                m[v] = fexp(m[v] - M);
+                L += l[v] * m[v];
+                o += p[v] * m[v];
+            }
+            o *= 1.f / L;
+            // eight features' high parts to a quad of lanes, their low parts to the next; the quads' first lanes store
+            uint32_t h01, h23, l01, l23;
+            split_bf16x2(dpp_f<0x00, 0xF>(0.f, o), dpp_f<0x55, 0xF>(0.f, o), h01, l01);
+            split_bf16x2(dpp_f<0xAA, 0xF>(0.f, o), dpp_f<0xFF, 0xF>(0.f, o), h23, l23);
+            auto from = [](auto ctrl, uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xF, 0xF, true); };
+            using Next = std::integral_constant<int, 0x104>;  // row_shl:4: the lane four on
+            using Last = std::integral_constant<int, 0x114>;  // row_shr:4
+            const bool low = c.lane & 4;
+            const uint32_t n01 = from(Next{}, h01), n23 = from(Next{}, h23), p01 = from(Last{}, l01), p23 = from(Last{}, l23);  // (of all lanes)
+            const v4u v = {low ? p01 : h01, low ? p23 : h23, low ? l01 : n01, low ? l23 : n23};
+            const int off = h * 256 + (c.lane >> 2) * 16;
+            if ((c.lane & 3) == 0) {
+                __builtin_amdgcn_raw_buffer_store_b128(v, whole(out), off, 0, Walk::kOut);
+                __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, whole((const char*)out + c.clear), off, 0, Walk::kOut);
+            }
+        }
+    }
     // Up to eight rows are packed as in multiply().  Causal: query, keys and values of this pass' rows are handed over in `fresh`,
     // a block of keys of its own that one wave takes; else the query lies in LDS.
     __device__ __forceinline__ void run(Walk& c, const Fresh& fresh, float scale, int len, const float* relb, int rel_d, void* out, int h) {
+        if constexpr (ONE) return run_one(c, fresh, len, relb, rel_d, out, h);
         constexpr int P = PACK ? 1 : 2, IN = Walk::kIn;
-        bf16x8 Q[2][P];  // scaled, high parts (columns 0 .. 7 if packed) and low parts
+        bf16x8 Q[2][P];  // scaled, high parts (columns 0 .. 7 if packed) and low parts, as they were handed over
         uint4 Qf[4];     // fp32: scaled, inputs c * 16 + g * 4 ..
         const bool low = c.tok >= 8;
         const int row = PACK ? c.t8 : c.t;
@@ -103,21 +275,14 @@ struct Attend {
                 o[1] = as_bf(make_uint4(lo[0], lo[1], lo[2], lo[3]));
             }
         };
-        auto split_query = [&](const float4 (&qv)[2][2]) {
+        auto scale_query = [&](const float4 (&qv)[4]) {
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                if constexpr (F32) {
+            for (int i = 0; i < 4; ++i)
+                Qf[i] = make_uint4(__float_as_uint(qv[i].x * scale), __float_as_uint(qv[i].y * scale), __float_as_uint(qv[i].z * scale), __float_as_uint(qv[i].w * scale));
+        };
+        auto take_query = [&](const uint4 (&qv)[4]) {
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        const float4 q = qv[ks][p];
-                        Qf[ks * 2 + p] = make_uint4(__float_as_uint(q.x * scale), __float_as_uint(q.y * scale), __float_as_uint(q.z * scale), __float_as_uint(q.w * scale));
-                    }
-                    continue;
-                }
-                const float v[8] = {qv[ks][0].x * scale, qv[ks][0].y * scale, qv[ks][0].z * scale, qv[ks][0].w * scale,
-                                    qv[ks][1].x * scale, qv[ks][1].y * scale, qv[ks][1].z * scale, qv[ks][1].w * scale};
-                parts(v, Q[ks]);
-            }
+            for (int i = 0; i < 2 * P; ++i) Q[i / P][i % P] = as_bf(qv[i]);
         };
         float m_run = -INFINITY, l_run = 0.f;
         f32x4 O[4];
@@ -216,7 +381,9 @@ struct Attend {
         if constexpr (CAUSAL) {
             const bool newest = c.wave == (nblk & (kPassWaves - 1));
             if (c.wave < nblk || newest) {
-                float4 qv[2][2], vn[4];
+                constexpr int QL = F32 ? 4 : 2 * P;
+                uint4 qv[4];
+                float4 vn[4];
                 uint4 kn[KC];
                 int n = 0;
                 bool missing;
@@ -226,7 +393,7 @@ struct Attend {
                     unsigned m = 0u;
                     auto see = [&](unsigned a, unsigned b, unsigned d, unsigned e) { m = max(max(m, max(a, b)), max(d, e)); };
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) qv[i >> 1][i & 1] = ldf4<IN>(fresh.q, row * 256 + (F32 ? i * 64 + c.g * 16 : (i >> 1) * 128 + c.g * 32 + (i & 1) * 16));
+                    for (int i = 0; i < QL; ++i) qv[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fresh.q, row * 256 + (F32 ? i * 64 + c.g * 16 : query_piece<PACK>(c, i / P, i % P)), 0, IN));
                     if (newest) {
 #pragma unroll
                         for (int ks = 0; ks < KC; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fresh.k, c.t * (64 * Walk::ESZ) + ks * 64 + c.g * 16, 0, IN));
@@ -238,14 +405,12 @@ struct Attend {
                         for (int dt = 0; dt < 4; ++dt) see(__float_as_uint(vn[dt].x), __float_as_uint(vn[dt].y), __float_as_uint(vn[dt].z), __float_as_uint(vn[dt].w));
                     }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float4 v = qv[i >> 1][i & 1];
-                        see(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w));
-                    }
+                    for (int i = 0; i < QL; ++i) see(qv[i].x, qv[i].y, qv[i].z, qv[i].w);
                     missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
                 } while (missing && ++n < c.spins);
                 if (missing) c.give_up();
-                split_query(qv);
+                if constexpr (F32) scale_query({__builtin_bit_cast(float4, qv[0]), __builtin_bit_cast(float4, qv[1]), __builtin_bit_cast(float4, qv[2]), __builtin_bit_cast(float4, qv[3])});
+                else take_query(qv);
                 if (c.wave < nblk) process(One{}, {K0}, {V0}, {c.wave * BK}, c.wave * BK + BK - 1 >= nkeys, nkeys - 1, true);
                 for (int blk = c.wave + kPassWaves; blk < nblk; blk += kPassWaves) {
                     load(c, K0, V0, blk);
@@ -270,11 +435,15 @@ struct Attend {
                 }
             }
         } else {
-            const float* q = (const float*)(c.lds + kQ);
-            float4 qv[2][2];
+            if constexpr (F32) {
+                const float* q = (const float*)(c.lds + kQ) + row * kQLd;
+                scale_query({*(const float4*)(q + c.g * 4), *(const float4*)(q + 16 + c.g * 4), *(const float4*)(q + 32 + c.g * 4), *(const float4*)(q + 48 + c.g * 4)});
+            } else {
+                uint4 qv[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) qv[i >> 1][i & 1] = *(const float4*)(q + row * kQLd + (F32 ? i * 16 + c.g * 4 : (i >> 1) * 32 + c.g * 8 + (i & 1) * 4));
-            split_query(qv);
+                for (int i = 0; i < 2 * P; ++i) qv[i] = *(const uint4*)(c.lds + kQ + row * kQLd * 4 + query_piece<PACK>(c, i / P, i % P));
+                take_query(qv);
+            }
             if constexpr (F32) {  // (one set of registers)
                 for (int blk = c.wave; blk < nblk; blk += kPassWaves) {
                     process(One{}, {K0}, {V0}, {blk * BK}, blk * BK + BK - 1 >= nkeys, nkeys - 1, blk == c.wave);
@@ -343,9 +512,9 @@ __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; 
 // q holds those of tile q.
 template <bool GATED, bool PACK, class Cut, class Walk>
 __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
+    int T = a.T, d = a.d, I = a.I, F = a.F;
     constexpr int QT = Cut::QT, OT = Cut::OT, FT = Cut::FT, KD = Cut::KD, KF = Cut::KF;
     constexpr bool RD = Walk::template side<KD>() > 1, RF = Walk::template side<KF>() > 1;  // (tiles beside each other: sums by row)
-    int T = a.T, d = a.d, I = a.I, F = a.F;
     const int base = groups - a.heads;  // the workgroups with a head each follow
     const int len = *a.len_ptr;
     auto nd = [&] { return d >> 4; };
@@ -431,8 +600,9 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 const Rsrc o = whole(out), n = whole(out + c.clear), kv = whole(kept);
                 const int hd = nn >> 6, f0 = nn & 63;
                 if (seg == 0) {
-                    const int off = ((hd * c.R + c.tok) * 64 + f0) * 4;
-                    const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
+                    const int off = Walk::F32 ? ((hd * c.R + c.tok) * 64 + f0) * 4 : (hd * c.R + c.tok) * 256 + (f0 >> 4) * 64 + c.g * 16;
+                    v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
+                    if constexpr (!Walk::F32) v = query_parts(s * a.att_scale);
                     if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b128(v, o, off, 0, Walk::kOut);
                     if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, n, off, 0, Walk::kOut);
                 } else if (Walk::F32 && seg == 1) {
@@ -452,7 +622,18 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                     }
                     if (c.tok < c.R) st8<Walk::kOut>(n, off, kNotThere, kNotThere);
                 } else {
-                    const int room = fresh_room(c.R), off = ((hd * 64 + f0) * room + c.tok) * 4;
+                    const int room = Walk::ROOM1 ? 1 : fresh_room(c.R), off = ((hd * 64 + f0) * room + c.tok) * 4;
+                    if constexpr (Walk::ROOM1) {
+                        unsigned b[4];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) b[v] = f2bf(s[v]);
+                        if (c.tok == 0) {
+                            __builtin_amdgcn_raw_buffer_store_b128(v4u{b[0] << 16, b[1] << 16, b[2] << 16, b[3] << 16}, o, off, 0, Walk::kOut);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b[v], kv, ((nn + v) * a.vcap + pos) * 2, 0, Walk::kOut);
+                            __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, n, off, 0, Walk::kOut);
+                        }
+                    } else
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const unsigned b = Walk::F32 ? __float_as_uint(s[v]) : f2bf(s[v]);
@@ -584,7 +765,7 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
             if (!Walk::F32 && cross.nblk > kPassWaves) cross.load(c, cross.K1, cross.V1, c.wave + kPassWaves);
         }
         {
-            const int room = fresh_room(c.R);
+            const int room = Walk::ROOM1 ? 1 : fresh_room(c.R);
             const Fresh fresh = {whole(pinned(z + a.at.q + h * c.R * 256)), whole(pinned(z + a.at.k + h * c.R * 64 * c.ESZ)), whole(pinned(z + a.at.v + h * room * 256)), room};
             char* out = pinned(z + a.at.a1);
             const float sc = a.att_scale;
@@ -600,7 +781,8 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
             leave<4, true, RD>(c, acc);
             if (c.wave < 4) {
                 const f32x4 s = total<4, PACK, RD>(c, c.wave) * norm_factor(c, d, a.eps);
-                *(f32x4*)((float*)(c.lds + kQ) + c.tok * kQLd + c.wave * 16 + c.g * 4) = s;
+                if constexpr (Walk::F32) *(f32x4*)((float*)(c.lds + kQ) + c.tok * kQLd + c.wave * 16 + c.g * 4) = s;
+                else *(v4u*)(c.lds + kQ + c.tok * kQLd * 4 + c.wave * 64 + c.g * 16) = query_parts(s * sc);
             }
             lds_barrier();
             cross.run(c, Fresh{}, sc, len, nullptr, 0, out, h);

@@ -30,9 +30,9 @@ __device__ __forceinline__ void st8(Rsrc r, int off, unsigned a, unsigned b) {
 constexpr unsigned kNotThere = 0xFFFFFFFFu;  // (two NaNs of a kind no conversion gives, as bf16 parts; one as a sum)
 
 // LDS: sums of the waves (up to six tiles each; attention joins its waves there too), their (max, sum), the head's query, the
-// waves' sums of squares (twice, like the sums), the head's relative-position biases
+// waves' sums of squares (twice, like the sums), their weights of one row's keys, the head's relative-position biases
 constexpr int kRedBytes = kPassWaves * 6 * 1024;  // twice: a stage's sums are read while the next one's are written
-constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kSq = kQ + 16 * kQLd * 4, kSqBytes = kPassWaves * 16 * 4, kRel = kSq + 2 * kSqBytes;
+constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kSq = kQ + 16 * kQLd * 4, kSqBytes = kPassWaves * 16 * 4, kP = kSq + 2 * kSqBytes, kRel = kP + kPassWaves * 256;
 
 // Rows there is room for in the hand-over memory (the layout's): known to the kernel, or (0) not.
 template <int ROOM>
@@ -404,5 +404,20 @@ struct Fresh {
     int room;
 };
 __host__ __device__ inline int fresh_room(int rows) { return (rows + 3) & ~3; }
+
+// A row's scaled query of a head (bf16 models): [sixteen features][eight features][high, low parts], 256 bytes.
+// This lane's four features of a row as the 16 bytes it stores there, at [sixteen features] * 64 + g * 16
+__device__ __forceinline__ v4u query_parts(const f32x4& q) {
+    uint32_t h01, l01, h23, l23;
+    split_bf16x2(q[0], q[1], h01, l01);
+    split_bf16x2(q[2], q[3], h23, l23);
+    const auto p01 = __builtin_amdgcn_permlane16_swap(h01, l01, false, false), p23 = __builtin_amdgcn_permlane16_swap(h23, l23, false, false);
+    return v4u{p01[0], p23[0], p01[1], p23[1]};
+}
+// ... and where lane (row, g) finds features 32 ks + 8 g ..: high parts in columns 0 .. 7 and low ones in 8 .. 15, or part p
+template <bool PACK, class Walk>
+__device__ __forceinline__ int query_piece(const Walk& c, int ks, int p) {
+    return (2 * ks + (c.g >> 1)) * 64 + (c.g & 1) * 32 + (PACK ? c.tok >> 3 : p) * 16;
+}
 
 }  // namespace bild
