@@ -514,6 +514,20 @@ template <bool GATED, bool PACK, class Cut, class Walk>
 __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     int T = a.T, d = a.d, I = a.I, F = a.F;
     constexpr int QT = Cut::QT, OT = Cut::OT, FT = Cut::FT, KD = Cut::KD, KF = Cut::KF;
+    constexpr bool CHIP = Walk::kOut != 0;
+    // EARLY: input tiles of the FFN's output projection asked for before the self-attention's results are waited for, WQ: where the next
+    // layer's first weights are asked for (see there).  Over the chip 0, 0: with 4 to 16 of 16 early T5-large 372 -> 371 .. 390 us.  On one
+    // die, EARLY 0, 4, 8 and WQ 0, 1, 2: T5-small shape 87 (0, 0), 85 (0, 1), 84 (4, 1), 82.5 (4, 2), 85.5 (8, 2), mT5-small 152, 144, 143.5, 146, 146.
+    constexpr int EARLY = CHIP ? 0 : 4, WQ = CHIP ? 0 : GATED ? 1 : 2;
+    // Naps of workgroups whose part in between is the others' (see the head of this file), in turns of 95 ns: from their own result to
+    // what comes of it two stages on.  By width and rows; measured optima (none / best, us, 12 layers): 256 wide 1, 8 rows 15, 20 turns (149 / 149,
+    // 171 / 167), 512 20, 22 (154 / 152, 188 / 182), 768 23, 26 (167 / 163, 213 / 203), 1024 27, 31 (189 / 183, 244 / 230), gated 29, 34 (190 / 185, 248 /
+    // 234); two turns more here than in those measurements, whose naps also read their length.  Two turns too short or four too long lose
+    // half of it.
+    constexpr int RI = Walk::KNOWN <= 1 ? 0 : Walk::KNOWN == 2 ? 1 : Walk::KNOWN == 4 ? 2 : Walk::KNOWN == 8 ? 3 : 4;
+    constexpr int OUT_A[] = {14, 16, 16, 18, 20}, OUT_B[] = {15, 14, 14, 14, 17}, QKV_A[] = {18, 22, 18, 20, 20}, QKV_B[] = {8, 5, 14, 14, 16};
+    auto out_nap = [&] { return OUT_A[RI] + ((OUT_B[RI] * d + 512) >> 10) + (!GATED ? 0 : RI ? 4 : 2); };
+    auto qkv_nap = [&] { return QKV_A[RI] + ((QKV_B[RI] * d + 512) >> 10); };
     constexpr bool RD = Walk::template side<KD>() > 1, RF = Walk::template side<KF>() > 1;  // (tiles beside each other: sums by row)
     const int base = groups - a.heads;  // the workgroups with a head each follow
     const int len = *a.len_ptr;
@@ -523,7 +537,13 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     auto no = [&] { return ceil_div(nd(), OT); };
     auto nq = [&] { return ceil_div(tq(), QT); };
     auto nf = [&] { return ceil_div(tf(), FT); };       // workgroups
-    const bool owner = c.wg < no(), qkv = c.wg < nq(), ffn = c.wg < nf();
+    // This workgroup's part of q, k, v and of the FFN: the last workgroups', so that those that own features of the residual stream have
+    // as few other weights to ask for as there are compute units for: an owner that also had its part of the FFN's input asked for 224
+    // KB in front of the cross-attention's results, which came 2.6 us after they were handed over (1.5 now).  Sixteen rows of a gated
+    // model: the first ones' (mT5-large shape, 12 layers, 293 us apart and 286 together).
+    constexpr bool LAST = !(GATED && RI == 4);
+    const int uq = c.wg - (LAST ? base - nq() : 0), uf = c.wg - (LAST ? base - nf() : 0);
+    const bool owner = c.wg < no(), qkv = uq >= 0 && uq < nq(), ffn = uf >= 0 && uf < nf(), apart = LAST && no() + nf() <= base;
     uint4 Wq[KD * QT], Wo[KD * OT], Wi[KD * FT], Wf[KF * OT];
     float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);  // (owners, waves below OT) the residual stream of this lane's row, features n0 .. n0 + 3
@@ -575,7 +595,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         }
         publish(gn, z + a.at.x1);
     }
-    if (qkv) request<KD, QT>(c, Wq, L->wqkv, c.wg, d >> c.KS, tq());
+    if (qkv) request<KD, QT>(c, Wq, L->wqkv, uq, d >> c.KS, tq());
     for (int l = 0; l < a.n_layers; ++l) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         const bool last = l + 1 == a.n_layers;
@@ -586,17 +606,18 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         // ---- q, k, v (a workgroup's tiles are of one of the three) ----
         if (qkv) {
             const char* xs = pinned(z + a.at.x1);
-            const int seg = c.wg * QT * 16 / I;
+            const int seg = uq * QT * 16 / I;
             char* kept = pinned(seg == 1 ? L->kc : L->vc);
             char* out = pinned(z + (seg == 0 ? a.at.q : seg == 1 ? a.at.k : a.at.v));
             f32x4 acc[QT];
-            c.template nap<250>();
+            if (apart && !owner) c.rest(qkv_nap());
+            else c.template nap<250>();
             multiply<KD, QT, PACK, true>(c, acc, Wq, xs, d >> c.KS);
             leave<QT, true, RD>(c, acc);
             if (c.wave < QT) {
                 const float f = norm_factor(c, d, a.eps);
                 const f32x4 s = total<QT, PACK, RD>(c, c.wave) * f;
-                const int nn = (c.wg * QT + c.wave) * 16 + c.g * 4 - seg * I, pos = len + c.tok;
+                const int nn = (uq * QT + c.wave) * 16 + c.g * 4 - seg * I, pos = len + c.tok;
                 const Rsrc o = whole(out), n = whole(out + c.clear), kv = whole(kept);
                 const int hd = nn >> 6, f0 = nn & 63;
                 if (seg == 0) {
@@ -653,6 +674,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         if (owner) {
             request<KD, OT>(c, Wo, L->wo, c.wg, I >> c.KS, nd());
             const float4 gn = gain(a.cross ? L->lnc : L->ln2);
+            if (a.cross) request<KF, OT, 0, EARLY>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
             if (!a.cross) {
                 next_gain = gain(last ? L->ln2 : L[1].ln1);
                 request<KF, OT>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
@@ -672,9 +694,9 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 request<KD, OT>(c, Wo, L->cwo, c.wg, I >> c.KS, nd());
                 const float4 gn = gain(L->ln2);
                 next_gain = gain(last ? L->ln2 : L[1].ln1);
-                if (ffn) request<KD, FT>(c, Wi, L->win, c.wg, d >> c.KS, tf());
-                request<KF, OT>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
-                if (qkv && !last) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> c.KS, tq());
+                if (ffn) request<KD, FT>(c, Wi, L->win, uf, d >> c.KS, tf());
+                request<KF, OT, EARLY, KF>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
+                if (qkv && !last && WQ == 0) request<KD, QT>(c, Wq, L[1].wqkv, uq, d >> c.KS, tq());
                 const char* xs = pinned(z + a.at.a2);
                 char* ox = pinned(z + a.at.x3);
                 f32x4 acc[OT];
@@ -687,7 +709,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
         }
         // ---- FFN ----
         if (ffn) {
-            if (!owner || !a.cross) request<KD, FT>(c, Wi, L->win, c.wg, d >> c.KS, tf());
+            if (!owner || !a.cross) request<KD, FT>(c, Wi, L->win, uf, d >> c.KS, tf());
             const char* xs = pinned(xf);
             char* out = pinned(z + a.at.h);
             constexpr int FW = GATED ? FT / 2 : FT;  // waves with results
@@ -695,7 +717,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             c.template nap<250>();
             multiply<KD, FT, PACK, true>(c, acc, Wi, xs, d >> c.KS);
             leave<FT, true, RD>(c, acc);
-            const int tile = c.wg * FW + c.wave;  // of the hidden state
+            const int tile = uf * FW + c.wave;  // of the hidden state
             if (c.wave < FW && tile < F >> 4) {
                 const float r = norm_factor(c, d, a.eps);
                 float w[4];
@@ -711,7 +733,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
                 put_planes<PACK, false>(c, out, tile * 16 + c.g * 4, w);
             }
         }
-        if (qkv && !last && (!owner || !a.cross)) request<KD, QT>(c, Wq, L[1].wqkv, c.wg, d >> c.KS, tq());
+        if (qkv && !last && (!owner || !a.cross || WQ == 1)) request<KD, QT>(c, Wq, L[1].wqkv, uq, d >> c.KS, tq());
         const char* hidden = z + a.at.h;
         z = c.next(z, a.at.layer);
         c.walk_on(a.at.layer);
@@ -719,11 +741,13 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             const char* xs = pinned(hidden);
             char* ox = pinned(z + a.at.x1);
             f32x4 acc[OT];
-            c.template nap<GATED ? 650 : 400>();
+            if (apart) c.rest(out_nap());
+            else c.template nap<GATED ? 650 : 400>();
             multiply<KF, OT, PACK, false>(c, acc, Wf, xs, F >> c.KS);
             leave<OT, false, RF>(c, acc);
             if (mine) add(std::bool_constant<RF>{});
             if (!last) publish(next_gain, ox);
+            if (qkv && !last && a.cross && WQ == 2) request<KD, QT>(c, Wq, L[1].wqkv, uq, d >> c.KS, tq());
         }
     }
     if (owner && mine && c.tok < T) {
@@ -833,8 +857,8 @@ static bool cut_fits(int d, int I, int F, int inputs) {
 // Sizes the kernel is made for: runs of inputs that fit the registers, the workgroups on the chip at once.  Wider models: pass_wide.hip.
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<ChipCut>(d, heads * 64, F, 32)) return 0;
-    const int g = cut_groups<ChipCut>(d, heads, F, gated);
-    return g <= cus ? g : 0;
+    const int g = cut_groups<ChipCut>(d, heads, F, gated), apart = d / 16 + ceil_div(gated ? F / 8 : F / 16, ChipCut::FT) + heads;
+    return apart <= cus ? std::max(g, apart) : g <= cus ? g : 0;
 }
 // ... and of the form on one die: all of it on the 32 compute units of one.
 int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32) {

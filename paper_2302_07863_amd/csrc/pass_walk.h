@@ -48,6 +48,7 @@ struct Room<0> {
 template <bool DIE, bool FP32, int ROOM>
 struct Walk : Room<ROOM> {
     using Room<ROOM>::R;
+    static constexpr int KNOWN = ROOM;
     static constexpr bool F32 = FP32;      // of an fp32 model
     static constexpr bool ONE = FP32 && ROOM == 1;  // ... and one row (see multiply)
     static constexpr bool ROOM1 = !FP32 && ROOM == 1;  // a producer's sum of squares behind its sixteen features, in one line
@@ -95,6 +96,10 @@ struct Walk : Room<ROOM> {
         dead = true;
         if (lane == 0) asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(failed), "v"(1u) : "memory");
     }
+    __device__ __forceinline__ void rest(int turns) const {
+#pragma unroll 1
+        for (int i = 0; i < turns; ++i) __builtin_amdgcn_s_sleep(3);
+    }
     // (about NS nanoseconds; see the head of this file)
     template <int NS>
     __device__ __forceinline__ void nap() const {
@@ -119,14 +124,14 @@ __device__ __forceinline__ Run run_of(int wave, int tk) {
     return {wave * per, max(0, min(per, tk - wave * per))};
 }
 
-// (tiles past the last of the `tiles` there are: the last one again)
-template <int N, int RW, class Walk>
+// (tiles past the last of the `tiles` there are: the last one again; the wave's input tiles J0 .. J1 - 1)
+template <int N, int RW, int J0 = 0, int J1 = N, class Walk>
 __device__ __forceinline__ void request(const Walk& c, uint4 (&W)[N * RW], const void* w, int unit, int tk, int tiles) {
     const Run r = run_of(c.wave, tk);
     const Rsrc rs = whole((const char*)w + (size_t)unit * RW * tk * kTileBytes);
     const int most = tiles - 1 - unit * RW;
 #pragma unroll
-    for (int j = 0; j < N; ++j)
+    for (int j = J0; j < J1; ++j)
         if (j < r.n) {
 #pragma unroll
             for (int q = 0; q < RW; ++q) W[j * RW + q] = buf_load(rs, (unsigned)c.lane * 16u, ((RW == 1 ? 0 : min(q, most)) * tk + r.k0 + j) * kTileBytes);
