@@ -1546,9 +1546,9 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
     } else {
         f.mode = 3;
     }
-    // sampling variant under the threshold rule: the draw runs spread over the chip (seven launches instead of one)
+    // sampling variant under the threshold rule: the draw runs spread over the chip (three launches instead of one)
     const bool spread = f.top_p > 0.f && f.mode <= 2 && f.accept_mode == 0 && s->draw_spread && s->draw_ws &&
-                        c.vocab <= kDrawSliceIds * kDrawMaxSlices;
+                        c.vocab <= kDrawMaxVocab;
     s->stage_count += spread ? kFinishDrawStages : 1;
     if (spread) f.dws = s->draw_ws;
     if (!s->gemm_only) HIPC(spread ? launch_finish_draw(f, s->stream) : launch_finish(f, s->stream));
@@ -2146,9 +2146,8 @@ extern "C" int bild_set_sampling(bild_state* s, float top_p, const float* u_smal
         HIPC(hipMemcpy(s->u_dev[w], us[w], sizeof(float) * (size_t)s->max_len, hipMemcpyHostToDevice));
     }
     if (!s->draw_ws) {
-        rc = dev_alloc(s->allocs, (void**)&s->draw_ws, sizeof(DrawWs));
+        rc = dev_alloc(s->allocs, (void**)&s->draw_ws, std::max(draw_ws_bytes(s->ms[0].m->cfg.vocab), draw_ws_bytes(s->ms[1].m->cfg.vocab)));
         if (rc) return rc;
-        HIPC(hipMemset(s->draw_ws, 0, sizeof(DrawWs)));
         drop_graphs(s);  // (none can have been captured with a draw yet; kept for safety)
     }
     if (s->top_p != top_p) drop_graphs(s);

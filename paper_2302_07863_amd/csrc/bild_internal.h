@@ -316,18 +316,35 @@ struct FinishArgs {
 
 // Workspace of the nucleus draw that is spread over many workgroups (policy.hip).  Probability masses are integers
 // there: exp(z - max) in units of 2^-40, so sums do not depend on the order of their terms and atomics stay reproducible.
-constexpr int kDrawSliceIds = 1024;   // ids per workgroup of a sweep
-constexpr int kDrawMaxSlices = 1024;  // vocabularies of up to 1 048 576 ids
+// A thread has 4 ids of a row of up to 65 536, else 16: every workgroup reads the bins of all slices, 2 KiB each.
+constexpr int kDrawThreads = 256, kDrawBins = 256;  // (a thread has a bin)
+constexpr int kDrawFew = 4, kDrawMany = 16;
+constexpr int kDrawMaxSlices = 256;  // vocabularies of up to 1 048 576 ids
+constexpr int kDrawMaxVocab = kDrawMaxSlices * kDrawThreads * kDrawMany;
+__host__ __device__ constexpr int draw_per(int vocab) { return vocab <= 65536 ? kDrawFew : kDrawMany; }
+__host__ __device__ constexpr int draw_slices(int vocab) { return (vocab + kDrawThreads * draw_per(vocab) - 1) / (kDrawThreads * draw_per(vocab)); }
 struct DrawWs {
     int row, pos;                     // row of the pass the token is drawn from, sequence position it will take
     float m;                          // that row's largest logit
-    uint32_t key;                     // nucleus threshold: members have float_key(z) >= key
-    unsigned long long mass;          // mass of the nucleus
-    unsigned long long pad;
+    unsigned n;                       // ids listed
+    int bin;                          // the threshold's bin
+    int pad;
+    unsigned long long target;        // mass the nucleus has to reach
+    unsigned long long above, upto;   // mass of the bins before the threshold's, and with it
+    float u;                          // the uniform number of that position
     StatPart merged[kMaxRows];        // merged LM-head statistics of the pass (one "partial" per row for the commit)
-    unsigned long long hist[4][256];  // mass per value of key byte 3 (most significant) .. 0 among the keys still in play
-    unsigned long long slice[kDrawMaxSlices];  // members' mass per slice of kDrawSliceIds ids
+    unsigned long long slice[kDrawMaxSlices];  // a slice's mass in the bins before the threshold's
+    // behind it: [slices][kDrawBins] masses of the bins, and of the parts of the threshold's bin, then the ids in that bin as
+    // (logit, id), up to the vocabulary
+    __host__ __device__ unsigned long long* bins(int s) { return (unsigned long long*)(this + 1) + (size_t)s * kDrawBins; }
+    __host__ __device__ unsigned long long* parts(int nslices, int s) { return bins(nslices + s); }
+    __device__ const unsigned long long* parts(int nslices, int s) const { return const_cast<DrawWs*>(this)->bins(nslices + s); }
+    __device__ uint2* list(int nslices) { return (uint2*)bins(2 * nslices); }
+    __device__ const uint2* list(int nslices) const { return const_cast<DrawWs*>(this)->list(nslices); }
 };
+__host__ __device__ constexpr size_t draw_ws_bytes(int vocab) {
+    return sizeof(DrawWs) + (size_t)draw_slices(vocab) * kDrawBins * 16 + (size_t)vocab * 8;
+}
 
 size_t gemm_lds_bytes(const GemmArgs& a, int dtype);
 
@@ -404,9 +421,9 @@ struct CtlArgs {
     int n, n2;
 };
 hipError_t launch_ctl(const CtlArgs& a, hipStream_t st);
-// sampling variant with the threshold rule: the same result as launch_finish, the draw spread over the chip (seven launches)
+// sampling variant with the threshold rule: the same result as launch_finish, the draw spread over the chip (three launches)
 hipError_t launch_finish_draw(const FinishArgs& a, hipStream_t st);
-constexpr int kFinishDrawStages = 7;
+constexpr int kFinishDrawStages = 3;
 hipError_t launch_row_copy(const RowCopyArgs& a, hipStream_t st);
 hipError_t kernels_init();  // one-time function attributes, which also load the kernels; call before any stream capture
 // (called by kernels_init)

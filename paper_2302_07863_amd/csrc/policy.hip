@@ -271,9 +271,12 @@ __device__ __forceinline__ void merge_partials(const FinishArgs& a, float* rm, f
     __syncthreads();
 }
 
-// drawn_in >= 0: the token of the sampling variant, drawn before the call (finish_draw_kernel)
-template <bool SAMPLE>
-__device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int drawn_in = -1) {
+// draw(): the token of the sampling variant, drawn from what draw_bins_kernel and draw_split_kernel left; -1: none
+struct NoDraw {
+    __device__ __forceinline__ int operator()() const { return -1; }
+};
+template <bool SAMPLE, class Draw = NoDraw>
+__device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, Draw&& draw = Draw()) {
     float* rm = (float*)lds;
     float* rsum = rm + kMaxRows;
     int* ridx = (int*)(rsum + kMaxRows);
@@ -292,7 +295,7 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, int 
         merge_partials(a, rm, rsum, ridx, [&] { if (a.mode == 1) z_draft = a.zt[a.row_off + min(lane, max(a.T - 2, 0))]; });
     // Sampling variant: the token that will be committed is drawn by the whole workgroup from the row the
     // policy selects (the last row of a step; row r of a review), at the position it will occupy.
-    int drawn = drawn_in;
+    int drawn = draw();
     int r_given = -1;  // rejection-sampling acceptance: the index of the first refused draft (n: none), decided here
     if (SAMPLE && a.top_p > 0.f && a.mode <= 2) {
         int* sel = (int*)(lds + kFinishLds);  // [0] row, [1] position
@@ -488,266 +491,408 @@ __global__ __launch_bounds__(1024) void finish_sample_kernel(const FinishArgs a)
 // Nucleus draw spread over the chip (sampling variant with the threshold rule of the review).
 //
 // The single-workgroup draw above sweeps a row of logits eight times on one compute unit (80 us at 32 128 ids, 650 us
-// at 250 112).  Here the row is cut into slices of kDrawSliceIds ids, one workgroup each, and every probability mass
+// at 250 112).  Here the row is cut into slices (draw_per), one workgroup each, and every probability mass
 // is an INTEGER: exp(z - max) in units of 2^-40, truncated.  Integer sums do not depend on the order of their terms,
-// so masses can be added with atomics and the result is still the same on every run; and the nucleus mass found by the
-// threshold search equals the sum of the members' masses of the walk exactly, so the walk always ends inside the nucleus.
+// so the result is the same on every run; and the nucleus mass found by the threshold search equals the sum of the
+// members' masses of the walk exactly, so the walk always ends inside the nucleus.
 //
-//   draw_select_kernel   (1 workgroup)  merges the LM-head partials, applies the rollback test to find the row the
-//                        token comes from, leaves (row, position, max) and the merged statistics in the workspace,
-//                        clears the histograms
-//   draw_sweep_kernel<L> (slices)       L = 0..3: mass per value of key byte 3-L among the ids whose higher key bytes
-//                        equal the threshold's (every workgroup re-derives those bytes from the earlier histograms)
-//   draw_mass_kernel     (slices)       threshold key and nucleus mass complete; members' mass per slice
-//   finish_draw_kernel   (1 workgroup)  floor(u * mass) -> slice -> id by two integer prefix sums; then the policy and
-//                        the commit of finish_body with that token
+//   draw_bins_kernel   (slices)       merges the LM-head partials and applies the rollback test to find the row the token
+//                      comes from (every workgroup for itself; the first leaves row, position, max and the merged statistics),
+//                      then its slice's mass per bin of max - z
+//   draw_split_kernel  (slices)       the bin the threshold lies in, from all slices' bins; its slice's mass in the bins
+//                      before it and in the parts of this bin, and a list of the ids in it
+//   draw_pick_kernel   (1 workgroup)  the threshold key: where more ids are listed than there are threads the part of the bin first,
+//                      then a radix search of the bits in which the candidates' keys differ; floor(u * mass) -> slice -> id by two
+//                      integer prefix sums; then the policy and the commit of finish_body with that token
+//
+// Bound by launches and trips to memory.  A search by the four bytes of the key, a sweep over the row each, with a launch in front
+// to merge and one behind for the members' masses, were seven launches: 4.7 + 4 x 4.6 + 4.7 + 7.5 us at 32 128 ids, 4.8 + 4 x 6.4 + 4.7
+// + 7.9 at 250 112; these are 5.0 + 5.8 + 12.9 and 6.4 + 9.9 + 21.9 us, of which the policy's commit alone takes 4 (a request
+// of 40 drawn tokens, T5 shapes, 12.74 -> 12.22 ms).  Bins by distance from the maximum divide what has any mass evenly (2^-40 of
+// the largest is 27.7 below it), where a key's top byte is a sign and most of an exponent.  Workgroups of 1024 threads 6.4 + 6.1
+// + 15.9 us, slices of 4096 ids at 256 threads 7.0 + 7.6 + 13.2; a list of thousands of ids (a row with one likely id and a flat
+// rest) searched without the parts 35 us, and 81 with a third of the bins for what lies further than 6 below the maximum.
 // =====================================================================================
 typedef unsigned long long u64;
 
 __device__ __forceinline__ u64 mass_units(float z, float m) { return (u64)(expf(z - m) * 1099511627776.f); }  // 2^40
 
-// Sums over the 256 threads of a workgroup: inside each wavefront by lane shifts (no barrier), then the four wave totals
-// through LDS (buf: 4 words).  Both end with a barrier, so buf may be reused at once.
-__device__ __forceinline__ u64 suffix_sum_256(u64 v, u64* buf) {  // sum over the threads at and above this one
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const u64 t = __shfl_down(v, off, 64);
-        if (lane + off < 64) v += t;
-    }
-    if (lane == 0) buf[wave] = v;
-    __syncthreads();
-    u64 add = 0;
-#pragma unroll
-    for (int w = 1; w < 4; ++w)
-        if (w > wave) add += buf[w];
-    __syncthreads();
-    return v + add;
+// Place of an id among the bins: not decreasing where z falls (rounding keeps the order), so that an id in an earlier bin, or an
+// earlier part of the same bin, has a larger key.  Ids without mass may be in any bin (NaN: the first).
+__device__ __forceinline__ float draw_place(float z, float m) { return fmaxf((m - z) * (kDrawBins / 28.f), 0.f); }
+__device__ __forceinline__ int draw_bin(float place) { return (int)fminf(place, (float)(kDrawBins - 1)); }
+__device__ __forceinline__ int draw_part(float place, int bin) { return draw_bin((place - (float)bin) * (float)kDrawBins); }
+
+// Sum over the threads up to and with this one, in `all` over all: lane shifts inside a wavefront, the waves' totals through LDS
+// (buf: a word per wave; it may be used again behind the caller's next barrier).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u64 dpp_add(u64 v) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, ROWS, 0xF, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, ROWS, 0xF, false);
+    return v + ((u64)hi << 32 | lo);
 }
-__device__ __forceinline__ u64 prefix_excl_256(u64 v, u64* buf) {  // sum over the threads below this one
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    u64 acc = v;
+__device__ __forceinline__ u64 wave_prefix(u64 v) {
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 to rows 1 and 3
+    return dpp_add<0x143, 0xC>(v);  // row_bcast:31 to rows 2 and 3
+}
+__device__ __forceinline__ u64 prefix_sum(u64 v, u64* buf, u64& all) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    v = wave_prefix(v);
+    if (lane == 63) buf[wave] = v;
+    __syncthreads();
+    u64 before = 0;
+    all = 0;
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const u64 t = __shfl_up(acc, off, 64);
-        if (lane >= off) acc += t;
+    for (int w = 0; w < kDrawThreads / 64; ++w) {
+        const u64 t = buf[w];
+        all += t;
+        before += w < wave ? t : 0ull;
     }
-    if (lane == 63) buf[wave] = acc;
-    __syncthreads();
-    u64 add = 0;
-#pragma unroll
-    for (int w = 0; w < 3; ++w)
-        if (w < wave) add += buf[w];
-    __syncthreads();
-    return acc + add - v;
+    return v + before;
 }
 
-// The threshold's key bytes decided by histograms 0..LEVELS-1 (thread j holds bin j of each), the mass of the keys
-// strictly above that prefix's range, and the target top_p * total.  With S_l[j] the mass of bins j.. of level l, the byte
-// of level l is the largest j with above + S_l[j] >= target (0 if none); `in_play` returns the mass of that bin onward.
-// lds: 256 u64 + 8 u64.  All threads return the same values.
-template <int LEVELS>
-__device__ __forceinline__ void threshold_prefix(const DrawWs* ws, float top_p, u64* lds, uint32_t& K, u64& above, u64& at_or_above) {
-    const int tid = threadIdx.x;
-    u64 h[LEVELS > 0 ? LEVELS : 1];
+// This workgroup's slice of the row: ids first + c * kDrawThreads.  PER: of a thread (draw_per)
+template <int PER>
+__device__ __forceinline__ void load_slice(float (&z)[PER], const FinishArgs& a, int row, int first) {
+    const float* zr = a.logits + (size_t)(a.row_off + row) * a.vocab;
 #pragma unroll
-    for (int l = 0; l < LEVELS; ++l) h[l] = ws->hist[l][tid];
-    u64* sc = lds + 256;
-    K = 0;
-    above = 0;
-    at_or_above = 0;
-    u64 target = 0;
-#pragma unroll
-    for (int l = 0; l < LEVELS; ++l) {
-        const u64 S = suffix_sum_256(h[l], lds);       // mass of bins tid..255
-        if (l == 0) {
-            if (tid == 0) sc[0] = (u64)ceil((double)top_p * (double)S);
-            __syncthreads();
-            target = sc[0];
-        }
-        const u64 Snext = S - h[l];                    // mass of bins tid+1..255
-        const bool here = above + S >= target || tid == 0;
-        const bool next = tid < 255 && above + Snext >= target;
-        if (here && !next) {                           // exactly one thread
-            sc[1] = (u64)tid;
-            sc[2] = above + Snext;
-            sc[3] = above + S;
-        }
-        __syncthreads();
-        K |= (uint32_t)sc[1] << (24 - 8 * l);
-        above = sc[2];
-        at_or_above = sc[3];
-        __syncthreads();
-    }
+    for (int c = 0; c < PER; ++c) z[c] = zr[min(first + c * kDrawThreads, a.vocab - 1)];
 }
 
-__global__ __launch_bounds__(1024) void draw_select_kernel(const FinishArgs a) {
+template <int PER>
+__global__ __launch_bounds__(kDrawThreads) void draw_bins_kernel(const FinishArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[kFinishLds];
+    __shared__ u64 bins[kDrawBins];
     float* rm = (float*)lds;
     float* rsum = rm + kMaxRows;
     int* ridx = (int*)(rsum + kMaxRows);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const Ctl* c = a.ctl;
-    const int c_ylen = c->y_len, c_ds = c->draft_start;
+    const int c_ylen = c->y_len, c_ds = c->draft_start, n = a.T - 1;
     const float c_arb = c->alpha_rb;
     DrawWs* ws = a.dws;
-    u64* hist = &ws->hist[0][0];
-    for (int i = tid; i < 4 * 256; i += blockDim.x) hist[i] = 0ull;
-    merge_partials(a, rm, rsum, ridx, [] {});
-    if (tid < a.T) {
-        StatPart sp;
-        sp.m = rm[tid]; sp.s = rsum[tid]; sp.idx = ridx[tid]; sp.pad = 0;
-        ws->merged[a.row_off + tid] = sp;
-    }
-    if (tid == 0) {
-        int row = a.T - 1, pos = c_ylen;
-        if (a.mode == 1) {  // review: the first draft whose cross-entropy exceeds the threshold (Section 3.4), else the row after the last
-            const int n = a.T - 1;
-            row = n;
-            for (int i = 0; i < n; ++i)
-                if ((rm[i] + logf(rsum[i])) - a.zt[a.row_off + i] > c_arb) {
-                    row = i;
-                    break;
-                }
-            pos = c_ds + row;
-        }
-        ws->row = row;
-        ws->pos = pos;
-        ws->m = rm[row];
-    }
-}
-
-template <int L>
-__global__ __launch_bounds__(256) void draw_sweep_kernel(const FinishArgs a) {
-    __shared__ u64 lds[256 + 8];
-    __shared__ u64 bins[256];
-    const int tid = threadIdx.x;
-    const DrawWs* ws = a.dws;
-    const int row = ws->row;
-    const float m = ws->m;
-    const float* z = a.logits + (size_t)(a.row_off + row) * a.vocab;
-    constexpr int PER = kDrawSliceIds / 256;
-    const int i0 = (int)blockIdx.x * kDrawSliceIds + tid;
-    float zi[PER];
-#pragma unroll
-    for (int c = 0; c < PER; ++c) zi[c] = z[min(i0 + c * 256, a.vocab - 1)];
+    const int first = (int)blockIdx.x * (PER * kDrawThreads) + tid;
+    float z[PER], z_draft = 0.f;
+    load_slice(z, a, n, first);  // (the row unless a draft is refused)
     bins[tid] = 0ull;
-    uint32_t K = 0;
-    u64 above, at;
-    threshold_prefix<L>(ws, a.top_p, lds, K, above, at);  // (barriers inside; L == 0: none, hence the one below)
-    __syncthreads();
-    constexpr int shift = 24 - 8 * L;
+    merge_partials(a, rm, rsum, ridx, [&] { if (a.mode == 1) z_draft = a.zt[a.row_off + min(lane, max(n - 1, 0))]; });
+    int row = n, pos = c_ylen;
+    if (a.mode == 1) {  // review: the first draft whose cross-entropy exceeds the threshold (Section 3.4), else the row after the last
+        const int t = min(lane, n);
+        const u64 over = __builtin_amdgcn_ballot_w64(lane < n && (rm[t] + logf(rsum[t])) - z_draft > c_arb);
+        row = over ? (int)__builtin_ctzll(over) : n;
+        pos = c_ds + row;
+        if (row != n) load_slice(z, a, row, first);
+    }
+    const float m = rm[row];
 #pragma unroll
-    for (int c = 0; c < PER; ++c) {
-        const uint32_t k = float_key(zi[c]);
-        bool mine = i0 + c * 256 < a.vocab;
-        if constexpr (L > 0) mine = mine && ((k ^ K) >> (shift + 8)) == 0u;  // the higher key bytes are the threshold's
-        if (mine) {
-            const u64 e = mass_units(zi[c], m);
-            if (e) atomicAdd(&bins[(k >> shift) & 255u], e);
+    for (int k = 0; k < PER; ++k)
+        if (first + k * kDrawThreads < a.vocab) {
+            const u64 e = mass_units(z[k], m);
+            if (e) atomicAdd(&bins[draw_bin(draw_place(z[k], m))], e);
+        }
+    __syncthreads();
+    ws->bins(blockIdx.x)[tid] = bins[tid];
+    if (blockIdx.x == 0) {
+        if (tid < a.T) {
+            StatPart sp;
+            sp.m = rm[tid]; sp.s = rsum[tid]; sp.idx = ridx[tid]; sp.pad = 0;
+            ws->merged[a.row_off + tid] = sp;
+        }
+        if (tid == 0) {
+            ws->row = row;
+            ws->pos = pos;
+            ws->m = m;
+            ws->n = 0u;
         }
     }
-    __syncthreads();
-    const u64 mine = bins[tid];
-    if (mine) atomicAdd(&a.dws->hist[L][tid], mine);
 }
 
-__global__ __launch_bounds__(256) void draw_mass_kernel(const FinishArgs a) {
-    __shared__ u64 lds[256 + 8];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <int PER>
+__global__ __launch_bounds__(kDrawThreads) void draw_split_kernel(const FinishArgs a) {
+    __shared__ u64 parts[kDrawBins], buf[kDrawThreads / 64], buf2[kDrawThreads / 64], found[2];
+    __shared__ unsigned listed, base;
+    __shared__ int at_bin;
+    const int tid = threadIdx.x, lane = tid & 63, nslices = (int)gridDim.x;
     DrawWs* ws = a.dws;
-    const int row = ws->row;
+    const int first = (int)blockIdx.x * (PER * kDrawThreads) + tid;
     const float m = ws->m;
-    const float* z = a.logits + (size_t)(a.row_off + row) * a.vocab;
-    constexpr int PER = kDrawSliceIds / 256;
-    const int i0 = (int)blockIdx.x * kDrawSliceIds + tid;
-    float zi[PER];
+    const int pos = ws->pos;
+    float z[PER];
+    load_slice(z, a, ws->row, first);
+    const float u = a.u[pos];
+    u64 mine = 0, total;  // of bin tid
+    for (int s = 0; s < nslices; s += 8) {
+        u64 v[8];
 #pragma unroll
-    for (int c = 0; c < PER; ++c) zi[c] = z[min(i0 + c * 256, a.vocab - 1)];
-    uint32_t K;
-    u64 above, at;
-    threshold_prefix<4>(ws, a.top_p, lds, K, above, at);
-    u64 mine = 0;
+        for (int k = 0; k < 8; ++k) v[k] = ws->bins(min(s + k, nslices - 1))[tid];
 #pragma unroll
-    for (int c = 0; c < PER; ++c)
-        if (i0 + c * 256 < a.vocab && float_key(zi[c]) >= K) mine += mass_units(zi[c], m);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-    if (lane == 0) lds[wave] = mine;
-    __syncthreads();
+        for (int k = 0; k < 8; ++k) mine += s + k < nslices ? v[k] : 0ull;
+    }
+    parts[tid] = 0ull;
     if (tid == 0) {
-        ws->slice[blockIdx.x] = lds[0] + lds[1] + lds[2] + lds[3];
+        listed = 0u;
+        at_bin = kDrawBins;  // (no mass, or a target above all of it: every id is a member)
+    }
+    const u64 upto = prefix_sum(mine, buf, total);
+    const u64 target = (u64)ceil((double)a.top_p * (double)total);
+    if (upto >= target && upto - mine < target) {  // one thread at most
+        at_bin = tid;
+        found[0] = upto - mine;
+        found[1] = upto;
+    }
+    __syncthreads();
+    const int b = at_bin;
+    u64 mass = 0, in[PER];  // (lanes with an id in the bin)
+    unsigned many = 0, from = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        bool here = false;
+        if (first + k * kDrawThreads < a.vocab) {
+            const float place = draw_place(z[k], m);
+            const int bin = draw_bin(place);
+            if (bin <= b) {
+                const u64 e = mass_units(z[k], m);
+                here = bin == b && e != 0ull;
+                mass += bin < b ? e : 0ull;
+                if (here) atomicAdd(&parts[draw_part(place, b)], e);
+            }
+        }
+        in[k] = __builtin_amdgcn_ballot_w64(here);
+        many += (unsigned)__builtin_popcountll(in[k]);
+    }
+    if (many != 0u) {  // (uniform over the wavefront)
+        if (lane == 0) from = atomicAdd(&listed, many);
+        from = __builtin_amdgcn_readfirstlane(from);
+    }
+    u64 slice;
+    prefix_sum(mass, buf2, slice);  // (a barrier: `listed` and `parts` are complete)
+    ws->parts(nslices, blockIdx.x)[tid] = parts[tid];
+    if (tid == 0) {
+        base = listed ? atomicAdd(&ws->n, listed) : 0u;
+        ws->slice[blockIdx.x] = slice;
         if (blockIdx.x == 0) {
-            ws->key = K;
-            ws->mass = at;  // every key >= K: the mass above the last byte's bin plus that bin's
+            ws->u = u;
+            ws->bin = b;
+            ws->target = target;
+            ws->above = b == kDrawBins ? total : found[0];
+            ws->upto = b == kDrawBins ? total : found[1];
+        }
+    }
+    __syncthreads();
+    if (many != 0u) {
+        uint2* list = ws->list(nslices) + base;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (in[k] >> lane & 1ull) list[from + (unsigned)__builtin_popcountll(in[k] & ((1ull << lane) - 1ull))] = make_uint2(__float_as_uint(z[k]), (unsigned)(first + k * kDrawThreads));
+            from += (unsigned)__builtin_popcountll(in[k]);
         }
     }
 }
 
-__global__ __launch_bounds__(256) void finish_draw_kernel(const FinishArgs a, const int nslices) {
+template <int PER>
+__global__ __launch_bounds__(kDrawThreads) void draw_pick_kernel(const FinishArgs a, const int nslices) {
     __shared__ __attribute__((aligned(16))) char lds[kFinishLds];
-    __shared__ u64 buf[256];
-    __shared__ u64 sc[4];
-    const int tid = threadIdx.x;
+    __shared__ u64 bins[kDrawBins], slice[kDrawMaxSlices], buf[2][kDrawThreads / 64], found[2];
+    constexpr int IDS = PER * kDrawThreads;
+    __shared__ float zs[IDS + kDrawThreads];  // (a word between a thread's ids and the next one's)
+    __shared__ float low[kDrawThreads / 64], high[kDrawThreads / 64];
+    __shared__ uint2 cand[kDrawThreads];
+    __shared__ int at_bin, token;
+    __shared__ unsigned ncand;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // (requested ahead of the policy's words and the statistics: one trip for all of it)
     const DrawWs* ws = a.dws;
-    const int row = ws->row, pos = ws->pos;
-    const float m = ws->m;
-    const uint32_t K = ws->key;
-    const u64 mass = ws->mass;
-    const float u = a.u[pos];
-    // target: the first member (ids increasing) whose running mass exceeds u * mass, i.e. exceeds t = floor(u * mass)
-    const u64 t = (u64)((double)u * (double)mass);
-    // ---- slice ----
-    constexpr int SPT = kDrawMaxSlices / 256;  // slices per thread, consecutive
-    u64 sm[SPT], mine = 0;
-#pragma unroll
-    for (int k = 0; k < SPT; ++k) {
-        const int sl = tid * SPT + k;
-        sm[k] = sl < nslices ? ws->slice[sl] : 0ull;
-        mine += sm[k];
-    }
-    const u64 before = prefix_excl_256(mine, buf);
-    if (tid == 0) { sc[0] = 0; sc[1] = 0; }
-    __syncthreads();
-    if (before <= t && t < before + mine) {  // exactly one thread (the masses add up to `mass` > t exactly)
-        u64 run = before;
-        int k = 0;
-        for (; k < SPT - 1; ++k) {
-            if (t < run + sm[k]) break;
-            run += sm[k];
+    const int row = ws->row, n = (int)ws->n, bin = ws->bin;
+    const float m = ws->m, u = ws->u;
+    const u64 target = ws->target;
+    u64 above = ws->above, upto = ws->upto;
+    const uint2* list = ws->list(nslices);
+    uint2 own = list[min(tid, a.vocab - 1)];  // this thread's candidate
+    const u64 of_slice = ws->slice[tid];
+    finish_body<false>(a, lds, [&]() -> int {
+        slice[tid] = tid < nslices ? of_slice : 0ull;
+        if (tid == 0) {
+            token = ((const int*)lds)[2 * kMaxRows + row];  // (argmax; stays only where no id has any mass)
+            ncand = 0u;
         }
-        sc[0] = (u64)(tid * SPT + k);
-        sc[1] = run;
-    }
-    __syncthreads();
-    const int sl = (int)sc[0];
-    const u64 rem = t - sc[1];  // mass to pass inside the slice
-    __syncthreads();
-    // ---- id inside the slice: thread j owns ids 4j .. 4j+3 of it ----
-    const float* z = a.logits + (size_t)(a.row_off + row) * a.vocab;
-    constexpr int PER = kDrawSliceIds / 256;
-    const int i0 = sl * kDrawSliceIds + tid * PER;
-    u64 e[PER], tot = 0;
+        // (wavefronts with candidates as a whole, the last one's surplus lanes with `there` false)
+        int many = n, part = -1;  // candidates; part of the bin they are in
+        auto each = [&](auto&& f) {
+            if (many <= kDrawThreads) {
+                if (wave * 64 < many) f(own, tid < many);
+                return;
+            }
+            for (int i = tid; i - lane < n; i += kDrawThreads) {  // (so many ids so close together)
+                const uint2 e = list[min(i, n - 1)];
+                f(e, i < n && draw_part(draw_place(__uint_as_float(e.x), m), bin) == part);
+            }
+        };
+        if (n > kDrawThreads) {  // the part of the bin that the threshold lies in, and a thread for each id in it
+            u64 sum = 0, all;
+            for (int s = 0; s < nslices; s += 8) {
+                u64 v[8];
 #pragma unroll
-    for (int c = 0; c < PER; ++c) {
-        const float zi = z[min(i0 + c, a.vocab - 1)];
-        e[c] = (i0 + c < a.vocab && float_key(zi) >= K) ? mass_units(zi, m) : 0ull;
-        tot += e[c];
-    }
-    const u64 bef = prefix_excl_256(tot, buf);
-    if (tid == 0) sc[2] = (u64)(uint32_t)ws->merged[a.row_off + row].idx;  // (never used: rem < the slice's mass)
-    __syncthreads();
-    if (bef <= rem && rem < bef + tot) {
-        u64 run = bef;
-        int c = 0;
-        for (; c < PER - 1; ++c) {
-            run += e[c];
-            if (run > rem) break;
+                for (int k = 0; k < 8; ++k) v[k] = ws->parts(nslices, min(s + k, nslices - 1))[tid];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sum += s + k < nslices ? v[k] : 0ull;
+            }
+            const u64 s = above + prefix_sum(sum, buf[0], all);
+            if (s >= target && s - sum < target) {  // exactly one thread
+                at_bin = tid;
+                found[0] = s - sum;
+                found[1] = s;
+            }
+            __syncthreads();
+            part = at_bin;
+            above = found[0];
+            upto = found[1];
+            for (int s0 = wave; s0 < nslices; s0 += 4 * (kDrawThreads / 64)) {  // members in the parts before it, to their slices
+                u64 v[4][4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[k][j] = ws->parts(nslices, min(s0 + k * (kDrawThreads / 64), nslices - 1))[j * 64 + lane];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int sl = s0 + k * (kDrawThreads / 64);
+                    u64 t = 0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) t += j * 64 + lane < part ? v[k][j] : 0ull;
+                    t = wave_prefix(t);
+                    if (lane == 63 && sl < nslices) slice[sl] += t;
+                }
+            }
+            for (int i0 = tid; i0 < n; i0 += 8 * kDrawThreads) {
+                uint2 e[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) e[k] = list[min(i0 + k * kDrawThreads, n - 1)];
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (i0 + k * kDrawThreads < n && draw_part(draw_place(__uint_as_float(e[k].x), m), bin) == part) {
+                        const unsigned at = atomicAdd(&ncand, 1u);
+                        if (at < (unsigned)kDrawThreads) cand[at] = e[k];
+                    }
+            }
+            __syncthreads();
+            many = (int)ncand;
+            own = cand[min(tid, many - 1) & (kDrawThreads - 1)];
         }
-        sc[2] = (u64)(i0 + c);
-    }
-    __syncthreads();
-    finish_body<false>(a, lds, (int)sc[2]);
+        uint32_t K = 0u;
+        if (n > 0) {
+            float zmin = INFINITY, zmax = -INFINITY;
+            each([&](const uint2& e, bool there) {
+                const float z = __uint_as_float(e.x);
+                zmin = there ? fminf(zmin, z) : zmin;
+                zmax = there ? fmaxf(zmax, z) : zmax;
+            });
+            zmin = -wave_max(-zmin);
+            zmax = wave_max(zmax);
+            if (lane == 0) {
+                low[wave] = zmin;
+                high[wave] = zmax;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kDrawThreads / 64; ++w) {
+                zmin = fminf(zmin, low[w]);
+                zmax = fmaxf(zmax, high[w]);
+            }
+            // (of two zeros either may have been taken, and they have keys of their own)
+            const uint32_t kmin = float_key(zmin == 0.f ? -0.f : zmin), kmax = float_key(zmax == 0.f ? 0.f : zmax);
+            // The largest key whose members' mass reaches the target, as its distance from the least: eight bits at a time
+            uint32_t D = 0u;
+            const int bits = kmax == kmin ? 0 : 32 - __builtin_clz(kmax - kmin);
+            for (int shift = (bits + 7) / 8 * 8 - 8; shift >= 0; shift -= 8) {
+                bins[tid] = 0ull;
+                __syncthreads();
+                each([&](const uint2& e, bool there) {
+                    const float z = __uint_as_float(e.x);
+                    const uint32_t k = float_key(z) - kmin;
+                    if (there && (shift == 24 || ((k ^ D) >> (shift + 8)) == 0u)) atomicAdd(&bins[(k >> shift) & 255u], mass_units(z, m));
+                });
+                __syncthreads();
+                u64 all;
+                const u64 mine = bins[kDrawBins - 1 - tid];
+                const u64 s = above + prefix_sum(mine, buf[shift >> 3 & 1], all);
+                if (s >= target && s - mine < target) {  // exactly one thread
+                    at_bin = kDrawBins - 1 - tid;
+                    found[0] = s - mine;
+                    found[1] = s;
+                }
+                __syncthreads();
+                D |= (uint32_t)at_bin << shift;
+                above = found[0];
+                upto = found[1];
+            }
+            K = kmin + D;
+            // the list's members to their slices (a slice's ids lie together: a sum over the wavefront for each slice in it)
+            each([&](const uint2& e, bool there) {
+                const float z = __uint_as_float(e.x);
+                const bool member = there && float_key(z) >= K;
+                const u64 units = member ? mass_units(z, m) : 0ull;
+                for (u64 left = __builtin_amdgcn_ballot_w64(member); left != 0ull;) {
+                    const unsigned s = __builtin_amdgcn_readlane(e.y, (int)__builtin_ctzll(left)) / IDS;
+                    const bool here = member && e.y / IDS == s;
+                    const u64 sum = wave_prefix(here ? units : 0ull);
+                    if (lane == 63) atomicAdd(&slice[s], sum);
+                    left &= ~__builtin_amdgcn_ballot_w64(here);
+                }
+            });
+        }
+        __syncthreads();
+        // target of the walk: the first member (ids increasing) whose running mass exceeds u * mass, i.e. exceeds t = floor(u * mass)
+        const u64 t = (u64)((double)u * (double)upto);
+        if (tid == 0) {
+            at_bin = 0;
+            found[0] = 0;
+        }
+        u64 all;
+        {
+            const u64 mine = slice[tid];
+            const u64 s = prefix_sum(mine, buf[0], all);
+            if (s - mine <= t && t < s) {  // exactly one thread (the masses add up to `upto` > t exactly)
+                at_bin = tid;
+                found[0] = s - mine;
+            }
+        }
+        __syncthreads();
+        const u64 rem = t - found[0];  // mass to pass inside the slice, whose ids j * PER .. are thread j's
+        const int base = at_bin * IDS, i0 = base + tid * PER;
+        float z[PER];
+        load_slice(z, a, row, base + tid);
+#pragma unroll
+        for (int c = 0; c < PER; ++c) {
+            const int i = tid + c * kDrawThreads;
+            zs[i + i / PER] = z[c];
+        }
+        __syncthreads();
+        u64 e[PER], tot = 0;
+#pragma unroll
+        for (int c = 0; c < PER; ++c) z[c] = zs[tid * (PER + 1) + c];
+#pragma unroll
+        for (int c = 0; c < PER; ++c) {
+            e[c] = (i0 + c < a.vocab && float_key(z[c]) >= K) ? mass_units(z[c], m) : 0ull;
+            tot += e[c];
+        }
+        const u64 s = prefix_sum(tot, buf[1], all);
+        if (s - tot <= rem && rem < s) {
+            u64 run = s - tot;
+            int c = -1;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                run += e[j];
+                c = c < 0 && run > rem ? j : c;
+            }
+            token = i0 + c;
+        }
+        __syncthreads();
+        return token;
+    });
 }
 
 // What the host changes between passes.  As a kernel's arguments it costs its enqueueing, about 3 us and no wait; as a copy
@@ -775,18 +920,20 @@ hipError_t launch_ctl(const CtlArgs& a, hipStream_t st) {
 hipError_t launch_finish_draw(const FinishArgs& a, hipStream_t st) {
     if (!(a.top_p > 0.f) || a.mode > 2 || a.accept_mode != 0 || !a.logits || !a.u || !a.dws || a.vocab < 1 || a.T < 1 || a.T > kMaxRows)
         return hipErrorInvalidValue;
-    const int ns = (a.vocab + kDrawSliceIds - 1) / kDrawSliceIds;
+    const int ns = draw_slices(a.vocab);
     if (ns > kDrawMaxSlices) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(draw_select_kernel, dim3(1), dim3(a.T > 4 || a.nparts > 1024 ? 1024 : 256), 0, st, a);
-    hipLaunchKernelGGL(draw_sweep_kernel<0>, dim3(ns), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(draw_sweep_kernel<1>, dim3(ns), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(draw_sweep_kernel<2>, dim3(ns), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(draw_sweep_kernel<3>, dim3(ns), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(draw_mass_kernel, dim3(ns), dim3(256), 0, st, a);
-    FinishArgs f = a;  // the commit merges one "partial" per row: the statistics draw_select_kernel left
+    FinishArgs f = a;  // the commit merges one "partial" per row: the statistics draw_bins_kernel left
     f.part = a.dws->merged;  // (address arithmetic only: dws is a device pointer)
     f.nparts = f.part_ld = 1;
-    hipLaunchKernelGGL(finish_draw_kernel, dim3(1), dim3(256), 0, st, f, ns);
+    if (draw_per(a.vocab) == kDrawFew) {
+        hipLaunchKernelGGL(draw_bins_kernel<kDrawFew>, dim3(ns), dim3(kDrawThreads), 0, st, a);
+        hipLaunchKernelGGL(draw_split_kernel<kDrawFew>, dim3(ns), dim3(kDrawThreads), 0, st, a);
+        hipLaunchKernelGGL(draw_pick_kernel<kDrawFew>, dim3(1), dim3(kDrawThreads), 0, st, f, ns);
+    } else {
+        hipLaunchKernelGGL(draw_bins_kernel<kDrawMany>, dim3(ns), dim3(kDrawThreads), 0, st, a);
+        hipLaunchKernelGGL(draw_split_kernel<kDrawMany>, dim3(ns), dim3(kDrawThreads), 0, st, a);
+        hipLaunchKernelGGL(draw_pick_kernel<kDrawMany>, dim3(1), dim3(kDrawThreads), 0, st, f, ns);
+    }
     return hipGetLastError();
 }
 

@@ -77,7 +77,7 @@ def free_running(tokens, stats, ref, n0, fb, rb, margin):
 @pytest.mark.parametrize("name", ["f32-relu-tied", "f32-geglu-untied", "f32-rope-swiglu-deconly", "f32-wide",
                                   "bf16-relu-tied"])
 def test_sampling_toy_parity(name, route, monkeypatch):
-    """Both routes of the draw: spread over the chip (integer masses, one workgroup per 1024 ids; the default) and the
+    """Both routes of the draw: spread over the chip (integer masses, a workgroup per slice; the default) and the
     policy kernel's own single workgroup (BILD_DRAW_ONE_WG=1, read when a state is created)."""
     monkeypatch.setenv("BILD_DRAW_ONE_WG", "0" if route == "spread" else "1")
     R = Rig(bi.toy_pair(**TOY_VARIANTS[name]))
@@ -232,3 +232,34 @@ def test_sampling_vocabulary_beyond_the_register_cache(route, monkeypatch):
             toks, stats = st.generate(R.src, 0.15, 3.0, cfg.max_new)
             print("V=40000", dtype, top_p, res, free_running(toks, stats, ref, R.n0, 0.15, 3.0, _margin(cfg)), ref.stats, flush=True)
             assert res["excused"] <= 3 and len(set(ref.tokens)) > 4      # (every excused step passed the margin rule) a real draw, not one repeated token
+
+
+@pytest.mark.parametrize("top_p", [0.05, TOP_P, 1.0])
+@pytest.mark.parametrize("vocab,logit_scale", [(50, 16.0), (1023, 24.0), (1024, 6.0), (1025, 1e-3), (12289, 1e-3), (65536, 24.0), (65537, 24.0), (69633, 24.0)])
+def test_draw_at_the_edges_of_its_slices(vocab, logit_scale, top_p):
+    """The draw that is spread over the chip against the oracle's on the library's own logits: a slice (1024 ids) less one, exactly,
+    and one id more; the last row with slices of 1024 ids and the first ones with 4096; rows so flat that all ids lie in the
+    threshold's bin, one and many more of them than the picking workgroup's threads keep in registers, and peaked ones.  The
+    margin: z - max is rounded to 2^-24 of at most 32, exp to 2^-23 and its value to 2^-40 of the largest, together 2.2e-6 of a
+    mass, so that a ratio of sums moves by less than 1e-5."""
+    from oracle import sampling
+    R = Rig(bi.toy_pair(vocab=vocab, logit_scale=logit_scale, tie_shift=min(1021, vocab // 3), max_new=24))
+    n = R.n0 + 40
+    us, ul = _uniforms(R.cfg, n)
+    st = R.state(30, 4)
+    st.set_sampling(top_p, us, ul)
+    st.debug_enable_logits(True)
+    st.encode(R.src)
+    ds, off, drawn = R.n0, 0, 0
+    while len(st.sequence()) < R.n0 + 18:
+        pos = len(st.sequence())
+        tok, fallback, _ = st.small_step(0.0)
+        own, dm = sampling.draw(st.debug_logits(pkg.SMALL, 0).astype(np.float64), top_p, float(us[pos]))
+        assert tok == own or dm < 1e-5, ("small", pos, tok, own, dm)
+        off, drawn = off + (tok != own), drawn + 1
+        if fallback:
+            out, r, _ = st.large_verify(3.0)
+            own, dm = sampling.draw(st.debug_logits(pkg.LARGE, r).astype(np.float64), top_p, float(ul[ds + r]))
+            assert out[-1] == own or dm < 1e-5, ("large", ds + r, out[-1], own, dm)
+            off, drawn, ds = off + (out[-1] != own), drawn + 1, len(st.sequence())
+    assert drawn >= 20 and off <= 1, (drawn, off)
