@@ -12,7 +12,7 @@
 //     other waves wait for that too (with the requests first, publishing took 2 to 13 us of each stage: 2048-wide, 16 layers, 527 us
 //     either way because the weights then come later; 4096-wide, 8 layers, 708 -> 663);
 //   - models up to 2048 wide ask for all of the FFN's first weights already when q, k and v are handed over, which keeps the memory
-//     busy while the heads work (536 -> 455 us); so much of a 4096-wide model's would only delay the output projection's activations
+//     busy while the heads work (536 -> 455 us, with heads and projections together); so much of a 4096-wide model's would only delay the output projection's activations
 //     (663 -> 685).  Asking for the FFN's second weights or the next layer's first ones a stage earlier loses for the same reason
 //     (455 -> 466, 482);
 //   - a head's keys are cut into ranges of at least 256 keys, eight at most, a workgroup each, whose waves take blocks of 32; the
@@ -20,11 +20,31 @@
 //   - a workgroup has the same sixteen features of the residual stream in all layers: they stay in registers.
 //
 // us per pass with the LM head, separate kernels / this, at 1064 positions: 2048-wide, 16 layers, 1, 2, 4, 8 rows 661, 731, 784, 805 /
-// 455, 459, 480, 513; 4096-wide, 8 layers 772, 836, 838, 841 / 663, 667, 679, 714, of which the layers' weights alone take 270 and 530 at
-// the 6.1 TB/s of a large copy.
+// 437, 443, 462, 500; 4096-wide, 8 layers 772, 836, 838, 841 / 663, 667, 679, 714, of which the layers' weights alone take 270 and 530 at
+// the 6.1 TB/s of a large copy.  Heads and projections apart, up to 1280 keys (see wide_kernel), before / with: 457, 461, 480, 514 / 442,
+// 444, 462, 500; a load of several tiles' activations for one and two rows (run_few) 442, 444 / 437, 443 and at 200 positions 413, 420 /
+// 409, 413.
 #include "pass_walk.h"
 
 namespace bild {
+
+// What the lane j on has (of sixteen; j is a constant once unrolled).
+template <int J = 1>
+__device__ __forceinline__ uint4 lanes_on(const uint4& v, int j) {
+    if constexpr (J < 8) {
+        if (j == 0) return v;
+        if (j != J) return lanes_on<J + 1>(v, j);
+        return make_uint4(__builtin_amdgcn_update_dpp(0, v.x, 0x100 + J, 0xF, 0xF, true), __builtin_amdgcn_update_dpp(0, v.y, 0x100 + J, 0xF, 0xF, true),
+                          __builtin_amdgcn_update_dpp(0, v.z, 0x100 + J, 0xF, 0xF, true), __builtin_amdgcn_update_dpp(0, v.w, 0x100 + J, 0xF, 0xF, true));
+    }
+    return v;
+}
+
+// (a layout of its own where rows are few: a producer's sum of squares is not behind its features here)
+template <int ROOM>
+struct WideWalk : Walk<false, false, ROOM> {
+    static constexpr bool ROOM1 = false;
+};
 
 // A projection's weights on their way: N input tiles per wave at most, RW feature tiles, in pieces of CH input tiles of which two
 // are requested before their activations are there.  The next piece's activations are requested ahead of the weights that follow
@@ -38,9 +58,10 @@ struct Stream {
         Rsrc rs;
         int k0, n, tk, most;
     };
-    __device__ __forceinline__ static Where where(int wave, const void* w, int unit, int tk, int tiles) {
+    // (tiles first .. end - 1; past the last one: that one again.  Without a request there: 4096-wide, 8 rows, 0.7 % more)
+    __device__ __forceinline__ static Where where(int wave, const void* w, int first, int tk, int end) {
         const Run r = run_of(wave, tk);
-        return {whole((const char*)w + (size_t)unit * RW * tk * kTileBytes), min(r.k0, tk - 1), r.n, tk, tiles - 1 - unit * RW};
+        return {whole((const char*)w + (size_t)first * tk * kTileBytes), min(r.k0, tk - 1), r.n, tk, end - 1 - first};
     }
     __device__ __forceinline__ static void ask(int lane, uint4 (&w)[CH * RW], const Where& a, int i) {
 #pragma unroll
@@ -59,17 +80,18 @@ struct Stream {
             for (uint4& v : w) asm volatile("" : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w));
     }
     template <class Walk>
-    __device__ __forceinline__ void open(const Walk& c, const void* w, int unit, int tk, int tiles) {
-        const Where a = where(c.wave, w, unit, tk, tiles);
+    __device__ __forceinline__ void open(const Walk& c, const void* w, int first, int tk, int end) {
+        const Where a = where(c.wave, w, first, tk, end);
         ask(c.lane, W[0], a, 0);
         if constexpr (NC > 1) ask(c.lane, W[1], a, 1);
     }
     // acc = W x over this wave's inputs, up to eight rows packed (see multiply() in pass_walk.h)
     template <class Walk>
-    __device__ __forceinline__ void run(Walk& c, f32x4 (&acc)[RW], const void* planes, const void* weights, int unit, int tk, int tiles) {
-        const Where a = where(c.wave, weights, unit, tk, tiles);
+    __device__ __forceinline__ void run(Walk& c, f32x4 (&acc)[RW], const void* planes, const void* weights, int first, int tk, int end) {
+        const Where a = where(c.wave, weights, first, tk, end);
         const int k0 = a.k0, n = a.n;
         const Rsrc xs = whole(planes);
+        if constexpr (Walk::KNOWN > 0) return run_few(c, acc, xs, a);
         const int S = tile_bytes(NORM, c.R, false), at = ((c.g * 2 + (c.tok >> 3)) * c.R + c.t8) * 16;
         uint4 X[NC > 1 ? 2 : 1][CH];
         v2u sq[NC > 1 ? 2 : 1][SQ];
@@ -133,6 +155,70 @@ struct Stream {
         }
         if constexpr (NORM) c.ss = quad_rows_sum(ss);
     }
+    // One or two rows: a load brings eight tiles' activations, or four tiles' (see multiply() in pass_walk.h for what a load takes
+    // however few of its bytes differ): columns (tile, row) of a tile's high and low parts, which move down to the rows' own for its
+    // products.  What is in the other columns then is no row's.  All of a wave's activations are asked for at once, its tiles'
+    // sums of squares in a load or two.
+    template <class Walk>
+    __device__ __forceinline__ void run_few(Walk& c, f32x4 (&acc)[RW], const Rsrc xs, const Where& a) {
+        constexpr int R = Walk::KNOWN, SIDE = 8 / R, NX = (N + SIDE - 1) / SIDE, NS = NORM ? (N * R + 15) / 16 : 0;
+        const int S = tile_bytes(NORM, R, false), last = max(a.n - 1, 0), row = min(c.tok & (R - 1), c.T - 1);
+        const int at = ((c.g * 2 + (c.tok >> 3)) * R + row) * 16, beside = (c.tok & 7) / R;
+        uint4 X[NX];
+        v2u sq[NS + 1];
+        auto get = [&] {
+#pragma unroll
+            for (int i = 0; i < NX; ++i) X[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at + min(i * SIDE + beside, last) * S, a.k0 * S, Walk::kIn));
+#pragma unroll
+            for (int i = 0; i < NS; ++i) sq[i] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, min((i * 16 + c.tok) / R, last) * S + R * 128 + row * 8, a.k0 * S, Walk::kIn));
+        };
+        auto missing = [&] {
+            unsigned m = 0u;
+#pragma unroll
+            for (int i = 0; i < NX; ++i) m = max(max(m, max(X[i].x, X[i].y)), max(X[i].z, X[i].w));
+#pragma unroll
+            for (int i = 0; i < NS; ++i) m = max(m, max(sq[i].x, sq[i].y));
+            return __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+        };
+        get();
+        if (__builtin_expect(missing(), 0)) {
+            int tries = 0;
+            bool more;
+#pragma unroll 1
+            do {
+                asm volatile("" ::: "memory");
+                get();
+                more = missing();
+            } while (more && ++tries < c.spins);
+            if (more) c.give_up();
+        }
+        if constexpr (NORM) {
+            float ss = 0.f;
+#pragma unroll
+            for (int i = 0; i < NS; ++i) ss += (i * 16 + c.tok) / R < a.n ? __uint_as_float(sq[i].x) + __uint_as_float(sq[i].y) : 0.f;
+            ss += dpp_f<0x128, 0xF>(0.f, ss);  // row_ror
+            ss += dpp_f<0x124, 0xF>(0.f, ss);
+            ss += dpp_f<0x122, 0xF>(0.f, ss);
+            if constexpr (R == 1) ss += dpp_f<0x121, 0xF>(0.f, ss);
+            c.ss = ss;
+        }
+#pragma unroll
+        for (int q = 0; q < RW; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (i * CH + j < N && i * CH + j < a.n) {
+                    const int tile = i * CH + j;
+                    const uint4 x = lanes_on(X[tile / SIDE], tile % SIDE * R);
+#pragma unroll
+                    for (int q = 0; q < RW; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[i & 1][j * RW + q]), as_bf(x), acc[q], 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 2 < NC) ask(c.lane, W[i & 1], a, i + 2);
+        }
+    }
 };
 
 // One key range of a head: the waves of the head's workgroups take blocks of 32 keys in turn.
@@ -170,8 +256,10 @@ struct WideCut {
     using Ffn = Stream<KF, 1, 8, false>;
 };
 // (pieces of the 4096-wide cut: 8 and 6 tiles a request of q, k, v and the FFN 669 and 673 us, 12 and 12 663, 15 and 18 the same)
-using Cut2048 = WideCut<2, 4, 8, 24, 4, 4>;
+using Cut2048 = WideCut<3, 4, 8, 24, 4, 4>;
 using Cut4096 = WideCut<3, 6, 16, 44, 4, 2>;
+
+__host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Key ranges of a head: 256 keys each, a power of two, as long as there are workgroups.
 __device__ inline int wide_splits(int nkeys, int heads, int groups) {
@@ -181,10 +269,10 @@ __device__ inline int wide_splits(int nkeys, int heads, int groups) {
 }
 
 // Workgroups [0, d / 16) own sixteen features of the residual stream each; the last heads x ranges are the heads'.
-template <bool GATED, class Cut>
+template <bool GATED, class Cut, int ROOM>
 __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    using Way = Walk<false, false, 0>;
+    using Way = WideWalk<ROOM>;
     constexpr int QT = Cut::QT, FT = Cut::FT, DH = kWideHead;
     constexpr bool EARLY = Cut::In::NC <= 2;  // the FFN's first weights all fit the registers
     Way c;
@@ -200,10 +288,22 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
     const int len = *a.len_ptr;
     auto tq = [&] { return 3 * (I >> 4); };
     auto tf = [&] { return GATED ? F >> 3 : F >> 4; };
-    const bool owner = c.wg < d >> 4, qkv = c.wg * QT < tq(), ffn = c.wg * FT < tf();
+    // Who does what.  Apart, up to 1280 keys: the heads are the first workgroups', in ranges that half of those with features
+    // of the residual stream hold, q, k, v and the FFN's input the last ones', so that these weights are asked for while the heads work and
+    // nobody's heads wait behind them.  More keys take more workgroups than that: the heads are the last ones', the rest begins
+    // with the first, q, k, v in two tiles a workgroup (three above 2304 keys, where workgroups with heads had better have no part of
+    // them).  2048-wide, 16 layers, one row, us, two tiles / three / apart: 200 keys 451, 471, 412; 700 468, 471, 420; 1000 471, 472, 438;
+    // 1100 457, 485, 442; 1250 461, 487, 454; 1350 464, 489, 464; 2000 483, 492, 529; 4000 593, 548, 672.  (The two tiles ask for
+    // the second one twice: eight rows 531 at 1400 keys, 524 with registers for two only.)
+    const int keys = len + T;
+    const bool apart = EARLY && keys <= 1280;
+    const int qt = EARLY && !apart && keys <= 2304 ? QT - 1 : QT;
+    const int uq = c.wg - (apart ? a.groups - ceil_div(tq(), QT) : 0), uf = c.wg - (apart ? a.groups - ceil_div(tf(), FT) : 0);
+    const int q0 = uq * qt, q1 = min(q0 + qt, tq()), i0 = uf * FT;  // tiles of the projections
+    const bool owner = c.wg < d >> 4, qkv = uq >= 0 && q0 < tq(), ffn = uf >= 0 && i0 < tf();
     const bool mine = owner && c.wave == 0;
-    const int S = wide_splits(len + T, a.heads, a.groups), place = c.wg - (a.groups - a.heads * S);
-    const bool att = place >= 0;
+    const int S = wide_splits(keys, a.heads, apart ? d >> 5 : a.groups), place = apart ? c.wg : c.wg - (a.groups - a.heads * S);
+    const bool att = place >= 0 && place < a.heads * S;
     const int h = att ? place / S : 0, split = att ? place % S : 0;
 
     float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f), x = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -251,7 +351,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         publish(gn, z + a.at.x1);
     }
     sq.forget();
-    if (qkv) sq.open(c, L->wqkv, c.wg, d >> 5, tq());
+    if (qkv) sq.open(c, L->wqkv, q0, d >> 5, q1);
     for (int l = 0; l < a.n_layers; ++l) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         const bool last = l + 1 == a.n_layers;
@@ -260,7 +360,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         c.place(T, a.room);
         // ---- q, k, v ----
         if (qkv) {
-            const int nf = min(c.wg * QT + c.wave, tq() - 1) * 16 + c.g * 4;
+            const int nf = min(q0 + c.wave, q1 - 1) * 16 + c.g * 4;
             double2 turn[2] = {};  // cos and sin of this lane's two pairs
             if (a.rope && c.wave < QT) {
                 const double2* tb = a.rope + ((size_t)(len + c.t) * DH + nf % DH) / 2;
@@ -270,9 +370,9 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
             const char* xs = pinned(z + a.at.x1);
             f32x4 acc[QT];
             c.template nap<350>();
-            sq.run(c, acc, xs, L->wqkv, c.wg, d >> 5, tq());
+            sq.run(c, acc, xs, L->wqkv, q0, d >> 5, q1);
             leave<QT, true, false>(c, acc);
-            if (c.wave < QT && c.wg * QT + c.wave < tq()) {
+            if (q0 + c.wave < q1) {
                 const float f = norm_factor(c, d, a.eps);
                 f32x4 s = total<QT, true, false>(c, c.wave) * f;
                 const int seg = nf / I, nn = nf - seg * I, pos = len + c.tok, hd = nn / DH, f0 = nn % DH;
@@ -324,7 +424,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
             if constexpr (EARLY) {
                 c.template nap<1000>();  // (behind the keys and values)
                 si.forget();
-                if (ffn) si.open(c, L->win, c.wg, d >> 5, tf());
+                if (ffn) si.open(c, L->win, i0, d >> 5, tf());
             }
         } else {
             const int nblk = (len + 31) >> 5;
@@ -536,7 +636,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
             if (owner) so.open(c, L->wo, c.wg, I >> 5, d >> 4);
             if constexpr (EARLY) {
                 si.forget();
-                if (ffn) si.open(c, L->win, c.wg, d >> 5, tf());
+                if (ffn) si.open(c, L->win, i0, d >> 5, tf());
             }
         }
         // ---- output projection ----
@@ -551,7 +651,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         }
         if constexpr (!EARLY) {
             si.forget();
-            if (ffn) si.open(c, L->win, c.wg, d >> 5, tf());
+            if (ffn) si.open(c, L->win, i0, d >> 5, tf());
         }
         // ---- FFN ----
         if (ffn) {
@@ -559,9 +659,9 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
             const char* xs = pinned(z + a.at.x2);
             f32x4 acc[FT];
             c.template nap<350>();
-            si.run(c, acc, xs, L->win, c.wg, d >> 5, tf());
+            si.run(c, acc, xs, L->win, i0, d >> 5, tf());
             leave<FT, true, false>(c, acc);
-            const int tile = c.wg * FW + c.wave;  // of the hidden state
+            const int tile = uf * FW + c.wave;  // of the hidden state
             if (c.wave < FW && tile < F >> 4) {
                 const float rms = norm_factor(c, d, a.eps);
                 float w[4];
@@ -594,7 +694,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
             lds_barrier();
         }
         sq.forget();
-        if (qkv && !last) sq.open(c, L[1].wqkv, c.wg, d >> 5, tq());
+        if (qkv && !last) sq.open(c, L[1].wqkv, q0, d >> 5, q1);
     }
     if (mine && c.tok < T) {
         *(float4*)(a.x_out + (size_t)c.tok * d + n0()) = x;
@@ -617,7 +717,9 @@ int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
 
 hipError_t wide_init() {
     static hipError_t done = [] {
-        const void* fns[] = {(const void*)wide_kernel<false, Cut2048>, (const void*)wide_kernel<true, Cut2048>, (const void*)wide_kernel<false, Cut4096>, (const void*)wide_kernel<true, Cut4096>};
+#define BILD_W(RV) (const void*)wide_kernel<false, Cut2048, RV>, (const void*)wide_kernel<true, Cut2048, RV>, (const void*)wide_kernel<false, Cut4096, RV>, (const void*)wide_kernel<true, Cut4096, RV>
+        const void* fns[] = {BILD_W(0), BILD_W(1), BILD_W(2)};
+#undef BILD_W
         return raise_lds_limit(fns, 160 * 1024);
     }();
     return done;
@@ -631,10 +733,17 @@ hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
         return hipErrorInvalidValue;
     const dim3 grid(a.groups), block(kPassThreads);
     const bool small = wide_fits<Cut2048>(a.d, a.heads, a.F, gated, a.groups);
-    if (small && gated) hipLaunchKernelGGL((wide_kernel<true, Cut2048>), grid, block, kRel, st, a);
-    else if (small) hipLaunchKernelGGL((wide_kernel<false, Cut2048>), grid, block, kRel, st, a);
-    else if (gated) hipLaunchKernelGGL((wide_kernel<true, Cut4096>), grid, block, kRel, st, a);
-    else hipLaunchKernelGGL((wide_kernel<false, Cut4096>), grid, block, kRel, st, a);
+#define BILD_W(RV)                                                                                                     \
+    do {                                                                                                               \
+        if (small && gated) hipLaunchKernelGGL((wide_kernel<true, Cut2048, RV>), grid, block, kRel, st, a);            \
+        else if (small) hipLaunchKernelGGL((wide_kernel<false, Cut2048, RV>), grid, block, kRel, st, a);               \
+        else if (gated) hipLaunchKernelGGL((wide_kernel<true, Cut4096, RV>), grid, block, kRel, st, a);                \
+        else hipLaunchKernelGGL((wide_kernel<false, Cut4096, RV>), grid, block, kRel, st, a);                          \
+    } while (0)
+    if (a.room == 1) BILD_W(1);
+    else if (a.room == 2) BILD_W(2);
+    else BILD_W(0);
+#undef BILD_W
     return hipGetLastError();
 }
 

@@ -133,3 +133,39 @@ def test_many_layers_and_long_caches(layers, have, monkeypatch):
     worst = [float(np.abs(a - b).max()) for a, b in zip(got["1"], got["0"])]
     print("worst", max(worst), "one token", moved, flush=True)
     assert max(worst) <= min(moved / 4, 2 * parity.logit_tol(cfg))
+
+
+@pytest.mark.parametrize("shape", [dict(), dict(act=bi.ACT_RELU, pos=bi.POS_SINUSOIDAL, d=1280, heads=10, d_ff=96)])
+def test_who_does_what_changes_with_the_length(shape, monkeypatch):
+    """Models up to 2048 wide: workgroups have other parts from 1281 keys and from 2305 on, so that passes on both sides of the lines
+    follow each other in the same hand-over memory; one, two and more rows, whose activations come in loads of their own kinds."""
+    cfg = bi.toy_pair(**{**BASE, **shape, "truncate": False, "n_large": 4, "n_small": 4, "max_new": 2320})
+    R = Rig(cfg)
+    got = {}
+    for one in ("1", "0"):
+        monkeypatch.setenv("BILD_ONE_KERNEL", one)
+        st = R.state(cfg.max_new, 31)
+        st.encode(R.src)
+        st.debug_enable_logits(True)
+        rows_seen = []
+        for n in (1278, 2302, 130):
+            st.seq_truncate(R.n0)
+            st.force_tokens(R.n0, bi.make_tokens(cfg.large.vocab, n - R.n0, seed=n), n)
+            st.large_verify(float("inf"), draft=[])
+            before = st.pass_routes()
+            for rows in (1, 2, 3, 4, 5, 8, 2, 1):
+                st.seq_truncate(n)
+                st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+                rows_seen += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+            st.seq_truncate(n)
+            for _ in range(5):
+                st.small_step(0.0)
+                rows_seen.append(st.debug_logits(pkg.SMALL, 0))
+            now = {k: v - before[k] for k, v in st.pass_routes().items() if v > before[k]}
+            assert now == {"chip" if one == "1" else "kernels": 13}, (n, now)
+        got[one] = np.stack(rows_seen)
+        moved = one_token_moves(st, R, 130)
+        st.close()
+    worst = float(np.abs(got["1"] - got["0"]).max())
+    print("worst", worst, "one token", moved, flush=True)
+    assert worst <= min(moved / 4, 2 * parity.logit_tol(cfg))
