@@ -223,23 +223,26 @@ __global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) vo
             }
         }
     } else {
-        constexpr int D = RT * 2 + FT == 12 ? 3 : 4;  // steps requested ahead
+        // Steps requested ahead: a small step's loads do not cover their trip from L2, a large one's (12 KiB a wave) already fill the
+        // compute unit's queue.  Encode of 40, 77, 201, 512, 1531 tokens, T5 shapes, us: three or four ahead and a request past the end of
+        // a wave's few steps for each 1018, 1125, 1373, 2028, 4562; without those 985, 1086, 1326, 1951, 4424 (998, 1109, 1336, 1992, 4482
+        // before, that run); by size as here 975, 1065, 1326, 1959, 4416; 8, 6, 5, 3 by size 996, 1079, 1333, 2041, 4440 (that run).
+        constexpr int LOADS = RT * 2 + FT, D = LOADS <= 6 ? 6 : LOADS == 8 ? 5 : LOADS <= 10 ? 4 : 2;
         uint4 W[D][FT], X[D][RT][2];
-        auto request = [&](int d, int k) {  // a step past the end reads zeros or another feature's tile, never multiplied
-            const int kc = min(k, ke - 1);
+        auto request = [&](int d, int k) {
 #pragma unroll
-            for (int f = 0; f < FT; ++f) W[d][f] = buf_load(wr, lane16, woff[f] + kc * kTileBytes);
+            for (int f = 0; f < FT; ++f) W[d][f] = buf_load(wr, lane16, woff[f] + k * kTileBytes);
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
-                X[d][r][0] = buf_load(xr, lane16, xoff[r] + kc * (2 * kTileBytes));
-                X[d][r][1] = buf_load(xr, lane16 + kTileBytes, xoff[r] + kc * (2 * kTileBytes));
+                X[d][r][0] = buf_load(xr, lane16, xoff[r] + k * (2 * kTileBytes));
+                X[d][r][1] = buf_load(xr, lane16 + kTileBytes, xoff[r] + k * (2 * kTileBytes));
             }
         };
 #pragma unroll
-        for (int d = 0; d < D; ++d) request(d, kb + d);
+        for (int d = 0; d < D; ++d) request(d, min(kb + d, ke - 1));
         row_sums();
         int k = kb;
-        for (; k + D <= ke; k += D) {
+        for (; k + 2 * D <= ke; k += D) {
 #pragma unroll
             for (int j = 0; j < D; ++j) {
                 multiply(W[j], X[j]);
@@ -248,9 +251,18 @@ __global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) vo
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        // (nothing past the end is asked for: a wave of sliced inputs has a few steps)
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if (k + j < ke) {
+                multiply(W[j], X[j]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (k + j + D < ke) request(j, k + j + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
         for (int j = 0; j < D - 1; ++j)
-            if (k + j < ke) multiply(W[j], X[j]);
+            if (k + j + D < ke) multiply(W[j], X[j]);
     }
     if constexpr (SPLIT) {
 #pragma unroll
