@@ -154,6 +154,34 @@ def test_the_forms_of_a_pass_agree(shape, monkeypatch):
         assert worst <= tol
 
 
+@pytest.mark.parametrize("shape", [dict(d=512, heads=6, d_ff=1024, act=bi.ACT_GATED_GELU), dict(d=768, heads=12, d_ff=2112),
+                                   dict(d=1024, heads=16, d_ff=4096, n_src=290), dict(d=1024, heads=16, d_ff=2816, act=bi.ACT_SWIGLU)])
+def test_loads_of_several_tiles(shape, monkeypatch):
+    """Loads that bring eight tiles' activations of one row, four of two rows, or one, whole and with the last tiles missing, and one
+    row's attention, at the widths where a wave has more than one tile.  Against the separate kernels, as above."""
+    cfg = bi.toy_pair(**{**dict(dtype=bi.DT_BF16, d_head=64, n_src=20, max_new=16, vocab=300, n_large=2, logit_scale=4.0), **shape})
+    R = Rig(cfg)
+    got = {}
+    for form in ("chip", "kernels"):
+        with monkeypatch.context() as m:
+            for k, v in FORMS[form].items():
+                m.setenv(k, v)
+            st = R.state(cfg.max_new, 15)
+        st.encode(R.src)
+        st.debug_enable_logits(True)
+        logits = []
+        for rows in (1, 2, 3, 4, 5, 8, 2, 1):
+            st.seq_truncate(R.n0)
+            before = st.pass_routes()
+            st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+            assert {k for k, v in st.pass_routes().items() if v > before[k]} == {form}, (form, rows)
+            logits += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+        got[form] = np.stack(logits)
+    worst = float(np.abs(got["chip"] - got["kernels"]).max())
+    print(worst)
+    assert worst <= 2 * parity.logit_tol(cfg)
+
+
 F32 = dict(dtype=bi.DT_F32, truncate=False, d=256, heads=4, d_head=64, n_src=20)
 
 

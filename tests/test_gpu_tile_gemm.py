@@ -34,6 +34,14 @@ def test_prompt_lengths_around_the_row_tiles(n_src):
                        n_src=n_src, max_new=6))
 
 
+@pytest.mark.parametrize("n_src", [20, 65])
+@pytest.mark.parametrize("d_ff", [32, 160, 672, 896, 1440, 1664])
+def test_input_counts_around_the_steps_requested_ahead(d_ff, n_src):
+    """The FFN's output projection over inputs in four slices: of one step or none, of fewer steps than are requested ahead (two to six),
+    of one more, of twice as many and one more, the last slice shorter (21 and 45 tiles) or past the end (5)."""
+    _check(bi.toy_pair(dtype=bi.DT_BF16, d_ff=d_ff, n_src=n_src, max_new=4))
+
+
 def test_wide_layers_take_the_shared_row_tiles():
     """1100 rows of a 1024-wide model with 4096 hidden units: the launch shapes whose rows go through LDS."""
     _check(bi.toy_pair(dtype=bi.DT_BF16, d=1024, heads=16, d_head=64, d_ff=4096, vocab=300, n_large=2, n_src=1100, max_new=4,
