@@ -775,6 +775,7 @@ __device__ __forceinline__ void header(Walk& c, const PassArgs& a, int groups) {
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
     char* z = c.scratch(a);
     if (a.cross) request<KD, 4>(c, Wc, L->cwq, h, d >> c.KS, I >> 4);
+    if (a.rel_bias) lds_barrier();  // (a wave reads biases that others have left, and the first scores come before any other barrier)
     for (int l = 0; l < a.n_layers; ++l, z = c.next(z, a.at.layer), c.walk_on(a.at.layer)) {
         L = (const CLayer*)(uintptr_t)a.layers + l;
         asm volatile("" : "+v"(c.lane));

@@ -75,6 +75,36 @@ def test_blocks_of_earlier_keys(shape, monkeypatch):
         assert float(np.abs(got[form] - got["kernels"]).max()) <= tol, form
 
 
+@pytest.mark.parametrize("dtype", [bi.DT_BF16, bi.DT_F32])
+def test_the_longest_row_of_relative_biases(dtype, monkeypatch):
+    """8193 biases of a head take its workgroup seventeen trips to bring to LDS, and the first layer's scores of one row, two and more
+    read any of them: passes of states that have just been made, each against the separate kernels (both within logit_tol of the exact
+    value)."""
+    cfg = bi.toy_pair(dtype=dtype, pos=bi.POS_RELATIVE, rel_max_dist=4096, rel_buckets=64, d=256, heads=4, d_head=64, d_ff=512, truncate=dtype == bi.DT_BF16,
+                      n_small=1, n_large=1, n_src=20, max_new=700)
+    R = Rig(cfg)
+    got = {}
+    for form in ("die", "chip", "kernels") if dtype == bi.DT_BF16 else ("die", "kernels"):
+        logits = []
+        for rows in (1, 2, 4, 13):
+            with monkeypatch.context() as m:
+                for k, v in FORMS[form].items():
+                    m.setenv(k, v)
+                st = R.state(cfg.max_new, 15)
+            st.encode(R.src)
+            st.debug_enable_logits(True)
+            st.force_tokens(R.n0, bi.make_tokens(cfg.large.vocab, 600 - R.n0, seed=7), 600)
+            st.large_verify(float("inf"), draft=[])
+            st.seq_truncate(600)
+            st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+            logits += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+            assert st.pass_routes()["gave_up"] == 0 and st.pass_routes()["chip" if form == "die" and dtype == bi.DT_BF16 and rows > 4 else form] > 0
+            st.close()
+        got[form] = np.stack(logits)
+    for form in set(got) - {"kernels"}:
+        assert float(np.abs(got[form] - got["kernels"]).max()) <= 2 * parity.logit_tol(cfg), form
+
+
 @pytest.mark.parametrize("n_src", [1, 32, 33, 257, 530])
 def test_source_lengths_around_the_key_blocks(n_src):
     _check(n_src=n_src)
