@@ -63,6 +63,9 @@ struct Attend {
     // blocks of sixteen or (bf16) twice sixteen keys; pieces of sixteen keys' rows and of a block's values
     static constexpr int AB = F32 ? 1 : 2, BK = 16 * AB, KC = F32 ? 4 : 2, VC = 4;
     uint4 K0[AB][KC], K1[AB][KC], V0[VC], V1[VC];
+    // The waves' (max, sum) have a place for each of the two attentions: a wave without keys of the sequence waits for nothing and may leave
+    // the next layer's while others still read those of this layer's cross-attention.
+    static constexpr int kTops = kMl + (CAUSAL ? 0 : kMlBytes);
 
     __device__ __forceinline__ void load(const Walk& c, uint4 (&Kr)[AB][KC], uint4 (&Vr)[VC], int blk) const {
         const int key0 = min(blk, nblk - 1) * BK;
@@ -209,7 +212,7 @@ struct Attend {
                 if (blk + 3 * kPassWaves < nblk) load(c, K1, V1, blk + 3 * kPassWaves);
             }
         }
-        float* const cm = (float*)(c.lds + kMl);  // the waves' maxima and sums
+        float* const cm = (float*)(c.lds + kTops);  // the waves' maxima and sums
         c.red = kRedBytes - c.red;
         float* const co = (float*)(c.lds + kRed + c.red) + c.lane;
         const float sum = wave_sum(l_run);
@@ -459,7 +462,7 @@ struct Attend {
                 }
             }
         }
-        float* cm = (float*)(c.lds + kMl);
+        float* cm = (float*)(c.lds + kTops);
         float* cl = cm + kPassWaves * 16;
         if (c.g == 0) {
             cm[c.wave * 16 + c.tok] = m_run;

@@ -29,10 +29,10 @@ __device__ __forceinline__ void st8(Rsrc r, int off, unsigned a, unsigned b) {
 
 constexpr unsigned kNotThere = 0xFFFFFFFFu;  // (two NaNs of a kind no conversion gives, as bf16 parts; one as a sum)
 
-// LDS: sums of the waves (up to six tiles each; attention joins its waves there too), their (max, sum), the head's query, the
+// LDS: sums of the waves (up to six tiles each; attention joins its waves there too), their (max, sum) of either attention, the head's query, the
 // waves' sums of squares (twice, like the sums), their weights of one row's keys, the head's relative-position biases
 constexpr int kRedBytes = kPassWaves * 6 * 1024;  // twice: a stage's sums are read while the next one's are written
-constexpr int kRed = 0, kMl = 2 * kRedBytes, kQ = kMl + 2 * kPassWaves * 16 * 4, kQLd = 68, kSq = kQ + 16 * kQLd * 4, kSqBytes = kPassWaves * 16 * 4, kP = kSq + 2 * kSqBytes, kRel = kP + kPassWaves * 256;
+constexpr int kRed = 0, kMl = 2 * kRedBytes, kMlBytes = 2 * kPassWaves * 16 * 4, kQ = kMl + 2 * kMlBytes, kQLd = 68, kSq = kQ + 16 * kQLd * 4, kSqBytes = kPassWaves * 16 * 4, kP = kSq + 2 * kSqBytes, kRel = kP + kPassWaves * 256;
 
 // Rows there is room for in the hand-over memory (the layout's): known to the kernel, or (0) not.
 template <int ROOM>

@@ -105,6 +105,32 @@ def test_the_longest_row_of_relative_biases(dtype, monkeypatch):
         assert float(np.abs(got[form] - got["kernels"]).max()) <= 2 * parity.logit_tol(cfg), form
 
 
+def test_waves_without_keys_of_the_sequence(monkeypatch):
+    """Every wave has keys of the source (530 tokens), one or two have keys of the sequence, over ten layers: a wave without any is through
+    with the next layer's self-attention while others join this layer's cross-attention.  Against the separate kernels, as above."""
+    cfg = bi.toy_pair(dtype=bi.DT_BF16, d=256, heads=4, d_head=64, d_ff=512, truncate=True, n_small=10, n_large=10, n_src=530, max_new=40)
+    R = Rig(cfg)
+    got = {}
+    for form, env in FORMS.items():
+        with monkeypatch.context() as m:
+            for k, v in env.items():
+                m.setenv(k, v)
+            st = R.state(cfg.max_new, 15)
+        st.encode(R.src)
+        st.debug_enable_logits(True)
+        logits = []
+        for rows in (1, 2, 3, 8, 16):
+            st.seq_truncate(R.n0)
+            st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+            logits += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+            st.small_step(0.0)
+            logits.append(st.debug_logits(pkg.SMALL, 0))
+        assert st.pass_routes()["gave_up"] == 0
+        got[form] = np.stack(logits)
+    for form in ("die", "chip"):
+        assert float(np.abs(got[form] - got["kernels"]).max()) <= 2 * parity.logit_tol(cfg), form
+
+
 @pytest.mark.parametrize("n_src", [1, 32, 33, 257, 530])
 def test_source_lengths_around_the_key_blocks(n_src):
     _check(n_src=n_src)
