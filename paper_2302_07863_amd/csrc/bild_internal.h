@@ -251,6 +251,9 @@ hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st);
 constexpr int kWideRows = 8, kWideHead = 128;  // most rows; features of a head
 constexpr int kWideSplits = 8;                 // most key ranges of a head
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // as pass_groups, of pass_wide.hip
+// who does what in a pass that ends with `keys` keys (wide_parts): {tiles of q, k, v a workgroup, its first workgroup, the same of the FFN's
+// input, the heads' first workgroup, ranges, apart}; false: not a shape it is made for
+bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int out[7]);
 hipError_t launch_wide(const PassArgs& a, hipStream_t st);
 
 struct EmbedArgs {

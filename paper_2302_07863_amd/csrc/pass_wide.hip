@@ -254,6 +254,7 @@ struct WideCut {
     using Out = Stream<KD, 1, 8, false>;
     using In = Stream<KD, FT, FC, true>;
     using Ffn = Stream<KF, 1, 8, false>;
+    static constexpr bool EARLY = In::NC <= 2;  // the FFN's first weights all fit the registers
 };
 // (pieces of the 4096-wide cut: 8 and 6 tiles a request of q, k, v and the FFN 669 and 673 us, 12 and 12 663, 15 and 18 the same)
 using Cut2048 = WideCut<3, 4, 8, 24, 4, 4>;
@@ -262,19 +263,43 @@ using Cut4096 = WideCut<3, 6, 16, 44, 4, 2>;
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Key ranges of a head: 256 keys each, a power of two, as long as there are workgroups.
-__device__ inline int wide_splits(int nkeys, int heads, int groups) {
+__host__ __device__ inline int wide_splits(int nkeys, int heads, int groups) {
     int s = 1;
     while (s < kWideSplits && s * 256 < nkeys && heads * s * 2 <= groups) s *= 2;
     return s;
 }
 
-// Workgroups [0, d / 16) own sixteen features of the residual stream each; the last heads x ranges are the heads'.
+// Who does what: the first workgroups with q, k, v (qt tiles each), the FFN's input and the heads (head0, each in `ranges`).
+// Apart, up to 1280 keys: the heads are the first workgroups', in ranges that half of those with features
+// of the residual stream hold, q, k, v and the FFN's input the last ones', so that these weights are asked for while the heads work and
+// nobody's heads wait behind them.  More keys take more workgroups than that: the heads are the last ones', the rest begins
+// with the first, q, k, v in two tiles a workgroup where that many workgroups there are (three above 2304 keys, where workgroups with heads had
+// better have no part of them).  2048-wide, 16 layers, one row, us, two tiles / three / apart: 200 keys 451, 471, 412; 700 468, 471, 420; 1000 471, 472, 438;
+// 1100 457, 485, 442; 1250 461, 487, 454; 1350 464, 489, 464; 2000 483, 492, 529; 4000 593, 548, 672.  (The two tiles ask for
+// the second one twice: eight rows 531 at 1400 keys, 524 with registers for two only.)
+struct WideParts {
+    bool apart;
+    int qt, q, i, head0, ranges;
+};
+template <class Cut>
+__host__ __device__ inline WideParts wide_parts(int keys, int d, int heads, int tq, int tf, int groups) {
+    WideParts p;
+    p.apart = Cut::EARLY && keys <= 1280;
+    p.qt = Cut::EARLY && !p.apart && keys <= 2304 && (Cut::QT - 1) * groups >= tq ? Cut::QT - 1 : Cut::QT;
+    p.q = p.apart ? groups - ceil_div(tq, p.qt) : 0;
+    p.i = p.apart ? groups - ceil_div(tf, Cut::FT) : 0;
+    p.ranges = wide_splits(keys, heads, p.apart ? d >> 5 : groups);
+    p.head0 = p.apart ? 0 : groups - heads * p.ranges;
+    return p;
+}
+
+// Workgroups [0, d / 16) own sixteen features of the residual stream each; the rest: wide_parts.
 template <bool GATED, class Cut, int ROOM>
 __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     using Way = WideWalk<ROOM>;
     constexpr int QT = Cut::QT, FT = Cut::FT, DH = kWideHead;
-    constexpr bool EARLY = Cut::In::NC <= 2;  // the FFN's first weights all fit the registers
+    constexpr bool EARLY = Cut::EARLY;
     Way c;
     c.lds = smem;
     c.failed = a.sync + kPassSyncWords - 1;
@@ -288,21 +313,12 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
     const int len = *a.len_ptr;
     auto tq = [&] { return 3 * (I >> 4); };
     auto tf = [&] { return GATED ? F >> 3 : F >> 4; };
-    // Who does what.  Apart, up to 1280 keys: the heads are the first workgroups', in ranges that half of those with features
-    // of the residual stream hold, q, k, v and the FFN's input the last ones', so that these weights are asked for while the heads work and
-    // nobody's heads wait behind them.  More keys take more workgroups than that: the heads are the last ones', the rest begins
-    // with the first, q, k, v in two tiles a workgroup (three above 2304 keys, where workgroups with heads had better have no part of
-    // them).  2048-wide, 16 layers, one row, us, two tiles / three / apart: 200 keys 451, 471, 412; 700 468, 471, 420; 1000 471, 472, 438;
-    // 1100 457, 485, 442; 1250 461, 487, 454; 1350 464, 489, 464; 2000 483, 492, 529; 4000 593, 548, 672.  (The two tiles ask for
-    // the second one twice: eight rows 531 at 1400 keys, 524 with registers for two only.)
-    const int keys = len + T;
-    const bool apart = EARLY && keys <= 1280;
-    const int qt = EARLY && !apart && keys <= 2304 ? QT - 1 : QT;
-    const int uq = c.wg - (apart ? a.groups - ceil_div(tq(), QT) : 0), uf = c.wg - (apart ? a.groups - ceil_div(tf(), FT) : 0);
-    const int q0 = uq * qt, q1 = min(q0 + qt, tq()), i0 = uf * FT;  // tiles of the projections
+    const WideParts who = wide_parts<Cut>(len + T, d, a.heads, tq(), tf(), a.groups);
+    const int uq = c.wg - who.q, uf = c.wg - who.i;
+    const int q0 = uq * who.qt, q1 = min(q0 + who.qt, tq()), i0 = uf * FT;  // tiles of the projections
     const bool owner = c.wg < d >> 4, qkv = uq >= 0 && q0 < tq(), ffn = uf >= 0 && i0 < tf();
     const bool mine = owner && c.wave == 0;
-    const int S = wide_splits(keys, a.heads, apart ? d >> 5 : a.groups), place = apart ? c.wg : c.wg - (a.groups - a.heads * S);
+    const int S = who.ranges, place = c.wg - who.head0;
     const bool att = place >= 0 && place < a.heads * S;
     const int h = att ? place / S : 0, split = att ? place % S : 0;
 
@@ -713,6 +729,15 @@ static bool wide_fits(int d, int heads, int F, bool gated, int cus) {
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     if (d_head != kWideHead || d <= 1024 || d % 256 != 0 || F % 32 != 0) return 0;
     return wide_fits<Cut2048>(d, heads, F, gated, cus) || wide_fits<Cut4096>(d, heads, F, gated, cus) ? cus : 0;
+}
+
+bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int out[7]) {
+    if (!wide_groups(d, heads, kWideHead, F, gated, cus)) return false;
+    const int tq = 3 * heads * kWideHead / 16, tf = gated ? F / 8 : F / 16;
+    const bool small = wide_fits<Cut2048>(d, heads, F, gated, cus);
+    const WideParts p = small ? wide_parts<Cut2048>(keys, d, heads, tq, tf, cus) : wide_parts<Cut4096>(keys, d, heads, tq, tf, cus);
+    out[0] = p.qt; out[1] = p.q; out[2] = small ? Cut2048::FT : Cut4096::FT; out[3] = p.i; out[4] = p.head0; out[5] = p.ranges; out[6] = p.apart;
+    return true;
 }
 
 hipError_t wide_init() {

@@ -155,3 +155,24 @@ def test_caches_past_32_bit_offsets_stay_with_64_bit_addresses(heads, d_head):
     for positions in (last + 1, last + 33, 2 * (last + 1), 4 * (last + 1)):
         for nkeys in (64, positions):
             assert b.cache_rule(heads, d_head, positions, nkeys) == dict(one_kernel=0, splits=0, waves=0), positions
+
+
+@pytest.mark.parametrize("units", [64, 96, 128, 144, 160, 191, 192, 256, 304])
+def test_every_tile_of_a_wide_pass_has_a_workgroup(units):
+    """Passes of wide models in one kernel, for whole and partitioned cards: where such a pass is taken at all, the workgroups from the
+    first with a part of q, k, v (the FFN's input, a head) on hold all of it, at every length around the lines of the rule."""
+    taken = 0
+    for d, heads in ((1280, 10), (1536, 12), (1536, 6), (2048, 16), (2048, 8), (2560, 20), (3072, 24), (4096, 32)):
+        for d_ff, gated in ((96, False), (d, True), (4096, True), (5632, True), (4 * d, False), (11008, True)):
+            for keys in (1, 256, 257, 1024, 1280, 1281, 2000, 2048, 2304, 2305, 8192):
+                s = b.wide_split(d, heads, d_ff, gated, units, keys)
+                if not s["qkv_tiles"]:
+                    assert not any(s.values())
+                    continue
+                taken += 1
+                case = (d, heads, d_ff, gated, keys, s)
+                assert s["qkv_first"] >= 0 and (units - s["qkv_first"]) * s["qkv_tiles"] >= 3 * heads * 128 // 16, case
+                assert s["ffn_first"] >= 0 and (units - s["ffn_first"]) * s["ffn_tiles"] >= (d_ff // 8 if gated else d_ff // 16), case
+                assert s["heads_first"] >= 0 and s["heads_first"] + heads * s["ranges"] <= units and s["ranges"] in (1, 2, 4, 8), case
+                assert d // 16 <= units
+    assert taken > 0 or units < 96
