@@ -1386,6 +1386,12 @@ static bool takes_thin(const bild_state* s, int w, int T) {
 // Counts the passes of model w with room for T rows.
 static unsigned* pass_turn(const bild_state* s, int w, int T) { return s->pass_sync + kPassSyncWords + w * kPassRooms + pass_room_index(T); }
 
+static bool two_tiles(const bild_state* s, int w, int T) {
+    const ModelState& M = s->ms[w];
+    const bild_model_config& c = M.m->cfg;
+    return M.pass_wide && wide_two(c.d_model, c.n_heads, c.d_ff, M.m->gated(), M.pass_groups, s->len[w] + T);
+}
+
 // One decoder pass of model w over rows y[len .. len+T): embed, layers, and (lm_rows > 0)
 // the LM head over the last lm_rows rows followed by the policy `mode`; lm_rows == 0
 // only advances the cache (catch-up / prefill).
@@ -1431,6 +1437,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         s->stage_count += 1;
         p.groups = die ? M.pass_die_groups : M.pass_groups;
         p.wide = M.pass_wide;
+        p.two = two_tiles(s, w, T);
         p.rope = M.rope;
         HIPC(M.pass_wide ? launch_wide(p, s->stream) : launch_pass(p, die ? s->cus : p.groups, s->stream));
     } else if (takes_thin(s, w, T)) {
@@ -1616,7 +1623,7 @@ int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
         return rc;
     }
     const int source = one || s->pair->decoder_only ? 0 : key_bucket(s->n_src);
-    const std::array<int, 7> key = {w, T, lm_rows, mode, bucket, source, (s->debug_logits ? 1 : 0) | (s->gemm_only ? 2 : 0) | (s->top_p > 0.f ? 4 : 0) | (s->accept_mode ? 8 : 0) | (one ? 16 : 0)};
+    const std::array<int, 7> key = {w, T, lm_rows, mode, bucket, source, (s->debug_logits ? 1 : 0) | (s->gemm_only ? 2 : 0) | (s->top_p > 0.f ? 4 : 0) | (s->accept_mode ? 8 : 0) | (one ? 16 : 0) | (one && two_tiles(s, w, T) ? 32 : 0)};
     auto it = s->graphs.find(key);
     if (it == s->graphs.end()) {
         hipGraph_t g = nullptr;

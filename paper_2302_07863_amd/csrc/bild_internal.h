@@ -220,6 +220,7 @@ struct PassArgs {
     int die;                  // 1: on one die
     int f32;                  // 1: of an fp32 model (on one die)
     int wide;                 // 1: pass_wide.hip
+    int two;                  // (there) 1: two tiles of q, k, v a workgroup (wide_two)
     int d, heads, I, F, act, cross;
     // embedding of y[len ..]; emb null: the rows are x_in[len ..]
     const void* emb;
@@ -250,7 +251,9 @@ PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide);
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st);
 constexpr int kWideRows = 8, kWideHead = 128;  // most rows; features of a head
 constexpr int kWideSplits = 8;                 // most key ranges of a head
+constexpr int kWideApart = 1280;               // most keys with which heads and projections are different workgroups'
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // as pass_groups, of pass_wide.hip
+bool wide_two(int d, int heads, int F, bool gated, int cus, int keys);
 // who does what in a pass that ends with `keys` keys (wide_parts): {tiles of q, k, v a workgroup, its first workgroup, the same of the FFN's
 // input, the heads' first workgroup, ranges, apart}; false: not a shape it is made for
 bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int out[7]);

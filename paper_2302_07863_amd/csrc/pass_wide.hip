@@ -258,6 +258,7 @@ struct WideCut {
 };
 // (pieces of the 4096-wide cut: 8 and 6 tiles a request of q, k, v and the FFN 669 and 673 us, 12 and 12 663, 15 and 18 the same)
 using Cut2048 = WideCut<3, 4, 8, 24, 4, 4>;
+using Cut2048Two = WideCut<2, 4, 8, 24, 4, 4>;
 using Cut4096 = WideCut<3, 6, 16, 44, 4, 2>;
 
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -269,24 +270,20 @@ __host__ __device__ inline int wide_splits(int nkeys, int heads, int groups) {
     return s;
 }
 
-// Who does what: the first workgroups with q, k, v (qt tiles each), the FFN's input and the heads (head0, each in `ranges`).
+// Who does what: the first workgroups with q, k, v and the FFN's input, and the heads (head0, each in `ranges`).
 // Apart, up to 1280 keys: the heads are the first workgroups', in ranges that half of those with features
 // of the residual stream hold, q, k, v and the FFN's input the last ones', so that these weights are asked for while the heads work and
 // nobody's heads wait behind them.  More keys take more workgroups than that: the heads are the last ones', the rest begins
-// with the first, q, k, v in two tiles a workgroup where that many workgroups there are (three above 2304 keys, where workgroups with heads had
-// better have no part of them).  2048-wide, 16 layers, one row, us, two tiles / three / apart: 200 keys 451, 471, 412; 700 468, 471, 420; 1000 471, 472, 438;
-// 1100 457, 485, 442; 1250 461, 487, 454; 1350 464, 489, 464; 2000 483, 492, 529; 4000 593, 548, 672.  (The two tiles ask for
-// the second one twice: eight rows 531 at 1400 keys, 524 with registers for two only.)
+// with the first (q, k, v: see wide_two).
 struct WideParts {
     bool apart;
-    int qt, q, i, head0, ranges;
+    int q, i, head0, ranges;
 };
 template <class Cut>
 __host__ __device__ inline WideParts wide_parts(int keys, int d, int heads, int tq, int tf, int groups) {
     WideParts p;
-    p.apart = Cut::EARLY && keys <= 1280;
-    p.qt = Cut::EARLY && !p.apart && keys <= 2304 && (Cut::QT - 1) * groups >= tq ? Cut::QT - 1 : Cut::QT;
-    p.q = p.apart ? groups - ceil_div(tq, p.qt) : 0;
+    p.apart = Cut::EARLY && keys <= kWideApart;
+    p.q = p.apart ? groups - ceil_div(tq, Cut::QT) : 0;
     p.i = p.apart ? groups - ceil_div(tf, Cut::FT) : 0;
     p.ranges = wide_splits(keys, heads, p.apart ? d >> 5 : groups);
     p.head0 = p.apart ? 0 : groups - heads * p.ranges;
@@ -315,7 +312,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
     auto tf = [&] { return GATED ? F >> 3 : F >> 4; };
     const WideParts who = wide_parts<Cut>(len + T, d, a.heads, tq(), tf(), a.groups);
     const int uq = c.wg - who.q, uf = c.wg - who.i;
-    const int q0 = uq * who.qt, q1 = min(q0 + who.qt, tq()), i0 = uf * FT;  // tiles of the projections
+    const int q0 = uq * QT, q1 = min(q0 + QT, tq()), i0 = uf * FT;  // tiles of the projections
     const bool owner = c.wg < d >> 4, qkv = uq >= 0 && q0 < tq(), ffn = uf >= 0 && i0 < tf();
     const bool mine = owner && c.wave == 0;
     const int S = who.ranges, place = c.wg - who.head0;
@@ -731,19 +728,36 @@ int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     return wide_fits<Cut2048>(d, heads, F, gated, cus) || wide_fits<Cut4096>(d, heads, F, gated, cus) ? cus : 0;
 }
 
+// Two tiles of q, k, v a workgroup instead of three, where that many workgroups there are: models up to 2048 wide whose heads and
+// projections are not apart, up to 2304 keys or as long as workgroups with heads have no part of q, k, v.  2048-wide, 16 layers, one row, us, two tiles / three /
+// apart: 200 keys 451, 471, 412; 700 468, 471, 420; 1000 471, 472, 438; 1100 457, 485, 442; 1250 461, 487, 454; 1350 464, 489, 464; 2000 483, 492,
+// 529; 4000 593, 548, 672.  A kernel of its own, chosen by the host: in the one with registers for three, two tiles cost eight rows at 1400 and
+// 2000 keys 511, 525 (506, 520 here), with a body for either in one kernel the other lengths lose 1.2 %.  1280-wide, one row, at 1400, 2000, 2400 keys with
+// registers for three (three tiles above 2304) 313, 317, 341, here 305, 309, 327.
+bool wide_two(int d, int heads, int F, bool gated, int cus, int keys) {
+    const int tq = 3 * heads * kWideHead / 16, two = ceil_div(tq, Cut2048Two::QT);
+    return wide_fits<Cut2048Two>(d, heads, F, gated, cus) && keys > kWideApart && (keys <= 2304 || two <= cus - heads * wide_splits(keys, heads, cus));
+}
+
 bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int out[7]) {
     if (!wide_groups(d, heads, kWideHead, F, gated, cus)) return false;
     const int tq = 3 * heads * kWideHead / 16, tf = gated ? F / 8 : F / 16;
-    const bool small = wide_fits<Cut2048>(d, heads, F, gated, cus);
-    const WideParts p = small ? wide_parts<Cut2048>(keys, d, heads, tq, tf, cus) : wide_parts<Cut4096>(keys, d, heads, tq, tf, cus);
-    out[0] = p.qt; out[1] = p.q; out[2] = small ? Cut2048::FT : Cut4096::FT; out[3] = p.i; out[4] = p.head0; out[5] = p.ranges; out[6] = p.apart;
+    auto is = [&](auto cut) {
+        using Cut = decltype(cut);
+        const WideParts p = wide_parts<Cut>(keys, d, heads, tq, tf, cus);
+        out[0] = Cut::QT; out[1] = p.q; out[2] = Cut::FT; out[3] = p.i; out[4] = p.head0; out[5] = p.ranges; out[6] = p.apart;
+    };
+    if (wide_two(d, heads, F, gated, cus, keys)) is(Cut2048Two());
+    else if (wide_fits<Cut2048>(d, heads, F, gated, cus)) is(Cut2048());
+    else is(Cut4096());
     return true;
 }
 
 hipError_t wide_init() {
     static hipError_t done = [] {
-#define BILD_W(RV) (const void*)wide_kernel<false, Cut2048, RV>, (const void*)wide_kernel<true, Cut2048, RV>, (const void*)wide_kernel<false, Cut4096, RV>, (const void*)wide_kernel<true, Cut4096, RV>
-        const void* fns[] = {BILD_W(0), BILD_W(1), BILD_W(2)};
+#define BILD_W(CV, RV) (const void*)wide_kernel<false, CV, RV>, (const void*)wide_kernel<true, CV, RV>
+        const void* fns[] = {BILD_W(Cut2048, 0), BILD_W(Cut2048, 1), BILD_W(Cut2048, 2), BILD_W(Cut2048Two, 0), BILD_W(Cut2048Two, 1), BILD_W(Cut2048Two, 2),
+                             BILD_W(Cut4096, 0), BILD_W(Cut4096, 1), BILD_W(Cut4096, 2)};
 #undef BILD_W
         return raise_lds_limit(fns, 160 * 1024);
     }();
@@ -758,17 +772,23 @@ hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
         return hipErrorInvalidValue;
     const dim3 grid(a.groups), block(kPassThreads);
     const bool small = wide_fits<Cut2048>(a.d, a.heads, a.F, gated, a.groups);
+    if (a.two && !wide_fits<Cut2048Two>(a.d, a.heads, a.F, gated, a.groups)) return hipErrorInvalidValue;
+#define BILD_WC(CV, RV)                                                                                                \
+    do {                                                                                                               \
+        if (gated) hipLaunchKernelGGL((wide_kernel<true, CV, RV>), grid, block, kRel, st, a);                          \
+        else hipLaunchKernelGGL((wide_kernel<false, CV, RV>), grid, block, kRel, st, a);                               \
+    } while (0)
 #define BILD_W(RV)                                                                                                     \
     do {                                                                                                               \
-        if (small && gated) hipLaunchKernelGGL((wide_kernel<true, Cut2048, RV>), grid, block, kRel, st, a);            \
-        else if (small) hipLaunchKernelGGL((wide_kernel<false, Cut2048, RV>), grid, block, kRel, st, a);               \
-        else if (gated) hipLaunchKernelGGL((wide_kernel<true, Cut4096, RV>), grid, block, kRel, st, a);                \
-        else hipLaunchKernelGGL((wide_kernel<false, Cut4096, RV>), grid, block, kRel, st, a);                          \
+        if (a.two) BILD_WC(Cut2048Two, RV);                                                                            \
+        else if (small) BILD_WC(Cut2048, RV);                                                                          \
+        else BILD_WC(Cut4096, RV);                                                                                     \
     } while (0)
     if (a.room == 1) BILD_W(1);
     else if (a.room == 2) BILD_W(2);
     else BILD_W(0);
 #undef BILD_W
+#undef BILD_WC
     return hipGetLastError();
 }
 

@@ -176,3 +176,11 @@ def test_every_tile_of_a_wide_pass_has_a_workgroup(units):
                 assert s["heads_first"] >= 0 and s["heads_first"] + heads * s["ranges"] <= units and s["ranges"] in (1, 2, 4, 8), case
                 assert d // 16 <= units
     assert taken > 0 or units < 96
+
+
+def test_tiles_of_a_wide_pass_at_the_lines_of_the_rule():
+    """Three tiles of q, k, v a workgroup up to 1280 keys, then two where all of them have a workgroup, above 2304 keys only if none of those has a
+    head as well."""
+    tiles = lambda d, heads, units: [b.wide_split(d, heads, 5632, True, units, keys)["qkv_tiles"] for keys in (1280, 1281, 2304, 2305, 8192)]
+    assert tiles(2048, 16, 256) == [3, 2, 2, 3, 3] and tiles(2048, 16, 191) == [3, 3, 3, 3, 3]
+    assert tiles(1280, 10, 256) == [3, 2, 2, 2, 2] and tiles(4096, 32, 256) == [3] * 5 and tiles(2560, 20, 256) == [3] * 5
