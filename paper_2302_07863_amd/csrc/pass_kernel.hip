@@ -526,7 +526,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     // what comes of it two stages on.  By width and rows; measured optima (none / best, us, 12 layers): 256 wide 1, 8 rows 15, 20 turns (149 / 149,
     // 171 / 167), 512 20, 22 (154 / 152, 188 / 182), 768 23, 26 (167 / 163, 213 / 203), 1024 27, 31 (189 / 183, 244 / 230), gated 29, 34 (190 / 185, 248 /
     // 234); two turns more here than in those measurements, whose naps also read their length.  Two turns too short or four too long lose
-    // half of it.
+    // half of it.  Over the chip only: on one die, where a hand-over takes 0.3 us, 256-wide models of a narrow FFN lost by it (d_ff 256, 12 layers, one,
+    // two, four rows 126, 134, 134 us with, 116, 123, 123 without; gated, d_ff 128, 128, 139, 137 and 118, 125, 124; fp32, d_ff 512, 145, 176, 176 and 137, 174, 175).
     constexpr int RI = Walk::KNOWN <= 1 ? 0 : Walk::KNOWN == 2 ? 1 : Walk::KNOWN == 4 ? 2 : Walk::KNOWN == 8 ? 3 : 4;
     constexpr int OUT_A[] = {14, 16, 16, 18, 20}, OUT_B[] = {15, 14, 14, 14, 17}, QKV_A[] = {18, 22, 18, 20, 20}, QKV_B[] = {8, 5, 14, 14, 16};
     auto out_nap = [&] { return OUT_A[RI] + ((OUT_B[RI] * d + 512) >> 10) + (!GATED ? 0 : RI ? 4 : 2); };
@@ -546,7 +547,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     // model: the first ones' (mT5-large shape, 12 layers, 293 us apart and 286 together).
     constexpr bool LAST = !(GATED && RI == 4);
     const int uq = c.wg - (LAST ? base - nq() : 0), uf = c.wg - (LAST ? base - nf() : 0);
-    const bool owner = c.wg < no(), qkv = uq >= 0 && uq < nq(), ffn = uf >= 0 && uf < nf(), apart = LAST && no() + nf() <= base;
+    const bool owner = c.wg < no(), qkv = uq >= 0 && uq < nq(), ffn = uf >= 0 && uf < nf(), apart = CHIP && LAST && no() + nf() <= base;  // apart: who owns features has no part of the FFN's input
     uint4 Wq[KD * QT], Wo[KD * OT], Wi[KD * FT], Wf[KF * OT];
     float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);  // (owners, waves below OT) the residual stream of this lane's row, features n0 .. n0 + 3
