@@ -521,7 +521,9 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     // EARLY: input tiles of the FFN's output projection asked for before the self-attention's results are waited for, WQ: where the next
     // layer's first weights are asked for (see there).  Over the chip 0, 0: with 4 to 16 of 16 early T5-large 372 -> 371 .. 390 us.  On one
     // die, EARLY 0, 4, 8 and WQ 0, 1, 2: T5-small shape 87 (0, 0), 85 (0, 1), 84 (4, 1), 82.5 (4, 2), 85.5 (8, 2), mT5-small 152, 144, 143.5, 146, 146.
-    constexpr int EARLY = CHIP ? 0 : 4, WQ = CHIP ? 0 : GATED ? 1 : 2;
+    // fp32, whose weights are twice as large and whose rows travel whole: 0, 0 too (256 wide, d_ff 1024, 12 layers, 1, 2, 4, 11 rows 139.5, 182, 183, 188 with
+    // 4, 2 and 133, 175, 176, 181; gated, d_ff 512, 139, 174, 175, 180 with 4, 1 and 135, 171, 172, 176).
+    constexpr int EARLY = CHIP || Walk::F32 ? 0 : 4, WQ = CHIP || Walk::F32 ? 0 : GATED ? 1 : 2;
     // Naps of workgroups whose part in between is the others' (see the head of this file), in turns of 95 ns: from their own result to
     // what comes of it two stages on.  By width and rows; measured optima (none / best, us, 12 layers): 256 wide 1, 8 rows 15, 20 turns (149 / 149,
     // 171 / 167), 512 20, 22 (154 / 152, 188 / 182), 768 23, 26 (167 / 163, 213 / 203), 1024 27, 31 (189 / 183, 244 / 230), gated 29, 34 (190 / 185, 248 /
