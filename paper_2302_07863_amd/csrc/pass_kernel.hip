@@ -616,7 +616,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             char* kept = pinned(seg == 1 ? L->kc : L->vc);
             char* out = pinned(z + (seg == 0 ? a.at.q : seg == 1 ? a.at.k : a.at.v));
             f32x4 acc[QT];
-            if (apart && !owner) c.rest(qkv_nap());
+            if (apart && !owner) c.rest(l ? qkv_nap() : 0);  // (the first layer's come from the embedding)
             else c.template nap<250>();
             multiply<KD, QT, PACK, true>(c, acc, Wq, xs, d >> c.KS);
             leave<QT, true, RD>(c, acc);
