@@ -437,7 +437,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         const bool in_int = cache_in_int(s->cap_len, I, esz) && (!m->cfg.cross_attn || cache_in_int(s->cap_src, I, esz));
         if (s->one_kernel && in_int && m->cfg.pos != BILD_POS_ROPE) {
             const int die = s->one_die && s->cus == 256 ? pass_die_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), !bf16) : 0;
-            M.pass_groups = bf16 ? pass_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus) : die;
+            M.pass_groups = bf16 ? pass_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus, false) : die;
             if (M.pass_groups) {
                 M.pass_die_groups = die;
                 M.pass_die_rows = die == 0 ? 0 : !bf16 ? kPassRows : w == 0 ? 1 : kPassDieRows;
@@ -1435,7 +1435,9 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         p.sync = s->pass_sync;
         p.spins = s->pass_spins;
         s->stage_count += 1;
-        p.groups = die ? M.pass_die_groups : M.pass_groups;
+        const size_t head = lm_rows > 0 ? (size_t)c.vocab * d * m->esz() : 0;
+        p.last = !M.pass_wide && pass_last(d, c.d_ff, m->gated(), T, p.n_layers * m->layer_weight_bytes() + head);
+        p.groups = die ? M.pass_die_groups : p.last ? pass_groups(d, c.n_heads, c.d_head, c.d_ff, m->gated(), s->cus, true) : M.pass_groups;
         p.wide = M.pass_wide;
         p.two = two_tiles(s, w, T);
         p.rope = M.rope;

@@ -239,13 +239,15 @@ struct PassArgs {
     const unsigned* turn;     // passes so far, mod 3
     PassPlan at;
     int groups;               // workgroups that take part
+    int last;                 // 1: q, k, v and the FFN's input are the last ones' (pass_last; over the chip)
     int spins;                // polls (of about 0.7 us) after which a workgroup gives up
     unsigned* sync;           // [kPassSyncWords], zero before the pass; the policy kernel clears it
 };
 // Kernels that address a layer's keys or values by 32-bit byte offsets (pass_kernel.hip, pass_wide.hip, attn_split.hip) take caches whose
 // largest offset is a positive int: up to 262 143 positions of a bf16 model 4096 wide.  Longer ones go to attention.hip's 64-bit addresses.
 inline bool cache_in_int(size_t positions, size_t i_dim, size_t esz) { return positions * i_dim * esz < (size_t)1 << 31; }
-int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // workgroups, 0: not a shape it is made for
+int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus, bool last);  // workgroups, 0: not a shape it is made for
+bool pass_last(int d, int F, bool gated, int T, size_t bytes);
 int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32);
 PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide);
 hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st);

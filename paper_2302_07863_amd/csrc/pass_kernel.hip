@@ -543,13 +543,13 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     auto no = [&] { return ceil_div(nd(), OT); };
     auto nq = [&] { return ceil_div(tq(), QT); };
     auto nf = [&] { return ceil_div(tf(), FT); };       // workgroups
-    // This workgroup's part of q, k, v and of the FFN: the last workgroups', so that those that own features of the residual stream have
+    // This workgroup's part of q, k, v and of the FFN: the last workgroups' (pass_last), so that those that own features of the residual stream have
     // as few other weights to ask for as there are compute units for: an owner that also had its part of the FFN's input asked for 224
-    // KB in front of the cross-attention's results, which came 2.6 us after they were handed over (1.5 now).  Sixteen rows of a gated
-    // model: the first ones' (mT5-large shape, 12 layers, 293 us apart and 286 together).
-    constexpr bool LAST = !(GATED && RI == 4);
-    const int uq = c.wg - (LAST ? base - nq() : 0), uf = c.wg - (LAST ? base - nf() : 0);
-    const bool owner = c.wg < no(), qkv = uq >= 0 && uq < nq(), ffn = uf >= 0 && uf < nf(), apart = CHIP && LAST && no() + nf() <= base;  // apart: who owns features has no part of the FFN's input
+    // KB in front of the cross-attention's results, which came 2.6 us after they were handed over (1.5 now).
+    const bool back = !CHIP || a.last;
+    const int uq = c.wg - (back ? base - nq() : 0), uf = c.wg - (back ? base - nf() : 0);
+    const bool owner = c.wg < no(), qkv = uq >= 0 && uq < nq(), ffn = uf >= 0 && uf < nf();
+    const bool apart = CHIP && back && no() + nf() <= base;  // who owns features has no part of the FFN's input
     uint4 Wq[KD * QT], Wo[KD * OT], Wi[KD * FT], Wf[KF * OT];
     float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);  // (owners, waves below OT) the residual stream of this lane's row, features n0 .. n0 + 3
@@ -862,10 +862,24 @@ static bool cut_fits(int d, int I, int F, int inputs) {
 }
 
 // Sizes the kernel is made for: runs of inputs that fit the registers, the workgroups on the chip at once.  Wider models: pass_wide.hip.
-int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
+// last: see pass_last
+int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus, bool last) {
     if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<ChipCut>(d, heads * 64, F, 32)) return 0;
     const int g = cut_groups<ChipCut>(d, heads, F, gated), apart = d / 16 + ceil_div(gated ? F / 8 : F / 16, ChipCut::FT) + heads;
-    return apart <= cus ? std::max(g, apart) : g <= cus ? g : 0;
+    return last && apart <= cus ? std::max(g, apart) : g <= cus ? g : 0;
+}
+// Whether the FFN's input and q, k, v are the last workgroups' over the chip, apart from the owners of features, or the first ones'.  It pays where the
+// weights of a pass come from memory (`bytes` of them, which the 256 MiB of the last-level cache do not hold from pass to pass), one row always, more
+// rows where the FFN's output weights, which an owner asks for as well, are many.  us, 64 source tokens, first / last, 1, 2, 4, 8, 11 rows, 1024
+// wide, 16 heads: d_ff 4096, 8 layers (256 MiB) 118, 135, 142, 150, 177 / 120, 136, 144, 152, 181, 9 layers 139, 155, 163, 173, 206 / 133, 154, 162,
+// 171, 205, 24 layers 370, 406, 426, 449, 539 / 344, 389, 412, 431, 528; 24 layers of 3584 360, 399, 418, 442, 530 / 336, 386, 409, 430, 517, of 3072 349, 389,
+// 406, 428, 510 / 327, 383, 402, 423, 496 (512 tokens 356, 404, 419, 435, 515 / 346, 402, 421, 440, 511), of 2560 342, 382, 395, 415, 494 / 326, 381, 399, 419, 485 (512
+// tokens 423 / 436 for eight rows), of 2048 332, 371, 381, 400, 474 / 321, 379, 392, 415, 474; gated, 2816, 24 layers 360, 410, 423, 445, 526 / 342, 410, 428, 447, 529, 8 layers 122, 142, 147, 153,
+// 179 / 122, 142, 148, 157, 186.  768 wide, d_ff 3072, 12 layers (216 MiB) 157, 178, 187, 197, 230 / 158, 178, 186, 197, 231, 24 layers 319, 351, 369, 388, 456 / 303, 349, 362,
+// 381, 454.  Narrower models, held by the cache, are 0 to 2 % faster with the last ones, gated ones above eight rows 2 to 4 % slower.
+bool pass_last(int d, int F, bool gated, int T, size_t bytes) {
+    if (d < 768) return !(gated && T > 8);
+    return bytes > (size_t)270 << 20 && (T == 1 || F >= 3 * d);
 }
 // ... and of the form on one die: all of it on the 32 compute units of one.
 int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32) {

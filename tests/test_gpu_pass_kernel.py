@@ -238,6 +238,34 @@ def test_loads_of_several_tiles(shape, monkeypatch):
     assert worst <= 2 * parity.logit_tol(cfg)
 
 
+@pytest.mark.parametrize("shape", [dict(d=1024, heads=16, d_ff=4096), dict(d=1024, heads=16, d_ff=2816, act=bi.ACT_GATED_GELU), dict(d=768, heads=12, d_ff=2304, vocab=185000),
+                                   dict(d=1024, heads=4, d_ff=3072)])
+def test_who_does_what_with_weights_from_memory(shape, monkeypatch):
+    """A head of more than 270 MiB: q, k, v and the FFN's input are the last workgroups' for one row, and for more where the FFN is three times as wide as the
+    model; passes of both kinds follow each other in the same hand-over memory.  Against the separate kernels, as above."""
+    cfg = bi.toy_pair(**{**dict(dtype=bi.DT_BF16, d_head=64, n_src=20, max_new=16, vocab=140000, n_small=1, n_large=3, logit_scale=4.0, tie_shift=0), **shape})
+    R = Rig(cfg)
+    got = {}
+    for form in ("chip", "kernels"):
+        with monkeypatch.context() as m:
+            for k, v in FORMS[form].items():
+                m.setenv(k, v)
+            st = R.state(cfg.max_new, 15)
+        st.encode(R.src)
+        st.debug_enable_logits(True)
+        logits = []
+        for rows in (1, 2, 1, 5, 11, 1, 4, 16):
+            st.seq_truncate(R.n0)
+            before = st.pass_routes()
+            st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+            assert {k for k, v in st.pass_routes().items() if v > before[k]} == {form}, (form, rows)
+            logits += [st.debug_logits(pkg.LARGE, i)[::37] for i in range(rows)]
+        got[form] = np.stack(logits)
+    worst = float(np.abs(got["chip"] - got["kernels"]).max())
+    print(worst)
+    assert worst <= 2 * parity.logit_tol(cfg)
+
+
 F32 = dict(dtype=bi.DT_F32, truncate=False, d=256, heads=4, d_head=64, n_src=20)
 
 
