@@ -331,28 +331,40 @@ constexpr int kDrawMaxSlices = 256;  // vocabularies of up to 1 048 576 ids
 constexpr int kDrawMaxVocab = kDrawMaxSlices * kDrawThreads * kDrawMany;
 __host__ __device__ constexpr int draw_per(int vocab) { return vocab <= 65536 ? kDrawFew : kDrawMany; }
 __host__ __device__ constexpr int draw_slices(int vocab) { return (vocab + kDrawThreads * draw_per(vocab) - 1) / (kDrawThreads * draw_per(vocab)); }
+constexpr int kDrawStarts = kDrawBins + 4;  // words of a slice's table of starts
+// Bins of max - z: the first kDrawNear of equal width up to `knee`, the others of equal width behind it.
+constexpr int kDrawNear = 192;
+struct DrawMap {
+    float near, knee, far;
+};
 struct DrawWs {
     int row, pos;                     // row of the pass the token is drawn from, sequence position it will take
     float m;                          // that row's largest logit
     unsigned n;                       // ids listed
     int bin;                          // the threshold's bin
-    int pad;
+    DrawMap map;
     unsigned long long target;        // mass the nucleus has to reach
     unsigned long long above, upto;   // mass of the bins before the threshold's, and with it
     float u;                          // the uniform number of that position
+    int pad;
     StatPart merged[kMaxRows];        // merged LM-head statistics of the pass (one "partial" per row for the commit)
     unsigned long long slice[kDrawMaxSlices];  // a slice's mass in the bins before the threshold's
-    // behind it: [slices][kDrawBins] masses of the bins, and of the parts of the threshold's bin, then the ids in that bin as
-    // (logit, id), up to the vocabulary
+    uint2 range[kDrawMaxSlices];      // least and largest key of its listed ids (the least as its complement; 0, 0: none)
+    // behind it: [slices][kDrawBins] masses of the bins, then of the threshold's bin up to and with each of its parts; [slices][kDrawStarts]
+    // where the ids of a part lie in the list, and the end of the slice's; the ids in that bin as (logit, id), a slice's together and in
+    // the order of their parts, up to the vocabulary
     __host__ __device__ unsigned long long* bins(int s) { return (unsigned long long*)(this + 1) + (size_t)s * kDrawBins; }
     __host__ __device__ unsigned long long* parts(int nslices, int s) { return bins(nslices + s); }
     __device__ const unsigned long long* parts(int nslices, int s) const { return const_cast<DrawWs*>(this)->bins(nslices + s); }
-    __device__ uint2* list(int nslices) { return (uint2*)bins(2 * nslices); }
+    __device__ unsigned* starts(int nslices, int s) { return (unsigned*)bins(2 * nslices) + (size_t)s * kDrawStarts; }
+    __device__ const unsigned* starts(int nslices, int s) const { return const_cast<DrawWs*>(this)->starts(nslices, s); }
+    __device__ uint2* list(int nslices) { return (uint2*)starts(nslices, nslices); }
     __device__ const uint2* list(int nslices) const { return const_cast<DrawWs*>(this)->list(nslices); }
 };
 __host__ __device__ constexpr size_t draw_ws_bytes(int vocab) {
-    return sizeof(DrawWs) + (size_t)draw_slices(vocab) * kDrawBins * 16 + (size_t)vocab * 8;
+    return sizeof(DrawWs) + (size_t)draw_slices(vocab) * (kDrawBins * 16 + kDrawStarts * 4) + (size_t)(vocab + 1) / 2 * 16;
 }
+static_assert(sizeof(DrawWs) % 16 == 0, "the list is read in pairs");
 
 size_t gemm_lds_bytes(const GemmArgs& a, int dtype);
 

@@ -500,26 +500,40 @@ __global__ __launch_bounds__(1024) void finish_sample_kernel(const FinishArgs a)
 //                      comes from (every workgroup for itself; the first leaves row, position, max and the merged statistics),
 //                      then its slice's mass per bin of max - z
 //   draw_split_kernel  (slices)       the bin the threshold lies in, from all slices' bins; its slice's mass in the bins
-//                      before it and in the parts of this bin, and a list of the ids in it
-//   draw_pick_kernel   (1 workgroup)  the threshold key: where more ids are listed than there are threads the part of the bin first,
-//                      then a radix search of the bits in which the candidates' keys differ; floor(u * mass) -> slice -> id by two
-//                      integer prefix sums; then the policy and the commit of finish_body with that token
+//                      before it and in the parts of this bin, and a list of the ids in it in the order of their parts
+//   draw_pick_kernel   (1 workgroup)  the threshold key: where more ids are listed than there are threads those in the threshold's part
+//                      of the bin only, then a radix search of the bits in which the candidates' keys differ; floor(u * mass) -> slice ->
+//                      id by two integer prefix sums; then the policy and the commit of finish_body with that token
 //
 // Bound by launches and trips to memory.  A search by the four bytes of the key, a sweep over the row each, with a launch in front
 // to merge and one behind for the members' masses, were seven launches: 4.7 + 4 x 4.6 + 4.7 + 7.5 us at 32 128 ids, 4.8 + 4 x 6.4 + 4.7
-// + 7.9 at 250 112; these are 5.0 + 5.8 + 12.9 and 6.4 + 9.9 + 21.9 us, of which the policy's commit alone takes 4 (a request
-// of 40 drawn tokens, T5 shapes, 12.74 -> 12.22 ms).  Bins by distance from the maximum divide what has any mass evenly (2^-40 of
-// the largest is 27.7 below it), where a key's top byte is a sign and most of an exponent.  Workgroups of 1024 threads 6.4 + 6.1
-// + 15.9 us, slices of 4096 ids at 256 threads 7.0 + 7.6 + 13.2; a list of thousands of ids (a row with one likely id and a flat
-// rest) searched without the parts 35 us, and 81 with a third of the bins for what lies further than 6 below the maximum.
+// + 7.9 at 250 112; these are 4.9 + 4.9 + 6.8 and 6.0 + 8.3 + 9.5 us for a peaked row and one row of statistics, 8.5 + 8.3 + 11.6 for the eleven of a review
+// (every slice's workgroup merges all of them; the merge alone took 8.3 before), and 4.5 + 6.1 + 10.8 and 6.1 + 10.7 + 16.3 us where all logits lie within 1e-3 of each other.  A
+// step of one layer, wall clock, seven launches / three: 32 128 ids peaked 64.5 / 52.8 us, flat 65.9 / 57.8; 250 112 ids 95.7 / 86.0 and 102.6 / 94.6.
+// Bins by distance from the maximum divide what has any mass evenly, where a key's top byte is a sign and most of an exponent; they are as wide as
+// the row asks for (draw_map), because with one width for all rows a flat row lies in a few of them: a list of all ids, swept by one
+// workgroup, 288 and 1829 us a step.  What is left of that: many ids with two keys in one part, as a row of zeros of both signs (129 and 613 us).
+// Workgroups of 1024 threads lost 3 us, slices of 4096 ids at 256 threads 2.
 // =====================================================================================
 typedef unsigned long long u64;
 
 __device__ __forceinline__ u64 mass_units(float z, float m) { return (u64)(expf(z - m) * 1099511627776.f); }  // 2^40
 
+// How a row's bins lie: the near ones up to twice ln(vocab / sum of exp(z - max)), which the mean distance of the row's mass from its
+// maximum never exceeds, the far ones up to where there is no mass.
+__device__ __forceinline__ DrawMap draw_map(float sum, int vocab) {
+    DrawMap w;
+    w.knee = fminf(fmaxf(1.3862944f * __builtin_amdgcn_logf((float)vocab * __builtin_amdgcn_rcpf(sum)), 0x1p-20f), 28.f);  // (2^-40 of the largest mass is 27.7 below it)
+    w.near = (float)kDrawNear * __builtin_amdgcn_rcpf(w.knee);
+    w.far = (float)(kDrawBins - kDrawNear) * __builtin_amdgcn_rcpf(fmaxf(28.f - w.knee, 1.f));
+    return w;
+}
 // Place of an id among the bins: not decreasing where z falls (rounding keeps the order), so that an id in an earlier bin, or an
 // earlier part of the same bin, has a larger key.  Ids without mass may be in any bin (NaN: the first).
-__device__ __forceinline__ float draw_place(float z, float m) { return fmaxf((m - z) * (kDrawBins / 28.f), 0.f); }
+__device__ __forceinline__ float draw_place(float z, float m, const DrawMap& w) {
+    const float d = fmaxf(m - z, 0.f);
+    return __builtin_fmaf(fmaxf(d - w.knee, 0.f), w.far, fminf(d * w.near, (float)kDrawNear));  // (the same in every kernel)
+}
 __device__ __forceinline__ int draw_bin(float place) { return (int)fminf(place, (float)(kDrawBins - 1)); }
 __device__ __forceinline__ int draw_part(float place, int bin) { return draw_bin((place - (float)bin) * (float)kDrawBins); }
 
@@ -531,13 +545,30 @@ __device__ __forceinline__ u64 dpp_add(u64 v) {
     const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, ROWS, 0xF, false);
     return v + ((u64)hi << 32 | lo);
 }
-__device__ __forceinline__ u64 wave_prefix(u64 v) {
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_add(unsigned v) {
+    return v + (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <class T>
+__device__ __forceinline__ T wave_prefix(T v) {
     v = dpp_add<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8
     v = dpp_add<0x112, 0xF>(v);
     v = dpp_add<0x114, 0xF>(v);
     v = dpp_add<0x118, 0xF>(v);
     v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 to rows 1 and 3
     return dpp_add<0x143, 0xC>(v);  // row_bcast:31 to rows 2 and 3
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_umax(uint32_t v) {
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ uint32_t wave_umax(uint32_t v) {  // (as wave_prefix: the last lane has it)
+    v = dpp_umax<0x111, 0xF>(v);
+    v = dpp_umax<0x112, 0xF>(v);
+    v = dpp_umax<0x114, 0xF>(v);
+    v = dpp_umax<0x118, 0xF>(v);
+    v = dpp_umax<0x142, 0xA>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)dpp_umax<0x143, 0xC>(v), 63);
 }
 __device__ __forceinline__ u64 prefix_sum(u64 v, u64* buf, u64& all) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -589,11 +620,12 @@ __global__ __launch_bounds__(kDrawThreads) void draw_bins_kernel(const FinishArg
         if (row != n) load_slice(z, a, row, first);
     }
     const float m = rm[row];
+    const DrawMap map = draw_map(rsum[row], a.vocab);
 #pragma unroll
     for (int k = 0; k < PER; ++k)
         if (first + k * kDrawThreads < a.vocab) {
             const u64 e = mass_units(z[k], m);
-            if (e) atomicAdd(&bins[draw_bin(draw_place(z[k], m))], e);
+            if (e) atomicAdd(&bins[draw_bin(draw_place(z[k], m, map))], e);
         }
     __syncthreads();
     ws->bins(blockIdx.x)[tid] = bins[tid];
@@ -607,6 +639,7 @@ __global__ __launch_bounds__(kDrawThreads) void draw_bins_kernel(const FinishArg
             ws->row = row;
             ws->pos = pos;
             ws->m = m;
+            ws->map = map;
             ws->n = 0u;
         }
     }
@@ -614,13 +647,15 @@ __global__ __launch_bounds__(kDrawThreads) void draw_bins_kernel(const FinishArg
 
 template <int PER>
 __global__ __launch_bounds__(kDrawThreads) void draw_split_kernel(const FinishArgs a) {
-    __shared__ u64 parts[kDrawBins], buf[kDrawThreads / 64], buf2[kDrawThreads / 64], found[2];
-    __shared__ unsigned listed, base;
+    __shared__ u64 parts[kDrawBins], buf[3][kDrawThreads / 64], found[2];
+    __shared__ unsigned count[kDrawBins], base;
+    __shared__ uint4 range[kDrawThreads / 64];
     __shared__ int at_bin;
-    const int tid = threadIdx.x, lane = tid & 63, nslices = (int)gridDim.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nslices = (int)gridDim.x;
     DrawWs* ws = a.dws;
     const int first = (int)blockIdx.x * (PER * kDrawThreads) + tid;
     const float m = ws->m;
+    const DrawMap map = ws->map;
     const int pos = ws->pos;
     float z[PER];
     load_slice(z, a, ws->row, first);
@@ -634,11 +669,9 @@ __global__ __launch_bounds__(kDrawThreads) void draw_split_kernel(const FinishAr
         for (int k = 0; k < 8; ++k) mine += s + k < nslices ? v[k] : 0ull;
     }
     parts[tid] = 0ull;
-    if (tid == 0) {
-        listed = 0u;
-        at_bin = kDrawBins;  // (no mass, or a target above all of it: every id is a member)
-    }
-    const u64 upto = prefix_sum(mine, buf, total);
+    count[tid] = 0u;
+    if (tid == 0) at_bin = kDrawBins;  // (no mass, or a target above all of it: every id is a member)
+    const u64 upto = prefix_sum(mine, buf[0], total);
     const u64 target = (u64)ceil((double)a.top_p * (double)total);
     if (upto >= target && upto - mine < target) {  // one thread at most
         at_bin = tid;
@@ -647,34 +680,63 @@ __global__ __launch_bounds__(kDrawThreads) void draw_split_kernel(const FinishAr
     }
     __syncthreads();
     const int b = at_bin;
-    u64 mass = 0, in[PER];  // (lanes with an id in the bin)
-    unsigned many = 0, from = 0;
+    u64 mass = 0;
+    int part[PER];       // of the id if it lies in the bin, else -1
+    unsigned rank[PER];  // among the slice's ids in that part
+    uint32_t least = 0u, largest = 0u;  // key of this thread's (the least: its complement)
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        bool here = false;
+        part[k] = -1;
         if (first + k * kDrawThreads < a.vocab) {
-            const float place = draw_place(z[k], m);
+            const float place = draw_place(z[k], m, map);
             const int bin = draw_bin(place);
             if (bin <= b) {
                 const u64 e = mass_units(z[k], m);
-                here = bin == b && e != 0ull;
                 mass += bin < b ? e : 0ull;
-                if (here) atomicAdd(&parts[draw_part(place, b)], e);
+                if (bin == b && e != 0ull) {
+                    part[k] = draw_part(place, b);
+                    atomicAdd(&parts[part[k]], e);
+                    rank[k] = atomicAdd(&count[part[k]], 1u);
+                    least = max(least, ~float_key(z[k]));
+                    largest = max(largest, float_key(z[k]));
+                }
             }
         }
-        in[k] = __builtin_amdgcn_ballot_w64(here);
-        many += (unsigned)__builtin_popcountll(in[k]);
     }
-    if (many != 0u) {  // (uniform over the wavefront)
-        if (lane == 0) from = atomicAdd(&listed, many);
-        from = __builtin_amdgcn_readfirstlane(from);
+    __syncthreads();  // (`count` and `parts` are complete)
+    const unsigned own = count[tid];
+    u64 in_parts = wave_prefix(parts[tid]);
+    mass = wave_prefix(mass);
+    unsigned before = wave_prefix(own);
+    least = wave_umax(least);
+    largest = wave_umax(largest);
+    if (lane == 63) {
+        buf[1][wave] = in_parts;
+        buf[2][wave] = mass;
+        range[wave] = make_uint4(before, least, largest, 0u);
     }
-    u64 slice;
-    prefix_sum(mass, buf2, slice);  // (a barrier: `listed` and `parts` are complete)
-    ws->parts(nslices, blockIdx.x)[tid] = parts[tid];
+    before -= own;
+    __syncthreads();
+    u64 slice = 0;
+    unsigned listed = 0;
+#pragma unroll
+    for (int w = 0; w < kDrawThreads / 64; ++w) {
+        const uint4 r = range[w];
+        in_parts += w < wave ? buf[1][w] : 0ull;
+        before += w < wave ? r.x : 0u;
+        slice += buf[2][w];
+        listed += r.x;
+        least = max(least, r.y);
+        largest = max(largest, r.z);
+    }
+    count[tid] = before;
+    ws->parts(nslices, blockIdx.x)[tid] = in_parts;
+    unsigned* starts = ws->starts(nslices, blockIdx.x);
     if (tid == 0) {
         base = listed ? atomicAdd(&ws->n, listed) : 0u;
+        starts[kDrawBins] = base + listed;
         ws->slice[blockIdx.x] = slice;
+        ws->range[blockIdx.x] = make_uint2(least, largest);
         if (blockIdx.x == 0) {
             ws->u = u;
             ws->bin = b;
@@ -684,14 +746,12 @@ __global__ __launch_bounds__(kDrawThreads) void draw_split_kernel(const FinishAr
         }
     }
     __syncthreads();
-    if (many != 0u) {
-        uint2* list = ws->list(nslices) + base;
+    const unsigned at = base;
+    starts[tid] = at + before;
+    uint2* list = ws->list(nslices) + at;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            if (in[k] >> lane & 1ull) list[from + (unsigned)__builtin_popcountll(in[k] & ((1ull << lane) - 1ull))] = make_uint2(__float_as_uint(z[k]), (unsigned)(first + k * kDrawThreads));
-            from += (unsigned)__builtin_popcountll(in[k]);
-        }
-    }
+    for (int k = 0; k < PER; ++k)
+        if (part[k] >= 0) list[count[part[k]] + rank[k]] = make_uint2(__float_as_uint(z[k]), (unsigned)(first + k * kDrawThreads));
 }
 
 template <int PER>
@@ -700,14 +760,13 @@ __global__ __launch_bounds__(kDrawThreads) void draw_pick_kernel(const FinishArg
     __shared__ u64 bins[kDrawBins], slice[kDrawMaxSlices], buf[2][kDrawThreads / 64], found[2];
     constexpr int IDS = PER * kDrawThreads;
     __shared__ float zs[IDS + kDrawThreads];  // (a word between a thread's ids and the next one's)
-    __shared__ float low[kDrawThreads / 64], high[kDrawThreads / 64];
-    __shared__ uint2 cand[kDrawThreads];
+    __shared__ uint2 range[kDrawThreads / 64];
+    __shared__ uint2 cand[kDrawThreads];  // where the list has candidate tid, or (more of them than threads) those of slice tid
     __shared__ int at_bin, token;
-    __shared__ unsigned ncand;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // (requested ahead of the policy's words and the statistics: one trip for all of it)
     const DrawWs* ws = a.dws;
-    const int row = ws->row, n = (int)ws->n, bin = ws->bin;
+    const int row = ws->row, n = (int)ws->n;
     const float m = ws->m, u = ws->u;
     const u64 target = ws->target;
     u64 above = ws->above, upto = ws->upto;
@@ -716,24 +775,34 @@ __global__ __launch_bounds__(kDrawThreads) void draw_pick_kernel(const FinishArg
     const u64 of_slice = ws->slice[tid];
     finish_body<false>(a, lds, [&]() -> int {
         slice[tid] = tid < nslices ? of_slice : 0ull;
-        if (tid == 0) {
-            token = ((const int*)lds)[2 * kMaxRows + row];  // (argmax; stays only where no id has any mass)
-            ncand = 0u;
-        }
-        // (wavefronts with candidates as a whole, the last one's surplus lanes with `there` false)
-        int many = n, part = -1;  // candidates; part of the bin they are in
+        if (tid == 0) token = ((const int*)lds)[2 * kMaxRows + row];  // (argmax; stays only where no id has any mass)
+        int many = n;  // candidates
+        u64 in_part = 0;  // (more ids listed than there are threads) mass of slice tid in the candidates' part of the bin
+        uint32_t least = 0u, largest = 0u;  // candidates' keys (the least: its complement), or those of all ids in the bin
+        // (wavefronts with candidates as a whole, surplus lanes with `there` false)
         auto each = [&](auto&& f) {
             if (many <= kDrawThreads) {
                 if (wave * 64 < many) f(own, tid < many);
                 return;
             }
-            for (int i = tid; i - lane < n; i += kDrawThreads) {  // (so many ids so close together)
-                const uint2 e = list[min(i, n - 1)];
-                f(e, i < n && draw_part(draw_place(__uint_as_float(e.x), m), bin) == part);
+            for (int s = wave; s < nslices; s += kDrawThreads / 64) {  // (so many ids so close together)
+                const unsigned from = cand[s].x, to = cand[s].y;
+                for (unsigned i = from & ~1u; i < to; i += 64 * 2 * 8) {
+                    uint4 e[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) e[k] = *(const uint4*)(list + min(i + (k * 64 + lane) * 2, (unsigned)(a.vocab - 1) & ~1u));
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const unsigned j = i + (k * 64 + lane) * 2;
+                        if (i + k * 128 >= to) break;
+                        f(make_uint2(e[k].x, e[k].y), j >= from && j < to);
+                        f(make_uint2(e[k].z, e[k].w), j + 1 < to);
+                    }
+                }
             }
         };
-        if (n > kDrawThreads) {  // the part of the bin that the threshold lies in, and a thread for each id in it
-            u64 sum = 0, all;
+        if (n > kDrawThreads) {  // the part of the bin that the threshold lies in: its ids are the candidates
+            u64 sum = 0, all;    // of the parts up to and with part tid
             for (int s = 0; s < nslices; s += 8) {
                 u64 v[8];
 #pragma unroll
@@ -741,69 +810,62 @@ __global__ __launch_bounds__(kDrawThreads) void draw_pick_kernel(const FinishArg
 #pragma unroll
                 for (int k = 0; k < 8; ++k) sum += s + k < nslices ? v[k] : 0ull;
             }
-            const u64 s = above + prefix_sum(sum, buf[0], all);
-            if (s >= target && s - sum < target) {  // exactly one thread
-                at_bin = tid;
-                found[0] = s - sum;
-                found[1] = s;
+            bins[tid] = sum;
+            if (tid == 0) {
+                at_bin = 0;
+                found[0] = above;
+                found[1] = upto;
             }
             __syncthreads();
-            part = at_bin;
+            const u64 upto_part = above + sum, upto_last = above + (tid ? bins[tid - 1] : 0ull);
+            if (upto_part >= target && upto_last < target) {  // exactly one thread
+                at_bin = tid;
+                found[0] = upto_last;
+                found[1] = upto_part;
+            }
+            __syncthreads();
+            const int part = at_bin;
             above = found[0];
             upto = found[1];
-            for (int s0 = wave; s0 < nslices; s0 += 4 * (kDrawThreads / 64)) {  // members in the parts before it, to their slices
-                u64 v[4][4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v[k][j] = ws->parts(nslices, min(s0 + k * (kDrawThreads / 64), nslices - 1))[j * 64 + lane];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int sl = s0 + k * (kDrawThreads / 64);
-                    u64 t = 0;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) t += j * 64 + lane < part ? v[k][j] : 0ull;
-                    t = wave_prefix(t);
-                    if (lane == 63 && sl < nslices) slice[sl] += t;
-                }
+            unsigned from = 0u, to = 0u;
+            if (tid < nslices) {  // members in the parts before it, to their slices
+                const u64* p = ws->parts(nslices, tid);
+                const unsigned* st = ws->starts(nslices, tid);
+                const u64 before = part ? p[part - 1] : 0ull;
+                in_part = p[part] - before;
+                slice[tid] += before;
+                from = st[part];
+                to = st[part + 1];
             }
-            for (int i0 = tid; i0 < n; i0 += 8 * kDrawThreads) {
-                uint2 e[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) e[k] = list[min(i0 + k * kDrawThreads, n - 1)];
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (i0 + k * kDrawThreads < n && draw_part(draw_place(__uint_as_float(e[k].x), m), bin) == part) {
-                        const unsigned at = atomicAdd(&ncand, 1u);
-                        if (at < (unsigned)kDrawThreads) cand[at] = e[k];
-                    }
+            const unsigned first = (unsigned)prefix_sum(to - from, buf[0], all) - (to - from);
+            many = (int)all;
+            if (many <= kDrawThreads) {
+                for (unsigned i = from; i < to; ++i) cand[first + i - from].x = i;
+                __syncthreads();
+                own = list[min(cand[min(tid, max(many - 1, 0))].x, (unsigned)a.vocab - 1u)];
+            } else {
+                cand[tid] = make_uint2(from, to);
+                const uint2 r = ws->range[min(tid, nslices - 1)];
+                least = r.x;
+                largest = r.y;
+                __syncthreads();
             }
-            __syncthreads();
-            many = (int)ncand;
-            own = cand[min(tid, many - 1) & (kDrawThreads - 1)];
         }
         uint32_t K = 0u;
         if (n > 0) {
-            float zmin = INFINITY, zmax = -INFINITY;
-            each([&](const uint2& e, bool there) {
-                const float z = __uint_as_float(e.x);
-                zmin = there ? fminf(zmin, z) : zmin;
-                zmax = there ? fmaxf(zmax, z) : zmax;
-            });
-            zmin = -wave_max(-zmin);
-            zmax = wave_max(zmax);
-            if (lane == 0) {
-                low[wave] = zmin;
-                high[wave] = zmax;
+            if (many <= kDrawThreads && tid < many) {
+                least = ~float_key(__uint_as_float(own.x));
+                largest = float_key(__uint_as_float(own.x));
             }
+            least = wave_umax(least);
+            largest = wave_umax(largest);
+            if (lane == 0) range[wave] = make_uint2(least, largest);
             __syncthreads();
-#pragma unroll
-            for (int w = 0; w < kDrawThreads / 64; ++w) {
-                zmin = fminf(zmin, low[w]);
-                zmax = fmaxf(zmax, high[w]);
+            for (const uint2& r : range) {
+                least = max(least, r.x);
+                largest = max(largest, r.y);
             }
-            // (of two zeros either may have been taken, and they have keys of their own)
-            const uint32_t kmin = float_key(zmin == 0.f ? -0.f : zmin), kmax = float_key(zmax == 0.f ? 0.f : zmax);
+            const uint32_t kmin = ~least, kmax = largest;
             // The largest key whose members' mass reaches the target, as its distance from the least: eight bits at a time
             uint32_t D = 0u;
             const int bits = kmax == kmin ? 0 : 32 - __builtin_clz(kmax - kmin);
@@ -830,8 +892,9 @@ __global__ __launch_bounds__(kDrawThreads) void draw_pick_kernel(const FinishArg
                 upto = found[1];
             }
             K = kmin + D;
-            // the list's members to their slices (a slice's ids lie together: a sum over the wavefront for each slice in it)
-            each([&](const uint2& e, bool there) {
+            // the candidates that are members to their slices (a slice's ids lie together: a sum over the wavefront for each slice in it)
+            if (many > kDrawThreads && bits == 0) slice[tid] += in_part;  // (all of them are)
+            else each([&](const uint2& e, bool there) {
                 const float z = __uint_as_float(e.x);
                 const bool member = there && float_key(z) >= K;
                 const u64 units = member ? mass_units(z, m) : 0ull;

@@ -235,11 +235,12 @@ def test_sampling_vocabulary_beyond_the_register_cache(route, monkeypatch):
 
 
 @pytest.mark.parametrize("top_p", [0.05, TOP_P, 1.0])
-@pytest.mark.parametrize("vocab,logit_scale", [(50, 16.0), (1023, 24.0), (1024, 6.0), (1025, 1e-3), (12289, 1e-3), (65536, 24.0), (65537, 24.0), (69633, 24.0)])
+@pytest.mark.parametrize("vocab,logit_scale", [(50, 16.0), (1023, 24.0), (1024, 6.0), (1025, 1e-3), (12289, 1e-3), (17409, 1e-3), (32128, 1e-3), (32128, 4.0), (65536, 24.0),
+                                               (65537, 24.0), (69633, 24.0), (69633, 1e-3), (250112, 1e-3), (250112, 1.0)])
 def test_draw_at_the_edges_of_its_slices(vocab, logit_scale, top_p):
     """The draw that is spread over the chip against the oracle's on the library's own logits: a slice (1024 ids) less one, exactly,
-    and one id more; the last row with slices of 1024 ids and the first ones with 4096; rows so flat that all ids lie in the
-    threshold's bin, one and many more of them than the picking workgroup's threads keep in registers, and peaked ones.  The
+    and one id more; the last row with slices of 1024 ids and the first ones with 4096; rows so flat that more ids lie in the
+    threshold's bin than the picking workgroup has threads, in more slices of either size than it takes at a time, and peaked ones.  The
     margin: z - max is rounded to 2^-24 of at most 32, exp to 2^-23 and its value to 2^-40 of the largest, together 2.2e-6 of a
     mass, so that a ratio of sums moves by less than 1e-5."""
     from oracle import sampling
@@ -263,3 +264,54 @@ def test_draw_at_the_edges_of_its_slices(vocab, logit_scale, top_p):
             assert out[-1] == own or dm < 1e-5, ("large", ds + r, out[-1], own, dm)
             off, drawn, ds = off + (out[-1] != own), drawn + 1, len(st.sequence())
     assert drawn >= 20 and off <= 1, (drawn, off)
+
+
+@pytest.mark.parametrize("top_p", [0.05, TOP_P, 1.0])
+@pytest.mark.parametrize("vocab", [300, 32128, 69633])
+def test_draw_from_a_row_of_equal_logits(vocab, top_p):
+    """Every id has the same embedding, so every id has the same logit: all lie in one part of one bin, with one key, and all are members.  The
+    masses are equal powers of two and a uniform number has 24 bits, so u * mass is exact and the token is floor(u * vocab)."""
+    cfg = bi.toy_pair(vocab=vocab, tie_shift=0, max_new=24)
+    ws, wl = bi.make_pair_weights(cfg)
+    for w in (ws, wl):
+        w["emb"][:] = w["emb"][0]
+    st = pkg.State(parity.make_gpu_pair(cfg, ws, wl), cfg.n_src, 40, 4)
+    us, ul = _uniforms(cfg, 40)
+    st.set_sampling(top_p, us, ul)
+    st.debug_enable_logits(True)
+    st.encode(bi.make_source(cfg))
+    st.small_step(0.0)
+    assert np.ptp(st.debug_logits(pkg.SMALL, 0)) == 0.0
+    st.seq_truncate(1)
+    ds = 1
+    for _ in range(12):
+        pos = len(st.sequence())
+        tok, fallback, _ = st.small_step(0.0)
+        assert tok == int(np.float64(us[pos]) * vocab), ("small", pos, tok)
+        if fallback:
+            out, r, _ = st.large_verify(float("inf"))
+            assert out[-1] == int(np.float64(ul[ds + r]) * vocab), ("large", ds + r, out[-1])
+            ds = len(st.sequence())
+    assert ds > 1
+
+
+def test_a_draw_from_a_flat_row_takes_no_longer_than_from_a_peaked_one():
+    """Reviews of one row over 250 112 ids.  (Bins as wide for a flat row as for a peaked one: 20 times as long; as they are 1.1.)"""
+    import time
+    took = {}
+    for scale in (24.0, 1e-3):
+        R = Rig(bi.toy_pair(vocab=250112, logit_scale=scale, tie_shift=1021, max_new=24))
+        us, ul = _uniforms(R.cfg, 40)
+        st = R.state(30, 4)
+        st.set_sampling(TOP_P, us, ul)
+        st.encode(R.src)
+        times = []
+        for _ in range(60):
+            st.seq_truncate(R.n0)
+            t0 = time.perf_counter()
+            st.large_verify(float("inf"), draft=[])
+            times.append(time.perf_counter() - t0)
+        took[scale] = sorted(times)[10]
+        st.close()
+    print({k: round(v * 1e6, 1) for k, v in took.items()}, flush=True)
+    assert took[1e-3] < 3 * took[24.0], took
