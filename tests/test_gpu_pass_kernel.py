@@ -241,7 +241,7 @@ def test_loads_of_several_tiles(shape, monkeypatch):
 @pytest.mark.parametrize("shape", [dict(d=1024, heads=16, d_ff=4096), dict(d=1024, heads=16, d_ff=2816, act=bi.ACT_GATED_GELU), dict(d=768, heads=12, d_ff=2304, vocab=185000),
                                    dict(d=1024, heads=4, d_ff=3072)])
 def test_who_does_what_with_weights_from_memory(shape, monkeypatch):
-    """A head of more than 270 MiB: q, k, v and the FFN's input are the last workgroups' for one row, and for more where the FFN is three times as wide as the
+    """A head of more than 250 MiB: q, k, v and the FFN's input are the last workgroups' for one row, and for more where the FFN is three times as wide as the
     model; passes of both kinds follow each other in the same hand-over memory.  Against the separate kernels, as above."""
     cfg = bi.toy_pair(**{**dict(dtype=bi.DT_BF16, d_head=64, n_src=20, max_new=16, vocab=140000, n_small=1, n_large=3, logit_scale=4.0, tie_shift=0), **shape})
     R = Rig(cfg)
