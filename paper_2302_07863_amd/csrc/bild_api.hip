@@ -1568,25 +1568,28 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // its passes follow each other without the host's look at their outcome.
 //
 // Source.  One workgroup per head has all its keys to itself: up to 512 arrive ahead of their use, each further one costs a layer
-// 11 ns, where the separate kernels split them over more workgroups and stay as they are.  us per pass, separate kernels / one
-// kernel over the chip, at 512, 1024, 1536, 2048 tokens: T5-large shape one row 676 / 447, 675 / 575, 714 / 704, 713 / 834; two rows
-// 785 / 448, 796 / 578, 836 / 705, 836 / 835; eight 986 / 475, 1020 / 597, 1062 / 729, 1066 / 859; mT5-large shape one row 726 / 456,
-// 731 / 586, 772 / 715, 773 / 846; 768-wide, one row 348 / 212, 349 / 275, 369 / 339, 373 / 401; 256-wide, two rows 112 / 73, 114 / 93,
-// 121 / 114, 124 / 135.  Break-even lies at 1580 (T5-large, one row) to 1720 tokens (768-wide) and above 1700 for more rows: the lines
-// below are inside of it for every width, activation and row count measured (256 to 1024 wide).
-// On one die one row costs 148 / 96, 149 / 125, 159 / 156, 159 / 187 (T5-small shape; mT5-small 206 / 117, 206 / 159, 220 / 199,
-// 219 / 241; 256-wide 95 / 67, 96 / 87, 102 / 108, 104 / 128).
+// 7 to 11 ns, where the separate kernels split them over more workgroups and stay as they are.  us per pass with its head, separate kernels / one
+// kernel over the chip, 12 layers, at 512, 1024, 1408 tokens and (two rows and more) 1536: T5-large shape one row 348 / 184, 349 / 237, 369 / 279; two
+// rows 406 / 212, 412 / 279, 432 / 326, 433 / 343; eight 510 / 240, 530 / 307, 551 / 353, 551 / 371; eleven 596 / 281, 619 / 349, 637 / 395, 642 / 412;
+// mT5-large shape one row 365 / 185, 366 / 239, 390 / 281, two and eleven at 1536 471 / 350, 626 / 406; 768-wide one row 345 / 161, 349 / 209,
+// 370 / 246, two and eleven at 1536 398 / 320, 560 / 371.
+// On one die one row at 512, 1024, 1280 tokens costs 145 / 79, 146 / 101, 156 / 112 (T5-small shape; mT5-small 196 / 96, 197 / 125, 210 / 139; 256-wide,
+// 6 layers 135 / 71, 136 / 92, 145 / 103).
+// The lines come from passes that took 676 / 447 us at the T5-large shape (512 tokens, 24 layers) and met at 1580 (one row) to 1720
+// tokens; by the costs of a token above they would meet past 2000 now, which has not been measured.
 //
-// fp32, 256 wide, 4 layers, one row at 32, 256, 512, 1024 tokens 120 / 63, 126 / 73, 130 / 86, 130 / 115; 2 layers 68 / 41, 72 / 45, 72 / 53, 72 / 67.
+// fp32, 256 wide, 4 layers, at 32, 256, 512, 1024 tokens: one row 121 / 58, 127 / 67, 129 / 81, 130 / 109, four 146 / 72, 145 / 82, 147 / 96, 152 / 124, eleven
+// 154 / 74, 158 / 84, 164 / 98, 167 / 126.
 //
-// Sequence.  Its keys past the first 256 are not asked for ahead.  At 256, 512, 1024 positions: T5-large shape one row 708 / 478,
-// 713 / 522, 746 / 639; eight 1053 / 526, 1091 / 575, 1125 / 688; T5-small shape on one die 158 / 105, 160 / 113, 167 / 134; no shape and
-// row count loses before the 1024 that were measured.
+// Sequence.  Its keys past the first 256 are not asked for ahead.  At 256, 512, 1024 positions: T5-large shape, 12 layers, one row 348 / 185, 349 / 213,
+// 351 / 267, two 405 / 208, 408 / 240, 416 / 302, eight 501 / 236, 512 / 267, 530 / 330, eleven 575 / 281, 597 / 311, 621 / 377; T5-small shape on one die
+// 147 / 79, 147 / 91, 149 / 111: no shape and row count loses before the 1024 that were measured.
 //
-// Wide models (pass_wide.hip), rows 1, 2, 4, 8, separate kernels / one, 6 layers: 1280 wide at 40 positions 161, 193, 206, 230 / 123, 124,
-// 128, 137, at 8100 258, 271, 279, 298 / 227, 228, 234, 243; 2048 wide 228, 265, 285, 284 / 174, 176, 182, 196 and 338, 342, 357, 384 / 291, 295,
-// 303, 316; 3072 wide 374, 402, 445, 383 / 318, 309, 320, 341 and 546, 556, 598, 539 / 476, 479, 488, 509; 4096 wide 534, 575, 577, 580 /
-// 476, 467, 475, 495 and 743, 762, 762, 766 / 655, 660, 668, 686: never slower up to the 8192 positions that were measured.
+// Wide models (pass_wide.hip), rows 1, 2, 4, 8, separate kernels / one, 6 layers: 1280 wide at 40 positions 155, 182, 194, 209 / 98, 98, 111, 119,
+// at 2200 204, 231, 243, 266 / 133, 134, 148, 159, at 8100 256, 263, 275, 300 / 222, 223, 232, 241; 2048 wide 221, 255, 270, 275 / 156, 158, 166, 180,
+// at 2200 274, 314, 331, 327 / 200, 201, 213, 224, at 8100 330, 338, 355, 388 / 295, 297, 302, 312; 3072 wide 366, 384, 425, 374 / 284, 288, 316, 336
+// and at 8100 530, 548, 590, 543 / 451, 456, 484, 507; 4096 wide 525, 567, 569, 572 / 455, 458, 465, 480 and 719, 759, 760, 766 / 648, 651,
+// 660, 681: never slower up to the 8192 positions that were measured.
 static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
     if (s->ms[w].pass_wide) return s->one_kernel && T <= kWideRows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= 8192;

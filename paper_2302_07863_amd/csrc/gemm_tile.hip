@@ -227,6 +227,9 @@ __global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) vo
         // compute unit's queue.  Encode of 40, 77, 201, 512, 1531 tokens, T5 shapes, us: three or four ahead and a request past the end of
         // a wave's few steps for each 1018, 1125, 1373, 2028, 4562; without those 985, 1086, 1326, 1951, 4424 (998, 1109, 1336, 1992, 4482
         // before, that run); by size as here 975, 1065, 1326, 1959, 4416; 8, 6, 5, 3 by size 996, 1079, 1333, 2041, 4440 (that run).
+        // Six steps of 32 rows take 174 to 182 registers with two feature tiles and 142 to 150 with one (128 with four steps): two or three
+        // waves a SIMD fit instead of four.  These forms are launched with a workgroup per compute unit at most (tile_shape), one wave a
+        // SIMD, two beside the pair's other encoder.
         constexpr int LOADS = RT * 2 + FT, D = LOADS <= 6 ? 6 : LOADS == 8 ? 5 : LOADS <= 10 ? 4 : 2;
         uint4 W[D][FT], X[D][RT][2];
         auto request = [&](int d, int k) {

@@ -13,11 +13,13 @@
 //     has brought the data: between two dies 0.65 - 0.8 us from a store to its reader, 0.3 us on one die, where publish, count, poll
 //     and read back took 1.8 us over the chip.  A read misses its die's L2 only after somebody has written the line, so waiting
 //     workgroups stay off the fabric.  A line that is polled before it is written has to be taken away from eight L2s and
-//     fetched again, 0.3 us: where a stage's results cannot be there yet its readers sleep first (nap: q, k, v and the FFN's
-//     input projection 0.25 us, its output projection 0.4, behind a gated input projection 0.65.  T5-large shape, one row, without / with:
-//     q, k, v 413 / 413, input 413 / 412, output 418 / 406; two to eight rows gain 2, 5 to 10 and 10 us by the three.  mT5-large shape,
-//     eight rows, output 550 / 538; one row 480 / 479.  Twice as long loses 5 to 20 us everywhere, naps in front of the other stages
-//     gain nothing or 2 us.  As much was measured from 256 to 1024 wide with somewhat longer ones, 2 to 20 us of 180 to 290);
+//     fetched again, 0.3 us: where a stage's results cannot be there yet its readers sleep first.  A reader whose part in between is
+//     the others' (who owns features has none of the FFN's input, as in the T5-large shape and in one-row passes of the mT5-large one)
+//     sleeps until just before the results of two stages on (out_nap, qkv_nap: 1.7 to 3.9 us, see there).  One that has a part in between has a
+//     shorter nap: q, k, v and the FFN's input projection 0.25 us, its output projection 0.4, behind a gated input projection 0.65
+//     (measured while the T5-large shape's owners had a part of everything, one row, without / with: q, k, v 413 / 413, input 413 / 412, output
+//     418 / 406; two to eight rows gain 2, 5 to 10 and 10 us by the three; mT5-large shape, eight rows, output 550 / 538, one row 480 / 479.  Twice
+//     as long loses 5 to 20 us everywhere, naps in front of the other stages gain nothing or 2 us);
 //   - what belongs together lies together: a row's sums of squares beside its planes (a line that all producers write is taken
 //     away from its readers by each of them: 623 -> 714 us when the sums had two lines of their own), a head's query, keys
 //     and values of the new rows, which it needs before they can be read from the caches.  Sixteen features' high and low parts
@@ -37,7 +39,7 @@
 // fp32 models keep fp32 everywhere: activations travel as they are, sixteen rows in a matrix-core operand, attention in blocks of sixteen
 // keys (a block's 64 fp32 products take 0.85 us of a wave's SIMD for 32 keys); one row's projections run on the vector ALU (multiply).
 //
-// Per pass, us, as separate kernels, with counters (and flags on one die) and now, 512 source tokens: T5-small shape one row 147, 97, 96;
+// Per pass, us, as separate kernels, with counters (and flags on one die) and with results as flags, 512 source tokens: T5-small shape one row 147, 97, 96;
 // mT5-small shape 206, 121, 117; T5-large shape 1, 2, 4, 8, 11, 16 rows 676, 785, 853, 986, -, 1211 / 623, 631, 624, 638, 702, 713 / 447,
 // 448, 456, 475, 544, 552; mT5-large shape 1 and 8 rows 726, 1045 / 644, 666 / 443, 462.  fp32, 256 wide, 32 source tokens, as separate kernels
 // and now: 2 layers, one row 68, 40.5 (49.7 with the matrix cores for it, 43.5 with blocks of 32 keys); 4 layers, 1, 4, 11 rows 120, 145,
@@ -521,6 +523,9 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     // EARLY: input tiles of the FFN's output projection asked for before the self-attention's results are waited for, WQ: where the next
     // layer's first weights are asked for (see there).  Over the chip 0, 0: with 4 to 16 of 16 early T5-large 372 -> 371 .. 390 us.  On one
     // die, EARLY 0, 4, 8 and WQ 0, 1, 2: T5-small shape 87 (0, 0), 85 (0, 1), 84 (4, 1), 82.5 (4, 2), 85.5 (8, 2), mT5-small 152, 144, 143.5, 146, 146.
+    // WQ, 12 layers, one row, 1 / 2: without gate, 512 wide, d_ff 512, 1024, 1408, 2048 125.7, 134, 135.4, 139 / 125.3, 134, 134, 136, 256 wide, d_ff 512, 704,
+    // 1024 118.3, 119, 119.5 / 117, 118, 118.5 (four rows up to 1.5 % the other way, d_ff 2048 2 % this way); gated the two lie within 1 % of each other (512 wide,
+    // d_ff 512 127, 128, six heads and 1024 130.7, 131.8, eight heads and 1024 137.4, 136.6; 256 wide 121 either way).
     // fp32, whose weights are twice as large and whose rows travel whole: 0, 0 too (256 wide, d_ff 1024, 12 layers, 1, 2, 4, 11 rows 139.5, 182, 183, 188 with
     // 4, 2 and 133, 175, 176, 181; gated, d_ff 512, 139, 174, 175, 180 with 4, 1 and 135, 171, 172, 176).
     constexpr int EARLY = CHIP || Walk::F32 ? 0 : 4, WQ = CHIP || Walk::F32 ? 0 : GATED ? 1 : 2;
@@ -528,7 +533,8 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
     // what comes of it two stages on.  By width and rows; measured optima (none / best, us, 12 layers): 256 wide 1, 8 rows 15, 20 turns (149 / 149,
     // 171 / 167), 512 20, 22 (154 / 152, 188 / 182), 768 23, 26 (167 / 163, 213 / 203), 1024 27, 31 (189 / 183, 244 / 230), gated 29, 34 (190 / 185, 248 /
     // 234); two turns more here than in those measurements, whose naps also read their length.  Two turns too short or four too long lose
-    // half of it.  Over the chip only: on one die, where a hand-over takes 0.3 us, 256-wide models of a narrow FFN lost by it (d_ff 256, 12 layers, one,
+    // half of it where d_ff is 4 d.  d_ff is not part of it: with three or six turns less in front of q, k, v (256 to 1024 wide) passes of 1 to 8 rows take -0.4 to +0.7 %
+    // at d_ff of 1 to 2 d, -0.5 to +2.5 % at 2.75 d and -1.1 to +2.6 % at 4 d, eleven rows -1.3 to +0.2 %.  Over the chip only: on one die, where a hand-over takes 0.3 us, 256-wide models of a narrow FFN lost by it (d_ff 256, 12 layers, one,
     // two, four rows 126, 134, 134 us with, 116, 123, 123 without; gated, d_ff 128, 128, 139, 137 and 118, 125, 124; fp32, d_ff 512, 145, 176, 176 and 137, 174, 175).
     constexpr int RI = Walk::KNOWN <= 1 ? 0 : Walk::KNOWN == 2 ? 1 : Walk::KNOWN == 4 ? 2 : Walk::KNOWN == 8 ? 3 : 4;
     constexpr int OUT_A[] = {14, 16, 16, 18, 20}, OUT_B[] = {15, 14, 14, 14, 17}, QKV_A[] = {18, 22, 18, 20, 20}, QKV_B[] = {8, 5, 14, 14, 16};
@@ -862,7 +868,9 @@ static bool cut_fits(int d, int I, int F, int inputs) {
 }
 
 // Sizes the kernel is made for: runs of inputs that fit the registers, the workgroups on the chip at once.  Wider models: pass_wide.hip.
-// last: see pass_last
+// last: see pass_last.  Apart, a pass may take every compute unit there is (one row of the mT5-large shape, 64 + 176 + 16): another stream's
+// kernel on one of them then holds it up until that ends or the workgroups give up and it runs again as kernels.  The arrangement with the first ones
+// leaves 48 of 256 free at the mT5-large shape and takes 360 us instead of 342 for one row there; a state takes either only while it is alone inside a call.
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus, bool last) {
     if (d_head != 64 || d % 256 != 0 || F % 32 != 0 || !cut_fits<ChipCut>(d, heads * 64, F, 32)) return 0;
     const int g = cut_groups<ChipCut>(d, heads, F, gated), apart = d / 16 + ceil_div(gated ? F / 8 : F / 16, ChipCut::FT) + heads;
