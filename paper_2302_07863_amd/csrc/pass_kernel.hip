@@ -885,8 +885,13 @@ int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus, bool l
 // tokens 423 / 436 for eight rows), of 2048 332, 371, 381, 400, 474 / 321, 379, 392, 415, 474; gated, 2816, 24 layers 360, 410, 423, 445, 526 / 342, 410, 428, 447, 529, 8 layers 122, 142, 147, 153,
 // 179 / 122, 142, 148, 157, 186.  768 wide, d_ff 3072, 12 layers (216 MiB) 157, 178, 187, 197, 230 / 158, 178, 186, 197, 231, 24 layers 319, 351, 369, 388, 456 / 303, 349, 362,
 // 381, 454.  Narrower models, held by the cache, are 0 to 2 % faster with the last ones, gated ones above eight rows 2 to 4 % slower.
-// The line lies below the cache's size, because other passes of a request come in between: the 255 MiB of the T5-large shape's first six layers and its head,
-// early exit, three small steps between reviews, 14.73 ms a request with the first ones, 14.55 with the last.
+// The line lies where the two are about the same in requests, whose reviews by a larger model come in between and whose caches are read as well: rounds
+// of eight small steps and a review, 64 source tokens, us a step that the last ones take more (+) or less, small model of 4, 5, 6, 7 layers with its head, by d_ff of
+// 1024-wide models: 4096 (191, 223, 255, 287 MiB) +1.1, -1.4, -2.0, -4.8, as early exit +0.9, +1.8, +2.0, -4.6; gated, 2816 (193, 225, 258, 290 MiB) +0.4, 0, -0.8,
+// -3.2, as early exit +0.2, 0, +0.7, -2.8; 768 wide, d_ff 3072, 8, 10, 11, 12 layers (191, 227, 245, 263 MiB) -0.6, -0.2, -1.8, -2.2, as early exit +1.7, -2.4, -1.1,
+// -2.6; of steps of 80 to 130 us.  1024 wide, d_ff 2048, 7, 8, 9 layers (231, 255, 279 MiB) +1.3, +2.1, +0.7, as early exit +4.2, +1.9, +1.9: there the line could
+// lie higher.  With 512 source tokens the six layers of the T5-large shape as early exit, three small steps between reviews, take 14.73 ms a request with the first
+// ones and 14.55 with the last.
 bool pass_last(int d, int F, bool gated, int T, size_t bytes) {
     if (d < 768) return !(gated && T > 8);
     return bytes > (size_t)250 << 20 && (T == 1 || F >= 3 * d);
