@@ -53,7 +53,12 @@ bool config_ok(const bild_model_config& c) {
 
 // what the workgroups of a pass in one kernel hand over: three layers' memory
 size_t pass_turns_bytes(const ModelState& M, int room) {
-    return 3 * (size_t)pass_plan(1 << room, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff, M.m->cfg.dtype == BILD_DT_F32, M.pass_wide).layer;
+    const bool f32 = M.m->cfg.dtype == BILD_DT_F32;
+    const PassPlan p = pass_plan(1 << room, M.m->cfg.d_model, M.m->inner(), M.m->cfg.d_ff, f32, M.pass_wide);
+    PassHead h = {};
+    if (room != 0 || M.pass_die_groups == 0) return 3 * (size_t)p.layer;
+    pass_head_plan(h, p, M.m->cfg.d_model, f32, 256);  // (on one die: of 256 compute units)
+    return (size_t)h.at + 2 * (size_t)h.bytes;
 }
 
 // captured passes carry some of the state's settings by value: where one changes they are captured anew
@@ -387,7 +392,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
     const int positions = std::max(s->cap_len, s->cap_src);
-    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + 2 * kPassRooms), true);
+    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + 2 * kPassRooms + 2), true);
     if (p->m[0]->cfg.dtype == BILD_DT_BF16 || p->m[1]->cfg.dtype == BILD_DT_BF16) {
         want(s->thin_sums, sizeof(float) * kThinSums);
         want(s->thin_arrived, sizeof(unsigned) * kThinArrivals, true);
@@ -1441,7 +1446,31 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         p.wide = M.pass_wide;
         p.two = two_tiles(s, w, T);
         p.rope = M.rope;
-        HIPC(M.pass_wide ? launch_wide(p, s->stream) : launch_pass(p, die ? s->cus : p.groups, s->stream));
+        PassHead in;
+        const bool inside = die && T == 1 && lm_rows == 1 && mode != 3 && !s->debug_logits && s->top_p == 0.f;  // (pass_head.h)
+        if (inside) {
+            std::memset((void*)&in, 0, sizeof(in));
+            in.w = m->head.w;
+            in.tn = m->head.tn;
+            in.vocab = c.vocab;
+            in.gain = m->dec_final;
+            in.scale = c.logit_scale;
+            in.turn = s->pass_sync + kPassSyncWords + 2 * kPassRooms + w;
+            pass_head_plan(in, p.at, d, p.f32, s->cus);
+            FinishArgs& f = in.f;
+            f.ctl = s->ctl;
+            f.y = s->y;
+            f.which = w;
+            f.rows_consumed = T;
+            f.y_cap = s->max_len;
+            f.host_mirror = s->hctl_dev;
+            f.sync = s->pass_sync;
+            f.turn = pass_turn(s, w, T);
+            f.T = 1;
+            f.mode = mode;
+        }
+        HIPC(M.pass_wide ? launch_wide(p, s->stream) : launch_pass(p, inside ? &in : nullptr, die ? s->cus : p.groups, s->stream));
+        if (inside) return BILD_OK;
     } else if (takes_thin(s, w, T)) {
         const int rc = emit_thin(s, w, T, key_hint, lm_rows > 0, &thin_parts);
         if (rc) return rc;
@@ -1661,6 +1690,7 @@ int pass_gave_up(bild_state* s, int w, int T) {
     // what it handed over is in no known state: nothing is there yet
     const ModelState& M = s->ms[w];
     HIPC(hipMemsetAsync(M.pass_turns[pass_room_index(T)], 0xFF, pass_turns_bytes(M, pass_room_index(T)), s->stream));
+    HIPC(hipMemsetAsync(s->pass_sync, 0, sizeof(unsigned) * kPassSyncWords, s->stream));  // (workgroups may have started behind its end)
     return BILD_OK;
 }
 

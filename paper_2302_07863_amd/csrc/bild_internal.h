@@ -202,7 +202,9 @@ constexpr int kPassRows = 16, kPassDieRows = 4;
 // The hand-over memory is laid out for 1, 2, 4, 8 or 16 rows.
 constexpr int kPassRooms = 5;
 constexpr int pass_room_index(int rows) { return rows <= 1 ? 0 : rows <= 2 ? 1 : rows <= 4 ? 2 : rows <= 8 ? 3 : 4; }
-constexpr int kPassSyncWords = 128;  // the ranks given out on a die; on another line, the last word: a workgroup gave up
+// The ranks given out on a die; on lines of their own, of passes with the head inside (pass_head.h), the ranks given out on the die, mod 32, and on
+// the others; and, the last word: a workgroup gave up
+constexpr int kPassSyncWords = 128, kPassGoingOn = 32, kPassOthers = 64;
 struct PassLayer {
     const void *wqkv, *wo, *cwq, *cwo, *win, *wout;
     const float *ln1, *lnc, *ln2;
@@ -212,6 +214,47 @@ struct PassPlan {  // where a layer's hand-over buffers lie in its piece of the 
     int x1, q, k, v, a1, x2, a2, x3, h;
     int part, top;            // (pass_wide.hip) attention results of the key ranges, their (max, sum)
     int layer;
+};
+struct FinishArgs {
+    Ctl* ctl;
+    int* y;
+    const StatPart* part;  // [rows][part_ld]
+    int nparts, part_ld;
+    const float* zt;
+    int T;       // rows that went through the LM head
+    int row_off; // first such row within the pass
+    int which;   // 0 small, 1 large
+    int mode;    // 0 small step, 1 verify, 2 plain greedy (always append), 3 advance only, 4 measure
+    int rows_consumed;  // rows the pass consumed (cache advance)
+    int y_cap;
+    Ctl* host_mirror;   // device-visible pinned host copy of the control block, written last
+    // sampling variant (top_p > 0): the committed token is drawn from the nucleus of its row instead of the argmax
+    float top_p;
+    const float* logits;  // [rows][vocab] logits of the pass (row_off applies)
+    int vocab;
+    const float* u;       // uniform number per sequence position, for the model of this pass
+    // rejection-sampling acceptance (accept_mode 1, sampling variant only): the review keeps a draft iff
+    // u_acc[position] * p_S(draft) < p_L(draft) and replaces the first refused one by a draw from max(0, p_L - p_S)
+    int accept_mode;
+    const float* u_acc;   // uniform number per sequence position for the acceptance test
+    float* s_ring;        // [kMaxRows][vocab] the small model's logits of each pending draft, by draft index
+    float4* s_draw;       // [sequence capacity] (max logit, nucleus threshold key, nucleus mass, -) of the small model's row
+    unsigned* turn;       // counts the passes with room for a number of rows, mod 3
+    unsigned* sync;       // of the pass kernel, cleared here for its next pass; a flagged pass is not committed
+    // nucleus draw spread over the chip (launch_finish_draw): its workspace
+    struct DrawWs* dws;
+};
+
+// LM head and policy in the pass kernel (pass_head.h).
+struct PassHead {
+    const void* w;
+    int tn, vocab;
+    const float* gain;        // of the final norm
+    float scale;
+    int groups;               // workgroups of the other dies
+    int at, rec, bytes;       // in PassArgs::scratch, two places of `bytes` each: the hidden state, at `rec` the partials
+    unsigned* turn;           // whose turn it is of the two
+    FinishArgs f;
 };
 struct PassArgs {
     const PassLayer* layers;  // device array, from the pass' first layer on
@@ -249,8 +292,10 @@ inline bool cache_in_int(size_t positions, size_t i_dim, size_t esz) { return po
 int pass_groups(int d, int heads, int d_head, int F, bool gated, int cus, bool last);  // workgroups, 0: not a shape it is made for
 bool pass_last(int d, int F, bool gated, int T, size_t bytes);
 int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32);
+void pass_head_plan(PassHead& h, const PassPlan& at, int d, bool f32, int cus);  // h.groups, at, rec, bytes
 PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide);
-hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st);
+// head null: LM head and policy follow as kernels
+hipError_t launch_pass(const PassArgs& a, const PassHead* head, int grid, hipStream_t st);
 constexpr int kWideRows = 8, kWideHead = 128;  // most rows; features of a head
 constexpr int kWideSplits = 8;                 // most key ranges of a head
 constexpr int kWideApart = 1280;               // most keys with which heads and projections are different workgroups'
@@ -290,36 +335,6 @@ struct RowCopyArgs {
     const int* dst_row_ptr;
     int src_row_add, dst_row_add;
     int d, T;
-};
-
-struct FinishArgs {
-    Ctl* ctl;
-    int* y;
-    const StatPart* part;  // [rows][part_ld]
-    int nparts, part_ld;
-    const float* zt;
-    int T;       // rows that went through the LM head
-    int row_off; // first such row within the pass
-    int which;   // 0 small, 1 large
-    int mode;    // 0 small step, 1 verify, 2 plain greedy (always append), 3 advance only, 4 measure
-    int rows_consumed;  // rows the pass consumed (cache advance)
-    int y_cap;
-    Ctl* host_mirror;   // device-visible pinned host copy of the control block, written last
-    // sampling variant (top_p > 0): the committed token is drawn from the nucleus of its row instead of the argmax
-    float top_p;
-    const float* logits;  // [rows][vocab] logits of the pass (row_off applies)
-    int vocab;
-    const float* u;       // uniform number per sequence position, for the model of this pass
-    // rejection-sampling acceptance (accept_mode 1, sampling variant only): the review keeps a draft iff
-    // u_acc[position] * p_S(draft) < p_L(draft) and replaces the first refused one by a draw from max(0, p_L - p_S)
-    int accept_mode;
-    const float* u_acc;   // uniform number per sequence position for the acceptance test
-    float* s_ring;        // [kMaxRows][vocab] the small model's logits of each pending draft, by draft index
-    float4* s_draw;       // [sequence capacity] (max logit, nucleus threshold key, nucleus mass, -) of the small model's row
-    unsigned* turn;       // counts the passes with room for a number of rows, mod 3
-    unsigned* sync;       // of the pass kernel, cleared here for its next pass; a flagged pass is not committed
-    // nucleus draw spread over the chip (launch_finish_draw): its workspace
-    struct DrawWs* dws;
 };
 
 // Workspace of the nucleus draw that is spread over many workgroups (policy.hip).  Probability masses are integers

@@ -34,7 +34,7 @@
 //
 // A model small enough for the 32 compute units of one die (pass_die_groups: T5-small, mT5-small) walks there: what is handed over
 // then only goes to that die's L2 and back, at 1.25 TB/s for the weights instead of the chip's 4.8, which a layer of 7 MB in 13 us
-// does not notice.  Workgroups of the other dies end at once.
+// does not notice.  Workgroups of the other dies end at once, or, in a pass of one row, have the LM head and the policy (pass_head.h).
 //
 // fp32 models keep fp32 everywhere: activations travel as they are, sixteen rows in a matrix-core operand, attention in blocks of sixteen
 // keys (a block's 64 fp32 products take 0.85 us of a wave's SIMD for 32 keys); one row's projections run on the vector ALU (multiply).
@@ -52,7 +52,7 @@
 // handed over is ever used as an address), so every workgroup ends.  The policy kernel then commits nothing and the host runs
 // the pass again as separate kernels; after some passes it tries this kernel again.  That happens only if the workgroups cannot
 // all be resident, because of another process' kernel of the same kind, for instance.
-#include "pass_walk.h"
+#include "pass_head.h"
 
 namespace bild {
 
@@ -515,8 +515,8 @@ __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; 
 
 // Workgroups [0, workers) do the projections; the first of them own sixteen features (OT times) of the residual stream each: wave
 // q holds those of tile q.
-template <bool GATED, bool PACK, class Cut, class Walk>
-__device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
+template <bool GATED, bool PACK, class Cut, class Walk, class... Head>
+__device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups, const Head&... head) {
     int T = a.T, d = a.d, I = a.I, F = a.F;
     constexpr int QT = Cut::QT, OT = Cut::OT, FT = Cut::FT, KD = Cut::KD, KF = Cut::KF;
     constexpr bool CHIP = Walk::kOut != 0;
@@ -688,7 +688,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             const float4 gn = gain(a.cross ? L->lnc : L->ln2);
             if (a.cross) request<KF, OT, 0, EARLY>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
             if (!a.cross) {
-                next_gain = gain(last ? L->ln2 : L[1].ln1);
+                next_gain = gain(last ? final_gain(L->ln2, head...) : L[1].ln1);
                 request<KF, OT>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
             }
             const char* xs = pinned(z + a.at.a1);
@@ -705,7 +705,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             if (owner) {
                 request<KD, OT>(c, Wo, L->cwo, c.wg, I >> c.KS, nd());
                 const float4 gn = gain(L->ln2);
-                next_gain = gain(last ? L->ln2 : L[1].ln1);
+                next_gain = gain(last ? final_gain(L->ln2, head...) : L[1].ln1);
                 if (ffn) request<KD, FT>(c, Wi, L->win, uf, d >> c.KS, tf());
                 request<KF, OT, EARLY, KF>(c, Wf, L->wout, c.wg, F >> c.KS, nd());
                 if (qkv && !last && WQ == 0) request<KD, QT>(c, Wq, L[1].wqkv, uq, d >> c.KS, tq());
@@ -759,6 +759,7 @@ __device__ __forceinline__ void worker(Walk& c, const PassArgs& a, int groups) {
             leave<OT, false, RF>(c, acc);
             if (mine) add(std::bool_constant<RF>{});
             if (!last) publish(next_gain, ox);
+            else if constexpr (Walk::HEAD) publish_final(c, a, head..., mine, n0(), x, next_gain);
             if (qkv && !last && a.cross && WQ == 2) request<KD, QT>(c, Wq, L[1].wqkv, uq, d >> c.KS, tq());
         }
     }
@@ -858,6 +859,38 @@ __global__ __launch_bounds__(kPassThreads, 1) void pass_kernel(const PassArgs a)
     else header<GATED, PACK, Cut>(c, a, a.groups);
 }
 
+// The same on one die for one row, with LM head and policy (pass_head.h): die 0 walks the layers, the others have the head.
+template <bool GATED, bool F32>
+__global__ __launch_bounds__(kPassThreads, 1) void pass_head_kernel(const PassArgs a, const PassHead head) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    using Cut = std::conditional_t<F32, DieCutF32, DieCut>;
+    constexpr bool PACK = !F32;
+    HeadWalk<F32> c;
+    c.lds = smem;
+    c.failed = a.sync + kPassSyncWords - 1;
+    c.spins = a.spins;
+    c.wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    c.lane = (int)threadIdx.x & 63;
+    c.dead = false;
+    c.place(1, 1);
+    if (__builtin_amdgcn_s_getreg((3 << 11) | 20) != 0) {
+        head_part<Cut>(c, a, head);
+        return;
+    }
+    c.odd = *head.turn & 1u;
+    if (threadIdx.x == 0) {
+        unsigned rank;
+        asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)" : "=v"(rank) : "v"(a.sync + kPassGoingOn), "v"(1u) : "memory");
+        *(unsigned*)smem = rank;
+    }
+    lds_barrier();
+    c.wg = __builtin_amdgcn_readfirstlane(*(volatile int*)smem) & 31;  // (counted on from pass to pass)
+    if (c.wg >= a.groups) return;
+    lds_barrier();
+    if (c.wg < a.groups - a.heads) worker<GATED, PACK, Cut>(c, a, a.groups, head);
+    else header<GATED, PACK, Cut>(c, a, a.groups);
+}
+
 template <class Cut>
 static int cut_groups(int d, int heads, int F, bool gated) {
     return std::max(std::max(ceil_div(3 * heads * 4, Cut::QT), ceil_div(gated ? F / 8 : F / 16, Cut::FT)), ceil_div(d / 16, Cut::OT)) + heads;
@@ -903,6 +936,14 @@ int pass_die_groups(int d, int heads, int d_head, int F, bool gated, bool f32) {
     return g <= 32 ? g : 0;
 }
 
+void pass_head_plan(PassHead& h, const PassPlan& at, int d, bool f32, int cus) {
+    const int x = d / (f32 ? 16 : 32) * tile_bytes(true, 1, f32), nv = f32 ? HeadCut<true>::NV : HeadCut<false>::NV;
+    h.groups = cus - cus / 8;  // (workgroups go to the eight dies in turn)
+    h.at = 3 * at.layer;
+    h.rec = (x + 255) / 256 * 256;
+    h.bytes = (h.rec + h.groups * nv * 16 + 255) / 256 * 256;
+}
+
 PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide) {
     PassPlan p;
     size_t at = 0;
@@ -929,27 +970,37 @@ hipError_t pass_init() {
     static hipError_t done = [] {
 #define BILD_P(DV, FV, RV) (const void*)pass_kernel<false, DV, FV, RV>, (const void*)pass_kernel<true, DV, FV, RV>
         const void* fns[] = {BILD_P(true, false, 1), BILD_P(true, false, 2), BILD_P(true, false, 4), BILD_P(false, false, 1), BILD_P(false, false, 2), BILD_P(false, false, 4),
-                             BILD_P(false, false, 8), BILD_P(false, false, 16), BILD_P(true, true, 1), BILD_P(true, true, 0)};
+                             BILD_P(false, false, 8), BILD_P(false, false, 16), BILD_P(true, true, 1), BILD_P(true, true, 0),
+                             (const void*)pass_head_kernel<false, false>, (const void*)pass_head_kernel<true, false>,
+                             (const void*)pass_head_kernel<false, true>, (const void*)pass_head_kernel<true, true>};
 #undef BILD_P
         return raise_lds_limit(fns, 160 * 1024);
     }();
     return done;
 }
 
-hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
+hipError_t launch_pass(const PassArgs& a, const PassHead* head, int grid, hipStream_t st) {
     if (hipError_t e = pass_init(); e != hipSuccess) return e;
     if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > kPassRows || a.room < a.T || (a.die && !a.f32 && a.T > kPassDieRows) || (a.f32 && !a.die) || !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
-        (a.cross && !a.nsrc_ptr))
+        (a.cross && !a.nsrc_ptr) || (head && (!a.die || a.room != 1 || !head->w || !head->gain || !head->turn || head->groups != grid - grid / 8 || !head->f.ctl)))
         return hipErrorInvalidValue;
     const size_t smem = kRel + (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);
     if (smem > 160 * 1024) return hipErrorInvalidValue;
     const bool gated = a.act != BILD_ACT_RELU;
+#define BILD_PH(FV)                                                                                                           \
+    do {                                                                                                                     \
+        if (gated) hipLaunchKernelGGL((pass_head_kernel<true, FV>), dim3(grid), dim3(kPassThreads), smem, st, a, *head);     \
+        else hipLaunchKernelGGL((pass_head_kernel<false, FV>), dim3(grid), dim3(kPassThreads), smem, st, a, *head);          \
+        return hipGetLastError();                                                                                            \
+    } while (0)
 #define BILD_P(DV, FV, RV)                                                                                                   \
     do {                                                                                                                     \
         if (gated) hipLaunchKernelGGL((pass_kernel<true, DV, FV, RV>), dim3(grid), dim3(kPassThreads), smem, st, a);         \
         else hipLaunchKernelGGL((pass_kernel<false, DV, FV, RV>), dim3(grid), dim3(kPassThreads), smem, st, a);              \
         return hipGetLastError();                                                                                            \
     } while (0)
+    if (head && a.f32) BILD_PH(true);
+    if (head) BILD_PH(false);
     if (a.f32 && a.room == 1) BILD_P(true, true, 1);
     if (a.f32) BILD_P(true, true, 0);
     if (a.die && a.room == 1) BILD_P(true, false, 1);
@@ -961,6 +1012,7 @@ hipError_t launch_pass(const PassArgs& a, int grid, hipStream_t st) {
     if (!a.die && a.room == 8) BILD_P(false, false, 8);
     if (!a.die && a.room == 16) BILD_P(false, false, 16);
 #undef BILD_P
+#undef BILD_PH
     return hipErrorInvalidValue;
 }
 

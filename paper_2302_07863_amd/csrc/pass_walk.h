@@ -49,6 +49,7 @@ template <bool DIE, bool FP32, int ROOM>
 struct Walk : Room<ROOM> {
     using Room<ROOM>::R;
     static constexpr int KNOWN = ROOM;
+    static constexpr bool HEAD = false;    // LM head and policy inside (pass_head.h)
     static constexpr bool F32 = FP32;      // of an fp32 model
     static constexpr bool ONE = FP32 && ROOM == 1;  // ... and one row (see multiply)
     static constexpr bool ROOM1 = !FP32 && ROOM == 1;  // a producer's sum of squares behind its sixteen features, in one line

@@ -2,7 +2,7 @@
 // (Section 3.3), the rollback test (Section 3.4), the commit of Algorithm 1 on the device, and the draws of the
 // sampling variant (Appendix, "BiLD with Sampling") with the rejection-sampling acceptance of the methods the
 // paper compares with (Section 4.2).
-#include "kernel_common.h"
+#include "policy_commit.h"
 
 namespace bild {
 
@@ -282,13 +282,11 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, Draw
     int* ridx = (int*)(rsum + kMaxRows);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nthr = blockDim.x, nwv = nthr >> 6;
-    Ctl* c = a.ctl;
     // the control words the policy needs, requested now (nothing in this kernel writes them before they are used): their
     // trip from memory overlaps with the partials' instead of following it
-    const int c_ylen = c->y_len, c_ds = c->draft_start, c_nmax = c->n_max, c_len0 = c->len[0], c_len1 = c->len[1], c_lenw = c->len[a.which];
-    const float c_afb = c->alpha_fb, c_arb = c->alpha_rb;
-    const int c_seq = c->seq;
-    const unsigned c_turn = a.turn ? *a.turn : 0u;
+    const Controls k(a);
+    const int c_ylen = k.ylen, c_ds = k.ds;
+    const float c_arb = k.arb;
     const bool failed = a.sync && a.sync[kPassSyncWords - 1] != 0u;
     float z_draft = 0.f;
     if (a.mode != 3)
@@ -379,94 +377,11 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, char* lds, Draw
             }
         }
     }
-    // From here on wave 0 alone, lane t with row t: no barrier, no trip through LDS.  The results go to the control block and,
-    // for the caller, to its mirror in pinned host memory (the words not written are the host's own).  The mirror is written
-    // past the caches and the pass counter once those stores have been acknowledged, so that a host that sees the new count also
-    // sees every other word.  (Volatile stores, one word after the other, each waited for its acknowledgement over the host
-    // link, and a system-wide fence writes the L2 back besides: 5 us for this kernel and 10 us for a wide one.)
+    // From here on wave 0 alone, lane t with row t: no barrier, no trip through LDS.
     if (tid >= 64) return;
-    const int w = a.which, n = a.T - 1;
-    Ctl* v = a.host_mirror;
-    const __amdgpu_buffer_rsrc_t mirror = make_rsrc(v, v ? sizeof(Ctl) : 0);  // (none: the stores are out of bounds and dropped)
-    auto tell = [&](int word, int off) { __builtin_amdgcn_raw_buffer_store_b32((unsigned)word, mirror, off, 0, 17); };  // sc0 sc1
-    const int t = min(lane, max(n, 0));
-    int row_tok = 0;
-    float nll = 0.f, pmax = 0.f;
-    if (a.mode != 3) {
-        row_tok = ridx[t];
-        pmax = 1.f / rsum[t];
-        if (lane <= n) {
-            c->res_rowtok[lane] = row_tok;
-            tell(row_tok, (int)offsetof(Ctl, res_rowtok) + lane * 4);
-        }
-    }
-    if (a.sync) {
-        if (lane == 0 && a.turn) *a.turn = c_turn == 2u ? 0u : c_turn + 1u;
-        if (lane == 0) a.sync[0] = a.sync[kPassSyncWords - 1] = 0u;
-        if (failed) {  // the pass kernel's workgroups did not all run: nothing happened but the count of passes
-            if (lane == 0) {
-                c->seq = c_seq + 1;
-                tell(kFlagFailed, (int)offsetof(Ctl, res_flag));
-            }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (lane == 0) tell(c_seq + 1, (int)offsetof(Ctl, seq));
-            return;
-        }
-    }
-    int n_ylen = c_ylen, n_ds = c_ds, n_len0 = c_len0, n_lenw = c_lenw + a.rows_consumed;
-    int res_tok = 0, res_flag = 0, res_r = 0, res_n = 0, y_at = -1;
-    float res_pmax = 0.f;
-    if (a.mode == 0 || a.mode == 2) {
-        res_tok = drawn >= 0 ? drawn : __builtin_amdgcn_readlane(row_tok, n);
-        res_pmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pmax), n));
-        const bool low = a.mode == 0 && res_pmax < c_afb;
-        const bool forced = a.mode == 0 && c_nmax > 0 && (c_ylen - c_ds) >= c_nmax;
-        if (!low && !forced && c_ylen < a.y_cap) {
-            y_at = c_ylen;
-            n_ylen = c_ylen + 1;
-            if (a.mode == 2) n_ds = c_ylen + 1;
-        }
-        res_flag = (low || forced ? 1 : 0) | ((forced && !low) ? 2 : 0);
-    } else if (a.mode == 1) {  // review of n drafts: -ln p_L(draft) of each against the threshold
-        nll = (rm[t] + logf(rsum[t])) - z_draft;
-        int r = r_given;       // (the rejection rule decided above)
-        if (r < 0) {
-            const unsigned long long over = __builtin_amdgcn_ballot_w64(lane < n && nll > c_arb);
-            r = over ? (int)__builtin_ctzll(over) : n;
-        }
-        if (lane < n && (r_given < 0 || lane <= r)) {
-            c->res_nll[lane] = nll;
-            tell(__float_as_int(nll), (int)offsetof(Ctl, res_nll) + lane * 4);
-        }
-        res_tok = drawn >= 0 ? drawn : __builtin_amdgcn_readlane(row_tok, r);
-        res_pmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pmax), r));
-        y_at = c_ds + r;
-        n_ylen = n_ds = c_ds + r + 1;
-        n_lenw = c_ds + r;     // (w == 1)
-        n_len0 = min(c_len0, c_ds + r);
-        res_r = r;
-        res_n = n;
-    }
-    const int l0 = w == 0 ? n_lenw : n_len0, l1 = w == 1 ? n_lenw : c_len1;
-    const int sq = c_seq + 1;
-    if (a.mode != 4) {
-        if (lane == 0 && y_at >= 0) a.y[y_at] = res_tok;
-        static_assert(offsetof(Ctl, res_tok) == 32 && offsetof(Ctl, res_pmax) == 48, "words 0 .. 3 and 8 .. 12");
-        const int words[13] = {n_ylen, n_ds, l0, l1, 0, 0, 0, 0, res_tok, res_flag, res_r, res_n, __float_as_int(res_pmax)};
-        int mine = 0;  // lane i has word i: one store
-#pragma unroll
-        for (int i = 0; i < 13; ++i) mine = lane == i ? words[i] : mine;
-        if (lane < 13 && (lane < 4 || lane >= 8)) {
-            tell(mine, lane * 4);
-            ((int*)c)[lane] = mine;
-        }
-    }
-    if (v) {
-        static_assert(offsetof(Ctl, seq) == sizeof(Ctl) - 4, "seq must be the last word of the control block");
-        if (lane == 0) c->seq = sq;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == 0) tell(sq, (int)offsetof(Ctl, seq));
-    }
+    const int t = min(lane, max(a.T - 1, 0));
+    const bool rows = a.mode != 3;
+    commit(a, k, failed, rows ? ridx[t] : 0, rows ? rm[t] : 0.f, rows ? rsum[t] : 0.f, z_draft, drawn, r_given);
 }
 
 __global__ __launch_bounds__(256) void finish_kernel(const FinishArgs a) {

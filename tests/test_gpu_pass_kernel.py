@@ -327,3 +327,29 @@ def test_embedding_rows_past_twice_the_vocabulary(shape, one, monkeypatch):
     parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, cfg)
     routes = st.pass_routes()
     assert (routes["chip"] + routes["die"] > 0) == (one == "1"), routes
+
+
+@pytest.mark.parametrize("dtype,vocab", [
+    (bi.DT_BF16, 17), (bi.DT_BF16, 160), (bi.DT_BF16, 161), (bi.DT_BF16, 224 * 160), (bi.DT_BF16, 224 * 160 + 1), (bi.DT_BF16, 3 * 224 * 160 + 1000),
+    (bi.DT_F32, 63), (bi.DT_F32, 65), (bi.DT_F32, 224 * 64 + 1), (bi.DT_F32, 40000)])
+def test_head_and_policy_inside_the_pass(dtype, vocab):
+    """Passes of one row whose head's workgroups are those of the other dies: less than a tile and than a unit of ten (fp32: four) tiles, a unit for each
+    of the 224, one more, several rounds.  Against the oracle; then steps whose logits are kept, which run head and policy as kernels,
+    between others in the same hand-over memory."""
+    cfg = bi.toy_pair(dtype=dtype, d=256, heads=4, d_head=64, d_ff=512, truncate=dtype == bi.DT_BF16, n_src=20, max_new=8, vocab=vocab, tie_shift=min(37, vocab - 1))
+    R = Rig(cfg)
+    ref = oracle.bild_generate(R.req, 0.4, 1.0, 4, cfg.max_new, keep_logits=True)
+    st = R.state(cfg.max_new, 4)
+    st.encode(R.src)
+    parity.teacher_forced(st, ref, R.n0, 0.4, 1.0, cfg, check_logits=False)
+    steps = []
+    for turn in range(6):
+        st.debug_enable_logits(turn in (1, 2, 4))
+        st.seq_truncate(R.n0)
+        steps.append([st.small_step(0.0) for _ in range(3)])
+    for other in steps[1:]:
+        for (tok, flag, p), (tok0, flag0, p0) in zip(other, steps[0]):
+            # (the same sums in another order: fp32 products of at most 512 inputs)
+            assert (tok, flag) == (tok0, flag0) and abs(p - p0) <= 1e-4 * p0
+    r = st.pass_routes()
+    assert r["die"] > 0 and r["kernels"] == r["gave_up"] == 0
