@@ -27,6 +27,9 @@ __host__ __device__ constexpr int tile_sums(int rt) { return rt * 16 * kTileWave
 // Three workgroups per compute unit (see the shared form below)
 constexpr bool tile_lean(int rt, int epi, bool gated) { return rt == 4 && (epi == EPI_QKV || gated); }
 
+// One workgroup per compute unit (sliced inputs, 24 tiles of sums and more a wave)
+constexpr bool tile_alone(int rt, int ft, bool share) { return !share && rt * ft >= 24; }
+
 // Row block and feature group of a workgroup.  Workgroups go to the eight dies in turn; the dies form a grid of a.gr row
 // shares x 8 / a.gr feature shares (launch_gemm_tile), and a die walks the row blocks of its share before the next feature
 // group, so that the weights of a group come from memory once and are then in that die's L2 while the rows pass.
@@ -44,7 +47,7 @@ __device__ __forceinline__ bool tile_block(const TileGemmArgs& a, int& rb, int& 
 // FT: feature tiles per wave.  GATED: feature tiles 2j / 2j+1 hold gate and linear branch of output block j.
 // SPLIT: the waves of a workgroup (also) slice the inputs, a.wk of them per feature group.
 template <int RT, int FT, int EPI, int ROPE, bool GATED, bool SPLIT, bool SHARE>
-__global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) void gemm_tile_kernel(const TileGemmArgs a) {
+__global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : tile_alone(RT, FT, SHARE) ? 1 : 2) void gemm_tile_kernel(const TileGemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr bool norm = EPI != EPI_RESID;  // residual-adding projections read un-normalised input
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -93,7 +96,8 @@ __global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) vo
     float ssum = 0.f;
     auto row_sums = [&]() {
         if (!norm) return;
-        const float* sp = a.ssq + min(r0 + (tid & (ROWS - 1)), a.M - 1);
+        if (SHARES * ROWS < 256 && tid >= SHARES * ROWS) return;
+        const float* sp = a.ssq + min(r0 + tid % ROWS, a.M - 1);
         for (int p0 = tid / ROWS; p0 < a.ssq_parts; p0 += 8 * SHARES) {
             float v[8];
 #pragma unroll
@@ -110,8 +114,10 @@ __global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) vo
         return rsqrtf(sum / (float)a.W.k + a.eps);
     };
     // With sliced inputs a wave finishes 1 / WK of the row tiles: what it adds to is requested ahead of the products.
-    float4 old[FT], gain[FT];
-    if constexpr (EPI == EPI_RESID) {
+    // (not where a wave has so many sums)
+    constexpr bool AHEAD = FT <= 4;
+    float4 old[AHEAD ? FT : 1], gain[AHEAD ? FT : 1];
+    if constexpr (EPI == EPI_RESID && AHEAD) {
 #pragma unroll
         for (int f = 0; f < FT; ++f) {
             const int n0 = min(tile0 + f, a.W.tn - 1) * 16 + kq * 4;
@@ -133,7 +139,7 @@ __global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) vo
         constexpr bool SPREAD = tile_lean(RT, EPI, GATED) || (RT == 4 && EPI == EPI_RESID);
         constexpr int AH = SPREAD ? 2 : 1;        // steps from the store to the use
         char* xs = (char*)red;                    // [2 AH][RT][2][1 KiB]
-        constexpr int D = RT == 8 ? 2 : tile_lean(RT, EPI, GATED) ? 3 : 4;  // steps requested ahead (spread: one less of the weights)
+        constexpr int D = RT == 8 ? 2 : RT == 6 || tile_lean(RT, EPI, GATED) ? 3 : 4;  // steps requested ahead (spread: one less of the weights)
         uint4 W[D][FT], XR[D][UPW], B[2][2];
         int xu[UPW];
 #pragma unroll
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) vo
         // Six steps of 32 rows take 174 to 182 registers with two feature tiles and 142 to 150 with one (128 with four steps): two or three
         // waves a SIMD fit instead of four.  These forms are launched with a workgroup per compute unit at most (tile_shape), one wave a
         // SIMD, two beside the pair's other encoder.
-        constexpr int LOADS = RT * 2 + FT, D = LOADS <= 6 ? 6 : LOADS == 8 ? 5 : LOADS <= 10 ? 4 : 2;
+        constexpr int LOADS = RT * 2 + FT, D = LOADS <= 6 ? 6 : LOADS == 8 ? 5 : LOADS <= 10 ? 4 : tile_alone(RT, FT, SHARE) ? 3 : 2;
         uint4 W[D][FT], X[D][RT][2];
         auto request = [&](int d, int k) {
 #pragma unroll
@@ -303,10 +309,10 @@ __global__ __launch_bounds__(256, SHARE && tile_lean(RT, EPI, GATED) ? 3 : 2) vo
             float v4[4] = {c[f][0] * sc, c[f][1] * sc, c[f][2] * sc, c[f][3] * sc};
             if constexpr (EPI == EPI_RESID) {
                 float4* px = (float4*)(a.x + (size_t)t * a.ldx + n0);
-                const float4 o = SPLIT && r == wkid ? old[f] : *px;
+                const float4 o = SPLIT && AHEAD && r == wkid ? old[AHEAD ? f : 0] : *px;
                 const float xn[4] = {o.x + v4[0], o.y + v4[1], o.z + v4[2], o.w + v4[3]};
                 *px = make_float4(xn[0], xn[1], xn[2], xn[3]);
-                const float4 gn = gain[f];
+                const float4 gn = AHEAD ? gain[AHEAD ? f : 0] : *(const float4*)(a.np_gain + n0);
                 const float w[4] = {xn[0] * gn.x, xn[1] * gn.y, xn[2] * gn.z, xn[3] * gn.w};
                 put_tile_planes(a.np, a.np_tk, t, n0, w);
                 ss += xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
@@ -467,23 +473,30 @@ hipError_t launch_rope_table(double2* table, int positions, int d_head, float ba
 // of that each.  The shape with the smallest total is taken: the wide shared tiles where there are enough of them, else
 // smaller tiles and sliced inputs.  (1023 x 22016 x 4096: 285 us, 1.3 PFLOP/s issued of the 1.75 the matrix cores keep up on
 // random operands; 512 x 1024 x 4096: 18.5 us; 64 x 1024 x 1024: 5.2 us.)
+// Shapes of 96 rows x 192 or 256 features (shared) and of 48 x 128 (sliced, one workgroup per compute unit, `once` us for joining 24 tiles of sums) are
+// for products that they cut into one round where the others make a round and a bit of another: 1531 rows, features x inputs, us, best of the others /
+// with: 3072 x 1024 (256 workgroups of 96 x 192) 31.4 / 25.4, 4096 x 1024 (256 of 96 x 256) 31.0 / 27.4, 1024 x 4096 (256 of 48 x 128) 42.5 / 34.1, but
+// 1024 x 1024 16.4 / 17.6.  Measured beside them and not taken: sliced, 96 x 64 as 48 x 128; 64 x 96, which gains 1 us at 512 x 3072 x 1024 alone; 64 x 128.
 struct TileShape {
     int rt, ft, wk;
     bool share;
-    float us;
+    float us, once;
+    bool fills;  // only where it makes one round
 };
 static TileShape tile_shape(const TileGemmArgs& a) {
-    static const TileShape shapes[] = {{8, 4, 1, true, 0.94f}, {4, 4, 1, true, 0.57f}, {4, 4, 2, false, 0.84f},
-                                       {4, 4, 4, false, 0.80f}, {4, 2, 4, false, 0.69f}, {4, 1, 4, false, 0.60f},
-                                       {2, 4, 4, false, 0.56f}, {2, 2, 4, false, 0.42f}, {2, 1, 4, false, 0.36f}};
+    static const TileShape shapes[] = {{8, 4, 1, true, 0.94f, 0.f, false}, {4, 4, 1, true, 0.57f, 0.f, false}, {4, 4, 2, false, 0.84f, 0.f, false},
+                                       {4, 4, 4, false, 0.80f, 0.f, false}, {4, 2, 4, false, 0.69f, 0.f, false}, {4, 1, 4, false, 0.60f, 0.f, false},
+                                       {2, 4, 4, false, 0.56f, 0.f, false}, {2, 2, 4, false, 0.42f, 0.f, false}, {2, 1, 4, false, 0.36f, 0.f, false},
+                                       {6, 4, 1, true, 0.83f, 0.f, true}, {6, 3, 1, true, 0.75f, 0.f, true}, {3, 8, 4, false, 0.70f, 11.f, true}};
     const bool gated = a.epi == EPI_ACT && a.act != BILD_ACT_RELU;
     const TileShape* best = nullptr;
     float least = 0.f;
     for (const TileShape& t : shapes) {
-        if (gated && t.ft == 1) continue;
+        if (gated && t.ft % 2) continue;
         const int rows = t.rt * 16, feats = t.ft * (kTileWaves / t.wk);
         const int rounds = (((a.M + rows - 1) / rows) * ((a.W.tn + feats - 1) / feats) + 255) / 256;
-        const float us = (float)((a.W.tk + t.wk - 1) / t.wk) * t.us * (rounds == 1 ? 1.f : 0.8f * (float)rounds);
+        if (t.fills && rounds > 1) continue;
+        const float us = (float)((a.W.tk + t.wk - 1) / t.wk) * t.us * (rounds == 1 ? 1.f : 0.8f * (float)rounds) + t.once;
         if (!best || us < least) { best = &t; least = us; }
     }
     return *best;
@@ -502,14 +515,17 @@ hipError_t gemm_tile_init() {
     BILD_T(8, 4, EPIV, ROPEV, false, false, true), BILD_T(4, 4, EPIV, ROPEV, false, false, true),                            \
     BILD_T(2, 4, EPIV, ROPEV, false, true, false), BILD_T(2, 2, EPIV, ROPEV, false, true, false),                            \
     BILD_T(2, 1, EPIV, ROPEV, false, true, false), BILD_T(4, 4, EPIV, ROPEV, false, true, false),                            \
-    BILD_T(4, 2, EPIV, ROPEV, false, true, false), BILD_T(4, 1, EPIV, ROPEV, false, true, false)
+    BILD_T(4, 2, EPIV, ROPEV, false, true, false), BILD_T(4, 1, EPIV, ROPEV, false, true, false),                            \
+    BILD_T(6, 4, EPIV, ROPEV, false, false, true), BILD_T(6, 3, EPIV, ROPEV, false, false, true),                            \
+    BILD_T(3, 8, EPIV, ROPEV, false, true, false)
         const void* fns[] = {BILD_TF(EPI_RESID, 0), BILD_TF(EPI_ACT, 0), BILD_TF(EPI_QKV, 0), BILD_TF(EPI_QKV, 1),
                              BILD_T(8, 4, EPI_ACT, 0, true, false, true), BILD_T(4, 4, EPI_ACT, 0, true, false, true),
                              BILD_T(2, 4, EPI_ACT, 0, true, true, false), BILD_T(2, 2, EPI_ACT, 0, true, true, false),
-                             BILD_T(4, 4, EPI_ACT, 0, true, true, false), BILD_T(4, 2, EPI_ACT, 0, true, true, false)};
+                             BILD_T(4, 4, EPI_ACT, 0, true, true, false), BILD_T(4, 2, EPI_ACT, 0, true, true, false),
+                             BILD_T(6, 4, EPI_ACT, 0, true, false, true), BILD_T(3, 8, EPI_ACT, 0, true, true, false)};
 #undef BILD_TF
 #undef BILD_T
-        return raise_lds_limit(fns, 80 * 1024);
+        return raise_lds_limit(fns, 160 * 1024);
     }();
     return done;
 }
@@ -549,6 +565,9 @@ hipError_t launch_gemm_tile(const TileGemmArgs& a0, hipStream_t st) {
 #define BILD_TF(EPIV, ROPEV)                                                                                                 \
     do {                                                                                                                     \
         if (t.share && t.rt == 8) BILD_T(8, 4, EPIV, ROPEV, false, false, true);                                             \
+        if (t.share && t.rt == 6 && t.ft == 4) BILD_T(6, 4, EPIV, ROPEV, false, false, true);                                \
+        if (t.share && t.rt == 6) BILD_T(6, 3, EPIV, ROPEV, false, false, true);                                             \
+        if (t.rt == 3) BILD_T(3, 8, EPIV, ROPEV, false, true, false);                                                        \
         if (t.share) BILD_T(4, 4, EPIV, ROPEV, false, false, true);                                                          \
         if (t.rt == 2 && t.ft == 4) BILD_T(2, 4, EPIV, ROPEV, false, true, false);                                           \
         if (t.rt == 2 && t.ft == 2) BILD_T(2, 2, EPIV, ROPEV, false, true, false);                                           \
@@ -562,6 +581,8 @@ hipError_t launch_gemm_tile(const TileGemmArgs& a0, hipStream_t st) {
         case EPI_ACT:
             if (!gated) BILD_TF(EPI_ACT, 0);
             if (t.share && t.rt == 8) BILD_T(8, 4, EPI_ACT, 0, true, false, true);
+            if (t.share && t.rt == 6) BILD_T(6, 4, EPI_ACT, 0, true, false, true);
+            if (t.rt == 3) BILD_T(3, 8, EPI_ACT, 0, true, true, false);
             if (t.share) BILD_T(4, 4, EPI_ACT, 0, true, false, true);
             if (t.rt == 2 && t.ft == 4) BILD_T(2, 4, EPI_ACT, 0, true, true, false);
             if (t.rt == 2) BILD_T(2, 2, EPI_ACT, 0, true, true, false);

@@ -53,3 +53,10 @@ def test_pair_of_two_storage_types_with_a_borrowed_encoder(small, large):
     """The small model attends to the encoder output of a large model that stores another type."""
     cfg = bi.toy_pair(dtype=bi.DT_BF16, n_src=40, max_new=6)   # weights that both types hold exactly
     _check(replace(cfg, small=replace(cfg.small, dtype=small), large=replace(cfg.large, dtype=large)), bar=cfg)
+
+
+@pytest.mark.parametrize("n_src,act,heads,d_ff", [(1531, bi.ACT_RELU, 8, 2048), (1441, bi.ACT_RELU, 7, 2000), (1488, bi.ACT_GATED_GELU, 8, 1008)])
+def test_products_cut_into_one_round(n_src, act, heads, d_ff):
+    """Workgroups of 96 rows x 192 and 256 features and of 48 x 128 (the large model, twice as wide): the last rows' block nearly whole, of a
+    single row, whole; the last features' block short."""
+    _check(bi.toy_pair(dtype=bi.DT_BF16, act=act, truncate=True, d=512, heads=heads, d_head=64, d_ff=d_ff, n_src=n_src, max_new=4, vocab=300, n_large=1, logit_scale=4.0))
