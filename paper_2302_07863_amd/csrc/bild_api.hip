@@ -1512,7 +1512,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         if (f.nparts > M.nparts_cap) return BILD_ECAP;
         const int rc = run_thin(s, m, g);
         if (rc) return rc;
-    } else if (const int groups = takes_sweep(m, lm_rows) && !parts ? head_groups(m->head, lm_rows) : 0; groups > 0) {
+    } else if (const int groups = takes_sweep(m, lm_rows) && !parts ? head_groups(m->head, lm_rows, false) : 0; groups > 0) {
         HeadArgs h;
         std::memset((void*)&h, 0, sizeof(h));
         h.W = m->head;

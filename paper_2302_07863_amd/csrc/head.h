@@ -1,4 +1,4 @@
-// LM head of bf16 models: final norm, vocabulary sweep, softmax statistics (head.hip).
+// LM head: final norm, vocabulary sweep, softmax statistics (head.hip).
 #pragma once
 #include "bild_internal.h"
 
@@ -8,6 +8,7 @@ struct HeadArgs {
     TMat W;
     const float* x;      // [T][ldx]
     int ldx, T;
+    bool f32;            // of an fp32 model
     const float* gain;
     float eps, scale;
     int vocab;
@@ -23,7 +24,7 @@ struct HeadArgs {
     unsigned *done, call;  // (done nullable) pinned host memory: `call` goes to done[row] once the row's result is in memory
 };
 // workgroups (partials per row); 0: not a shape the kernel is made for
-int head_groups(const TMat& W, int T);
+int head_groups(const TMat& W, int T, bool f32);
 hipError_t launch_head(const HeadArgs& a, hipStream_t st);
 hipError_t head_init();
 

@@ -1,4 +1,4 @@
-// LM head of bf16 models over 1 .. 32 rows: the vocabulary matrix streamed once, softmax statistics of every row.
+// LM head over 1 .. 32 rows: the vocabulary matrix streamed once, softmax statistics of every row.
 //
 // Bound: the matrix' way from memory.  A workgroup per compute unit at most stays for the whole sweep: it norms and splits the rows once,
 // each of its eight waves the inputs it multiplies, and keeps them in operand registers (up to eight rows one operand holds the high
@@ -12,6 +12,11 @@
 // 131 072 x 2048, 1, 21 rows 88 / 103, 136 / 94, 103.  bild_head_stats where this kernel joins and the host polls, one row: 512 x 16 000 ids 21.7 -> 16.6,
 // 2048 x 32 000 40.3 -> 32.0 (the short workgroups and the merge with the host polling 17.1, 35.7: where they are taken, see head_stats.hip).  Sums against 64 bits as before: rms of lse 4.1e-7, 6.3e-7, 6.4e-7 at 1000,
 // 32 128 and 250 112 ids (4.0e-7, 6.4e-7, 6.3e-7).
+//
+// fp32 models (F32): tiles of sixteen inputs, rows and weights as they are, four fp32 products a tile of sixteen rows, which take a compute unit
+// 32 bytes a clock of weights with up to sixteen rows and 16 with more (19 and 10 TB/s over the chip): the matrix' way from memory still.  A row
+// of 2048 and 4096 inputs takes 64 and 128 registers; 17 rows and more of the latter do not fit.  50 000 ids, 1, 16, 32 rows, short workgroups / now (floor
+// 17, 34, 67 us): 512 wide 34.5, 38.7, 50.1 / 32.0, 34.1, 42.0; 1024 53.6, 58.4, 98.7 / 46.5, 51.2, 59.7; 2048 98, 130, 191 / 86, 89, 106 (more: sweep_groups).
 #include "head.h"
 
 #include <algorithm>
@@ -23,10 +28,11 @@ namespace bild {
 constexpr int kHeadWaves = 8;
 
 // KP: input tiles per wave at most; RW feature tiles per group; U input tiles per batch
-template <int KP, int RW, int U, int NT, bool PACK>
+template <int KP, int RW, int U, int NT, bool PACK, bool F32 = false>
 __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* __restrict__ h_x, const void* __restrict__ h_w, const float* __restrict__ h_gain, const int h_ldx,
                                                                  const int h_tn, const int h_tk, const int h_T, const HeadArgs a0) {
-    constexpr int P = PACK ? 1 : 2, BATCHES = KP / U, UNITS = RW * NT;
+    constexpr int P = PACK || F32 ? 1 : 2, BATCHES = KP / U, UNITS = RW * NT;
+    constexpr int KT = F32 ? 16 : 32, Q = F32 ? 1 : 2;  // inputs of a tile; a lane's, in fours
     static_assert(KP % U == 0 && UNITS <= kHeadWaves && kHeadWaves % NT == 0, "whole batches; a wave keeps one row tile's statistics");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     f32x4* red = (f32x4*)smem;                                    // [wave][RW * NT][64]
@@ -40,7 +46,7 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
 
     // ---- rows and gain requested (JC input tiles at a time, what the registers hold), behind them the first weights ----
     constexpr int JC = KP * NT > 8 ? 4 : KP;
-    float4 xv[JC][NT][2], gv[JC][2];
+    float4 xv[JC][NT][Q], gv[JC][Q];
     const __amdgpu_buffer_rsrc_t xr = make_rsrc(h_x, 0xFFFFFFFFu), gr = make_rsrc(h_gain, 0xFFFFFFFFu);
     auto fetch = [&](int j0) {
 #pragma unroll
@@ -50,10 +56,10 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
             for (int i = 0; i < NT; ++i) {
                 const int row = min(PACK ? tok & 7 : i * 16 + tok, T - 1);
 #pragma unroll
-                for (int p = 0; p < 2; ++p) xv[j][i][p] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(xr, (row * h_ldx + g * 8) * 4, kt * 128 + p * 16, 0));
+                for (int p = 0; p < Q; ++p) xv[j][i][p] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(xr, (row * h_ldx + g * 4 * Q) * 4, kt * (KT * 4) + p * 16, 0));
             }
 #pragma unroll
-            for (int p = 0; p < 2; ++p) gv[j][p] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(gr, g * 32, kt * 128 + p * 16, 0));
+            for (int p = 0; p < Q; ++p) gv[j][p] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(gr, g * 16 * Q, kt * (KT * 4) + p * 16, 0));
         }
     };
     fetch(0);
@@ -83,7 +89,7 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
         if (t < T && ti < *a.ylen_ptr) target = a.y[ti];
     }
     // ---- operands ----
-    bf16x8 X[KP][NT][P];
+    uint4 X[KP][NT][P];
     {
         float ss[NT];
 #pragma unroll
@@ -94,24 +100,29 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
             if (j > 0 && c == 0) fetch(j);
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                float v[8] = {xv[c][i][0].x, xv[c][i][0].y, xv[c][i][0].z, xv[c][i][0].w, xv[c][i][1].x, xv[c][i][1].y, xv[c][i][1].z, xv[c][i][1].w};
-                const float gg[8] = {gv[c][0].x, gv[c][0].y, gv[c][0].z, gv[c][0].w, gv[c][1].x, gv[c][1].y, gv[c][1].z, gv[c][1].w};
+                constexpr int Z = Q - 1;
+                float v[8] = {xv[c][i][0].x, xv[c][i][0].y, xv[c][i][0].z, xv[c][i][0].w, xv[c][i][Z].x, xv[c][i][Z].y, xv[c][i][Z].z, xv[c][i][Z].w};
+                const float gg[8] = {gv[c][0].x, gv[c][0].y, gv[c][0].z, gv[c][0].w, gv[c][Z].x, gv[c][Z].y, gv[c][Z].z, gv[c][Z].w};
                 float sq = 0.f;
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
+                for (int q = 0; q < 4 * Q; ++q) {
                     sq += v[q] * v[q];
                     v[q] = j < n ? v[q] * gg[q] : 0.f;  // (inputs past this wave's last count for nothing)
                 }
                 ss[i] += j < n ? sq : 0.f;
+                if constexpr (F32) {
+                    X[j][i][0] = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+                    continue;
+                }
                 uint32_t hi[4], lo[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) split_bf16x2(v[2 * q], v[2 * q + 1], hi[q], lo[q]);
                 if constexpr (PACK) {
                     const bool low = tok >= 8;
-                    X[j][i][0] = __builtin_bit_cast(bf16x8, make_uint4(low ? lo[0] : hi[0], low ? lo[1] : hi[1], low ? lo[2] : hi[2], low ? lo[3] : hi[3]));
+                    X[j][i][0] = make_uint4(low ? lo[0] : hi[0], low ? lo[1] : hi[1], low ? lo[2] : hi[2], low ? lo[3] : hi[3]);
                 } else {
-                    X[j][i][0] = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
-                    X[j][i][P - 1] = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+                    X[j][i][0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+                    X[j][i][P - 1] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
                 }
             }
         }
@@ -124,6 +135,17 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
     f32x4 acc[RW][NT];
     auto multiply = [&](const uint4 (&W)[U][RW], auto batch) {
         constexpr int B = decltype(batch)::value;
+        if constexpr (F32) {
+            auto part = [](const uint4& v, int q) { return __uint_as_float(q == 0 ? v.x : q == 1 ? v.y : q == 2 ? v.z : v.w); };
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < NT; ++i)
+#pragma unroll
+                        for (int r = 0; r < RW; ++r) acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(part(W[u][r], q), part(X[B * U + u][i][0], q), acc[r][i], 0, 0, 0);
+        } else
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -132,9 +154,10 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
                 for (int p = 0; p < P; ++p)
 #pragma unroll
                     for (int r = 0; r < RW; ++r)
-                        acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, W[u][r]), X[B * U + u][i][p], acc[r][i], 0, 0, 0);
+                        acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, W[u][r]), __builtin_bit_cast(bf16x8, X[B * U + u][i][p]), acc[r][i], 0, 0, 0);
     };
     Stat st = stat_neutral();
+    float lost = 0.f;  // (fp32) of the running sum
     float scale = 1.f;
     bool first = true;
     const int nt = wave % NT, t = nt * 16 + tok;
@@ -158,7 +181,7 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
             for (int w = 0; w < kHeadWaves; ++w) p[w] = rsum[w * 32 + (PACK ? tok & 7 : t)];
 #pragma unroll
             for (int w = 0; w < kHeadWaves; ++w) s += p[w];
-            scale = __builtin_amdgcn_rsqf(s * __builtin_amdgcn_rcpf((float)tk * 32.f) + a.eps);
+            scale = __builtin_amdgcn_rsqf(s * __builtin_amdgcn_rcpf((float)(tk * KT)) + a.eps);
         }
         first = false;
         const int tile = gg * RW + wave / NT;
@@ -192,7 +215,14 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
         float e[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) e[v] = fexp_full(z[v] - base);
-        st.s = st.s * fexp_full(st.m - base) + ((e[0] + e[1]) + (e[2] + e[3]));
+        const float f = fexp_full(st.m - base), add = (e[0] + e[1]) + (e[2] + e[3]);
+        if constexpr (F32) {  // (a sum of as many groups: what an addition loses goes into the next)
+            const float y = add - lost * f, kept = st.s * f, sum = kept + y;
+            lost = (sum - kept) - y;
+            st.s = sum;
+        } else {
+            st.s = st.s * f + add;
+        }
         st.m = m;
     };
     if constexpr (BATCHES == 1) {  // a group per batch
@@ -209,7 +239,7 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
             join(grp + step);
         }
     } else {
-        static_assert(BATCHES == 1 || BATCHES == 2 || BATCHES == 4, "two buffers");
+        static_assert(BATCHES == 1 || BATCHES == 2 || BATCHES == 4 || BATCHES == 8, "two buffers");
 #pragma unroll 1
         for (; grp < groups; grp += step) {
             clear();
@@ -217,16 +247,27 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
             ask(W0, grp, 2);
             multiply(W1, std::integral_constant<int, 1 % BATCHES>{});
             ask(W1, grp, 3);
-            if constexpr (BATCHES == 4) {
+            if constexpr (BATCHES >= 4) {
                 multiply(W0, std::integral_constant<int, 2 % BATCHES>{});
                 ask(W0, grp, 4);
                 multiply(W1, std::integral_constant<int, 3 % BATCHES>{});
                 ask(W1, grp, 5);
             }
+            if constexpr (BATCHES == 8) {
+                multiply(W0, std::integral_constant<int, 4 % BATCHES>{});
+                ask(W0, grp, 6);
+                multiply(W1, std::integral_constant<int, 5 % BATCHES>{});
+                ask(W1, grp, 7);
+                multiply(W0, std::integral_constant<int, 6 % BATCHES>{});
+                ask(W0, grp, 8);
+                multiply(W1, std::integral_constant<int, 7 % BATCHES>{});
+                ask(W1, grp, 9);
+            }
             join(grp);
         }
     }
     // ---- the workgroup's partials ----
+    if constexpr (F32) st.s -= lost;
     {  // lanes of a row
         Stat x, y;
         uint32_t p, q;
@@ -276,30 +317,34 @@ __global__ __launch_bounds__(64 * kHeadWaves, 1) void head_kernel(const float* _
 }
 
 // Feature tiles per group: as many as the registers hold, unless fewer leave less to the last round of groups.
-static int head_tiles(const TMat& W, int T) {
-    const int per = (W.tk + kHeadWaves - 1) / kHeadWaves, most = per <= 4 ? 4 : 2;
-    if (per > 8) return 0;  // (wider rows do not fit the registers beside the weights: 4096 x 65 536 ids 138 us for 8 rows against 119)
+static int head_tiles(const TMat& W, int T, bool f32) {
+    const int per = (W.tk + kHeadWaves - 1) / kHeadWaves, most = per <= 4 ? 4 : f32 && (per > 16 || (per > 8 && T > 16)) ? 1 : 2;
+    if (f32 ? per > (T > 16 ? 16 : 32) : per > 8) return 0;  // (wider rows do not fit the registers beside the weights: 4096 x 65 536 ids 138 us for 8 rows against 119)
     int best = most;
     auto rounds = [&](int rw) { return ((W.tn + rw - 1) / rw + 255) / 256 * rw; };
     for (int rw = most; rw >= 1; rw /= 2)
         if (rounds(rw) < rounds(best)) best = rw;
     return best;
 }
-int head_groups(const TMat& W, int T) {
-    const int rw = head_tiles(W, T);
+int head_groups(const TMat& W, int T, bool f32) {
+    const int rw = head_tiles(W, T, f32);
     return rw ? std::min((W.tn + rw - 1) / rw, 256) : 0;
 }
 
 // (input tiles per wave, feature tiles, input tiles per batch)
 #define BILD_HEAD_EACH(X) X(2, 4, 2) X(2, 2, 2) X(2, 1, 2) X(4, 4, 2) X(4, 2, 2) X(4, 1, 4) X(8, 2, 4) X(8, 1, 4)
+// (fp32 models: tiles of sixteen inputs)
+#define BILD_HEAD_F32(X) X(16, 2, 4) X(16, 1, 4) X(32, 1, 4)
 
 hipError_t head_init() {
     static hipError_t done = [] {
 #define BILD_F(KPV, RWV, UV) (const void*)head_kernel<KPV, RWV, UV, 1, true>, (const void*)head_kernel<KPV, RWV, UV, 1, false>,
 #define BILD_F2(KPV, RWV, UV) (const void*)head_kernel<KPV, RWV, UV, 2, false>,
-        const void* fns[] = {BILD_HEAD_EACH(BILD_F) BILD_HEAD_EACH(BILD_F2)};
+#define BILD_F3(KPV, RWV, UV) (const void*)head_kernel<KPV, RWV, UV, 1, false, true>, (const void*)head_kernel<KPV, RWV, UV, KPV * RWV >= 32 ? 1 : 2, false, true>,
+        const void* fns[] = {BILD_HEAD_EACH(BILD_F) BILD_HEAD_EACH(BILD_F2) BILD_HEAD_EACH(BILD_F3) BILD_HEAD_F32(BILD_F3)};
 #undef BILD_F
 #undef BILD_F2
+#undef BILD_F3
         return raise_lds_limit(fns, 160 * 1024);
     }();
     return done;
@@ -307,14 +352,24 @@ hipError_t head_init() {
 
 hipError_t launch_head(const HeadArgs& a, hipStream_t st) {
     if (hipError_t e = head_init(); e != hipSuccess) return e;
-    const int rw = head_tiles(a.W, a.T), per = (a.W.tk + kHeadWaves - 1) / kHeadWaves, kp = per <= 2 ? 2 : per <= 4 ? 4 : 8;
+    const int rw = head_tiles(a.W, a.T, a.f32), per = (a.W.tk + kHeadWaves - 1) / kHeadWaves, kp = per <= 2 ? 2 : per <= 4 ? 4 : per <= 8 ? 8 : per <= 16 ? 16 : 32;
     if (!rw || a.T < 1 || a.T > kMaxRows || !a.x || !a.gain || !a.part || !a.zt || !a.y || !a.ylen_ptr || a.ldx < a.W.k || a.ldx % 4 || (a.out && !a.arrived) ||
-        a.part_ld < head_groups(a.W, a.T) || (size_t)a.part_ld * sizeof(StatPart) * kMaxRows >= (size_t)1 << 31)
+        a.part_ld < head_groups(a.W, a.T, a.f32) || (size_t)a.part_ld * sizeof(StatPart) * kMaxRows >= (size_t)1 << 31)
         return hipErrorInvalidValue;
     const int nt = a.T > 16 ? 2 : 1;
     const size_t smem = (size_t)kHeadWaves * (rw * nt * 1024 + 32 * 4 + 16 * sizeof(StatPart)) + 16;
-    const dim3 grid(head_groups(a.W, a.T)), block(64 * kHeadWaves);
+    const dim3 grid(head_groups(a.W, a.T, a.f32)), block(64 * kHeadWaves);
 #define BILD_L(KPV, RWV, UV, NTV, PV) hipLaunchKernelGGL((head_kernel<KPV, RWV, UV, NTV, PV>), grid, block, smem, st, a.x, a.W.w, a.gain, a.ldx, a.W.tn, a.W.tk, a.T, a)
+#define BILD_X3(KPV, RWV, UV)                                                                                                                                      \
+    if (kp == KPV && rw == RWV) {                                                                                                                                  \
+        if (nt == 1) hipLaunchKernelGGL((head_kernel<KPV, RWV, UV, 1, false, true>), grid, block, smem, st, a.x, a.W.w, a.gain, a.ldx, a.W.tn, a.W.tk, a.T, a);     \
+        else hipLaunchKernelGGL((head_kernel<KPV, RWV, UV, KPV * RWV >= 32 ? 1 : 2, false, true>), grid, block, smem, st, a.x, a.W.w, a.gain, a.ldx, a.W.tn, a.W.tk, a.T, a); \
+        return hipGetLastError();                                                                                                                                  \
+    }
+    if (a.f32) {
+        BILD_HEAD_EACH(BILD_X3) BILD_HEAD_F32(BILD_X3)
+        return hipErrorInvalidValue;
+    }
 #define BILD_X(KPV, RWV, UV)                              \
     if (kp == KPV && rw == RWV && nt == 1) {              \
         if (a.T <= 8) BILD_L(KPV, RWV, UV, 1, true);      \

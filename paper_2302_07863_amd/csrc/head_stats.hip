@@ -141,6 +141,7 @@ int head_sweep_run(const bild_model* m, const float* x, int rows, const int32_t*
     h.x = x;
     h.ldx = m->cfg.d_model;
     h.T = rows;
+    h.f32 = m->cfg.dtype == BILD_DT_F32;
     h.gain = g.gain;
     h.eps = g.eps;
     h.scale = g.scale;
@@ -172,12 +173,19 @@ int head_sweep_run(const bild_model* m, const float* x, int rows, const int32_t*
 // 2048 wide 32.7 / 27.7, 25.6 / 26.8, 28.2 / 26.8 and 41.2 / 33.0, 33.6 / 32.7, 35.7 / 32.3.  Two, four, eight rows: 512 x 64 000 20.7, 20.7, 21.2 / 18.3, 18.6,
 // 18.7; 1024 x 16 000 10.7, 11.4, 13.0 / 10.3, 10.8, 11.8; x 32 128 16.8, 17.1, 17.8 / 18.0, 18.2, 19.1; 2048 x 7809 11.4, 12.5, 14.7 / 11.5, 12.4, 13.8; x 16 000 17.4,
 // 17.4, 20.9 / 18.3, 19.2, 20.6.  From nine rows on the sweep is never slower.
+// fp32, a call that waits, 1, 8, 16, 32 rows: 512 x 50 000 34.5, 36.3, 38.7, 50.1 / 32.0, 32.1, 34.1, 42.0; x 250 112 119, 123, 124, 157 / 102, 102, 104, 116; 1024 x 4000
+// 20.7, 20.4, 22.4, 26.1 / 18.4, 19.6, 21.2, 24.1; x 50 000 53.6, 51.4, 58.4, 98.7 / 46.5, 47.7, 51.2, 59.7; 2048 x 1000 20.1, 22.2, 24.2, 31.7 / 18.3, 19.6, 23.7, 28.8; x 4000
+// 20.6, 22.9, 25.4, 32.6 / 21.8, 22.7, 25.9, 30.2; x 16 000 38.6, 40.4, 51.5, 73.7 / 38.2, 40.1, 45.1, 49.9 (four rows 36.4 / 39.4); x 50 000 98, 101, 130, 191 / 86, 87, 89, 106;
+// 4096 x 4000, 1, 8, 16 rows 33.4, 34.4, 39.3 / 37.0, 38.1, 42.0; x 16 000 55.4, 68.3, 81.4 / 67.3, 67.9, 72.0; x 50 000 179, 204, 229 / 173, 172, 178.
 int sweep_groups(const bild_model* m, int rows) {
-    if (m->cfg.dtype != BILD_DT_BF16) return 0;
     const int tk = m->head.tk;
     const size_t mb = ((size_t)m->head.tn * tk * kTileBytes) >> 20;
+    if (m->cfg.dtype != BILD_DT_BF16) {
+        const bool f32_taken = tk <= 64 || (tk <= 128 ? rows > 8 || mb < 16 || mb >= 200 : mb >= (rows > 8 ? 128u : 400u));
+        return f32_taken ? head_groups(m->head, rows, true) : 0;
+    }
     const bool taken = rows > 8 || mb >= 96 || (rows > 1 ? mb < 48 || tk <= 16 : mb < (tk > 32 ? 8u : 24u));
-    return taken ? head_groups(m->head, rows) : 0;
+    return taken ? head_groups(m->head, rows, false) : 0;
 }
 
 bool all_done(const unsigned* done, unsigned call, int rows) {

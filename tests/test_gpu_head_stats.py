@@ -105,11 +105,13 @@ def test_merge_of_many_partials_is_exact_to_the_sums_rounding():
     assert np.abs(err).max() < 4.4e-7
 
 
-@pytest.mark.parametrize("d,vocab", [(64, 17), (512, 4100), (1056, 1030), (2048, 9000), (512, 66000), (4096, 600)])
-def test_sweep_shapes(d, vocab):
+@pytest.mark.parametrize("d,vocab,dtype", [(64, 17, bi.DT_BF16), (512, 4100, bi.DT_BF16), (1056, 1030, bi.DT_BF16), (2048, 9000, bi.DT_BF16), (512, 66000, bi.DT_BF16),
+                                           (4096, 600, bi.DT_BF16), (64, 17, bi.DT_F32), (256, 33000, bi.DT_F32), (512, 4100, bi.DT_F32), (1024, 9000, bi.DT_F32),
+                                           (1056, 1030, bi.DT_F32), (2048, 9000, bi.DT_F32), (2112, 8300, bi.DT_F32), (4096, 8300, bi.DT_F32)])
+def test_sweep_shapes(d, vocab, dtype):
     """Input tiles per wave (none for some waves, a short last one), feature tiles per group, several groups per workgroup, both
     entry points: the same results from a launch that joins and from one that does not."""
-    cfg = bi.toy_pair(dtype=bi.DT_BF16, d=d, vocab=vocab, n_large=1)
+    cfg = bi.toy_pair(dtype=dtype, d=d, vocab=vocab, n_large=1)
     _, wl = bi.make_pair_weights(cfg)
     shape = cfg.large
     model = parity.make_gpu_model(shape, wl)
