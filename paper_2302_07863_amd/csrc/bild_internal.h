@@ -434,7 +434,7 @@ struct TileGemmArgs {
 int tile_gemm_parts(const TileGemmArgs& a);
 hipError_t launch_gemm_tile(const TileGemmArgs& a, hipStream_t st);
 hipError_t launch_embed_tiles(const EmbedArgs& a, char* np, hipStream_t st);
-// row copy (see RowCopyArgs) that also leaves the rows' planes times `gain` and their sums of squares
+// row copy (see RowCopyArgs; dst null: no copy) that also leaves the rows' planes times `gain` and their sums of squares
 hipError_t launch_row_tiles(const RowCopyArgs& a, const float* gain, char* np, float* ssq, hipStream_t st);
 hipError_t launch_rope_table(double2* table, int positions, int d_head, float base, hipStream_t st);
 hipError_t launch_attention_tile(const AttnArgs& a, hipStream_t st);  // bf16 models, output as tile planes (attn_tile.hip)

@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256) void row_tile_kernel(const RowCopyArgs a, cons
     float ss = 0.f;
     for (int i = tid; i < a.d / 4; i += 256) {
         const float4 v = src[i], g = *(const float4*)(gain + i * 4);
-        dst[i] = v;
+        if (a.dst) dst[i] = v;
         ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
         const float w[4] = {v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w};
         put_tile_planes(np, np_tk, t, i * 4, w);

@@ -13,6 +13,7 @@
 #include <cstring>
 
 #include "bild_state.h"
+#include "gemm_thin.h"
 #include "head.h"
 #include "kernel_common.h"
 
@@ -20,7 +21,7 @@ using namespace bild;
 
 namespace {
 
-// Scratch layout (bytes): [0, 256) workgroups that have arrived (pool buffers: zero between calls); [256, 512) logits of the targets, one float per row; [512, ...) partial statistics,
+// Scratch layout (bytes): [0, 256) workgroups that have arrived (pool buffers: zero between calls); [256, 512) logits of the targets, one float per row, and the rows' sums of squares; [512, ...) partial statistics,
 // StatPart[rows][workgroups].
 constexpr size_t kHdrBytes = 512;
 constexpr size_t kStaticScratchBytes = (size_t)4 << 20;  // 4 MiB
@@ -165,6 +166,50 @@ int head_sweep_run(const bild_model* m, const float* x, int rows, const int32_t*
     }
     return BILD_OK;
 }
+// Rows wider than the sweep's registers hold: as tile planes, for the thin GEMM (gemm_thin.hip), which has them on their way beside the weights, where every
+// short workgroup stages all of them.  A launch more, so from five rows on.  us, a call that waits, short workgroups / this, 5, 9, 16, 20, 32 rows: 4096 x 4000
+// 24.9, 28.2, 36.7, 36.5, 52.6 / 22.6, 24.4, 28.7, 28.8, 30.7; x 16 000 49.3, 43.6, 66.5, 80.9, 102 / 43.9, 45.8, 41.7, 45.5, 48.0; x 50 000 121, 104 to 110, 158, 196, 234 / 104, 108, 113, 114,
+// 120 (nine rows of 4096 inputs alone are as fast either way: ten 139 / 107); 2112 x 50 000, 5, 9, 20 rows 55, 78, 118 / 52, 54, 60; 3072 76, 101, 147 / 72, 73, 83; 5120 143, 155, 236 / 118,
+// 122, 131.  Eight rows and less of 8 MB the same, one and four rows of any size 0 to 10 % slower.
+bool takes_planes(const bild_model* m, int rows) {
+    if (m->cfg.dtype != BILD_DT_BF16 || m->head.tk <= 64) return false;
+    return rows > 8 || (rows > 4 && (size_t)m->head.tn * m->head.tk * kTileBytes >= (size_t)16 << 20);
+}
+// (behind `parts` workgroups' partial statistics)
+size_t planes_at(int rows, int parts) { return (kHdrBytes + (size_t)parts * rows * sizeof(StatPart) + 1023) / 1024 * 1024; }
+ThinArgs planes_head(const bild_model* m, int rows, const GemmArgs& g, void* scr) {
+    ThinArgs a;
+    std::memset((void*)&a, 0, sizeof(a));
+    a.W = m->head;
+    a.T = rows;
+    a.epi = EPI_LMHEAD;
+    a.part_ld = thin_shape(m->head, EPI_LMHEAD, 0, rows).groups;
+    a.xp = (const char*)scr + planes_at(rows, a.part_ld);
+    a.ssq = (const float*)((const char*)scr + 384);
+    a.ssq_parts = 1;
+    a.eps = g.eps;
+    a.scale = g.scale;
+    a.vocab = g.vocab;
+    a.y = g.y;
+    a.ylen_ptr = g.ylen_ptr;
+    a.part = g.part;
+    a.zt = g.zt;
+    return a;
+}
+size_t planes_scratch(const bild_model* m, int rows, int parts) { return planes_at(rows, parts) + plane_bytes(rows, (size_t)m->head.tk * 32); }
+int head_planes_run(const bild_model* m, const float* x, int rows, const int32_t* targets, bild_row_stats* out, hipStream_t st, const ThinArgs& a, unsigned* done, unsigned call) {
+    RowCopyArgs r;
+    std::memset((void*)&r, 0, sizeof(r));
+    r.src = x;
+    r.d = m->cfg.d_model;
+    r.T = rows;
+    HIPC(launch_row_tiles(r, m->dec_final, const_cast<char*>(a.xp), const_cast<float*>(a.ssq), st));
+    HIPC(launch_gemm_thin(a, st));
+    const MergeArgs ma = {a.part, a.part_ld, a.zt, targets, m->cfg.vocab, out, done, call};
+    hipLaunchKernelGGL(head_stats_merge_kernel, dim3(rows), dim3(256), 0, st, ma);
+    HIPC(hipGetLastError());
+    return BILD_OK;
+}
 // Its workgroups; 0: the GEMM's short workgroups and the merge.  One rule for both entry points, whose results are the same bits.  Up to eight
 // rows of matrices of 50 MB or so are the short workgroups', of which more are on a compute unit when weights begin to arrive.  us, short
 // workgroups / sweep, a call that does not wait and one that does (there the sweep joins its results itself), one row: 512 x 16 000 ids
@@ -218,13 +263,14 @@ int check_args(const bild_model* m, const float* x, int rows, bild_row_stats* ou
 extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows, const int32_t* targets_dev,
                                bild_row_stats* out_dev, void* hip_stream) {
     if (int rc = check_args(m, x_dev, rows, out_dev)) return rc;
-    if (gemm_init() != hipSuccess || head_init() != hipSuccess) return BILD_EHIP;
+    if (gemm_init() != hipSuccess || head_init() != hipSuccess || gemm_thin_init() != hipSuccess) return BILD_EHIP;
     hipStream_t st = (hipStream_t)hip_stream;
     void* slots = nullptr;
     if (int rc = of_device(g_counts_ptr, HIP_SYMBOL(counts), &slots)) return rc;
     GemmArgs g = head_gemm(m, x_dev, rows, targets_dev, nullptr, (const int*)slots);
     const int groups = sweep_groups(m, rows);
-    const size_t bytes = kHdrBytes + (size_t)std::max(g.part_ld, groups) * sizeof(StatPart) * rows;
+    const bool planes = takes_planes(m, rows);
+    const size_t bytes = std::max(kHdrBytes + (size_t)std::max(g.part_ld, groups) * sizeof(StatPart) * rows, planes ? planes_scratch(m, rows, thin_shape(m->head, EPI_LMHEAD, 0, rows).groups) : 0);
     HeadScratch b = m->head_pool.take(bytes, st);
     if (!b.p) return BILD_ENOMEM;
     g.zt = (float*)((char*)b.p + 256);
@@ -232,8 +278,9 @@ extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows
     // (one row per wave of the last workgroup: more are joined sooner by a launch of a workgroup each; 512 x 32 128 ids, 1, 8, 16, 32
     // rows: 22.2, 23.0, 25.0, 29.9 us joined in the sweep, 22.9, 23.3, 23.6, 25.4 by a launch)
     b.calls += 1;
-    int rc = groups ? head_sweep_run(m, x_dev, rows, targets_dev, out_dev, st, g, groups, rows <= 8, b.done_dev, b.calls)
-                    : head_stats_run(m, rows, targets_dev, out_dev, st, g, b.done_dev, b.calls);
+    int rc = planes   ? head_planes_run(m, x_dev, rows, targets_dev, out_dev, st, planes_head(m, rows, g, b.p), b.done_dev, b.calls)
+             : groups ? head_sweep_run(m, x_dev, rows, targets_dev, out_dev, st, g, groups, rows <= 8, b.done_dev, b.calls)
+                      : head_stats_run(m, rows, targets_dev, out_dev, st, g, b.done_dev, b.calls);
     // the scratch is in use until here
     const bool seen = rc == BILD_OK && b.done && rows_done(b.done, b.calls, rows);
     if (!seen && hipStreamSynchronize(st) != hipSuccess && rc == BILD_OK) rc = BILD_EHIP;
@@ -246,12 +293,16 @@ extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows
 extern "C" int bild_head_stats_static(const bild_model* m, const float* x_dev, int rows, const int32_t* targets_dev,
                                       bild_row_stats* out_dev, void* hip_stream) {
     if (int rc = check_args(m, x_dev, rows, out_dev)) return rc;
-    if (gemm_init() != hipSuccess || head_init() != hipSuccess) return BILD_EHIP;
+    if (gemm_init() != hipSuccess || head_init() != hipSuccess || gemm_thin_init() != hipSuccess) return BILD_EHIP;
     void *scr = nullptr, *slots = nullptr;
     if (int rc = of_device(g_scratch_ptr, HIP_SYMBOL(scratch), &scr)) return rc;
     if (int rc = of_device(g_counts_ptr, HIP_SYMBOL(counts), &slots)) return rc;
     const GemmArgs g = head_gemm(m, x_dev, rows, targets_dev, scr, (const int*)slots);
     if (g.part_ld > kStaticMaxParts) return BILD_ECAP;  // more partial statistics than the array holds
+    if (takes_planes(m, rows)) {
+        const ThinArgs a = planes_head(m, rows, g, scr);
+        if (planes_scratch(m, rows, a.part_ld) <= kStaticScratchBytes) return head_planes_run(m, x_dev, rows, targets_dev, out_dev, (hipStream_t)hip_stream, a, nullptr, 0);
+    }
     // (calls that overlap on a GPU share the scratch: a count left wrong by them would outlast them)
     if (const int groups = sweep_groups(m, rows)) return head_sweep_run(m, x_dev, rows, targets_dev, out_dev, (hipStream_t)hip_stream, g, groups, false, nullptr, 0);
     return head_stats_run(m, rows, targets_dev, out_dev, (hipStream_t)hip_stream, g, nullptr, 0);
