@@ -451,6 +451,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (s->one_kernel && in_int && bf16 && !m->cfg.cross_attn && m->cfg.pos != BILD_POS_RELATIVE && !M.pass_groups) {
             M.pass_groups = wide_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus);
             M.pass_wide = M.pass_groups > 0;
+            if (M.pass_wide) M.pass_wide_rows = wide_rows((int)d, m->cfg.n_heads, (int)F, m->gated(), s->cus);
         }
         M.nparts_cap = m->head.tn + 1;  // at most one partial per feature tile
         want(M.part, sizeof(StatPart) * (size_t)M.nparts_cap * kMaxRows);
@@ -471,7 +472,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     // passes in one kernel: what both models' hand over, one behind the other, and their layers
     size_t turns_bytes = 0, layers_n = 0;
     for (ModelState& M : s->ms)
-        for (int r = 0; M.pass_groups && r <= (M.pass_wide ? pass_room_index(kWideRows) : kPassRooms - 1); ++r) {
+        for (int r = 0; M.pass_groups && r <= (M.pass_wide ? pass_room_index(M.pass_wide_rows) : kPassRooms - 1); ++r) {
             want(M.pass_turns[r], pass_turns_bytes(M, r));
             turns_bytes += wants.back().bytes;
         }
@@ -1471,6 +1472,17 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         }
         HIPC(M.pass_wide ? launch_wide(p, s->stream) : launch_pass(p, inside ? &in : nullptr, die ? s->cus : p.groups, s->stream));
         if (inside) return BILD_OK;
+        // (rows wider than the sweep of the vocabulary takes, from five on: as tile planes for the thin GEMM, see takes_planes in head_stats.hip)
+        if (lm_rows > 4 && d > 2048 && dt == BILD_DT_BF16) {
+            RowCopyArgs r;
+            std::memset((void*)&r, 0, sizeof(r));
+            r.src = M.x;
+            r.d = d;
+            r.T = T;
+            s->stage_count += 1;
+            HIPC(launch_row_tiles(r, m->dec_final, (char*)M.xb, M.ssq, s->stream));
+            thin_parts = 1;
+        }
     } else if (takes_thin(s, w, T)) {
         const int rc = emit_thin(s, w, T, key_hint, lm_rows > 0, &thin_parts);
         if (rc) return rc;
@@ -1621,7 +1633,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // 660, 681: never slower up to the 8192 positions that were measured.
 static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
-    if (s->ms[w].pass_wide) return s->one_kernel && T <= kWideRows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= 8192;
+    if (s->ms[w].pass_wide) return s->one_kernel && T <= s->ms[w].pass_wide_rows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= 8192;
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
            s->n_src <= (s->ms[w].m->cfg.dtype == BILD_DT_F32 ? 1024 : on_one_die(s, w, T) ? 1280 : T == 1 ? 1408 : 1536) && s->len[w] + T <= 1024;
 }

@@ -296,10 +296,11 @@ void pass_head_plan(PassHead& h, const PassPlan& at, int d, bool f32, int cus); 
 PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide);
 // head null: LM head and policy follow as kernels
 hipError_t launch_pass(const PassArgs& a, const PassHead* head, int grid, hipStream_t st);
-constexpr int kWideRows = 8, kWideHead = 128;  // most rows; features of a head
+constexpr int kWideRows = 8, kWideRowsMost = 16, kWideHead = 128;  // most rows (wide_rows); features of a head
 constexpr int kWideSplits = 8;                 // most key ranges of a head
 constexpr int kWideApart = 1280;               // most keys with which heads and projections are different workgroups'
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // as pass_groups, of pass_wide.hip
+int wide_rows(int d, int heads, int F, bool gated, int cus);
 bool wide_two(int d, int heads, int F, bool gated, int cus, int keys);
 // who does what in a pass that ends with `keys` keys (wide_parts): {tiles of q, k, v a workgroup, its first workgroup, the same of the FFN's
 // input, the heads' first workgroup, ranges, apart}; false: not a shape it is made for

@@ -229,6 +229,7 @@ struct ModelState {
     int pass_groups = 0;      // workgroups; 0: the shape is not made for it
     int pass_die_groups = 0;  // the same of the form on one die
     bool pass_wide = false;   // the form of pass_wide.hip
+    int pass_wide_rows = 0;   // most rows there
     bild::PassLayer* pass_layers = nullptr;  // device
     int pass_die_rows = 0;    // most rows there (the small model's passes with an LM head have one)
     char* pass_turns[bild::kPassRooms] = {};  // what its workgroups hand over, by the rows there is room for

@@ -1,5 +1,5 @@
 // One decoder pass of a wide bf16 model without cross-attention (above 1024 and up to 4096 wide, heads of 128) in ONE kernel, up to
-// eight rows: pass_kernel.hip's way of handing results over (its head explains it; nothing is counted, results are their own flags),
+// eight rows, or sixteen (wide_rows): pass_kernel.hip's way of handing results over (its head explains it; nothing is counted, results are their own flags),
 // for layers of 60 to 400 MB.
 //
 // Bound: the weights from memory.  As kernels of their own the six stages of a layer each end with a few microseconds in which the
@@ -24,6 +24,10 @@
 // the 6.1 TB/s of a large copy.  Heads and projections apart, up to 1280 keys (see wide_kernel), before / with: 457, 461, 480, 514 / 442,
 // 444, 462, 500; a load of several tiles' activations for one and two rows (run_few) 442, 444 / 437, 443 and at 200 positions 413, 420 /
 // 409, 413.
+// Nine to sixteen rows have high and low parts in operands of their own, twice the activations and products; the weights still take longer.  The 7B shape, nine, sixteen
+// rows over 64, 1024, 4097 tokens, separate kernels / this, us: 3305, 3311, 3463, 3473, 3770, 3779 / 2837, 2843, 2918, 2927, 3239, 3246 (eight rows 2591, 2680, 2993); six
+// layers of 2304 (without gate), 2560, 3072, 4096 (without gate) and of 1536 with a hidden state of 8192, twelve rows over 64 and 8100 tokens 336, 410, 452, 522, 387 and 501, 576, 618, 703, 458 / 338, 381, 415,
+// 474, 322 and 466, 528, 582, 675, 424.
 #include "pass_walk.h"
 
 namespace bild {
@@ -44,6 +48,9 @@ __device__ __forceinline__ uint4 lanes_on(const uint4& v, int j) {
 template <int ROOM>
 struct WideWalk : Walk<false, false, ROOM> {
     static constexpr bool ROOM1 = false;
+    static constexpr bool PACKED = ROOM <= 8;  // high and low parts in one operand (multiply() in pass_walk.h); above eight rows one each
+    static constexpr int P = PACKED ? 1 : 2;
+    __device__ __forceinline__ int row() const { return PACKED ? this->t8 : this->t; }
 };
 
 // A projection's weights on their way: N input tiles per wave at most, RW feature tiles, in pieces of CH input tiles of which two
@@ -85,32 +92,36 @@ struct Stream {
         ask(c.lane, W[0], a, 0);
         if constexpr (NC > 1) ask(c.lane, W[1], a, 1);
     }
-    // acc = W x over this wave's inputs, up to eight rows packed (see multiply() in pass_walk.h)
+    // acc = W x over this wave's inputs
     template <class Walk>
     __device__ __forceinline__ void run(Walk& c, f32x4 (&acc)[RW], const void* planes, const void* weights, int first, int tk, int end) {
         const Where a = where(c.wave, weights, first, tk, end);
         const int k0 = a.k0, n = a.n;
         const Rsrc xs = whole(planes);
-        if constexpr (Walk::KNOWN > 0) return run_few(c, acc, xs, a);
-        const int S = tile_bytes(NORM, c.R, false), at = ((c.g * 2 + (c.tok >> 3)) * c.R + c.t8) * 16;
-        uint4 X[NC > 1 ? 2 : 1][CH];
+        if constexpr (Walk::KNOWN == 1 || Walk::KNOWN == 2) return run_few(c, acc, xs, a);
+        constexpr int P = Walk::P;
+        const int S = tile_bytes(NORM, c.R, false), at = (Walk::PACKED ? (c.g * 2 + (c.tok >> 3)) * c.R + c.row() : c.g * c.R + c.row()) * 16;
+        uint4 X[NC > 1 ? 2 : 1][CH * P];
         v2u sq[NC > 1 ? 2 : 1][SQ];
         float ss = 0.f;
-        auto get = [&](uint4 (&x)[CH], v2u (&s)[SQ], int i) {
+        auto get = [&](uint4 (&x)[CH * P], v2u (&s)[SQ], int i) {
 #pragma unroll
             for (int j = 0; j < CH; ++j)
-                if (i * CH + j < N) x[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at, (k0 + min(i * CH + j, max(n - 1, 0))) * S, Walk::kIn));
+                if (i * CH + j < N) {
+#pragma unroll
+                    for (int p = 0; p < P; ++p) x[P * j + p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at + p * c.R * 64, (k0 + min(i * CH + j, max(n - 1, 0))) * S, Walk::kIn));
+                }
             if constexpr (NORM) {  // (lane group g: tiles g, g + 4 of the piece)
 #pragma unroll
                 for (int u = 0; u < SQ; ++u)
-                    s[u] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, min(i * CH + u * 4 + c.g, max(n - 1, 0)) * S + c.R * 128 + c.t8 * 8, k0 * S, Walk::kIn));
+                    s[u] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, min(i * CH + u * 4 + c.g, max(n - 1, 0)) * S + c.R * 128 + c.row() * 8, k0 * S, Walk::kIn));
             }
         };
-        auto missing = [&](const uint4 (&x)[CH], const v2u (&s)[SQ], int i) {
+        auto missing = [&](const uint4 (&x)[CH * P], const v2u (&s)[SQ], int i) {
             unsigned m = 0u;
 #pragma unroll
-            for (int j = 0; j < CH; ++j)
-                if (i * CH + j < N) m = max(max(m, max(x[j].x, x[j].y)), max(x[j].z, x[j].w));
+            for (int j = 0; j < CH * P; ++j)
+                if (i * CH + j / P < N) m = max(max(m, max(x[j].x, x[j].y)), max(x[j].z, x[j].w));
             if constexpr (NORM) {
 #pragma unroll
                 for (int u = 0; u < SQ; ++u) m = max(m, max(s[u].x, s[u].y));
@@ -122,7 +133,7 @@ struct Stream {
         get(X[0], sq[0], 0);
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            uint4 (&x)[CH] = X[i & 1];
+            uint4 (&x)[CH * P] = X[i & 1];
             v2u (&s)[SQ] = sq[i & 1];
             // (the first look apart: the wait of a loop would be for everything requested since)
             if (__builtin_expect(missing(x, s, i), 0)) {
@@ -143,7 +154,9 @@ struct Stream {
             for (int j = 0; j < CH; ++j)
                 if (i * CH + j < N && i * CH + j < n) {
 #pragma unroll
-                    for (int q = 0; q < RW; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[i & 1][j * RW + q]), as_bf(x[j]), acc[q], 0, 0, 0);
+                    for (int p = 0; p < P; ++p)
+#pragma unroll
+                        for (int q = 0; q < RW; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[i & 1][j * RW + q]), as_bf(x[P * j + p]), acc[q], 0, 0, 0);
                 }
             if constexpr (NORM) {
 #pragma unroll
@@ -296,7 +309,8 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
     extern __shared__ __attribute__((aligned(16))) char smem[];
     using Way = WideWalk<ROOM>;
     constexpr int QT = Cut::QT, FT = Cut::FT, DH = kWideHead;
-    constexpr bool EARLY = Cut::EARLY;
+    constexpr bool EARLY = Cut::EARLY, PACK = Way::PACKED;
+    constexpr int P = Way::P;
     Way c;
     c.lds = smem;
     c.failed = a.sync + kPassSyncWords - 1;
@@ -326,7 +340,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         if (!mine) return;
         const float w[4] = {x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w};
         const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
-        put_planes<true, true>(c, planes, n0(), w);
+        put_planes<PACK, true>(c, planes, n0(), w);
         if (c.g == 0) {
             const int off = (n0() >> 5) * tile_bytes(true, c.R, false) + c.R * 128 + (c.tok * 2 + ((n0() >> 4) & 1)) * 4;
             if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(planes), off, 0, Way::kOut);
@@ -334,7 +348,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         }
     };
     auto add = [&] {
-        const f32x4 s = total<1, true, false>(c, 0);
+        const f32x4 s = total<1, PACK, false>(c, 0);
         x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]);
     };
     typename Cut::Qkv sq;
@@ -387,7 +401,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
             leave<QT, true, false>(c, acc);
             if (q0 + c.wave < q1) {
                 const float f = norm_factor(c, d, a.eps);
-                f32x4 s = total<QT, true, false>(c, c.wave) * f;
+                f32x4 s = total<QT, PACK, false>(c, c.wave) * f;
                 const int seg = nf / I, nn = nf - seg * I, pos = len + c.tok, hd = nn / DH, f0 = nn % DH;
                 if (a.rope && seg < 2) {
 #pragma unroll
@@ -465,7 +479,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                         unsigned m = 0u;
                         auto see = [&](const uint4& v) { m = max(max(m, max(v.x, v.y)), max(v.z, v.w)); };
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) qv[i >> 1][i & 1] = ldf4<Way::kIn>(fq, c.t8 * DH * 4 + (i >> 1) * 128 + c.g * 32 + (i & 1) * 16);
+                        for (int i = 0; i < 8; ++i) qv[i >> 1][i & 1] = ldf4<Way::kIn>(fq, c.row() * DH * 4 + (i >> 1) * 128 + c.g * 32 + (i & 1) * 16);
                         if (fresh) {
 #pragma unroll
                             for (int ks = 0; ks < 4; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fk, c.t * DH * 2 + ks * 64 + c.g * 16, 0, Way::kIn));
@@ -482,20 +496,25 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                     } while (missing && ++tries < c.spins);
                     if (missing) c.give_up();
                 };
-                auto parts = [&](const float (&v)[8]) {  // high parts in columns 0 .. 7, low parts in 8 .. 15
+                auto parts = [&](const float (&v)[8], bf16x8 (&o)[P]) {  // packed: high parts in columns 0 .. 7, low parts in 8 .. 15
                     uint32_t hi[4], lo[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) split_bf16x2(v[2 * j], v[2 * j + 1], hi[j], lo[j]);
-                    return as_bf(make_uint4(low ? lo[0] : hi[0], low ? lo[1] : hi[1], low ? lo[2] : hi[2], low ? lo[3] : hi[3]));
+                    if constexpr (PACK) {
+                        o[0] = as_bf(make_uint4(low ? lo[0] : hi[0], low ? lo[1] : hi[1], low ? lo[2] : hi[2], low ? lo[3] : hi[3]));
+                    } else {
+                        o[0] = as_bf(make_uint4(hi[0], hi[1], hi[2], hi[3]));
+                        o[P - 1] = as_bf(make_uint4(lo[0], lo[1], lo[2], lo[3]));
+                    }
                 };
-                bf16x8 Q[4];
+                bf16x8 Q[4][P];
                 auto split_query = [&] {
                     const float sc = a.att_scale;
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks) {
                         const float v[8] = {qv[ks][0].x * sc, qv[ks][0].y * sc, qv[ks][0].z * sc, qv[ks][0].w * sc,
                                             qv[ks][1].x * sc, qv[ks][1].y * sc, qv[ks][1].z * sc, qv[ks][1].w * sc};
-                        Q[ks] = parts(v);
+                        parts(v, Q[ks]);
                     }
                 };
                 auto process = [&](int key, bool edge, int lim) {
@@ -503,12 +522,14 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                        for (int ab = 0; ab < 2; ++ab) s[ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(r.K[ab][ks]), Q[ks], s[ab], 0, 0, 0);
+                        for (int p = 0; p < P; ++p)
+#pragma unroll
+                            for (int ab = 0; ab < 2; ++ab) s[ab] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(r.K[ab][ks]), Q[ks][p], s[ab], 0, 0, 0);
                     float p[8], top = m_run;
 #pragma unroll
                     for (int v = 0; v < 8; ++v) {
                         p[v] = s[v >> 2][v & 3];
-                        p[v] += dpp_f<0x128, 0xF>(0.f, p[v]);
+                        if constexpr (PACK) p[v] += dpp_f<0x128, 0xF>(0.f, p[v]);
                         if (edge && key + (v >> 2) * 16 + c.g * 4 + (v & 3) > lim) p[v] = -INFINITY;
                         top = fmaxf(top, p[v]);
                     }
@@ -522,11 +543,13 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                     const float f = fexp(m_run - base);
                     l_run = l_run * f + quad_rows_sum(sum);
                     m_run = m_new;
-                    const bf16x8 w = parts(p);
+                    bf16x8 w[P];
+                    parts(p, w);
 #pragma unroll
                     for (int dt = 0; dt < 8; ++dt) {
                         O[dt] *= f;
-                        O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(r.V[dt]), w, O[dt], 0, 0, 0);
+#pragma unroll
+                        for (int u = 0; u < P; ++u) O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(r.V[dt]), w[u], O[dt], 0, 0, 0);
                     }
                 };
                 if (newest) {
@@ -542,7 +565,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                         const uint4 v = __builtin_bit_cast(uint4, vn[dt]);
                         r.V[dt] = make_uint4(__builtin_amdgcn_perm(v.y, v.x, 0x07060302u), __builtin_amdgcn_perm(v.w, v.z, 0x07060302u), 0u, 0u);
                     }
-                    process(len, true, len + c.t8);
+                    process(len, true, len + c.row());
                     if (busy) r.load(c, first);
                 } else {
                     fetch(false);
@@ -581,14 +604,16 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                 Lsum += cl[v * 16 + c.tok] * f;
                 o += *(const f32x4*)(c.lds + kRed + ((v * 8 + c.wave) * 64 + c.lane) * 16) * f;
             }
+            if constexpr (PACK) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] += dpp_f<0x128, 0xF>(0.f, o[v]);
+                for (int v = 0; v < 4; ++v) o[v] += dpp_f<0x128, 0xF>(0.f, o[v]);
+            }
             lds_barrier();  // (read: the next stage's sums may come)
             char* out = pinned(z + a.at.a1);
             auto give = [&](int dt, const f32x4& v, float sum) {
                 const float inv = 1.f / sum;
                 const float t4[4] = {v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv};
-                put_planes<true, false>(c, out, h * DH + dt * 16 + c.g * 4, t4);
+                put_planes<PACK, false>(c, out, h * DH + dt * 16 + c.g * 4, t4);
             };
             {
                 // parts handed over between its workgroups, each of which joins 128 / S of the features
@@ -619,7 +644,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                         unsigned m = 0u;
 #pragma unroll
                         for (int s = 0; s < kWideSplits; ++s) {
-                            const int e = min(s, S - 1) * c.R + c.t8;
+                            const int e = min(s, S - 1) * c.R + c.row();
                             v[s] = ldf4<Way::kIn>(po, (e * DH + dt * 16 + c.g * 4) * 4);
                             ml[s] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(to, e * 8, 0, Way::kIn));
                         }
@@ -679,15 +704,15 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                 const float rms = norm_factor(c, d, a.eps);
                 float w[4];
                 if constexpr (GATED) {
-                    const f32x4 s = total<FT, true, false>(c, 2 * c.wave) * rms, u = total<FT, true, false>(c, 2 * c.wave + 1) * rms;
+                    const f32x4 s = total<FT, PACK, false>(c, 2 * c.wave) * rms, u = total<FT, PACK, false>(c, 2 * c.wave + 1) * rms;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(s[v]) : silu_f(s[v])) * u[v];
                 } else {
-                    const f32x4 s = total<FT, true, false>(c, c.wave) * rms;
+                    const f32x4 s = total<FT, PACK, false>(c, c.wave) * rms;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = fmaxf(s[v], 0.f);
                 }
-                put_planes<true, false>(c, z + a.at.h, tile * 16 + c.g * 4, w);
+                put_planes<PACK, false>(c, z + a.at.h, tile * 16 + c.g * 4, w);
             }
             lds_barrier();
         }
@@ -723,6 +748,10 @@ static bool wide_fits(int d, int heads, int F, bool gated, int cus) {
            d / 16 <= cus && heads <= cus;
 }
 
+// Most rows: above eight, which take twice the registers for activations, models of the widest cut alone (its FFN's first weights do not wait in
+// registers while others are multiplied).
+int wide_rows(int d, int heads, int F, bool gated, int cus) { return wide_fits<Cut2048>(d, heads, F, gated, cus) ? kWideRows : kWideRowsMost; }
+
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     if (d_head != kWideHead || d <= 1024 || d % 256 != 0 || F % 32 != 0) return 0;
     return wide_fits<Cut2048>(d, heads, F, gated, cus) || wide_fits<Cut4096>(d, heads, F, gated, cus) ? cus : 0;
@@ -757,7 +786,7 @@ hipError_t wide_init() {
     static hipError_t done = [] {
 #define BILD_W(CV, RV) (const void*)wide_kernel<false, CV, RV>, (const void*)wide_kernel<true, CV, RV>
         const void* fns[] = {BILD_W(Cut2048, 0), BILD_W(Cut2048, 1), BILD_W(Cut2048, 2), BILD_W(Cut2048Two, 0), BILD_W(Cut2048Two, 1), BILD_W(Cut2048Two, 2),
-                             BILD_W(Cut4096, 0), BILD_W(Cut4096, 1), BILD_W(Cut4096, 2)};
+                             BILD_W(Cut4096, 0), BILD_W(Cut4096, 1), BILD_W(Cut4096, 2), BILD_W(Cut4096, 16)};
 #undef BILD_W
         return raise_lds_limit(fns, 160 * 1024);
     }();
@@ -767,7 +796,7 @@ hipError_t wide_init() {
 hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
     if (hipError_t e = wide_init(); e != hipSuccess) return e;
     const bool gated = a.act != BILD_ACT_RELU;
-    if (a.groups < 1 || a.groups != wide_groups(a.d, a.heads, a.I / std::max(a.heads, 1), a.F, gated, a.groups) || a.T < 1 || a.T > kWideRows || a.room < a.T || a.cross || a.rel_bias ||
+    if (a.groups < 1 || a.groups != wide_groups(a.d, a.heads, a.I / std::max(a.heads, 1), a.F, gated, a.groups) || a.T < 1 || a.T > wide_rows(a.d, a.heads, a.F, gated, a.groups) || a.room < a.T || a.cross || a.rel_bias ||
         !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr)
         return hipErrorInvalidValue;
     const dim3 grid(a.groups), block(kPassThreads);
@@ -784,7 +813,8 @@ hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
         else if (small) BILD_WC(Cut2048, RV);                                                                          \
         else BILD_WC(Cut4096, RV);                                                                                     \
     } while (0)
-    if (a.room == 1) BILD_W(1);
+    if (a.room > 8) BILD_WC(Cut4096, 16);
+    else if (a.room == 1) BILD_W(1);
     else if (a.room == 2) BILD_W(2);
     else BILD_W(0);
 #undef BILD_W

@@ -169,3 +169,36 @@ def test_who_does_what_changes_with_the_length(shape, monkeypatch):
     worst = float(np.abs(got["1"] - got["0"]).max())
     print("worst", worst, "one token", moved, flush=True)
     assert worst <= min(moved / 4, 2 * parity.logit_tol(cfg))
+
+
+@pytest.mark.parametrize("shape", [dict(), dict(act=bi.ACT_RELU, pos=bi.POS_SINUSOIDAL, d=1280, heads=10, d_ff=96, n_large=4)])
+def test_nine_to_sixteen_rows(shape, monkeypatch):
+    """Models of the widest cut (the large ones): high and low parts in operands of their own, no earlier key up to eight key ranges, the new keys'
+    block whole and short, passes of other rooms between.  Against the separate kernels, as above."""
+    cfg = bi.toy_pair(**{**BASE, **shape, "max_new": 2100})
+    R = Rig(cfg)
+    got = {}
+    for one in ("1", "0"):
+        monkeypatch.setenv("BILD_ONE_KERNEL", one)
+        st = R.state(cfg.max_new, 31)
+        st.encode(R.src)
+        st.debug_enable_logits(True)
+        rows_seen = []
+        for have in (R.n0, R.n0 + 24, 300, 1018, 2060):
+            st.seq_truncate(R.n0)
+            if have > R.n0:
+                st.force_tokens(R.n0, bi.make_tokens(cfg.large.vocab, have - R.n0, seed=have), have)
+            st.large_verify(float("inf"), draft=[])
+            before = st.pass_routes()
+            for rows in (9, 16, 8, 11, 16, 1, 15):
+                st.seq_truncate(have)
+                st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
+                rows_seen += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
+            now = {k: v - before[k] for k, v in st.pass_routes().items() if v > before[k]}
+            assert now == {"chip" if one == "1" else "kernels": 7}, (have, now)
+        got[one] = np.stack(rows_seen)
+        moved = one_token_moves(st, R, 300)
+        st.close()
+    worst = float(np.abs(got["1"] - got["0"]).max())
+    print("worst", worst, "one token", moved, flush=True)
+    assert worst <= min(moved / 4, 2 * parity.logit_tol(cfg))
