@@ -472,7 +472,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
     // passes in one kernel: what both models' hand over, one behind the other, and their layers
     size_t turns_bytes = 0, layers_n = 0;
     for (ModelState& M : s->ms)
-        for (int r = 0; M.pass_groups && r <= (M.pass_wide ? pass_room_index(M.pass_wide_rows) : kPassRooms - 1); ++r) {
+        for (int r = 0; M.pass_groups && r <= pass_room_index(M.pass_wide ? M.pass_wide_rows : kPassRows); ++r) {
             want(M.pass_turns[r], pass_turns_bytes(M, r));
             turns_bytes += wants.back().bytes;
         }
@@ -1633,7 +1633,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // 660, 681: never slower up to the 8192 positions that were measured.
 static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
-    if (s->ms[w].pass_wide) return s->one_kernel && T <= s->ms[w].pass_wide_rows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= 8192;
+    if (s->ms[w].pass_wide) return s->one_kernel && T <= s->ms[w].pass_wide_rows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= wide_keys(T);
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
            s->n_src <= (s->ms[w].m->cfg.dtype == BILD_DT_F32 ? 1024 : on_one_die(s, w, T) ? 1280 : T == 1 ? 1408 : 1536) && s->len[w] + T <= 1024;
 }

@@ -199,9 +199,9 @@ struct AttnArgs {
 // Most rows; on one die.  (One die, the whole chip, us, T5-small shape, 512 tokens: one row 97, 137, two 99, 138, four 100, 140;
 // mT5-small shape 120, 178; 121, 180; 122, 181.  The small model of a pair has one row; a narrow large one reviews.)
 constexpr int kPassRows = 16, kPassDieRows = 4;
-// The hand-over memory is laid out for 1, 2, 4, 8 or 16 rows.
-constexpr int kPassRooms = 5;
-constexpr int pass_room_index(int rows) { return rows <= 1 ? 0 : rows <= 2 ? 1 : rows <= 4 ? 2 : rows <= 8 ? 3 : 4; }
+// The hand-over memory is laid out for 1, 2, 4, 8, 16 or 32 rows.
+constexpr int kPassRooms = 6;
+constexpr int pass_room_index(int rows) { return rows <= 1 ? 0 : rows <= 2 ? 1 : rows <= 4 ? 2 : rows <= 8 ? 3 : rows <= 16 ? 4 : 5; }
 // The ranks given out on a die; on lines of their own, of passes with the head inside (pass_head.h), the ranks given out on the die, mod 32, and on
 // the others; and, the last word: a workgroup gave up
 constexpr int kPassSyncWords = 128, kPassGoingOn = 32, kPassOthers = 64;
@@ -296,11 +296,12 @@ void pass_head_plan(PassHead& h, const PassPlan& at, int d, bool f32, int cus); 
 PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide);
 // head null: LM head and policy follow as kernels
 hipError_t launch_pass(const PassArgs& a, const PassHead* head, int grid, hipStream_t st);
-constexpr int kWideRows = 8, kWideRowsMost = 16, kWideHead = 128;  // most rows (wide_rows); features of a head
+constexpr int kWideRows = 8, kWideRowsMost = 32, kWideRowsFrom = 4096, kWideHead = 128;  // most rows (wide_rows), the width from which on; features of a head
 constexpr int kWideSplits = 8;                 // most key ranges of a head
 constexpr int kWideApart = 1280;               // most keys with which heads and projections are different workgroups'
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // as pass_groups, of pass_wide.hip
 int wide_rows(int d, int heads, int F, bool gated, int cus);
+int wide_keys(int T);
 bool wide_two(int d, int heads, int F, bool gated, int cus, int keys);
 // who does what in a pass that ends with `keys` keys (wide_parts): {tiles of q, k, v a workgroup, its first workgroup, the same of the FFN's
 // input, the heads' first workgroup, ranges, apart}; false: not a shape it is made for

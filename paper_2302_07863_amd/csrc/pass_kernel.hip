@@ -953,7 +953,7 @@ PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide) {
         return (int)r;
     };
     const int inputs = f32 ? 16 : 32;
-    const size_t x = (size_t)(d / inputs) * tile_bytes(true, room, f32), i = (size_t)(I / inputs) * tile_bytes(false, room, f32);
+    const size_t x = (size_t)(d / inputs) * (tile_bytes(true, room, f32) + (room > 16 ? 128 : 0)), i = (size_t)(I / inputs) * tile_bytes(false, room, f32);
     p.x1 = take(x); p.q = take((size_t)room * I * 4); p.k = take((size_t)room * I * (f32 ? 4 : 2)); p.v = take((size_t)fresh_room(room) * I * 4);
     p.a1 = take(i); p.x2 = take(x);
     p.a2 = wide ? 0 : take(i); p.x3 = wide ? 0 : take(x);  // (cross-attention)

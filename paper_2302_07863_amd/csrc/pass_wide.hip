@@ -1,5 +1,5 @@
 // One decoder pass of a wide bf16 model without cross-attention (above 1024 and up to 4096 wide, heads of 128) in ONE kernel, up to
-// eight rows, or sixteen (wide_rows): pass_kernel.hip's way of handing results over (its head explains it; nothing is counted, results are their own flags),
+// eight rows, or sixteen, or thirty-two (wide_rows): pass_kernel.hip's way of handing results over (its head explains it; nothing is counted, results are their own flags),
 // for layers of 60 to 400 MB.
 //
 // Bound: the weights from memory.  As kernels of their own the six stages of a layer each end with a few microseconds in which the
@@ -27,7 +27,7 @@
 // Nine to sixteen rows have high and low parts in operands of their own, twice the activations and products; the weights still take longer.  The 7B shape, nine, sixteen
 // rows over 64, 1024, 4097 tokens, separate kernels / this, us: 3305, 3311, 3463, 3473, 3770, 3779 / 2837, 2843, 2918, 2927, 3239, 3246 (eight rows 2591, 2680, 2993); six
 // layers of 2304 (without gate), 2560, 3072, 4096 (without gate) and of 1536 with a hidden state of 8192, twelve rows over 64 and 8100 tokens 336, 410, 452, 522, 387 and 501, 576, 618, 703, 458 / 338, 381, 415,
-// 474, 322 and 466, 528, 582, 675, 424.
+// 474, 322 and 466, 528, 582, 675, 424.  Seventeen to thirty-two have two row tiles (figures at wide_keys).
 #include "pass_walk.h"
 
 namespace bild {
@@ -50,8 +50,51 @@ struct WideWalk : Walk<false, false, ROOM> {
     static constexpr bool ROOM1 = false;
     static constexpr bool PACKED = ROOM <= 8;  // high and low parts in one operand (multiply() in pass_walk.h); above eight rows one each
     static constexpr int P = PACKED ? 1 : 2;
-    __device__ __forceinline__ int row() const { return PACKED ? this->t8 : this->t; }
+    static constexpr int NT = ROOM == 32 ? 2 : 1;  // row tiles of sixteen
+    float ss2;                                     // as ss, of the second row tile
+    __device__ __forceinline__ int row(int u = 0) const { return NT > 1 ? min(u * 16 + this->tok, this->T - 1) : PACKED ? this->t8 : this->t; }
 };
+// (thirty-two rows' sums of squares take twice the place)
+template <class Walk>
+__device__ __forceinline__ int tile_size(const Walk& c, bool normed) {
+    return tile_bytes(normed, c.R, false) + (Walk::NT > 1 && normed ? 128 : 0);
+}
+// The waves' results side by side in LDS, and the rows' factors (leave(), norm_factor() in pass_walk.h).  Two row tiles take both halves of that memory:
+// a barrier behind every stage's results keeps the next one's away from them.
+template <int RW, bool NORM, class Walk>
+__device__ __forceinline__ void leave_rows(Walk& c, const f32x4 (&acc)[RW * Walk::NT]) {
+    if constexpr (Walk::NT == 1) {
+        leave<RW, NORM, false>(c, acc);
+    } else {
+        static_assert(kPassWaves * RW * Walk::NT * 1024 <= 2 * kRedBytes, "room for both row tiles' sums");
+        if (NORM && c.g < 2) *(float*)(c.lds + kSq + (c.wave * 32 + c.g * 16 + c.tok) * 4) = c.g ? c.ss2 : c.ss;
+#pragma unroll
+        for (int q = 0; q < RW * Walk::NT; ++q) *(f32x4*)(c.lds + kRed + ((c.wave * RW * Walk::NT + q) * 64 + c.lane) * 16) = acc[q];
+        lds_barrier();
+    }
+}
+template <class Walk>
+__device__ __forceinline__ float row_factor(const Walk& c, int d, float eps, int u) {
+    if constexpr (Walk::NT == 1) return norm_factor(c, d, eps);
+    float p[kPassWaves], s = 0.f;
+#pragma unroll
+    for (int v = 0; v < kPassWaves; ++v) p[v] = *(const float*)(c.lds + kSq + (v * 32 + u * 16 + c.tok) * 4);
+#pragma unroll
+    for (int v = 0; v < kPassWaves; ++v) s += p[v];
+    return __builtin_amdgcn_rsqf(s * __builtin_amdgcn_rcpf((float)d) + eps);
+}
+// put_planes() of row tile u
+template <bool PACK, bool NORM, class Walk>
+__device__ __forceinline__ void put_rows(const Walk& c, void* planes, int n0, const float (&w)[4], int u) {
+    if constexpr (Walk::NT == 1) {
+        put_planes<PACK, NORM>(c, planes, n0, w);
+    } else {
+        const int row = u * 16 + c.tok, off = (n0 >> 5) * tile_size(c, NORM) + (((n0 >> 4) & 1) * 2 + (c.g >> 1)) * 16 * c.R + (c.g & 1) * 64 * c.R + row * 16;
+        const v4u v = query_parts(f32x4{w[0], w[1], w[2], w[3]});  // (eight features' high parts to the even lane groups, their low parts to the odd ones)
+        if (row < c.T) __builtin_amdgcn_raw_buffer_store_b128(v, whole(planes), off, 0, Walk::kOut);
+        __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, whole((const char*)planes + c.clear), off, 0, Walk::kOut);
+    }
+}
 
 // A projection's weights on their way: N input tiles per wave at most, RW feature tiles, in pieces of CH input tiles of which two
 // are requested before their activations are there.  The next piece's activations are requested ahead of the weights that follow
@@ -94,47 +137,50 @@ struct Stream {
     }
     // acc = W x over this wave's inputs
     template <class Walk>
-    __device__ __forceinline__ void run(Walk& c, f32x4 (&acc)[RW], const void* planes, const void* weights, int first, int tk, int end) {
+    __device__ __forceinline__ void run(Walk& c, f32x4 (&acc)[RW * Walk::NT], const void* planes, const void* weights, int first, int tk, int end) {
         const Where a = where(c.wave, weights, first, tk, end);
         const int k0 = a.k0, n = a.n;
         const Rsrc xs = whole(planes);
         if constexpr (Walk::KNOWN == 1 || Walk::KNOWN == 2) return run_few(c, acc, xs, a);
-        constexpr int P = Walk::P;
-        const int S = tile_bytes(NORM, c.R, false), at = (Walk::PACKED ? (c.g * 2 + (c.tok >> 3)) * c.R + c.row() : c.g * c.R + c.row()) * 16;
-        uint4 X[NC > 1 ? 2 : 1][CH * P];
-        v2u sq[NC > 1 ? 2 : 1][SQ];
-        float ss = 0.f;
-        auto get = [&](uint4 (&x)[CH * P], v2u (&s)[SQ], int i) {
+        constexpr int P = Walk::P, NT = Walk::NT, XL = P * NT;  // loads of a tile
+        const int S = tile_size(c, NORM);
+        int at[NT];
+#pragma unroll
+        for (int u = 0; u < NT; ++u) at[u] = (Walk::PACKED ? (c.g * 2 + (c.tok >> 3)) * c.R + c.row() : c.g * c.R + c.row(u)) * 16;
+        uint4 X[NC > 1 ? 2 : 1][CH * XL];
+        v2u sq[NC > 1 ? 2 : 1][SQ * NT];
+        float ss = 0.f, ss2 = 0.f;
+        auto get = [&](uint4 (&x)[CH * XL], v2u (&s)[SQ * NT], int i) {
 #pragma unroll
             for (int j = 0; j < CH; ++j)
                 if (i * CH + j < N) {
 #pragma unroll
-                    for (int p = 0; p < P; ++p) x[P * j + p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at + p * c.R * 64, (k0 + min(i * CH + j, max(n - 1, 0))) * S, Walk::kIn));
+                    for (int p = 0; p < XL; ++p) x[XL * j + p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at[p / P] + p % P * c.R * 64, (k0 + min(i * CH + j, max(n - 1, 0))) * S, Walk::kIn));
                 }
             if constexpr (NORM) {  // (lane group g: tiles g, g + 4 of the piece)
 #pragma unroll
-                for (int u = 0; u < SQ; ++u)
-                    s[u] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, min(i * CH + u * 4 + c.g, max(n - 1, 0)) * S + c.R * 128 + c.row() * 8, k0 * S, Walk::kIn));
+                for (int u = 0; u < SQ * NT; ++u)
+                    s[u] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(xs, min(i * CH + u / NT * 4 + c.g, max(n - 1, 0)) * S + c.R * 128 + c.row(u % NT) * 8, k0 * S, Walk::kIn));
             }
         };
-        auto missing = [&](const uint4 (&x)[CH * P], const v2u (&s)[SQ], int i) {
+        auto missing = [&](const uint4 (&x)[CH * XL], const v2u (&s)[SQ * NT], int i) {
             unsigned m = 0u;
 #pragma unroll
-            for (int j = 0; j < CH * P; ++j)
-                if (i * CH + j / P < N) m = max(max(m, max(x[j].x, x[j].y)), max(x[j].z, x[j].w));
+            for (int j = 0; j < CH * XL; ++j)
+                if (i * CH + j / XL < N) m = max(max(m, max(x[j].x, x[j].y)), max(x[j].z, x[j].w));
             if constexpr (NORM) {
 #pragma unroll
-                for (int u = 0; u < SQ; ++u) m = max(m, max(s[u].x, s[u].y));
+                for (int u = 0; u < SQ * NT; ++u) m = max(m, max(s[u].x, s[u].y));
             }
             return __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
         };
 #pragma unroll
-        for (int q = 0; q < RW; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < RW * NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
         get(X[0], sq[0], 0);
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            uint4 (&x)[CH * P] = X[i & 1];
-            v2u (&s)[SQ] = sq[i & 1];
+            uint4 (&x)[CH * XL] = X[i & 1];
+            v2u (&s)[SQ * NT] = sq[i & 1];
             // (the first look apart: the wait of a loop would be for everything requested since)
             if (__builtin_expect(missing(x, s, i), 0)) {
                 int tries = 0;
@@ -154,19 +200,23 @@ struct Stream {
             for (int j = 0; j < CH; ++j)
                 if (i * CH + j < N && i * CH + j < n) {
 #pragma unroll
-                    for (int p = 0; p < P; ++p)
+                    for (int p = 0; p < XL; ++p)
 #pragma unroll
-                        for (int q = 0; q < RW; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[i & 1][j * RW + q]), as_bf(x[P * j + p]), acc[q], 0, 0, 0);
+                        for (int q = 0; q < RW; ++q) acc[q * NT + p / P] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(W[i & 1][j * RW + q]), as_bf(x[XL * j + p]), acc[q * NT + p / P], 0, 0, 0);
                 }
             if constexpr (NORM) {
 #pragma unroll
                 for (int u = 0; u < SQ; ++u)
-                    if (u * 4 + c.g < CH && i * CH + u * 4 + c.g < n) ss += __uint_as_float(s[u].x) + __uint_as_float(s[u].y);
+                    if (u * 4 + c.g < CH && i * CH + u * 4 + c.g < n) {
+                        ss += __uint_as_float(s[u * NT].x) + __uint_as_float(s[u * NT].y);
+                        if constexpr (NT > 1) ss2 += __uint_as_float(s[u * NT + NT - 1].x) + __uint_as_float(s[u * NT + NT - 1].y);
+                    }
             }
             __builtin_amdgcn_sched_barrier(0);
             if (i + 2 < NC) ask(c.lane, W[i & 1], a, i + 2);
         }
         if constexpr (NORM) c.ss = quad_rows_sum(ss);
+        if constexpr (NORM && NT > 1) c.ss2 = quad_rows_sum(ss2);
     }
     // One or two rows: a load brings eight tiles' activations, or four tiles' (see multiply() in pass_walk.h for what a load takes
     // however few of its bytes differ): columns (tile, row) of a tile's high and low parts, which move down to the rows' own for its
@@ -260,19 +310,20 @@ struct Range {
 // (the attention's results [wave][8][64] take both halves of the sums' memory)
 static_assert(2 * kRedBytes >= kPassWaves * 8 * 1024, "room for eight waves' results");
 
-template <int QTV, int FTV, int KDV, int KFV, int QC, int FC>
+template <int QTV, int FTV, int KDV, int KFV, int QC, int FC, int OC = 8>
 struct WideCut {
     static constexpr int QT = QTV, FT = FTV, KD = KDV, KF = KFV;  // as in pass_kernel.hip
     using Qkv = Stream<KD, QT, QC, true>;
-    using Out = Stream<KD, 1, 8, false>;
+    using Out = Stream<KD, 1, OC, false>;
     using In = Stream<KD, FT, FC, true>;
-    using Ffn = Stream<KF, 1, 8, false>;
+    using Ffn = Stream<KF, 1, OC, false>;
     static constexpr bool EARLY = In::NC <= 2;  // the FFN's first weights all fit the registers
 };
 // (pieces of the 4096-wide cut: 8 and 6 tiles a request of q, k, v and the FFN 669 and 673 us, 12 and 12 663, 15 and 18 the same)
 using Cut2048 = WideCut<3, 4, 8, 24, 4, 4>;
 using Cut2048Two = WideCut<2, 4, 8, 24, 4, 4>;
 using Cut4096 = WideCut<3, 6, 16, 44, 4, 2>;
+using Cut4096Rows = WideCut<3, 6, 16, 44, 2, 1, 4>;  // two row tiles: four loads of activations a tile
 
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -310,7 +361,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
     using Way = WideWalk<ROOM>;
     constexpr int QT = Cut::QT, FT = Cut::FT, DH = kWideHead;
     constexpr bool EARLY = Cut::EARLY, PACK = Way::PACKED;
-    constexpr int P = Way::P;
+    constexpr int P = Way::P, NT = Way::NT;
     Way c;
     c.lds = smem;
     c.failed = a.sync + kPassSyncWords - 1;
@@ -324,14 +375,14 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
     const int len = *a.len_ptr;
     auto tq = [&] { return 3 * (I >> 4); };
     auto tf = [&] { return GATED ? F >> 3 : F >> 4; };
-    const WideParts who = wide_parts<Cut>(len + T, d, a.heads, tq(), tf(), a.groups);
+    const WideParts who = wide_parts<Cut>(len + T, d, a.heads * NT, tq(), tf(), a.groups);
     const int uq = c.wg - who.q, uf = c.wg - who.i;
     const int q0 = uq * QT, q1 = min(q0 + QT, tq()), i0 = uf * FT;  // tiles of the projections
     const bool owner = c.wg < d >> 4, qkv = uq >= 0 && q0 < tq(), ffn = uf >= 0 && i0 < tf();
-    const bool mine = owner && c.wave == 0;
+    const bool mine = owner && c.wave < NT;  // (a row tile each)
     const int S = who.ranges, place = c.wg - who.head0;
-    const bool att = place >= 0 && place < a.heads * S;
-    const int h = att ? place / S : 0, split = att ? place % S : 0;
+    const bool att = place >= 0 && place < a.heads * NT * S;
+    const int h = att ? place / (S * NT) : 0, rt = NT > 1 && att ? place / S % NT : 0, split = att ? place % S : 0;  // (rt: the row tile)
 
     float4 next_gain = make_float4(0.f, 0.f, 0.f, 0.f), x = make_float4(0.f, 0.f, 0.f, 0.f);
     auto n0 = [&] { return c.wg * 16 + c.g * 4; };
@@ -340,15 +391,16 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         if (!mine) return;
         const float w[4] = {x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w};
         const float ss = quad_rows_sum(x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w);
-        put_planes<PACK, true>(c, planes, n0(), w);
+        put_rows<PACK, true>(c, planes, n0(), w, c.wave);
         if (c.g == 0) {
-            const int off = (n0() >> 5) * tile_bytes(true, c.R, false) + c.R * 128 + (c.tok * 2 + ((n0() >> 4) & 1)) * 4;
-            if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(planes), off, 0, Way::kOut);
-            if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, whole(planes + c.clear), off, 0, Way::kOut);
+            const int row = NT > 1 ? c.wave * 16 + c.tok : c.tok;
+            const int off = (n0() >> 5) * tile_size(c, true) + c.R * 128 + (row * 2 + ((n0() >> 4) & 1)) * 4;
+            if (row < T) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ss), whole(planes), off, 0, Way::kOut);
+            if (row < c.R) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, whole(planes + c.clear), off, 0, Way::kOut);
         }
     };
     auto add = [&] {
-        const f32x4 s = total<1, PACK, false>(c, 0);
+        const f32x4 s = total<NT, PACK, false>(c, NT > 1 ? c.wave : 0);
         x = make_float4(x.x + s[0], x.y + s[1], x.z + s[2], x.w + s[3]);
     };
     typename Cut::Qkv sq;
@@ -358,7 +410,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
     const CLayer* L = (const CLayer*)(uintptr_t)a.layers;
     char* z = c.scratch(a);
     if (owner) {
-        const int pos = len + c.t;
+        const int pos = len + (NT > 1 ? c.row(c.wave) : c.t);
         const float4 gn = gain(L->ln1);
         if (mine) {
             if (a.emb) {
@@ -387,22 +439,24 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         c.place(T, a.room);
         // ---- q, k, v ----
         if (qkv) {
-            const int nf = min(q0 + c.wave, q1 - 1) * 16 + c.g * 4;
+            const int qq = NT > 1 ? c.wave >> 1 : c.wave, qu = NT > 1 ? c.wave & 1 : 0;  // this wave's tile and row tile
+            const int nf = min(q0 + qq, q1 - 1) * 16 + c.g * 4;
             double2 turn[2] = {};  // cos and sin of this lane's two pairs
-            if (a.rope && c.wave < QT) {
-                const double2* tb = a.rope + ((size_t)(len + c.t) * DH + nf % DH) / 2;
+            if (a.rope && qq < QT) {
+                const double2* tb = a.rope + ((size_t)(len + (NT > 1 ? c.row(qu) : c.t)) * DH + nf % DH) / 2;
                 turn[0] = tb[0];
                 turn[1] = tb[1];
             }
             const char* xs = pinned(z + a.at.x1);
-            f32x4 acc[QT];
+            f32x4 acc[QT * NT];
             c.template nap<350>();
             sq.run(c, acc, xs, L->wqkv, q0, d >> 5, q1);
-            leave<QT, true, false>(c, acc);
-            if (q0 + c.wave < q1) {
-                const float f = norm_factor(c, d, a.eps);
-                f32x4 s = total<QT, PACK, false>(c, c.wave) * f;
-                const int seg = nf / I, nn = nf - seg * I, pos = len + c.tok, hd = nn / DH, f0 = nn % DH;
+            leave_rows<QT, true>(c, acc);
+            if (q0 + qq < q1) {
+                const float f = row_factor(c, d, a.eps, qu);
+                f32x4 s = total<QT * NT, PACK, false>(c, qq * NT + qu) * f;
+                const int row = NT > 1 ? qu * 16 + c.tok : c.tok;
+                const int seg = nf / I, nn = nf - seg * I, pos = len + row, hd = nn / DH, f0 = nn % DH;
                 if (a.rope && seg < 2) {
 #pragma unroll
                     for (int p = 0; p < 2; ++p) {
@@ -414,26 +468,26 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                 char* out = z + (seg == 0 ? a.at.q : seg == 1 ? a.at.k : a.at.v);
                 const Rsrc o = whole(out), n = whole(out + c.clear), kv = whole(seg == 1 ? L->kc : L->vc);
                 if (seg == 0) {
-                    const int off = ((hd * c.R + c.tok) * DH + f0) * 4;
+                    const int off = ((hd * c.R + row) * DH + f0) * 4;
                     const v4u v = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
-                    if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b128(v, o, off, 0, Way::kOut);
-                    if (c.tok < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, n, off, 0, Way::kOut);
+                    if (row < T) __builtin_amdgcn_raw_buffer_store_b128(v, o, off, 0, Way::kOut);
+                    if (row < c.R) __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, n, off, 0, Way::kOut);
                 } else if (seg == 1) {
-                    const int off = ((hd * c.R + c.tok) * DH + f0) * 2;
+                    const int off = ((hd * c.R + row) * DH + f0) * 2;
                     const unsigned k01 = pack_bf16x2(s[0], s[1]), k23 = pack_bf16x2(s[2], s[3]);
-                    if (c.tok < T) {
+                    if (row < T) {
                         st8<Way::kOut>(o, off, k01, k23);
                         st8<Way::kOut>(kv, (pos * I + nn) * 2, k01, k23);
                     }
-                    if (c.tok < c.R) st8<Way::kOut>(n, off, kNotThere, kNotThere);
+                    if (row < c.R) st8<Way::kOut>(n, off, kNotThere, kNotThere);
                 } else {
-                    const int room = fresh_room(c.R), off = ((hd * DH + f0) * room + c.tok) * 4;
+                    const int room = fresh_room(c.R), off = ((hd * DH + f0) * room + row) * 4;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const unsigned b = f2bf(s[v]);
-                        if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(c.tok < T ? b << 16 : 0u, o, off + v * room * 4, 0, Way::kOut);
-                        if (c.tok < T) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, kv, ((nn + v) * a.vcap + pos) * 2, 0, Way::kOut);
-                        if (c.tok < room) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, n, off + v * room * 4, 0, Way::kOut);
+                        if (row < room) __builtin_amdgcn_raw_buffer_store_b32(row < T ? b << 16 : 0u, o, off + v * room * 4, 0, Way::kOut);
+                        if (row < T) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, kv, ((nn + v) * a.vcap + pos) * 2, 0, Way::kOut);
+                        if (row < room) __builtin_amdgcn_raw_buffer_store_b32(kNotThere, n, off + v * room * 4, 0, Way::kOut);
                     }
                 }
             }
@@ -468,8 +522,9 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                 const int room = fresh_room(c.R);
                 const Rsrc fq = whole(z + a.at.q + h * c.R * DH * 4), fk = whole(z + a.at.k + h * c.R * DH * 2), fv = whole(z + a.at.v + h * room * DH * 4);
                 float4 qv[4][2];
-                uint4 kn[4];
-                float4 vn[8];
+                uint4 kn[4 * NT];
+                float4 vn[8 * NT];
+                const int mine_row = NT > 1 ? c.row(rt) : c.row();
                 auto fetch = [&](bool fresh) {  // the queries; the new rows' keys and values too
                     int tries = 0;
                     bool missing;
@@ -479,16 +534,16 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                         unsigned m = 0u;
                         auto see = [&](const uint4& v) { m = max(max(m, max(v.x, v.y)), max(v.z, v.w)); };
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) qv[i >> 1][i & 1] = ldf4<Way::kIn>(fq, c.row() * DH * 4 + (i >> 1) * 128 + c.g * 32 + (i & 1) * 16);
+                        for (int i = 0; i < 8; ++i) qv[i >> 1][i & 1] = ldf4<Way::kIn>(fq, mine_row * DH * 4 + (i >> 1) * 128 + c.g * 32 + (i & 1) * 16);
                         if (fresh) {
 #pragma unroll
-                            for (int ks = 0; ks < 4; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fk, c.t * DH * 2 + ks * 64 + c.g * 16, 0, Way::kIn));
+                            for (int ks = 0; ks < 4 * NT; ++ks) kn[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(fk, (NT > 1 ? c.row(ks >> 2) : c.t) * DH * 2 + (ks & 3) * 64 + c.g * 16, 0, Way::kIn));
 #pragma unroll
-                            for (int dt = 0; dt < 8; ++dt) vn[dt] = ldf4<Way::kIn>(fv, ((dt * 16 + c.tok) * room + min(c.g * 4, room - 4)) * 4);
+                            for (int dt = 0; dt < 8 * NT; ++dt) vn[dt] = ldf4<Way::kIn>(fv, (((dt & 7) * 16 + c.tok) * room + (NT > 1 ? c.g * 4 + (dt >> 3) * 16 : min(c.g * 4, room - 4))) * 4);
 #pragma unroll
-                            for (int ks = 0; ks < 4; ++ks) see(kn[ks]);
+                            for (int ks = 0; ks < 4 * NT; ++ks) see(kn[ks]);
 #pragma unroll
-                            for (int dt = 0; dt < 8; ++dt) see(__builtin_bit_cast(uint4, vn[dt]));
+                            for (int dt = 0; dt < 8 * NT; ++dt) see(__builtin_bit_cast(uint4, vn[dt]));
                         }
 #pragma unroll
                         for (int i = 0; i < 8; ++i) see(__builtin_bit_cast(uint4, qv[i >> 1][i & 1]));
@@ -558,14 +613,16 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks) {
                         r.K[0][ks] = kn[ks];
-                        r.K[1][ks] = make_uint4(0u, 0u, 0u, 0u);
+                        r.K[1][ks] = NT > 1 ? kn[4 * (NT - 1) + ks] : make_uint4(0u, 0u, 0u, 0u);
                     }
 #pragma unroll
                     for (int dt = 0; dt < 8; ++dt) {  // (bf16 values in the upper halves)
                         const uint4 v = __builtin_bit_cast(uint4, vn[dt]);
-                        r.V[dt] = make_uint4(__builtin_amdgcn_perm(v.y, v.x, 0x07060302u), __builtin_amdgcn_perm(v.w, v.z, 0x07060302u), 0u, 0u);
+                        const uint4 v2 = __builtin_bit_cast(uint4, vn[8 * (NT - 1) + dt]);
+                        r.V[dt] = make_uint4(__builtin_amdgcn_perm(v.y, v.x, 0x07060302u), __builtin_amdgcn_perm(v.w, v.z, 0x07060302u), NT > 1 ? __builtin_amdgcn_perm(v2.y, v2.x, 0x07060302u) : 0u,
+                                             NT > 1 ? __builtin_amdgcn_perm(v2.w, v2.z, 0x07060302u) : 0u);
                     }
-                    process(len, true, len + c.row());
+                    process(len, true, len + mine_row);
                     if (busy) r.load(c, first);
                 } else {
                     fetch(false);
@@ -613,22 +670,23 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
             auto give = [&](int dt, const f32x4& v, float sum) {
                 const float inv = 1.f / sum;
                 const float t4[4] = {v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv};
-                put_planes<PACK, false>(c, out, h * DH + dt * 16 + c.g * 4, t4);
+                put_rows<PACK, false>(c, out, h * DH + dt * 16 + c.g * 4, t4, rt);
             };
             {
                 // parts handed over between its workgroups, each of which joins 128 / S of the features
                 char* pp = z + a.at.part + h * kWideSplits * c.R * DH * 4;
                 char* pt = z + a.at.top + h * kWideSplits * c.R * 8;
                 const Rsrc po = whole(pp), to = whole(pt), pn = whole(pp + c.clear), tn = whole(pt + c.clear);
-                if (S > 1 && c.tok < T) {
+                const int row = NT > 1 ? rt * 16 + c.tok : c.tok;
+                if (S > 1 && row < T) {
                     const v4u v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
-                    __builtin_amdgcn_raw_buffer_store_b128(v, po, ((split * c.R + c.tok) * DH + c.wave * 16 + c.g * 4) * 4, 0, Way::kOut);
-                    if (c.wave == 0 && c.g == 0) st8<Way::kOut>(to, (split * c.R + c.tok) * 8, __float_as_uint(M), __float_as_uint(Lsum));
+                    __builtin_amdgcn_raw_buffer_store_b128(v, po, ((split * c.R + row) * DH + c.wave * 16 + c.g * 4) * 4, 0, Way::kOut);
+                    if (c.wave == 0 && c.g == 0) st8<Way::kOut>(to, (split * c.R + row) * 8, __float_as_uint(M), __float_as_uint(Lsum));
                 }
                 for (int s = split; s < kWideSplits; s += S)  // (also the places of ranges that there are not in this pass)
-                    if (c.tok < c.R) {
-                        __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, pn, ((s * c.R + c.tok) * DH + c.wave * 16 + c.g * 4) * 4, 0, Way::kOut);
-                        if (c.wave == 0 && c.g == 0) st8<Way::kOut>(tn, (s * c.R + c.tok) * 8, kNotThere, kNotThere);
+                    if (row < c.R) {
+                        __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, pn, ((s * c.R + row) * DH + c.wave * 16 + c.g * 4) * 4, 0, Way::kOut);
+                        if (c.wave == 0 && c.g == 0) st8<Way::kOut>(tn, (s * c.R + row) * 8, kNotThere, kNotThere);
                     }
                 const int per = 8 / S, dt = split * per + c.wave;
                 if (S == 1) {
@@ -644,7 +702,7 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
                         unsigned m = 0u;
 #pragma unroll
                         for (int s = 0; s < kWideSplits; ++s) {
-                            const int e = min(s, S - 1) * c.R + c.row();
+                            const int e = min(s, S - 1) * c.R + (NT > 1 ? c.row(rt) : c.row());
                             v[s] = ldf4<Way::kIn>(po, (e * DH + dt * 16 + c.g * 4) * 4);
                             ml[s] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(to, e * 8, 0, Way::kIn));
                         }
@@ -680,9 +738,9 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         // ---- output projection ----
         if (owner) {
             const char* xs = pinned(z + a.at.a1);
-            f32x4 acc[1];
+            f32x4 acc[NT];
             so.run(c, acc, xs, L->wo, c.wg, I >> 5, d >> 4);
-            leave<1, false, false>(c, acc);
+            leave_rows<1, false>(c, acc);
             if (mine) add();
             publish(gn, z + a.at.x2);
             lds_barrier();
@@ -695,24 +753,30 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         if (ffn) {
             constexpr int FW = GATED ? FT / 2 : FT;  // waves with results
             const char* xs = pinned(z + a.at.x2);
-            f32x4 acc[FT];
+            f32x4 acc[FT * NT];
             c.template nap<350>();
             si.run(c, acc, xs, L->win, i0, d >> 5, tf());
-            leave<FT, true, false>(c, acc);
-            const int tile = uf * FW + c.wave;  // of the hidden state
-            if (c.wave < FW && tile < F >> 4) {
-                const float rms = norm_factor(c, d, a.eps);
+            leave_rows<FT, true>(c, acc);
+            auto hidden = [&](int unit, int u) {
+                const int tile = uf * FW + unit;  // of the hidden state
+                if (unit >= FW || tile >= F >> 4) return;
+                const float rms = row_factor(c, d, a.eps, u);
                 float w[4];
                 if constexpr (GATED) {
-                    const f32x4 s = total<FT, PACK, false>(c, 2 * c.wave) * rms, u = total<FT, PACK, false>(c, 2 * c.wave + 1) * rms;
+                    const f32x4 s = total<FT * NT, PACK, false>(c, 2 * unit * NT + u) * rms, up = total<FT * NT, PACK, false>(c, (2 * unit + 1) * NT + u) * rms;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) w[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(s[v]) : silu_f(s[v])) * u[v];
+                    for (int v = 0; v < 4; ++v) w[v] = (a.act == BILD_ACT_GATED_GELU ? gelu_tanh_f(s[v]) : silu_f(s[v])) * up[v];
                 } else {
-                    const f32x4 s = total<FT, PACK, false>(c, c.wave) * rms;
+                    const f32x4 s = total<FT * NT, PACK, false>(c, unit * NT + u) * rms;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) w[v] = fmaxf(s[v], 0.f);
                 }
-                put_planes<PACK, false>(c, z + a.at.h, tile * 16 + c.g * 4, w);
+                put_rows<PACK, false>(c, z + a.at.h, tile * 16 + c.g * 4, w, u);
+            };
+            if constexpr (NT == 1) {
+                hidden(c.wave, 0);
+            } else {
+                for (int k = c.wave; k < FW * NT; k += kPassWaves) hidden(k >> 1, k & 1);
             }
             lds_barrier();
         }
@@ -723,10 +787,10 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         c.walk_on(a.at.layer);
         if (owner) {
             const char* xs = pinned(hidden);
-            f32x4 acc[1];
+            f32x4 acc[NT];
             c.template nap<650>();
             sf.run(c, acc, xs, L->wout, c.wg, F >> 5, d >> 4);
-            leave<1, false, false>(c, acc);
+            leave_rows<1, false>(c, acc);
             if (mine) add();
             if (!last) publish(next_gain, z + a.at.x1);
             lds_barrier();
@@ -734,9 +798,10 @@ __global__ __launch_bounds__(kPassThreads, 1) void wide_kernel(const PassArgs a)
         sq.forget();
         if (qkv && !last) sq.open(c, L[1].wqkv, q0, d >> 5, q1);
     }
-    if (mine && c.tok < T) {
-        *(float4*)(a.x_out + (size_t)c.tok * d + n0()) = x;
-        if (a.x_keep) *(float4*)(a.x_keep + (size_t)(len + c.tok) * d + n0()) = x;
+    const int row = NT > 1 ? c.wave * 16 + c.tok : c.tok;
+    if (mine && row < T) {
+        *(float4*)(a.x_out + (size_t)row * d + n0()) = x;
+        if (a.x_keep) *(float4*)(a.x_keep + (size_t)(len + row) * d + n0()) = x;
     }
 }
 
@@ -750,7 +815,15 @@ static bool wide_fits(int d, int heads, int F, bool gated, int cus) {
 
 // Most rows: above eight, which take twice the registers for activations, models of the widest cut alone (its FFN's first weights do not wait in
 // registers while others are multiplied).
-int wide_rows(int d, int heads, int F, bool gated, int cus) { return wide_fits<Cut2048>(d, heads, F, gated, cus) ? kWideRows : kWideRowsMost; }
+// Above sixteen, two row tiles: models of 4096 features, whose layers take long enough to read; as kernels of their own / this, us, 17 and 32
+// rows over 64 tokens, six layers of 2304 (without gate) 410, 415 / 424, 455, of 3072 517, 522 / 515, 556, of 1536 with a hidden state of 8192 (24 rows) 343 / 428.
+int wide_rows(int d, int heads, int F, bool gated, int cus) {
+    return wide_fits<Cut2048>(d, heads, F, gated, cus) ? kWideRows : d < kWideRowsFrom ? 16 : kWideRowsMost;
+}
+
+// Most keys: each row tile goes over a head's keys by itself.  The 7B shape, 17 and 32 rows, kernels of their own / this, us, over 64 tokens 3647, 3663 /
+// 3270, 3488, 1800 3896, 3964 / 3601, 3813, 3200 4067, 4118 / 3840, 4087, 4097 4130, 4178 / 4075, 4268; six layers without a gate, 17, 24, 32 rows over 64, 1500, 2500 609, 610, 615, 654, 655, 658, 674, 679, 688 / 578, 576, 619, 629, 629, 663, 660, 663, 703.
+int wide_keys(int T) { return T <= 16 ? 8192 : T <= 24 ? 4096 : 2048; }
 
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     if (d_head != kWideHead || d <= 1024 || d % 256 != 0 || F % 32 != 0) return 0;
@@ -786,7 +859,7 @@ hipError_t wide_init() {
     static hipError_t done = [] {
 #define BILD_W(CV, RV) (const void*)wide_kernel<false, CV, RV>, (const void*)wide_kernel<true, CV, RV>
         const void* fns[] = {BILD_W(Cut2048, 0), BILD_W(Cut2048, 1), BILD_W(Cut2048, 2), BILD_W(Cut2048Two, 0), BILD_W(Cut2048Two, 1), BILD_W(Cut2048Two, 2),
-                             BILD_W(Cut4096, 0), BILD_W(Cut4096, 1), BILD_W(Cut4096, 2), BILD_W(Cut4096, 16)};
+                             BILD_W(Cut4096, 0), BILD_W(Cut4096, 1), BILD_W(Cut4096, 2), BILD_W(Cut4096, 16), BILD_W(Cut4096Rows, 32)};
 #undef BILD_W
         return raise_lds_limit(fns, 160 * 1024);
     }();
@@ -813,7 +886,8 @@ hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
         else if (small) BILD_WC(Cut2048, RV);                                                                          \
         else BILD_WC(Cut4096, RV);                                                                                     \
     } while (0)
-    if (a.room > 8) BILD_WC(Cut4096, 16);
+    if (a.room > 16) BILD_WC(Cut4096Rows, 32);
+    else if (a.room > 8) BILD_WC(Cut4096, 16);
     else if (a.room == 1) BILD_W(1);
     else if (a.room == 2) BILD_W(2);
     else BILD_W(0);

@@ -171,10 +171,12 @@ def test_who_does_what_changes_with_the_length(shape, monkeypatch):
     assert worst <= min(moved / 4, 2 * parity.logit_tol(cfg))
 
 
-@pytest.mark.parametrize("shape", [dict(), dict(act=bi.ACT_RELU, pos=bi.POS_SINUSOIDAL, d=1280, heads=10, d_ff=96, n_large=4)])
-def test_nine_to_sixteen_rows(shape, monkeypatch):
-    """Models of the widest cut (the large ones): high and low parts in operands of their own, no earlier key up to eight key ranges, the new keys'
-    block whole and short, passes of other rooms between.  Against the separate kernels, as above."""
+@pytest.mark.parametrize("many", [(9, 16, 8, 11, 16, 1, 15), (17, 32, 16, 25, 32, 2, 31)])
+@pytest.mark.parametrize("shape", [dict(), dict(act=bi.ACT_RELU, pos=bi.POS_SINUSOIDAL, d=1280, heads=10, d_ff=96, n_large=4), dict(act=bi.ACT_RELU, pos=bi.POS_SINUSOIDAL, d_ff=96)])
+def test_nine_to_thirty_two_rows(shape, many, monkeypatch):
+    """Models of the widest cut (the large ones): high and low parts in operands of their own, two row tiles, no earlier key up to eight key ranges, the new
+    keys' block whole and short, passes of other rooms between; above sixteen rows the widest models, up to 4096 keys, from 25 rows on
+    2048, beyond which the separate kernels stay.  Against the separate kernels, as above."""
     cfg = bi.toy_pair(**{**BASE, **shape, "max_new": 2100})
     R = Rig(cfg)
     got = {}
@@ -184,18 +186,19 @@ def test_nine_to_sixteen_rows(shape, monkeypatch):
         st.encode(R.src)
         st.debug_enable_logits(True)
         rows_seen = []
-        for have in (R.n0, R.n0 + 24, 300, 1018, 2060):
+        for have in (R.n0, R.n0 + 24, 300, 1018, 2020):
             st.seq_truncate(R.n0)
             if have > R.n0:
                 st.force_tokens(R.n0, bi.make_tokens(cfg.large.vocab, have - R.n0, seed=have), have)
             st.large_verify(float("inf"), draft=[])
             before = st.pass_routes()
-            for rows in (9, 16, 8, 11, 16, 1, 15):
+            for rows in many:
                 st.seq_truncate(have)
                 st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=40 + rows)])
                 rows_seen += [st.debug_logits(pkg.LARGE, i) for i in range(rows)]
             now = {k: v - before[k] for k, v in st.pass_routes().items() if v > before[k]}
-            assert now == {"chip" if one == "1" else "kernels": 7}, (have, now)
+            chip = sum(r <= 16 or (cfg.large.d == 4096 and have + r <= (4096 if r <= 24 else 2048)) for r in many) if one == "1" else 0
+            assert now == {k: n for k, n in (("chip", chip), ("kernels", 7 - chip)) if n}, (have, now)
         got[one] = np.stack(rows_seen)
         moved = one_token_moves(st, R, 300)
         st.close()
