@@ -6,7 +6,8 @@
   python -m paper_2302_07863_amd.profsum passes <kernel_trace.csv> [passes]
 
 `passes` lists, per kernel instantiation and launch size, the launches of the last `passes` (default 10) decoder passes
-of a `bench.py --profile-run --profile-rows T` run (a pass ends with the policy kernel).
+of a `bench.py --profile-run --profile-rows T` run (a pass ends with the policy kernel, or with
+the pass kernel that has the policy inside).
 `stats` groups the template instantiations of one kernel under one name and prints calls,
 total and mean duration.  `pmc` scales FETCH_SIZE / WRITE_SIZE per dispatch by what the same
 counters read for bild::probe_copy_kernel, a plain copy of known size (1 GiB read, 1 GiB written).
@@ -26,6 +27,8 @@ PROBE_BYTES = 1 << 30
 # wrapper (row blocks, bild::gemm_rows_kernel) works in another regime and stays separate.
 _DECODE_GEMM = ("bild::gemm_kernel", "bild::gemm_row_kernel", "bild::gemm_few_kernel", "bild::gemm_merge_kernel",
                 "bild::gemm_pre_kernel", "bild::gemm_merge_nx_kernel", "bild::gemm_part_row_kernel", "bild::gemm_part_few_kernel")
+# The pass kernel and its form with LM head and policy inside: one name, whichever form the passes of a run took.
+_PASS = ("bild::pass_kernel", "bild::pass_head_kernel")
 
 
 def _group(name: str) -> str:
@@ -33,6 +36,8 @@ def _group(name: str) -> str:
     base = re.sub(r"<.*>$", "", name)
     if base in _DECODE_GEMM:
         return "bild::gemm_kernel<*>"
+    if base in _PASS:
+        return "bild::pass_kernel<*>"
     return base + "<*>" if "<" in name else name
 
 
@@ -146,7 +151,7 @@ def verify(path: str) -> str:
 
 def passes(path: str, count: int = 10) -> str:
     rows = sorted(csv.DictReader(open(path)), key=lambda r: int(r["Start_Timestamp"]))
-    fin = [i for i, r in enumerate(rows) if "finish" in r["Kernel_Name"]]
+    fin = [i for i, r in enumerate(rows) if "finish" in r["Kernel_Name"] or "pass_head_kernel" in r["Kernel_Name"]]
     if not fin:
         return "no policy kernel in the trace: not a run of decoder passes"
     lo = fin[-count - 1] + 1 if len(fin) > count else 0
