@@ -52,6 +52,9 @@ int bild_probe_launch(bild_state* s, int reps, float* us_per_launch);
  * (groups = 1) and how the total grows with the number of workgroups.  reps <= 64; the probe allocates
  * groups * kib_per_group KiB * (reps + 1) for its own use (at most 16 GiB, else BILD_EINVAL) and frees it. */
 int bild_probe_stream(bild_state* s, int groups, int kib_per_group, int reps, float* us_per_launch);
+/* Enqueues a kernel on hip_stream that keeps every compute unit of the dies whose bits are set in `dies` (1 .. 255) to itself for `us`
+ * microseconds (at most 100 000), and does nothing else: work of somebody else's beside which passes are run.  Does not wait. */
+int bild_probe_occupy(void* hip_stream, int dies, int us);
 /* GEMM launches ISSUED by the host since the last reset and the algorithmic weight bytes they stream
  * (replays of captured graphs are not counted: meaningful when graph replay is disabled). */
 int bild_gemm_tally(bild_state* s, int64_t* launches, int64_t* bytes, int reset);

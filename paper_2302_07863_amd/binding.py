@@ -86,6 +86,7 @@ _SIGS = {
     "bild_pass_routes": (C.c_int, [C.c_void_p, C.POINTER(C.c_int64)]),
     "bild_debug_pass_spins": (C.c_int, [C.c_void_p, C.c_int]),
     "bild_probe_stream": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_float)]),
+    "bild_probe_occupy": (C.c_int, [C.c_void_p, C.c_int, C.c_int]),
     "bild_probe_launch": (C.c_int, [C.c_void_p, C.c_int, C.POINTER(C.c_float)]),
     "bild_debug_tiled_bytes": (C.c_int64, [C.c_int, C.c_int, C.c_int]),
     "bild_debug_tile_matrix": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]),

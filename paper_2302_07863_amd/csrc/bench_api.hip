@@ -54,6 +54,13 @@ static hipError_t launch_probe_copy(const void* src, void* dst, size_t bytes, hi
     return hipGetLastError();
 }
 
+// Somebody else's work: a workgroup keeps a compute unit of a die of `dies` to itself (all of its LDS) for `us` microseconds.
+__global__ __launch_bounds__(64) void probe_occupy_kernel(const unsigned dies, const unsigned us) {
+    const unsigned die = (unsigned)__builtin_amdgcn_s_getreg((3 << 11) | 20);
+    if (!((dies >> die) & 1u)) return;
+    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();  // (100 MHz)
+    for (unsigned i = 0; i < us && __builtin_amdgcn_s_memrealtime() - t0 < 100ull * us; ++i) __builtin_amdgcn_s_sleep(64);  // (a turn is more than a microsecond)
+}
 
 }  // namespace bild
 
@@ -219,6 +226,18 @@ extern "C" int bild_probe_copy(bild_state* s, int64_t bytes, int reps) {
     (void)hipFree(a);
     (void)hipFree(b);
     return rc;
+}
+
+extern "C" int bild_probe_occupy(void* hip_stream, int dies, int us) {
+    if (dies < 1 || dies > 255 || us < 1 || us > 100000) return BILD_EINVAL;
+    static const hipError_t ready = [] {
+        const void* fns[] = {(const void*)probe_occupy_kernel};
+        return raise_lds_limit(fns, 160 * 1024);
+    }();
+    if (ready != hipSuccess) return BILD_EHIP;
+    hipLaunchKernelGGL(probe_occupy_kernel, dim3(256), dim3(64), 160 * 1024, (hipStream_t)hip_stream, (unsigned)dies, (unsigned)us);
+    HIPC(hipGetLastError());
+    return BILD_OK;
 }
 
 extern "C" int bild_profile_begin(bild_state* s, int max_records) {

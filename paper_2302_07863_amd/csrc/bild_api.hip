@@ -392,7 +392,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
     const int positions = std::max(s->cap_len, s->cap_src);
-    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + 2 * kPassRooms + 2), true);
+    if (s->one_kernel) want(s->pass_sync, sizeof(unsigned) * (kPassSyncWords + kPassTurnWords + 2 * kPassHeadWords), true);
     if (p->m[0]->cfg.dtype == BILD_DT_BF16 || p->m[1]->cfg.dtype == BILD_DT_BF16) {
         want(s->thin_sums, sizeof(float) * kThinSums);
         want(s->thin_arrived, sizeof(unsigned) * kThinArrivals, true);
@@ -1391,6 +1391,9 @@ static bool takes_thin(const bild_state* s, int w, int T) {
 
 // Counts the passes of model w with room for T rows.
 static unsigned* pass_turn(const bild_state* s, int w, int T) { return s->pass_sync + kPassSyncWords + w * kPassRooms + pass_room_index(T); }
+static_assert(2 * kPassRooms <= kPassTurnWords, "a word for each model's rooms");
+// Counts what has started of its passes with the head inside (PassHead::started).
+static unsigned* pass_heads(const bild_state* s, int w) { return s->pass_sync + kPassSyncWords + kPassTurnWords + w * kPassHeadWords; }
 
 static bool two_tiles(const bild_state* s, int w, int T) {
     const ModelState& M = s->ms[w];
@@ -1456,7 +1459,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
             in.vocab = c.vocab;
             in.gain = m->dec_final;
             in.scale = c.logit_scale;
-            in.turn = s->pass_sync + kPassSyncWords + 2 * kPassRooms + w;
+            in.started = pass_heads(s, w);
             pass_head_plan(in, p.at, d, p.f32, s->cus);
             FinishArgs& f = in.f;
             f.ctl = s->ctl;
@@ -1703,6 +1706,7 @@ int pass_gave_up(bild_state* s, int w, int T) {
     const ModelState& M = s->ms[w];
     HIPC(hipMemsetAsync(M.pass_turns[pass_room_index(T)], 0xFF, pass_turns_bytes(M, pass_room_index(T)), s->stream));
     HIPC(hipMemsetAsync(s->pass_sync, 0, sizeof(unsigned) * kPassSyncWords, s->stream));  // (workgroups may have started behind its end)
+    if (T == 1) HIPC(hipMemsetAsync(pass_heads(s, w), 0, sizeof(unsigned) * kPassHeadWords, s->stream));  // (both counts again with one turn, as the memory filled above)
     return BILD_OK;
 }
 

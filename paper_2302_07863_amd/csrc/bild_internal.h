@@ -202,9 +202,9 @@ constexpr int kPassRows = 16, kPassDieRows = 4;
 // The hand-over memory is laid out for 1, 2, 4, 8, 16 or 32 rows.
 constexpr int kPassRooms = 6;
 constexpr int pass_room_index(int rows) { return rows <= 1 ? 0 : rows <= 2 ? 1 : rows <= 4 ? 2 : rows <= 8 ? 3 : rows <= 16 ? 4 : 5; }
-// The ranks given out on a die; on lines of their own, of passes with the head inside (pass_head.h), the ranks given out on the die, mod 32, and on
-// the others; and, the last word: a workgroup gave up
-constexpr int kPassSyncWords = 128, kPassGoingOn = 32, kPassOthers = 64;
+// The ranks given out on a die; on another line, the last word: a workgroup gave up.  Behind them the passes' counts (pass_turn), and for each
+// model the workgroups of its passes with the head inside that have started (pass_head.h): word 0 on die 0, word kPassOthers on the others
+constexpr int kPassSyncWords = 128, kPassTurnWords = 32, kPassHeadWords = 64, kPassOthers = 32;
 struct PassLayer {
     const void *wqkv, *wo, *cwq, *cwo, *win, *wout;
     const float *ln1, *lnc, *ln2;
@@ -253,7 +253,7 @@ struct PassHead {
     float scale;
     int groups;               // workgroups of the other dies
     int at, rec, bytes;       // in PassArgs::scratch, two places of `bytes` each: the hidden state, at `rec` the partials
-    unsigned* turn;           // whose turn it is of the two
+    unsigned* started;        // [kPassHeadWords], counted on from pass to pass
     FinishArgs f;
 };
 struct PassArgs {

@@ -11,8 +11,12 @@
 // instructions' sake, and the weights 7.6 us later, out of the way of the first layer's (0.9 us there, which then came in the next one): no gain.
 //
 // The hidden state and the partials have two places that take turns (a pass fills the other one's with "not there yet"; nobody looks
-// there before the next kernel).  Who joins has seen that every other workgroup has started, and so has read the turn, before
-// it counts the pass; the ranks on die 0 are counted on and on (commit).
+// there before the next kernel).  Rank and turn are one count's, which goes on from pass to pass: 32 a pass on die 0, 256 a pass on the others (the
+// last of the 224 to start adds what is left).  So nobody has to have started for the pass to be counted: other streams' kernels may
+// have any compute unit of these dies, as when head and policy were kernels.  The first workgroup (rank 0) has the parts of those that have not started when it has
+// done its own; who starts behind that does its part once more, the same words in the same place, and ends.  A workgroup waits
+// for the hidden state 64 times as often as others for theirs, 0.3 s: die 0 may be in use too.  Whoever hands something over there has given up before
+// that if it cannot, and the flag is looked at here.
 #pragma once
 #include "pass_walk.h"
 #include "policy_commit.h"
@@ -69,15 +73,16 @@ template <class Cut, class Walk>
 __device__ __forceinline__ void head_part(Walk& c, const PassArgs& a, const PassHead& h) {
     constexpr bool F32 = Walk::F32;
     constexpr int N = Cut::KD, RW = HeadCut<F32>::RW, NV = HeadCut<F32>::NV;
+    unsigned* const others = h.started + kPassOthers;
     if (threadIdx.x == 0) {
-        const unsigned turn = *h.turn;
-        asm volatile("" ::"v"(turn) : "memory");  // (read before this workgroup is counted)
-        ((unsigned*)c.lds)[0] = __hip_atomic_fetch_add(a.sync + kPassOthers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ((unsigned*)c.lds)[1] = turn;
+        const unsigned n = __hip_atomic_fetch_add(others, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((int)(n & 255u) == h.groups - 1) __hip_atomic_fetch_add(others, 256u - (unsigned)h.groups, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // (the last one)
+        *(unsigned*)c.lds = n;
     }
     lds_barrier();
-    const int rank = __builtin_amdgcn_readfirstlane(((volatile int*)c.lds)[0]);
-    const bool odd = c.odd = __builtin_amdgcn_readfirstlane(((volatile int*)c.lds)[1]) & 1;
+    const unsigned before = (unsigned)__builtin_amdgcn_readfirstlane(*(volatile int*)c.lds);
+    const int rank = (int)(before & 255u);
+    const bool odd = c.odd = (before >> 8) & 1u;
     lds_barrier();
     const int units = (h.tn + RW - 1) / RW, workers = min(units, h.groups);
     if (rank >= workers) return;
@@ -85,38 +90,36 @@ __device__ __forceinline__ void head_part(Walk& c, const PassArgs& a, const Pass
     char* const mem = a.scratch + h.at + (odd ? h.bytes : 0);
     const Run r = run_of(c.wave, tk);
     const int n = workers * NV;  // partials
-    auto part = [&](auto several) {
+    // The part of workgroup `who`.
+    auto part = [&](auto several, const int who) {
         constexpr bool MORE = decltype(several)::value;
         uint4 W[MORE ? 2 : 1][N * RW];
-        request<N, RW>(c, W[0], h.w, rank, tk, h.tn);
-        if constexpr (MORE) request<N, RW>(c, W[1], h.w, min(rank + h.groups, units - 1), tk, h.tn);
-        if (rank == 0 && c.wave == 0) {  // everybody has started?
-            int tries = 0;
-            bool missing;
-            do {
-                missing = (int)__hip_atomic_load(a.sync + kPassOthers, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < h.groups;
-                if (missing) __builtin_amdgcn_s_sleep(16);
-            } while (missing && ++tries < c.spins);
-            if (missing) c.give_up();
-        }
-        const Rsrc xs = whole(mem);
+        request<N, RW>(c, W[0], h.w, who, tk, h.tn);
+        if constexpr (MORE) request<N, RW>(c, W[1], h.w, min(who + h.groups, units - 1), tk, h.tn);
+        const Rsrc xs = whole(mem), count = whole(others);
         // ---- the final hidden state ----
         uint4 X;
         unsigned sum = 0u;
         {
             const int beside = F32 ? c.tok : c.tok & 3, last = max(r.n - 1, 0), from = r.n > 0 ? r.k0 * S : 0;
             const int at = (F32 ? c.g * 16 : (c.tok & 4) ? (c.g & 1) * 128 + 64 : (c.g >> 1) * 128 + (c.g & 1) * 32 + (c.tok >> 3) * 16) + min(beside, last) * S;
+            const int most = c.spins > 1 << 24 ? 1 << 30 : 64 * c.spins;
             int tries = 0;
+            unsigned seen = 0u, lost = 0u;
             bool missing;
             do {
                 asm volatile("" ::: "memory");
                 X = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xs, at, from, Walk::kIn));
                 if constexpr (F32) sum = __builtin_amdgcn_raw_buffer_load_b32(xs, min(c.g, last) * S + 64, from, Walk::kIn);
+                if (rank == 0) seen = __builtin_amdgcn_raw_buffer_load_b32(count, 0, 0, Walk::kIn);
+                if ((tries & 15) == 15) lost = __builtin_amdgcn_raw_buffer_load_b32(whole(c.failed), 0, 0, Walk::kIn);
                 const unsigned m = max(max(max(X.x, X.y), max(X.z, X.w)), sum);
                 missing = __builtin_amdgcn_ballot_w64(m == kNotThere) != 0ull && !c.dead;
+                if (__builtin_amdgcn_readfirstlane(lost) != 0u) c.dead = true, missing = false;  // (nobody may be left who would hand it over)
                 if (missing) __builtin_amdgcn_s_sleep(4);  // (0.1 us)
-            } while (missing && ++tries < 4 * c.spins);    // (all of a pass in one wait)
+            } while (missing && ++tries < most);
             if (missing) c.give_up();
+            if (rank == 0 && threadIdx.x == 0) *(unsigned*)(c.lds + kMl + 512) = seen - before;  // (behind the waves' statistics)
         }
         if constexpr (F32) c.ss = quad_rows_sum(c.g < r.n ? __uint_as_float(sum) : 0.f);
         else c.ss = (c.tok & 3) < r.n ? __uint_as_float(X.x) : 0.f;
@@ -178,9 +181,9 @@ __device__ __forceinline__ void head_part(Walk& c, const PassArgs& a, const Pass
             st.s = st.s * fexp_full(st.m - base) + fexp_full(z - base);
             st.m = m;
         };
-        unit(W[0], rank, std::true_type{});
+        unit(W[0], who, std::true_type{});
         if constexpr (MORE) {
-            for (int u = rank + h.groups; u < units; u += 2 * h.groups) {
+            for (int u = who + h.groups; u < units; u += 2 * h.groups) {
                 unit(W[1], u, std::false_type{});
                 if (u + h.groups >= units) break;
                 unit(W[0], u + h.groups, std::false_type{});
@@ -189,16 +192,21 @@ __device__ __forceinline__ void head_part(Walk& c, const PassArgs& a, const Pass
         if (c.wave < NV) {
             const Stat o = join_parts(st);
             if (c.lane == 0) {
-                const int off = h.rec + (rank * NV + c.wave) * 16;
+                const int off = h.rec + (who * NV + c.wave) * 16;
                 __builtin_amdgcn_raw_buffer_store_b128(v4u{__float_as_uint(o.m), __float_as_uint(o.s), (unsigned)o.idx, 0u}, whole(mem), off, 0, 17);
                 __builtin_amdgcn_raw_buffer_store_b128(v4u{kNotThere, kNotThere, kNotThere, kNotThere}, whole(mem + clear), off, 0, 17);
             }
         }
     };
-    if (units > h.groups) part(std::true_type{});
-    else part(std::false_type{});
+    for (int who = rank; who < workers;) {
+        if (units > h.groups) part(std::true_type{}, who);
+        else part(std::false_type{}, who);
+        if (rank != 0) return;
+        // (the first one: then the parts of those that have not started)
+        who = max(who + 1, __builtin_amdgcn_readfirstlane(*(volatile int*)(c.lds + kMl + 512)));
+        lds_barrier();
+    }
     // ---- the partials' join and the policy ----
-    if (rank != 0) return;
     const Controls k(h.f);
     static_assert(256 * NV <= 2 * kPassThreads, "two partials a thread");
     uint4 p[2];
@@ -229,7 +237,6 @@ __device__ __forceinline__ void head_part(Walk& c, const PassArgs& a, const Pass
     if (c.lane < kPassWaves) q = all[c.lane];
     const bool lost = __builtin_amdgcn_ballot_w64(q.pad != 0) != 0ull;
     s = join_parts(Stat{q.m, q.s, q.idx});
-    if (c.lane == 0) *h.turn = odd ? 0u : 1u;
     commit<true>(h.f, k, lost, s.idx, s.m, s.s, 0.f, -1, -1);
 }
 

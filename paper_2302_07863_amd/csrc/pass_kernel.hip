@@ -877,14 +877,15 @@ __global__ __launch_bounds__(kPassThreads, 1) void pass_head_kernel(const PassAr
         head_part<Cut>(c, a, head);
         return;
     }
-    c.odd = *head.turn & 1u;
     if (threadIdx.x == 0) {
-        unsigned rank;
-        asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)" : "=v"(rank) : "v"(a.sync + kPassGoingOn), "v"(1u) : "memory");
-        *(unsigned*)smem = rank;
+        unsigned n;
+        asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)" : "=v"(n) : "v"(head.started), "v"(1u) : "memory");
+        *(unsigned*)smem = n;
     }
     lds_barrier();
-    c.wg = __builtin_amdgcn_readfirstlane(*(volatile int*)smem) & 31;  // (counted on from pass to pass)
+    const unsigned before = (unsigned)__builtin_amdgcn_readfirstlane(*(volatile int*)smem);  // (32 a pass)
+    c.wg = (int)(before & 31u);
+    c.odd = (before >> 5) & 1u;
     if (c.wg >= a.groups) return;
     lds_barrier();
     if (c.wg < a.groups - a.heads) worker<GATED, PACK, Cut>(c, a, a.groups, head);
@@ -982,7 +983,7 @@ hipError_t pass_init() {
 hipError_t launch_pass(const PassArgs& a, const PassHead* head, int grid, hipStream_t st) {
     if (hipError_t e = pass_init(); e != hipSuccess) return e;
     if (a.groups < 1 || grid < a.groups || a.T < 1 || a.T > kPassRows || a.room < a.T || (a.die && !a.f32 && a.T > kPassDieRows) || (a.f32 && !a.die) || !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr ||
-        (a.cross && !a.nsrc_ptr) || (head && (!a.die || a.room != 1 || !head->w || !head->gain || !head->turn || head->groups != grid - grid / 8 || !head->f.ctl)))
+        (a.cross && !a.nsrc_ptr) || (head && (!a.die || a.room != 1 || !head->w || !head->gain || !head->started || grid != 256 || head->groups != grid - grid / 8 || !head->f.ctl)))
         return hipErrorInvalidValue;
     const size_t smem = kRel + (a.rel_bias ? (size_t)(2 * a.rel_d + 1) * 4 : 0);
     if (smem > 160 * 1024) return hipErrorInvalidValue;

@@ -25,8 +25,7 @@ struct Controls {
 // link, and a system-wide fence writes the L2 back besides: 5 us for this kernel and 10 us for a wide one.)
 // `failed`: the pass kernel's workgroups did not all run: nothing happened but the count of passes.  z_draft: logit of draft t; drawn: the
 // sampling variant's token (-1: none); r_given: the first draft that the rejection rule refused (-1: the threshold decides).
-// INSIDE: in the pass kernel itself (pass_head.h).  The ranks given out on die 0 stay then: its L2 holds their line, and what is written here
-// from another die could be overwritten by it.
+// INSIDE: in the pass kernel itself (pass_head.h), whose counts go on; the flag of a failed pass stays for its workgroups that still wait (pass_gave_up).
 template <bool INSIDE = false>
 __device__ __forceinline__ void commit(const FinishArgs& a, const Controls& k, bool failed, int row_tok, float row_max, float row_sum, float z_draft, int drawn, int r_given) {
     const int lane = (int)threadIdx.x & 63, w = a.which, n = a.T - 1;
@@ -45,7 +44,7 @@ __device__ __forceinline__ void commit(const FinishArgs& a, const Controls& k, b
     }
     if (a.sync) {
         if (lane == 0 && a.turn) *a.turn = k.turn == 2u ? 0u : k.turn + 1u;
-        if (lane == 0) a.sync[INSIDE ? kPassOthers : 0] = a.sync[kPassSyncWords - 1] = 0u;
+        if (!INSIDE && lane == 0) a.sync[0] = a.sync[kPassSyncWords - 1] = 0u;
         if (failed) {
             if (lane == 0) {
                 c->seq = c_seq + 1;
