@@ -84,6 +84,10 @@ int64_t bild_pass_bytes(const bild_state* s, int which, int t_cache, int rows);
 int64_t bild_debug_tiled_bytes(int n, int k, int dtype);
 int bild_debug_tile_matrix(const float* src, int src_is_k_by_n, int n, int k, int dtype, void* dst);
 int bild_debug_gemm_shape(int n, int k, int rows, int gated, int lm_head, int dtype, int32_t out[8]);
+/* The launch shape of a bf16 projection of n features x k inputs over many rows (encoder, prompt): out = {rows and features of a
+ * workgroup, input slices, 1 if the rows go through LDS, workgroups on the die with most of them}.  gated: n counts gate and linear branch;
+ * rotary: queries, keys and values with rotary positions. */
+int bild_debug_tile_shape(int n, int k, int rows, int gated, int rotary, int32_t out[5]);
 /* The launch shape of attention for `rows` query rows over nkeys cached keys: out = {key splits, 1 if the consumer
  * projection merges the split partials (no merge kernel), waves per workgroup, dynamic LDS bytes}. */
 int bild_debug_attn_shape(int heads, int d_head, int rows, int nkeys, int max_splits, int dtype, int32_t out[4]);

@@ -92,6 +92,7 @@ _SIGS = {
     "bild_debug_tile_matrix": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]),
     "bild_debug_cache_rule": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
     "bild_debug_wide_split": (C.c_int, [C.c_int] * 6 + [C.POINTER(C.c_int32)]),
+    "bild_debug_tile_shape": (C.c_int, [C.c_int] * 5 + [C.POINTER(C.c_int32)]),
     "bild_debug_attn_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
     "bild_debug_gemm_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
     "bild_probe_copy": (C.c_int, [C.c_void_p, C.c_int64, C.c_int]),
@@ -382,6 +383,12 @@ def gemm_shape(n: int, k: int, rows: int, gated: bool = False, lm_head: bool = F
     _check(lib().bild_debug_gemm_shape(n, k, rows, int(gated), int(lm_head), dtype, out), "bild_debug_gemm_shape")
     keys = ("wk", "nwv", "rw", "kc", "blocks", "row_blocks", "lds", "lds_limit")
     return dict(zip(keys, [int(v) for v in out]))
+
+
+def tile_shape(n: int, k: int, rows: int, gated: bool = False, rotary: bool = False) -> dict:
+    out = (C.c_int32 * 5)()
+    _check(lib().bild_debug_tile_shape(n, k, rows, int(gated), int(rotary), out), "bild_debug_tile_shape")
+    return dict(zip(("rows", "features", "slices", "shared", "busiest"), [int(v) for v in out]))
 
 
 def attn_shape(heads: int, d_head: int, rows: int, nkeys: int, max_splits: int = 8, dtype: int = 1) -> dict:

@@ -324,6 +324,25 @@ extern "C" int bild_debug_gemm_shape(int n, int k, int rows, int gated, int lm_h
     return BILD_OK;
 }
 
+extern "C" int bild_debug_tile_shape(int n, int k, int rows, int gated, int rotary, int32_t out[5]) {
+    if (!out || n < 1 || k < 32 || k % 32 || rows < 1) return BILD_EINVAL;
+    const double2 table = {};
+    TileGemmArgs g;
+    std::memset((void*)&g, 0, sizeof(g));
+    g.W.n = n;
+    g.W.k = k;
+    g.W.tn = (n + 15) / 16;
+    g.W.tk = k / 32;
+    g.M = rows;
+    g.epi = gated ? EPI_ACT : rotary ? EPI_QKV : EPI_RESID;
+    g.act = gated ? BILD_ACT_SWIGLU : BILD_ACT_RELU;
+    g.rope = rotary ? &table : nullptr;
+    int o[5];
+    tile_gemm_shape(g, o);
+    std::copy(o, o + 5, out);
+    return BILD_OK;
+}
+
 extern "C" int bild_debug_attn_shape(int heads, int d_head, int rows, int nkeys, int max_splits, int dtype, int32_t out[4]) {
     if (!out || heads < 1 || d_head < 8 || d_head > 128 || rows < 1 || nkeys < 1 || max_splits < 1 || dtype < 0 || dtype > 1)
         return BILD_EINVAL;

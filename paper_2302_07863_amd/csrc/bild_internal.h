@@ -434,6 +434,7 @@ struct TileGemmArgs {
     int fgs, rbs, gr;       // (set by the launcher) feature groups, row blocks, row shares of the dies
 };
 int tile_gemm_parts(const TileGemmArgs& a);
+void tile_gemm_shape(const TileGemmArgs& a, int (&out)[5]);  // (see bild_debug_tile_shape)
 hipError_t launch_gemm_tile(const TileGemmArgs& a, hipStream_t st);
 hipError_t launch_embed_tiles(const EmbedArgs& a, char* np, hipStream_t st);
 // row copy (see RowCopyArgs; dst null: no copy) that also leaves the rows' planes times `gain` and their sums of squares

@@ -17,6 +17,8 @@
 // one is multiplied.  Waves of a workgroup share nothing in the loop (no barrier, no LDS): either they own different
 // features of the same rows (the rows' operands then come from the vector cache), or, where a product has too few tiles
 // to occupy the chip, they take slices of the inputs and add their sums in LDS at the end, in a fixed order.
+#include <algorithm>
+
 #include "kernel_common.h"
 
 namespace bild {
@@ -477,25 +479,46 @@ hipError_t launch_rope_table(double2* table, int positions, int d_head, float ba
 // for products that they cut into one round where the others make a round and a bit of another: 1531 rows, features x inputs, us, best of the others /
 // with: 3072 x 1024 (256 workgroups of 96 x 192) 31.4 / 25.4, 4096 x 1024 (256 of 96 x 256) 31.0 / 27.4, 1024 x 4096 (256 of 48 x 128) 42.5 / 34.1, but
 // 1024 x 1024 16.4 / 17.6.  Measured beside them and not taken: sliced, 96 x 64 as 48 x 128; 64 x 96, which gains 1 us at 512 x 3072 x 1024 alone; 64 x 128.
+// One round is 32 workgroups on the busiest die, not 256 of them (features x inputs, rows, us, best of the others / with, 33 to 44 on that
+// die): 768 x 3072, 2016 rows 29.5 / 44.4; 5632 x 1024 gated, 1056 28.4 / 38.0; 3072 x 1024, 2016 31.2 / 41.9; 4096 x 4096, 1056 97 / 105.
+// Weights from memory are no reason against them: 12288 x 4096 rotary, 80, 352, 432 rows 43.7, 98.9, 100.5 / 40.2, 76.7, 92.8; 22016 x 4096 gated, 40 55.2 / 47.9;
+// 4096 x 4096, 320 44.6 / 34.8; 4096 x 11008, 320 105.7 / 72.7; 6144 x 2048 rotary, 704 53.7 / 45.5; 2048 x 5504, 640 54.0 / 41.3; 11008 x 2048 gated, 464 51.5 / 45.1.
+// The epilogue of so many sums is dear where there are few inputs, with the rotation in double precision above all, so there is a least number of input
+// tiles (`from`, with rotation `turned`).  Ratio to the others, 1200 products of 128 to 11008 inputs drawn at random, 96 x 256: rotary 1.21 to 1.34 up to 1024 inputs,
+// 1.07 to 1.16 at 1280 and 1536, 0.98 to 1.03 at 2048, 0.95 to 1.06 at 2560 to 3072, 0.88 to 0.94 at 4096; the others 0.96 to 1.14 up to 640, 0.77 to 1.00 from 768 on.
+// 96 x 192: rotary 0.85 to 1.04 up to 768, 0.73 to 1.00 from 1024 on; the others 0.56 to 0.92.  48 x 128 (by its cost from 2560 inputs on) 0.67 to 0.98.
 struct TileShape {
     int rt, ft, wk;
     bool share;
     float us, once;
-    bool fills;  // only where it makes one round
+    int from, turned;  // > 0: only where it makes one round, and from so many input tiles on
 };
+// Row shares of the dies (see tile_block): every feature share fetches all its rows, every row share all its weights; least bytes into the
+// eight L2s, without leaving dies idle where there are few row blocks or feature groups.  Returns the workgroups of the busiest die.
+static long die_shares(const TileGemmArgs& a, int rbs, int fgs, int& best) {
+    long least = 0, most = 0;
+    for (int gr = 1; gr <= 8; gr *= 2) {
+        const int gf = 8 / gr;
+        const long slots = (long)((rbs + gr - 1) / gr) * ((fgs + gf - 1) / gf);
+        const long cost = (long)(gf * (long)a.M * 4 + gr * (long)a.W.n * 2) * (slots * 8 * 4 > 5 * (long)rbs * fgs ? 4 : 1) * 16 + slots;
+        if (gr == 1 || cost < least) { least = cost; most = slots; best = gr; }
+    }
+    return most;
+}
 static TileShape tile_shape(const TileGemmArgs& a) {
-    static const TileShape shapes[] = {{8, 4, 1, true, 0.94f, 0.f, false}, {4, 4, 1, true, 0.57f, 0.f, false}, {4, 4, 2, false, 0.84f, 0.f, false},
-                                       {4, 4, 4, false, 0.80f, 0.f, false}, {4, 2, 4, false, 0.69f, 0.f, false}, {4, 1, 4, false, 0.60f, 0.f, false},
-                                       {2, 4, 4, false, 0.56f, 0.f, false}, {2, 2, 4, false, 0.42f, 0.f, false}, {2, 1, 4, false, 0.36f, 0.f, false},
-                                       {6, 4, 1, true, 0.83f, 0.f, true}, {6, 3, 1, true, 0.75f, 0.f, true}, {3, 8, 4, false, 0.70f, 11.f, true}};
+    static const TileShape shapes[] = {{8, 4, 1, true, 0.94f, 0.f, 0, 0}, {4, 4, 1, true, 0.57f, 0.f, 0, 0}, {4, 4, 2, false, 0.84f, 0.f, 0, 0},
+                                       {4, 4, 4, false, 0.80f, 0.f, 0, 0}, {4, 2, 4, false, 0.69f, 0.f, 0, 0}, {4, 1, 4, false, 0.60f, 0.f, 0, 0},
+                                       {2, 4, 4, false, 0.56f, 0.f, 0, 0}, {2, 2, 4, false, 0.42f, 0.f, 0, 0}, {2, 1, 4, false, 0.36f, 0.f, 0, 0},
+                                       {6, 4, 1, true, 0.83f, 0.f, 24, 128}, {6, 3, 1, true, 0.75f, 0.f, 1, 32}, {3, 8, 4, false, 0.70f, 11.f, 1, 1}};
     const bool gated = a.epi == EPI_ACT && a.act != BILD_ACT_RELU;
     const TileShape* best = nullptr;
     float least = 0.f;
     for (const TileShape& t : shapes) {
         if (gated && t.ft % 2) continue;
         const int rows = t.rt * 16, feats = t.ft * (kTileWaves / t.wk);
-        const int rounds = (((a.M + rows - 1) / rows) * ((a.W.tn + feats - 1) / feats) + 255) / 256;
-        if (t.fills && rounds > 1) continue;
+        const int rbs = (a.M + rows - 1) / rows, fgs = (a.W.tn + feats - 1) / feats, rounds = (rbs * fgs + 255) / 256;
+        int gr;
+        if (t.from > 0 && (a.W.tk < (a.rope ? t.turned : t.from) || die_shares(a, rbs, fgs, gr) > 32)) continue;
         const float us = (float)((a.W.tk + t.wk - 1) / t.wk) * t.us * (rounds == 1 ? 1.f : 0.8f * (float)rounds) + t.once;
         if (!best || us < least) { best = &t; least = us; }
     }
@@ -506,6 +529,15 @@ int tile_gemm_parts(const TileGemmArgs& a) {
     const TileShape t = tile_shape(a);
     const int per = t.ft * (kTileWaves / t.wk);
     return (a.W.tn + per - 1) / per;
+}
+
+void tile_gemm_shape(const TileGemmArgs& a, int (&out)[5]) {
+    const TileShape t = tile_shape(a);
+    const int rows = t.rt * 16;
+    int gr;
+    const long most = die_shares(a, (a.M + rows - 1) / rows, tile_gemm_parts(a), gr);
+    const int o[5] = {rows, t.ft * (kTileWaves / t.wk) * 16, t.wk, t.share, (int)most};
+    std::copy(o, o + 5, out);
 }
 
 hipError_t gemm_tile_init() {
@@ -544,17 +576,7 @@ hipError_t launch_gemm_tile(const TileGemmArgs& a0, hipStream_t st) {
     const int rows = t.rt * 16;
     a.fgs = tile_gemm_parts(a);
     a.rbs = (a.M + rows - 1) / rows;
-    // dies in gr row shares x 8 / gr feature shares: every feature share fetches all its rows, every row share all its weights;
-    // least bytes into the eight L2s, without leaving dies idle where there are few row blocks or feature groups
-    long least = 0;
-    for (int gr = 1; gr <= 8; gr *= 2) {
-        const int gf = 8 / gr;
-        const long slots = (long)((a.rbs + gr - 1) / gr) * ((a.fgs + gf - 1) / gf);  // workgroups of the busiest die
-        const long cost = (long)(gf * (long)a.M * 4 + gr * (long)a.W.n * 2) * (slots * 8 * 4 > 5 * (long)a.rbs * a.fgs ? 4 : 1) * 16 + slots;
-        if (gr == 1 || cost < least) { least = cost; a.gr = gr; }
-    }
-    const int gf = 8 / a.gr;
-    const dim3 grid((unsigned)(8 * ((a.rbs + a.gr - 1) / a.gr) * ((a.fgs + gf - 1) / gf))), block(64 * kTileWaves);
+    const dim3 grid((unsigned)(8 * die_shares(a, a.rbs, a.fgs, a.gr))), block(64 * kTileWaves);
     // (shared forms: what the largest needs; 16 KiB for 64 rows without spreading: 1531 x 1024 inputs the same, 1290 an encode 0.7 % slower)
     const size_t smem = (size_t)tile_sums(t.rt) * 4 + (t.share ? (size_t)32 * 1024 : a.wk > 1 ? (size_t)kTileWaves * t.rt * t.ft * 1024 : 0);
 #define BILD_T(RTV, FTV, EPIV, ROPEV, GV, SP, SH)                                                                            \

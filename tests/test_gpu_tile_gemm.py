@@ -6,6 +6,7 @@ import pytest
 
 import bild_inputs as bi
 import oracle
+from paper_2302_07863_amd import binding as b
 from tests import parity
 from tests.test_gpu_parity import Rig
 
@@ -60,3 +61,16 @@ def test_products_cut_into_one_round(n_src, act, heads, d_ff):
     """Workgroups of 96 rows x 192 and 256 features and of 48 x 128 (the large model, twice as wide): the last rows' block nearly whole, of a
     single row, whole; the last features' block short."""
     _check(bi.toy_pair(dtype=bi.DT_BF16, act=act, truncate=True, d=512, heads=heads, d_head=64, d_ff=d_ff, n_src=n_src, max_new=4, vocab=300, n_large=1, logit_scale=4.0))
+
+
+@pytest.mark.parametrize("n_src,d,heads,d_ff,takes", [(151, 2560, 20, 4096, {"qkv": (48, 128), "ffn": (48, 128)}), (343, 2560, 32, 1024, {"qkv": (96, 192)}),
+                                                      (451, 4096, 32, 1024, {"qkv": (96, 256)})])
+def test_prompts_cut_into_one_round(n_src, d, heads, d_ff, takes):
+    """The same launch shapes with rotary positions and a gated hidden state: a row block of 6, 54 and 66 rows at the end."""
+    inner, rows = heads * 128, n_src - 1  # (the prompt's last token is a pass' first row)
+    for what, (n, k, gated, rotary) in {"qkv": (3 * inner, d, False, True), "out": (d, inner, False, False), "ffn": (2 * d_ff, d, True, False)}.items():
+        s = b.tile_shape(n, k, rows, gated, rotary)
+        if what in takes:
+            assert (s["rows"], s["features"]) == takes[what], (what, s)
+    _check(bi.toy_pair(dtype=bi.DT_BF16, act=bi.ACT_SWIGLU, pos=bi.POS_ROPE, cross=False, tied=False, d=d, heads=heads, d_head=128, d_ff=d_ff, n_src=n_src, max_new=3, vocab=300, n_small=1,
+                       n_large=2, logit_scale=4.0))

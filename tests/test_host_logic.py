@@ -184,3 +184,24 @@ def test_tiles_of_a_wide_pass_at_the_lines_of_the_rule():
     tiles = lambda d, heads, units: [b.wide_split(d, heads, 5632, True, units, keys)["qkv_tiles"] for keys in (1280, 1281, 2304, 2305, 8192)]
     assert tiles(2048, 16, 256) == [3, 2, 2, 3, 3] and tiles(2048, 16, 191) == [3, 3, 3, 3, 3]
     assert tiles(1280, 10, 256) == [3, 2, 2, 2, 2] and tiles(4096, 32, 256) == [3] * 5 and tiles(2560, 20, 256) == [3] * 5
+
+
+ONE_ROUND = {(96, 256): (768, 4096), (96, 192): (32, 1024), (48, 128): (32, 32)}  # least inputs, and with rotary positions
+
+
+@pytest.mark.parametrize("n,k,gated,rotary", [(768, 3072, 0, 0), (5632, 1024, 1, 0), (3072, 1024, 0, 0), (4096, 1024, 0, 0), (1024, 4096, 0, 0), (4096, 4096, 0, 0), (6144, 2048, 0, 1),
+                                              (12288, 4096, 0, 1), (22016, 4096, 1, 0), (4096, 11008, 0, 0), (3072, 640, 0, 1), (4608, 384, 0, 0), (3072, 768, 0, 0)])
+def test_tile_shapes_of_one_round_make_one_on_every_die(n, k, gated, rotary):
+    """Launch shapes that pay where each compute unit has one workgroup: no die has more than its 32, and enough inputs for their epilogue."""
+    seen = set()
+    for rows in range(33, 2049):
+        s = b.tile_shape(n, k, rows, bool(gated), bool(rotary))
+        shape = (s["rows"], s["features"])
+        if shape in ONE_ROUND:
+            seen.add(shape)
+            assert s["busiest"] <= 32, (rows, s)
+            assert k >= ONE_ROUND[shape][rotary], (rows, s)
+    want = {(768, 3072): {(48, 128)}, (3072, 1024): {(96, 256), (96, 192)}, (12288, 4096): set(ONE_ROUND), (22016, 4096): {(48, 128)}, (6144, 2048): {(96, 192)},
+            (3072, 640): set(), (4608, 384): {(96, 192)}, (4096, 4096): {(96, 256), (48, 128)}}
+    if (n, k) in want:
+        assert seen == want[n, k]
