@@ -389,6 +389,7 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (const char* fe = std::getenv("BILD_FUSE_EMBED")) s->fuse_embed = std::atoi(fe) != 0;  // tests and measurements
         if (const char* kd = std::getenv("BILD_KSPLIT_MAX_D")) s->ksplit_max_d = std::atoi(kd);
         if (const char* tr = std::getenv("BILD_THIN_MIN_ROWS")) s->thin_min_rows = std::atoi(tr);  // tests and measurements
+        if (const char* wr = std::getenv("BILD_WIDE_ROWS")) s->wide_most_rows = std::atoi(wr);  // tests and measurements
         if (const char* km = std::getenv("BILD_KSPLIT_MIN_F")) s->ksplit_min_f = std::atoi(km);  // tests: small widths; 0 turns the split off
     }
     const int positions = std::max(s->cap_len, s->cap_src);
@@ -451,7 +452,10 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
         if (s->one_kernel && in_int && bf16 && !m->cfg.cross_attn && m->cfg.pos != BILD_POS_RELATIVE && !M.pass_groups) {
             M.pass_groups = wide_groups((int)d, m->cfg.n_heads, m->cfg.d_head, (int)F, m->gated(), s->cus);
             M.pass_wide = M.pass_groups > 0;
-            if (M.pass_wide) M.pass_wide_rows = wide_rows((int)d, m->cfg.n_heads, (int)F, m->gated(), s->cus);
+            if (M.pass_wide) {
+                const int most = wide_most((int)d, m->cfg.n_heads, (int)F, m->gated(), s->cus);
+                M.pass_wide_rows = s->wide_most_rows > 0 ? std::min(most, s->wide_most_rows) : wide_rows((int)d, m->cfg.n_heads, (int)F, m->gated(), s->cus);
+            }
         }
         M.nparts_cap = m->head.tn + 1;  // at most one partial per feature tile
         want(M.part, sizeof(StatPart) * (size_t)M.nparts_cap * kMaxRows);
@@ -1633,10 +1637,10 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // at 2200 204, 231, 243, 266 / 133, 134, 148, 159, at 8100 256, 263, 275, 300 / 222, 223, 232, 241; 2048 wide 221, 255, 270, 275 / 156, 158, 166, 180,
 // at 2200 274, 314, 331, 327 / 200, 201, 213, 224, at 8100 330, 338, 355, 388 / 295, 297, 302, 312; 3072 wide 366, 384, 425, 374 / 284, 288, 316, 336
 // and at 8100 530, 548, 590, 543 / 451, 456, 484, 507; 4096 wide 525, 567, 569, 572 / 455, 458, 465, 480 and 719, 759, 760, 766 / 648, 651,
-// 660, 681: never slower up to the 8192 positions that were measured.
+// 660, 681: never slower up to the 8192 positions that were measured.  More rows: wide_rows, wide_keys.
 static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
-    if (s->ms[w].pass_wide) return s->one_kernel && T <= s->ms[w].pass_wide_rows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= wide_keys(T);
+    if (s->ms[w].pass_wide) return s->one_kernel && T <= s->ms[w].pass_wide_rows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= wide_keys(T, s->ms[w].m->cfg.d_model);
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
            s->n_src <= (s->ms[w].m->cfg.dtype == BILD_DT_F32 ? 1024 : on_one_die(s, w, T) ? 1280 : T == 1 ? 1408 : 1536) && s->len[w] + T <= 1024;
 }

@@ -296,16 +296,17 @@ void pass_head_plan(PassHead& h, const PassPlan& at, int d, bool f32, int cus); 
 PassPlan pass_plan(int room, int d, int I, int F, bool f32, bool wide);
 // head null: LM head and policy follow as kernels
 hipError_t launch_pass(const PassArgs& a, const PassHead* head, int grid, hipStream_t st);
-constexpr int kWideRows = 8, kWideRowsMost = 32, kWideRowsFrom = 4096, kWideHead = 128;  // most rows (wide_rows), the width from which on; features of a head
+constexpr int kWideRows = 8, kWideRowsMost = 32, kWideRowsFrom = 4096, kWideHead = 128;  // most rows (wide_most), the width from which on; features of a head
 constexpr int kWideSplits = 8;                 // most key ranges of a head
 constexpr int kWideApart = 1280;               // most keys with which heads and projections are different workgroups'
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // as pass_groups, of pass_wide.hip
+int wide_most(int d, int heads, int F, bool gated, int cus);
 int wide_rows(int d, int heads, int F, bool gated, int cus);
-int wide_keys(int T);
+int wide_keys(int T, int d);
 bool wide_two(int d, int heads, int F, bool gated, int cus, int keys);
-// who does what in a pass that ends with `keys` keys (wide_parts): {tiles of q, k, v a workgroup, its first workgroup, the same of the FFN's
-// input, the heads' first workgroup, ranges, apart}; false: not a shape it is made for
-bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int out[7]);
+// who does what in a pass of `rows` rows that ends with `keys` keys (wide_parts): {tiles of q, k, v a workgroup, its first workgroup, the same of the
+// FFN's input, the heads' first workgroup, ranges, apart}; false: such passes are kernels of their own
+bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int rows, int out[7]);
 hipError_t launch_wide(const PassArgs& a, hipStream_t st);
 
 struct EmbedArgs {

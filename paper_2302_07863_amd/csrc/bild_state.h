@@ -229,7 +229,7 @@ struct ModelState {
     int pass_groups = 0;      // workgroups; 0: the shape is not made for it
     int pass_die_groups = 0;  // the same of the form on one die
     bool pass_wide = false;   // the form of pass_wide.hip
-    int pass_wide_rows = 0;   // most rows there
+    int pass_wide_rows = 0;   // most rows of passes there
     bild::PassLayer* pass_layers = nullptr;  // device
     int pass_die_rows = 0;    // most rows there (the small model's passes with an LM head have one)
     char* pass_turns[bild::kPassRooms] = {};  // what its workgroups hand over, by the rows there is room for
@@ -255,6 +255,7 @@ struct bild_state {
     unsigned* thin_arrived = nullptr;
     float* split_part = nullptr;  // of the workgroups that share a head's keys
     unsigned* split_arrived = nullptr;
+    int wide_most_rows = 0;   // > 0: passes of wide models in one kernel have up to so many rows, where there is a kernel for them (else see wide_rows)
     int thin_min_rows = 0;    // > 0: passes of a bf16 model from so many rows on take the thin GEMM (else see takes_thin)
     unsigned* pass_sync = nullptr;
     bool last_one = false;    // the pass issued last is one kernel

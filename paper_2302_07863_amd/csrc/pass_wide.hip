@@ -813,17 +813,34 @@ static bool wide_fits(int d, int heads, int F, bool gated, int cus) {
            d / 16 <= cus && heads <= cus;
 }
 
-// Most rows: above eight, which take twice the registers for activations, models of the widest cut alone (its FFN's first weights do not wait in
-// registers while others are multiplied).
-// Above sixteen, two row tiles: models of 4096 features, whose layers take long enough to read; as kernels of their own / this, us, 17 and 32
-// rows over 64 tokens, six layers of 2304 (without gate) 410, 415 / 424, 455, of 3072 517, 522 / 515, 556, of 1536 with a hidden state of 8192 (24 rows) 343 / 428.
-int wide_rows(int d, int heads, int F, bool gated, int cus) {
-    return wide_fits<Cut2048>(d, heads, F, gated, cus) ? kWideRows : d < kWideRowsFrom ? 16 : kWideRowsMost;
+// Most rows there is a kernel for: above eight, which take twice the registers for activations, models of the widest cut alone (its FFN's first
+// weights do not wait in registers while others are multiplied); above sixteen, two row tiles and twice the workgroups of heads, 4096-wide ones.
+int wide_most(int d, int heads, int F, bool gated, int cus) {
+    return wide_fits<Cut2048>(d, heads, F, gated, cus) ? kWideRows : d < kWideRowsFrom || 2 * heads > cus ? 16 : kWideRowsMost;
 }
 
-// Most keys: each row tile goes over a head's keys by itself.  The 7B shape, 17 and 32 rows, kernels of their own / this, us, over 64 tokens 3647, 3663 /
-// 3270, 3488, 1800 3896, 3964 / 3601, 3813, 3200 4067, 4118 / 3840, 4087, 4097 4130, 4178 / 4075, 4268; six layers without a gate, 17, 24, 32 rows over 64, 1500, 2500 609, 610, 615, 654, 655, 658, 674, 679, 688 / 578, 576, 619, 629, 629, 663, 660, 663, 703.
-int wide_keys(int T) { return T <= 16 ? 8192 : T <= 24 ? 4096 : 2048; }
+// Most rows it is taken for: the layers' weights have to take long enough to read, as that is what it does better than kernels of their own.
+// Its time over theirs, six layers, least and most of 9, 10, 12, 16 rows over 64, 1000, 2500, 5000, 8000 tokens.  4096 wide, without a gate, hidden
+// state of 1024 1.07 to 1.15, 2048 1.07 to 1.11, 4096 1.02 to 1.04, 5120 0.94 to 0.98, 8192 0.89 to 0.94, 11008 0.89 to 0.91; gated 2048 1.02 to 1.05, 3072 0.98 to 1.02,
+// 4096 0.95 to 0.96, 5120 0.91 to 0.94, 11008 0.86 to 0.88, heads of half the width 5120 0.92 to 1.02 and 0.95 to 1.05 without a gate.  3584 and 3072 wide, 1.5 and 2
+// times as wide a hidden state without a gate 0.92 to 1.00, gated 1.3 times 0.96 to 1.04, 2 times 0.92 to 1.00, heads of half the width 0.98 to 1.09.  2560 and 2304 wide, without a
+// gate 1 and 1.5 times 1.01 to 1.13, 2 times 0.96 to 1.01, 4 times 0.86 to 0.91; gated 1 and 1.3 times 0.97 to 1.07, 2 times 0.94 to 1.01, 2.7 times 0.90 to 0.99; heads
+// of half the width 0.99 to 1.12.  2048 wide (hidden states above 6144) without a gate 0.98 to 1.15, gated 0.91 to 1.08: not taken.  Narrower ones, whose separate kernels are others
+// (takes_thin), up to 5000 tokens: without a gate 6912 and 7168 0.84 to 1.02, 8192 0.80 to 1.00, gated 0.79 to 0.94, heads of half the width 0.91 to 1.09; 8000 tokens 0.87 to 1.10.
+// 17, 24, 25, 32 rows over 64, 700, 1500, 2016 tokens (25 and 32 not further), 3000, 4072: without a gate 4096 1.06 to 1.18, 6144 0.93 to 1.05, 8192 0.93 to 1.03, 8704
+// 0.85 to 0.95, 9216 0.86 to 0.95; gated 4096 0.98 to 1.10, 6144 0.96 to 1.08, 8192 0.96 to 1.06, 8704 0.89 to 0.99, 9216 0.89 to 0.98, 11008 0.89 to 0.97 (heads of 3072
+// 0.89 to 0.97; 8704 and heads of 2048 0.81 to 0.96).
+int wide_rows(int d, int heads, int F, bool gated, int cus) {
+    const int most = wide_most(d, heads, F, gated, cus);
+    if (most <= kWideRows || (d >= kWideRowsFrom && F >= 8704)) return most;
+    const bool taken = heads * kWideHead >= d && (d >= 4096 ? F >= 5120 : d >= 2304 ? F >= 2 * d : d < 2048 && (gated || F >= 8192));
+    return taken ? std::min(most, 16) : kWideRows;
+}
+
+// Most keys of a pass of T rows.  Each of two row tiles goes over a head's keys by itself: the 7B shape, 17, 24, 25, 32 rows, kernels of their own / this, us, over 64
+// tokens 3599, 3609, 3628, 3622 / 3270, 3265, 3492, 3496, 2016 3771, 3790, 3811, 3820 / 3429, 3434, 3666, 3674, 3200 3925, 3942 / 3684, 3687, 4072 3967, 3988 / 3856, 3857; 32 rows
+// over 3200 and 4097 4118, 4178 / 4087, 4268.  Narrow models: see wide_rows.
+int wide_keys(int T, int d) { return T <= 8 ? 8192 : T <= 16 ? (d < 2048 ? 5120 : 8192) : T <= 24 ? 4096 : 2048; }
 
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     if (d_head != kWideHead || d <= 1024 || d % 256 != 0 || F % 32 != 0) return 0;
@@ -841,16 +858,17 @@ bool wide_two(int d, int heads, int F, bool gated, int cus, int keys) {
     return wide_fits<Cut2048Two>(d, heads, F, gated, cus) && keys > kWideApart && (keys <= 2304 || two <= cus - heads * wide_splits(keys, heads, cus));
 }
 
-bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int out[7]) {
-    if (!wide_groups(d, heads, kWideHead, F, gated, cus)) return false;
+bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int rows, int out[7]) {
+    if (!wide_groups(d, heads, kWideHead, F, gated, cus) || rows > wide_rows(d, heads, F, gated, cus) || keys > wide_keys(rows, d)) return false;
     const int tq = 3 * heads * kWideHead / 16, tf = gated ? F / 8 : F / 16;
     auto is = [&](auto cut) {
         using Cut = decltype(cut);
-        const WideParts p = wide_parts<Cut>(keys, d, heads, tq, tf, cus);
+        const WideParts p = wide_parts<Cut>(keys, d, heads * (rows > 16 ? 2 : 1), tq, tf, cus);
         out[0] = Cut::QT; out[1] = p.q; out[2] = Cut::FT; out[3] = p.i; out[4] = p.head0; out[5] = p.ranges; out[6] = p.apart;
     };
     if (wide_two(d, heads, F, gated, cus, keys)) is(Cut2048Two());
     else if (wide_fits<Cut2048>(d, heads, F, gated, cus)) is(Cut2048());
+    else if (rows > 16) is(Cut4096Rows());
     else is(Cut4096());
     return true;
 }
@@ -869,7 +887,7 @@ hipError_t wide_init() {
 hipError_t launch_wide(const PassArgs& a, hipStream_t st) {
     if (hipError_t e = wide_init(); e != hipSuccess) return e;
     const bool gated = a.act != BILD_ACT_RELU;
-    if (a.groups < 1 || a.groups != wide_groups(a.d, a.heads, a.I / std::max(a.heads, 1), a.F, gated, a.groups) || a.T < 1 || a.T > wide_rows(a.d, a.heads, a.F, gated, a.groups) || a.room < a.T || a.cross || a.rel_bias ||
+    if (a.groups < 1 || a.groups != wide_groups(a.d, a.heads, a.I / std::max(a.heads, 1), a.F, gated, a.groups) || a.T < 1 || a.T > wide_most(a.d, a.heads, a.F, gated, a.groups) || a.room < a.T || a.cross || a.rel_bias ||
         !a.turn || !a.layers || !a.sync || !a.scratch || !a.x_out || !a.len_ptr)
         return hipErrorInvalidValue;
     const dim3 grid(a.groups), block(kPassThreads);

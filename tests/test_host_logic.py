@@ -164,8 +164,8 @@ def test_every_tile_of_a_wide_pass_has_a_workgroup(units):
     taken = 0
     for d, heads in ((1280, 10), (1536, 12), (1536, 6), (2048, 16), (2048, 8), (2560, 20), (3072, 24), (4096, 32)):
         for d_ff, gated in ((96, False), (d, True), (4096, True), (5632, True), (4 * d, False), (11008, True)):
-            for keys in (1, 256, 257, 1024, 1280, 1281, 2000, 2048, 2304, 2305, 8192):
-                s = b.wide_split(d, heads, d_ff, gated, units, keys)
+            for keys, rows in [(k, r) for k in (1, 256, 257, 1024, 1280, 1281, 2000, 2048, 2304, 2305, 8192) for r in (1, 16, 17, 32)]:
+                s = b.wide_split(d, heads, d_ff, gated, units, keys, rows)
                 if not s["qkv_tiles"]:
                     assert not any(s.values())
                     continue
@@ -173,7 +173,7 @@ def test_every_tile_of_a_wide_pass_has_a_workgroup(units):
                 case = (d, heads, d_ff, gated, keys, s)
                 assert s["qkv_first"] >= 0 and (units - s["qkv_first"]) * s["qkv_tiles"] >= 3 * heads * 128 // 16, case
                 assert s["ffn_first"] >= 0 and (units - s["ffn_first"]) * s["ffn_tiles"] >= (d_ff // 8 if gated else d_ff // 16), case
-                assert s["heads_first"] >= 0 and s["heads_first"] + heads * s["ranges"] <= units and s["ranges"] in (1, 2, 4, 8), case
+                assert s["heads_first"] >= 0 and s["heads_first"] + heads * (2 if rows > 16 else 1) * s["ranges"] <= units and s["ranges"] in (1, 2, 4, 8), case
                 assert d // 16 <= units
     assert taken > 0 or units < 96
 
@@ -205,3 +205,17 @@ def test_tile_shapes_of_one_round_make_one_on_every_die(n, k, gated, rotary):
             (3072, 640): set(), (4608, 384): {(96, 192)}, (4096, 4096): {(96, 256), (48, 128)}}
     if (n, k) in want:
         assert seen == want[n, k]
+
+
+@pytest.mark.parametrize("d,heads,d_ff,gated,most", [
+    (2048, 16, 5632, 1, 8), (2048, 16, 8192, 1, 8), (2048, 16, 8192, 0, 8),                            # 2048 wide
+    (1536, 12, 8192, 1, 16), (1536, 12, 8192, 0, 16), (1536, 12, 6912, 0, 8), (1536, 6, 8192, 1, 8),  # narrower, a wide hidden state
+    (2304, 18, 2304, 0, 8), (2304, 18, 4608, 0, 16), (2304, 9, 4608, 0, 8), (3072, 24, 4096, 1, 8), (3072, 24, 6144, 1, 16),
+    (4096, 32, 4096, 0, 8), (4096, 32, 5120, 0, 16), (4096, 32, 8192, 1, 16), (4096, 32, 8704, 1, 32), (4096, 16, 8704, 0, 32), (4096, 16, 8192, 0, 8), (4096, 32, 11008, 1, 32)])
+def test_rows_of_wide_passes_in_one_kernel(d, heads, d_ff, gated, most):
+    """Passes of nine rows and more are one kernel only where the weights of a layer, the hidden state's above all, outweigh the activations; up to
+    8192 keys, 4096 from 17 rows on, 2048 from 25, and 5120 of narrow models from nine rows on."""
+    one = lambda rows, keys: b.wide_split(d, heads, d_ff, bool(gated), 256, keys, rows)["qkv_tiles"] > 0
+    assert [r for r in range(1, 33) if one(r, 100)] == list(range(1, most + 1))
+    for rows, keys in ((8, 8192), (9, 5120 if d < 2048 else 8192), (17, 4096), (25, 2048)):
+        assert (one(rows, keys), one(rows, keys + 1)) == (rows <= most, False if rows > 8 else one(rows, keys + 1))
