@@ -455,6 +455,8 @@ extern "C" int bild_state_create(const bild_pair* p, int max_src, int max_len, i
             if (M.pass_wide) {
                 const int most = wide_most((int)d, m->cfg.n_heads, (int)F, m->gated(), s->cus);
                 M.pass_wide_rows = s->wide_most_rows > 0 ? std::min(most, s->wide_most_rows) : wide_rows((int)d, m->cfg.n_heads, (int)F, m->gated(), s->cus);
+                // (no room above eight rows for reviews that this state's own drafts do not reach: of the 7B shape 13 MB for 16 and 26 for 32 rows)
+                M.pass_wide_rows = std::min(M.pass_wide_rows, std::max(kWideRows, w == 0 ? 1 : 1 << pass_room_index(n_max + 1)));
             }
         }
         M.nparts_cap = m->head.tn + 1;  // at most one partial per feature tile

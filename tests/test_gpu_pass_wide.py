@@ -1,5 +1,7 @@
 """Passes of wide decoder-only models in one kernel (pass_wide.hip), at the edges of its key blocks, key ranges, row layouts and of the
 cuts of its projections, through the C ABI against the separate kernels (which the other tests hold against the oracle)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -8,6 +10,7 @@ import oracle
 import paper_2302_07863_amd as pkg
 from tests import parity
 from tests.test_gpu_early_exit import EERig
+from tests.hipmem import hip
 from tests.test_gpu_parity import Rig
 
 pytestmark = pytest.mark.gpu
@@ -207,3 +210,35 @@ def test_nine_to_thirty_two_rows(shape, many, monkeypatch):
     worst = float(np.abs(got["1"] - got["0"]).max())
     print("worst", worst, "one token", moved, flush=True)
     assert worst <= min(moved / 4, 2 * parity.logit_tol(cfg))
+
+
+def test_states_have_room_for_the_rows_of_their_own_drafts(monkeypatch):
+    """Hand-over memory above eight rows: up to n_max + 1 of the large model, in rooms of 16 and 32.  A longer draft of the caller's own is
+    reviewed by the separate kernels, with the same outcome."""
+    monkeypatch.setenv("BILD_WIDE_ROWS", "32")
+    cfg = bi.toy_pair(**{**BASE, "d_ff": 96, "max_new": 40})
+    R = Rig(cfg)
+
+    def free():
+        now, total = C.c_size_t(), C.c_size_t()
+        assert hip().hipMemGetInfo(C.byref(now), C.byref(total)) == 0
+        return now.value
+
+    taken, routes, kept = [], [], []
+    for n_max in (7, 15, 31, 7):   # (the first one loads what the others find)
+        before = free()
+        st = R.state(cfg.max_new, n_max)
+        taken.append(before - free())
+        st.encode(R.src)
+        st.large_verify(float("inf"), draft=[])
+        for rows in (8, 9, 16, 17, 32):
+            st.seq_truncate(R.n0)
+            kept.append(st.large_verify(float("inf"), draft=[int(t) for t in bi.make_tokens(cfg.large.vocab, rows - 1, seed=rows)])[:2])
+        r = st.pass_routes()
+        routes.append((r["chip"], r["kernels"]))
+        st.close()
+    assert routes == [(2, 4), (4, 2), (6, 0), (2, 4)]
+    assert kept[:5] == kept[5:10] == kept[10:15] == kept[15:]
+    sixteen, thirty_two = taken[1] - taken[3], taken[2] - taken[1]
+    print("MB", [t >> 20 for t in taken], flush=True)
+    assert 6 << 20 <= sixteen <= 16 << 20 and 12 << 20 <= thirty_two <= 32 << 20
