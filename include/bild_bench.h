@@ -88,6 +88,9 @@ int bild_debug_gemm_shape(int n, int k, int rows, int gated, int lm_head, int dt
  * workgroup, input slices, 1 if the rows go through LDS, workgroups on the die with most of them}.  gated: n counts gate and linear branch;
  * rotary: queries, keys and values with rotary positions. */
 int bild_debug_tile_shape(int n, int k, int rows, int gated, int rotary, int32_t out[5]);
+/* Which kernels have the head of bild_head_stats: 0 the skinny GEMM's workgroups and a merge, 1 the kernel whose workgroups stay for the whole
+ * sweep, 2 the thin GEMM on tile planes; negative: an error code. */
+int bild_debug_head_route(int d_model, int vocab, int rows, int dtype);
 /* The launch shape of attention for `rows` query rows over nkeys cached keys: out = {key splits, 1 if the consumer
  * projection merges the split partials (no merge kernel), waves per workgroup, dynamic LDS bytes}. */
 int bild_debug_attn_shape(int heads, int d_head, int rows, int nkeys, int max_splits, int dtype, int32_t out[4]);

@@ -92,6 +92,7 @@ _SIGS = {
     "bild_debug_tile_matrix": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]),
     "bild_debug_cache_rule": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
     "bild_debug_wide_split": (C.c_int, [C.c_int] * 7 + [C.POINTER(C.c_int32)]),
+    "bild_debug_head_route": (C.c_int, [C.c_int] * 4),
     "bild_debug_tile_shape": (C.c_int, [C.c_int] * 5 + [C.POINTER(C.c_int32)]),
     "bild_debug_attn_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
     "bild_debug_gemm_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
@@ -383,6 +384,13 @@ def gemm_shape(n: int, k: int, rows: int, gated: bool = False, lm_head: bool = F
     _check(lib().bild_debug_gemm_shape(n, k, rows, int(gated), int(lm_head), dtype, out), "bild_debug_gemm_shape")
     keys = ("wk", "nwv", "rw", "kc", "blocks", "row_blocks", "lds", "lds_limit")
     return dict(zip(keys, [int(v) for v in out]))
+
+
+def head_route(d_model: int, vocab: int, rows: int, dtype: int) -> str:
+    r = lib().bild_debug_head_route(d_model, vocab, rows, dtype)
+    if r < 0:
+        raise BildError(r, "bild_debug_head_route")
+    return ("short", "sweep", "planes")[r]
 
 
 def tile_shape(n: int, k: int, rows: int, gated: bool = False, rotary: bool = False) -> dict:

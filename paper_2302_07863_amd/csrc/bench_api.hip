@@ -10,6 +10,7 @@
 #include "bild_bench.h"
 #include "attn_split.h"
 #include "bild_state.h"
+#include "head.h"
 
 using namespace bild;
 
@@ -322,6 +323,16 @@ extern "C" int bild_debug_gemm_shape(int n, int k, int rows, int gated, int lm_h
     out[6] = (int32_t)gemm_lds_bytes(g, dtype);
     out[7] = 160 * 1024;
     return BILD_OK;
+}
+
+extern "C" int bild_debug_head_route(int d_model, int vocab, int rows, int dtype) {
+    if (d_model < 32 || d_model % 32 || vocab < 1 || rows < 1 || rows > kMaxRows || dtype < 0 || dtype > 1) return BILD_EINVAL;
+    TMat W;
+    W.n = vocab;
+    W.k = d_model;
+    W.tn = (vocab + 15) / 16;
+    W.tk = d_model / (dtype == BILD_DT_BF16 ? 32 : 16);
+    return head_route(W, dtype, rows);
 }
 
 extern "C" int bild_debug_tile_shape(int n, int k, int rows, int gated, int rotary, int32_t out[5]) {

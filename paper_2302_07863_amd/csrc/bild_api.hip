@@ -1482,7 +1482,7 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
         HIPC(M.pass_wide ? launch_wide(p, s->stream) : launch_pass(p, inside ? &in : nullptr, die ? s->cus : p.groups, s->stream));
         if (inside) return BILD_OK;
         // Rows wider than the sweep of the vocabulary takes, from five on: as tile planes for the thin GEMM.  (The entry points, whose call is the head alone, ask
-        // for 16 MB of matrix with five to eight rows, see takes_planes in head_stats.hip; a review of eight rows of two layers with that line / with none, us:
+        // for 16 MB of matrix with five to eight rows, see head_route; a review of eight rows of two layers with that line / with none, us:
         // 2560 wide, 700, 1500, 2500 ids 131.3, 131.6, 132.1 / 130.1, 130.2, 131.4, 4096 wide 201.0, 200.7, 202.7 / 200.1, 199.0, 200.9.)
         if (lm_rows > 4 && d > 2048 && dt == BILD_DT_BF16) {
             RowCopyArgs r;

@@ -27,6 +27,9 @@ struct HeadArgs {
 int head_groups(const TMat& W, int T, bool f32);
 hipError_t launch_head(const HeadArgs& a, hipStream_t st);
 hipError_t head_init();
+// which kernels have the head of bild_head_stats (head_stats.hip): the GEMM's short workgroups and a merge, this kernel, the thin GEMM on tile planes
+enum { HEAD_SHORT, HEAD_SWEEP, HEAD_PLANES };
+int head_route(const TMat& W, int dtype, int rows);
 
 #ifdef __HIPCC__
 // One row's result, by one lane: past the caches, and acknowledged before the host is told.

@@ -166,15 +166,6 @@ int head_sweep_run(const bild_model* m, const float* x, int rows, const int32_t*
     }
     return BILD_OK;
 }
-// Rows wider than the sweep's registers hold: as tile planes, for the thin GEMM (gemm_thin.hip), which has them on their way beside the weights, where every
-// short workgroup stages all of them.  A launch more, so from five rows on.  us, a call that waits, short workgroups / this, 5, 9, 16, 20, 32 rows: 4096 x 4000
-// 24.9, 28.2, 36.7, 36.5, 52.6 / 22.6, 24.4, 28.7, 28.8, 30.7; x 16 000 49.3, 43.6, 66.5, 80.9, 102 / 43.9, 45.8, 41.7, 45.5, 48.0; x 50 000 121, 104 to 110, 158, 196, 234 / 104, 108, 113, 114,
-// 120 (nine rows of 4096 inputs alone are as fast either way: ten 139 / 107); 2112 x 50 000, 5, 9, 20 rows 55, 78, 118 / 52, 54, 60; 3072 76, 101, 147 / 72, 73, 83; 5120 143, 155, 236 / 118,
-// 122, 131.  Eight rows and less of 8 MB the same, one and four rows of any size 0 to 10 % slower.
-bool takes_planes(const bild_model* m, int rows) {
-    if (m->cfg.dtype != BILD_DT_BF16 || m->head.tk <= 64) return false;
-    return rows > 8 || (rows > 4 && (size_t)m->head.tn * m->head.tk * kTileBytes >= (size_t)16 << 20);
-}
 // (behind `parts` workgroups' partial statistics)
 size_t planes_at(int rows, int parts) { return (kHdrBytes + (size_t)parts * rows * sizeof(StatPart) + 1023) / 1024 * 1024; }
 ThinArgs planes_head(const bild_model* m, int rows, const GemmArgs& g, void* scr) {
@@ -210,27 +201,73 @@ int head_planes_run(const bild_model* m, const float* x, int rows, const int32_t
     HIPC(hipGetLastError());
     return BILD_OK;
 }
-// Its workgroups; 0: the GEMM's short workgroups and the merge.  One rule for both entry points, whose results are the same bits.  Up to eight
-// rows of matrices of 50 MB or so are the short workgroups', of which more are on a compute unit when weights begin to arrive.  us, short
-// workgroups / sweep, a call that does not wait and one that does (there the sweep joins its results itself), one row: 512 x 16 000 ids
+// Whether the short workgroups of the GEMM, which stage all rows, find room for two on a compute unit.
+bool two_short(const TMat& W, int dtype, int rows) {
+    GemmArgs g;
+    std::memset((void*)&g, 0, sizeof(g));
+    g.W = W;
+    g.T = rows;
+    g.epi = EPI_LMHEAD;
+    gemm_pick_shape(g, dtype);
+    return gemm_lds_bytes(g, dtype) <= (size_t)80 * 1024;
+}
+
+}  // namespace
+
+// Which kernels have the head.  One rule for both entry points, whose results are the same bits.  All figures us, short workgroups / the other.
+//
+// Planes: bf16 rows wider than the sweep's registers hold, as tile planes for the thin GEMM (gemm_thin.hip), which has them on their way beside the weights, where
+// every short workgroup stages all of them.  A launch more, so from five rows on.  A call that waits, 5, 9, 16, 20, 32 rows: 4096 x 4000
+// 24.9, 28.2, 36.7, 36.5, 52.6 / 22.6, 24.4, 28.7, 28.8, 30.7; x 16 000 49.3, 43.6, 66.5, 80.9, 102 / 43.9, 41.5, 41.7, 45.5, 48.0; x 50 000 121, 104 to 110, 158, 196, 234 / 104, 108, 113, 114,
+// 120; 2112 x 50 000, 5, 9, 20 rows 55, 78, 118 / 52, 54, 60; 3072 76, 101, 147 / 72, 73, 83; 5120 143, 155, 236 / 118,
+// 122, 131.  Eight rows and less of 8 MB the same, one and four rows of any size 0 to 10 % slower.  Where two short workgroups fit a compute unit they are as fast: nine
+// rows of 4096 x 24 000, 32 000, 50 000, 64 000, 100 000 61.6, 60.9, 105, 117, 198 / 54.8, 64.7, 109, 119, 184; five of 7424 x 16 000, 24 000, 32 000, 50 000 57, 91, 106, 165 / 55, 95, 107, 169
+// (but twelve of 3072, eleven of 3456, ten of 3712, eight of 4608, seven of 5312, six of 6144 1.00 to 1.6 times as long at all sizes).
+//
+// Sweep (head.hip), bf16.  Up to eight rows of matrices of 50 MB or so are the short workgroups', of which more are on a compute unit when weights begin to arrive.
+// A call that does not wait and one that does (there the sweep joins its results itself), one row: 512 x 16 000 ids
 // 9.4 / 9.1, 17.1 / 16.8; x 32 128 9.9 / 10.4, 17.8 / 18.0; x 64 000 17.2 / 18.6, 25.0 / 24.0; 1024 x 4000 8.8 / 8.8, 16.8 / 16.6; x 16 000 9.9 / 10.4, 17.9 / 17.9;
 // x 32 128 16.7 / 18.4, 24.6 / 24.1; 2048 x 1000 9.7 / 10.4, 17.3 / 16.2; x 7809 10.3 / 11.4, 18.6 / 19.3; x 16 000 17.0 / 17.9, 24.7 / 24.2; 125 MB 512, 1024,
 // 2048 wide 32.7 / 27.7, 25.6 / 26.8, 28.2 / 26.8 and 41.2 / 33.0, 33.6 / 32.7, 35.7 / 32.3.  Two, four, eight rows: 512 x 64 000 20.7, 20.7, 21.2 / 18.3, 18.6,
 // 18.7; 1024 x 16 000 10.7, 11.4, 13.0 / 10.3, 10.8, 11.8; x 32 128 16.8, 17.1, 17.8 / 18.0, 18.2, 19.1; 2048 x 7809 11.4, 12.5, 14.7 / 11.5, 12.4, 13.8; x 16 000 17.4,
 // 17.4, 20.9 / 18.3, 19.2, 20.6.  From nine rows on the sweep is never slower.
-// fp32, a call that waits, 1, 8, 16, 32 rows: 512 x 50 000 34.5, 36.3, 38.7, 50.1 / 32.0, 32.1, 34.1, 42.0; x 250 112 119, 123, 124, 157 / 102, 102, 104, 116; 1024 x 4000
-// 20.7, 20.4, 22.4, 26.1 / 18.4, 19.6, 21.2, 24.1; x 50 000 53.6, 51.4, 58.4, 98.7 / 46.5, 47.7, 51.2, 59.7; 2048 x 1000 20.1, 22.2, 24.2, 31.7 / 18.3, 19.6, 23.7, 28.8; x 4000
-// 20.6, 22.9, 25.4, 32.6 / 21.8, 22.7, 25.9, 30.2; x 16 000 38.6, 40.4, 51.5, 73.7 / 38.2, 40.1, 45.1, 49.9 (four rows 36.4 / 39.4); x 50 000 98, 101, 130, 191 / 86, 87, 89, 106;
-// 4096 x 4000, 1, 8, 16 rows 33.4, 34.4, 39.3 / 37.0, 38.1, 42.0; x 16 000 55.4, 68.3, 81.4 / 67.3, 67.9, 72.0; x 50 000 179, 204, 229 / 173, 172, 178.
-int sweep_groups(const bild_model* m, int rows) {
-    const int tk = m->head.tk;
-    const size_t mb = ((size_t)m->head.tn * tk * kTileBytes) >> 20;
-    if (m->cfg.dtype != BILD_DT_BF16) {
-        const bool f32_taken = tk <= 64 || (tk <= 128 ? rows > 8 || mb < 16 || mb >= 200 : mb >= (rows > 8 ? 128u : 400u));
-        return f32_taken ? head_groups(m->head, rows, true) : 0;
+//
+// Sweep, fp32, a call that waits, 1, 8, 16, 32 rows: 512 x 50 000 34.5, 36.3, 38.7, 50.1 / 32.0, 32.1, 34.1, 42.0; x 250 112 119, 123, 124, 157 / 102, 102, 104, 116; 1024 x 4000
+// 20.7, 20.4, 22.4, 26.1 / 18.4, 19.6, 21.2, 24.1; x 50 000 53.6, 51.4, 58.4, 98.7 / 46.5, 47.7, 51.2, 59.7; up to 1024 wide at any size (0.7 to 1.03 times), but for
+// one row up to 256 wide (256 x 32 000, 50 000, 64 000 19.9, 25.4, 27.8 / 21.4, 28.0, 27.6).
+// Up to 2048 wide, small and large matrices, and the others from nine rows on: 2048 x 1000 20.1, 22.2, 24.2, 31.7 / 18.3, 19.6, 23.7, 28.8; x 4000
+// 20.6, 22.9, 25.4, 32.6 / 21.8, 22.7, 25.9, 30.2; x 16 000 38.6, 40.4, 51.5, 73.7 / 38.2, 40.1, 45.1, 49.9 (four rows 36.4 / 39.4); x 50 000 98, 101, 130, 191 / 86, 87, 89, 106; four rows x 32 000,
+// 36 000 57, 73 / 60, 63; 1536 x 50 000, 60 000, 90 000, one row 71, 82, 117 / 73, 84, 109.  Not a little above the last-level cache's 256 MB below 1536 wide (1280 x 40 000, 60 000, 90 000, 1, 9 rows
+// 51, 56; 68, 69; 105, 104 / 51, 51; 81, 78; 99, 96), nor large ones with two row tiles below 1792 (1280 x 60 000, 90 000, 17, 32 rows 114, 161; 120, 138 / 101, 103; 137, 140; 1536 x 90 000, 128 000 134, 147; 177, 191 / 142, 144; 194, 196).
+// Wider ones spill registers, and win only against short workgroups that do not fit a compute unit twice: 4096 x 12 000, 1, 8, 9, 10, 16 rows 48.6, 68.8, 60.2, 75.3, 88.2 /
+// 58, 58, 58.2, 58.2, 60.5; x 26 000 98, 111, 97, 116, 125 / 110, 108, 110, 110, 113; x 46 000 153, 167, 155, 170, 183 / 166, 163, 165, 166, 168; x 60 000 193, 212, 193, 219, 235 / 202, 195, 197, 198, 199;
+// 3840 x 20 000 10, 16 rows 94, 102 / 80, 83, x 46 000 151, 159 / 165, 166; 3712 x 12 000 12, 16 rows 68, 75 / 54, 56; 2112 to 3456 x 16 000 to 75 000 0.9 to 1.45 times as long.
+int bild::head_route(const TMat& W, int dtype, int rows) {
+    const int tk = W.tk;
+    const size_t mb = ((size_t)W.tn * tk * kTileBytes) >> 20;
+    if (dtype == BILD_DT_BF16) {
+        if (tk > 64) {
+            if (rows <= 4 || (rows <= 8 && (size_t)W.tn * tk * kTileBytes < (size_t)16 << 20)) return HEAD_SHORT;
+            const bool even = (rows > 8 ? tk > 120 && mb < 600 : tk >= 224) && mb >= 200;
+            return even && two_short(W, dtype, rows) ? HEAD_SHORT : HEAD_PLANES;
+        }
+        return rows > 8 || mb >= 96 || (rows > 1 ? mb < 48 || tk <= 16 : mb < (tk > 32 ? 8u : 24u)) ? HEAD_SWEEP : HEAD_SHORT;
     }
-    const bool taken = rows > 8 || mb >= 96 || (rows > 1 ? mb < 48 || tk <= 16 : mb < (tk > 32 ? 8u : 24u));
-    return taken ? head_groups(m->head, rows, false) : 0;
+    if (tk <= 64) return rows == 1 && tk <= 16 && mb >= 24 && mb < 60 ? HEAD_SHORT : HEAD_SWEEP;
+    if (tk <= 128) {
+        if (rows > 16) return tk < 112 && mb >= 400 ? HEAD_SHORT : HEAD_SWEEP;
+        if (tk < 96 && mb >= 256 && mb < 400) return HEAD_SHORT;
+        return rows > 8 || mb < 16 || mb >= (tk < 128 ? 320u : 256u) ? HEAD_SWEEP : HEAD_SHORT;
+    }
+    if (rows > 16 || tk < 232 || mb < 128 || (tk < 256 && mb >= 320) || (rows <= 9 && (tk < 256 || mb < 600))) return HEAD_SHORT;
+    return two_short(W, dtype, rows) ? HEAD_SHORT : HEAD_SWEEP;
+}
+
+namespace {
+
+// Workgroups of the sweep; 0: other kernels have the head.
+int sweep_groups(const bild_model* m, int rows) {
+    return head_route(m->head, m->cfg.dtype, rows) == HEAD_SWEEP ? head_groups(m->head, rows, m->cfg.dtype != BILD_DT_BF16) : 0;
 }
 
 bool all_done(const unsigned* done, unsigned call, int rows) {
@@ -269,7 +306,7 @@ extern "C" int bild_head_stats(const bild_model* m, const float* x_dev, int rows
     if (int rc = of_device(g_counts_ptr, HIP_SYMBOL(counts), &slots)) return rc;
     GemmArgs g = head_gemm(m, x_dev, rows, targets_dev, nullptr, (const int*)slots);
     const int groups = sweep_groups(m, rows);
-    const bool planes = takes_planes(m, rows);
+    const bool planes = head_route(m->head, m->cfg.dtype, rows) == HEAD_PLANES;
     const size_t bytes = std::max(kHdrBytes + (size_t)std::max(g.part_ld, groups) * sizeof(StatPart) * rows, planes ? planes_scratch(m, rows, thin_shape(m->head, EPI_LMHEAD, 0, rows).groups) : 0);
     HeadScratch b = m->head_pool.take(bytes, st);
     if (!b.p) return BILD_ENOMEM;
@@ -299,7 +336,7 @@ extern "C" int bild_head_stats_static(const bild_model* m, const float* x_dev, i
     if (int rc = of_device(g_counts_ptr, HIP_SYMBOL(counts), &slots)) return rc;
     const GemmArgs g = head_gemm(m, x_dev, rows, targets_dev, scr, (const int*)slots);
     if (g.part_ld > kStaticMaxParts) return BILD_ECAP;  // more partial statistics than the array holds
-    if (takes_planes(m, rows)) {
+    if (head_route(m->head, m->cfg.dtype, rows) == HEAD_PLANES) {
         const ThinArgs a = planes_head(m, rows, g, scr);
         if (planes_scratch(m, rows, a.part_ld) <= kStaticScratchBytes) return head_planes_run(m, x_dev, rows, targets_dev, out_dev, (hipStream_t)hip_stream, a, nullptr, 0);
     }

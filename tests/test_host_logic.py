@@ -219,3 +219,17 @@ def test_rows_of_wide_passes_in_one_kernel(d, heads, d_ff, gated, most):
     assert [r for r in range(1, 33) if one(r, 100)] == list(range(1, most + 1))
     for rows, keys in ((8, 8192), (9, 5120 if d < 2048 else 8192), (17, 4096), (25, 2048)):
         assert (one(rows, keys), one(rows, keys + 1)) == (rows <= most, False if rows > 8 else one(rows, keys + 1))
+
+
+@pytest.mark.parametrize("dtype,d,vocab,rows,want", [
+    # fp32: wider than 2048 only against short workgroups that do not fit twice, of matrices above the last-level cache's half
+    (bi.DT_F32, 2112, 60000, (1, 4, 9, 16), "short"), (bi.DT_F32, 3072, 32000, (9, 10, 12, 16), "short"), (bi.DT_F32, 3456, 60000, (1, 8, 9), "short"), (bi.DT_F32, 3840, 46000, (1, 8, 10, 16), "short"),
+    (bi.DT_F32, 3840, 12000, (10, 16), "sweep"), (bi.DT_F32, 4096, 16000, (1, 8, 9), "short"), (bi.DT_F32, 4096, 32000, (1, 4, 9), "short"), (bi.DT_F32, 4096, 32000, (10, 16), "sweep"), (bi.DT_F32, 4096, 50000, (5, 8), "sweep"),
+    (bi.DT_F32, 1280, 60000, (1, 9), "short"), (bi.DT_F32, 1280, 90000, (17, 32), "short"), (bi.DT_F32, 1536, 128000, (17, 24), "short"), (bi.DT_F32, 2048, 32000, (2, 4), "short"), (bi.DT_F32, 2048, 50000, (1, 9, 32), "sweep"),
+    (bi.DT_F32, 1024, 50000, (1, 32), "sweep"), (bi.DT_F32, 256, 50000, (1,), "short"), (bi.DT_F32, 256, 50000, (2, 32), "sweep"), (bi.DT_F32, 2112, 4000, (17, 32), "short"),
+    # bf16: wider than 2048 from five rows on as tile planes, but for nine rows of 4096 inputs of which the short workgroups fit twice
+    (bi.DT_BF16, 4096, 32000, (9,), "short"), (bi.DT_BF16, 4096, 32000, (5, 8, 10, 32), "planes"), (bi.DT_BF16, 4096, 64000, (9,), "short"), (bi.DT_BF16, 4096, 24000, (9,), "planes"), (bi.DT_BF16, 4096, 1000, (5, 8), "short"), (bi.DT_BF16, 4096, 1000, (9,), "planes"),
+    (bi.DT_BF16, 7424, 24000, (5,), "short"), (bi.DT_BF16, 5312, 24000, (7,), "planes"), (bi.DT_BF16, 3072, 32000, (12,), "planes"), (bi.DT_BF16, 2048, 32000, (9, 32), "sweep"), (bi.DT_BF16, 512, 32128, (1,), "short")])
+def test_kernels_of_the_head(dtype, d, vocab, rows, want):
+    """Which kernels have the head of bild_head_stats, at sizes where one of them is clearly the slower one."""
+    assert {r: b.head_route(d, vocab, r, dtype) for r in rows} == dict.fromkeys(rows, want)
