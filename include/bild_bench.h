@@ -64,7 +64,8 @@ int bild_pass_stages(bild_state* s, int32_t* stages);
 /* Passes with an LM head the state has run so far: out = {as one kernel over the whole chip, as one kernel on one die,
  * as a chain of kernels, those of the first two whose workgroups did not all get to run and that were run again}. */
 int bild_pass_routes(bild_state* s, int64_t out[4]);
-/* Polls after which a workgroup of a pass in one kernel gives up (6000 unless set: about 4 ms). */
+/* Polls after which a workgroup of a pass in one kernel gives up a wait (6000 unless set: about 4 ms; an LM head inside the pass waits for all
+ * of the layers, up to 64 times as often, or until one of their workgroups has given up). */
 int bild_debug_pass_spins(bild_state* s, int spins);
 int bild_profile_begin(bild_state* s, int max_records);
 int bild_profile_end(bild_state* s, bild_profile* out);

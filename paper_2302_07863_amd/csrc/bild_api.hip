@@ -287,8 +287,12 @@ namespace {
 
 // States that are inside a call, by device.  The workgroups of a pass kernel wait for each other, so all of them have to be on the
 // chip: two such passes at a time could keep half of each other's out, and a pass of separate kernels crawls where it finds them.
-// So only a state that is inside a call alone takes the pass kernel.  Calls return when their passes have ended: no other pass
-// kernel is in flight then.
+// So only a state that is inside a call alone takes the pass kernel.  When a call returns, its passes have ended, but for the last one with LM
+// head and policy inside (pass_head.h), which tells the host itself.  What is left of that kernel waits for nobody else's workgroups: on
+// die 0 all are past their last hand-over, the head's are past their partials, or have yet to start and will find the hidden state in its place; of
+// a pass that gave up, the waits that are left are bounded and look at its flag.  So it ends by itself, and another state's pass kernel, whose waits are
+// for its own workgroups alone, gets its compute units some microseconds later (where somebody else's work keeps the last workgroups
+// from starting, they take them no longer than that part of theirs).  The state's own next kernel, its rerun among them, is behind on the stream.
 // Two, three, four requests together, six generations each, T5-large / T5-small shapes, tokens/s, each on a hardware queue of its
 // own: a pass kernel for whoever finds none in flight 3870, 4066, 4320, this rule 3930, 5050, 5980, and 4100, 5560, 6800 once the
 // graphs of the separate kernels are captured (one alone: 3040 with the pass kernel, 2265 without).
@@ -1704,7 +1708,8 @@ int run_pass(bild_state* s, int w, int T, int lm_rows, int mode) {
 }
 
 // After a pass of T rows that gave up.  What kept workgroups out may be gone by the next pass (work of another stream) or stay
-// (another process' pass kernel), and each attempt takes 4 ms: the state's next 16 passes run as separate kernels, twice as many
+// (another process' pass kernel), and each attempt takes 4 ms (a wait for another workgroup; the head's of pass_head.h is longer, and ends
+// when one of the others has run out): the state's next 16 passes run as separate kernels, twice as many
 // after each further attempt in vain, 65 536 at most (which is 40 s of passes for 4 ms).
 int pass_gave_up(bild_state* s, int w, int T) {
     s->routes[ROUTE_GAVE_UP] += 1;

@@ -283,7 +283,7 @@ struct PassArgs {
     PassPlan at;
     int groups;               // workgroups that take part
     int last;                 // 1: q, k, v and the FFN's input are the last ones' (pass_last; over the chip)
-    int spins;                // polls (of about 0.7 us) after which a workgroup gives up
+    int spins;                // polls (of about 0.7 us) of a wait after which a workgroup gives up (the head's: 64 times as many, pass_head.h)
     unsigned* sync;           // [kPassSyncWords], zero before the pass; the policy kernel clears it
 };
 // Kernels that address a layer's keys or values by 32-bit byte offsets (pass_kernel.hip, pass_wide.hip, attn_split.hip) take caches whose

@@ -260,7 +260,8 @@ struct bild_state {
     unsigned* pass_sync = nullptr;
     bool last_one = false;    // the pass issued last is one kernel
     int pass_pause = 0, pass_fails = 0;  // passes to run as separate kernels before the next attempt; attempts in vain in a row
-    int pass_spins = 6000;    // 4 ms: kernels of other streams come to an end in that time, the same kernel of another process does not
+    int pass_spins = 6000;    // polls of a wait, about 4 ms: kernels of other streams come to an end in that time, the same kernel of another process
+                              // does not (64 times as many of the head inside a pass, which waits for all of the layers: pass_head.h)
     int device = 0, cus = 0;
     int depth = 0;            // calls of this state that are on the stack (see Call)
     int64_t routes[4] = {};   // passes with an LM head so far, by Route

@@ -17,7 +17,7 @@
 // 32 bytes a clock of weights with up to sixteen rows and 16 with more (19 and 10 TB/s over the chip): the matrix' way from memory still.  A row
 // of 2048 and 4096 inputs takes 64 and 128 registers; 17 rows and more of the latter do not fit, and up to sixteen of them spill 40 registers (164 bytes a
 // lane): 4096 x 50 000 takes 173 us, 134 at a large copy's rate (taken only where the short workgroups are slower still, head_route).  50 000 ids, 1, 16, 32 rows, short workgroups / now (floor
-// 17, 34, 67 us): 512 wide 34.5, 38.7, 50.1 / 32.0, 34.1, 42.0; 1024 53.6, 58.4, 98.7 / 46.5, 51.2, 59.7; 2048 98, 130, 191 / 86, 89, 106 (more: sweep_groups).
+// 17, 34, 67 us): 512 wide 34.5, 38.7, 50.1 / 32.0, 34.1, 42.0; 1024 53.6, 58.4, 98.7 / 46.5, 51.2, 59.7; 2048 98, 130, 191 / 86, 89, 106 (more: head_route).
 #include "head.h"
 
 #include <algorithm>
