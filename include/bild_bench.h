@@ -98,11 +98,13 @@ int bild_debug_attn_shape(int heads, int d_head, int rows, int nkeys, int max_sp
 /* Kernels that address a bf16 layer's cache of `positions` by 32-bit offsets: out = {1 if they may take it (passes in one
  * kernel), key splits of the attention that joins its ranges itself for up to nkeys keys (0: it is not taken), its waves}. */
 int bild_debug_cache_rule(int heads, int d_head, int positions, int nkeys, int32_t out[3]);
-/* Who does what in a one-kernel pass of `rows` rows of a wide decoder-only model (heads of 128 features; above 16 rows a head is twice as
- * many workgroups', by sixteen rows) on `units` compute units, a workgroup each, that ends with `keys` keys: out = {tiles of q, k, v a workgroup has, the first workgroup with any, the same two of the
+/* Who does what in a one-kernel pass of a row of a wide decoder-only model (heads of 128 features) on `units` compute units, a workgroup
+ * each, that ends with `keys` keys: out = {tiles of q, k, v a workgroup has, the first workgroup with any, the same two of the
  * FFN's input, the first workgroup of the heads, key ranges of a head (a workgroup each), 1 if heads and projections are
  * apart}; all zero where such passes run as kernels of their own. */
-int bild_debug_wide_split(int d_model, int heads, int d_ff, int gated, int units, int keys, int rows, int32_t out[7]);
+int bild_debug_wide_split(int d_model, int heads, int d_ff, int gated, int units, int keys, int32_t out[7]);
+/* The same of a pass of `rows` rows (above 16 rows a head is twice as many workgroups', by sixteen rows). */
+int bild_debug_wide_split_rows(int d_model, int heads, int d_ff, int gated, int units, int keys, int rows, int32_t out[7]);
 
 #ifdef __cplusplus
 }

@@ -91,7 +91,8 @@ _SIGS = {
     "bild_debug_tiled_bytes": (C.c_int64, [C.c_int, C.c_int, C.c_int]),
     "bild_debug_tile_matrix": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]),
     "bild_debug_cache_rule": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
-    "bild_debug_wide_split": (C.c_int, [C.c_int] * 7 + [C.POINTER(C.c_int32)]),
+    "bild_debug_wide_split": (C.c_int, [C.c_int] * 6 + [C.POINTER(C.c_int32)]),
+    "bild_debug_wide_split_rows": (C.c_int, [C.c_int] * 7 + [C.POINTER(C.c_int32)]),
     "bild_debug_head_route": (C.c_int, [C.c_int] * 4),
     "bild_debug_tile_shape": (C.c_int, [C.c_int] * 5 + [C.POINTER(C.c_int32)]),
     "bild_debug_attn_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int32)]),
@@ -413,5 +414,5 @@ def cache_rule(heads: int, d_head: int, positions: int, nkeys: int) -> dict:
 
 def wide_split(d_model: int, heads: int, d_ff: int, gated: bool, units: int, keys: int, rows: int = 1) -> dict:
     out = (C.c_int32 * 7)()
-    _check(lib().bild_debug_wide_split(d_model, heads, d_ff, int(gated), units, keys, rows, out), "bild_debug_wide_split")
+    _check(lib().bild_debug_wide_split_rows(d_model, heads, d_ff, int(gated), units, keys, rows, out), "bild_debug_wide_split_rows")
     return dict(zip(("qkv_tiles", "qkv_first", "ffn_tiles", "ffn_first", "heads_first", "ranges", "apart"), [int(v) for v in out]))

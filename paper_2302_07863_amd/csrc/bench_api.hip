@@ -377,8 +377,12 @@ extern "C" int bild_debug_cache_rule(int heads, int d_head, int positions, int n
     return BILD_OK;
 }
 
-extern "C" int bild_debug_wide_split(int d_model, int heads, int d_ff, int gated, int units, int keys, int rows, int32_t out[7]) {
+extern "C" int bild_debug_wide_split_rows(int d_model, int heads, int d_ff, int gated, int units, int keys, int rows, int32_t out[7]) {
     if (!out || d_model < 1 || heads < 1 || d_ff < 1 || units < 1 || keys < 1 || rows < 1) return BILD_EINVAL;
     if (!wide_split(d_model, heads, d_ff, gated != 0, units, keys, rows, out)) std::memset(out, 0, 7 * sizeof(int32_t));
     return BILD_OK;
+}
+
+extern "C" int bild_debug_wide_split(int d_model, int heads, int d_ff, int gated, int units, int keys, int32_t out[7]) {
+    return bild_debug_wide_split_rows(d_model, heads, d_ff, gated, units, keys, 1, out);
 }

@@ -179,9 +179,7 @@ def test_who_does_what_changes_with_the_length(shape, monkeypatch):
 def test_nine_to_thirty_two_rows(shape, many, monkeypatch):
     """Models of the widest cut (the large ones): high and low parts in operands of their own, two row tiles, no earlier key up to eight key ranges, the new
     keys' block whole and short, passes of other rooms between; above sixteen rows the widest models, up to 4096 keys, from 25 rows on
-    2048, beyond which the separate kernels stay.  Against the separate kernels, as above.  (The hidden states are narrower than those for which
-    passes of so many rows are one kernel by themselves.)"""
-    monkeypatch.setenv("BILD_WIDE_ROWS", "32")
+    2048, beyond which the separate kernels stay.  Against the separate kernels, as above."""
     cfg = bi.toy_pair(**{**BASE, **shape, "max_new": 2100})
     R = Rig(cfg)
     got = {}

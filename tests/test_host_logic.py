@@ -164,8 +164,8 @@ def test_every_tile_of_a_wide_pass_has_a_workgroup(units):
     taken = 0
     for d, heads in ((1280, 10), (1536, 12), (1536, 6), (2048, 16), (2048, 8), (2560, 20), (3072, 24), (4096, 32)):
         for d_ff, gated in ((96, False), (d, True), (4096, True), (5632, True), (4 * d, False), (11008, True)):
-            for keys, rows in [(k, r) for k in (1, 256, 257, 1024, 1280, 1281, 2000, 2048, 2304, 2305, 8192) for r in (1, 16, 17, 32)]:
-                s = b.wide_split(d, heads, d_ff, gated, units, keys, rows)
+            for keys in (1, 256, 257, 1024, 1280, 1281, 2000, 2048, 2304, 2305, 8192):
+                s = b.wide_split(d, heads, d_ff, gated, units, keys)
                 if not s["qkv_tiles"]:
                     assert not any(s.values())
                     continue
@@ -173,7 +173,7 @@ def test_every_tile_of_a_wide_pass_has_a_workgroup(units):
                 case = (d, heads, d_ff, gated, keys, s)
                 assert s["qkv_first"] >= 0 and (units - s["qkv_first"]) * s["qkv_tiles"] >= 3 * heads * 128 // 16, case
                 assert s["ffn_first"] >= 0 and (units - s["ffn_first"]) * s["ffn_tiles"] >= (d_ff // 8 if gated else d_ff // 16), case
-                assert s["heads_first"] >= 0 and s["heads_first"] + heads * (2 if rows > 16 else 1) * s["ranges"] <= units and s["ranges"] in (1, 2, 4, 8), case
+                assert s["heads_first"] >= 0 and s["heads_first"] + heads * s["ranges"] <= units and s["ranges"] in (1, 2, 4, 8), case
                 assert d // 16 <= units
     assert taken > 0 or units < 96
 
@@ -233,3 +233,22 @@ def test_rows_of_wide_passes_in_one_kernel(d, heads, d_ff, gated, most):
 def test_kernels_of_the_head(dtype, d, vocab, rows, want):
     """Which kernels have the head of bild_head_stats, at sizes where one of them is clearly the slower one."""
     assert {r: b.head_route(d, vocab, r, dtype) for r in rows} == dict.fromkeys(rows, want)
+
+
+@pytest.mark.parametrize("units", [144, 256, 304])
+def test_every_tile_of_a_wide_pass_of_many_rows_has_a_workgroup(units):
+    """The same above eight rows; above sixteen a head is twice as many workgroups'."""
+    taken = {}
+    for d, heads in ((1536, 12), (1536, 6), (2560, 20), (3072, 24), (4096, 32), (4096, 16)):
+        for d_ff, gated in ((4096, True), (5632, True), (8192, False), (4 * d, False), (11008, True)):
+            for keys, rows in [(k, r) for k in (1, 256, 257, 1024, 1280, 1281, 2000, 2048, 2304, 2305, 4096, 8192) for r in (9, 16, 17, 32)]:
+                s = b.wide_split(d, heads, d_ff, gated, units, keys, rows)
+                if not s["qkv_tiles"]:
+                    assert not any(s.values())
+                    continue
+                taken[rows] = taken.get(rows, 0) + 1
+                case = (d, heads, d_ff, gated, keys, rows, s)
+                assert s["qkv_first"] >= 0 and (units - s["qkv_first"]) * s["qkv_tiles"] >= 3 * heads * 128 // 16, case
+                assert s["ffn_first"] >= 0 and (units - s["ffn_first"]) * s["ffn_tiles"] >= (d_ff // 8 if gated else d_ff // 16), case
+                assert s["heads_first"] >= 0 and s["heads_first"] + heads * (2 if rows > 16 else 1) * s["ranges"] <= units and s["ranges"] in (1, 2, 4, 8), case
+    assert set(taken) == ({9, 16, 17, 32} if units >= 256 else {9, 16}), taken
