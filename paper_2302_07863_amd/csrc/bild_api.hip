@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <array>
 #include <atomic>
 #include <cmath>
@@ -1648,7 +1649,11 @@ int decoder_pass(bild_state* s, int w, int T, int lm_rows, int mode, int key_hin
 // 660, 681: never slower up to the 8192 positions that were measured.  More rows: wide_rows, wide_keys.
 static bool on_one_die(const bild_state* s, int w, int T) { return T <= s->ms[w].pass_die_rows; }
 static bool takes_one_kernel(const bild_state* s, int w, int T, int lm_rows) {
-    if (s->ms[w].pass_wide) return s->one_kernel && T <= s->ms[w].pass_wide_rows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= wide_keys(T, s->ms[w].m->cfg.d_model);
+    if (s->ms[w].pass_wide) {
+        const bild_model_config& c = s->ms[w].m->cfg;
+        const int keys = wide_keys(T, c.d_model, s->wide_most_rows > 0 ? INT_MAX : c.d_ff, s->ms[w].m->gated());  // (set for tests: as of the widest)
+        return s->one_kernel && T <= s->ms[w].pass_wide_rows && lm_rows > 0 && !s->gemm_only && !s->prof_on && s->len[w] + T <= keys;
+    }
     return s->one_kernel && s->ms[w].pass_groups > 0 && T <= kPassRows && lm_rows > 0 && !s->gemm_only && !s->prof_on &&
            s->n_src <= (s->ms[w].m->cfg.dtype == BILD_DT_F32 ? 1024 : on_one_die(s, w, T) ? 1280 : T == 1 ? 1408 : 1536) && s->len[w] + T <= 1024;
 }

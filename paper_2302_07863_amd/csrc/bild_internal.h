@@ -302,7 +302,7 @@ constexpr int kWideApart = 1280;               // most keys with which heads and
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus);  // as pass_groups, of pass_wide.hip
 int wide_most(int d, int heads, int F, bool gated, int cus);
 int wide_rows(int d, int heads, int F, bool gated, int cus);
-int wide_keys(int T, int d);
+int wide_keys(int T, int d, int F, bool gated);
 bool wide_two(int d, int heads, int F, bool gated, int cus, int keys);
 // who does what in a pass of `rows` rows that ends with `keys` keys (wide_parts): {tiles of q, k, v a workgroup, its first workgroup, the same of the
 // FFN's input, the heads' first workgroup, ranges, apart}; false: such passes are kernels of their own

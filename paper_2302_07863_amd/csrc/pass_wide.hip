@@ -819,28 +819,38 @@ int wide_most(int d, int heads, int F, bool gated, int cus) {
     return wide_fits<Cut2048>(d, heads, F, gated, cus) ? kWideRows : d < kWideRowsFrom || 2 * heads > cus ? 16 : kWideRowsMost;
 }
 
-// Most rows it is taken for: the layers' weights have to take long enough to read, as that is what it does better than kernels of their own.
-// Its time over theirs, six layers, least and most of 9, 10, 12, 16 rows over 64, 1000, 2500, 5000, 8000 tokens.  4096 wide, without a gate, hidden
-// state of 1024 1.07 to 1.15, 2048 1.07 to 1.11, 4096 1.02 to 1.04, 5120 0.94 to 0.98, 8192 0.89 to 0.94, 11008 0.89 to 0.91; gated 2048 1.02 to 1.05, 3072 0.98 to 1.02,
-// 4096 0.95 to 0.96, 5120 0.91 to 0.94, 11008 0.86 to 0.88, heads of half the width 5120 0.92 to 1.02 and 0.95 to 1.05 without a gate.  3584 and 3072 wide, 1.5 and 2
-// times as wide a hidden state without a gate 0.92 to 1.00, gated 1.3 times 0.96 to 1.04, 2 times 0.92 to 1.00, heads of half the width 0.98 to 1.09.  2560 and 2304 wide, without a
-// gate 1 and 1.5 times 1.01 to 1.13, 2 times 0.96 to 1.01, 4 times 0.86 to 0.91; gated 1 and 1.3 times 0.97 to 1.07, 2 times 0.94 to 1.01, 2.7 times 0.90 to 0.99; heads
-// of half the width 0.99 to 1.12.  2048 wide (hidden states above 6144) without a gate 0.98 to 1.15, gated 0.91 to 1.08: not taken.  Narrower ones, whose separate kernels are others
-// (takes_thin), up to 5000 tokens: without a gate 6912 and 7168 0.84 to 1.02, 8192 0.80 to 1.00, gated 0.79 to 0.94, heads of half the width 0.91 to 1.09; 8000 tokens 0.87 to 1.10.
-// 17, 24, 25, 32 rows over 64, 700, 1500, 2016 tokens (25 and 32 not further), 3000, 4072: without a gate 4096 1.06 to 1.18, 6144 0.93 to 1.05, 8192 0.93 to 1.03, 8704
-// 0.85 to 0.95, 9216 0.86 to 0.95; gated 4096 0.98 to 1.10, 6144 0.96 to 1.08, 8192 0.96 to 1.06, 8704 0.89 to 0.99, 9216 0.89 to 0.98, 11008 0.89 to 0.97 (heads of 3072
-// 0.89 to 0.97; 8704 and heads of 2048 0.81 to 0.96).
-int wide_rows(int d, int heads, int F, bool gated, int cus) {
-    const int most = wide_most(d, heads, F, gated, cus);
-    if (most <= kWideRows || (d >= kWideRowsFrom && F >= 8704)) return most;
-    const bool taken = heads * kWideHead >= d && (d >= 4096 ? F >= 5120 : d >= 2304 ? F >= 2 * d : d < 2048 && (gated || F >= 8192));
-    return taken ? std::min(most, 16) : kWideRows;
+// Passes of nine rows and more: where they are taken.  What they do better than kernels of their own is to read weights on while activations are handed
+// over; what they do worse, twice the activations' loads and products, goes with the width and is the same however wide the hidden state is.  So the line
+// is one of the hidden state (1.2 times for a gated one) and the heads' width against the model's.  Its time over the kernels' own, 900 shapes drawn at random, layers of 0.7 GB together, three
+// lengths from 64 to 7900 tokens, 9, 12 and 16 rows, by F + I / 2 - 2 d / 5 (1.2 F gated) of those 2304 to 4096 wide, the least, middle and most of the shapes' means: below 2560 1.02, 1.09, 1.23, to 3560 0.99, 1.06,
+// 1.14, to 4560 0.95, 1.01, 1.08, to 5560 0.92, 0.97, 1.02, to 8560 0.89, 0.94, 1.00, above 0.85, 0.90, 0.95.  Of 2340 times on this side three are over 1.04 (1.05), of 3700 on the other 49 under 0.96 (0.93).
+// 4096 wide, 32 heads, hidden states up to 3400, 4096, 5200, 6400, 8192, 11 264: without a gate 1.06, 1.05, 0.97, 0.96, 0.94, 0.90, gated 1.01, 0.99, 0.93, 0.93, 0.92, 0.86.  2048 wide (hidden states above 6144)
+// gated up to 8192 0.90 to 0.94, wider 1.01 to 1.07, without a gate 0.98 to 1.06.  Narrower ones, whose separate kernels are others (takes_thin), 0.77 to 0.99.
+static bool wide_many(int d, int heads, int F, bool gated) {
+    if (d < 2048) return true;
+    if (d == 2048) return gated && F <= 8192;
+    return (gated ? 12 * F / 10 : F) + heads * kWideHead / 2 - 2 * d / 5 >= 4560;
 }
 
-// Most keys of a pass of T rows.  Each of two row tiles goes over a head's keys by itself: the 7B shape, 17, 24, 25, 32 rows, kernels of their own / this, us, over 64
-// tokens 3599, 3609, 3628, 3622 / 3270, 3265, 3492, 3496, 2016 3771, 3790, 3811, 3820 / 3429, 3434, 3666, 3674, 3200 3925, 3942 / 3684, 3687, 4072 3967, 3988 / 3856, 3857; 32 rows
-// over 3200 and 4097 4118, 4178 / 4087, 4268.  Narrow models: see wide_rows.
-int wide_keys(int T, int d) { return T <= 8 ? 8192 : T <= 16 ? (d < 2048 ? 5120 : 8192) : T <= 24 ? 4096 : 2048; }
+// Most rows it is taken for at some length.
+int wide_rows(int d, int heads, int F, bool gated, int cus) {
+    const int most = wide_most(d, heads, F, gated, cus);
+    if (most <= kWideRows || !wide_many(d, heads, F, gated)) return std::min(most, kWideRows);
+    return std::min(most, F > 8192 ? kWideRowsMost : F > 4096 ? 24 : 16);
+}
+
+// Most keys of a pass of T rows.  Each of two row tiles goes over a head's keys by itself, and up to 4096 features of the hidden state the kernels of their own are
+// better, up to 8192 behind many keys.  4096 wide, 17 and 24 rows over 200, 1000, 2000, 3000, 4000, 5500 tokens, its time over the others', mean of 10 to 40 shapes, without a gate 4320 to 8192
+// 0.94, 0.94, 0.99, 1.00, 1.02, 1.06, above 0.86, 0.86, 0.90, 0.91, 0.94, 0.97, gated 0.96, 0.97, 1.01, 1.03, 1.04, 1.08 and 0.90, 0.90, 0.93, 0.94, 0.96, 1.00; 25 and 32 rows without a gate
+// 0.99, 1.02, 1.04, 1.06, 1.08, 1.12 and 0.91, 0.93, 0.95, 0.97, 0.99, 1.03, gated 1.01, 1.03, 1.05, 1.07, 1.09, 1.14 and 0.94, 0.95, 0.97, 0.99, 1.01, 1.05.  The 7B shape, 17, 24, 25, 32 rows, us, kernels of
+// their own / this, over 64 tokens 3599, 3609, 3628, 3622 / 3270, 3265, 3492, 3496, 2016 3771, 3790, 3811, 3820 / 3429, 3434, 3666, 3674, 3200 3925, 3942 / 3684, 3687, 4072 3967, 3988 / 3856, 3857; 32 rows
+// over 3200 and 4097 4118, 4178 / 4087, 4268.
+// Below 2048 wide, 9, 12, 16 rows: up to 6500 keys 0.92, 0.87, 0.84, nine rows without a gate below 7680 1.00 (0.92 to 1.12, wider 0.88); 8000 keys 1.07, 0.99, 0.95 below 8192, above 0.99, 0.93, 0.88.
+int wide_keys(int T, int d, int F, bool gated) {
+    if (T <= kWideRows) return 8192;
+    if (T <= 16) return d >= 2048 ? 8192 : T == 9 && !gated && F < 7680 ? 0 : T > 9 && F >= 8192 ? 8192 : 6656;
+    return T > 24 ? 2048 : F > 8192 ? 4096 : gated ? 1280 : 2048;
+}
 
 int wide_groups(int d, int heads, int d_head, int F, bool gated, int cus) {
     if (d_head != kWideHead || d <= 1024 || d % 256 != 0 || F % 32 != 0) return 0;
@@ -859,7 +869,7 @@ bool wide_two(int d, int heads, int F, bool gated, int cus, int keys) {
 }
 
 bool wide_split(int d, int heads, int F, bool gated, int cus, int keys, int rows, int out[7]) {
-    if (!wide_groups(d, heads, kWideHead, F, gated, cus) || rows > wide_rows(d, heads, F, gated, cus) || keys > wide_keys(rows, d)) return false;
+    if (!wide_groups(d, heads, kWideHead, F, gated, cus) || rows > wide_rows(d, heads, F, gated, cus) || keys > wide_keys(rows, d, F, gated)) return false;
     const int tq = 3 * heads * kWideHead / 16, tf = gated ? F / 8 : F / 16;
     auto is = [&](auto cut) {
         using Cut = decltype(cut);
